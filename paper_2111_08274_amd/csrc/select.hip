@@ -1,4 +1,4 @@
-// Probability-based replica selection (paper Sec. 3.3) as one wavefront on the device.
+// Probability-based replica selection (paper Sec. 3.3): one wavefront, or one workgroup above 64 replicas.
 // Built with -ffp-contract=off: every fp64 operation below is rounded on its own, so the result is a
 // function of the inputs alone and any IEEE-754 implementation of the same written steps gives the same bits.
 #include <climits>
@@ -57,33 +57,9 @@ __device__ __forceinline__ double lane_value(double v, int k)
     return __hiloint2double(hi, lo);
 }
 
-__device__ __forceinline__ int lane_value(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
-
-// Lane L receives the value of lane L - 1 (a wavefront-wide shift by one lane, DPP control wave_shr:1); lane 0, which
-// has no lane below it, receives +0.0.
-__device__ __forceinline__ double from_lane_below(double v)
+__device__ __forceinline__ long long uniform_key(long long v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-// Running sums of one chunk of 64 non-negative values, one per lane, added strictly one after another in ascending
-// lane order starting from `carry`: lane L ends with ((carry + v_0) + v_1) + ... + v_L, every addition rounded on its
-// own.  Each pass hands every lane its lower neighbour's sum and adds the lane's own value (lane 0 adds carry + v_0
-// to the +0.0 it is handed, which is exact).  A lane's sum is final one pass after its lower neighbour's is, and
-// recomputing a final sum gives the same value again, so the passes need no lane test, no cross-lane read into
-// scalar registers and no LDS.  On entry lanes below `first` must already hold their final sums in r (what they held
-// after an earlier call whose values differed only at lanes >= first); the other lanes' r is ignored.  64 - first
-// passes finish the chunk; they run in blocks of eight, the surplus passes change nothing.
-__device__ __forceinline__ double ascending_sums(double mine, double carry, double r, int first)
-{
-    const double add = __lane_id() == 0 ? carry + mine : mine;
-    for (int blk = (64 - first + 7) >> 3; blk > 0; --blk) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) r = from_lane_below(r) + add;
-    }
-    return r;
+    return ((long long)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 // Sixteen fp64 registers that a wave-uniform index can address (the compiler turns an indexed write into one
@@ -94,6 +70,25 @@ template <typename V> __device__ __forceinline__ const V* versions_of(const Sele
 template <> __device__ __forceinline__ const int* versions_of<int>(const SelectArgs& a) { return a.versions; }
 template <> __device__ __forceinline__ const double* versions_of<double>(const SelectArgs& a) { return a.versions_f64; }
 
+// the uniform of draw t: counter (cycle_lo, cycle_hi, draw, 0), key = seed, 53 bits of the first two words
+__device__ __forceinline__ double draw_uniform(const SelectArgs& a, int t)
+{
+    const U4 o = philox4x32_10(U4{(uint32_t)a.cycle, (uint32_t)(a.cycle >> 32), (uint32_t)t, 0u},
+                               (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+    const unsigned long long bits = ((unsigned long long)o.y << 32) | o.x;
+    return (double)(bits >> 11) * 0x1.0p-53;
+}
+
+// the Gaussian selection function of Sec. 3.3, its exponent clamped so that no available replica has probability 0
+__device__ __forceinline__ double selection_function(double v, double mu)
+{
+    const double d = v - mu;
+    double e = -(d * d) * 0.5;
+    if (e < -690.0) e = -690.0;
+    return exp_neg(e);
+}
+
+// Selection among at most 64 replicas, one wavefront.
 // V = int: versions are step counters; V = double: forecast (real-valued) versions (Sec. 3.2 feeding Sec. 3.3)
 //
 // What is serial in the rule and what is not.  The draws are sequential (draw t renormalises over the replicas that
@@ -101,233 +96,335 @@ template <> __device__ __forceinline__ const double* versions_of<double>(const S
 // addition after another: a chain of N dependent additions per draw that no reordering may touch, because the result
 // is compared bit for bit.  Everything else is taken off that chain: the uniforms of all draws are computed up
 // front (one Philox block per lane), f is computed once, and a step of the chain is a single v_add_f64 from
-// registers when N <= 64 (a one-lane shift of the running sums and a v_add_f64 per step above that, ascending_sums).
-// One wavefront on its own issues a dependent instruction only every 5 to 8 clocks, so what counts is the number of
-// instructions on the path, and straight-line code that runs once is paid for in instruction fetches: the loops
-// below are kept short rather than unrolled over all 64 lanes.
+// registers.  One wavefront on its own issues a dependent instruction only every 5 to 8 clocks, so what counts is the
+// number of instructions on the path, and straight-line code that runs once is paid for in instruction fetches: the
+// loops below are kept short rather than unrolled over all 64 lanes.
 template <typename V>
 __global__ __launch_bounds__(64) void select_kernel(SelectArgs a)
 {
     constexpr bool kIntVersions = std::is_same<V, int>::value;
-    __shared__ double s_sorted[kMaxReplicas];
-    __shared__ double s_f[kMaxReplicas];
-    __shared__ double s_u[kMaxReplicas];
-    __shared__ unsigned char s_flag[kMaxReplicas];
-    __shared__ V s_v[kMaxReplicas];
-    __shared__ unsigned char s_av[kMaxReplicas];
-    __shared__ long long s_key[kIntVersions ? kMaxReplicas : 1];
+    __shared__ double s_sorted[64];
+    __shared__ double s_f[64];
+    __shared__ long long s_key[kIntVersions ? 64 : 1];
     const int lane = threadIdx.x, N = a.n;
 
-    // versions and availability into LDS (one parallel load), then a rank-counting sort of the available versions:
-    // rank(i) = #{available j : v_j < v_i or (v_j == v_i and j < i)}.
-    const int chunks = (N + 63) / 64;
-    for (int i = lane; i < chunks * 64; i += 64) {
-        const bool on = i < N && (!a.avail || a.avail[i]);
-        if (i < N) {
-            s_v[i] = versions_of<V>(a)[i];
-            s_av[i] = on ? 1 : 0;
-            s_flag[i] = 0;
-        }
-        // step counters: (version, index) pairs are ordered by one integer key, version * 1024 + index; a replica
-        // that is not available, or beyond N, gets the largest key and is counted before nobody
-        if constexpr (kIntVersions) s_key[i] = on ? (long long)versions_of<V>(a)[i] * kMaxReplicas + i : LLONG_MAX;
-    }
-    // the uniform of every draw: counter (cycle_lo, cycle_hi, draw, 0), key = seed, 53 bits of the first two words
-    for (int t = lane; t < a.n_select; t += 64) {
-        const U4 o = philox4x32_10(U4{(uint32_t)a.cycle, (uint32_t)(a.cycle >> 32), (uint32_t)t, 0u},
-                                   (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-        const unsigned long long bits = ((unsigned long long)o.y << 32) | o.x;
-        s_u[t] = (double)(bits >> 11) * 0x1.0p-53;
-    }
+    // a rank-counting sort of the available versions: rank(i) = #{available j : v_j < v_i or (v_j == v_i and j < i)}
+    const bool on = lane < N && (!a.avail || a.avail[lane]);
+    const V vi = lane < N ? versions_of<V>(a)[lane] : V(0);
+    // step counters: (version, index) pairs are ordered by one integer key, version * 1024 + index; a replica
+    // that is not available, or beyond N, gets the largest key and is counted before nobody
+    if constexpr (kIntVersions) s_key[lane] = on ? (long long)vi * kMaxReplicas + lane : LLONG_MAX;
+    // the uniform of every draw, lane t's for draw t (n_select <= N <= 64)
+    const double my_u = draw_uniform(a, lane);
     __syncthreads();
-    int na = 0;
+    const unsigned long long avail = __ballot(on);
+    const int na = __popcll(avail);
+    int rank = 0;
     if constexpr (kIntVersions) {
         // every lane compares its own key with all keys, read from LDS at a wave-uniform address (a broadcast)
-        for (int q = 0; q < chunks; ++q) {
-            const int i = q * 64 + lane;
-            const long long mine = s_key[i];
-            na += __popcll(__ballot(mine != LLONG_MAX));
-            int rank = 0;
-            for (int j = 0; j < chunks * 64; j += 16) {
+        const long long mine = s_key[lane];
+        for (int j = 0; j < 64; j += 16) {
 #pragma unroll
-                for (int u = 0; u < 16; ++u) rank += s_key[j + u] < mine ? 1 : 0;
-            }
-            if (mine != LLONG_MAX) s_sorted[rank] = (double)s_v[i];
+            for (int u = 0; u < 16; ++u) rank += s_key[j + u] < mine ? 1 : 0;
         }
     } else {
-        // real-valued versions: lanes own elements i = 64q + lane and walk all j chunk by chunk with cross-lane reads
-        for (int q = 0; q < chunks; ++q) {
-            const int i = q * 64 + lane;
-            const V vi = i < N ? s_v[i] : V(0);
-            int rank = 0;
-            na = 0;
-            for (int c = 0; c < chunks; ++c) {
-                const int idx = c * 64 + lane;
-                const V vjm = idx < N ? s_v[idx] : V(0);
-                const unsigned long long mask = __ballot(idx < N && s_av[idx]);
-                na += __popcll(mask);
 #pragma unroll
-                for (int k = 0; k < 64; ++k) {
-                    const V vj = lane_value(vjm, k);
-                    const int j = c * 64 + k;
-                    const int before = (int)(vj < vi) | ((int)(vj == vi) & (int)(j < i));
-                    rank += before & (int)((mask >> k) & 1ull);
-                }
-            }
-            if (i < N && s_av[i]) s_sorted[rank] = (double)vi;
+        for (int k = 0; k < 64; ++k) {                     // real-valued versions: cross-lane reads
+            const V vj = lane_value(vi, k);
+            const int before = (int)(vj < vi) | ((int)(vj == vi) & (int)(k < lane));
+            rank += before & (int)((avail >> k) & 1ull);
         }
     }
+    if (on) s_sorted[rank] = (double)vi;
     __syncthreads();
     // third quartile: linear interpolation at 0.75*(na-1)
     const double pos = 0.75 * (double)(na - 1);
-    const int lo = (int)__builtin_floor(pos);
+    const int lo = na > 0 ? (int)__builtin_floor(pos) : 0;
     const double frac = pos - (double)lo;
     double mu = s_sorted[lo];
     if (lo + 1 < na) mu = s_sorted[lo] + frac * (s_sorted[lo + 1] - s_sorted[lo]);
-    __syncthreads();                                       // every lane has read the quartile before s_sorted is reused
 
-    for (int i = lane; i < chunks * 64; i += 64) {         // f = +0.0 beyond N: the draws below need no bound test
-        double f = 0.0;
-        if (i < N && s_av[i]) {
-            const double d = (double)s_v[i] - mu;
-            double e = -(d * d) * 0.5;
-            if (e < -690.0) e = -690.0;
-            f = exp_neg(e);
-        }
-        s_f[i] = f;
-        if (i < N) a.f[i] = f;
-    }
+    const double f = on ? selection_function((double)vi, mu) : 0.0;      // f = +0.0 beyond N: no bound test below
+    s_f[lane] = f;
+    if (lane < N) a.f[lane] = f;
     __syncthreads();
 
     // Sequential draws: draw t picks the first live replica whose running sum of f exceeds u_t * S, S the total over
     // the live replicas; dead replicas (picked, unavailable, or beyond N) add +0.0, which leaves a non-negative sum
-    // unchanged.
-    int n_picked = 0;
-    if (chunks == 1) {
-        // At most 64 replicas: the draws run from registers.  Lane L keeps g[j] = f_j for j <= L and +0.0 above, so
-        // the plain chain ((0 + g[0]) + g[1]) + ... + g[63], the same instructions in every lane and no lane
-        // waiting for another, leaves lane L with the running sum after replica L (the zeros above L change nothing)
-        // and lane 63 with S.  A dependent v_add_f64 issues every 5 to 6 clocks, a quarter of what one step costs
-        // when the running sum has to move to the next lane.  A picked replica is zeroed in every lane's g.
-        F16 g0, g1, g2, g3, g4;
+    // unchanged.  The draws run from registers.  Lane L keeps g[j] = f_j for j <= L and +0.0 above, so
+    // the plain chain ((0 + g[0]) + g[1]) + ... + g[63], the same instructions in every lane and no lane
+    // waiting for another, leaves lane L with the running sum after replica L (the zeros above L change nothing)
+    // and lane 63 with S.  A dependent v_add_f64 issues every 5 to 6 clocks, a quarter of what one step costs
+    // when the running sum has to move to the next lane.  A picked replica is zeroed in every lane's g.
+    F16 g0, g1, g2, g3, g4;
 #pragma unroll
-        for (int k = 0; k < 15; ++k) {
-            g0[k] = k <= lane ? s_f[k] : 0.0;
-            g1[k] = 15 + k <= lane ? s_f[15 + k] : 0.0;
-            g2[k] = 30 + k <= lane ? s_f[30 + k] : 0.0;
-            g3[k] = 45 + k <= lane ? s_f[45 + k] : 0.0;
-            g4[k] = (k < 4 && 60 + k <= lane) ? s_f[60 + k] : 0.0;
-        }
-        g0[15] = 0.0; g1[15] = 0.0; g2[15] = 0.0; g3[15] = 0.0; g4[15] = 0.0;
-        unsigned long long livemask = __ballot(s_f[lane] > 0.0);
-        const unsigned long long could = livemask;
-        const double my_u = lane < a.n_select ? s_u[lane] : 0.0;
-        int my_pick = -1;
-        for (int t = 0; t < a.n_select; ++t) {
-            double q = 0.0;
-#pragma unroll
-            for (int k = 0; k < 15; ++k) q = q + g0[k];
-#pragma unroll
-            for (int k = 0; k < 15; ++k) q = q + g1[k];
-#pragma unroll
-            for (int k = 0; k < 15; ++k) q = q + g2[k];
-#pragma unroll
-            for (int k = 0; k < 15; ++k) q = q + g3[k];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) q = q + g4[k];
-            const double S = lane_value(q, 63);
-            const double thr = lane_value(my_u, t) * S;
-            const unsigned long long hit = __ballot(q > thr) & livemask;
-            int pick = -1;
-            if (hit) pick = __ffsll((long long)hit) - 1;
-            else if (livemask) pick = 63 - __clzll(livemask);   // stays -1 only if no replica is left to draw from
-            pick = __builtin_amdgcn_readfirstlane(pick);
-            if (lane == t) my_pick = pick;
-            // the picked replica leaves every lane's g: one register-indexed write per group, aimed at the spare
-            // sixteenth element in the groups that do not hold it (and in all of them when nothing was picked)
-            const int grp = pick >= 0 ? pick / 15 : 5, slot = pick - 15 * grp;
-            g0[grp == 0 ? slot : 15] = 0.0;
-            g1[grp == 1 ? slot : 15] = 0.0;
-            g2[grp == 2 ? slot : 15] = 0.0;
-            g3[grp == 3 ? slot : 15] = 0.0;
-            g4[grp == 4 ? slot : 15] = 0.0;
-            if (pick >= 0) {
-                ++n_picked;
-                livemask &= ~(1ull << pick);
-            }
-        }
-        if (lane < a.n_select) a.selected[lane] = my_pick;
-        if (lane < N) s_flag[lane] = (unsigned char)(((could & ~livemask) >> lane) & 1ull);
-        __syncthreads();
-    } else {
-        // Sequential draws.  The wavefront walks the replicas in chunks of 64: every lane loads its own value once and
-        // ends with the running sum after its element (ascending_sums), the last lane's carries into the next chunk.  The
-        // total S is the last running sum; the pick is the first live element whose running sum exceeds u*S, found with one
-        // compare and a ballot.  Dead elements (picked, unavailable, or beyond N) add +0.0, which leaves a non-negative sum
-        // unchanged, so every chunk runs all 64 additions with no bound to test.
-        //
-        // Draw t + 1 differs from draw t in one element, the replica p picked last: the running sums below p are the same
-        // additions of the same values and are kept (in LDS, s_sorted is free after the quartile), the chain restarts at p.
-        int changed = 0;                                       // lowest replica whose running sum is not valid
-        for (int t = 0; t < a.n_select; ++t) {
-            const int c0 = changed >> 6;
-            double run = c0 > 0 ? s_sorted[c0 * 64 - 1] : 0.0;
-            for (int c = c0; c < chunks; ++c) {
-                const int idx = c * 64 + lane;
-                const bool live = idx < N && !s_flag[idx] && s_f[idx] > 0.0;
-                const int first = c == c0 ? (changed & 63) : 0;
-                const double prefix = ascending_sums(live ? s_f[idx] : 0.0, run, idx < N ? s_sorted[idx] : 0.0, first);
-                if (idx < N) s_sorted[idx] = prefix;
-                run = lane_value(prefix, 63);
-            }
-            const double S = run;
-            const double thr = s_u[t] * S;
-            int pick = -1, last = -1;
-            for (int c = 0; c < chunks; ++c) {
-                const int idx = c * 64 + lane;
-                const bool live = idx < N && !s_flag[idx] && s_f[idx] > 0.0;
-                const unsigned long long lm = __ballot(live);
-                const unsigned long long hit = __ballot(live && s_sorted[idx < N ? idx : 0] > thr);
-                if (lm) last = c * 64 + 63 - __clzll(lm);
-                if (pick < 0 && hit) pick = c * 64 + __ffsll((long long)hit) - 1;
-            }
-            if (pick < 0) pick = last;                         // stays -1 only if no replica is left to draw from
-            n_picked += pick >= 0 ? 1 : 0;
-            __syncthreads();
-            if (lane == 0) { a.selected[t] = pick; if (pick >= 0) s_flag[pick] = 1; }
-            changed = pick >= 0 ? pick : N;                     // nothing left: later draws change nothing either
-            __syncthreads();
-        }
+    for (int k = 0; k < 15; ++k) {
+        g0[k] = k <= lane ? s_f[k] : 0.0;
+        g1[k] = 15 + k <= lane ? s_f[15 + k] : 0.0;
+        g2[k] = 30 + k <= lane ? s_f[30 + k] : 0.0;
+        g3[k] = 45 + k <= lane ? s_f[45 + k] : 0.0;
+        g4[k] = (k < 4 && 60 + k <= lane) ? s_f[60 + k] : 0.0;
     }
+    g0[15] = 0.0; g1[15] = 0.0; g2[15] = 0.0; g3[15] = 0.0; g4[15] = 0.0;
+    unsigned long long livemask = __ballot(f > 0.0);
+    const unsigned long long could = livemask;
+    int my_pick = -1;
+    for (int t = 0; t < a.n_select; ++t) {
+        double q = 0.0;
+#pragma unroll
+        for (int k = 0; k < 15; ++k) q = q + g0[k];
+#pragma unroll
+        for (int k = 0; k < 15; ++k) q = q + g1[k];
+#pragma unroll
+        for (int k = 0; k < 15; ++k) q = q + g2[k];
+#pragma unroll
+        for (int k = 0; k < 15; ++k) q = q + g3[k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q = q + g4[k];
+        const double S = lane_value(q, 63);
+        const double thr = lane_value(my_u, t) * S;
+        const unsigned long long hit = __ballot(q > thr) & livemask;
+        int pick = -1;
+        if (hit) pick = __ffsll((long long)hit) - 1;
+        else if (livemask) pick = 63 - __clzll(livemask);   // stays -1 only if no replica is left to draw from
+        pick = __builtin_amdgcn_readfirstlane(pick);
+        if (lane == t) my_pick = pick;
+        // the picked replica leaves every lane's g: one register-indexed write per group, aimed at the spare
+        // sixteenth element in the groups that do not hold it (and in all of them when nothing was picked)
+        const int grp = pick >= 0 ? pick / 15 : 5, slot = pick - 15 * grp;
+        g0[grp == 0 ? slot : 15] = 0.0;
+        g1[grp == 1 ? slot : 15] = 0.0;
+        g2[grp == 2 ? slot : 15] = 0.0;
+        g3[grp == 3 ? slot : 15] = 0.0;
+        g4[grp == 4 ? slot : 15] = 0.0;
+        if (pick >= 0) livemask &= ~(1ull << pick);
+    }
+    if (lane < a.n_select) a.selected[lane] = my_pick;
 
     // aggregation weights a_k and the ascending list the aggregate kernel walks.  With unit terms the denominator is
     // the count itself (a sum of ones is exact); with f-weighted terms it adds the selected replicas' f in
-    // ascending index, one after another, the same chain as above.
-    double denom = (double)n_picked;
+    // ascending index, one after another.
+    const unsigned long long picked = could & ~livemask;
+    double denom = (double)__popcll(picked);
     if (a.weight_mode == 1) {
         denom = 0.0;
-        for (int c = 0; c < chunks; ++c) {
-            const int idx = c * 64 + lane;
-            denom = lane_value(ascending_sums((idx < N && s_flag[idx]) ? s_f[idx] : 0.0, denom, 0.0, 0), 63);
+        for (unsigned long long m = picked; m; m &= m - 1) denom = denom + s_f[__ffsll((long long)m) - 1];
+    }
+    if (lane < N) {
+        const bool sel = (picked >> lane) & 1ull;
+        float w = 0.f;
+        if (sel) {
+            w = (float)(((a.weight_mode == 1) ? f : 1.0) / denom);
+            const int at = __popcll(picked & ((1ull << lane) - 1ull));
+            a.sel_sorted[at] = lane;
+            a.sel_weight[at] = w;
+        }
+        a.flag[lane] = sel ? 1 : 0;
+        a.weights[lane] = w;
+    }
+}
+
+// ---- selection among 65 to kMaxReplicas replicas ----
+constexpr int kManyThreads = 256;
+
+// A version as an integer of the same order, and back
+__device__ __forceinline__ long long order_key(int v) { return v; }
+__device__ __forceinline__ long long order_key(double v)
+{
+    const long long b = __double_as_longlong(v);
+    return b ^ ((b >> 63) & LLONG_MAX);
+}
+template <typename V> __device__ __forceinline__ double key_value(long long k)
+{
+    return std::is_same<V, int>::value ? (double)k : __longlong_as_double(k ^ ((k >> 63) & LLONG_MAX));
+}
+
+typedef double D2 __attribute__((ext_vector_type(2)));
+
+// The running sum of g[64 c0 ..  64 c1), added to `run` one after another in ascending index, every addition rounded on
+// its own.  All lanes run the same chain on values read from LDS at a wave-uniform address, sixteen bytes at a time and
+// half a chunk ahead of the additions, so a step is one v_add_f64 and half an LDS read: 8 clocks, against 23 when the
+// running sums move from lane to lane.  What the lanes are for: lane L of rec keeps the sum after element 16 L + 15.
+// Reads up to 32 elements past the end of the last chunk (g is that much longer; they are not used).
+__device__ __forceinline__ double uniform_chain(const double* g, int c0, int c1, double run, double& rec, int lane)
+{
+    D2 v[2][16];
+    const D2* p = reinterpret_cast<const D2*>(g + c0 * 64);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[0][k] = p[k];
+    for (int c = c0; c < c1; ++c) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            p += 16;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[h ^ 1][k] = p[k];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                run = run + v[h][k][0];
+                run = run + v[h][k][1];
+                if (k == 7) rec = lane == 4 * c + 2 * h ? run : rec;
+            }
+            rec = lane == 4 * c + 2 * h + 1 ? run : rec;
+            // here, not before: the values just read must stay in registers (the compiler would read them again at
+            // the head of the loop and wait for them there)
+            __builtin_amdgcn_sched_barrier(0);
+            D2 (&n)[16] = v[h ^ 1];
+            asm volatile("" : "+v"(n[0]), "+v"(n[1]), "+v"(n[2]), "+v"(n[3]), "+v"(n[4]), "+v"(n[5]), "+v"(n[6]), "+v"(n[7]),
+                              "+v"(n[8]), "+v"(n[9]), "+v"(n[10]), "+v"(n[11]), "+v"(n[12]), "+v"(n[13]), "+v"(n[14]), "+v"(n[15]));
         }
     }
+    return run;
+}
+
+// One workgroup of four wavefronts; the draws are wavefront 0's alone (see select_kernel for what is serial in them), the
+// rest is shared.  Bound by the chains: a draw re-adds the values from the chunk of the replica picked last, half of
+// them on average.  1000 replicas, 100 draws: 1205 us with one wavefront, running sums moved from lane to lane and a full
+// rank-counting sort of the versions, 257 us here; 65 replicas and one draw: 9 us, launch included.
+template <typename V>
+__global__ __launch_bounds__(kManyThreads) void select_many_kernel(SelectArgs a)
+{
+    constexpr int kPer = kMaxReplicas / 64;                // values per lane of wavefront 0
+    __shared__ __attribute__((aligned(16))) double s_g[kMaxReplicas + 32];     // f of the replicas still to be drawn from, else +0.0
+    __shared__ double s_f[kMaxReplicas];
+    __shared__ double s_u[kMaxReplicas];
+    __shared__ long long s_key[kMaxReplicas];
+    __shared__ unsigned char s_flag[kMaxReplicas];
+    __shared__ double s_mu;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.n;
+    const int chunks = (N + 63) / 64;
+
+    for (int i = tid; i < chunks * 64; i += kManyThreads) {
+        const bool on = i < N && (!a.avail || a.avail[i]);
+        s_key[i] = on ? order_key(versions_of<V>(a)[i]) : LLONG_MAX;      // (no version maps to the largest key)
+        s_flag[i] = on ? 1 : 0;                            // until f is known: available
+        if (i < a.n_select) s_u[i] = draw_uniform(a, i);
+    }
+    __syncthreads();
+    // Third quartile, linear interpolation at 0.75 * (na - 1): two neighbouring order statistics, found by bisection of
+    // the keys' range with a count per step (no sort).
+    if (wave == 0) {
+        long long key[kPer], kmin = LLONG_MAX, kmax = LLONG_MIN;
+        int na = 0;
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            key[r] = r < chunks ? s_key[r * 64 + lane] : LLONG_MAX;
+            na += __popcll(__ballot(key[r] != LLONG_MAX));
+            kmin = key[r] < kmin ? key[r] : kmin;
+            if (key[r] != LLONG_MAX) kmax = key[r] > kmax ? key[r] : kmax;
+        }
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) {
+            const long long x = __shfl_xor(kmin, w), y = __shfl_xor(kmax, w);
+            kmin = x < kmin ? x : kmin; kmax = y > kmax ? y : kmax;
+        }
+        const double pos = 0.75 * (double)(na - 1);
+        const int lo = (int)__builtin_floor(pos);
+        const double frac = pos - (double)lo;
+        // smallest key with more than `lo` keys at or below it
+        long long b0 = uniform_key(kmin), b1 = uniform_key(kmax);
+        while (b0 < b1) {
+            const long long mid = b0 + (long long)(((unsigned long long)b1 - (unsigned long long)b0) >> 1);
+            int at_most = 0;
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) at_most += __popcll(__ballot(key[r] <= mid));
+            if (at_most > lo) b1 = mid; else b0 = mid + 1;
+        }
+        double mu = key_value<V>(b0);
+        if (lo + 1 < na) {
+            int at_most = 0;
+            long long above = LLONG_MAX;                   // smallest key above b0
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) {
+                at_most += __popcll(__ballot(key[r] <= b0));
+                if (key[r] > b0) above = key[r] < above ? key[r] : above;
+            }
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) { const long long x = __shfl_xor(above, w); above = x < above ? x : above; }
+            const double next = at_most > lo + 1 ? mu : key_value<V>(above);
+            mu = mu + frac * (next - mu);
+        }
+        if (lane == 0) s_mu = mu;
+    }
+    __syncthreads();
+    const double mu = s_mu;
+    for (int i = tid; i < chunks * 64; i += kManyThreads) {
+        const double f = s_flag[i] ? selection_function(key_value<V>(s_key[i]), mu) : 0.0;
+        s_f[i] = f;
+        s_g[i] = f > 0.0 ? f : 0.0;
+        s_flag[i] = 0;                                     // from here on: picked
+        if (i < N) a.f[i] = f;
+    }
+    __syncthreads();
+
+    // Sequential draws: draw t picks the first replica whose running sum exceeds u_t * S (it is a live one: a dead one
+    // leaves the sum where it was).  The running sums below the replica picked last are the same additions of the
+    // same values as in the draw before and are kept; the chain restarts at its chunk.
+    if (wave == 0) {
+        double rec = 0.0;
+        int c0 = 0;
+        for (int t = 0; t < a.n_select; ++t) {
+            const double u = s_u[t];
+            const double S = uniform_chain(s_g, c0, chunks, c0 > 0 ? lane_value(rec, 4 * c0 - 1) : 0.0, rec, lane);
+            const double thr = u * S;
+            const unsigned long long hit = __ballot(rec > thr);
+            int pick = -1;                                  // stays -1 only if no replica is left to draw from (S = 0)
+            if (hit) {
+                const int seg = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
+                double q = seg > 0 ? lane_value(rec, seg - 1) : 0.0;
+                const D2* p = reinterpret_cast<const D2*>(s_g + seg * 16);
+                D2 v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = p[k];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) q = q + (k <= lane ? v[k >> 1][k & 1] : 0.0);     // lane L: after element 16 seg + L
+                pick = seg * 16 + __ffsll((long long)__ballot(q > thr)) - 1;
+                pick = __builtin_amdgcn_readfirstlane(pick);
+                c0 = pick >> 6;
+                if (lane == 0) { s_g[pick] = 0.0; s_flag[pick] = 1; }
+            } else {
+                c0 = chunks;                                // nothing left: later draws change nothing either
+            }
+            if (lane == 0) a.selected[t] = pick;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+    __syncthreads();
+
+    // aggregation weights a_k and the ascending list the aggregate kernel walks (see select_kernel)
+    unsigned long long picked[kPer];
+    int count = 0;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        picked[r] = __ballot(r < chunks && s_flag[r * 64 + lane]);
+        count += __popcll(picked[r]);
+    }
+    double denom = (double)count;
+    if (a.weight_mode == 1) {
+        for (int i = tid; i < chunks * 64; i += kManyThreads) s_g[i] = s_flag[i] ? s_f[i] : 0.0;
+        __syncthreads();
+        double rec = 0.0;
+        denom = uniform_chain(s_g, 0, chunks, 0.0, rec, lane);
+    }
     int before = 0;                                        // selected replicas in earlier chunks
-    for (int c = 0; c < chunks; ++c) {
-        const int idx = c * 64 + lane;
-        const bool on = idx < N && s_flag[idx];
-        const unsigned long long m = __ballot(on);
-        if (idx < N) {
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int idx = r * 64 + lane;
+        if (r % (kManyThreads / 64) == wave && idx < N) {
+            const bool on = (picked[r] >> lane) & 1ull;
             float w = 0.f;
             if (on) {
                 w = (float)(((a.weight_mode == 1) ? s_f[idx] : 1.0) / denom);
-                const int pos = before + __popcll(m & ((1ull << lane) - 1ull));
-                a.sel_sorted[pos] = idx;
-                a.sel_weight[pos] = w;
+                const int at = before + __popcll(picked[r] & ((1ull << lane) - 1ull));
+                a.sel_sorted[at] = idx;
+                a.sel_weight[at] = w;
             }
-            a.flag[idx] = s_flag[idx];
+            a.flag[idx] = on ? 1 : 0;
             a.weights[idx] = w;
         }
-        before += __popcll(m);
+        before += __popcll(picked[r]);
     }
 }
 
@@ -400,8 +497,14 @@ hipError_t launch_select_static(SelectArgs a, hipStream_t s)
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t s)
 {
-    if (a.versions_f64) hipLaunchKernelGGL(select_kernel<double>, dim3(1), dim3(64), 0, s, a);
-    else hipLaunchKernelGGL(select_kernel<int>, dim3(1), dim3(64), 0, s, a);
+    // 64 replicas fit the registers of one wavefront, which is the fastest chain (6.5 us at 64 replicas and 8 draws)
+    if (a.n <= 64) {
+        if (a.versions_f64) hipLaunchKernelGGL(select_kernel<double>, dim3(1), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL(select_kernel<int>, dim3(1), dim3(64), 0, s, a);
+    } else {
+        if (a.versions_f64) hipLaunchKernelGGL(select_many_kernel<double>, dim3(1), dim3(kManyThreads), 0, s, a);
+        else hipLaunchKernelGGL(select_many_kernel<int>, dim3(1), dim3(kManyThreads), 0, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -81,6 +81,33 @@ def test_selection_weight_mode_1_weights_match_the_oracle(N, n_select):
     ctx.close()
 
 
+@pytest.mark.parametrize("N,n_select", [(65, 65), (127, 5), (128, 128), (129, 40), (1000, 100), (1023, 1023), (1024, 64)])
+def test_selection_of_many_replicas_is_bit_exact(N, n_select):
+    """The kernel for more than one chunk of 64 replicas, at the edges of its chunks and down to the last replica, from
+    step counters (small ranges: ties; the whole int32 range: the bisection's) and from real-valued versions."""
+    import torch
+    rng = np.random.default_rng(N + 7 * n_select)
+    ctx, _ = _ctx(N, n_select, 64, weight_mode=1)
+    for trial, (lo, hi) in enumerate([(0, 3), (0, 50), (-2 ** 31, 2 ** 31 - 1), (7, 7)]):
+        v = rng.integers(lo, hi + 1, size=N)
+        for real in (False, True):
+            vv = v + (rng.integers(0, 3, size=N) * 0.375 if real else 0)
+            avail = None
+            if trial % 2 and N > n_select:
+                avail = np.ones(N, dtype=np.uint8)
+                avail[rng.choice(N, size=N - n_select, replace=False)] = 0
+            if real:
+                ctx.select_real(trial, versions=torch.as_tensor(vv.astype(np.float64)).cuda(), avail=avail)
+            else:
+                ctx.select(trial, versions=torch.as_tensor(vv.astype(np.int32)).cuda(), avail=avail)
+            sel, flag, w = ctx.selected()
+            osel, oflag, of, _ = oracle.select(vv if real else vv.astype(np.int32), n_select, synth.SELECT_SEED, trial, avail)
+            assert sel.tolist() == osel.tolist(), (N, n_select, trial, real)
+            assert flag.tolist() == oflag.tolist()
+            assert np.array_equal(w, oracle.aggregation_weights(oflag, of, 1).astype(np.float32))
+    ctx.close()
+
+
 @pytest.mark.parametrize("N,n_select,m", [(6, 3, 100037), (4, 1, 5), (9, 8, 70001), (12, 11, 4099), (3, 3, 1 << 20)])
 def test_aggregate_matches_fp64_sum_and_resync_copies_it(N, n_select, m):
     import torch
