@@ -1,0 +1,804 @@
+// fp32 convolutions and dense layers on the bf16 matrix cores: forward and data gradient of every local step (paper
+// Sec. 2.1) in the fp32 configuration, without giving up fp32 accuracy.
+//
+// The fp32 matrix instruction runs at a sixteenth of the bf16 rate (157 against 2500 TFLOP/s).  A float is the exact sum
+// of three bf16 numbers, x = xh + xm + xl, so a product is the sum of nine bf16 products, and the six of them that are
+// not below 2^-26 of it,
+//       xh*yh  +  (xh*ym + xm*yh + xm*ym + xh*yl + xl*yh),
+// cost 6 / 16 of the fp32 instruction's time.  Every bf16 product is exact in fp32; what rounds is the accumulation.
+// The large products xh*yh have an accumulator of their own and the five small ones another, joined once at the end:
+// the small ones are then never rounded to the size of the running sum, and the large accumulator rounds once per
+// sixteen products where the fp32 instruction rounds after each.  Root-mean-square error against 64 bits, 32 x 32 products of
+// length K, in units of the products' 2-norm (fp32 instruction / this, one accumulator for all six / this, two):
+//   normal x normal          K = 64: 1.4e-7 / 1.1e-7 / 4.9e-8    1152: 5.9e-7 / 5.2e-7 / 1.9e-7    16384: 2.4e-6 / 2.1e-6 / 8.2e-7
+//   ReLU(normal) x normal    K = 64: 1.0e-7 / 1.1e-7 / 3.8e-8    1152: 4.3e-7 / 5.0e-7 / 1.5e-7    16384: 1.6e-6 / 2.0e-6 / 7.2e-7
+//   positive x positive      K = 64: 6.4e-7 / 4.6e-7 / 2.7e-7    1152: 1.1e-5 / 7.6e-6 / 4.0e-6    16384: 1.6e-4 / 1.1e-4 / 5.8e-5
+// A value that is not finite, or an accumulator that overflows, makes the six products disagree with the one (Inf * 0):
+// a tile that finds a result that is not finite is computed again with the fp32 instruction, which is what it then stores.
+//
+//   * The weights are kept as two split matrices per layer, refreshed from the master before every forward pass:
+//       Wf[co][tap][ci]  and  Wb[ci][flipped tap][co],
+//     so that forward and data gradient are the same kernel: a data gradient is a convolution of dY with the flipped,
+//     transposed filter.  For stride s an input pixel only meets the taps of its own residue (y mod s, x mod s); the
+//     pixels of one residue class are a dense problem over that class's taps, one class after another in the grid.
+//   * K is walked in slabs of 32 channels of one tap (channels padded to 32 with zeros).  A slab of a row is 208 bytes
+//     of LDS: three planes of 32 bf16 and 16 bytes of padding, so that sixteen consecutive rows start in distinct groups
+//     of four banks and the 16-byte operand reads run at full rate.  The weights lie in memory in that very order, 192
+//     contiguous bytes per slab; the activations are split on their way into LDS.
+//   * Position of channel k inside a slab: pos = ((k / 4) % 4) * 8 + (k / 16) * 4 + k % 4, the same for both operands:
+//     a thread reads channels 4g..4g+3 and 16+4g..16+4g+3 (64 contiguous bytes over four lanes each) and stores one
+//     16-byte group per plane.
+//   * MFMA operands are swapped (C^T = B^T A^T): four consecutive output channels per lane, 16-byte stores.
+#include "train_kernels.h"
+#include "conv_stats.h"
+#include "mfma_tiles.h"
+
+namespace hadfl {
+namespace {
+
+using namespace tiles;
+using conv_stats::store_column_stats;
+using conv_stats::kStatLdsBytes;
+
+constexpr int kSlab = 32;                 // channels per slab
+constexpr int kRow = 208;                 // LDS bytes per row of a slab
+constexpr int kSlabBytes = 192;           // the same row in memory (weights)
+
+// What one residue class of pixels needs (one class, the whole image, unless it is a strided data gradient)
+struct ClassGeo {
+    int ph, pw;                           // output pixel = (y * ostride + ph, x * ostride + pw)
+    int hc, wc;                           // rows of the class: y < hc, x < wc
+    int ny, nx;                           // taps of the class (ny * nx)
+    int wy0, wx0;                         // filter tap of (iy, ix) = ((wy0 + iy * wst) * S + wx0 + ix * wst)
+    int by, bx;                           // source pixel of tap (iy, ix) = (y * sstride + by + iy, x * sstride + bx + ix)
+};
+__device__ __forceinline__ ClassGeo class_geo(const SplitConvParams& p, int cls)
+{
+    ClassGeo c;
+    if (p.classes == 1) {
+        c.ph = c.pw = 0; c.hc = p.Ho; c.wc = p.Wo; c.ny = p.R; c.nx = p.S; c.wy0 = c.wx0 = 0; c.by = c.bx = -p.pad;
+        return c;
+    }
+    const int st = p.ostride;
+    c.ph = cls / st; c.pw = cls - c.ph * st;
+    c.hc = (p.Ho - c.ph + st - 1) / st; c.wc = (p.Wo - c.pw + st - 1) / st;
+    c.wy0 = ((p.pad - c.ph) % st + st) % st; c.wx0 = ((p.pad - c.pw) % st + st) % st;
+    c.ny = c.wy0 < p.R ? (p.R - c.wy0 + st - 1) / st : 0;
+    c.nx = c.wx0 < p.S ? (p.S - c.wx0 + st - 1) / st : 0;
+    c.by = (c.ph - p.pad + c.wy0) / st; c.bx = (c.pw - p.pad + c.wx0) / st;       // exact
+    return c;
+}
+
+// KG groups of WGM x WGN waves share a BMT x BN tile (wave tile BMT/WGM x BN/WGN): group kg multiplies slabs kg, kg + KG,
+// ..., and the groups' sums are joined in group order through LDS at the end.  One LDS buffer per group: the next slab
+// waits in registers while the current one is multiplied, two barriers per slab.
+// EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate.
+template <int BMT, int BN, int WGM, int WGN, int KG, int EPI>
+__global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM * WGN * KG / 4) void conv_split_kernel(SplitConvParams p)
+{
+    constexpr int NW = WGM * WGN, NT = NW * 64;
+    constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32;
+    constexpr int NQA = BMT * 4 / NT, NQB = (BN * 12 + NT - 1) / NT;
+    static_assert(NQA >= 1 && TM >= 1 && TN >= 1 && BMT * 4 % NT == 0, "tile does not fit the thread count");
+    constexpr unsigned A_BUF = BMT * kRow, GROUP = (BMT + BN) * kRow;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    const int tid = threadIdx.x % NT, kg = threadIdx.x / NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    char* const sAc = smem + kg * GROUP;              // [BMT][kRow]
+    char* const sBc = sAc + A_BUF;                    // [BN][kRow]
+    // logical item = (slot, class, column tile, row tile), row tiles fastest
+    const unsigned tiles_m = (unsigned)p.tiles_m, tiles_n = (unsigned)(p.N + BN - 1) / BN, per_class = tiles_m * tiles_n;
+    const unsigned item = logical_block();
+    if (item >= per_class * (unsigned)p.classes * (unsigned)p.n_active) return;
+    const int slot = (int)(item / (per_class * (unsigned)p.classes));
+    const int rep = p.order[slot];
+    const ClassGeo cg = class_geo(p, (int)((item / per_class) % (unsigned)p.classes));
+    const int m0 = (int)(item % tiles_m) * BMT, n0 = (int)((item / tiles_m) % tiles_n) * BN;
+    const int hw = cg.hc * cg.wc, M = p.B * hw;
+    if (m0 >= M) return;
+    const char* abase;
+    if (p.cursor) {                                   // the batch inside the data set
+        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        abase = (const char*)(p.a + ((long long)rep * p.n_samples + first) * p.sample_sz);
+    } else {
+        abase = (const char*)(p.a + (long long)rep * p.a_rep);
+    }
+    const char* wbase = (const char*)(p.wmat + (long long)rep * p.wmat_rep);
+
+    // A slots of this thread: (row, group g) with g = tid % 4
+    unsigned aoff[NQA], tapmask[NQA], sa_st[NQA];
+#pragma unroll
+    for (int q = 0; q < NQA; ++q) {
+        const int i = tid + q * NT, arow = i >> 2, m = m0 + arow;
+        aoff[q] = 0; tapmask[q] = 0;
+        if (m < M) {
+            int b, pos;
+            if (p.perm) { const int ps = m / p.B; b = m - ps * p.B; pos = p.perm[ps]; }
+            else { b = m / hw; pos = m - b * hw; }
+            const int y = pos / cg.wc, x = pos - y * cg.wc;
+            const int sy = y * p.sstride + cg.by, sx = x * p.sstride + cg.bx;
+            aoff[q] = (unsigned)(((b * p.H + sy) * p.W + sx) * p.C + (tid & 3) * 4) * 4u;      // (may lie outside: only used with a tap's delta)
+            for (int iy = 0, t = 0; iy < cg.ny; ++iy)
+                for (int ix = 0; ix < cg.nx; ++ix, ++t)
+                    if (sy + iy >= 0 && sy + iy < p.H && sx + ix >= 0 && sx + ix < p.W) tapmask[q] |= 1u << t;
+        }
+        sa_st[q] = (unsigned)(arow * kRow + (tid & 3) * 16);
+    }
+    const int cs = (p.C + kSlab - 1) / kSlab;         // slabs per tap
+    const unsigned wrow = (unsigned)(p.R * p.S * cs * kSlabBytes);
+    unsigned boff[NQB], sb_st[NQB]; bool b_ok[NQB];
+#pragma unroll
+    for (int q = 0; q < NQB; ++q) {
+        const int i = tid + q * NT, r = i / 12, c = i - r * 12;
+        b_ok[q] = r < BN && n0 + r < p.N;
+        boff[q] = b_ok[q] ? (unsigned)(n0 + r) * wrow + (unsigned)c * 16u : 0u;
+        sb_st[q] = (unsigned)(r * kRow + c * 16);
+    }
+    const unsigned a_rd = (unsigned)((wm * (BMT / WGM) + (lane & 31)) * kRow + (lane >> 5) * 16);
+    const unsigned b_rd = (unsigned)((wn * (BN / WGN) + (lane & 31)) * kRow + (lane >> 5) * 16);
+
+    // slabs: (tap, 32 channels) for the taps some row of the tile can reach, taps ascending
+    const int ntap = cg.ny * cg.nx;
+    unsigned taps = ntap >= 32 ? 0xffffffffu : (1u << ntap) - 1u;
+    if (p.perm) {
+        const int last = min(m0 + BMT, M) - 1;
+        unsigned u = 0;
+        for (int ps = m0 / p.B; ps <= last / p.B; ++ps) u |= p.posmask[ps];
+        taps &= u;
+    }
+    const int nslab = __builtin_popcount(taps) * cs;
+    unsigned taps_left = taps;
+    int tap = 0, ch = 0;                              // the slab that load_tiles fetches next: tap and 32-channel group
+    auto start = [&]() { taps_left = taps; tap = taps ? __builtin_ctz(taps) : 0; ch = 0; };
+    auto advance = [&](int by) {
+        ch += by;
+        while (ch >= cs && taps_left) {
+            ch -= cs;
+            taps_left &= taps_left - 1u;              // drop the tap just finished
+            tap = taps_left ? __builtin_ctz(taps_left) : 0;
+        }
+    };
+    f4 ra[NQA][2];
+    u4 rb[NQB];
+    auto load_tiles = [&]() {
+        const int iy = tap / cg.nx, ix = tap - iy * cg.nx;
+        const int c0 = ch * kSlab + (tid & 3) * 4;
+        const unsigned delta = (unsigned)((iy * p.W + ix) * p.C + ch * kSlab) * 4u;
+        const bool in0 = c0 < p.C, in1 = c0 + 16 < p.C;
+#pragma unroll
+        for (int q = 0; q < NQA; ++q) {
+            ra[q][0] = f4{0.f, 0.f, 0.f, 0.f}; ra[q][1] = f4{0.f, 0.f, 0.f, 0.f};
+            const bool ok = (tapmask[q] >> tap) & 1u;
+            const unsigned o = aoff[q] + delta;
+            if (ok && in0) ra[q][0] = *reinterpret_cast<const f4*>(abase + o);
+            if (ok && in1) ra[q][1] = *reinterpret_cast<const f4*>(abase + o + 64u);
+        }
+        const int wt = (cg.wy0 + iy * p.wst) * p.S + cg.wx0 + ix * p.wst;
+        const unsigned kb = (unsigned)((wt * cs + ch) * kSlabBytes);
+#pragma unroll
+        for (int q = 0; q < NQB; ++q) {
+            rb[q] = u4{0u, 0u, 0u, 0u};
+            if (b_ok[q]) rb[q] = ldg16(wbase, boff[q] + kb);
+        }
+    };
+    auto store_weights = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQB; ++q)
+            if (BN * 12 % NT == 0 || tid + q * NT < BN * 12) *reinterpret_cast<u4*>(sBc + sb_st[q]) = rb[q];
+    };
+    auto store_tiles = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQA; ++q) {
+            bf16x4 h0, m0_, l0, h1, m1, l1;
+            split3(ra[q][0], h0, m0_, l0);
+            split3(ra[q][1], h1, m1, l1);
+            *reinterpret_cast<u4*>(sAc + sa_st[q]) = join8(h0, h1);
+            *reinterpret_cast<u4*>(sAc + sa_st[q] + 64) = join8(m0_, m1);
+            *reinterpret_cast<u4*>(sAc + sa_st[q] + 128) = join8(l0, l1);
+        }
+        store_weights();
+    };
+
+    f16 acc[TM][TN], low[TM][TN];                     // sums of the large and of the small products
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
+    };
+    auto compute = [&]() {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 a[TM][3], b[TN][3];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) a[i][s] = *reinterpret_cast<const bf16x8*>(sAc + a_rd + i * 32 * kRow + s * 64 + ks * 32);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(sBc + b_rd + j * 32 * kRow + s * 64 + ks * 32);
+            // operands swapped: the accumulator holds the transposed tile.  Small products in ascending size.
+            constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
+#pragma unroll
+            for (int t = 0; t < 5; ++t)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][SB[t]], a[i][SA[t]], low[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][0], a[i][0], acc[i][j], 0, 0, 0);
+        }
+    };
+
+    clear();
+    start();
+    advance(kg);
+    const int rounds = (nslab + KG - 1) / KG;
+    if (kg < nslab) load_tiles();
+    for (int t = 0; t < rounds; ++t) {
+        const int mine = t * KG + kg;
+        __syncthreads();                              // every wave is done reading the previous slab
+        if (mine < nslab) store_tiles();
+        __syncthreads();
+        if (mine + KG < nslab) { advance(KG); load_tiles(); }
+        if (mine < nslab) compute();
+    }
+    float bad = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            acc[i][j] += low[i][j];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bad = __builtin_fmaf(acc[i][j][v], 0.f, bad);
+        }
+    if (__syncthreads_or(bad != 0.f)) {               // (NaN != 0) something is not finite: the tile again, with the fp32 instruction
+        clear();
+        start();
+        advance(kg);
+        for (int t = 0; t < rounds; ++t) {
+            const int mine = t * KG + kg;
+            __syncthreads();
+            if (mine < nslab) {
+                load_tiles();
+                advance(KG);
+#pragma unroll
+                for (int q = 0; q < NQA; ++q) {
+                    char* const dst = sAc + (sa_st[q] - (tid & 3) * 16) + (tid & 3) * 32;
+                    *reinterpret_cast<f4*>(dst) = ra[q][0];
+                    *reinterpret_cast<f4*>(dst + 16) = ra[q][1];
+                }
+                store_weights();
+            }
+            __syncthreads();
+            if (mine < nslab) {
+                for (int k = lane >> 5; k < kSlab; k += 2) {
+                    float a[TM], b[TN];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        a[i] = *reinterpret_cast<const float*>(sAc + (wm * (BMT / WGM) + i * 32 + (lane & 31)) * kRow + k * 4);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const __bf16* w = reinterpret_cast<const __bf16*>(sBc + (wn * (BN / WGN) + j * 32 + (lane & 31)) * kRow) + k;
+                        b[j] = ((float)w[64] + (float)w[32]) + (float)w[0];
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j], a[i], acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (KG > 1) {                                     // (the barrier of the test above: nobody reads a slab any more)
+        float* const part = reinterpret_cast<float*>(smem);
+        static_assert((size_t)(KG - 1) * NW * TM * TN * 16 * 64 * 4 <= (size_t)KG * GROUP, "the groups' sums do not fit the LDS of the K loop");
+        if (kg > 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        part[((((kg - 1) * NW + wave) * TM * TN + i * TN + j) * 16 + v) * 64 + lane] = acc[i][j][v];
+        }
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            acc[i][j][v] += part[(((g * NW + wave) * TM * TN + i * TN + j) * 16 + v) * 64 + lane];
+        }
+    }
+
+    // ---- epilogue: lane holds output row (lane & 31) and channels 8*g + 4*(lane >> 5) + {0..3}, g = 0..3 ----
+    const bool stats = EPI == 0 && p.stat != nullptr;         // per-channel sums of the outputs for a batch norm that follows
+    float ss[TN][16], qq[TN][16];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) { ss[j][k] = 0.f; qq[j][k] = 0.f; }
+    if (kg == 0) {
+        float* obase = p.out + (long long)rep * p.out_rep;
+        const float* bias = (EPI == 0 && p.bias) ? p.bias + (long long)rep * p.bias_rep : nullptr;
+        const float* mask = (EPI == 1 && p.mask) ? p.mask + (long long)rep * p.mask_rep : nullptr;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mm = m0 + wm * (BMT / WGM) + i * 32 + (lane & 31);
+            if (mm >= M) continue;
+            int b, pos;
+            if (p.perm) { const int ps = mm / p.B; b = mm - ps * p.B; pos = p.perm[ps]; }
+            else { b = mm / hw; pos = mm - b * hw; }
+            const int y = pos / cg.wc, x = pos - y * cg.wc;
+            const long long pix = ((long long)b * p.Ho + y * p.ostride + cg.ph) * p.Wo + x * p.ostride + cg.pw;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int n = n0 + wn * (BN / WGN) + j * 32 + 8 * g + 4 * (lane >> 5);
+                    if (n >= p.N) continue;
+                    const long long o = pix * p.N + n;
+                    f4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                    f4 sh = {0.f, 0.f, 0.f, 0.f};              // what the statistics are centred on: the bias
+                    if (EPI == 0) {
+                        if (bias) { sh = *reinterpret_cast<const f4*>(bias + n); v += sh; }
+                        if (p.relu) { v[0] = fmaxf(v[0], 0.f); v[1] = fmaxf(v[1], 0.f); v[2] = fmaxf(v[2], 0.f); v[3] = fmaxf(v[3], 0.f); }
+                    } else {
+                        if (mask) {
+                            const f4 mk = *reinterpret_cast<const f4*>(mask + o);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) if (!(mk[e] > 0.f)) v[e] = 0.f;
+                        }
+                        if (p.accumulate) v += *reinterpret_cast<const f4*>(obase + o);
+                    }
+                    *reinterpret_cast<f4*>(obase + o) = v;
+                    if (stats) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { const float f = v[e] - sh[e]; ss[j][4 * g + e] += f; qq[j][4 * g + e] += f * f; }
+                    }
+                }
+            }
+        }
+    }
+    if (stats) {                                              // (the launcher asks for the larger of the K loop's LDS and kStatLdsBytes)
+        __syncthreads();                                      // every wave is past its last read of LDS
+        if (kg == 0)
+            store_column_stats<TN, WGM, WGN>(ss, qq, reinterpret_cast<float*>(smem), wave, lane, p.stat + (long long)slot * p.stat_rep,
+                                             m0 / BMT, n0 + wn * (BN / WGN), p.N);
+        else
+            __syncthreads();                                  // the barrier inside store_column_stats
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Weight gradient: dW[m = (tap, ci)][n = co] = sum over pixels k of x[source pixel(k, tap)][ci] * dy[k][co]
+// ---------------------------------------------------------------------------------------------------------------
+// Both operands are contiguous along channels and the contraction runs over pixels: tiles of 32 pixels are split on their
+// way into LDS as [pixel][plane][channel] and transposed on the way out (ds_read_b64_tr_b16).  A pixel's row is a multiple of
+// 256 bytes plus or minus 64, so that the four rows a transposing read touches land in distinct banks.  Pixels advance by
+// 32 per slab with carries instead of divisions, and a thread's tap is fixed, so a slab costs a few additions per
+// address.  The bias gradient is summed in fp32 by the tiles of the first row of tiles, from the dY values they stage anyway.
+template <int COLS> constexpr int kPixelRow = COLS == 32 ? 320 : COLS * 6 + 64;
+
+// Each wave passes its 32 x 32 blocks through a private piece of LDS and takes them back with eight lanes per row, so that
+// global accesses cover whole lines.  With w set the block is the complete gradient and the update is applied instead.
+constexpr int kStagePitch = 36;                               // floats per staged row
+__device__ __forceinline__ void put_gradient(const f4& v, long long o, const SplitWgradParams& p, float* out, float* w, float* buf)
+{
+    if (!w) { *reinterpret_cast<f4*>(out + o) = v; return; }
+    f4 d = v;
+    if (buf) { d = *reinterpret_cast<const f4*>(buf + o) * p.momentum + d; *reinterpret_cast<f4*>(buf + o) = d; }
+    *reinterpret_cast<f4*>(w + o) = *reinterpret_cast<const f4*>(w + o) - d * p.lr;
+}
+
+template <int BMT, int BN, int WGM, int WGN>
+__global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
+{
+    static_assert(WGM * WGN == 4, "four waves");
+    constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32, BK = 32;
+    constexpr int PA = kPixelRow<BMT>, PB = kPixelRow<BN>;
+    constexpr int AG = BMT / 4, BG = BN / 4;                  // groups of four channels per pixel
+    constexpr int AR = 256 / AG, BR = 256 / BG;               // pixels the threads cover per pass
+    constexpr int NQA = BK / AR, NQB = BK / BR;
+    static_assert(NQA >= 1 && NQB >= 1 && TM >= 1 && TN >= 1, "tile does not fit the thread count");
+    constexpr unsigned A_BUF = BK * PA, B_BUF = BK * PB;
+    static_assert(A_BUF + B_BUF >= 4 * 32 * kStagePitch * 4 && A_BUF + B_BUF >= BR * BN * 4, "epilogue staging does not fit the LDS of the K loop");
+    __shared__ __attribute__((aligned(16))) char smem[A_BUF + B_BUF];
+    char* const sA = smem;                                    // [BK][PA]
+    char* const sB = smem + A_BUF;                            // [BK][PB]
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    // logical item = (slot, split, tile): the tiles of one split of one replica read the same pixels
+    const int mw = p.R * p.S * p.C;                           // rows that are weights; row mw is the bias gradient
+    const unsigned tiles_n = (unsigned)(p.N + BN - 1) / BN, tiles = (unsigned)((mw + BMT - 1) / BMT) * tiles_n;
+    const unsigned item = logical_block();
+    if (item >= tiles * (unsigned)p.splits * (unsigned)p.n_active) return;
+    const int slot = (int)(item / (tiles * (unsigned)p.splits));
+    const int rep = p.order[slot];
+    const unsigned tile = item % tiles;
+    const int m0 = (int)(tile / tiles_n) * BMT, n0 = (int)(tile % tiles_n) * BN;
+    const int split = (int)((item / tiles) % (unsigned)p.splits);
+    const int kbeg = split * p.kchunk, kend = min(p.K, kbeg + p.kchunk);
+    const char* xbase;
+    if (p.cursor) {
+        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        xbase = (const char*)(p.x + ((long long)rep * p.n_samples + first) * p.sample_sz);
+    } else {
+        xbase = (const char*)(p.x + (long long)rep * p.x_rep);
+    }
+    const char* dbase = (const char*)(p.dy + (long long)rep * p.dy_rep);
+
+    // A slots: channels am..am+3 of one tap, pixels arow + AR * q;  B slots: channels bn..bn+3, pixels brow + BR * q
+    const int am = m0 + (tid % AG) * 4, arow = tid / AG;
+    const int bn = n0 + (tid % BG) * 4, brow = tid / BG;
+    const bool a_ok = am < mw, b_ok = bn < p.N;
+    const int atap = am / p.C, aci = am - atap * p.C;
+    const int ady = atap / p.S - p.pad, adx = atap % p.S - p.pad;
+    // output rows y with a source row inside the image: ylo <= y < ylo + yn (likewise x)
+    const int ylo = ady < 0 ? (-ady + p.stride - 1) / p.stride : 0, xlo = adx < 0 ? (-adx + p.stride - 1) / p.stride : 0;
+    const int yn = p.H - 1 - ady >= 0 ? max(0, (p.H - 1 - ady) / p.stride + 1 - ylo) : 0;
+    const int xn = p.W - 1 - adx >= 0 ? max(0, (p.W - 1 - adx) / p.stride + 1 - xlo) : 0;
+    const unsigned a_shift = (unsigned)((ady * p.W + adx) * p.C + aci) * 4u;
+    // 32 pixels further: x += dx, y += dyy, image += db, in source bytes step (carries adjust by cx, cy)
+    const int hw = p.Ho * p.Wo;
+    const int dx = BK % p.Wo, dyy = (BK / p.Wo) % p.Ho, db = BK / hw;
+    const unsigned pc = (unsigned)p.C * 4u, st = (unsigned)p.stride;
+    const unsigned cx = (st * (unsigned)p.W - (unsigned)p.Wo * st) * pc, cy = ((unsigned)p.H - (unsigned)p.Ho * st) * (unsigned)p.W * pc;
+    const unsigned step = (((unsigned)db * (unsigned)p.H + (unsigned)dyy * st) * (unsigned)p.W + (unsigned)dx * st) * pc;
+    int px[NQA], py[NQA]; unsigned poff[NQA];
+    auto seek = [&](int k0) {                                 // (no position table)
+#pragma unroll
+        for (int q = 0; q < NQA; ++q) {
+            const int k = k0 + arow + AR * q, b = k / hw, rem = k - b * hw;
+            py[q] = rem / p.Wo; px[q] = rem - py[q] * p.Wo;
+            poff[q] = ((unsigned)(b * p.H + py[q] * p.stride) * (unsigned)p.W + (unsigned)(px[q] * p.stride)) * pc + a_shift;
+        }
+    };
+    // Contraction order.  With a position table, index k = ps * B + b is image b at pixel perm[ps] (B a multiple of the slab
+    // length); a slab whose position cannot reach any tap of this row tile contributes exact zeros and is left out, but for
+    // the tiles that sum the bias gradient.
+    const bool with_bias = p.has_bias && m0 == 0;
+    unsigned tile_tapbits = 0xffffffffu;
+    if (p.perm && !with_bias) {
+        const int tlo = m0 / p.C, thi = min(m0 + BMT - 1, mw - 1) / p.C;
+        tile_tapbits = (thi >= 31 ? 0xffffffffu : ((2u << thi) - 1u)) & ~((1u << tlo) - 1u);
+    }
+    auto next_slab = [&](int k) {
+        if (p.perm)
+            while (k < kend && !(p.posmask[k / p.B] & tile_tapbits)) k += BK;
+        return k;
+    };
+    f4 ra[NQA], rb[NQB], bsum = {0.f, 0.f, 0.f, 0.f};
+    auto load_tiles = [&](int k0) {
+        int bbase = 0, pos = 0;
+        if (p.perm) { const int ps = k0 / p.B; bbase = k0 - ps * p.B; pos = p.perm[ps]; }
+        if (p.perm) {                                         // stride 1, source and output images alike
+            const int y = pos / p.W, x = pos - y * p.W;
+            const bool in = a_ok && (unsigned)(y - ylo) < (unsigned)yn && (unsigned)(x - xlo) < (unsigned)xn;
+#pragma unroll
+            for (int q = 0; q < NQA; ++q) {
+                const int kr = arow + AR * q;
+                ra[q] = f4{0.f, 0.f, 0.f, 0.f};
+                if (in && k0 + kr < kend) ra[q] = *reinterpret_cast<const f4*>(xbase + ((unsigned)((bbase + kr) * hw + pos) * pc + a_shift));
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NQA; ++q) {
+                ra[q] = f4{0.f, 0.f, 0.f, 0.f};
+                const bool in = a_ok && (unsigned)(py[q] - ylo) < (unsigned)yn && (unsigned)(px[q] - xlo) < (unsigned)xn;
+                if (in && k0 + arow + AR * q < kend) ra[q] = *reinterpret_cast<const f4*>(xbase + poff[q]);
+                px[q] += dx; py[q] += dyy; poff[q] += step;
+                if (px[q] >= p.Wo) { px[q] -= p.Wo; py[q] += 1; poff[q] += cx; }
+                if (py[q] >= p.Ho) { py[q] -= p.Ho; poff[q] += cy; }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NQB; ++q) {
+            const int kr = brow + BR * q;
+            const unsigned pix = p.perm ? (unsigned)((bbase + kr) * hw + pos) : (unsigned)(k0 + kr);
+            rb[q] = f4{0.f, 0.f, 0.f, 0.f};
+            if (b_ok && k0 + kr < kend) rb[q] = *reinterpret_cast<const f4*>(dbase + (pix * (unsigned)p.N + (unsigned)bn) * 4u);
+        }
+    };
+    const unsigned sa_st = (unsigned)(arow * PA + (tid % AG) * 8), sb_st = (unsigned)(brow * PB + (tid % BG) * 8);
+    auto store_tiles = [&]() {
+#pragma unroll
+        for (int q = 0; q < NQA; ++q) {
+            bf16x4 h, m, l;
+            split3(ra[q], h, m, l);
+            char* const o = sA + sa_st + AR * q * PA;
+            *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BMT * 2) = m; *reinterpret_cast<bf16x4*>(o + BMT * 4) = l;
+        }
+#pragma unroll
+        for (int q = 0; q < NQB; ++q) {
+            bf16x4 h, m, l;
+            split3(rb[q], h, m, l);
+            char* const o = sB + sb_st + BR * q * PB;
+            *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BN * 2) = m; *reinterpret_cast<bf16x4*>(o + BN * 4) = l;
+            if (with_bias) bsum += rb[q];
+        }
+    };
+    // operand reads (see lds_read_tr8): lane L of a 16-lane group points at pixel L / 4, channels 4 * (L % 4)
+    const unsigned rd_lane = (unsigned)((lane >> 5) * 8 + ((lane & 15) >> 2));
+    const unsigned a_rd = rd_lane * PA + (unsigned)(wm * (BMT / WGM) + ((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2u;
+    const unsigned b_rd = rd_lane * PB + (unsigned)(wn * (BN / WGN) + ((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2u;
+
+    f16 acc[TM][TN], low[TM][TN];                             // sums of the large and of the small products
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
+    };
+    clear();
+    int k0 = next_slab(kbeg);
+    seek(kbeg);
+    if (k0 < kend) load_tiles(k0);
+    while (k0 < kend) {
+        __syncthreads();                                      // every wave is done reading the previous slab
+        store_tiles();
+        __syncthreads();
+        k0 = next_slab(k0 + BK);
+        if (k0 < kend) load_tiles(k0);
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            bf16x8 a[TM][3], b[TN][3];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) a[i][s] = lds_read_tr8(sA, a_rd + ks * 16 * PA + s * BMT * 2 + i * 64, PA);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) b[j][s] = lds_read_tr8(sB, b_rd + ks * 16 * PB + s * BN * 2 + j * 64, PB);
+            constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
+#pragma unroll
+            for (int t = 0; t < 5; ++t)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][SB[t]], a[i][SA[t]], low[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][0], a[i][0], acc[i][j], 0, 0, 0);
+        }
+    }
+    float bad = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            acc[i][j] += low[i][j];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bad = __builtin_fmaf(acc[i][j][v], 0.f, bad);
+        }
+    if (__syncthreads_or(bad != 0.f)) {                       // (NaN != 0) something is not finite: the tile again, with the fp32 instruction
+        clear();
+        seek(kbeg);
+        for (k0 = next_slab(kbeg); k0 < kend; k0 = next_slab(k0 + BK)) {
+            __syncthreads();
+            load_tiles(k0);
+#pragma unroll
+            for (int q = 0; q < NQA; ++q) *reinterpret_cast<f4*>(sA + (arow + AR * q) * PA + (tid % AG) * 16) = ra[q];
+#pragma unroll
+            for (int q = 0; q < NQB; ++q) *reinterpret_cast<f4*>(sB + (brow + BR * q) * PB + (tid % BG) * 16) = rb[q];
+            __syncthreads();
+            for (int k = lane >> 5; k < BK; k += 2) {
+                float a[TM], b[TN];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const float*>(sA + k * PA + (wm * (BMT / WGM) + i * 32 + (lane & 31)) * 4);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const float*>(sB + k * PB + (wn * (BN / WGN) + j * 32 + (lane & 31)) * 4);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j], a[i], acc[i][j], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- epilogue (the barrier above: nobody reads a slab any more) ----
+    float* const out = (p.splits > 1) ? p.out + (long long)slot * p.out_rep + (long long)split * p.out_split
+                                      : p.out + (long long)rep * p.out_rep;
+    float* const w = (p.splits == 1 && p.sgd_w) ? p.sgd_w + (long long)rep * p.out_rep : nullptr;
+    float* const buf = (w && p.sgd_buf) ? p.sgd_buf + (long long)rep * p.out_rep : nullptr;
+    float* const stage = reinterpret_cast<float*>(smem) + wave * (32 * kStagePitch);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f4*>(stage + (lane & 31) * kStagePitch + 8 * q + 4 * (lane >> 5)) =
+                    f4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int rr = (lane >> 3) + 8 * t, cc = (lane & 7) * 4;
+                const f4 v = *reinterpret_cast<const f4*>(stage + rr * kStagePitch + cc);
+                const int mm = m0 + wm * (BMT / WGM) + i * 32 + rr, nn = n0 + wn * (BN / WGN) + j * 32 + cc;
+                if (mm < mw && nn < p.N) put_gradient(v, (long long)mm * p.N + nn, p, out, w, buf);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    if (with_bias) {                                          // join the partial sums of the threads that share a channel group, pixels ascending
+        __syncthreads();
+        float* const red = reinterpret_cast<float*>(smem);    // [BR][BN]
+        *reinterpret_cast<f4*>(red + brow * BN + (tid % BG) * 4) = bsum;
+        __syncthreads();
+        if (brow == 0 && b_ok) {
+            f4 v = bsum;
+#pragma unroll
+            for (int r = 1; r < BR; ++r) v += *reinterpret_cast<const f4*>(red + r * BN + (tid % BG) * 4);
+            put_gradient(v, (long long)mw * p.N + bn, p, out, w, buf);
+        }
+    }
+}
+
+// fp32 master W[tap][ci][co] -> Wf[co][tap][ci] and Wb[ci][T-1-tap][co] as described at the top.  A workgroup handles one
+// tap and a 64 x 64 (ci, co) tile; each thread forms the three 16-byte groups of eight positions.  Bound by memory: 4 bytes
+// read and 12 written per weight.  A weight whose bf16 rounding overflows is cut instead, and one that is not finite
+// has zero lower parts, so that the three parts always add up to the weight.
+__device__ __forceinline__ void split_weight(float x, __bf16& h, __bf16& m, __bf16& l)
+{
+    h = (__bf16)x;
+    if (!(fabsf((float)h) < __builtin_inff())) h = __builtin_bit_cast(__bf16, (unsigned short)(__builtin_bit_cast(unsigned, x) >> 16));
+    float r = x - (float)h;
+    if (!(fabsf(x) < __builtin_inff())) { h = (__bf16)x; r = 0.f; }
+    m = (__bf16)r;
+    l = (__bf16)(r - (float)m);
+}
+__global__ __launch_bounds__(256) void weight_split_kernel(WeightSplitParams p)
+{
+    __shared__ float tile[64][65];                            // [ci][co], zero outside the layer
+    const int rep = p.order[blockIdx.z];
+    const int tap = blockIdx.y % p.taps, co0 = (blockIdx.y / p.taps) * 64, ci0 = blockIdx.x * 64;
+    const float* w = p.w + (long long)rep * p.w_rep + (long long)tap * p.C * p.N;
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int ci = ci0 + ty + 4 * r;
+        tile[ty + 4 * r][tx] = (ci < p.C && co0 + tx < p.N) ? w[(long long)ci * p.N + co0 + tx] : 0.f;
+    }
+    __syncthreads();
+    const int csf = (p.C + kSlab - 1) / kSlab, csb = (p.N + kSlab - 1) / kSlab;
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        __bf16* const dst = which ? p.wb : p.wf;
+        if (!dst) continue;
+        const int row0 = which ? ci0 : co0, rows = which ? p.C : p.N;       // rows of the copy and the channels along its slabs
+        const int k0 = which ? co0 : ci0, cs = which ? csb : csf, t = which ? p.taps - 1 - tap : tap;
+        char* const base = (char*)(dst + (long long)rep * p.wcopy_rep);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int i = threadIdx.x + q * 256, g = i & 3, sl = (i >> 2) & 1, row = i >> 3;
+            const int slab = k0 / kSlab + sl;
+            if (row0 + row >= rows || slab >= cs) continue;
+            bf16x8 h, m, l;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = sl * kSlab + (e >> 2) * 16 + g * 4 + (e & 3);
+                __bf16 a, b, c;
+                split_weight(which ? tile[row][k] : tile[k][row], a, b, c);
+                h[e] = a; m[e] = b; l[e] = c;
+            }
+            char* const o = base + ((long long)(row0 + row) * p.taps * cs + t * cs + slab) * kSlabBytes + g * 16;
+            *reinterpret_cast<bf16x8*>(o) = h;
+            *reinterpret_cast<bf16x8*>(o + 64) = m;
+            *reinterpret_cast<bf16x8*>(o + 128) = l;
+        }
+    }
+}
+
+template <int BMT, int BN, int WGM, int WGN, int KG>
+hipError_t launch_t(SplitConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows)
+{
+    constexpr size_t loop_lds = (size_t)KG * (BMT + BN) * kRow, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
+    constexpr size_t lds = loop_lds > stat_lds ? loop_lds : stat_lds;
+    if (lds > 65536) {
+        static const bool ok =
+            hipFuncSetAttribute((const void*)conv_split_kernel<BMT, BN, WGM, WGN, KG, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
+            hipFuncSetAttribute((const void*)conv_split_kernel<BMT, BN, WGM, WGN, KG, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+        if (!ok) return hipErrorInvalidValue;
+    }
+    if (stat_rows) *stat_rows = BMT;
+    const int rows0 = p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);     // largest class
+    p.tiles_m = (rows0 + BMT - 1) / BMT;
+    const dim3 grid(die_grid((long long)p.tiles_m * ((p.N + BN - 1) / BN) * p.classes * n_active)), block(WGM * WGN * KG * 64);
+    if (epi == 0) hipLaunchKernelGGL((conv_split_kernel<BMT, BN, WGM, WGN, KG, 0>), grid, block, lds, s, p);
+    else hipLaunchKernelGGL((conv_split_kernel<BMT, BN, WGM, WGN, KG, 1>), grid, block, lds, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+long long split_weight_units(int rows, int taps, int channels)
+{
+    return (long long)rows * taps * ((channels + kSlab - 1) / kSlab) * (kSlabBytes / 2);
+}
+
+hipError_t launch_conv_split(const SplitConvParams& p0, int epi, int n_active, hipStream_t s, int* stat_rows)
+{
+    if (n_active < 1) return hipSuccess;
+    SplitConvParams p = p0;
+    p.n_active = n_active;
+    if (p.C % 4 != 0 || p.N % 4 != 0 || p.R * p.S > 32 || (p.perm && p.classes != 1)) return hipErrorInvalidValue;
+    const long long rows0 = (long long)p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);
+    const long long groups = (long long)p.classes * n_active;
+    const long long t64 = (rows0 + 63) / 64 * ((p.N + 63) / 64) * groups, t128 = (rows0 + 127) / 128 * ((p.N + 127) / 128) * groups;
+    // How many workgroups a tile size gives decides: a workgroup's time is the length of its K loop, so a launch that cannot
+    // fill 256 compute units takes smaller tiles and several groups of waves along K.  Measured (us; 512 x 512 channels,
+    // 3 x 3, batch 64; 2 x 2 images with 1 replica, 4 x 4 with 1, 4 x 4 with 4, 8 x 8 x 256 channels with 4, 4 x 4 with 16):
+    //   32 x 32, 8 groups:   43    85   319   373  1368         64 x 64, 1 group:    131   133   148   144   526
+    //   64 x 64, 4 groups:   73    76   162   179   637         128 x 128, 2 groups: 216   218   223   131   504
+    //   64 x 64, 2 groups:   91    94   139   147   536         128 x 128, 1 group:  262   267   272   149   448
+    const bool large = p.tile_hint == 1;
+    if (large && p.N > 64) return launch_t<128, 128, 2, 2, 1>(p, epi, n_active, s, stat_rows);
+    if (large && p.N > 32) return launch_t<128, 64, 4, 1, 1>(p, epi, n_active, s, stat_rows);
+    if (large) return launch_t<128, 32, 4, 1, 1>(p, epi, n_active, s, stat_rows);
+    if (t64 <= 48) return launch_t<32, 32, 1, 1, 8>(p, epi, n_active, s, stat_rows);
+    if (t64 <= 256) return launch_t<64, 64, 2, 2, 4>(p, epi, n_active, s, stat_rows);
+    if (t64 <= 640) return launch_t<64, 64, 2, 2, 2>(p, epi, n_active, s, stat_rows);
+    if (p.N <= 32) return launch_t<128, 32, 4, 1, 1>(p, epi, n_active, s, stat_rows);
+    if (p.N > 64) {
+        if (t128 > 256) return launch_t<128, 128, 2, 2, 1>(p, epi, n_active, s, stat_rows);
+        if (t64 > 880) return launch_t<128, 128, 2, 2, 2>(p, epi, n_active, s, stat_rows);
+    }
+    if (p.N <= 64 && t64 > 2048) return launch_t<128, 64, 4, 1, 1>(p, epi, n_active, s, stat_rows);
+    return launch_t<64, 64, 2, 2, 1>(p, epi, n_active, s, stat_rows);
+}
+
+int split_wgrad_tiles(int rows, int N)
+{
+    const int bn = N > 64 ? 128 : N > 32 ? 64 : 32;
+    return (rows + 127) / 128 * ((N + bn - 1) / bn);
+}
+
+hipError_t launch_wgrad_split(const SplitWgradParams& p0, int n_active, hipStream_t s)
+{
+    if (n_active < 1) return hipSuccess;
+    SplitWgradParams p = p0;
+    p.n_active = n_active;
+    if (p.C % 4 != 0 || p.N % 4 != 0 || (p.splits > 1 && p.kchunk % 32 != 0)) return hipErrorInvalidValue;
+    if (p.perm && (p.B % 32 != 0 || p.stride != 1 || p.R * p.S > 32)) return hipErrorInvalidValue;
+    const dim3 grid(die_grid((long long)split_wgrad_tiles(p.R * p.S * p.C, p.N) * p.splits * n_active)), block(256);
+    if (p.N > 64) hipLaunchKernelGGL((wgrad_split_kernel<128, 128, 2, 2>), grid, block, 0, s, p);
+    else if (p.N > 32) hipLaunchKernelGGL((wgrad_split_kernel<128, 64, 4, 1>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((wgrad_split_kernel<128, 32, 4, 1>), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_weight_split(const WeightSplitParams& p, int n_active, hipStream_t s)
+{
+    if (n_active < 1) return hipSuccess;
+    const dim3 grid((unsigned)((p.C + 63) / 64), (unsigned)(p.taps * ((p.N + 63) / 64)), (unsigned)n_active), block(256);
+    hipLaunchKernelGGL(weight_split_kernel, grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace hadfl

@@ -74,7 +74,7 @@ __device__ __forceinline__ void store_column_stats(const float (&ss)[TN][16], co
                 a += *reinterpret_cast<const f4*>(cross + (((r * WGN + wn) * 2 + which) * (4 * TN) + c4) * 8 + h * 4);
             // column quad c4 of the area = (j, g) = (c4 / 4, c4 % 4): channels j*32 + 8g + 4h + {0..3}
             const int n = n_base + (c4 / 4) * 32 + 8 * (c4 % 4) + 4 * h;
-            *reinterpret_cast<f4*>(stat_slot + (long long)entry * 2 * N + which * N + n) = a;
+            if (n < N) *reinterpret_cast<f4*>(stat_slot + (long long)entry * 2 * N + which * N + n) = a;
         }
     }
 }

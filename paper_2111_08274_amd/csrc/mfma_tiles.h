@@ -1,0 +1,65 @@
+// Pieces shared by the tiled matrix-core kernels.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace hadfl {
+namespace tiles {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+
+// Workgroups are handed to the eight accelerator dies in turn (workgroup i runs on die i % 8), and each die has its own
+// L2.  With a one-dimensional grid of 8 * chunk workgroups, die d takes the consecutive logical items
+// [d * chunk, (d + 1) * chunk): the tiles of one replica, which share its weights and activations, meet in one L2.
+constexpr int kDies = 8;
+__device__ __forceinline__ unsigned logical_block()
+{
+    const unsigned chunk = gridDim.x / kDies;
+    return (blockIdx.x % kDies) * chunk + blockIdx.x / kDies;
+}
+inline unsigned die_grid(long long items) { return (unsigned)((items + kDies - 1) / kDies * kDies); }
+
+__device__ __forceinline__ u4 ldg16(const char* base, unsigned off) { return *reinterpret_cast<const u4*>(base + off); }
+
+// Three bf16 values whose sum is the float: h = bf16(x), m = bf16(x - h), l = x - h - m.  The two differences are exact,
+// and what is left for l fits bf16's eight significant bits, so h + m + l = x for every finite x whose parts stay in
+// range; |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.
+__device__ __forceinline__ void split3(const f4& x, bf16x4& h, bf16x4& m, bf16x4& l)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (__bf16)x[e];
+    f4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = x[e] - (float)h[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = (__bf16)r[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) l[e] = (__bf16)(r[e] - (float)m[e]);
+}
+__device__ __forceinline__ u4 join8(const bf16x4& a, const bf16x4& b)
+{
+    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    return u4{x[0], x[1], y[0], y[1]};
+}
+
+// Transposing LDS read: within a group of 16 lanes, lane i receives element (i % 4) of the 8 bytes addressed by lane
+// 4*j + i/4, for j = 0..3.  Pointing lane L at row k0 + L/4, columns 4*(L%4).. of a 16-column block therefore hands lane i
+// the four consecutive k of column i -- half of an MFMA operand.
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef short s8v __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s4v lds_s4v;
+__device__ __forceinline__ bf16x8 lds_read_tr8(const char* base, unsigned off, unsigned row_pitch_bytes)
+{
+    // base + off addresses this lane's 8 bytes in row k0; rows k0+4.. supply the upper four k
+    const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)(base + off));
+    const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)(base + off + 4 * row_pitch_bytes));
+    const s8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+}  // namespace tiles
+}  // namespace hadfl

@@ -114,16 +114,52 @@ struct WeightPrepParams {    // fp32 W[tap][C][N] -> bf16 Wf[N][tap*C + ci] and 
 };
 hipError_t launch_weight_prep(const WeightPrepParams& p, int n_active, hipStream_t s);
 
-// fp32 configuration: the same kernel plan in fp32 (conv_f32_fast.hip).  FastConvParams with a, wmat, out, mask pointing at
-// floats (wmat_rep in floats); needs C % 32 == 0, N % 64 == 0.  stat / stat_rows as in launch_conv_fast.
-hipError_t launch_conv_f32_fast(const FastConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows = nullptr);
-struct WeightPrepF32Params {    // fp32 W[tap][C][N] -> fp32 Wf[N][tap*C + ci] and Wb[C][(taps-1-tap)*N + co]
+// ---- fp32 configuration: convolutions and dense layers on the bf16 matrix cores, every float as three bf16 (conv_f32_split.hip) ----
+struct SplitConvParams {     // out[pixel][n] = sum over taps and channels of a[source pixel][c] * wmat[n][tap][c]
+    int B, H, W, C;                            // source: X (forward) or dY (data gradient)
+    int Ho, Wo, N;                             // output image and channels
+    int R, S, pad;                             // filter in the copy's (forward or flipped) order
+    int sstride;                               // source pixels per output pixel: the stride (forward), 1 (data gradient)
+    int ostride, wst, classes;                 // data gradient: stride, stride, stride^2; forward 1, 1, 1
+    const float* a; long long a_rep;
+    const long long* cursor; int n_samples, batch; long long sample_sz;   // a is the data set when cursor != null
+    const __bf16* wmat; long long wmat_rep;    // split copy, per-replica stride in 2-byte units
+    float* out; long long out_rep;
+    const float* bias; long long bias_rep;     // forward: bias inside the replica rows, or null
+    int relu;
+    const float* mask; long long mask_rep; int accumulate;   // data gradient
+    const int* order;
+    const int* perm; const unsigned* posmask;  // optional position table as in FastConvParams (stride 1)
+    float* stat; long long stat_rep;           // forward, optional: statistics entries as in FastConvParams
+    int tile_hint;                             // 1: the largest tiles whatever the launch size
+    int tiles_m, n_active;                     // set by the launcher
+};
+// epi 0: forward (+bias, ReLU); epi 1: data gradient (mask, accumulate).  Needs C % 4 == 0, N % 4 == 0, R * S <= 32, tensors
+// of less than 4 GiB per replica.  stat_rows (may be null): rows per statistics entry of the kernel that was launched.
+hipError_t launch_conv_split(const SplitConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows = nullptr);
+struct SplitWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias) the bias gradient as row R*S*C
+    int B, H, W, C, Ho, Wo, N, R, S, pad, stride;
+    int K, kchunk, splits, has_bias;           // K = B*Ho*Wo; kchunk a multiple of 32 when splits > 1
+    const float* x; long long x_rep;
+    const long long* cursor; int n_samples, batch; long long sample_sz;   // x is the data set when cursor != null
+    const float* dy; long long dy_rep;
+    float* out; long long out_rep, out_split;
+    const int* order;
+    const int* perm; const unsigned* posmask;  // optional position table as in FastWgradParams; stride 1, B % 32 == 0
+    float* sgd_w; float* sgd_buf; float lr, momentum;    // as in FastWgradParams
+    int n_active;                              // set by the launcher
+};
+// Needs C % 4 == 0, N % 4 == 0, tensors of less than 4 GiB per replica.
+hipError_t launch_wgrad_split(const SplitWgradParams& p, int n_active, hipStream_t s);
+int split_wgrad_tiles(int rows, int N);                              // workgroups per split and replica (rows = R*S*C)
+long long split_weight_units(int rows, int taps, int channels);      // 2-byte units of a split copy [rows][taps][channels]
+struct WeightSplitParams {    // fp32 W[tap][C][N] -> split copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
     const float* w; long long w_rep;
-    float* wf; float* wb; long long wcopy_rep;
+    __bf16* wf; __bf16* wb; long long wcopy_rep;
     int C, N, taps;
     const int* order;
 };
-hipError_t launch_weight_prep_f32(const WeightPrepF32Params& p, int n_active, hipStream_t s);
+hipError_t launch_weight_split(const WeightSplitParams& p, int n_active, hipStream_t s);
 
 struct DenseSmallParams {     // out[m][n] = sum_k x[m][k] w[k][n] + bias[n], N <= 16
     const float* x; long long x_rep;

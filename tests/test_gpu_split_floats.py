@@ -1,0 +1,91 @@
+"""fp32 layers that run on split floats (three bf16 per float): ragged channel counts, images, strides and batches, each tile
+size of the launchers, and values that bf16 cannot hold."""
+import numpy as np
+import pytest
+
+from oracle import nets
+from paper_2111_08274_amd import hadfl
+from tests import parity_metrics as pm
+from tests.pair import Pair
+
+pytestmark = pytest.mark.gpu
+
+
+def _nets():
+    c = {}
+    b = nets._Builder()                       # channels of 4 .. 132, stride 2 and 3, filters of 1, 3 and 5, a padded 1 x 1
+    t = b.relu(b.conv(b.relu(b.conv(0, 4)), 36))
+    t = b.relu(b.bn(b.conv(t, 68, stride=2, bias=False)))
+    t = b.relu(b.conv(t, 132, k=5, stride=3, pad=2))
+    t = b.relu(b.conv(t, 12, k=1, pad=1))
+    b.dense(b.relu(b.dense(t, 20)), 5)
+    c["ragged"] = (b.array(), (13, 9, 3), 7)
+    b = nets._Builder()                       # a residual block whose two convolutions meet in one gradient, projection with stride 2
+    t = b.relu(b.bn(b.conv(0, 40, bias=False)))
+    u = b.bn(b.conv(b.relu(b.bn(b.conv(t, 80, stride=2, bias=False))), 80, bias=False))
+    t = b.relu(b.add(u, b.bn(b.conv(t, 80, k=1, stride=2, pad=0, bias=False))))
+    b.dense(b.gap(t), 5)
+    c["residual"] = (b.array(), (10, 10, 3), 33)
+    b = nets._Builder()                       # positions sorted by their taps, in both directions and the weight gradient
+    t = b.relu(b.conv(b.relu(b.conv(0, 32)), 128))
+    t = b.relu(b.conv(b.maxpool(t), 96, bias=False))
+    b.dense(b.gap(t), 5)
+    c["tables"] = (b.array(), (8, 6, 3), 64)
+    return c
+
+
+NETS = _nets()
+
+
+@pytest.mark.parametrize("hint", [0, 1])
+@pytest.mark.parametrize("name", sorted(NETS))
+@pytest.mark.parametrize("replicas", [2, 9])
+def test_split_layers_against_oracle(name, replicas, hint):
+    """Every tensor's update of every step against the oracle.  Two and nine replicas put the launches on both sides of the
+    tile rules (a few workgroups with several wave groups along K; one group), hint 1 takes the largest tiles."""
+    ops, shape, batch = NETS[name]
+    rng = np.random.default_rng(31)
+    x = rng.standard_normal((replicas, 2 * batch) + shape).astype(np.float32)
+    y = rng.integers(0, 5, size=(replicas, 2 * batch)).astype(np.int32)
+    p = Pair(ops, shape, replicas, 1, x, y, batch, 0.01, 0.9, [2] + [1] * (replicas - 1), options={hadfl.OPT_TILE_HINT: hint})
+    w = p.forced_steps()
+    print(name, replicas, hint, pm.show(w), flush=True)
+    assert w["compared"] > 0 and p.max_param_diff() <= 1e-4
+    p.close()
+
+
+def test_values_bf16_cannot_hold():
+    """A dense classifier on the data set, compared with 64-bit arithmetic where fp32 stays finite but the bf16 parts do not:
+    a weight of -Inf (logit -Inf, probability 0), a weight and an input above bf16's largest number, the input against
+    zero weights.  Error bound: 64 products and 24 samples in fp32, 88 * 2^-24 < 1e-5 relative."""
+    d, classes, batch, lr = 64, 20, 24, 0.5
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((1, batch, 1, 1, d)).astype(np.float32)
+    y = rng.integers(0, 7, size=(1, batch)).astype(np.int32)
+    x[0, :, 0, 0, 3] = 1.0
+    x[0, 2, 0, 0, 5] = 3.4e38
+    b = nets._Builder()
+    b.dense(0, classes)
+    cfg = hadfl.make_config(1, 1, net="custom", custom_ops=b.array()[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=batch, n_samples=batch,
+                            in_shape=(1, 1, d), n_classes=classes, lr=lr, momentum=0.0)
+    w = (0.1 * rng.standard_normal((d, classes))).astype(np.float32)
+    w[5] = 0.0
+    w[3, 7] = -np.inf
+    w[3, 8] = -3.4e38
+    bias = np.zeros(classes, dtype=np.float32)
+    ctx = hadfl.Context(cfg, [1], w0=np.concatenate([w.ravel(), bias]), x=x, y=y)
+    ctx.local_steps()
+    got, loss = ctx.params(0), float(ctx.losses()[0])
+    ctx.close()
+    xd, wd = x[0, :, 0, 0].astype(np.float64), w.astype(np.float64)
+    logits = xd @ wd
+    e = np.exp(logits - logits.max(1, keepdims=True))
+    p = e / e.sum(1, keepdims=True)
+    assert np.isfinite(loss)
+    assert abs(loss + np.log(p[np.arange(batch), y[0]]).mean()) <= 1e-5
+    p[np.arange(batch), y[0]] -= 1.0
+    want = np.concatenate([(wd - lr * (xd.T @ (p / batch))).ravel(), -lr * p.sum(0) / batch])
+    same = np.isfinite(want)
+    assert np.array_equal(got[~same].astype(np.float64), want[~same]) and np.isfinite(got[same]).all()
+    scale = np.concatenate([np.abs(wd) + lr * (np.abs(xd).T @ (np.abs(p) / batch)), lr * np.abs(p).sum(0)[None] / batch])
+    assert (np.abs(got[same] - want[same]) <= 1e-5 * scale.ravel()[same] + 1e-30).all()
