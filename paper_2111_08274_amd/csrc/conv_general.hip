@@ -1,7 +1,8 @@
-// fp32 convolutions and dense layers on the bf16 matrix cores: forward and data gradient of every local step (paper
-// Sec. 2.1) in the fp32 configuration, without giving up fp32 accuracy.
+// Convolutions and dense layers of any geometry, forward, data gradient and weight gradient of every local step (paper Sec. 2.1),
+// on the bf16 matrix cores: the fp32 configuration (T = float) without giving up fp32 accuracy, and the layers of the bf16
+// configuration (T = __bf16) that the lean kernels of conv_bf16_fast.hip do not take (strides, ragged channel counts, odd images).
 //
-// The fp32 matrix instruction runs at a sixteenth of the bf16 rate (157 against 2500 TFLOP/s).  A float is the exact sum
+// T = float.  The fp32 matrix instruction runs at a sixteenth of the bf16 rate (157 against 2500 TFLOP/s).  A float is the exact sum
 // of three bf16 numbers, x = xh + xm + xl, so a product is the sum of nine bf16 products, and the six of them that are
 // not below 2^-26 of it,
 //       xh*yh  +  (xh*ym + xm*yh + xm*ym + xh*yl + xl*yh),
@@ -16,19 +17,22 @@
 // A value that is not finite, or an accumulator that overflows, makes the six products disagree with the one (Inf * 0):
 // a tile that finds a result that is not finite is computed again with the fp32 instruction, which is what it then stores.
 //
-//   * The weights are kept as two split matrices per layer, refreshed from the master before every forward pass:
+//   * The weights are kept as two copies per layer, refreshed from the master before every forward pass,
 //       Wf[co][tap][ci]  and  Wb[ci][flipped tap][co],
 //     so that forward and data gradient are the same kernel: a data gradient is a convolution of dY with the flipped,
 //     transposed filter.  For stride s an input pixel only meets the taps of its own residue (y mod s, x mod s); the
 //     pixels of one residue class are a dense problem over that class's taps, one class after another in the grid.
-//   * K is walked in slabs of 32 channels of one tap (channels padded to 32 with zeros).  A slab of a row is 208 bytes
-//     of LDS: three planes of 32 bf16 and 16 bytes of padding, so that sixteen consecutive rows start in distinct groups
-//     of four banks and the 16-byte operand reads run at full rate.  The weights lie in memory in that very order, 192
-//     contiguous bytes per slab; the activations are split on their way into LDS.
-//   * Position of channel k inside a slab: pos = ((k / 4) % 4) * 8 + (k / 16) * 4 + k % 4, the same for both operands:
+//   * K is walked in slabs of 32 (float) or 64 (bf16) channels of one tap, the last one of a tap padded with zeros.  A
+//     slab of a row is 208 bytes of LDS (three planes of 32 bf16 and 16 bytes of padding) or 144 (64 bf16 and 16), so that
+//     sixteen consecutive rows start in distinct groups of four banks and the 16-byte operand reads run at full rate.
+//     The weights lie in memory in that very order, 192 or 128 contiguous bytes per slab; float activations are split
+//     on their way into LDS.
+//   * Position of float channel k inside a slab: pos = ((k / 4) % 4) * 8 + (k / 16) * 4 + k % 4, the same for both operands:
 //     a thread reads channels 4g..4g+3 and 16+4g..16+4g+3 (64 contiguous bytes over four lanes each) and stores one
 //     16-byte group per plane.
-//   * MFMA operands are swapped (C^T = B^T A^T): four consecutive output channels per lane, 16-byte stores.
+//   * MFMA operands are swapped (C^T = B^T A^T): four consecutive output channels per lane, 8- or 16-byte stores.
+#include <type_traits>
+
 #include "train_kernels.h"
 #include "conv_stats.h"
 #include "mfma_tiles.h"
@@ -40,9 +44,31 @@ using namespace tiles;
 using conv_stats::store_column_stats;
 using conv_stats::kStatLdsBytes;
 
-constexpr int kSlab = 32;                 // channels per slab
-constexpr int kRow = 208;                 // LDS bytes per row of a slab
-constexpr int kSlabBytes = 192;           // the same row in memory (weights)
+// channels per slab, LDS bytes per row of a slab, bytes of the same row in memory (weights), groups of a row that a thread
+// stages at a time (32 bytes of float, 16 of bf16), planes
+template <typename T> struct Slab;
+template <> struct Slab<float> { static constexpr int channels = 32, row = 208, bytes = 192, groups = 4, planes = 3; };
+template <> struct Slab<__bf16> { static constexpr int channels = 64, row = 144, bytes = 128, groups = 8, planes = 1; };
+
+// four consecutive elements as floats
+__device__ __forceinline__ f4 load4(const float* p) { return *reinterpret_cast<const f4*>(p); }
+__device__ __forceinline__ f4 load4(const __bf16* p)
+{
+    const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
+    return f4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+// stores v rounded to the element type and leaves the rounded values in v
+__device__ __forceinline__ void store4(float* p, f4& v) { *reinterpret_cast<f4*>(p) = v; }
+__device__ __forceinline__ void store4(__bf16* p, f4& v)
+{
+    const bf16x4 r = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+    *reinterpret_cast<bf16x4*>(p) = r;
+    v = f4{(float)r[0], (float)r[1], (float)r[2], (float)r[3]};
+}
+__device__ __forceinline__ u4 round8(const f4& a, const f4& b)
+{
+    return join8(bf16x4{(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3]}, bf16x4{(__bf16)b[0], (__bf16)b[1], (__bf16)b[2], (__bf16)b[3]});
+}
 
 // What one residue class of pixels needs (one class, the whole image, unless it is a strided data gradient)
 struct ClassGeo {
@@ -52,7 +78,7 @@ struct ClassGeo {
     int wy0, wx0;                         // filter tap of (iy, ix) = ((wy0 + iy * wst) * S + wx0 + ix * wst)
     int by, bx;                           // source pixel of tap (iy, ix) = (y * sstride + by + iy, x * sstride + bx + ix)
 };
-__device__ __forceinline__ ClassGeo class_geo(const SplitConvParams& p, int cls)
+__device__ __forceinline__ ClassGeo class_geo(const GeneralConvParams& p, int cls)
 {
     ClassGeo c;
     if (p.classes == 1) {
@@ -73,13 +99,17 @@ __device__ __forceinline__ ClassGeo class_geo(const SplitConvParams& p, int cls)
 // ..., and the groups' sums are joined in group order through LDS at the end.  One LDS buffer per group: the next slab
 // waits in registers while the current one is multiplied, two barriers per slab.
 // EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate.
-template <int BMT, int BN, int WGM, int WGN, int KG, int EPI>
-__global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM * WGN * KG / 4) void conv_split_kernel(SplitConvParams p)
+// SRC: type of the source tensor; float for T = __bf16 is the data set, rounded on its way into LDS.
+template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, int KG, int EPI>
+__global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM * WGN * KG / 4) void conv_general_kernel(GeneralConvParams p)
 {
+    constexpr bool kSplit = std::is_same<T, float>::value, kRound = !kSplit && std::is_same<SRC, float>::value;
+    constexpr int kSlab = Slab<T>::channels, kRow = Slab<T>::row, kSlabBytes = Slab<T>::bytes, GR = Slab<T>::groups, CH = kSlabBytes / 16;
+    constexpr unsigned ES = sizeof(SRC);
     constexpr int NW = WGM * WGN, NT = NW * 64;
     constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32;
-    constexpr int NQA = BMT * 4 / NT, NQB = (BN * 12 + NT - 1) / NT;
-    static_assert(NQA >= 1 && TM >= 1 && TN >= 1 && BMT * 4 % NT == 0, "tile does not fit the thread count");
+    constexpr int NQA = BMT * GR / NT, NQB = (BN * CH + NT - 1) / NT;
+    static_assert(NQA >= 1 && TM >= 1 && TN >= 1 && BMT * GR % NT == 0, "tile does not fit the thread count");
     constexpr unsigned A_BUF = BMT * kRow, GROUP = (BMT + BN) * kRow;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -106,11 +136,12 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     }
     const char* wbase = (const char*)(p.wmat + (long long)rep * p.wmat_rep);
 
-    // A slots of this thread: (row, group g) with g = tid % 4
+    // A slots of this thread: (row, group g)
+    const int ag = tid % GR;
     unsigned aoff[NQA], tapmask[NQA], sa_st[NQA];
 #pragma unroll
     for (int q = 0; q < NQA; ++q) {
-        const int i = tid + q * NT, arow = i >> 2, m = m0 + arow;
+        const int i = tid + q * NT, arow = i / GR, m = m0 + arow;
         aoff[q] = 0; tapmask[q] = 0;
         if (m < M) {
             int b, pos;
@@ -118,19 +149,19 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
             else { b = m / hw; pos = m - b * hw; }
             const int y = pos / cg.wc, x = pos - y * cg.wc;
             const int sy = y * p.sstride + cg.by, sx = x * p.sstride + cg.bx;
-            aoff[q] = (unsigned)(((b * p.H + sy) * p.W + sx) * p.C + (tid & 3) * 4) * 4u;      // (may lie outside: only used with a tap's delta)
+            aoff[q] = (unsigned)(((b * p.H + sy) * p.W + sx) * p.C + ag * (kSplit ? 4 : 8)) * ES;      // (may lie outside: only used with a tap's delta)
             for (int iy = 0, t = 0; iy < cg.ny; ++iy)
                 for (int ix = 0; ix < cg.nx; ++ix, ++t)
                     if (sy + iy >= 0 && sy + iy < p.H && sx + ix >= 0 && sx + ix < p.W) tapmask[q] |= 1u << t;
         }
-        sa_st[q] = (unsigned)(arow * kRow + (tid & 3) * 16);
+        sa_st[q] = (unsigned)(arow * kRow + ag * 16);
     }
     const int cs = (p.C + kSlab - 1) / kSlab;         // slabs per tap
     const unsigned wrow = (unsigned)(p.R * p.S * cs * kSlabBytes);
     unsigned boff[NQB], sb_st[NQB]; bool b_ok[NQB];
 #pragma unroll
     for (int q = 0; q < NQB; ++q) {
-        const int i = tid + q * NT, r = i / 12, c = i - r * 12;
+        const int i = tid + q * NT, r = i / CH, c = i - r * CH;
         b_ok[q] = r < BN && n0 + r < p.N;
         boff[q] = b_ok[q] ? (unsigned)(n0 + r) * wrow + (unsigned)c * 16u : 0u;
         sb_st[q] = (unsigned)(r * kRow + c * 16);
@@ -138,7 +169,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     const unsigned a_rd = (unsigned)((wm * (BMT / WGM) + (lane & 31)) * kRow + (lane >> 5) * 16);
     const unsigned b_rd = (unsigned)((wn * (BN / WGN) + (lane & 31)) * kRow + (lane >> 5) * 16);
 
-    // slabs: (tap, 32 channels) for the taps some row of the tile can reach, taps ascending
+    // slabs: (tap, kSlab channels) for the taps some row of the tile can reach, taps ascending
     const int ntap = cg.ny * cg.nx;
     unsigned taps = ntap >= 32 ? 0xffffffffu : (1u << ntap) - 1u;
     if (p.perm) {
@@ -149,7 +180,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     }
     const int nslab = __builtin_popcount(taps) * cs;
     unsigned taps_left = taps;
-    int tap = 0, ch = 0;                              // the slab that load_tiles fetches next: tap and 32-channel group
+    int tap = 0, ch = 0;                              // the slab that load_tiles fetches next: tap and group of channels
     auto start = [&]() { taps_left = taps; tap = taps ? __builtin_ctz(taps) : 0; ch = 0; };
     auto advance = [&](int by) {
         ch += by;
@@ -159,20 +190,21 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
             tap = taps_left ? __builtin_ctz(taps_left) : 0;
         }
     };
-    f4 ra[NQA][2];
+    f4 ra[NQA][2];                                    // (bf16 source: ra[q][0] holds the eight elements)
     u4 rb[NQB];
     auto load_tiles = [&]() {
         const int iy = tap / cg.nx, ix = tap - iy * cg.nx;
-        const int c0 = ch * kSlab + (tid & 3) * 4;
-        const unsigned delta = (unsigned)((iy * p.W + ix) * p.C + ch * kSlab) * 4u;
-        const bool in0 = c0 < p.C, in1 = c0 + 16 < p.C;
+        constexpr int kSecond = kSplit ? 16 : 4;      // channels from the first to the second piece of a group (float source)
+        const int c0 = ch * kSlab + ag * (kSplit ? 4 : 8);
+        const unsigned delta = (unsigned)((iy * p.W + ix) * p.C + ch * kSlab) * ES;
+        const bool in0 = c0 < p.C, in1 = c0 + kSecond < p.C;
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
             ra[q][0] = f4{0.f, 0.f, 0.f, 0.f}; ra[q][1] = f4{0.f, 0.f, 0.f, 0.f};
             const bool ok = (tapmask[q] >> tap) & 1u;
             const unsigned o = aoff[q] + delta;
             if (ok && in0) ra[q][0] = *reinterpret_cast<const f4*>(abase + o);
-            if (ok && in1) ra[q][1] = *reinterpret_cast<const f4*>(abase + o + 64u);
+            if (ES == 4 && ok && in1) ra[q][1] = *reinterpret_cast<const f4*>(abase + o + kSecond * 4u);
         }
         const int wt = (cg.wy0 + iy * p.wst) * p.S + cg.wx0 + ix * p.wst;
         const unsigned kb = (unsigned)((wt * cs + ch) * kSlabBytes);
@@ -185,17 +217,23 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     auto store_weights = [&]() {
 #pragma unroll
         for (int q = 0; q < NQB; ++q)
-            if (BN * 12 % NT == 0 || tid + q * NT < BN * 12) *reinterpret_cast<u4*>(sBc + sb_st[q]) = rb[q];
+            if (BN * CH % NT == 0 || tid + q * NT < BN * CH) *reinterpret_cast<u4*>(sBc + sb_st[q]) = rb[q];
     };
     auto store_tiles = [&]() {
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
-            bf16x4 h0, m0_, l0, h1, m1, l1;
-            split3(ra[q][0], h0, m0_, l0);
-            split3(ra[q][1], h1, m1, l1);
-            *reinterpret_cast<u4*>(sAc + sa_st[q]) = join8(h0, h1);
-            *reinterpret_cast<u4*>(sAc + sa_st[q] + 64) = join8(m0_, m1);
-            *reinterpret_cast<u4*>(sAc + sa_st[q] + 128) = join8(l0, l1);
+            if constexpr (kSplit) {
+                bf16x4 h0, m0_, l0, h1, m1, l1;
+                split3(ra[q][0], h0, m0_, l0);
+                split3(ra[q][1], h1, m1, l1);
+                *reinterpret_cast<u4*>(sAc + sa_st[q]) = join8(h0, h1);
+                *reinterpret_cast<u4*>(sAc + sa_st[q] + 64) = join8(m0_, m1);
+                *reinterpret_cast<u4*>(sAc + sa_st[q] + 128) = join8(l0, l1);
+            } else if constexpr (kRound) {
+                *reinterpret_cast<u4*>(sAc + sa_st[q]) = round8(ra[q][0], ra[q][1]);
+            } else {
+                *reinterpret_cast<f4*>(sAc + sa_st[q]) = ra[q][0];
+            }
         }
         store_weights();
     };
@@ -211,25 +249,28 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     };
     auto compute = [&]() {
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 a[TM][3], b[TN][3];
+        for (int ks = 0; ks < kSlab / 16; ++ks) {
+            constexpr int PL = Slab<T>::planes;
+            bf16x8 a[TM][PL], b[TN][PL];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int s = 0; s < 3; ++s) a[i][s] = *reinterpret_cast<const bf16x8*>(sAc + a_rd + i * 32 * kRow + s * 64 + ks * 32);
+                for (int s = 0; s < PL; ++s) a[i][s] = *reinterpret_cast<const bf16x8*>(sAc + a_rd + i * 32 * kRow + s * 64 + ks * 32);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int s = 0; s < 3; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(sBc + b_rd + j * 32 * kRow + s * 64 + ks * 32);
+                for (int s = 0; s < PL; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(sBc + b_rd + j * 32 * kRow + s * 64 + ks * 32);
             // operands swapped: the accumulator holds the transposed tile.  Small products in ascending size.
-            constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
+            if constexpr (kSplit) {
+                constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
 #pragma unroll
-            for (int t = 0; t < 5; ++t)
+                for (int t = 0; t < 5; ++t)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                    for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][SB[t]], a[i][SA[t]], low[i][j], 0, 0, 0);
+                        for (int j = 0; j < TN; ++j)
+                            low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][SB[t]], a[i][SA[t]], low[i][j], 0, 0, 0);
+            }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -251,6 +292,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
         if (mine + KG < nslab) { advance(KG); load_tiles(); }
         if (mine < nslab) compute();
     }
+    if constexpr (kSplit) {
     float bad = 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -272,7 +314,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
                 advance(KG);
 #pragma unroll
                 for (int q = 0; q < NQA; ++q) {
-                    char* const dst = sAc + (sa_st[q] - (tid & 3) * 16) + (tid & 3) * 32;
+                    char* const dst = sAc + sa_st[q] + ag * 16;
                     *reinterpret_cast<f4*>(dst) = ra[q][0];
                     *reinterpret_cast<f4*>(dst + 16) = ra[q][1];
                 }
@@ -299,7 +341,10 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
         }
         __syncthreads();
     }
-    if (KG > 1) {                                     // (the barrier of the test above: nobody reads a slab any more)
+    } else {
+        __syncthreads();                              // nobody reads a slab any more
+    }
+    if (KG > 1) {                                     // (behind the barriers above nobody reads a slab any more)
         float* const part = reinterpret_cast<float*>(smem);
         static_assert((size_t)(KG - 1) * NW * TM * TN * 16 * 64 * 4 <= (size_t)KG * GROUP, "the groups' sums do not fit the LDS of the K loop");
         if (kg > 0) {
@@ -333,9 +378,9 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
 #pragma unroll
         for (int k = 0; k < 16; ++k) { ss[j][k] = 0.f; qq[j][k] = 0.f; }
     if (kg == 0) {
-        float* obase = p.out + (long long)rep * p.out_rep;
+        T* const obase = reinterpret_cast<T*>(p.out + (long long)rep * p.out_rep);
         const float* bias = (EPI == 0 && p.bias) ? p.bias + (long long)rep * p.bias_rep : nullptr;
-        const float* mask = (EPI == 1 && p.mask) ? p.mask + (long long)rep * p.mask_rep : nullptr;
+        const T* mask = (EPI == 1 && p.mask) ? reinterpret_cast<const T*>(p.mask + (long long)rep * p.mask_rep) : nullptr;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int mm = m0 + wm * (BMT / WGM) + i * 32 + (lane & 31);
@@ -359,13 +404,13 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
                         if (p.relu) { v[0] = fmaxf(v[0], 0.f); v[1] = fmaxf(v[1], 0.f); v[2] = fmaxf(v[2], 0.f); v[3] = fmaxf(v[3], 0.f); }
                     } else {
                         if (mask) {
-                            const f4 mk = *reinterpret_cast<const f4*>(mask + o);
+                            const f4 mk = load4(mask + o);
 #pragma unroll
                             for (int e = 0; e < 4; ++e) if (!(mk[e] > 0.f)) v[e] = 0.f;
                         }
-                        if (p.accumulate) v += *reinterpret_cast<const f4*>(obase + o);
+                        if (p.accumulate) v += load4(obase + o);
                     }
-                    *reinterpret_cast<f4*>(obase + o) = v;
+                    store4(obase + o, v);
                     if (stats) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { const float f = v[e] - sh[e]; ss[j][4 * g + e] += f; qq[j][4 * g + e] += f * f; }
@@ -392,12 +437,12 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
 // 256 bytes plus or minus 64, so that the four rows a transposing read touches land in distinct banks.  Pixels advance by
 // 32 per slab with carries instead of divisions, and a thread's tap is fixed, so a slab costs a few additions per
 // address.  The bias gradient is summed in fp32 by the tiles of the first row of tiles, from the dY values they stage anyway.
-template <int COLS> constexpr int kPixelRow = COLS == 32 ? 320 : COLS * 6 + 64;
+template <typename T, int COLS> constexpr int kPixelRow = COLS == 32 ? (Slab<T>::planes == 3 ? 320 : 192) : COLS * 2 * Slab<T>::planes + 64;
 
 // Each wave passes its 32 x 32 blocks through a private piece of LDS and takes them back with eight lanes per row, so that
 // global accesses cover whole lines.  With w set the block is the complete gradient and the update is applied instead.
 constexpr int kStagePitch = 36;                               // floats per staged row
-__device__ __forceinline__ void put_gradient(const f4& v, long long o, const SplitWgradParams& p, float* out, float* w, float* buf)
+__device__ __forceinline__ void put_gradient(const f4& v, long long o, const GeneralWgradParams& p, float* out, float* w, float* buf)
 {
     if (!w) { *reinterpret_cast<f4*>(out + o) = v; return; }
     f4 d = v;
@@ -405,19 +450,22 @@ __device__ __forceinline__ void put_gradient(const f4& v, long long o, const Spl
     *reinterpret_cast<f4*>(w + o) = *reinterpret_cast<const f4*>(w + o) - d * p.lr;
 }
 
-template <int BMT, int BN, int WGM, int WGN>
-__global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
+template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN>
+__global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParams p)
 {
     static_assert(WGM * WGN == 4, "four waves");
     constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32, BK = 32;
-    constexpr int PA = kPixelRow<BMT>, PB = kPixelRow<BN>;
-    constexpr int AG = BMT / 4, BG = BN / 4;                  // groups of four channels per pixel
-    constexpr int AR = 256 / AG, BR = 256 / BG;               // pixels the threads cover per pass
-    constexpr int NQA = BK / AR, NQB = BK / BR;
-    static_assert(NQA >= 1 && NQB >= 1 && TM >= 1 && TN >= 1, "tile does not fit the thread count");
+    constexpr bool kSplit = std::is_same<T, float>::value, kRound = !kSplit && std::is_same<SRC, float>::value;
+    constexpr unsigned ES = sizeof(SRC);
+    constexpr int PA = kPixelRow<T, BMT>, PB = kPixelRow<T, BN>;
+    constexpr int GS = 16 / sizeof(T);                        // channels per group: 16 bytes
+    constexpr int AG = BMT / GS, BG = BN / GS;                // groups per pixel
+    constexpr int AR = 256 / AG, BR = 256 / BG;               // pixels the threads cover per pass (more than a slab has: the rest idles)
+    constexpr int NQA = (BK + AR - 1) / AR, NQB = (BK + BR - 1) / BR;
+    static_assert(TM >= 1 && TN >= 1 && 256 % AG == 0 && 256 % BG == 0, "tile does not fit the thread count");
     constexpr unsigned A_BUF = BK * PA, B_BUF = BK * PB;
-    static_assert(A_BUF + B_BUF >= 4 * 32 * kStagePitch * 4 && A_BUF + B_BUF >= BR * BN * 4, "epilogue staging does not fit the LDS of the K loop");
-    __shared__ __attribute__((aligned(16))) char smem[A_BUF + B_BUF];
+    constexpr unsigned STAGE = 4 * 32 * kStagePitch * 4 > BR * BN * 4 ? 4 * 32 * kStagePitch * 4 : BR * BN * 4;
+    __shared__ __attribute__((aligned(16))) char smem[A_BUF + B_BUF > STAGE ? A_BUF + B_BUF : STAGE];
     char* const sA = smem;                                    // [BK][PA]
     char* const sB = smem + A_BUF;                            // [BK][PB]
 
@@ -443,21 +491,21 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
     }
     const char* dbase = (const char*)(p.dy + (long long)rep * p.dy_rep);
 
-    // A slots: channels am..am+3 of one tap, pixels arow + AR * q;  B slots: channels bn..bn+3, pixels brow + BR * q
-    const int am = m0 + (tid % AG) * 4, arow = tid / AG;
-    const int bn = n0 + (tid % BG) * 4, brow = tid / BG;
-    const bool a_ok = am < mw, b_ok = bn < p.N;
+    // A slots: channels am..am+GS-1 of one tap, pixels arow + AR * q;  B slots: channels bn.., pixels brow + BR * q
+    const int am = m0 + (tid % AG) * GS, arow = tid / AG;
+    const int bn = n0 + (tid % BG) * GS, brow = tid / BG;
+    const bool a_ok = am < mw && arow < BK, b_ok = bn < p.N && brow < BK;
     const int atap = am / p.C, aci = am - atap * p.C;
     const int ady = atap / p.S - p.pad, adx = atap % p.S - p.pad;
     // output rows y with a source row inside the image: ylo <= y < ylo + yn (likewise x)
     const int ylo = ady < 0 ? (-ady + p.stride - 1) / p.stride : 0, xlo = adx < 0 ? (-adx + p.stride - 1) / p.stride : 0;
     const int yn = p.H - 1 - ady >= 0 ? max(0, (p.H - 1 - ady) / p.stride + 1 - ylo) : 0;
     const int xn = p.W - 1 - adx >= 0 ? max(0, (p.W - 1 - adx) / p.stride + 1 - xlo) : 0;
-    const unsigned a_shift = (unsigned)((ady * p.W + adx) * p.C + aci) * 4u;
+    const unsigned a_shift = (unsigned)((ady * p.W + adx) * p.C + aci) * ES;
     // 32 pixels further: x += dx, y += dyy, image += db, in source bytes step (carries adjust by cx, cy)
     const int hw = p.Ho * p.Wo;
     const int dx = BK % p.Wo, dyy = (BK / p.Wo) % p.Ho, db = BK / hw;
-    const unsigned pc = (unsigned)p.C * 4u, st = (unsigned)p.stride;
+    const unsigned pc = (unsigned)p.C * ES, st = (unsigned)p.stride;
     const unsigned cx = (st * (unsigned)p.W - (unsigned)p.Wo * st) * pc, cy = ((unsigned)p.H - (unsigned)p.Ho * st) * (unsigned)p.W * pc;
     const unsigned step = (((unsigned)db * (unsigned)p.H + (unsigned)dyy * st) * (unsigned)p.W + (unsigned)dx * st) * pc;
     int px[NQA], py[NQA]; unsigned poff[NQA];
@@ -483,7 +531,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
             while (k < kend && !(p.posmask[k / p.B] & tile_tapbits)) k += BK;
         return k;
     };
-    f4 ra[NQA], rb[NQB], bsum = {0.f, 0.f, 0.f, 0.f};
+    f4 ra[NQA], ra2[kRound ? NQA : 1], rb[NQB];              // (bf16 tensors: eight elements in the 16 bytes)
+    float bsum[GS] = {};
     auto load_tiles = [&](int k0) {
         int bbase = 0, pos = 0;
         if (p.perm) { const int ps = k0 / p.B; bbase = k0 - ps * p.B; pos = p.perm[ps]; }
@@ -495,13 +544,19 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
                 const int kr = arow + AR * q;
                 ra[q] = f4{0.f, 0.f, 0.f, 0.f};
                 if (in && k0 + kr < kend) ra[q] = *reinterpret_cast<const f4*>(xbase + ((unsigned)((bbase + kr) * hw + pos) * pc + a_shift));
+                if constexpr (kRound) ra2[q] = f4{0.f, 0.f, 0.f, 0.f};            // (the data set has no position table)
             }
         } else {
 #pragma unroll
             for (int q = 0; q < NQA; ++q) {
                 ra[q] = f4{0.f, 0.f, 0.f, 0.f};
                 const bool in = a_ok && (unsigned)(py[q] - ylo) < (unsigned)yn && (unsigned)(px[q] - xlo) < (unsigned)xn;
-                if (in && k0 + arow + AR * q < kend) ra[q] = *reinterpret_cast<const f4*>(xbase + poff[q]);
+                const bool on = in && k0 + arow + AR * q < kend;
+                if (on) ra[q] = *reinterpret_cast<const f4*>(xbase + poff[q]);
+                if constexpr (kRound) {
+                    ra2[q] = f4{0.f, 0.f, 0.f, 0.f};
+                    if (on) ra2[q] = *reinterpret_cast<const f4*>(xbase + poff[q] + 16u);
+                }
                 px[q] += dx; py[q] += dyy; poff[q] += step;
                 if (px[q] >= p.Wo) { px[q] -= p.Wo; py[q] += 1; poff[q] += cx; }
                 if (py[q] >= p.Ho) { py[q] -= p.Ho; poff[q] += cy; }
@@ -512,25 +567,42 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
             const int kr = brow + BR * q;
             const unsigned pix = p.perm ? (unsigned)((bbase + kr) * hw + pos) : (unsigned)(k0 + kr);
             rb[q] = f4{0.f, 0.f, 0.f, 0.f};
-            if (b_ok && k0 + kr < kend) rb[q] = *reinterpret_cast<const f4*>(dbase + (pix * (unsigned)p.N + (unsigned)bn) * 4u);
+            if (b_ok && k0 + kr < kend) rb[q] = *reinterpret_cast<const f4*>(dbase + (pix * (unsigned)p.N + (unsigned)bn) * (unsigned)sizeof(T));
         }
     };
-    const unsigned sa_st = (unsigned)(arow * PA + (tid % AG) * 8), sb_st = (unsigned)(brow * PB + (tid % BG) * 8);
+    const unsigned sa_st = (unsigned)(arow * PA + (tid % AG) * GS * 2), sb_st = (unsigned)(brow * PB + (tid % BG) * GS * 2);
     auto store_tiles = [&]() {
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
-            bf16x4 h, m, l;
-            split3(ra[q], h, m, l);
             char* const o = sA + sa_st + AR * q * PA;
-            *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BMT * 2) = m; *reinterpret_cast<bf16x4*>(o + BMT * 4) = l;
+            if constexpr (kSplit) {
+                bf16x4 h, m, l;
+                split3(ra[q], h, m, l);
+                *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BMT * 2) = m; *reinterpret_cast<bf16x4*>(o + BMT * 4) = l;
+            } else if (AR <= BK || arow < BK) {
+                if constexpr (kRound) *reinterpret_cast<u4*>(o) = round8(ra[q], ra2[q]);
+                else *reinterpret_cast<f4*>(o) = ra[q];
+            }
         }
 #pragma unroll
         for (int q = 0; q < NQB; ++q) {
-            bf16x4 h, m, l;
-            split3(rb[q], h, m, l);
             char* const o = sB + sb_st + BR * q * PB;
-            *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BN * 2) = m; *reinterpret_cast<bf16x4*>(o + BN * 4) = l;
-            if (with_bias) bsum += rb[q];
+            if constexpr (kSplit) {
+                bf16x4 h, m, l;
+                split3(rb[q], h, m, l);
+                *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BN * 2) = m; *reinterpret_cast<bf16x4*>(o + BN * 4) = l;
+                if (with_bias) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bsum[e] += rb[q][e];
+                }
+            } else if (BR <= BK || brow < BK) {
+                *reinterpret_cast<f4*>(o) = rb[q];
+                if (with_bias) {
+                    const bf16x8 v = __builtin_bit_cast(bf16x8, rb[q]);
+#pragma unroll
+                    for (int e = 0; e < GS; ++e) bsum[e] += (float)v[e];
+                }
+            }
         }
     };
     // operand reads (see lds_read_tr8): lane L of a 16-lane group points at pixel L / 4, channels 4 * (L % 4)
@@ -559,23 +631,26 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
         if (k0 < kend) load_tiles(k0);
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
-            bf16x8 a[TM][3], b[TN][3];
+            constexpr int PL = Slab<T>::planes;
+            bf16x8 a[TM][PL], b[TN][PL];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int s = 0; s < 3; ++s) a[i][s] = lds_read_tr8(sA, a_rd + ks * 16 * PA + s * BMT * 2 + i * 64, PA);
+                for (int s = 0; s < PL; ++s) a[i][s] = lds_read_tr8(sA, a_rd + ks * 16 * PA + s * BMT * 2 + i * 64, PA);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int s = 0; s < 3; ++s) b[j][s] = lds_read_tr8(sB, b_rd + ks * 16 * PB + s * BN * 2 + j * 64, PB);
-            constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
+                for (int s = 0; s < PL; ++s) b[j][s] = lds_read_tr8(sB, b_rd + ks * 16 * PB + s * BN * 2 + j * 64, PB);
+            if constexpr (kSplit) {
+                constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
 #pragma unroll
-            for (int t = 0; t < 5; ++t)
+                for (int t = 0; t < 5; ++t)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                    for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][SB[t]], a[i][SA[t]], low[i][j], 0, 0, 0);
+                        for (int j = 0; j < TN; ++j)
+                            low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][SB[t]], a[i][SA[t]], low[i][j], 0, 0, 0);
+            }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -583,6 +658,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][0], a[i][0], acc[i][j], 0, 0, 0);
         }
     }
+    if constexpr (kSplit) {
     float bad = 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -617,6 +693,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
         }
         __syncthreads();
     }
+    } else {
+        __syncthreads();                                      // nobody reads a slab any more
+    }
 
     // ---- epilogue (the barrier above: nobody reads a slab any more) ----
     float* const out = (p.splits > 1) ? p.out + (long long)slot * p.out_rep + (long long)split * p.out_split
@@ -649,20 +728,24 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradParams p)
     if (with_bias) {                                          // join the partial sums of the threads that share a channel group, pixels ascending
         __syncthreads();
         float* const red = reinterpret_cast<float*>(smem);    // [BR][BN]
-        *reinterpret_cast<f4*>(red + brow * BN + (tid % BG) * 4) = bsum;
+#pragma unroll
+        for (int e = 0; e < GS; e += 4) *reinterpret_cast<f4*>(red + brow * BN + (tid % BG) * GS + e) = f4{bsum[e], bsum[e + 1], bsum[e + 2], bsum[e + 3]};
         __syncthreads();
         if (brow == 0 && b_ok) {
-            f4 v = bsum;
 #pragma unroll
-            for (int r = 1; r < BR; ++r) v += *reinterpret_cast<const f4*>(red + r * BN + (tid % BG) * 4);
-            put_gradient(v, (long long)mw * p.N + bn, p, out, w, buf);
+            for (int e = 0; e < GS; e += 4) {
+                f4 v = *reinterpret_cast<const f4*>(red + (tid % BG) * GS + e);
+#pragma unroll
+                for (int r = 1; r < (BR < BK ? BR : BK); ++r) v += *reinterpret_cast<const f4*>(red + r * BN + (tid % BG) * GS + e);
+                put_gradient(v, (long long)mw * p.N + bn + e, p, out, w, buf);
+            }
         }
     }
 }
 
 // fp32 master W[tap][ci][co] -> Wf[co][tap][ci] and Wb[ci][T-1-tap][co] as described at the top.  A workgroup handles one
-// tap and a 64 x 64 (ci, co) tile; each thread forms the three 16-byte groups of eight positions.  Bound by memory: 4 bytes
-// read and 12 written per weight.  A weight whose bf16 rounding overflows is cut instead, and one that is not finite
+// tap and a 64 x 64 (ci, co) tile; each thread forms 16-byte groups of eight positions.  Bound by memory: 4 bytes read and
+// 12 (bf16: 4) written per weight.  A weight whose bf16 rounding overflows is cut instead, and one that is not finite
 // has zero lower parts, so that the three parts always add up to the weight.
 __device__ __forceinline__ void split_weight(float x, __bf16& h, __bf16& m, __bf16& l)
 {
@@ -673,8 +756,11 @@ __device__ __forceinline__ void split_weight(float x, __bf16& h, __bf16& m, __bf
     m = (__bf16)r;
     l = (__bf16)(r - (float)m);
 }
-__global__ __launch_bounds__(256) void weight_split_kernel(WeightSplitParams p)
+template <typename T>
+__global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
 {
+    constexpr bool kSplit = std::is_same<T, float>::value;
+    constexpr int kSlab = Slab<T>::channels, kSlabBytes = Slab<T>::bytes, GR = Slab<T>::groups;
     __shared__ float tile[64][65];                            // [ci][co], zero outside the layer
     const int rep = p.order[blockIdx.z];
     const int tap = blockIdx.y % p.taps, co0 = (blockIdx.y / p.taps) * 64, ci0 = blockIdx.x * 64;
@@ -696,108 +782,123 @@ __global__ __launch_bounds__(256) void weight_split_kernel(WeightSplitParams p)
         char* const base = (char*)(dst + (long long)rep * p.wcopy_rep);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int i = threadIdx.x + q * 256, g = i & 3, sl = (i >> 2) & 1, row = i >> 3;
+            const int i = threadIdx.x + q * 256, g = i % GR, sl = (i / GR) % (64 / kSlab), row = i >> 3;
             const int slab = k0 / kSlab + sl;
             if (row0 + row >= rows || slab >= cs) continue;
+            char* const o = base + ((long long)(row0 + row) * p.taps * cs + t * cs + slab) * kSlabBytes + g * 16;
             bf16x8 h, m, l;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int k = sl * kSlab + (e >> 2) * 16 + g * 4 + (e & 3);
+                const int k = kSplit ? sl * kSlab + (e >> 2) * 16 + g * 4 + (e & 3) : g * 8 + e;
+                const float v = which ? tile[row][k] : tile[k][row];
                 __bf16 a, b, c;
-                split_weight(which ? tile[row][k] : tile[k][row], a, b, c);
-                h[e] = a; m[e] = b; l[e] = c;
+                if (kSplit) { split_weight(v, a, b, c); h[e] = a; m[e] = b; l[e] = c; }
+                else h[e] = (__bf16)v;
             }
-            char* const o = base + ((long long)(row0 + row) * p.taps * cs + t * cs + slab) * kSlabBytes + g * 16;
             *reinterpret_cast<bf16x8*>(o) = h;
-            *reinterpret_cast<bf16x8*>(o + 64) = m;
-            *reinterpret_cast<bf16x8*>(o + 128) = l;
+            if (kSplit) { *reinterpret_cast<bf16x8*>(o + 64) = m; *reinterpret_cast<bf16x8*>(o + 128) = l; }
         }
     }
 }
 
-template <int BMT, int BN, int WGM, int WGN, int KG>
-hipError_t launch_t(SplitConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows)
+template <typename T, typename SRC, int EPI, int BMT, int BN, int WGM, int WGN, int KG>
+hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)
 {
-    constexpr size_t loop_lds = (size_t)KG * (BMT + BN) * kRow, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
+    constexpr size_t loop_lds = (size_t)KG * (BMT + BN) * Slab<T>::row, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
     constexpr size_t lds = loop_lds > stat_lds ? loop_lds : stat_lds;
     if (lds > 65536) {
-        static const bool ok =
-            hipFuncSetAttribute((const void*)conv_split_kernel<BMT, BN, WGM, WGN, KG, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
-            hipFuncSetAttribute((const void*)conv_split_kernel<BMT, BN, WGM, WGN, KG, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, SRC, BMT, BN, WGM, WGN, KG, EPI>,
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
         if (!ok) return hipErrorInvalidValue;
     }
     if (stat_rows) *stat_rows = BMT;
     const int rows0 = p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);     // largest class
     p.tiles_m = (rows0 + BMT - 1) / BMT;
     const dim3 grid(die_grid((long long)p.tiles_m * ((p.N + BN - 1) / BN) * p.classes * n_active)), block(WGM * WGN * KG * 64);
-    if (epi == 0) hipLaunchKernelGGL((conv_split_kernel<BMT, BN, WGM, WGN, KG, 0>), grid, block, lds, s, p);
-    else hipLaunchKernelGGL((conv_split_kernel<BMT, BN, WGM, WGN, KG, 1>), grid, block, lds, s, p);
+    hipLaunchKernelGGL((conv_general_kernel<T, SRC, BMT, BN, WGM, WGN, KG, EPI>), grid, block, lds, s, p);
+    return hipGetLastError();
+}
+
+template <typename T, typename SRC, int EPI>
+hipError_t launch_conv(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)
+{
+    const long long rows0 = (long long)p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);
+    const long long groups = (long long)p.classes * n_active;
+    const long long t64 = (rows0 + 63) / 64 * ((p.N + 63) / 64) * groups, t128 = (rows0 + 127) / 128 * ((p.N + 127) / 128) * groups;
+    // How many workgroups a tile size gives decides: a workgroup's time is the length of its K loop, so a launch that cannot
+    // fill 256 compute units takes smaller tiles and several groups of waves along K.  Measured with floats (us; 512 x 512
+    // channels, 3 x 3, batch 64; 2 x 2 images with 1 replica, 4 x 4 with 1, 4 x 4 with 4, 8 x 8 x 256 channels with 4, 4 x 4 with 16):
+    //   32 x 32, 8 groups:   43    85   319   373  1368         64 x 64, 1 group:    131   133   148   144   526
+    //   64 x 64, 4 groups:   73    76   162   179   637         128 x 128, 2 groups: 216   218   223   131   504
+    //   64 x 64, 2 groups:   91    94   139   147   536         128 x 128, 1 group:  262   267   272   149   448
+    const bool large = p.tile_hint == 1;
+    if (!large && t64 <= 48) return launch_t<T, SRC, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
+    if (!large && t64 <= 256) return launch_t<T, SRC, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
+    if (!large && t64 <= 640) return launch_t<T, SRC, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
+    if (p.N <= 32) return launch_t<T, SRC, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
+    if (p.N > 64) {
+        if (large || t128 > 256) return launch_t<T, SRC, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
+        if (t64 > 880) return launch_t<T, SRC, EPI, 128, 128, 2, 2, 2>(p, n_active, s, stat_rows);
+    }
+    if (p.N <= 64 && (large || t64 > 2048)) return launch_t<T, SRC, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
+    return launch_t<T, SRC, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
+}
+
+template <typename T, typename SRC>
+hipError_t launch_wgrad(const GeneralWgradParams& p, int n_active, hipStream_t s)
+{
+    const dim3 grid(die_grid((long long)wgrad_general_tiles(p.R * p.S * p.C, p.N, n_active) * p.splits * n_active)), block(256);
+    if (p.N > 64) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 128, 2, 2>), grid, block, 0, s, p);
+    else if (p.N > 32) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 64, 4, 1>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 32, 4, 1>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
 }  // namespace
 
-long long split_weight_units(int rows, int taps, int channels)
+long long weight_copy_units(int bf16, int rows, int taps, int channels)
 {
-    return (long long)rows * taps * ((channels + kSlab - 1) / kSlab) * (kSlabBytes / 2);
+    const int per = bf16 ? Slab<__bf16>::channels : Slab<float>::channels, bytes = bf16 ? Slab<__bf16>::bytes : Slab<float>::bytes;
+    return (long long)rows * taps * ((channels + per - 1) / per) * (bytes / 2);
 }
 
-hipError_t launch_conv_split(const SplitConvParams& p0, int epi, int n_active, hipStream_t s, int* stat_rows)
+hipError_t launch_conv_general(const GeneralConvParams& p0, int epi, int n_active, hipStream_t s, int* stat_rows)
 {
     if (n_active < 1) return hipSuccess;
-    SplitConvParams p = p0;
+    GeneralConvParams p = p0;
     p.n_active = n_active;
-    if (p.C % 4 != 0 || p.N % 4 != 0 || p.R * p.S > 32 || (p.perm && p.classes != 1)) return hipErrorInvalidValue;
-    const long long rows0 = (long long)p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);
-    const long long groups = (long long)p.classes * n_active;
-    const long long t64 = (rows0 + 63) / 64 * ((p.N + 63) / 64) * groups, t128 = (rows0 + 127) / 128 * ((p.N + 127) / 128) * groups;
-    // How many workgroups a tile size gives decides: a workgroup's time is the length of its K loop, so a launch that cannot
-    // fill 256 compute units takes smaller tiles and several groups of waves along K.  Measured (us; 512 x 512 channels,
-    // 3 x 3, batch 64; 2 x 2 images with 1 replica, 4 x 4 with 1, 4 x 4 with 4, 8 x 8 x 256 channels with 4, 4 x 4 with 16):
-    //   32 x 32, 8 groups:   43    85   319   373  1368         64 x 64, 1 group:    131   133   148   144   526
-    //   64 x 64, 4 groups:   73    76   162   179   637         128 x 128, 2 groups: 216   218   223   131   504
-    //   64 x 64, 2 groups:   91    94   139   147   536         128 x 128, 1 group:  262   267   272   149   448
-    const bool large = p.tile_hint == 1;
-    if (large && p.N > 64) return launch_t<128, 128, 2, 2, 1>(p, epi, n_active, s, stat_rows);
-    if (large && p.N > 32) return launch_t<128, 64, 4, 1, 1>(p, epi, n_active, s, stat_rows);
-    if (large) return launch_t<128, 32, 4, 1, 1>(p, epi, n_active, s, stat_rows);
-    if (t64 <= 48) return launch_t<32, 32, 1, 1, 8>(p, epi, n_active, s, stat_rows);
-    if (t64 <= 256) return launch_t<64, 64, 2, 2, 4>(p, epi, n_active, s, stat_rows);
-    if (t64 <= 640) return launch_t<64, 64, 2, 2, 2>(p, epi, n_active, s, stat_rows);
-    if (p.N <= 32) return launch_t<128, 32, 4, 1, 1>(p, epi, n_active, s, stat_rows);
-    if (p.N > 64) {
-        if (t128 > 256) return launch_t<128, 128, 2, 2, 1>(p, epi, n_active, s, stat_rows);
-        if (t64 > 880) return launch_t<128, 128, 2, 2, 2>(p, epi, n_active, s, stat_rows);
-    }
-    if (p.N <= 64 && t64 > 2048) return launch_t<128, 64, 4, 1, 1>(p, epi, n_active, s, stat_rows);
-    return launch_t<64, 64, 2, 2, 1>(p, epi, n_active, s, stat_rows);
+    const int unit = p.bf16 ? 8 : 4;
+    if (p.C % unit != 0 || p.N % 4 != 0 || p.R * p.S > 32 || (p.perm && p.classes != 1)) return hipErrorInvalidValue;
+    if (!p.bf16) return epi == 0 ? launch_conv<float, float, 0>(p, n_active, s, stat_rows) : launch_conv<float, float, 1>(p, n_active, s, stat_rows);
+    if (epi == 0 && p.cursor) return launch_conv<__bf16, float, 0>(p, n_active, s, stat_rows);
+    return epi == 0 ? launch_conv<__bf16, __bf16, 0>(p, n_active, s, stat_rows) : launch_conv<__bf16, __bf16, 1>(p, n_active, s, stat_rows);
 }
 
-int split_wgrad_tiles(int rows, int N)
+int wgrad_general_tiles(int rows, int N, int n_active)
 {
+    (void)n_active;
     const int bn = N > 64 ? 128 : N > 32 ? 64 : 32;
     return (rows + 127) / 128 * ((N + bn - 1) / bn);
 }
 
-hipError_t launch_wgrad_split(const SplitWgradParams& p0, int n_active, hipStream_t s)
+hipError_t launch_wgrad_general(const GeneralWgradParams& p0, int n_active, hipStream_t s)
 {
     if (n_active < 1) return hipSuccess;
-    SplitWgradParams p = p0;
+    GeneralWgradParams p = p0;
     p.n_active = n_active;
-    if (p.C % 4 != 0 || p.N % 4 != 0 || (p.splits > 1 && p.kchunk % 32 != 0)) return hipErrorInvalidValue;
-    if (p.perm && (p.B % 32 != 0 || p.stride != 1 || p.R * p.S > 32)) return hipErrorInvalidValue;
-    const dim3 grid(die_grid((long long)split_wgrad_tiles(p.R * p.S * p.C, p.N) * p.splits * n_active)), block(256);
-    if (p.N > 64) hipLaunchKernelGGL((wgrad_split_kernel<128, 128, 2, 2>), grid, block, 0, s, p);
-    else if (p.N > 32) hipLaunchKernelGGL((wgrad_split_kernel<128, 64, 4, 1>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((wgrad_split_kernel<128, 32, 4, 1>), grid, block, 0, s, p);
-    return hipGetLastError();
+    const int unit = p.bf16 ? 8 : 4;
+    if (p.C % unit != 0 || p.N % unit != 0 || (p.splits > 1 && p.kchunk % 32 != 0)) return hipErrorInvalidValue;
+    if (p.perm && (p.B % 32 != 0 || p.stride != 1 || p.R * p.S > 32 || p.cursor)) return hipErrorInvalidValue;
+    if (!p.bf16) return launch_wgrad<float, float>(p, n_active, s);
+    return p.cursor ? launch_wgrad<__bf16, float>(p, n_active, s) : launch_wgrad<__bf16, __bf16>(p, n_active, s);
 }
 
-hipError_t launch_weight_split(const WeightSplitParams& p, int n_active, hipStream_t s)
+hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s)
 {
     if (n_active < 1) return hipSuccess;
     const dim3 grid((unsigned)((p.C + 63) / 64), (unsigned)(p.taps * ((p.N + 63) / 64)), (unsigned)n_active), block(256);
-    hipLaunchKernelGGL(weight_split_kernel, grid, block, 0, s, p);
+    if (p.bf16) hipLaunchKernelGGL(weight_copy_kernel<__bf16>, grid, block, 0, s, p);
+    else hipLaunchKernelGGL(weight_copy_kernel<float>, grid, block, 0, s, p);
     return hipGetLastError();
 }
 

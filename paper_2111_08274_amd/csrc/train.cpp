@@ -26,7 +26,7 @@ public:
     int64_t shared_floats = 0;
     int64_t bn_off = 0;                   // per-chunk partial sums of the batch-norm reductions (their own region: weight
                                           // gradients may run beside them on the side stream)
-    std::vector<int> splits;              // per layer: split-K factor of the weight gradient (split layers: chosen per launch)
+    std::vector<int> splits;              // per layer: split-K factor of the weight gradient (general layers: chosen per launch)
     std::vector<int> bn_chunks;           // per layer
     std::vector<char> grad_written;       // scratch for the backward pass
     // ReLU fusion: a ReLU that is the only consumer of a conv / dense / BN / add output is folded into that layer's
@@ -41,7 +41,7 @@ public:
     // BN kernels: forward writes the pooled tensor as well, backward forms the full-resolution gradient on the fly from
     // the pooled gradient.  The pool layer itself issues nothing.
     std::vector<int> pool_of;             // per layer: index of the folded pool layer, or -1
-    // Statistics fusion: a lean (or split) convolution whose output feeds a batch norm only leaves the per-channel
+    // Statistics fusion: a lean or general convolution whose output feeds a batch norm only leaves the per-channel
     // sums of its output in the BN partial region, and that BN's forward skips its own sums pass.
     std::vector<int> stat_for;            // per layer: the BN layer fed by this convolution's statistics, or -1
     std::vector<int> stat_from;           // per layer (BN): the convolution that supplies them, or -1
@@ -54,7 +54,7 @@ public:
     std::vector<int64_t> bstat_rep;       // per layer (BN): floats per replica slot of those entries
     // bf16 configuration: regular convolution layers keep two bf16 weight matrices (forward / data-gradient order)
     std::vector<char> fast;               // per layer: the lean bf16 kernels apply
-    std::vector<char> split32;            // per layer (fp32 configuration): the kernels on split floats apply (conv_f32_split.hip)
+    std::vector<char> general;            // per layer: not lean, but the kernels of conv_general.hip apply
     std::vector<int64_t> wf_off, wb_off;  // per layer: offsets (2-byte units) inside one replica's block of weight copies, or -1
     int64_t wbf_rep = 0;                  // bf16 elements per replica
     int64_t wbf_off = 0;                  // start of the bf16 weight region inside `work` (floats)
@@ -88,7 +88,7 @@ struct Layout {
     std::vector<int64_t> act_off, grad_off, saved_off;
     std::vector<int> splits, bn_chunks;
     int64_t rep_block = 0, shared_floats = 0, bn_floats = 0;
-    std::vector<char> fast, split32;
+    std::vector<char> fast, general;
     std::vector<int64_t> wf_off, wb_off;       // in 2-byte units inside one replica's block of weight copies
     int64_t wbf_rep = 0;
     std::vector<int64_t> tab_idx;
@@ -103,43 +103,47 @@ int64_t up64(int64_t v) { return (v + 63) / 64 * 64; }
 // to 4 x 4; beyond that the scattered rows of a position-major tile cost more than the skipped taps save.
 constexpr int kMaxTablePositions = 64, kMaxTablePositionsWgrad = 16;
 
-// fp32 configuration: convolution and dense layers whose channel counts are multiples of four run on split floats.  Not the
-// layers on the data set but for dense ones (few input channels, read as they lie), nor narrow classifiers, which have
-// their own kernel.  Offsets inside one replica's tensor are 32-bit byte offsets.
-bool split_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
+// bf16 configuration: the lean kernels take stride-1 "same" convolutions with 64-multiple channels on power-of-two images
+bool lean_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
-    if (cfg.bf16 || (l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE)) return false;
+    if (!cfg.bf16 || l.type != HADFL_OP_CONV || l.in0 == 0) return false;
+    const TensorShape a = plan.tensors[l.in0];
+    return l.stride == 1 && 2 * l.pad == l.k - 1 && l.k * l.k <= 32 && a.c % 64 == 0 && l.cout % 64 == 0 && is_pow2(a.h) && is_pow2(a.w);
+}
+
+// The kernels of conv_general.hip take the other convolution and dense layers whose channels come in 16-byte groups.  Not
+// the layers on the data set but for dense ones (few input channels, read as they lie), nor narrow classifiers, which have
+// their own kernel.  Offsets inside one replica's tensor are 32-bit byte offsets.
+bool general_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
+{
+    if ((l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE) || lean_layer(cfg, plan, l)) return false;
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
-    const int64_t cin = conv ? a.c : a.numel(), taps = conv ? l.k * l.k : 1;
-    if (cin % 4 != 0 || l.cout % 4 != 0 || taps > 32) return false;
+    const int64_t cin = conv ? a.c : a.numel(), taps = conv ? l.k * l.k : 1, unit = cfg.bf16 ? 8 : 4;
+    if (cin % unit != 0 || l.cout % unit != 0 || taps > 32) return false;
     if (conv ? l.in0 == 0 : (l.cout <= 16 || (l.in0 == 0 && cin % 16 != 0))) return false;
     if (l.w_off % 4 != 0 || (l.bias && l.b_off != l.w_off + l.w_count)) return false;
     const int64_t limit = int64_t(1) << 31, B = cfg.batch;
     return B * a.numel() * 4 < limit && B * r.numel() * 4 < limit &&
-           split_weight_units(l.cout, (int)taps, (int)cin) * 2 < limit && split_weight_units((int)cin, (int)taps, l.cout) * 2 < limit;
+           weight_copy_units(cfg.bf16, l.cout, (int)taps, (int)cin) * 2 < limit && weight_copy_units(cfg.bf16, (int)cin, (int)taps, l.cout) * 2 < limit;
 }
 
-// Split-K factor of a split layer's weight gradient with n active replicas.  Measured on the ResNet-18 layers: a launch
+// Split-K factor of a general layer's weight gradient with n active replicas.  Measured on the ResNet-18 layers: a launch
 // wants two workgroups per compute unit even if a split is then only 128 pixels long, and up to 2048 workgroups (an even
 // last round) as long as a split keeps 1024 pixels; beyond that the partial sums cost more than they gain.
-int split_wgrad_count(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
+int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
     const int64_t K = (int64_t)cfg.batch * (conv ? r.h * r.w : 1);
-    const int64_t wgs = (int64_t)split_wgrad_tiles((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout) * n;
+    const int64_t wgs = (int64_t)wgrad_general_tiles((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, n) * n;
     const int64_t fill = std::min<int64_t>((512 + wgs - 1) / wgs, K / 128), even = std::min<int64_t>((2048 + wgs - 1) / wgs, K / 1024);
     return (int)std::max<int64_t>(1, std::max(fill, even));
 }
 
-// floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels (fp32 tiles
-// have at least 32 rows, bf16 ones at least 128)
-int64_t stat_floats(const hadfl_config& cfg, int64_t rows, int c)
-{
-    const int64_t per = cfg.bf16 ? 128 : 32;
-    return (rows + per - 1) / per * 2 * c;
-}
+// floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels (tiles have at
+// least 32 rows)
+int64_t stat_floats(int64_t rows, int c) { return (rows + 31) / 32 * 2 * c; }
 
 Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
 {
@@ -171,10 +175,10 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
             int64_t want = (2048 + tiles * cfg.n_replicas - 1) / (tiles * cfg.n_replicas);
             int64_t maxs = std::max<int64_t>(1, K / 128);
             int s = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, maxs), 256));
-            if (split_layer(cfg, plan, l)) {
+            if (general_layer(cfg, plan, l)) {
                 s = 1;
                 for (int n = 1; n <= cfg.n_replicas; ++n) {
-                    const int sn = split_wgrad_count(cfg, plan, l, n);
+                    const int sn = general_wgrad_splits(cfg, plan, l, n);
                     if (sn > 1) shared = std::max<int64_t>(shared, (int64_t)n * sn * up64(M * l.cout));
                 }
             }
@@ -184,48 +188,39 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
     }
     L.rep_block = up64(off);
     L.shared_floats = up64(shared);
-    L.fast.assign(plan.layers.size(), 0); L.split32.assign(plan.layers.size(), 0);
+    L.fast.assign(plan.layers.size(), 0); L.general.assign(plan.layers.size(), 0);
     L.wf_off.assign(plan.layers.size(), -1); L.wb_off.assign(plan.layers.size(), -1);
-    if (cfg.bf16) {
+    {
         int64_t woff = 0;
         for (size_t i = 0; i < plan.layers.size(); ++i) {
             const Layer& l = plan.layers[i];
-            if (l.type != HADFL_OP_CONV || l.in0 == 0) continue;
-            const TensorShape a = plan.tensors[l.in0];
-            if (l.stride != 1 || 2 * l.pad != l.k - 1 || l.k * l.k > 32) continue;
-            if (a.c % 64 != 0 || l.cout % 64 != 0 || !is_pow2(a.h) || !is_pow2(a.w)) continue;
-            L.fast[i] = 1;
-            L.wf_off[i] = woff; woff += up64(l.w_count);
-            L.wb_off[i] = woff; woff += up64(l.w_count);
+            if (lean_layer(cfg, plan, l)) {
+                L.fast[i] = 1;
+                L.wf_off[i] = woff; woff += up64(l.w_count);
+                L.wb_off[i] = woff; woff += up64(l.w_count);
+            } else if (general_layer(cfg, plan, l)) {
+                const TensorShape a = plan.tensors[l.in0];
+                const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
+                L.general[i] = 1;
+                L.wf_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, l.cout, taps, cin));
+                if (l.in0 != 0) { L.wb_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, cin, taps, l.cout)); }
+            }
         }
         L.wbf_rep = woff;
     }
-    if (!cfg.bf16) {
-        int64_t woff = 0;
-        for (size_t i = 0; i < plan.layers.size(); ++i) {
-            const Layer& l = plan.layers[i];
-            if (!split_layer(cfg, plan, l)) continue;
-            const TensorShape a = plan.tensors[l.in0];
-            const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
-            L.split32[i] = 1;
-            L.wf_off[i] = woff; woff += up64(split_weight_units(l.cout, taps, cin));
-            if (l.in0 != 0) { L.wb_off[i] = woff; woff += up64(split_weight_units(cin, taps, l.cout)); }
-        }
-        L.wbf_rep = woff;
-    }
-    // a lean convolution in front of a batch norm leaves statistics entries of its output
+    // a lean or general convolution in front of a batch norm leaves statistics entries of its output
     for (size_t k = 0; k < plan.layers.size(); ++k) {
         const Layer& l = plan.layers[k];
-        if (l.type != HADFL_OP_BN || l.in0 < 1 || (!L.fast[l.in0 - 1] && !L.split32[l.in0 - 1])) continue;
+        if (l.type != HADFL_OP_BN || l.in0 < 1 || (!L.fast[l.in0 - 1] && !L.general[l.in0 - 1])) continue;
         const TensorShape a = plan.tensors[l.in0];
-        bn_shared = std::max<int64_t>(bn_shared, cfg.n_replicas * stat_floats(cfg, B * a.h * a.w, a.c));
+        bn_shared = std::max<int64_t>(bn_shared, cfg.n_replicas * stat_floats(B * a.h * a.w, a.c));
     }
     L.bn_floats = up64(bn_shared);
     // position tables: worth it for small images (many border pixels), and the weight gradient needs slabs of 32
     // contraction indices to hold a single position
     L.tab_idx.assign(plan.layers.size(), -1);
     for (size_t i = 0; i < plan.layers.size(); ++i) {
-        if ((!L.fast[i] && !L.split32[i]) || cfg.batch % 32 != 0) continue;
+        if ((!L.fast[i] && !L.general[i]) || cfg.batch % 32 != 0) continue;
         const Layer& l = plan.layers[i];
         const TensorShape a = plan.tensors[l.in0];
         if (l.type != HADFL_OP_CONV || l.k == 1 || l.stride != 1 || 2 * l.pad != l.k - 1 || a.h * a.w > kMaxTablePositions) continue;
@@ -260,7 +255,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
     e->rep_block = L.rep_block;
     e->shared_off = L.rep_block * cfg.n_replicas;
     e->shared_floats = L.shared_floats;
-    e->fast = L.fast; e->split32 = L.split32; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
+    e->fast = L.fast; e->general = L.general; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
     e->bn_off = e->shared_off + L.shared_floats;
     e->wbf_off = e->bn_off + L.bn_floats;
     {
@@ -269,12 +264,12 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
         for (size_t i = 0; i < plan.layers.size(); ++i) {
             const Layer& l = plan.layers[i];
             if (l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE) continue;
-            // in the weight-gradient epilogue (lean and split kernels, K not split), or in the split-K reduction of a layer
+            // in the weight-gradient epilogue (lean and general kernels, K not split), or in the split-K reduction of a layer
             // whose fp32 weights nothing reads between its weight gradient and the update: the data gradients of the lean
-            // and split layers read the copies, a layer on the data set has no data gradient
+            // and general layers read the copies, a layer on the data set has no data gradient
             const bool in_epilogue = e->fast[i] && e->splits[i] == 1;
             const bool in_reduce = e->splits[i] > 1 && (e->fast[i] || l.in0 == 0);
-            if (!in_epilogue && !in_reduce && !e->split32[i]) continue;
+            if (!in_epilogue && !in_reduce && !e->general[i]) continue;
             const int64_t cnt = l.w_count + (l.bias ? l.cout : 0);      // bias sits directly behind the weights
             if (l.w_off % 4 != 0 || cnt % 4 != 0 || l.w_off < pos || (l.bias && l.b_off != l.w_off + l.w_count)) continue;
             e->fused_update[i] = 1;
@@ -324,7 +319,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             const Layer& b = plan.layers[k];
             if (b.type != HADFL_OP_BN || b.in0 < 1 || consumers[b.in0] != 1) continue;
             const int i = b.in0 - 1;                        // layer i writes tensor i + 1
-            if ((!e->fast[i] && !e->split32[i]) || plan.layers[i].type != HADFL_OP_CONV || e->out_tensor[i] != b.in0) continue;
+            if ((!e->fast[i] && !e->general[i]) || plan.layers[i].type != HADFL_OP_CONV || e->out_tensor[i] != b.in0) continue;
             e->stat_for[i] = k; e->stat_from[k] = i;
         }
         e->pool_of.assign(nl, -1);
@@ -431,12 +426,12 @@ struct Runner {
         const int keep_na = na, keep_layer = cur_layer;
         na = n; cur_layer = (int)i;
         const Layer& l = e.plan.layers[i];
-        if (e.split32[i]) {
-            WeightSplitParams w{};
+        if (e.general[i]) {
+            WeightCopyParams w{};
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
             w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
-            w.C = split_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.order = e.buf.order;
-            run("weight_prep", 0, (w.wb ? 16.0 : 10.0) * l.w_count, [&] { return launch_weight_split(w, na, s); });
+            w.C = layer_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.bf16 = e.cfg.bf16; w.order = e.buf.order;
+            run("weight_prep", 0, (4.0 + (w.wb ? 2 : 1) * (e.cfg.bf16 ? 2.0 : 6.0)) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
         } else {
             WeightPrepParams w{};
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
@@ -446,16 +441,16 @@ struct Runner {
         }
         na = keep_na; cur_layer = keep_layer;
     }
-    int split_channels(const Layer& l) const
+    int layer_channels(const Layer& l) const
     {
         const TensorShape a = e.plan.tensors[l.in0];
         return (int)(l.type == HADFL_OP_CONV ? a.c : a.numel());
     }
-    // what forward and data gradient of a split layer have in common
-    SplitConvParams split_base(size_t i, const GemmParams& g) const
+    // what forward and data gradient of a general layer have in common
+    GeneralConvParams general_base(size_t i, const GemmParams& g) const
     {
-        SplitConvParams f{};
-        f.B = g.B; f.R = g.R; f.S = g.S; f.wmat_rep = e.wbf_rep; f.out_rep = e.rep_block; f.a_rep = e.rep_block;
+        GeneralConvParams f{};
+        f.bf16 = e.cfg.bf16; f.B = g.B; f.R = g.R; f.S = g.S; f.wmat_rep = e.wbf_rep; f.out_rep = e.rep_block; f.a_rep = e.rep_block;
         f.n_samples = g.n_samples; f.batch = g.batch; f.sample_sz = g.sample_sz;
         f.sstride = f.ostride = f.wst = f.classes = 1;
         f.order = e.buf.order; f.perm = perm(i); f.posmask = posmask(i); f.tile_hint = e.tile_hint;
@@ -464,7 +459,7 @@ struct Runner {
     void prepare_weights()
     {
         for (size_t i = 0; i < e.plan.layers.size(); ++i) {
-            if (!e.fast[i] && !e.split32[i]) continue;
+            if (!e.fast[i] && !e.general[i]) continue;
             if (e.prepped[i]) { e.prepped[i] = 0; continue; }      // written during the previous sub-step's backward pass
             prep_layer(i, na);
         }
@@ -577,14 +572,14 @@ struct Runner {
                 f.perm = perm(i); f.posmask = posmask(i);
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat = bn_shared(); f.stat_rep = stat_floats(e.cfg, p.M, p.Cout);
+                    f.stat = bn_shared(); f.stat_rep = stat_floats(p.M, p.Cout);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run("conv_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_fast(f, 0, na, s, srows); });
                 break;
             }
-            if (e.split32[i]) {
-                SplitConvParams f = split_base(i, p);
+            if (e.general[i]) {
+                GeneralConvParams f = general_base(i, p);
                 f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.pad = p.pad; f.sstride = p.stride;
                 f.a = act(l.in0); f.cursor = p.cursor;
                 f.wmat = wbf() + e.wf_off[i];
@@ -593,10 +588,10 @@ struct Runner {
                 f.relu = p.relu;
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat = bn_shared(); f.stat_rep = stat_floats(e.cfg, p.M, p.Cout);
+                    f.stat = bn_shared(); f.stat_rep = stat_floats(p.M, p.Cout);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
-                run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_split(f, 0, na, s, srows); });
+                run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_general(f, 0, na, s, srows); });
                 break;
             }
             if (l.type == HADFL_OP_DENSE && l.cout <= 16 && l.in0 != 0 && !p.relu) {
@@ -621,7 +616,7 @@ struct Runner {
             b.y = actw(ot); b.relu = e.fused_relu[i];
             if (e.stat_from[i] >= 0 && e.stat_rows[i] > 0) {          // the convolution in front left the sums
                 b.stats_done = 1; b.stat_entries = (b.rows + e.stat_rows[i] - 1) / e.stat_rows[i];
-                b.partial_rep = stat_floats(e.cfg, b.rows, b.C);
+                b.partial_rep = stat_floats(b.rows, b.C);
                 const Layer& conv = e.plan.layers[e.stat_from[i]];
                 b.stat_shift = conv.bias ? e.buf.replicas + conv.b_off : nullptr; b.stat_shift_rep = e.plan.row_stride;
             }
@@ -698,7 +693,7 @@ struct Runner {
             p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr;
             p.a_f32 = l.in0 == 0;
             p.dy = grad(ot); p.dy_rep = e.rep_block;
-            p.splits = e.split32[i] ? split_wgrad_count(e.cfg, e.plan, l, na) : e.splits[i];
+            p.splits = e.general[i] ? general_wgrad_splits(e.cfg, e.plan, l, na) : e.splits[i];
             const int64_t mn = (int64_t)p.M * p.N;
             if (p.splits > 1 && e.fast[i]) {
                 // The planned split count fills the chip when every replica is active.  A sub-step with fewer active
@@ -712,7 +707,7 @@ struct Runner {
                 p.splits = (int)std::max<int64_t>(p.splits, std::min<int64_t>(std::min<int64_t>(want, by_buffer), std::min<int64_t>(by_k, 256)));
             }
             if (p.splits > 1) {
-                const int unit = e.fast[i] ? 64 : e.split32[i] ? 32 : 16;      // slab length of the kernel that will run
+                const int unit = e.fast[i] ? 64 : e.general[i] ? 32 : 16;      // slab length of the kernel that will run
                 const int slabs = (p.K + unit - 1) / unit;
                 p.kchunk = ((slabs + p.splits - 1) / p.splits) * unit;
                 p.out_split = (mn + 63) / 64 * 64;
@@ -743,8 +738,9 @@ struct Runner {
                 run("conv_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_wgrad_fast(f, na, s); });
                 if (e.fused_update[i] && na_next > 0) pending_prep = (int)i;
             } else
-            if (e.split32[i]) {
-                SplitWgradParams f{};
+            if (e.general[i]) {
+                GeneralWgradParams f{};
+                f.bf16 = e.cfg.bf16;
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
                 f.stride = p.stride; f.K = p.K; f.kchunk = p.kchunk; f.splits = p.splits; f.has_bias = l.bias;
                 f.x = act(l.in0); f.x_rep = e.rep_block; f.dy = grad(ot); f.dy_rep = e.rep_block;
@@ -755,7 +751,7 @@ struct Runner {
                     f.sgd_w = e.buf.replicas + l.w_off; f.sgd_buf = e.buf.mom ? e.buf.mom + l.w_off : nullptr;
                     f.lr = e.cfg.lr; f.momentum = e.cfg.momentum;
                 }
-                run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_wgrad_split(f, na, s); });
+                run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_wgrad_general(f, na, s); });
                 if (e.fused_update[i] && na_next > 0) pending_prep = (int)i;
             } else
                 run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return gemm(p); });
@@ -788,21 +784,21 @@ struct Runner {
                     int* brows = nullptr;
                     if (e.bstat_for[i] >= 0 && !acc0) {        // this data gradient is the whole gradient of a BN's output
                         const int k = e.bstat_for[i];
-                        f.stat = bn_shared(); f.stat_rep = stat_floats(e.cfg, d.M, d.N);
+                        f.stat = bn_shared(); f.stat_rep = stat_floats(d.M, d.N);
                         f.stat_y = act(l.in0); f.stat_y_rep = e.rep_block; f.stat_relu = e.fused_relu[k];
                         e.bstat_rep[k] = f.stat_rep;
                         brows = &e.bstat_rows[k];
                     }
                     run("conv_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return launch_conv_fast(f, 1, na, s, brows); });
-                } else if (e.split32[i]) {
-                    SplitConvParams f = split_base(i, d);
+                } else if (e.general[i]) {
+                    GeneralConvParams f = general_base(i, d);
                     f.H = d.Ho; f.W = d.Wo; f.C = d.Cout; f.Ho = d.H; f.Wo = d.W; f.N = d.Cin; f.pad = d.R - 1 - d.pad;
                     f.ostride = f.wst = d.stride; f.classes = d.stride * d.stride;
                     f.a = grad(ot);
                     f.wmat = wbf() + e.wb_off[i];
                     f.out = grad(l.in0);
                     f.mask = mask0; f.mask_rep = e.rep_block; f.accumulate = acc0;
-                    run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return launch_conv_split(f, 1, na, s); });
+                    run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return launch_conv_general(f, 1, na, s); });
                 } else
                 run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return gemm(d); });
             }

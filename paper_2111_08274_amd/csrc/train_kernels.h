@@ -114,16 +114,17 @@ struct WeightPrepParams {    // fp32 W[tap][C][N] -> bf16 Wf[N][tap*C + ci] and 
 };
 hipError_t launch_weight_prep(const WeightPrepParams& p, int n_active, hipStream_t s);
 
-// ---- fp32 configuration: convolutions and dense layers on the bf16 matrix cores, every float as three bf16 (conv_f32_split.hip) ----
-struct SplitConvParams {     // out[pixel][n] = sum over taps and channels of a[source pixel][c] * wmat[n][tap][c]
+// ---- convolutions and dense layers of any geometry (conv_general.hip): fp32 on split floats, and the bf16 layers that are not lean ----
+struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of a[source pixel][c] * wmat[n][tap][c]
+    int bf16;                                  // element type of the tensors (pointers are typed float*, strides count 4 bytes)
     int B, H, W, C;                            // source: X (forward) or dY (data gradient)
     int Ho, Wo, N;                             // output image and channels
     int R, S, pad;                             // filter in the copy's (forward or flipped) order
     int sstride;                               // source pixels per output pixel: the stride (forward), 1 (data gradient)
     int ostride, wst, classes;                 // data gradient: stride, stride, stride^2; forward 1, 1, 1
     const float* a; long long a_rep;
-    const long long* cursor; int n_samples, batch; long long sample_sz;   // a is the data set when cursor != null
-    const __bf16* wmat; long long wmat_rep;    // split copy, per-replica stride in 2-byte units
+    const long long* cursor; int n_samples, batch; long long sample_sz;   // a is the (fp32) data set when cursor != null
+    const __bf16* wmat; long long wmat_rep;    // weight copy, per-replica stride in 2-byte units
     float* out; long long out_rep;
     const float* bias; long long bias_rep;     // forward: bias inside the replica rows, or null
     int relu;
@@ -134,14 +135,15 @@ struct SplitConvParams {     // out[pixel][n] = sum over taps and channels of a[
     int tile_hint;                             // 1: the largest tiles whatever the launch size
     int tiles_m, n_active;                     // set by the launcher
 };
-// epi 0: forward (+bias, ReLU); epi 1: data gradient (mask, accumulate).  Needs C % 4 == 0, N % 4 == 0, R * S <= 32, tensors
-// of less than 4 GiB per replica.  stat_rows (may be null): rows per statistics entry of the kernel that was launched.
-hipError_t launch_conv_split(const SplitConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows = nullptr);
-struct SplitWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias) the bias gradient as row R*S*C
+// epi 0: forward (+bias, ReLU); epi 1: data gradient (mask, accumulate).  Needs C % 4 == 0 (bf16: 8), N % 4 == 0, R * S <= 32,
+// tensors of less than 4 GiB per replica.  stat_rows (may be null): rows per statistics entry of the kernel that was launched.
+hipError_t launch_conv_general(const GeneralConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows = nullptr);
+struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias) the bias gradient as row R*S*C
+    int bf16;                                  // element type of x and dy
     int B, H, W, C, Ho, Wo, N, R, S, pad, stride;
     int K, kchunk, splits, has_bias;           // K = B*Ho*Wo; kchunk a multiple of 32 when splits > 1
     const float* x; long long x_rep;
-    const long long* cursor; int n_samples, batch; long long sample_sz;   // x is the data set when cursor != null
+    const long long* cursor; int n_samples, batch; long long sample_sz;   // x is the (fp32) data set when cursor != null
     const float* dy; long long dy_rep;
     float* out; long long out_rep, out_split;
     const int* order;
@@ -149,17 +151,17 @@ struct SplitWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias) t
     float* sgd_w; float* sgd_buf; float lr, momentum;    // as in FastWgradParams
     int n_active;                              // set by the launcher
 };
-// Needs C % 4 == 0, N % 4 == 0, tensors of less than 4 GiB per replica.
-hipError_t launch_wgrad_split(const SplitWgradParams& p, int n_active, hipStream_t s);
-int split_wgrad_tiles(int rows, int N);                              // workgroups per split and replica (rows = R*S*C)
-long long split_weight_units(int rows, int taps, int channels);      // 2-byte units of a split copy [rows][taps][channels]
-struct WeightSplitParams {    // fp32 W[tap][C][N] -> split copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
+// Needs C and N multiples of 4 (bf16: 8), tensors of less than 4 GiB per replica.
+hipError_t launch_wgrad_general(const GeneralWgradParams& p, int n_active, hipStream_t s);
+int wgrad_general_tiles(int rows, int N, int n_active);              // workgroups per split and replica (rows = R*S*C)
+long long weight_copy_units(int bf16, int rows, int taps, int channels);   // 2-byte units of a copy [rows][taps][channels]
+struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
     const float* w; long long w_rep;
     __bf16* wf; __bf16* wb; long long wcopy_rep;
-    int C, N, taps;
+    int C, N, taps, bf16;
     const int* order;
 };
-hipError_t launch_weight_split(const WeightSplitParams& p, int n_active, hipStream_t s);
+hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s);
 
 struct DenseSmallParams {     // out[m][n] = sum_k x[m][k] w[k][n] + bias[n], N <= 16
     const float* x; long long x_rep;
