@@ -99,13 +99,12 @@ __device__ __forceinline__ ClassGeo class_geo(const GeneralConvParams& p, int cl
 // ..., and the groups' sums are joined in group order through LDS at the end.  One LDS buffer per group: the next slab
 // waits in registers while the current one is multiplied, two barriers per slab.
 // EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate.
-// SRC: type of the source tensor; float for T = __bf16 is the data set, rounded on its way into LDS.
-template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, int KG, int EPI>
+template <typename T, int BMT, int BN, int WGM, int WGN, int KG, int EPI>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM * WGN * KG / 4) void conv_general_kernel(GeneralConvParams p)
 {
-    constexpr bool kSplit = std::is_same<T, float>::value, kRound = !kSplit && std::is_same<SRC, float>::value;
+    constexpr bool kSplit = std::is_same<T, float>::value;
     constexpr int kSlab = Slab<T>::channels, kRow = Slab<T>::row, kSlabBytes = Slab<T>::bytes, GR = Slab<T>::groups, CH = kSlabBytes / 16;
-    constexpr unsigned ES = sizeof(SRC);
+    constexpr unsigned ES = sizeof(T);
     constexpr int NW = WGM * WGN, NT = NW * 64;
     constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32;
     constexpr int NQA = BMT * GR / NT, NQB = (BN * CH + NT - 1) / NT;
@@ -127,13 +126,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     const int m0 = (int)(item % tiles_m) * BMT, n0 = (int)((item / tiles_m) % tiles_n) * BN;
     const int hw = cg.hc * cg.wc, M = p.B * hw;
     if (m0 >= M) return;
-    const char* abase;
-    if (p.cursor) {                                   // the batch inside the data set
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
-        abase = (const char*)(p.a + ((long long)rep * p.n_samples + first) * p.sample_sz);
-    } else {
-        abase = (const char*)(p.a + (long long)rep * p.a_rep);
-    }
+    const char* abase = (const char*)(p.a + (long long)rep * p.a_rep);
     const char* wbase = (const char*)(p.wmat + (long long)rep * p.wmat_rep);
 
     // A slots of this thread: (row, group g)
@@ -190,21 +183,20 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
             tap = taps_left ? __builtin_ctz(taps_left) : 0;
         }
     };
-    f4 ra[NQA][2];                                    // (bf16 source: ra[q][0] holds the eight elements)
+    f4 ra[NQA][2];                                    // (bf16: ra[q][0] holds the eight elements)
     u4 rb[NQB];
     auto load_tiles = [&]() {
         const int iy = tap / cg.nx, ix = tap - iy * cg.nx;
-        constexpr int kSecond = kSplit ? 16 : 4;      // channels from the first to the second piece of a group (float source)
         const int c0 = ch * kSlab + ag * (kSplit ? 4 : 8);
         const unsigned delta = (unsigned)((iy * p.W + ix) * p.C + ch * kSlab) * ES;
-        const bool in0 = c0 < p.C, in1 = c0 + kSecond < p.C;
+        const bool in0 = c0 < p.C, in1 = c0 + 16 < p.C;
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
             ra[q][0] = f4{0.f, 0.f, 0.f, 0.f}; ra[q][1] = f4{0.f, 0.f, 0.f, 0.f};
             const bool ok = (tapmask[q] >> tap) & 1u;
             const unsigned o = aoff[q] + delta;
             if (ok && in0) ra[q][0] = *reinterpret_cast<const f4*>(abase + o);
-            if (ES == 4 && ok && in1) ra[q][1] = *reinterpret_cast<const f4*>(abase + o + kSecond * 4u);
+            if (kSplit && ok && in1) ra[q][1] = *reinterpret_cast<const f4*>(abase + o + 64u);
         }
         const int wt = (cg.wy0 + iy * p.wst) * p.S + cg.wx0 + ix * p.wst;
         const unsigned kb = (unsigned)((wt * cs + ch) * kSlabBytes);
@@ -229,8 +221,6 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
                 *reinterpret_cast<u4*>(sAc + sa_st[q]) = join8(h0, h1);
                 *reinterpret_cast<u4*>(sAc + sa_st[q] + 64) = join8(m0_, m1);
                 *reinterpret_cast<u4*>(sAc + sa_st[q] + 128) = join8(l0, l1);
-            } else if constexpr (kRound) {
-                *reinterpret_cast<u4*>(sAc + sa_st[q]) = round8(ra[q][0], ra[q][1]);
             } else {
                 *reinterpret_cast<f4*>(sAc + sa_st[q]) = ra[q][0];
             }
@@ -801,13 +791,13 @@ __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
     }
 }
 
-template <typename T, typename SRC, int EPI, int BMT, int BN, int WGM, int WGN, int KG>
+template <typename T, int EPI, int BMT, int BN, int WGM, int WGN, int KG>
 hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)
 {
     constexpr size_t loop_lds = (size_t)KG * (BMT + BN) * Slab<T>::row, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
     constexpr size_t lds = loop_lds > stat_lds ? loop_lds : stat_lds;
     if (lds > 65536) {
-        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, SRC, BMT, BN, WGM, WGN, KG, EPI>,
+        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI>,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
         if (!ok) return hipErrorInvalidValue;
     }
@@ -815,11 +805,11 @@ hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat
     const int rows0 = p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);     // largest class
     p.tiles_m = (rows0 + BMT - 1) / BMT;
     const dim3 grid(die_grid((long long)p.tiles_m * ((p.N + BN - 1) / BN) * p.classes * n_active)), block(WGM * WGN * KG * 64);
-    hipLaunchKernelGGL((conv_general_kernel<T, SRC, BMT, BN, WGM, WGN, KG, EPI>), grid, block, lds, s, p);
+    hipLaunchKernelGGL((conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI>), grid, block, lds, s, p);
     return hipGetLastError();
 }
 
-template <typename T, typename SRC, int EPI>
+template <typename T, int EPI>
 hipError_t launch_conv(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)
 {
     const long long rows0 = (long long)p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);
@@ -832,23 +822,28 @@ hipError_t launch_conv(GeneralConvParams& p, int n_active, hipStream_t s, int* s
     //   64 x 64, 4 groups:   73    76   162   179   637         128 x 128, 2 groups: 216   218   223   131   504
     //   64 x 64, 2 groups:   91    94   139   147   536         128 x 128, 1 group:  262   267   272   149   448
     const bool large = p.tile_hint == 1;
-    if (!large && t64 <= 48) return launch_t<T, SRC, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
-    if (!large && t64 <= 256) return launch_t<T, SRC, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
-    if (!large && t64 <= 640) return launch_t<T, SRC, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
-    if (p.N <= 32) return launch_t<T, SRC, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
+    if (!large && t64 <= 48) return launch_t<T, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
+    if (!large && t64 <= 256) return launch_t<T, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
+    if (!large && t64 <= 640) return launch_t<T, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
+    if (p.N <= 32) return launch_t<T, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
     if (p.N > 64) {
-        if (large || t128 > 256) return launch_t<T, SRC, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
-        if (t64 > 880) return launch_t<T, SRC, EPI, 128, 128, 2, 2, 2>(p, n_active, s, stat_rows);
+        if (large || t128 > 256) return launch_t<T, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
+        if (t64 > 880) return launch_t<T, EPI, 128, 128, 2, 2, 2>(p, n_active, s, stat_rows);
     }
-    if (p.N <= 64 && (large || t64 > 2048)) return launch_t<T, SRC, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
-    return launch_t<T, SRC, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
+    if (p.N <= 64 && (large || t64 > 2048)) return launch_t<T, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
+    return launch_t<T, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
 }
+
+// 64 x 64 tiles where the larger ones are so few that even with the contraction split they leave compute units idle, or the
+// fused update of a tile (16 bytes per weight, one workgroup after the other through its rows) is what takes the time
+bool small_wgrad(int rows, int N, int n_active) { return N > 32 && (long long)(rows + 127) / 128 * ((N + 127) / 128) * n_active <= 64; }
 
 template <typename T, typename SRC>
 hipError_t launch_wgrad(const GeneralWgradParams& p, int n_active, hipStream_t s)
 {
     const dim3 grid(die_grid((long long)wgrad_general_tiles(p.R * p.S * p.C, p.N, n_active) * p.splits * n_active)), block(256);
-    if (p.N > 64) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 128, 2, 2>), grid, block, 0, s, p);
+    if (small_wgrad(p.R * p.S * p.C, p.N, n_active)) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 64, 64, 2, 2>), grid, block, 0, s, p);
+    else if (p.N > 64) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 128, 2, 2>), grid, block, 0, s, p);
     else if (p.N > 32) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 64, 4, 1>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 32, 4, 1>), grid, block, 0, s, p);
     return hipGetLastError();
@@ -869,14 +864,13 @@ hipError_t launch_conv_general(const GeneralConvParams& p0, int epi, int n_activ
     p.n_active = n_active;
     const int unit = p.bf16 ? 8 : 4;
     if (p.C % unit != 0 || p.N % 4 != 0 || p.R * p.S > 32 || (p.perm && p.classes != 1)) return hipErrorInvalidValue;
-    if (!p.bf16) return epi == 0 ? launch_conv<float, float, 0>(p, n_active, s, stat_rows) : launch_conv<float, float, 1>(p, n_active, s, stat_rows);
-    if (epi == 0 && p.cursor) return launch_conv<__bf16, float, 0>(p, n_active, s, stat_rows);
-    return epi == 0 ? launch_conv<__bf16, __bf16, 0>(p, n_active, s, stat_rows) : launch_conv<__bf16, __bf16, 1>(p, n_active, s, stat_rows);
+    if (!p.bf16) return epi == 0 ? launch_conv<float, 0>(p, n_active, s, stat_rows) : launch_conv<float, 1>(p, n_active, s, stat_rows);
+    return epi == 0 ? launch_conv<__bf16, 0>(p, n_active, s, stat_rows) : launch_conv<__bf16, 1>(p, n_active, s, stat_rows);
 }
 
 int wgrad_general_tiles(int rows, int N, int n_active)
 {
-    (void)n_active;
+    if (small_wgrad(rows, N, n_active)) return (rows + 63) / 64 * ((N + 63) / 64);
     const int bn = N > 64 ? 128 : N > 32 ? 64 : 32;
     return (rows + 127) / 128 * ((N + bn - 1) / bn);
 }

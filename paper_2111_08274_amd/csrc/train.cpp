@@ -128,16 +128,29 @@ bool general_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
            weight_copy_units(cfg.bf16, l.cout, (int)taps, (int)cin) * 2 < limit && weight_copy_units(cfg.bf16, (int)cin, (int)taps, l.cout) * 2 < limit;
 }
 
+// The classifier (a dense layer with at most 16 outputs, not on the data set) has its own kernels
+bool small_dense_layer(const Layer& l)
+{
+    return l.type == HADFL_OP_DENSE && l.cout <= 16 && l.in0 != 0 && (!l.bias || l.b_off == l.w_off + l.w_count);
+}
+
+// Forward straight from the master weights: classifiers and the dense layers on the data set, whose copies no data gradient
+// would use
+bool dense_rows_layer(const Layer& l)
+{
+    return l.type == HADFL_OP_DENSE && (l.cout <= 16 || l.in0 == 0) && (!l.bias || l.b_off == l.w_off + l.w_count);
+}
+
 // Split-K factor of a general layer's weight gradient with n active replicas.  Measured on the ResNet-18 layers: a launch
-// wants two workgroups per compute unit even if a split is then only 128 pixels long, and up to 2048 workgroups (an even
-// last round) as long as a split keeps 1024 pixels; beyond that the partial sums cost more than they gain.
+// wants two workgroups per compute unit (and not a few more) even if a split is then only 128 pixels long, and up to 2048
+// workgroups (an even last round) as long as a split keeps 1024 pixels; beyond that the partial sums cost more than they gain.
 int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
     const int64_t K = (int64_t)cfg.batch * (conv ? r.h * r.w : 1);
     const int64_t wgs = (int64_t)wgrad_general_tiles((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, n) * n;
-    const int64_t fill = std::min<int64_t>((512 + wgs - 1) / wgs, K / 128), even = std::min<int64_t>((2048 + wgs - 1) / wgs, K / 1024);
+    const int64_t fill = std::min<int64_t>(512 / wgs, K / 128), even = std::min<int64_t>(2048 / wgs, K / 1024);
     return (int)std::max<int64_t>(1, std::max(fill, even));
 }
 
@@ -202,8 +215,9 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
                 const TensorShape a = plan.tensors[l.in0];
                 const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
                 L.general[i] = 1;
+                if (dense_rows_layer(l)) continue;
                 L.wf_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, l.cout, taps, cin));
-                if (l.in0 != 0) { L.wb_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, cin, taps, l.cout)); }
+                L.wb_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, cin, taps, l.cout));
             }
         }
         L.wbf_rep = woff;
@@ -269,8 +283,10 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             // and general layers read the copies, a layer on the data set has no data gradient
             const bool in_epilogue = e->fast[i] && e->splits[i] == 1;
             const bool in_reduce = e->splits[i] > 1 && (e->fast[i] || l.in0 == 0);
-            if (!in_epilogue && !in_reduce && !e->general[i]) continue;
-            const int64_t cnt = l.w_count + (l.bias ? l.cout : 0);      // bias sits directly behind the weights
+            const bool small = small_dense_layer(l);        // its backward kernel applies the update, element by element
+            if (!in_epilogue && !in_reduce && !e->general[i] && !small) continue;
+            int64_t cnt = l.w_count + (l.bias ? l.cout : 0);      // bias sits directly behind the weights
+            if (small) cnt = (cnt + 3) / 4 * 4;                   // (padding behind the slice: nothing there is ever updated)
             if (l.w_off % 4 != 0 || cnt % 4 != 0 || l.w_off < pos || (l.bias && l.b_off != l.w_off + l.w_count)) continue;
             e->fused_update[i] = 1;
             if (l.w_off > pos) e->update_segments.push_back({pos, l.w_off - pos});
@@ -376,6 +392,8 @@ void train_destroy(TrainEngine* e)
 
 namespace {
 
+constexpr double kMinSideFlops = 2e8;
+
 struct Runner {
     TrainEngine& e;
     hipStream_t s;
@@ -390,10 +408,18 @@ struct Runner {
     float* grad(int t) const { return e.buf.work + e.grad_off[t]; }
     hipStream_t main_stream = nullptr;
     bool forked = false;                  // a flag, not the handle: the caller's stream may be the null stream
-    // the launches that follow go to the side stream, ordered after everything enqueued on the main stream so far
-    void fork()
+    bool side_busy = false;               // the side stream has work of this sub-step
+    // The launches that follow, a layer's weight gradient of `flops`, go to the side stream, ordered after everything
+    // enqueued on the main stream so far.  A weight gradient that takes about as long as the two events (some 10 us) stays on
+    // the main stream as long as nothing of this sub-step is on the side stream; behind that everything follows
+    // in order there, for the scratch of the split sums and the updated weights are the side stream's until the join.
+    // Four perceptrons, ten sub-steps: 341 us with every weight gradient on the side stream, 230 us with none; a residual
+    // net of 40 channels on 5 replicas: 1650 us and 1800 us.
+    void fork(double flops)
     {
         if (!e.use_side || !e.side || rc != hipSuccess) return;
+        if (!side_busy && flops < kMinSideFlops) return;
+        side_busy = true;
         rc = hipEventRecord(e.ev_fork, s);
         if (rc == hipSuccess) rc = hipStreamWaitEvent(e.side, e.ev_fork, 0);
         if (rc != hipSuccess) { failed = "fork"; return; }
@@ -403,7 +429,8 @@ struct Runner {
     // the main stream waits for everything enqueued on the side stream
     void join()
     {
-        if (!e.use_side || !e.side || rc != hipSuccess) return;
+        if (!side_busy || rc != hipSuccess) return;
+        side_busy = false;
         rc = hipEventRecord(e.ev_join, e.side);
         if (rc == hipSuccess) rc = hipStreamWaitEvent(s, e.ev_join, 0);
         if (rc != hipSuccess) failed = "join";
@@ -429,9 +456,9 @@ struct Runner {
         if (e.general[i]) {
             WeightCopyParams w{};
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
-            w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
+            w.wf = wbf() + e.wf_off[i]; w.wb = wbf() + e.wb_off[i]; w.wcopy_rep = e.wbf_rep;
             w.C = layer_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.bf16 = e.cfg.bf16; w.order = e.buf.order;
-            run("weight_prep", 0, (4.0 + (w.wb ? 2 : 1) * (e.cfg.bf16 ? 2.0 : 6.0)) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
+            run("weight_prep", 0, (e.cfg.bf16 ? 8.0 : 16.0) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
         } else {
             WeightPrepParams w{};
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
@@ -451,7 +478,6 @@ struct Runner {
     {
         GeneralConvParams f{};
         f.bf16 = e.cfg.bf16; f.B = g.B; f.R = g.R; f.S = g.S; f.wmat_rep = e.wbf_rep; f.out_rep = e.rep_block; f.a_rep = e.rep_block;
-        f.n_samples = g.n_samples; f.batch = g.batch; f.sample_sz = g.sample_sz;
         f.sstride = f.ostride = f.wst = f.classes = 1;
         f.order = e.buf.order; f.perm = perm(i); f.posmask = posmask(i); f.tile_hint = e.tile_hint;
         return f;
@@ -459,7 +485,7 @@ struct Runner {
     void prepare_weights()
     {
         for (size_t i = 0; i < e.plan.layers.size(); ++i) {
-            if (!e.fast[i] && !e.general[i]) continue;
+            if (e.wf_off[i] < 0) continue;
             if (e.prepped[i]) { e.prepped[i] = 0; continue; }      // written during the previous sub-step's backward pass
             prep_layer(i, na);
         }
@@ -560,6 +586,14 @@ struct Runner {
                     break;
                 }
             }
+            if (dense_rows_layer(l)) {
+                DenseRowsParams d{};
+                d.x = act(l.in0); d.x_rep = e.rep_block; d.cursor = p.cursor; d.n_samples = p.n_samples; d.batch = p.batch;
+                d.w = p.w; d.w_rep = p.w_rep; d.out = actw(ot); d.out_rep = e.rep_block;
+                d.rows = (int)B; d.K = p.Cin; d.N = l.cout; d.has_bias = l.bias; d.relu = p.relu; d.bf16 = e.cfg.bf16; d.order = e.buf.order;
+                run("dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_dense_rows_fwd(d, na, s); });
+                break;
+            }
             if (e.fast[i]) {
                 FastConvParams f{};
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
@@ -581,7 +615,7 @@ struct Runner {
             if (e.general[i]) {
                 GeneralConvParams f = general_base(i, p);
                 f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.pad = p.pad; f.sstride = p.stride;
-                f.a = act(l.in0); f.cursor = p.cursor;
+                f.a = act(l.in0);
                 f.wmat = wbf() + e.wf_off[i];
                 f.out = actw(ot);
                 f.bias = l.bias ? e.buf.replicas + l.b_off : nullptr; f.bias_rep = e.plan.row_stride;
@@ -592,14 +626,6 @@ struct Runner {
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_general(f, 0, na, s, srows); });
-                break;
-            }
-            if (l.type == HADFL_OP_DENSE && l.cout <= 16 && l.in0 != 0 && !p.relu) {
-                DenseSmallParams d{};
-                d.x = act(l.in0); d.x_rep = e.rep_block; d.w = p.w; d.w_rep = p.w_rep;
-                d.out = actw(ot); d.out_rep = e.rep_block;
-                d.rows = (int)B; d.K = p.Cin; d.N = l.cout; d.has_bias = l.bias; d.order = e.buf.order; d.bf16 = e.cfg.bf16;
-                run("dense_small_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_dense_small_fwd(d, na, s); });
                 break;
             }
             run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return gemm(p); });
@@ -627,6 +653,14 @@ struct Runner {
             run("bn_fwd", 0, asz() * (8.0 * B * a.numel()), [&] { return launch_bn_fwd(b, na, s); });
             break; }
         }
+    }
+
+    DenseSmallParams dense_small(const Layer& l, const GemmParams& g) const
+    {
+        DenseSmallParams d{};
+        d.x = act(l.in0); d.x_rep = e.rep_block; d.w = e.buf.replicas + l.w_off; d.w_rep = e.plan.row_stride;
+        d.rows = g.B; d.K = g.Cin; d.N = l.cout; d.has_bias = l.bias; d.order = e.buf.order; d.bf16 = e.cfg.bf16;
+        return d;
     }
 
     // bf16 configuration: the first convolution (data set in) has its own kernels when its footprint fits one MFMA
@@ -687,6 +721,14 @@ struct Runner {
         case HADFL_OP_DENSE: {
             // weight (and bias) gradient
             GemmParams p = gemm_base(l);
+            if (small_dense_layer(l) && e.fused_update[i]) {
+                DenseSmallParams d = dense_small(l, p);
+                d.dy = grad(ot); d.dy_rep = e.rep_block; d.dx = grad(l.in0); d.dx_rep = e.rep_block;
+                d.mask = mask0; d.mask_rep = e.rep_block; d.accumulate = acc0;
+                d.buf = e.buf.mom ? e.buf.mom + l.w_off : nullptr; d.lr = e.cfg.lr; d.momentum = e.cfg.momentum;
+                run("dense_small_bwd", 2.0 * gemm_flops(p), 2.0 * gemm_bytes(p), [&] { return launch_dense_small_bwd(d, na, s); });
+                break;
+            }
             p.mode = kWgrad;
             p.M = p.R * p.S * p.Cin + (l.bias ? 1 : 0); p.N = p.Cout; p.K = (int)(B * p.Ho * p.Wo);
             p.a = act(l.in0); p.a_rep = e.rep_block;
@@ -715,7 +757,7 @@ struct Runner {
             } else {
                 p.out = e.buf.grad + l.w_off; p.out_rep = e.plan.row_stride;
             }
-            fork();
+            fork(na * gemm_flops(p));
             flush_pending_prep();
             FirstConvParams fc;
             if (first_conv(i, fc)) {
@@ -752,7 +794,7 @@ struct Runner {
                     f.lr = e.cfg.lr; f.momentum = e.cfg.momentum;
                 }
                 run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_wgrad_general(f, na, s); });
-                if (e.fused_update[i] && na_next > 0) pending_prep = (int)i;
+                if (e.fused_update[i] && na_next > 0 && e.wf_off[i] >= 0) pending_prep = (int)i;
             } else
                 run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return gemm(p); });
             if (p.splits > 1 && e.fused_update[i])
@@ -885,7 +927,7 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
         e->grad_written[T - 1] = 1;
         r.na_next = step + 1 < e->e_max ? e->n_active[step + 1] : 0;
         for (size_t i = e->plan.layers.size(); i-- > 0;) r.backward_layer(i);
-        if (r.pending_prep >= 0) { r.fork(); r.flush_pending_prep(); r.unfork(); }
+        if (r.pending_prep >= 0) { r.fork(0.0); r.flush_pending_prep(); r.unfork(); }
         r.join();
         SgdParams sp{};
         sp.w = e->buf.replicas; sp.g = e->buf.grad; sp.buf = e->buf.mom; sp.row_stride = e->plan.row_stride;

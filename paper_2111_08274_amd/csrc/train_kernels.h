@@ -123,7 +123,6 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     int sstride;                               // source pixels per output pixel: the stride (forward), 1 (data gradient)
     int ostride, wst, classes;                 // data gradient: stride, stride, stride^2; forward 1, 1, 1
     const float* a; long long a_rep;
-    const long long* cursor; int n_samples, batch; long long sample_sz;   // a is the (fp32) data set when cursor != null
     const __bf16* wmat; long long wmat_rep;    // weight copy, per-replica stride in 2-byte units
     float* out; long long out_rep;
     const float* bias; long long bias_rep;     // forward: bias inside the replica rows, or null
@@ -163,15 +162,30 @@ struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (u
 };
 hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s);
 
-struct DenseSmallParams {     // out[m][n] = sum_k x[m][k] w[k][n] + bias[n], N <= 16
+struct DenseRowsParams {      // out[m][n] = sum_k x[m][k] w[k][n] + bias[n]
     const float* x; long long x_rep;
+    const long long* cursor; int n_samples, batch;    // x is the (fp32) data set when cursor != null
     const float* w; long long w_rep;     // weights [K][N] followed by bias [N]
     float* out; long long out_rep;
+    int rows, K, N, has_bias, relu, bf16;
+    const int* order;
+};
+hipError_t launch_dense_rows_fwd(const DenseRowsParams& p, int n_active, hipStream_t s);
+
+struct DenseSmallParams {     // backward of a dense layer with N <= 16 outputs:
+    // dx[m][k] (+)= sum_n dy[m][n] w[k][n], zero where mask <= 0; then w and buf (the momentum of these parameters, or
+    // null; same stride) take the update of w's gradient sum_m x[m][k] dy[m][n]
+    const float* x; long long x_rep;
+    float* w; long long w_rep;           // weights [K][N] followed by bias [N]
     int rows, K, N, has_bias;
     int bf16;
     const int* order;
+    const float* dy; long long dy_rep;
+    float* dx; long long dx_rep;
+    const float* mask; long long mask_rep; int accumulate;
+    float* buf; float lr, momentum;
 };
-hipError_t launch_dense_small_fwd(const DenseSmallParams& p, int n_active, hipStream_t s);
+hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipStream_t s);
 
 struct EwParams {     // element-wise / pooling kernels
     const float* in; long long in_rep;
