@@ -99,7 +99,9 @@ __device__ __forceinline__ ClassGeo class_geo(const GeneralConvParams& p, int cl
 // ..., and the groups' sums are joined in group order through LDS at the end.  One LDS buffer per group: the next slab
 // waits in registers while the current one is multiplied, two barriers per slab.
 // EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate.
-template <typename T, int BMT, int BN, int WGM, int WGN, int KG, int EPI>
+// GATHER: a convolution on the data set, whose few channels come in no 16-byte groups.  All taps and channels are one
+// contraction in the order of the weights, (tap, channel), and the source values are gathered one by one.
+template <typename T, int BMT, int BN, int WGM, int WGN, int KG, int EPI, bool GATHER>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM * WGN * KG / 4) void conv_general_kernel(GeneralConvParams p)
 {
     constexpr bool kSplit = std::is_same<T, float>::value;
@@ -127,30 +129,42 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     const int hw = cg.hc * cg.wc, M = p.B * hw;
     if (m0 >= M) return;
     const char* abase = (const char*)(p.a + (long long)rep * p.a_rep);
+    if constexpr (GATHER) {                           // the batch inside the data set
+        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        abase = (const char*)(p.a + ((long long)rep * p.n_samples + first) * p.sample_sz);
+    }
     const char* wbase = (const char*)(p.wmat + (long long)rep * p.wmat_rep);
 
     // A slots of this thread: (row, group g)
     const int ag = tid % GR;
     unsigned aoff[NQA], tapmask[NQA], sa_st[NQA];
+    int row_y[GATHER ? NQA : 1], row_x[GATHER ? NQA : 1];     // source pixel of tap (0, 0); out of reach beyond the last row
 #pragma unroll
     for (int q = 0; q < NQA; ++q) {
         const int i = tid + q * NT, arow = i / GR, m = m0 + arow;
         aoff[q] = 0; tapmask[q] = 0;
+        if constexpr (GATHER) { row_y[q] = -(1 << 20); row_x[q] = 0; }
         if (m < M) {
             int b, pos;
             if (p.perm) { const int ps = m / p.B; b = m - ps * p.B; pos = p.perm[ps]; }
             else { b = m / hw; pos = m - b * hw; }
             const int y = pos / cg.wc, x = pos - y * cg.wc;
             const int sy = y * p.sstride + cg.by, sx = x * p.sstride + cg.bx;
+            if constexpr (GATHER) {
+                row_y[q] = sy; row_x[q] = sx;
+                aoff[q] = (unsigned)(((b * p.H + sy) * p.W + sx) * p.C) * ES;
+            } else {
             aoff[q] = (unsigned)(((b * p.H + sy) * p.W + sx) * p.C + ag * (kSplit ? 4 : 8)) * ES;      // (may lie outside: only used with a tap's delta)
             for (int iy = 0, t = 0; iy < cg.ny; ++iy)
                 for (int ix = 0; ix < cg.nx; ++ix, ++t)
                     if (sy + iy >= 0 && sy + iy < p.H && sx + ix >= 0 && sx + ix < p.W) tapmask[q] |= 1u << t;
+            }
         }
         sa_st[q] = (unsigned)(arow * kRow + ag * 16);
     }
-    const int cs = (p.C + kSlab - 1) / kSlab;         // slabs per tap
-    const unsigned wrow = (unsigned)(p.R * p.S * cs * kSlabBytes);
+    const int kflat = p.R * p.S * p.C;                // (GATHER)
+    const int cs = ((GATHER ? kflat : p.C) + kSlab - 1) / kSlab;         // slabs per tap
+    const unsigned wrow = (unsigned)((GATHER ? 1 : p.R * p.S) * cs * kSlabBytes);
     unsigned boff[NQB], sb_st[NQB]; bool b_ok[NQB];
 #pragma unroll
     for (int q = 0; q < NQB; ++q) {
@@ -163,7 +177,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     const unsigned b_rd = (unsigned)((wn * (BN / WGN) + (lane & 31)) * kRow + (lane >> 5) * 16);
 
     // slabs: (tap, kSlab channels) for the taps some row of the tile can reach, taps ascending
-    const int ntap = cg.ny * cg.nx;
+    const int ntap = GATHER ? 1 : cg.ny * cg.nx;
     unsigned taps = ntap >= 32 ? 0xffffffffu : (1u << ntap) - 1u;
     if (p.perm) {
         const int last = min(m0 + BMT, M) - 1;
@@ -186,6 +200,27 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     f4 ra[NQA][2];                                    // (bf16: ra[q][0] holds the eight elements)
     u4 rb[NQB];
     auto load_tiles = [&]() {
+        if constexpr (GATHER) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = ch * kSlab + (j >> 2) * 16 + ag * 4 + (j & 3);
+                const int t = k / p.C, r = t / p.S, c = k - t * p.C, x = t - r * p.S;
+                const unsigned o = (unsigned)((r * p.W + x) * p.C + c) * ES;
+#pragma unroll
+                for (int q = 0; q < NQA; ++q) {
+                    const int yy = row_y[q] + r, xx = row_x[q] + x;
+                    float v = 0.f;
+                    if (k < kflat && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W) v = *reinterpret_cast<const float*>(abase + (aoff[q] + o));   // (32-bit sum: aoff alone may lie outside)
+                    ra[q][j >> 2][j & 3] = v;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < NQB; ++q) {
+                rb[q] = u4{0u, 0u, 0u, 0u};
+                if (b_ok[q]) rb[q] = ldg16(wbase, boff[q] + (unsigned)(ch * kSlabBytes));
+            }
+            return;
+        }
         const int iy = tap / cg.nx, ix = tap - iy * cg.nx;
         const int c0 = ch * kSlab + ag * (kSplit ? 4 : 8);
         const unsigned delta = (unsigned)((iy * p.W + ix) * p.C + ch * kSlab) * ES;
@@ -440,10 +475,12 @@ __device__ __forceinline__ void put_gradient(const f4& v, long long o, const Gen
     *reinterpret_cast<f4*>(w + o) = *reinterpret_cast<const f4*>(w + o) - d * p.lr;
 }
 
-template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN>
+// GATHER: the source is the data set and its few channels come in no 16-byte groups; the four rows of a slot have a tap and a
+// channel each and are gathered one by one.  Tiles of 32 rows: the waves without a block only help to stage.
+template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, bool GATHER = false>
 __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParams p)
 {
-    static_assert(WGM * WGN == 4, "four waves");
+    static_assert(WGM * WGN == 4 || (GATHER && WGM * WGN < 4), "four waves");
     constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32, BK = 32;
     constexpr bool kSplit = std::is_same<T, float>::value, kRound = !kSplit && std::is_same<SRC, float>::value;
     constexpr unsigned ES = sizeof(SRC);
@@ -461,6 +498,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
+    const bool mma = wave < WGM * WGN;                        // (all waves but in GATHER tiles)
     // logical item = (slot, split, tile): the tiles of one split of one replica read the same pixels
     const int mw = p.R * p.S * p.C;                           // rows that are weights; row mw is the bias gradient
     const unsigned tiles_n = (unsigned)(p.N + BN - 1) / BN, tiles = (unsigned)((mw + BMT - 1) / BMT) * tiles_n;
@@ -492,6 +530,15 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
     const int yn = p.H - 1 - ady >= 0 ? max(0, (p.H - 1 - ady) / p.stride + 1 - ylo) : 0;
     const int xn = p.W - 1 - adx >= 0 ? max(0, (p.W - 1 - adx) / p.stride + 1 - xlo) : 0;
     const unsigned a_shift = (unsigned)((ady * p.W + adx) * p.C + aci) * ES;
+    int gy[GATHER ? 4 : 1], gx[GATHER ? 4 : 1]; unsigned gs[GATHER ? 4 : 1];     // GATHER: tap offset and shift of each row of the slot
+    if constexpr (GATHER) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = (am + e) / p.C;
+            gy[e] = am + e < mw ? t / p.S - p.pad : 1 << 20; gx[e] = t % p.S - p.pad;
+            gs[e] = (((unsigned)gy[e] * (unsigned)p.W + (unsigned)gx[e]) * (unsigned)p.C + (unsigned)(am + e - t * p.C)) * ES;
+        }
+    }
     // 32 pixels further: x += dx, y += dyy, image += db, in source bytes step (carries adjust by cx, cy)
     const int hw = p.Ho * p.Wo;
     const int dx = BK % p.Wo, dyy = (BK / p.Wo) % p.Ho, db = BK / hw;
@@ -504,7 +551,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
         for (int q = 0; q < NQA; ++q) {
             const int k = k0 + arow + AR * q, b = k / hw, rem = k - b * hw;
             py[q] = rem / p.Wo; px[q] = rem - py[q] * p.Wo;
-            poff[q] = ((unsigned)(b * p.H + py[q] * p.stride) * (unsigned)p.W + (unsigned)(px[q] * p.stride)) * pc + a_shift;
+            poff[q] = ((unsigned)(b * p.H + py[q] * p.stride) * (unsigned)p.W + (unsigned)(px[q] * p.stride)) * pc + (GATHER ? 0u : a_shift);
         }
     };
     // Contraction order.  With a position table, index k = ps * B + b is image b at pixel perm[ps] (B a multiple of the slab
@@ -542,7 +589,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
                 ra[q] = f4{0.f, 0.f, 0.f, 0.f};
                 const bool in = a_ok && (unsigned)(py[q] - ylo) < (unsigned)yn && (unsigned)(px[q] - xlo) < (unsigned)xn;
                 const bool on = in && k0 + arow + AR * q < kend;
-                if (on) ra[q] = *reinterpret_cast<const f4*>(xbase + poff[q]);
+                if constexpr (GATHER) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int yy = py[q] * p.stride + gy[e], xx = px[q] * p.stride + gx[e];
+                        if (k0 + arow + AR * q < kend && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W)
+                            ra[q][e] = *reinterpret_cast<const float*>(xbase + (poff[q] + gs[e]));     // (32-bit sum: gs may be negative)
+                    }
+                } else if (on) ra[q] = *reinterpret_cast<const f4*>(xbase + poff[q]);
                 if constexpr (kRound) {
                     ra2[q] = f4{0.f, 0.f, 0.f, 0.f};
                     if (on) ra2[q] = *reinterpret_cast<const f4*>(xbase + poff[q] + 16u);
@@ -619,6 +673,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
         __syncthreads();
         k0 = next_slab(k0 + BK);
         if (k0 < kend) load_tiles(k0);
+        if (mma)
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
             constexpr int PL = Slab<T>::planes;
@@ -669,7 +724,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
 #pragma unroll
             for (int q = 0; q < NQB; ++q) *reinterpret_cast<f4*>(sB + (brow + BR * q) * PB + (tid % BG) * 16) = rb[q];
             __syncthreads();
-            for (int k = lane >> 5; k < BK; k += 2) {
+            for (int k = lane >> 5; mma && k < BK; k += 2) {
                 float a[TM], b[TN];
 #pragma unroll
                 for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const float*>(sA + k * PA + (wm * (BMT / WGM) + i * 32 + (lane & 31)) * 4);
@@ -693,6 +748,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
     float* const w = (p.splits == 1 && p.sgd_w) ? p.sgd_w + (long long)rep * p.out_rep : nullptr;
     float* const buf = (w && p.sgd_buf) ? p.sgd_buf + (long long)rep * p.out_rep : nullptr;
     float* const stage = reinterpret_cast<float*>(smem) + wave * (32 * kStagePitch);
+    if (mma)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -791,13 +847,13 @@ __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
     }
 }
 
-template <typename T, int EPI, int BMT, int BN, int WGM, int WGN, int KG>
+template <typename T, int EPI, int BMT, int BN, int WGM, int WGN, int KG, bool GATHER = false>
 hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)
 {
     constexpr size_t loop_lds = (size_t)KG * (BMT + BN) * Slab<T>::row, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
     constexpr size_t lds = loop_lds > stat_lds ? loop_lds : stat_lds;
     if (lds > 65536) {
-        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI>,
+        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI, GATHER>,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
         if (!ok) return hipErrorInvalidValue;
     }
@@ -805,7 +861,7 @@ hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat
     const int rows0 = p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);     // largest class
     p.tiles_m = (rows0 + BMT - 1) / BMT;
     const dim3 grid(die_grid((long long)p.tiles_m * ((p.N + BN - 1) / BN) * p.classes * n_active)), block(WGM * WGN * KG * 64);
-    hipLaunchKernelGGL((conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI>), grid, block, lds, s, p);
+    hipLaunchKernelGGL((conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI, GATHER>), grid, block, lds, s, p);
     return hipGetLastError();
 }
 
@@ -841,7 +897,12 @@ bool small_wgrad(int rows, int N, int n_active) { return N > 32 && (long long)(r
 template <typename T, typename SRC>
 hipError_t launch_wgrad(const GeneralWgradParams& p, int n_active, hipStream_t s)
 {
-    const dim3 grid(die_grid((long long)wgrad_general_tiles(p.R * p.S * p.C, p.N, n_active) * p.splits * n_active)), block(256);
+    const bool gather = p.cursor && p.gather;
+    const dim3 grid(die_grid((long long)wgrad_general_tiles(p.R * p.S * p.C, p.N, n_active, gather) * p.splits * n_active)), block(256);
+    if constexpr (std::is_same<T, float>::value) {
+        if (gather && p.N <= 32) { hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 32, 32, 1, 1, true>), grid, block, 0, s, p); return hipGetLastError(); }
+        if (gather) { hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 32, 64, 1, 2, true>), grid, block, 0, s, p); return hipGetLastError(); }
+    }
     if (small_wgrad(p.R * p.S * p.C, p.N, n_active)) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 64, 64, 2, 2>), grid, block, 0, s, p);
     else if (p.N > 64) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 128, 2, 2>), grid, block, 0, s, p);
     else if (p.N > 32) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 64, 4, 1>), grid, block, 0, s, p);
@@ -863,13 +924,23 @@ hipError_t launch_conv_general(const GeneralConvParams& p0, int epi, int n_activ
     GeneralConvParams p = p0;
     p.n_active = n_active;
     const int unit = p.bf16 ? 8 : 4;
+    if (p.cursor) {
+        // one slab or a few: the tiles are bound by their loads and stores, so the small ones only serve launches that would
+        // leave units idle
+        if (p.bf16 || epi != 0 || p.N % 4 != 0 || p.perm || p.classes != 1) return hipErrorInvalidValue;
+        const long long rows = (long long)p.B * p.Ho * p.Wo;
+        if (p.N <= 32) return launch_t<float, 0, 128, 32, 4, 1, 1, true>(p, n_active, s, stat_rows);
+        if (rows / 128 * ((p.N + 63) / 64) * n_active < 512) return launch_t<float, 0, 64, 64, 2, 2, 1, true>(p, n_active, s, stat_rows);
+        return launch_t<float, 0, 128, 64, 4, 1, 1, true>(p, n_active, s, stat_rows);
+    }
     if (p.C % unit != 0 || p.N % 4 != 0 || p.R * p.S > 32 || (p.perm && p.classes != 1)) return hipErrorInvalidValue;
     if (!p.bf16) return epi == 0 ? launch_conv<float, 0>(p, n_active, s, stat_rows) : launch_conv<float, 1>(p, n_active, s, stat_rows);
     return epi == 0 ? launch_conv<__bf16, 0>(p, n_active, s, stat_rows) : launch_conv<__bf16, 1>(p, n_active, s, stat_rows);
 }
 
-int wgrad_general_tiles(int rows, int N, int n_active)
+int wgrad_general_tiles(int rows, int N, int n_active, int gather)
 {
+    if (gather) return (rows + 31) / 32 * ((N + (N <= 32 ? 31 : 63)) / (N <= 32 ? 32 : 64));
     if (small_wgrad(rows, N, n_active)) return (rows + 63) / 64 * ((N + 63) / 64);
     const int bn = N > 64 ? 128 : N > 32 ? 64 : 32;
     return (rows + 127) / 128 * ((N + bn - 1) / bn);
@@ -881,7 +952,8 @@ hipError_t launch_wgrad_general(const GeneralWgradParams& p0, int n_active, hipS
     GeneralWgradParams p = p0;
     p.n_active = n_active;
     const int unit = p.bf16 ? 8 : 4;
-    if (p.C % unit != 0 || p.N % unit != 0 || (p.splits > 1 && p.kchunk % 32 != 0)) return hipErrorInvalidValue;
+    if (p.gather && (!p.cursor || p.bf16)) return hipErrorInvalidValue;
+    if ((p.C % unit != 0 && !p.gather) || p.N % unit != 0 || (p.splits > 1 && p.kchunk % 32 != 0)) return hipErrorInvalidValue;
     if (p.perm && (p.B % 32 != 0 || p.stride != 1 || p.R * p.S > 32 || p.cursor)) return hipErrorInvalidValue;
     if (!p.bf16) return launch_wgrad<float, float>(p, n_active, s);
     return p.cursor ? launch_wgrad<__bf16, float>(p, n_active, s) : launch_wgrad<__bf16, __bf16>(p, n_active, s);

@@ -111,17 +111,20 @@ bool lean_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
     return l.stride == 1 && 2 * l.pad == l.k - 1 && l.k * l.k <= 32 && a.c % 64 == 0 && l.cout % 64 == 0 && is_pow2(a.h) && is_pow2(a.w);
 }
 
-// The kernels of conv_general.hip take the other convolution and dense layers whose channels come in 16-byte groups.  Not
-// the layers on the data set but for dense ones (few input channels, read as they lie), nor narrow classifiers, which have
-// their own kernel.  Offsets inside one replica's tensor are 32-bit byte offsets.
+// The kernels of conv_general.hip take the other convolution and dense layers whose channels come in 16-byte groups, and in
+// fp32 the convolutions on the data set, gathered value by value (in bf16 those have kernels of their own).  Not narrow
+// classifiers, which have their own kernels too.  Offsets inside one replica's tensor are 32-bit byte offsets.
+bool gather_layer(const hadfl_config& cfg, const Layer& l) { return !cfg.bf16 && l.type == HADFL_OP_CONV && l.in0 == 0; }
+
 bool general_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
     if ((l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE) || lean_layer(cfg, plan, l)) return false;
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
     const int64_t cin = conv ? a.c : a.numel(), taps = conv ? l.k * l.k : 1, unit = cfg.bf16 ? 8 : 4;
-    if (cin % unit != 0 || l.cout % unit != 0 || taps > 32) return false;
-    if (conv ? l.in0 == 0 : (l.cout <= 16 || (l.in0 == 0 && cin % 16 != 0))) return false;
+    const bool gather = gather_layer(cfg, l);
+    if (l.cout % unit != 0 || (!gather && (cin % unit != 0 || taps > 32))) return false;
+    if (conv ? l.in0 == 0 && !gather : (l.cout <= 16 || (l.in0 == 0 && cin % 16 != 0))) return false;
     if (l.w_off % 4 != 0 || (l.bias && l.b_off != l.w_off + l.w_count)) return false;
     const int64_t limit = int64_t(1) << 31, B = cfg.batch;
     return B * a.numel() * 4 < limit && B * r.numel() * 4 < limit &&
@@ -149,7 +152,7 @@ int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Lay
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
     const int64_t K = (int64_t)cfg.batch * (conv ? r.h * r.w : 1);
-    const int64_t wgs = (int64_t)wgrad_general_tiles((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, n) * n;
+    const int64_t wgs = (int64_t)wgrad_general_tiles((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, n, gather_layer(cfg, l)) * n;
     const int64_t fill = std::min<int64_t>(512 / wgs, K / 128), even = std::min<int64_t>(2048 / wgs, K / 1024);
     return (int)std::max<int64_t>(1, std::max(fill, even));
 }
@@ -216,6 +219,10 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
                 const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
                 L.general[i] = 1;
                 if (dense_rows_layer(l)) continue;
+                if (gather_layer(cfg, l)) {                            // all taps and channels in one contraction, no data gradient
+                    L.wf_off[i] = woff; woff += up64(weight_copy_units(0, l.cout, 1, taps * cin));
+                    continue;
+                }
                 L.wf_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, l.cout, taps, cin));
                 L.wb_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, cin, taps, l.cout));
             }
@@ -237,7 +244,7 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
         if ((!L.fast[i] && !L.general[i]) || cfg.batch % 32 != 0) continue;
         const Layer& l = plan.layers[i];
         const TensorShape a = plan.tensors[l.in0];
-        if (l.type != HADFL_OP_CONV || l.k == 1 || l.stride != 1 || 2 * l.pad != l.k - 1 || a.h * a.w > kMaxTablePositions) continue;
+        if (l.type != HADFL_OP_CONV || l.in0 == 0 || l.k == 1 || l.stride != 1 || 2 * l.pad != l.k - 1 || a.h * a.w > kMaxTablePositions) continue;
         L.tab_idx[i] = L.tab_ints; L.tab_ints += 2 * (int64_t)a.h * a.w;
     }
     return L;
@@ -456,8 +463,9 @@ struct Runner {
         if (e.general[i]) {
             WeightCopyParams w{};
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
-            w.wf = wbf() + e.wf_off[i]; w.wb = wbf() + e.wb_off[i]; w.wcopy_rep = e.wbf_rep;
+            w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
             w.C = layer_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.bf16 = e.cfg.bf16; w.order = e.buf.order;
+            if (gather_layer(e.cfg, l)) { w.C *= w.taps; w.taps = 1; }
             run("weight_prep", 0, (e.cfg.bf16 ? 8.0 : 16.0) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
         } else {
             WeightPrepParams w{};
@@ -615,7 +623,7 @@ struct Runner {
             if (e.general[i]) {
                 GeneralConvParams f = general_base(i, p);
                 f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.pad = p.pad; f.sstride = p.stride;
-                f.a = act(l.in0);
+                f.a = act(l.in0); f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz;
                 f.wmat = wbf() + e.wf_off[i];
                 f.out = actw(ot);
                 f.bias = l.bias ? e.buf.replicas + l.b_off : nullptr; f.bias_rep = e.plan.row_stride;
@@ -786,7 +794,7 @@ struct Runner {
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
                 f.stride = p.stride; f.K = p.K; f.kchunk = p.kchunk; f.splits = p.splits; f.has_bias = l.bias;
                 f.x = act(l.in0); f.x_rep = e.rep_block; f.dy = grad(ot); f.dy_rep = e.rep_block;
-                f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz;
+                f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz; f.gather = gather_layer(e.cfg, l);
                 f.out = p.out; f.out_rep = p.out_rep; f.out_split = p.out_split; f.order = e.buf.order;
                 if (p.H * p.W <= kMaxTablePositionsWgrad) { f.perm = perm(i); f.posmask = posmask(i); }
                 if (e.fused_update[i]) {

@@ -123,6 +123,8 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     int sstride;                               // source pixels per output pixel: the stride (forward), 1 (data gradient)
     int ostride, wst, classes;                 // data gradient: stride, stride, stride^2; forward 1, 1, 1
     const float* a; long long a_rep;
+    // forward of an fp32 convolution on the data set (a) when cursor != null: any C, the copy is [N][1][R*S*C]
+    const long long* cursor; int n_samples, batch; long long sample_sz;
     const __bf16* wmat; long long wmat_rep;    // weight copy, per-replica stride in 2-byte units
     float* out; long long out_rep;
     const float* bias; long long bias_rep;     // forward: bias inside the replica rows, or null
@@ -140,6 +142,7 @@ hipError_t launch_conv_general(const GeneralConvParams& p, int epi, int n_active
 struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias) the bias gradient as row R*S*C
     int bf16;                                  // element type of x and dy
     int B, H, W, C, Ho, Wo, N, R, S, pad, stride;
+    int gather;                                // fp32 convolution on the data set: any C
     int K, kchunk, splits, has_bias;           // K = B*Ho*Wo; kchunk a multiple of 32 when splits > 1
     const float* x; long long x_rep;
     const long long* cursor; int n_samples, batch; long long sample_sz;   // x is the (fp32) data set when cursor != null
@@ -152,7 +155,7 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
 };
 // Needs C and N multiples of 4 (bf16: 8), tensors of less than 4 GiB per replica.
 hipError_t launch_wgrad_general(const GeneralWgradParams& p, int n_active, hipStream_t s);
-int wgrad_general_tiles(int rows, int N, int n_active);              // workgroups per split and replica (rows = R*S*C)
+int wgrad_general_tiles(int rows, int N, int n_active, int gather);              // workgroups per split and replica (rows = R*S*C)
 long long weight_copy_units(int bf16, int rows, int taps, int channels);   // 2-byte units of a copy [rows][taps][channels]
 struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
     const float* w; long long w_rep;

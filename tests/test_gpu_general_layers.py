@@ -41,6 +41,10 @@ def _nets():
     b = nets._Builder()                       # a hidden layer on the (fp32) data set, contraction of 25 slabs
     b.dense(b.relu(b.dense(0, 128)), 5)
     c["dense"] = (b.array(), (1, 1, 784), 50)
+    for ch, cout, pad in ((3, 20, 2), (1, 72, 0)):       # convolutions on the data set, 75 and 25 values per output: ragged slabs and rows
+        b = nets._Builder()
+        b.dense(b.gap(b.relu(b.bn(b.conv(b.relu(b.conv(0, cout, k=5, stride=2, pad=pad)), 8, bias=False)))), 5)
+        c["first%d" % ch] = (b.array(), (11, 14, ch), 21)
     return c
 
 
@@ -49,7 +53,7 @@ NETS = _nets()
 
 @pytest.mark.parametrize("hint", [0, 1])
 @pytest.mark.parametrize("replicas", [2, 9])
-@pytest.mark.parametrize("name,bf16", [(n, False) for n in sorted(NETS)] + [(n, True) for n in sorted(NETS) if n != "ragged"])
+@pytest.mark.parametrize("name,bf16", [(n, False) for n in sorted(NETS)] + [(n, True) for n in sorted(NETS) if n in ("eights", "residual", "tables", "dense")])
 def test_general_layers_against_oracle(name, bf16, replicas, hint):
     """Every tensor's update of every step against the oracle.  Two and nine replicas put the launches on both sides of the
     tile rules (a few workgroups with several wave groups along K; one group), hint 1 takes the largest tiles."""
