@@ -31,6 +31,7 @@
 //     a thread reads channels 4g..4g+3 and 16+4g..16+4g+3 (64 contiguous bytes over four lanes each) and stores one
 //     16-byte group per plane.
 //   * MFMA operands are swapped (C^T = B^T A^T): four consecutive output channels per lane, 8- or 16-byte stores.
+#include <algorithm>
 #include <type_traits>
 
 #include "train_kernels.h"
@@ -67,7 +68,7 @@ __device__ __forceinline__ void store4(__bf16* p, f4& v)
 }
 __device__ __forceinline__ u4 round8(const f4& a, const f4& b)
 {
-    return join8(bf16x4{(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3]}, bf16x4{(__bf16)b[0], (__bf16)b[1], (__bf16)b[2], (__bf16)b[3]});
+    return u4{to_bf16x2(a[0], a[1]), to_bf16x2(a[2], a[3]), to_bf16x2(b[0], b[1]), to_bf16x2(b[2], b[3])};
 }
 
 // What one residue class of pixels needs (one class, the whole image, unless it is a strided data gradient)
@@ -96,12 +97,16 @@ __device__ __forceinline__ ClassGeo class_geo(const GeneralConvParams& p, int cl
 }
 
 // KG groups of WGM x WGN waves share a BMT x BN tile (wave tile BMT/WGM x BN/WGN): group kg multiplies slabs kg, kg + KG,
-// ..., and the groups' sums are joined in group order through LDS at the end.  One LDS buffer per group: the next slab
-// waits in registers while the current one is multiplied, two barriers per slab.
+// ..., and the groups' sums are joined in group order through LDS at the end.
+// NBUF = 1, one LDS buffer per group: the next slab waits in registers while the current one is multiplied, two barriers per
+// slab, and another workgroup or group fills the matrix cores meanwhile.  NBUF = 2, one workgroup of eight waves per compute
+// unit: slab t + 1 is split and written to the other buffer BETWEEN the matrix instructions of slab t (a matrix instruction
+// occupies its core for 32 clocks and the wave for 4), while slab t + 2 is on its way into a second set of registers;
+// one barrier per slab.
 // EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate.
 // GATHER: a convolution on the data set, whose few channels come in no 16-byte groups.  All taps and channels are one
 // contraction in the order of the weights, (tap, channel), and the source values are gathered one by one.
-template <typename T, int BMT, int BN, int WGM, int WGN, int KG, int EPI, bool GATHER>
+template <typename T, int BMT, int BN, int WGM, int WGN, int KG, int NBUF, int EPI, bool GATHER>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM * WGN * KG / 4) void conv_general_kernel(GeneralConvParams p)
 {
     constexpr bool kSplit = std::is_same<T, float>::value;
@@ -111,6 +116,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32;
     constexpr int NQA = BMT * GR / NT, NQB = (BN * CH + NT - 1) / NT;
     static_assert(NQA >= 1 && TM >= 1 && TN >= 1 && BMT * GR % NT == 0, "tile does not fit the thread count");
+    static_assert(NBUF == 1 || (KG == 1 && !GATHER), "two buffers: one group");
     constexpr unsigned A_BUF = BMT * kRow, GROUP = (BMT + BN) * kRow;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -197,9 +203,11 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
             tap = taps_left ? __builtin_ctz(taps_left) : 0;
         }
     };
-    f4 ra[NQA][2];                                    // (bf16: ra[q][0] holds the eight elements)
-    u4 rb[NQB];
-    auto load_tiles = [&]() {
+    struct Regs { f4 a[NQA][2]; u4 b[NQB]; };         // a slab on its way (bf16: a[q][0] holds the eight elements)
+    const Buffer abuf = buffer(abase, (unsigned)(p.B * p.H * p.W) * (unsigned)p.C * ES), wbuf = buffer(wbase, (unsigned)p.N * wrow);
+    auto load_tiles = [&](Regs& g, bool on) {         // (zeros unless on)
+        f4 (&ra)[NQA][2] = g.a;
+        u4 (&rb)[NQB] = g.b;
         if constexpr (GATHER) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -224,43 +232,40 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
         const int iy = tap / cg.nx, ix = tap - iy * cg.nx;
         const int c0 = ch * kSlab + ag * (kSplit ? 4 : 8);
         const unsigned delta = (unsigned)((iy * p.W + ix) * p.C + ch * kSlab) * ES;
-        const bool in0 = c0 < p.C, in1 = c0 + 16 < p.C;
+        const bool in0 = on && c0 < p.C, in1 = on && c0 + 16 < p.C;
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
-            ra[q][0] = f4{0.f, 0.f, 0.f, 0.f}; ra[q][1] = f4{0.f, 0.f, 0.f, 0.f};
             const bool ok = (tapmask[q] >> tap) & 1u;
             const unsigned o = aoff[q] + delta;
-            if (ok && in0) ra[q][0] = *reinterpret_cast<const f4*>(abase + o);
-            if (kSplit && ok && in1) ra[q][1] = *reinterpret_cast<const f4*>(abase + o + 64u);
+            ra[q][0] = __builtin_bit_cast(f4, ldb16(abuf, ok && in0 ? o : kOutside));
+            if (kSplit) ra[q][1] = __builtin_bit_cast(f4, ldb16(abuf, ok && in1 ? o + 64u : kOutside));
         }
         const int wt = (cg.wy0 + iy * p.wst) * p.S + cg.wx0 + ix * p.wst;
         const unsigned kb = (unsigned)((wt * cs + ch) * kSlabBytes);
 #pragma unroll
-        for (int q = 0; q < NQB; ++q) {
-            rb[q] = u4{0u, 0u, 0u, 0u};
-            if (b_ok[q]) rb[q] = ldg16(wbase, boff[q] + kb);
-        }
+        for (int q = 0; q < NQB; ++q) rb[q] = ldb16(wbuf, b_ok[q] && on ? boff[q] + kb : kOutside);
     };
-    auto store_weights = [&]() {
+    auto store_weights = [&](const Regs& g, unsigned at) {
 #pragma unroll
         for (int q = 0; q < NQB; ++q)
-            if (BN * CH % NT == 0 || tid + q * NT < BN * CH) *reinterpret_cast<u4*>(sBc + sb_st[q]) = rb[q];
+            if (BN * CH % NT == 0 || tid + q * NT < BN * CH) *reinterpret_cast<u4*>(sBc + at + sb_st[q]) = g.b[q];
     };
-    auto store_tiles = [&]() {
+    auto store_tiles = [&](const Regs& g, unsigned at) {
+        const f4 (&ra)[NQA][2] = g.a;
 #pragma unroll
         for (int q = 0; q < NQA; ++q) {
             if constexpr (kSplit) {
-                bf16x4 h0, m0_, l0, h1, m1, l1;
+                u2 h0, m0_, l0, h1, m1, l1;
                 split3(ra[q][0], h0, m0_, l0);
                 split3(ra[q][1], h1, m1, l1);
-                *reinterpret_cast<u4*>(sAc + sa_st[q]) = join8(h0, h1);
-                *reinterpret_cast<u4*>(sAc + sa_st[q] + 64) = join8(m0_, m1);
-                *reinterpret_cast<u4*>(sAc + sa_st[q] + 128) = join8(l0, l1);
+                *reinterpret_cast<u4*>(sAc + at + sa_st[q]) = join8(h0, h1);
+                *reinterpret_cast<u4*>(sAc + at + sa_st[q] + 64) = join8(m0_, m1);
+                *reinterpret_cast<u4*>(sAc + at + sa_st[q] + 128) = join8(l0, l1);
             } else {
-                *reinterpret_cast<f4*>(sAc + sa_st[q]) = ra[q][0];
+                *reinterpret_cast<f4*>(sAc + at + sa_st[q]) = ra[q][0];
             }
         }
-        store_weights();
+        store_weights(g, at);
     };
 
     f16 acc[TM][TN], low[TM][TN];                     // sums of the large and of the small products
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
 #pragma unroll
                 for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
     };
-    auto compute = [&]() {
+    auto compute = [&](unsigned at) {
 #pragma unroll
         for (int ks = 0; ks < kSlab / 16; ++ks) {
             constexpr int PL = Slab<T>::planes;
@@ -280,11 +285,11 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int s = 0; s < PL; ++s) a[i][s] = *reinterpret_cast<const bf16x8*>(sAc + a_rd + i * 32 * kRow + s * 64 + ks * 32);
+                for (int s = 0; s < PL; ++s) a[i][s] = *reinterpret_cast<const bf16x8*>(sAc + at + a_rd + i * 32 * kRow + s * 64 + ks * 32);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int s = 0; s < PL; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(sBc + b_rd + j * 32 * kRow + s * 64 + ks * 32);
+                for (int s = 0; s < PL; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(sBc + at + b_rd + j * 32 * kRow + s * 64 + ks * 32);
             // operands swapped: the accumulator holds the transposed tile.  Small products in ascending size.
             if constexpr (kSplit) {
                 constexpr int SA[5] = {0, 2, 1, 0, 1}, SB[5] = {2, 0, 1, 1, 0};
@@ -306,16 +311,39 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
 
     clear();
     start();
-    advance(kg);
     const int rounds = (nslab + KG - 1) / KG;
-    if (kg < nslab) load_tiles();
-    for (int t = 0; t < rounds; ++t) {
-        const int mine = t * KG + kg;
-        __syncthreads();                              // every wave is done reading the previous slab
-        if (mine < nslab) store_tiles();
+    if constexpr (NBUF == 1) {
+        Regs g;
+        advance(kg);
+        if (kg < nslab) load_tiles(g, true);
+        for (int t = 0; t < rounds; ++t) {
+            const int mine = t * KG + kg;
+            __syncthreads();                          // every wave is done reading the previous slab
+            if (mine < nslab) store_tiles(g, 0);
+            __syncthreads();
+            if (mine + KG < nslab) { advance(KG); load_tiles(g, true); }
+            if (mine < nslab) compute(0);
+        }
+    } else if (nslab > 0) {
+        Regs g0, g1;
+        load_tiles(g0, true);
+        store_tiles(g0, 0);
+        advance(1);
+        load_tiles(g0, nslab > 1);
         __syncthreads();
-        if (mine + KG < nslab) { advance(KG); load_tiles(); }
-        if (mine < nslab) compute();
+        // slab t is in buffer `at`, slab t + 1 in `have`; beyond the last slab zeros are loaded and stored, and not multiplied
+        auto step = [&](int t, unsigned at, const Regs& have, Regs& next) {
+            advance(1);
+            load_tiles(next, t + 2 < nslab);
+            store_tiles(have, GROUP - at);
+            compute(at);
+            __syncthreads();
+        };
+        for (int t = 0; t < nslab; t += 2) {
+            step(t, 0, g0, g1);
+            if (t + 1 >= nslab) break;
+            step(t + 1, GROUP, g1, g0);
+        }
     }
     if constexpr (kSplit) {
     float bad = 0.f;
@@ -331,19 +359,20 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
         clear();
         start();
         advance(kg);
+        Regs g;
         for (int t = 0; t < rounds; ++t) {
             const int mine = t * KG + kg;
             __syncthreads();
             if (mine < nslab) {
-                load_tiles();
+                load_tiles(g, true);
                 advance(KG);
 #pragma unroll
                 for (int q = 0; q < NQA; ++q) {
                     char* const dst = sAc + sa_st[q] + ag * 16;
-                    *reinterpret_cast<f4*>(dst) = ra[q][0];
-                    *reinterpret_cast<f4*>(dst + 16) = ra[q][1];
+                    *reinterpret_cast<f4*>(dst) = g.a[q][0];
+                    *reinterpret_cast<f4*>(dst + 16) = g.a[q][1];
                 }
-                store_weights();
+                store_weights(g, 0);
             }
             __syncthreads();
             if (mine < nslab) {
@@ -477,22 +506,23 @@ __device__ __forceinline__ void put_gradient(const f4& v, long long o, const Gen
 
 // GATHER: the source is the data set and its few channels come in no 16-byte groups; the four rows of a slot have a tap and a
 // channel each and are gathered one by one.  Tiles of 32 rows: the waves without a block only help to stage.
-template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, bool GATHER = false>
-__global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParams p)
+// One LDS buffer and two workgroups per compute unit: with two buffers and 256 x 128 tiles of eight waves (conv_general_kernel's
+// NBUF = 2) the transposing reads, at 90 bytes a clock, keep it from being faster (173 against 175 TFLOP/s on 16 replicas).
+template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, bool GATHER>
+__global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_general_kernel(GeneralWgradParams p)
 {
-    static_assert(WGM * WGN == 4 || (GATHER && WGM * WGN < 4), "four waves");
+    constexpr int NT = GATHER ? 256 : WGM * WGN * 64;
     constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32, BK = 32;
     constexpr bool kSplit = std::is_same<T, float>::value, kRound = !kSplit && std::is_same<SRC, float>::value;
     constexpr unsigned ES = sizeof(SRC);
     constexpr int PA = kPixelRow<T, BMT>, PB = kPixelRow<T, BN>;
     constexpr int GS = 16 / sizeof(T);                        // channels per group: 16 bytes
     constexpr int AG = BMT / GS, BG = BN / GS;                // groups per pixel
-    constexpr int AR = 256 / AG, BR = 256 / BG;               // pixels the threads cover per pass (more than a slab has: the rest idles)
+    constexpr int AR = NT / AG, BR = NT / BG;               // pixels the threads cover per pass (more than a slab has: the rest idles)
     constexpr int NQA = (BK + AR - 1) / AR, NQB = (BK + BR - 1) / BR;
-    static_assert(TM >= 1 && TN >= 1 && 256 % AG == 0 && 256 % BG == 0, "tile does not fit the thread count");
-    constexpr unsigned A_BUF = BK * PA, B_BUF = BK * PB;
-    constexpr unsigned STAGE = 4 * 32 * kStagePitch * 4 > BR * BN * 4 ? 4 * 32 * kStagePitch * 4 : BR * BN * 4;
-    __shared__ __attribute__((aligned(16))) char smem[A_BUF + B_BUF > STAGE ? A_BUF + B_BUF : STAGE];
+    static_assert(TM >= 1 && TN >= 1 && NT % AG == 0 && NT % BG == 0, "tile does not fit the thread count");
+    constexpr unsigned A_BUF = BK * PA;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     char* const sA = smem;                                    // [BK][PA]
     char* const sB = smem + A_BUF;                            // [BK][PB]
 
@@ -568,6 +598,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
             while (k < kend && !(p.posmask[k / p.B] & tile_tapbits)) k += BK;
         return k;
     };
+    const Buffer xbuf = buffer(xbase, (unsigned)(p.B * p.H * p.W) * pc), dbuf = buffer(dbase, (unsigned)p.K * (unsigned)p.N * (unsigned)sizeof(T));
     f4 ra[NQA], ra2[kRound ? NQA : 1], rb[NQB];              // (bf16 tensors: eight elements in the 16 bytes)
     float bsum[GS] = {};
     auto load_tiles = [&](int k0) {
@@ -579,39 +610,40 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
 #pragma unroll
             for (int q = 0; q < NQA; ++q) {
                 const int kr = arow + AR * q;
-                ra[q] = f4{0.f, 0.f, 0.f, 0.f};
-                if (in && k0 + kr < kend) ra[q] = *reinterpret_cast<const f4*>(xbase + ((unsigned)((bbase + kr) * hw + pos) * pc + a_shift));
+                ra[q] = __builtin_bit_cast(f4, ldb16(xbuf, in && k0 + kr < kend ? (unsigned)((bbase + kr) * hw + pos) * pc + a_shift : kOutside));
                 if constexpr (kRound) ra2[q] = f4{0.f, 0.f, 0.f, 0.f};            // (the data set has no position table)
             }
         } else {
 #pragma unroll
             for (int q = 0; q < NQA; ++q) {
-                ra[q] = f4{0.f, 0.f, 0.f, 0.f};
                 const bool in = a_ok && (unsigned)(py[q] - ylo) < (unsigned)yn && (unsigned)(px[q] - xlo) < (unsigned)xn;
                 const bool on = in && k0 + arow + AR * q < kend;
                 if constexpr (GATHER) {
+                    ra[q] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int yy = py[q] * p.stride + gy[e], xx = px[q] * p.stride + gx[e];
                         if (k0 + arow + AR * q < kend && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W)
                             ra[q][e] = *reinterpret_cast<const float*>(xbase + (poff[q] + gs[e]));     // (32-bit sum: gs may be negative)
                     }
-                } else if (on) ra[q] = *reinterpret_cast<const f4*>(xbase + poff[q]);
+                } else {
+                    ra[q] = __builtin_bit_cast(f4, ldb16(xbuf, on ? poff[q] : kOutside));
+                }
                 if constexpr (kRound) {
-                    ra2[q] = f4{0.f, 0.f, 0.f, 0.f};
-                    if (on) ra2[q] = *reinterpret_cast<const f4*>(xbase + poff[q] + 16u);
+                    ra2[q] = __builtin_bit_cast(f4, ldb16(xbuf, on ? poff[q] + 16u : kOutside));
                 }
                 px[q] += dx; py[q] += dyy; poff[q] += step;
-                if (px[q] >= p.Wo) { px[q] -= p.Wo; py[q] += 1; poff[q] += cx; }
-                if (py[q] >= p.Ho) { py[q] -= p.Ho; poff[q] += cy; }
+                const bool carry_x = px[q] >= p.Wo;
+                px[q] -= carry_x ? p.Wo : 0; py[q] += carry_x ? 1 : 0; poff[q] += carry_x ? cx : 0u;
+                const bool carry_y = py[q] >= p.Ho;
+                py[q] -= carry_y ? p.Ho : 0; poff[q] += carry_y ? cy : 0u;
             }
         }
 #pragma unroll
         for (int q = 0; q < NQB; ++q) {
             const int kr = brow + BR * q;
             const unsigned pix = p.perm ? (unsigned)((bbase + kr) * hw + pos) : (unsigned)(k0 + kr);
-            rb[q] = f4{0.f, 0.f, 0.f, 0.f};
-            if (b_ok && k0 + kr < kend) rb[q] = *reinterpret_cast<const f4*>(dbase + (pix * (unsigned)p.N + (unsigned)bn) * (unsigned)sizeof(T));
+            rb[q] = __builtin_bit_cast(f4, ldb16(dbuf, b_ok && k0 + kr < kend ? (pix * (unsigned)p.N + (unsigned)bn) * (unsigned)sizeof(T) : kOutside));
         }
     };
     const unsigned sa_st = (unsigned)(arow * PA + (tid % AG) * GS * 2), sb_st = (unsigned)(brow * PB + (tid % BG) * GS * 2);
@@ -620,9 +652,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
         for (int q = 0; q < NQA; ++q) {
             char* const o = sA + sa_st + AR * q * PA;
             if constexpr (kSplit) {
-                bf16x4 h, m, l;
+                u2 h, m, l;
                 split3(ra[q], h, m, l);
-                *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BMT * 2) = m; *reinterpret_cast<bf16x4*>(o + BMT * 4) = l;
+                *reinterpret_cast<u2*>(o) = h; *reinterpret_cast<u2*>(o + BMT * 2) = m; *reinterpret_cast<u2*>(o + BMT * 4) = l;
             } else if (AR <= BK || arow < BK) {
                 if constexpr (kRound) *reinterpret_cast<u4*>(o) = round8(ra[q], ra2[q]);
                 else *reinterpret_cast<f4*>(o) = ra[q];
@@ -632,20 +664,16 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
         for (int q = 0; q < NQB; ++q) {
             char* const o = sB + sb_st + BR * q * PB;
             if constexpr (kSplit) {
-                bf16x4 h, m, l;
+                u2 h, m, l;
                 split3(rb[q], h, m, l);
-                *reinterpret_cast<bf16x4*>(o) = h; *reinterpret_cast<bf16x4*>(o + BN * 2) = m; *reinterpret_cast<bf16x4*>(o + BN * 4) = l;
-                if (with_bias) {
+                *reinterpret_cast<u2*>(o) = h; *reinterpret_cast<u2*>(o + BN * 2) = m; *reinterpret_cast<u2*>(o + BN * 4) = l;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) bsum[e] += rb[q][e];
-                }
+                for (int e = 0; e < 4; ++e) bsum[e] += rb[q][e];          // (used by the tiles with the bias row only)
             } else if (BR <= BK || brow < BK) {
                 *reinterpret_cast<f4*>(o) = rb[q];
-                if (with_bias) {
-                    const bf16x8 v = __builtin_bit_cast(bf16x8, rb[q]);
+                const bf16x8 v = __builtin_bit_cast(bf16x8, rb[q]);
 #pragma unroll
-                    for (int e = 0; e < GS; ++e) bsum[e] += (float)v[e];
-                }
+                for (int e = 0; e < GS; ++e) bsum[e] += (float)v[e];
             }
         }
     };
@@ -663,16 +691,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
 #pragma unroll
                 for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
     };
-    clear();
-    int k0 = next_slab(kbeg);
-    seek(kbeg);
-    if (k0 < kend) load_tiles(k0);
-    while (k0 < kend) {
-        __syncthreads();                                      // every wave is done reading the previous slab
-        store_tiles();
-        __syncthreads();
-        k0 = next_slab(k0 + BK);
-        if (k0 < kend) load_tiles(k0);
+    auto compute = [&]() {
         if (mma)
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
@@ -702,6 +721,18 @@ __global__ __launch_bounds__(256, 2) void wgrad_general_kernel(GeneralWgradParam
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][0], a[i][0], acc[i][j], 0, 0, 0);
         }
+    };
+    clear();
+    int k0 = next_slab(kbeg);
+    seek(kbeg);
+    if (k0 < kend) load_tiles(k0);
+    while (k0 < kend) {
+        __syncthreads();                                      // every wave is done reading the previous slab
+        store_tiles();
+        __syncthreads();
+        k0 = next_slab(k0 + BK);
+        if (k0 < kend) load_tiles(k0);
+        compute();
     }
     if constexpr (kSplit) {
     float bad = 0.f;
@@ -847,13 +878,13 @@ __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
     }
 }
 
-template <typename T, int EPI, int BMT, int BN, int WGM, int WGN, int KG, bool GATHER = false>
+template <typename T, int EPI, int BMT, int BN, int WGM, int WGN, int KG, int NBUF = 1, bool GATHER = false>
 hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)
 {
-    constexpr size_t loop_lds = (size_t)KG * (BMT + BN) * Slab<T>::row, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
+    constexpr size_t loop_lds = (size_t)KG * NBUF * (BMT + BN) * Slab<T>::row, stat_lds = kStatLdsBytes<BN / WGN / 32, WGM, WGN>;
     constexpr size_t lds = loop_lds > stat_lds ? loop_lds : stat_lds;
     if (lds > 65536) {
-        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI, GATHER>,
+        static const bool ok = hipFuncSetAttribute((const void*)conv_general_kernel<T, BMT, BN, WGM, WGN, KG, NBUF, EPI, GATHER>,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
         if (!ok) return hipErrorInvalidValue;
     }
@@ -861,7 +892,7 @@ hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat
     const int rows0 = p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);     // largest class
     p.tiles_m = (rows0 + BMT - 1) / BMT;
     const dim3 grid(die_grid((long long)p.tiles_m * ((p.N + BN - 1) / BN) * p.classes * n_active)), block(WGM * WGN * KG * 64);
-    hipLaunchKernelGGL((conv_general_kernel<T, BMT, BN, WGM, WGN, KG, EPI, GATHER>), grid, block, lds, s, p);
+    hipLaunchKernelGGL((conv_general_kernel<T, BMT, BN, WGM, WGN, KG, NBUF, EPI, GATHER>), grid, block, lds, s, p);
     return hipGetLastError();
 }
 
@@ -870,44 +901,93 @@ hipError_t launch_conv(GeneralConvParams& p, int n_active, hipStream_t s, int* s
 {
     const long long rows0 = (long long)p.B * ((p.Ho + p.ostride - 1) / p.ostride) * ((p.Wo + p.ostride - 1) / p.ostride);
     const long long groups = (long long)p.classes * n_active;
-    const long long t64 = (rows0 + 63) / 64 * ((p.N + 63) / 64) * groups, t128 = (rows0 + 127) / 128 * ((p.N + 127) / 128) * groups;
-    // How many workgroups a tile size gives decides: a workgroup's time is the length of its K loop, so a launch that cannot
-    // fill 256 compute units takes smaller tiles and several groups of waves along K.  Measured with floats (us; 512 x 512
-    // channels, 3 x 3, batch 64; 2 x 2 images with 1 replica, 4 x 4 with 1, 4 x 4 with 4, 8 x 8 x 256 channels with 4, 4 x 4 with 16):
-    //   32 x 32, 8 groups:   43    85   319   373  1368         64 x 64, 1 group:    131   133   148   144   526
-    //   64 x 64, 4 groups:   73    76   162   179   637         128 x 128, 2 groups: 216   218   223   131   504
-    //   64 x 64, 2 groups:   91    94   139   147   536         128 x 128, 1 group:  262   267   272   149   448
     const bool large = p.tile_hint == 1;
-    if (!large && t64 <= 48) return launch_t<T, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
-    if (!large && t64 <= 256) return launch_t<T, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
-    if (!large && t64 <= 640) return launch_t<T, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
-    if (p.N <= 32) return launch_t<T, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
-    if (p.N > 64) {
-        if (large || t128 > 256) return launch_t<T, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
-        if (t64 > 880) return launch_t<T, EPI, 128, 128, 2, 2, 2>(p, n_active, s, stat_rows);
+    if constexpr (std::is_same<T, float>::value) {
+        // A launch's time is the length of its K loop while every compute unit has at most one workgroup, and the chip's
+        // throughput at that tile size once there are more, in whole rounds.  Per slab of 32 channels, measured in us on
+        // 3 x 3 layers of 64 to 512 channels, batch 64, 1 to 16 replicas: `alone` the loop step of a workgroup that has its
+        // unit to itself, `share` the unit's time per workgroup under load; about three slabs' time goes into the first
+        // loads and the epilogue.  The estimate's best is the measured best or within 6 % of it on those layers but for
+        // launches of some 10 us.  (512 channels, 4 x 4 images, 1 / 4 / 16 replicas: 64 x 64 in four groups 73 / 165 / 619 us,
+        // 128 x 64 133 / 140 / 432, 256 x 128 281 / 281 / 368.)
+        static constexpr struct { int m, n; float alone, share; } kTile[] = {
+            {32, 32, 0.28f, 0.37f}, {64, 64, 0.50f, 0.62f}, {64, 64, 0.61f, 0.46f}, {64, 64, 0.85f, 0.48f},
+            {128, 64, 0.92f, 0.83f}, {128, 64, 1.33f, 0.816f}, {128, 128, 1.22f, 1.50f}, {128, 128, 1.9f, 1.53f}, {256, 128, 1.95f, 2.83f}};
+        const float slabs = (float)(p.R * p.S * ((p.C + 31) / 32)) / (float)p.classes + 3.0f;
+        int best = 0;
+        float best_t = 0.f;
+        for (int i = 0; i < 9; ++i) {
+            if (p.N <= 64 && kTile[i].n > 64) continue;
+            const long long tiles = (rows0 + kTile[i].m - 1) / kTile[i].m * ((p.N + kTile[i].n - 1) / kTile[i].n) * groups;
+            const float step = tiles <= 256 ? kTile[i].alone : std::max(kTile[i].alone, (float)((tiles + 255) / 256) * kTile[i].share);
+            const float loaded = tiles > 128 && tiles <= 256 ? std::max(step, 0.9f * kTile[i].share) : step;
+            if (i == 0 || slabs * loaded < best_t) { best = i; best_t = slabs * loaded; }
+        }
+        if (p.N <= 32 && (large || best > 2)) return launch_t<T, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
+        if (large) best = p.N > 64 ? 8 : 5;
+        switch (best) {
+        case 0: return launch_t<T, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
+        case 1: return launch_t<T, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
+        case 2: return launch_t<T, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
+        case 3: return launch_t<T, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
+        case 4: return launch_t<T, EPI, 128, 64, 4, 2, 1, 2>(p, n_active, s, stat_rows);
+        case 5: return launch_t<T, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
+        case 6: return launch_t<T, EPI, 128, 128, 2, 4, 1, 2>(p, n_active, s, stat_rows);
+        case 7: return launch_t<T, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
+        default: return launch_t<T, EPI, 256, 128, 4, 2, 1, 2>(p, n_active, s, stat_rows);
+        }
+    } else {
+        // bf16 slabs are bound by their loads; the number of workgroups decides (within 10 % of the best of these and the
+        // two-buffer tiles on ResNet-18's strided layers, 1 to 16 replicas)
+        const long long t64 = (rows0 + 63) / 64 * ((p.N + 63) / 64) * groups, t128 = (rows0 + 127) / 128 * ((p.N + 127) / 128) * groups;
+        if (!large && t64 <= 48) return launch_t<T, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
+        if (!large && t64 <= 256) return launch_t<T, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
+        if (!large && t64 <= 640) return launch_t<T, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
+        if (p.N <= 32) return launch_t<T, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
+        if (p.N > 64) {
+            if (large || t128 > 256) return launch_t<T, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
+            if (t64 > 880) return launch_t<T, EPI, 128, 128, 2, 2, 2>(p, n_active, s, stat_rows);
+        }
+        if (p.N <= 64 && (large || t64 > 2048)) return launch_t<T, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
+        return launch_t<T, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
     }
-    if (p.N <= 64 && (large || t64 > 2048)) return launch_t<T, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
-    return launch_t<T, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
 }
 
 // 64 x 64 tiles where the larger ones are so few that even with the contraction split they leave compute units idle, or the
 // fused update of a tile (16 bytes per weight, one workgroup after the other through its rows) is what takes the time
 bool small_wgrad(int rows, int N, int n_active) { return N > 32 && (long long)(rows + 127) / 128 * ((N + 127) / 128) * n_active <= 64; }
 
+template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, bool GATHER = false>
+hipError_t launch_wgrad_t(const GeneralWgradParams& p, int n_active, hipStream_t s)
+{
+    constexpr int NT = GATHER ? 256 : WGM * WGN * 64, GS = 16 / sizeof(T);
+    constexpr size_t loop_lds = (size_t)32 * (kPixelRow<T, BMT> + kPixelRow<T, BN>);
+    constexpr size_t stage_lds = std::max<size_t>((size_t)NT / 64 * 32 * kStagePitch * 4, (size_t)NT / (BN / GS) * BN * 4);
+    constexpr size_t lds = std::max(loop_lds, stage_lds);
+    if (lds > 65536) {
+        static const bool ok = hipFuncSetAttribute((const void*)wgrad_general_kernel<T, SRC, BMT, BN, WGM, WGN, GATHER>,
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+        if (!ok) return hipErrorInvalidValue;
+    }
+    const long long tiles = (long long)((p.R * p.S * p.C + BMT - 1) / BMT) * ((p.N + BN - 1) / BN);
+    const dim3 grid(die_grid(tiles * p.splits * n_active)), block(NT);
+    hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, BMT, BN, WGM, WGN, GATHER>), grid, block, lds, s, p);
+    return hipGetLastError();
+}
+
 template <typename T, typename SRC>
 hipError_t launch_wgrad(const GeneralWgradParams& p, int n_active, hipStream_t s)
 {
     const bool gather = p.cursor && p.gather;
-    const dim3 grid(die_grid((long long)wgrad_general_tiles(p.R * p.S * p.C, p.N, n_active, gather) * p.splits * n_active)), block(256);
+    const int rows = p.R * p.S * p.C;
     if constexpr (std::is_same<T, float>::value) {
-        if (gather && p.N <= 32) { hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 32, 32, 1, 1, true>), grid, block, 0, s, p); return hipGetLastError(); }
-        if (gather) { hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 32, 64, 1, 2, true>), grid, block, 0, s, p); return hipGetLastError(); }
+        if (gather && p.N <= 32) return launch_wgrad_t<T, SRC, 32, 32, 1, 1, true>(p, n_active, s);
+        if (gather) return launch_wgrad_t<T, SRC, 32, 64, 1, 2, true>(p, n_active, s);
     }
-    if (small_wgrad(p.R * p.S * p.C, p.N, n_active)) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 64, 64, 2, 2>), grid, block, 0, s, p);
-    else if (p.N > 64) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 128, 2, 2>), grid, block, 0, s, p);
-    else if (p.N > 32) hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 64, 4, 1>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((wgrad_general_kernel<T, SRC, 128, 32, 4, 1>), grid, block, 0, s, p);
-    return hipGetLastError();
+    if (small_wgrad(rows, p.N, n_active)) return launch_wgrad_t<T, SRC, 64, 64, 2, 2>(p, n_active, s);
+    if (p.N > 64) return launch_wgrad_t<T, SRC, 128, 128, 2, 2>(p, n_active, s);
+    if (p.N > 32) return launch_wgrad_t<T, SRC, 128, 64, 4, 1>(p, n_active, s);
+    return launch_wgrad_t<T, SRC, 128, 32, 4, 1>(p, n_active, s);
 }
 
 }  // namespace
@@ -929,21 +1009,38 @@ hipError_t launch_conv_general(const GeneralConvParams& p0, int epi, int n_activ
         // leave units idle
         if (p.bf16 || epi != 0 || p.N % 4 != 0 || p.perm || p.classes != 1) return hipErrorInvalidValue;
         const long long rows = (long long)p.B * p.Ho * p.Wo;
-        if (p.N <= 32) return launch_t<float, 0, 128, 32, 4, 1, 1, true>(p, n_active, s, stat_rows);
-        if (rows / 128 * ((p.N + 63) / 64) * n_active < 512) return launch_t<float, 0, 64, 64, 2, 2, 1, true>(p, n_active, s, stat_rows);
-        return launch_t<float, 0, 128, 64, 4, 1, 1, true>(p, n_active, s, stat_rows);
+        if (p.N <= 32) return launch_t<float, 0, 128, 32, 4, 1, 1, 1, true>(p, n_active, s, stat_rows);
+        if (rows / 128 * ((p.N + 63) / 64) * n_active < 512) return launch_t<float, 0, 64, 64, 2, 2, 1, 1, true>(p, n_active, s, stat_rows);
+        return launch_t<float, 0, 128, 64, 4, 1, 1, 1, true>(p, n_active, s, stat_rows);
     }
     if (p.C % unit != 0 || p.N % 4 != 0 || p.R * p.S > 32 || (p.perm && p.classes != 1)) return hipErrorInvalidValue;
     if (!p.bf16) return epi == 0 ? launch_conv<float, 0>(p, n_active, s, stat_rows) : launch_conv<float, 1>(p, n_active, s, stat_rows);
     return epi == 0 ? launch_conv<__bf16, 0>(p, n_active, s, stat_rows) : launch_conv<__bf16, 1>(p, n_active, s, stat_rows);
 }
 
-int wgrad_general_tiles(int rows, int N, int n_active, int gather)
+// Split-K factor: the estimate of a launch's time with the least.  A workgroup walks K / s pixels in slabs of 32 (and about three
+// slabs' time of first loads and epilogue); per slab of a 128 x 128 tile 2.2 us when it has its compute unit to itself,
+// 2.7 when two share one, and 1.3 of the unit's time per workgroup in launches of more than two per unit, which end with half
+// a workgroup's time of partly filled units; smaller tiles in proportion `f`.  The partial sums move 8 bytes per weight and
+// split at 4 TB/s.  (Measured, 128 channels on 16 x 16 images, 16 replicas, s = 1 2 4 8 16 32: 1082 664 598 477 426 441 us;
+// 256 channels on 8 x 8, 4 replicas: 291 182 161 132 124 150.)
+int wgrad_general_splits(int rows, int N, int K, int n_active, int gather)
 {
-    if (gather) return (rows + 31) / 32 * ((N + (N <= 32 ? 31 : 63)) / (N <= 32 ? 32 : 64));
-    if (small_wgrad(rows, N, n_active)) return (rows + 63) / 64 * ((N + 63) / 64);
-    const int bn = N > 64 ? 128 : N > 32 ? 64 : 32;
-    return (rows + 127) / 128 * ((N + bn - 1) / bn);
+    int m = 128, n = N > 64 ? 128 : N > 32 ? 64 : 32;
+    float f = N > 64 ? 1.0f : N > 32 ? 0.62f : 0.45f;
+    if (gather) { m = 32; n = N > 32 ? 64 : 32; f = 0.25f; }
+    else if (small_wgrad(rows, N, n_active)) { m = n = 64; f = 0.4f; }
+    const float wgs = (float)((rows + m - 1) / m) * (float)((N + n - 1) / n) * (float)n_active;
+    const float moved = (float)rows * (float)N * (float)n_active * 8.0f / 4e6f;
+    int best = 1;
+    float best_t = 0.f;
+    for (int s = 1; s <= std::min(256, std::max(1, K / 128)); ++s) {
+        const float steps = ((float)K / (32.0f * (float)s) + 3.0f) * f, w = wgs * (float)s;
+        float t = w <= 256.f ? steps * 2.2f : w <= 512.f ? steps * 2.7f : w * steps * 1.3f / 256.f + 0.5f * steps * 2.2f;
+        if (s > 1) t += moved * (float)(s + 1);
+        if (s == 1 || t < best_t) { best = s; best_t = t; }
+    }
+    return best;
 }
 
 hipError_t launch_wgrad_general(const GeneralWgradParams& p0, int n_active, hipStream_t s)

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_update_kernel(const float* 
         f4 acc = {0.f, 0.f, 0.f, 0.f};
         if (i < count4 && sl < splits) {
             acc = __builtin_nontemporal_load(src + (long long)sl * stride4 + i);   // partial sums, parameters, momentum: each touched once
-#pragma unroll 4
+#pragma unroll 16
             for (int k = sl + LANES; k < splits; k += LANES) acc = acc + __builtin_nontemporal_load(src + (long long)k * stride4 + i);
         }
         if constexpr (LANES > 1) {
@@ -511,13 +511,13 @@ hipError_t launch_splitk_reduce(const float* partial, long long split_stride, in
 }
 
 hipError_t launch_splitk_reduce_update(const float* partial, long long split_stride, int splits, float* w, float* buf,
-                                       long long row_stride, long long count, float lr, float momentum, const int* order,
+                                       long long row_stride, long long count, float lr, float momentum, int one_chain, const int* order,
                                        int n_active, hipStream_t s)
 {
     if (n_active < 1 || count < 1) return hipSuccess;
     if (count % 4 != 0 || split_stride % 4 != 0 || row_stride % 4 != 0 ||
         (((uintptr_t)partial | (uintptr_t)w | (uintptr_t)buf) & 15) != 0) return hipErrorInvalidValue;
-    const bool shared = splits >= 16 && count / 4 * n_active < 256 * 256;
+    const bool shared = !one_chain && splits >= 16 && count / 4 * n_active < 256 * 256;
     const int per = shared ? 16 : 256;
     long long bx = (count / 4 + per - 1) / per;
     if (bx > 2048) bx = 2048;

@@ -964,12 +964,49 @@ __global__ __launch_bounds__(256) void sgd_kernel(SgdParams p)
     if (p.bump && blockIdx.x == 0 && threadIdx.x == 0) { p.cursor[rep] += 1; p.versions[rep] += 1; }
 }
 
+// Narrow dense layer (the classifier: out <= 16): one workgroup per sample row; threads stride over the input
+// features, keep `out` partial sums each and combine them with a fixed butterfly and a fixed LDS order.  Too small
+// for the matrix cores.  For long rows: 4096 features, 10 outputs, 64 rows 25 us, where dense_rows_fwd_kernel takes 40; 512
+// features 9 us and 5.
+template <int NMAX, typename T>
+__global__ __launch_bounds__(256) void dense_small_fwd_kernel(DenseSmallParams p)
+{
+    __shared__ float red[4][NMAX];
+    const int rep = p.order[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = blockIdx.x;
+    const T* x = tptr<T>(p.x, rep, p.x_rep) + (long long)m * p.K;
+    const float* w = p.w + rep * p.w_rep;
+    constexpr bool kRoundW = sizeof(T) == 2;      // bf16 configuration: weights take part rounded to bf16
+    float acc[NMAX];
+#pragma unroll
+    for (int n = 0; n < NMAX; ++n) acc[n] = 0.f;
+    for (int k = threadIdx.x; k < p.K; k += 256) {
+        const float xv = ldf(x, k);
+        const float* wr = w + (long long)k * p.N;
+#pragma unroll
+        for (int n = 0; n < NMAX; ++n) if (n < p.N) acc[n] += xv * (kRoundW ? (float)(__bf16)wr[n] : wr[n]);
+    }
+#pragma unroll
+    for (int n = 0; n < NMAX; ++n) {
+        float v = acc[n];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0) red[wave][n] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < p.N) {
+        const int n = threadIdx.x;
+        T* o = tptr<T>(p.out, rep, p.out_rep) + (long long)m * p.N;
+        stf(o, n, ((red[0][n] + red[1][n]) + (red[2][n] + red[3][n])) + (p.has_bias ? w[(long long)p.K * p.N + n] : 0.f));
+    }
+}
+
 // Forward of a dense layer with few rows: classifiers and layers on the data set.  A workgroup owns 32 rows x 32 outputs and its
 // sixteen waves share the contraction: a step is eight features, of which instruction e multiplies features e and 4 + e
 // (lanes of half 0 and half 1), so a lane's operand of a step is one 16-byte piece of its row; the weights are read as they
 // lie in the master.  Nothing passes through LDS but the waves' sums, added in wave order.  What bounds it is the latency of
-// K / 128 steps: 784 x 128 on 32 rows 5 us (generic tile kernel, one workgroup walking all of K: 77 us), 4096 x 10 on 64
-// rows 9 us (a workgroup per row with features over its threads: 25 us).
+// K / 128 steps: 784 x 128 on 32 rows 5 us (generic tile kernel, one workgroup walking all of K: 77 us).
 // SRC: type of x; float for T = __bf16 is the data set, rounded to bf16 like every operand of that configuration.
 template <typename T, typename SRC>
 __global__ __launch_bounds__(1024) void dense_rows_fwd_kernel(DenseRowsParams p)
@@ -1169,6 +1206,14 @@ hipError_t launch_maxpool_bwd(const EwParams& p, int n_active, hipStream_t s)
         if (p.bf16) hipLaunchKernelGGL(maxpool_bwd_kernel<__bf16>, ew_grid(p.count, n_active), dim3(256), 0, s, p);
         else hipLaunchKernelGGL(maxpool_bwd_kernel<float>, ew_grid(p.count, n_active), dim3(256), 0, s, p);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_dense_small_fwd(const DenseSmallParams& p, int n_active, hipStream_t s)
+{
+    if (n_active < 1 || p.rows < 1) return hipSuccess;
+    if (p.bf16) hipLaunchKernelGGL((dense_small_fwd_kernel<16, __bf16>), dim3((unsigned)p.rows, (unsigned)n_active), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((dense_small_fwd_kernel<16, float>), dim3((unsigned)p.rows, (unsigned)n_active), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

@@ -28,23 +28,35 @@ __device__ __forceinline__ u4 ldg16(const char* base, unsigned off) { return *re
 // Three bf16 values whose sum is the float: h = bf16(x), m = bf16(x - h), l = x - h - m.  The two differences are exact,
 // and what is left for l fits bf16's eight significant bits, so h + m + l = x for every finite x whose parts stay in
 // range; |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.
-__device__ __forceinline__ void split3(const f4& x, bf16x4& h, bf16x4& m, bf16x4& l)
+// Four at a time in pairs: a conversion yields two bf16 in one register, whose floats are a shift and a mask away.
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned to_bf16x2(float x, float y)
+{
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f2{x, y}), bf16x2));
+}
+__device__ __forceinline__ void split3(const f4& x, u2& h, u2& m, u2& l)
 {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = (__bf16)x[e];
-    f4 r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = x[e] - (float)h[e];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = (__bf16)r[e];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) l[e] = (__bf16)(r[e] - (float)m[e]);
+    for (int e = 0; e < 2; ++e) {
+        float a = x[2 * e], b = x[2 * e + 1];
+        h[e] = to_bf16x2(a, b);
+        a -= __builtin_bit_cast(float, h[e] << 16); b -= __builtin_bit_cast(float, h[e] & 0xffff0000u);
+        m[e] = to_bf16x2(a, b);
+        a -= __builtin_bit_cast(float, m[e] << 16); b -= __builtin_bit_cast(float, m[e] & 0xffff0000u);
+        l[e] = to_bf16x2(a, b);
+    }
 }
-__device__ __forceinline__ u4 join8(const bf16x4& a, const bf16x4& b)
+// Loads through a buffer descriptor: an offset outside the tensor (kOutside, or anything from `bytes` on) yields zeros, so
+// that padding costs a select instead of a branch.
+constexpr unsigned kOutside = 0xfffffff0u;
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer buffer(const void* base, unsigned bytes)
 {
-    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
-    return u4{x[0], x[1], y[0], y[1]};
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
 }
+__device__ __forceinline__ u4 ldb16(Buffer b, unsigned off) { return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, 0)); }
+__device__ __forceinline__ u4 join8(const u2& x, const u2& y) { return u4{x[0], x[1], y[0], y[1]}; }
 
 // Transposing LDS read: within a group of 16 lanes, lane i receives element (i % 4) of the 8 bytes addressed by lane
 // 4*j + i/4, for j = 0..3.  Pointing lane L at row k0 + L/4, columns 4*(L%4).. of a 16-column block therefore hands lane i

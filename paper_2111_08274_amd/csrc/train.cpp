@@ -114,11 +114,21 @@ bool lean_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 // The kernels of conv_general.hip take the other convolution and dense layers whose channels come in 16-byte groups, and in
 // fp32 the convolutions on the data set, gathered value by value (in bf16 those have kernels of their own).  Not narrow
 // classifiers, which have their own kernels too.  Offsets inside one replica's tensor are 32-bit byte offsets.
+// An fp32 network with convolutions and no batch norm amplifies the order of its sums: with the CNN workload's learning rate
+// one rounding of the initial weights moves the weights after two cycles by 2e-6 to 7e-5, and a run of it is reproducible
+// only in one order.  Such networks keep the kernels whose sums run along K in one chain (gemm.hip, dense_small_fwd).
+bool one_chain_net(const hadfl_config& cfg, const NetPlan& plan)
+{
+    bool conv = false, norm = false;
+    for (const Layer& l : plan.layers) { conv = conv || l.type == HADFL_OP_CONV; norm = norm || l.type == HADFL_OP_BN; }
+    return !cfg.bf16 && conv && !norm;
+}
+
 bool gather_layer(const hadfl_config& cfg, const Layer& l) { return !cfg.bf16 && l.type == HADFL_OP_CONV && l.in0 == 0; }
 
 bool general_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
-    if ((l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE) || lean_layer(cfg, plan, l)) return false;
+    if ((l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE) || lean_layer(cfg, plan, l) || one_chain_net(cfg, plan)) return false;
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
     const int64_t cin = conv ? a.c : a.numel(), taps = conv ? l.k * l.k : 1, unit = cfg.bf16 ? 8 : 4;
@@ -138,23 +148,19 @@ bool small_dense_layer(const Layer& l)
 }
 
 // Forward straight from the master weights: classifiers and the dense layers on the data set, whose copies no data gradient
-// would use
-bool dense_rows_layer(const Layer& l)
+// would use.  Classifiers on long rows have a workgroup per row instead (see the kernels).
+bool dense_rows_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
+    if (one_chain_net(cfg, plan) || (l.in0 != 0 && plan.tensors[l.in0].numel() >= 2048)) return false;
     return l.type == HADFL_OP_DENSE && (l.cout <= 16 || l.in0 == 0) && (!l.bias || l.b_off == l.w_off + l.w_count);
 }
 
-// Split-K factor of a general layer's weight gradient with n active replicas.  Measured on the ResNet-18 layers: a launch
-// wants two workgroups per compute unit (and not a few more) even if a split is then only 128 pixels long, and up to 2048
-// workgroups (an even last round) as long as a split keeps 1024 pixels; beyond that the partial sums cost more than they gain.
+// Split-K factor of a general layer's weight gradient with n active replicas
 int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
-    const int64_t K = (int64_t)cfg.batch * (conv ? r.h * r.w : 1);
-    const int64_t wgs = (int64_t)wgrad_general_tiles((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, n, gather_layer(cfg, l)) * n;
-    const int64_t fill = std::min<int64_t>(512 / wgs, K / 128), even = std::min<int64_t>(2048 / wgs, K / 1024);
-    return (int)std::max<int64_t>(1, std::max(fill, even));
+    return wgrad_general_splits((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
 }
 
 // floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels (tiles have at
@@ -218,7 +224,7 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
                 const TensorShape a = plan.tensors[l.in0];
                 const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
                 L.general[i] = 1;
-                if (dense_rows_layer(l)) continue;
+                if (dense_rows_layer(cfg, plan, l)) continue;
                 if (gather_layer(cfg, l)) {                            // all taps and channels in one contraction, no data gradient
                     L.wf_off[i] = woff; woff += up64(weight_copy_units(0, l.cout, 1, taps * cin));
                     continue;
@@ -290,7 +296,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             // and general layers read the copies, a layer on the data set has no data gradient
             const bool in_epilogue = e->fast[i] && e->splits[i] == 1;
             const bool in_reduce = e->splits[i] > 1 && (e->fast[i] || l.in0 == 0);
-            const bool small = small_dense_layer(l);        // its backward kernel applies the update, element by element
+            const bool small = small_dense_layer(l) && !one_chain_net(cfg, plan);        // its backward kernel applies the update, element by element
             if (!in_epilogue && !in_reduce && !e->general[i] && !small) continue;
             int64_t cnt = l.w_count + (l.bias ? l.cout : 0);      // bias sits directly behind the weights
             if (small) cnt = (cnt + 3) / 4 * 4;                   // (padding behind the slice: nothing there is ever updated)
@@ -594,7 +600,7 @@ struct Runner {
                     break;
                 }
             }
-            if (dense_rows_layer(l)) {
+            if (dense_rows_layer(e.cfg, e.plan, l)) {
                 DenseRowsParams d{};
                 d.x = act(l.in0); d.x_rep = e.rep_block; d.cursor = p.cursor; d.n_samples = p.n_samples; d.batch = p.batch;
                 d.w = p.w; d.w_rep = p.w_rep; d.out = actw(ot); d.out_rep = e.rep_block;
@@ -634,6 +640,12 @@ struct Runner {
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_general(f, 0, na, s, srows); });
+                break;
+            }
+            if (small_dense_layer(l) && !p.relu) {
+                DenseSmallParams d = dense_small(l, p);
+                d.out = actw(ot); d.out_rep = e.rep_block;
+                run("dense_small_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_dense_small_fwd(d, na, s); });
                 break;
             }
             run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return gemm(p); });
@@ -729,7 +741,7 @@ struct Runner {
         case HADFL_OP_DENSE: {
             // weight (and bias) gradient
             GemmParams p = gemm_base(l);
-            if (small_dense_layer(l) && e.fused_update[i]) {
+            if (small_dense_layer(l) && e.fused_update[i] && !one_chain_net(e.cfg, e.plan)) {
                 DenseSmallParams d = dense_small(l, p);
                 d.dy = grad(ot); d.dy_rep = e.rep_block; d.dx = grad(l.in0); d.dx_rep = e.rep_block;
                 d.mask = mask0; d.mask_rep = e.rep_block; d.accumulate = acc0;
@@ -809,7 +821,7 @@ struct Runner {
                 run("splitk_reduce", 0, 4.0 * mn * (p.splits + 4), [&] {
                     return launch_splitk_reduce_update(shared(), p.out_split, p.splits, e.buf.replicas + l.w_off,
                                                        e.buf.mom ? e.buf.mom + l.w_off : nullptr, e.plan.row_stride, mn, e.cfg.lr,
-                                                       e.cfg.momentum, e.buf.order, na, s); });
+                                                       e.cfg.momentum, one_chain_net(e.cfg, e.plan), e.buf.order, na, s); });
             else if (p.splits > 1)
                 run("splitk_reduce", 0, 4.0 * mn * (p.splits + 1), [&] { return launch_splitk_reduce(shared(), p.out_split, p.splits, e.buf.grad + l.w_off,
                                                                        e.plan.row_stride, mn, e.buf.order, na, s); });

@@ -41,9 +41,10 @@ hipError_t launch_gemm_bf16(const GemmParams& p, int n_active, hipStream_t s);
 hipError_t launch_splitk_reduce(const float* partial, long long split_stride, int splits, float* out, long long out_rep,
                                 long long count, const int* order, int n_active, hipStream_t s);
 // The same sum applied as the update of the layer's parameters (w, buf: first parameter of the layer in replica row 0;
-// buf may be null).  Needs count, split_stride and row_stride multiples of 4 and 16-byte aligned pointers.
+// buf may be null).  Needs count, split_stride and row_stride multiples of 4 and 16-byte aligned pointers.  one_chain: the
+// splits are added one after another, s ascending, whatever the launch size.
 hipError_t launch_splitk_reduce_update(const float* partial, long long split_stride, int splits, float* w, float* buf,
-                                       long long row_stride, long long count, float lr, float momentum, const int* order,
+                                       long long row_stride, long long count, float lr, float momentum, int one_chain, const int* order,
                                        int n_active, hipStream_t s);
 
 // ---- lean bf16 kernels for regular stride-1 "same" convolutions (conv_bf16_fast.hip) ----
@@ -155,7 +156,7 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
 };
 // Needs C and N multiples of 4 (bf16: 8), tensors of less than 4 GiB per replica.
 hipError_t launch_wgrad_general(const GeneralWgradParams& p, int n_active, hipStream_t s);
-int wgrad_general_tiles(int rows, int N, int n_active, int gather);              // workgroups per split and replica (rows = R*S*C)
+int wgrad_general_splits(int rows, int N, int K, int n_active, int gather);   // split-K factor for rows = R*S*C weights
 long long weight_copy_units(int bf16, int rows, int taps, int channels);   // 2-byte units of a copy [rows][taps][channels]
 struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
     const float* w; long long w_rep;
@@ -175,11 +176,12 @@ struct DenseRowsParams {      // out[m][n] = sum_k x[m][k] w[k][n] + bias[n]
 };
 hipError_t launch_dense_rows_fwd(const DenseRowsParams& p, int n_active, hipStream_t s);
 
-struct DenseSmallParams {     // backward of a dense layer with N <= 16 outputs:
+struct DenseSmallParams {     // dense layer with N <= 16 outputs.  Forward: out[m][n] = sum_k x[m][k] w[k][n] + bias[n].  Backward:
     // dx[m][k] (+)= sum_n dy[m][n] w[k][n], zero where mask <= 0; then w and buf (the momentum of these parameters, or
     // null; same stride) take the update of w's gradient sum_m x[m][k] dy[m][n]
     const float* x; long long x_rep;
     float* w; long long w_rep;           // weights [K][N] followed by bias [N]
+    float* out; long long out_rep;       // forward
     int rows, K, N, has_bias;
     int bf16;
     const int* order;
@@ -188,6 +190,7 @@ struct DenseSmallParams {     // backward of a dense layer with N <= 16 outputs:
     const float* mask; long long mask_rep; int accumulate;
     float* buf; float lr, momentum;
 };
+hipError_t launch_dense_small_fwd(const DenseSmallParams& p, int n_active, hipStream_t s);
 hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipStream_t s);
 
 struct EwParams {     // element-wise / pooling kernels

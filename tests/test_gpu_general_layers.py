@@ -27,7 +27,7 @@ def _nets():
     b.dense(b.gap(t), 5)
     c["residual"] = (b.array(), (10, 10, 3), 33)
     b = nets._Builder()                       # positions sorted by their taps, in both directions and the weight gradient
-    t = b.relu(b.conv(b.relu(b.conv(0, 32)), 128))
+    t = b.relu(b.conv(b.relu(b.bn(b.conv(0, 32))), 128))
     t = b.relu(b.conv(b.maxpool(t), 96, bias=False))
     b.dense(b.gap(t), 5)
     c["tables"] = (b.array(), (8, 6, 3), 64)
