@@ -12,14 +12,18 @@ constexpr int kAggThreads = 256;
 constexpr int kAggUnrollPlain = 2;  // float4 chunks per thread: 2*NP loads of 16 bytes in flight
 constexpr int kAggUnrollBcast = 4;  // (the broadcast rows are written with plain stores: 4 % faster than non-temporal ones there)
 
+// NP > 0: that many rows, all their loads in flight at once.  NP = 0: any number of rows, eight at a time with all their loads
+// in flight (a row after the other was a chain of load latencies: 12 of 24 rows of 1 M, every row written, 45 us; now 22 us
+// = 6.7 TB/s).  The sum runs in the order of the list either way.
+template <int NP, bool BCAST> constexpr int kAggUnrollFor = BCAST && NP > 0 ? kAggUnrollBcast : kAggUnrollPlain;
+
 // BCAST: the result is also written to n_bcast replica rows (a kernel name of its own in traces)
-template <int NP, bool BCAST, int kAggUnroll = BCAST ? kAggUnrollBcast : kAggUnrollPlain>
+template <int NP, bool BCAST, int kAggUnroll = kAggUnrollFor<NP, BCAST>>
 __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(
     const float* rows, int64_t row_stride, int64_t n4, const int32_t* __restrict__ sel,
     const float* __restrict__ wgt, int n_select, float* __restrict__ agg, int n_bcast, float* rows_out,
     const int32_t* __restrict__ bcast_list)
 {
-    const int np = NP > 0 ? NP : n_select;
     const int64_t base = ((int64_t)blockIdx.x * kAggUnroll) * kAggThreads + threadIdx.x;
     if (NP > 0) {
         const f4* src[NP > 0 ? NP : 1];
@@ -52,17 +56,43 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(
             }
         }
     } else {
+        constexpr int CH = 8;
+        f4 acc[kAggUnroll];
+        for (int i0 = 0; i0 < n_select; i0 += CH) {
+            f4 v[kAggUnroll][CH];
+            float a[CH];
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int r = i0 + i < n_select ? i0 + i : n_select - 1;
+                const f4* const src = reinterpret_cast<const f4*>(rows + (int64_t)sel[r] * row_stride);
+                a[i] = wgt[r];
+#pragma unroll
+                for (int u = 0; u < kAggUnroll; ++u) {
+                    const int64_t j = base + (int64_t)u * kAggThreads;
+                    if (j < n4 && i0 + i < n_select) v[u][i] = __builtin_nontemporal_load(src + j);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                if (i0 + i >= n_select) break;
+#pragma unroll
+                for (int u = 0; u < kAggUnroll; ++u) acc[u] = i0 + i == 0 ? v[u][i] * a[i] : acc[u] + v[u][i] * a[i];
+            }
+        }
+#pragma unroll
         for (int u = 0; u < kAggUnroll; ++u) {
             const int64_t j = base + (int64_t)u * kAggThreads;
-            if (j >= n4) continue;
-            f4 acc = __builtin_nontemporal_load(reinterpret_cast<const f4*>(rows + (int64_t)sel[0] * row_stride) + j) * wgt[0];
-            for (int i = 1; i < np; ++i)
-                acc = acc + __builtin_nontemporal_load(reinterpret_cast<const f4*>(rows + (int64_t)sel[i] * row_stride) + j) * wgt[i];
-            __builtin_nontemporal_store(acc, reinterpret_cast<f4*>(agg) + j);
-            if (BCAST)
-                for (int r = 0; r < n_bcast; ++r)
-                    __builtin_nontemporal_store(acc, reinterpret_cast<f4*>(rows_out + (int64_t)(bcast_list ? bcast_list[r] : r) * row_stride) + j);
+            if (j < n4) __builtin_nontemporal_store(acc[u], reinterpret_cast<f4*>(agg) + j);
         }
+        if (BCAST)
+            for (int r = 0; r < n_bcast; ++r) {
+                f4* const dst = reinterpret_cast<f4*>(rows_out + (int64_t)(bcast_list ? bcast_list[r] : r) * row_stride);
+#pragma unroll
+                for (int u = 0; u < kAggUnroll; ++u) {
+                    const int64_t j = base + (int64_t)u * kAggThreads;
+                    if (j < n4) dst[j] = acc[u];
+                }
+            }
     }
 }
 
@@ -98,9 +128,10 @@ hipError_t launch_aggregate(const float* rows, int64_t row_stride, int64_t len, 
                             const int32_t* bcast_list, hipStream_t s)
 {
     const int64_t n4 = len / 4;
-    const int64_t per_block = (int64_t)kAggThreads * (n_bcast > 0 ? kAggUnrollBcast : kAggUnrollPlain);
-    const dim3 grid((unsigned)((n4 + per_block - 1) / per_block)), block(kAggThreads);
+    const dim3 block(kAggThreads);
 #define HADFL_AGG(NP) do { \
+        const int64_t per_block = (int64_t)kAggThreads * (n_bcast > 0 ? kAggUnrollFor<NP, true> : kAggUnrollFor<NP, false>); \
+        const dim3 grid((unsigned)((n4 + per_block - 1) / per_block)); \
         if (n_bcast > 0) hipLaunchKernelGGL((aggregate_kernel<NP, true>), grid, block, 0, s, rows, row_stride, n4, sel_sorted, \
                                             sel_weight, n_select, agg, n_bcast, rows_out, bcast_list); \
         else hipLaunchKernelGGL((aggregate_kernel<NP, false>), grid, block, 0, s, rows, row_stride, n4, sel_sorted, \

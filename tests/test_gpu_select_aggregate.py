@@ -183,3 +183,9 @@ def test_aggregation_stress_workload_full_size():
             exact = oracle.aggregate_f32(sampled, oracle.aggregation_weights(oflag))
             assert np.abs(got.astype(np.float64) - exact).max() <= tol, cycle
     ctx.close()
+
+
+@pytest.mark.parametrize("N,n_select,m", [(10, 9, 515), (17, 16, 2049), (20, 17, 70001)])
+def test_aggregate_in_chunks_of_rows(N, n_select, m):
+    """More rows than the kernels with a fixed count take: one and more chunks of eight, full and ragged."""
+    test_aggregate_matches_fp64_sum_and_resync_copies_it(N, n_select, m)
