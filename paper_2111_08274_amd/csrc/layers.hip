@@ -660,6 +660,7 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_vec_kernel(BnParams p)
     if (!g.live) return;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     T* y = tptr<T>(p.y, rep, p.y_rep);
+    const T* add = p.add ? tptr<T>(p.add, rep, p.add_rep) : nullptr;
     const float* row = p.params + rep * p.row_stride;
     float sc[VEC], sh[VEC];
     const float* sv = p.saved + rep * p.saved_rep;
@@ -676,6 +677,12 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_vec_kernel(BnParams p)
         ldv(x, i, v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = bn_value(v[e], sc[e], sh[e], p.relu != 0);
+        if (add) {                                        // the sum of two tensors that follows, with its ReLU
+            float w[VEC];
+            ldv(add, i, w);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { const float u = (float)(T)v[e] + w[e]; v[e] = p.add_relu ? fmaxf(u, 0.f) : u; }
+        }
         stv(y, i, v);
     }
 }
@@ -1266,7 +1273,7 @@ hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
         }
         return hipGetLastError();
     }
-    if (p.pool || p.stats_done) return hipErrorInvalidValue;  // the caller asks for these only where the vector kernels apply
+    if (p.pool || p.stats_done || p.add) return hipErrorInvalidValue;  // the caller asks for these only where the vector kernels apply
     const dim3 grid((unsigned)(p.chunks * ((p.C + 63) / 64)), (unsigned)n_active);
     if (p.bf16) {
         hipLaunchKernelGGL((bn_reduce_kernel<0, __bf16>), grid, block, 0, s, p);

@@ -41,6 +41,11 @@ public:
     // BN kernels: forward writes the pooled tensor as well, backward forms the full-resolution gradient on the fly from
     // the pooled gradient.  The pool layer itself issues nothing.
     std::vector<int> pool_of;             // per layer: index of the folded pool layer, or -1
+    // Sum fusion: the addition of two tensors behind a batch norm that is only read there runs in that BN's forward store (the
+    // second of two such BNs: the other operand exists by then).  Its backward pass copies the gradient to both operands,
+    // but for those with no ReLU mask and no other reader: their gradient IS the sum's, and shares its buffer.
+    std::vector<int> add_into;            // per layer (BN): the ADD layer folded into its forward store, or -1
+    std::vector<char> add_done;           // per layer (ADD): forward folded away
     // Statistics fusion: a lean or general convolution whose output feeds a batch norm only leaves the per-channel
     // sums of its output in the BN partial region, and that BN's forward skips its own sums pass.
     std::vector<int> stat_for;            // per layer: the BN layer fed by this convolution's statistics, or -1
@@ -364,6 +369,20 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             if (t.c % vec != 0 || t.h % 2 != 0 || t.w % 2 != 0) continue;
             e->pool_of[i] = j; e->skip[j] = 1;
         }
+        e->add_into.assign(nl, -1); e->add_done.assign(nl, 0);
+        for (int j = nl; j-- > 0;) {
+            const Layer& q = plan.layers[j];
+            if (q.type != HADFL_OP_ADD || q.in0 == q.in1) continue;
+            for (int side = 0; side < 2; ++side) {
+                const int t = side ? q.in1 : q.in0, other = side ? q.in0 : q.in1;
+                if (t < 1 || consumers[t] != 1) continue;
+                if (!e->masked[t]) e->grad_off[t] = e->grad_off[e->out_tensor[j]];
+                const int i = t - 1;
+                if (plan.layers[i].type == HADFL_OP_BN && !e->fused_relu[i] && e->pool_of[i] < 0 && other < t && plan.tensors[t].c % vec == 0) {
+                    e->add_into[i] = j; e->add_done[j] = 1;
+                }
+            }
+        }
         e->bstat_for.assign(nl, -1); e->bstat_rows.assign(nl, 0); e->bstat_rep.assign(nl, 0);
         if (cfg.bf16)
             for (int k = 0; k < nl; ++k) {
@@ -653,6 +672,7 @@ struct Runner {
         case HADFL_OP_RELU: run("relu_fwd", 0, asz() * (8.0 * q.count), [&] { return launch_relu_fwd(q, na, s); }); break;
         case HADFL_OP_MAXPOOL: run("maxpool_fwd", 0, asz() * (4.0 * (B * a.numel() + q.count)), [&] { return launch_maxpool_fwd(q, na, s); }); break;
         case HADFL_OP_ADD:
+            if (e.add_done[i]) break;
             q.in2 = act(l.in1); q.in2_rep = e.rep_block;
             run("add_fwd", 0, asz() * (12.0 * q.count), [&] { return launch_add_fwd(q, na, s); });
             break;
@@ -670,7 +690,13 @@ struct Runner {
                 b.pool = 1; b.H = a.h; b.W = a.w;
                 b.pool_out = actw(e.plan.layers[e.pool_of[i]].out); b.pool_out_rep = e.rep_block;
             }
-            run("bn_fwd", 0, asz() * (8.0 * B * a.numel()), [&] { return launch_bn_fwd(b, na, s); });
+            const int j = e.add_into[i];
+            if (j >= 0) {
+                const Layer& sum = e.plan.layers[j];
+                b.add = act(sum.in0 == l.out ? sum.in1 : sum.in0); b.add_rep = e.rep_block; b.add_relu = e.fused_relu[j];
+                b.y = actw(e.out_tensor[j]);
+            }
+            run("bn_fwd", 0, asz() * ((j >= 0 ? 12.0 : 8.0) * B * a.numel()), [&] { return launch_bn_fwd(b, na, s); });
             break; }
         }
     }
@@ -877,12 +903,13 @@ struct Runner {
             break;
         case HADFL_OP_ADD: {
             q.in = grad(ot); q.in_rep = e.rep_block; q.count = B * a.numel();
-            run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q, na, s); });
+            const int64_t own = e.grad_off[ot];                // operands that share this buffer need no copy
+            if (e.grad_off[l.in0] != own) run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q, na, s); });
             EwParams q2 = q;
             if (l.in1 == l.in0) q2.accumulate = 1; else q2.accumulate = e.grad_written[l.in1] ? 1 : 0;
             q2.out = grad(l.in1);
             q2.mask = e.masked[l.in1] ? act(l.in1) : nullptr;
-            run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q2, na, s); });
+            if (e.grad_off[l.in1] != own) run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q2, na, s); });
             e.grad_written[l.in1] = 1;
             break; }
         case HADFL_OP_GAP:

@@ -245,6 +245,9 @@ struct BnParams {
     // backward: the data-gradient kernel of the layer above already left per-entry sums of g and g * y in `partial`
     // ([stat_entries][2][C], see FastConvParams::stat_y); the sums pass is skipped and d(gamma) is formed from them
     int bwd_stats_done;
+    // forward, optional (vector kernels, no pool): y = max(bn(x) + add, 0) or without the ReLU, bn(x) rounded to the stored
+    // type first as if it were stored: the layer that adds a second tensor to this one's output, folded in
+    const float* add; long long add_rep; int add_relu;
     float* pool_out; long long pool_out_rep;
     const float* pool_g; long long pool_g_rep;
 };

@@ -45,6 +45,15 @@ def _nets():
         b = nets._Builder()
         b.dense(b.gap(b.relu(b.bn(b.conv(b.relu(b.conv(0, cout, k=5, stride=2, pad=pad)), 8, bias=False)))), 5)
         c["first%d" % ch] = (b.array(), (11, 14, ch), 21)
+    b = nets._Builder()                       # sums: of two convolutions, of a sum, without a ReLU, of one tensor twice, of a normalised tensor read twice
+    t = b.relu(b.bn(b.conv(0, 16, bias=False)))
+    u = b.add(b.conv(t, 16), b.conv(t, 16, k=1, pad=0))
+    v = b.add(b.bn(b.conv(u, 16, bias=False)), u)
+    w = b.bn(b.conv(b.relu(v), 16, bias=False))
+    x = b.relu(b.add(b.add(w, w), b.bn(b.conv(w, 16, bias=False))))
+    y = b.add(b.bn(b.conv(x, 16, k=1, pad=0)), b.bn(b.conv(x, 16, bias=False)))
+    b.dense(b.gap(y), 5)
+    c["sums"] = (b.array(), (6, 8, 3), 16)
     return c
 
 
@@ -53,7 +62,7 @@ NETS = _nets()
 
 @pytest.mark.parametrize("hint", [0, 1])
 @pytest.mark.parametrize("replicas", [2, 9])
-@pytest.mark.parametrize("name,bf16", [(n, False) for n in sorted(NETS)] + [(n, True) for n in sorted(NETS) if n in ("eights", "residual", "tables", "dense")])
+@pytest.mark.parametrize("name,bf16", [(n, False) for n in sorted(NETS)] + [(n, True) for n in sorted(NETS) if n in ("eights", "residual", "tables", "dense", "sums")])
 def test_general_layers_against_oracle(name, bf16, replicas, hint):
     """Every tensor's update of every step against the oracle.  Two and nine replicas put the launches on both sides of the
     tile rules (a few workgroups with several wave groups along K; one group), hint 1 takes the largest tiles."""
