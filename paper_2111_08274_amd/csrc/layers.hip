@@ -918,6 +918,170 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_pool_vec_kernel(BnParams p)
     }
 }
 
+// ---- batch norm of a small tensor in one launch ----
+// A workgroup of 1024 threads owns 4 channel vectors of one replica over all rows: sums, statistics and the normalised output
+// (backward: sums, gradients and the data gradient), the second pass reading what the first left in the die's L2.  Three
+// dependent launches of 5 to 6 us each are what such a layer's backward pass otherwise costs (80 channels on 1250 rows, 5
+// replicas: 17 us and the gaps; here 9), two its forward pass where the convolution left the sums (10 and a gap; here
+// 10).  512 channels on 1024 rows, 4 replicas, 2 M values: 29 us, no better than three launches, hence the limit in bn_small().
+constexpr int kBnSmallThreads = 1024, kBnSmallWaves = kBnSmallThreads / 64;
+
+// Totals over the row lanes of one channel vector, in every thread: xor-shuffles inside the waves, the waves in order by one
+// thread per value.
+constexpr int kBnSmallCvb = 4;                                // channel vectors per workgroup: 64 bytes of a row
+template <int N>
+__device__ __forceinline__ void bn_small_total(float (&v)[N], float (*red)[kBnSmallCvb][N], int cvb)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cv = threadIdx.x % cvb;
+    for (int off = cvb; off < 64; off <<= 1)
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[e] += __shfl_xor(v[e], off, 64);
+    if (lane < cvb)
+#pragma unroll
+        for (int e = 0; e < N; ++e) red[wave][cv][e] = v[e];
+    __syncthreads();
+    if ((int)threadIdx.x < cvb * N) {
+        const int c = threadIdx.x / N, e = threadIdx.x % N;
+        float t = red[0][c][e];
+#pragma unroll
+        for (int w = 1; w < kBnSmallWaves; ++w) t += red[w][c][e];
+        red[0][c][e] = t;                                     // (read by this thread only until the barrier)
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = red[0][cv][e];
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams p)
+{
+    constexpr int VEC = VecOf<T>::n;
+    __shared__ __attribute__((aligned(16))) float red[kBnSmallWaves][kBnSmallCvb][2 * VEC];
+    const int gi = blockIdx.y, rep = p.order[gi];
+    const int CV = p.C / VEC, cv = blockIdx.x * p.cvb + threadIdx.x % p.cvb, rl = threadIdx.x / p.cvb, lanes = kBnSmallThreads / p.cvb;
+    const bool live = cv < CV;
+    const int c0 = live ? cv * VEC : 0;
+    const T* x = tptr<T>(p.x, rep, p.x_rep);
+    float x0[VEC], t[2 * VEC];                                // the shift the sums are taken with; sums of d and d^2
+#pragma unroll
+    for (int e = 0; e < 2 * VEC; ++e) t[e] = 0.f;
+    if (p.stats_done) {
+        const float* part = p.partial + gi * p.partial_rep;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) x0[e] = p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c0 + e] : 0.f;
+        if (live)
+            for (int k = rl; k < p.stat_entries; k += lanes)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) { t[e] += part[(long long)k * 2 * p.C + c0 + e]; t[VEC + e] += part[(long long)k * 2 * p.C + p.C + c0 + e]; }
+    } else {
+        ldv(x, c0, x0);
+        if (live)
+#pragma unroll 4
+            for (int r = rl; r < p.rows; r += lanes) {
+                float v[VEC];
+                ldv(x, (long long)r * p.C + c0, v);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) { const float d = v[e] - x0[e]; t[e] += d; t[VEC + e] += d * d; }
+            }
+    }
+    bn_small_total(t, red, p.cvb);
+    if (!live) return;
+    const float n = (float)p.rows;
+    float* row = p.params + rep * p.row_stride;
+    float sc[VEC], sh[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {                           // as in bn_finalize_kernel<0>
+        const int c = c0 + e;
+        const float md = t[e] / n, cen = fmaxf(t[VEC + e] - t[e] * md, 0.f), mean = x0[e] + md, var = cen / n, istd = 1.0f / sqrtf(var + kBnEps);
+        if (rl == 0) {
+            float* sv = p.saved + rep * p.saved_rep;
+            sv[c] = mean; sv[p.C + c] = istd;
+            const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
+            float* rm = row + p.stat_off;
+            rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * mean;
+            rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
+        }
+        bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
+    }
+    T* y = tptr<T>(p.y, rep, p.y_rep);
+    const T* add = p.add ? tptr<T>(p.add, rep, p.add_rep) : nullptr;
+#pragma unroll 4
+    for (int r = rl; r < p.rows; r += lanes) {
+        const long long i = (long long)r * p.C + c0;
+        float v[VEC];
+        ldv(x, i, v);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = bn_value(v[e], sc[e], sh[e], p.relu != 0);
+        if (add) {
+            float w[VEC];
+            ldv(add, i, w);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { const float u = (float)(T)v[e] + w[e]; v[e] = p.add_relu ? fmaxf(u, 0.f) : u; }
+        }
+        stv(y, i, v);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBnSmallThreads) void bn_small_bwd_kernel(BnParams p)
+{
+    constexpr int VEC = VecOf<T>::n;
+    __shared__ __attribute__((aligned(16))) float red[kBnSmallWaves][kBnSmallCvb][2 * VEC];
+    const int gi = blockIdx.y, rep = p.order[gi];
+    const int CV = p.C / VEC, cv = blockIdx.x * p.cvb + threadIdx.x % p.cvb, rl = threadIdx.x / p.cvb, lanes = kBnSmallThreads / p.cvb;
+    const bool live = cv < CV;
+    const int c0 = live ? cv * VEC : 0;
+    const T* x = tptr<T>(p.x, rep, p.x_rep);
+    const T* dy = tptr<T>(p.dy, rep, p.dy_rep);
+    const float* sv = p.saved + rep * p.saved_rep;
+    float mean[VEC], istd[VEC], t[2 * VEC];                   // sums of dy and dy * xhat
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { mean[e] = sv[c0 + e]; istd[e] = sv[p.C + c0 + e]; t[e] = 0.f; t[VEC + e] = 0.f; }
+    if (live)
+#pragma unroll 4
+        for (int r = rl; r < p.rows; r += lanes) {
+            float v[VEC], d[VEC];
+            ldv(x, (long long)r * p.C + c0, v);
+            ldv(dy, (long long)r * p.C + c0, d);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { t[e] += d[e]; t[VEC + e] += d[e] * ((v[e] - mean[e]) * istd[e]); }
+        }
+    bn_small_total(t, red, p.cvb);
+    if (!live) return;
+    const float inv_n = 1.0f / (float)p.rows;
+    float k1[VEC], kb[VEC], kg[VEC];
+    float* gr = p.grads + rep * p.row_stride + p.w_off;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        if (rl == 0) { gr[c0 + e] = t[VEC + e]; gr[p.C + c0 + e] = t[e]; }
+        k1[e] = p.params[rep * p.row_stride + p.w_off + c0 + e] * istd[e];
+        kb[e] = t[e] * inv_n; kg[e] = t[VEC + e] * inv_n;
+    }
+    T* dx = tptr<T>(p.y, rep, p.y_rep);
+    const T* mask = p.mask ? tptr<T>(p.mask, rep, p.mask_rep) : nullptr;
+#pragma unroll 4
+    for (int r = rl; r < p.rows; r += lanes) {
+        const long long i = (long long)r * p.C + c0;
+        float v[VEC], d[VEC], o[VEC];
+        ldv(x, i, v); ldv(dy, i, d);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o[e] = k1[e] * (d[e] - kb[e] - ((v[e] - mean[e]) * istd[e]) * kg[e]);
+        if (mask) {
+            float mk[VEC];
+            ldv(mask, i, mk);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) if (!(mk[e] > 0.f)) o[e] = 0.f;
+        }
+        if (p.accumulate) {
+            float old[VEC];
+            ldv(dx, i, old);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) o[e] += old[e];
+        }
+        stv(dx, i, o);
+    }
+}
+
 // One workgroup per replica, one thread per sample: softmax, loss, d(loss)/d(logits); loss summed by an LDS tree.
 template <typename T>
 __global__ __launch_bounds__(1024) void softmax_ce_kernel(LossParams p)
@@ -1247,6 +1411,14 @@ hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipSt
 namespace {
 // channel vectors per workgroup: the largest power of two that is at most min(C / vec, 32)
 int bn_cvb(int C, int vec) { int cv = C / vec, b = 1; while (b * 2 <= cv && b * 2 <= 32) b *= 2; return b; }
+// One launch for the whole layer: few rows, so that a workgroup's two walks over them take no longer than the launches saved,
+// and a tensor that the few workgroups can move in that time
+bool bn_small(const BnParams& p, int n_active) { return !p.pool && p.rows <= 2048 && (long long)p.rows * p.C * n_active <= (1 << 20); }
+dim3 bn_small_grid(BnParams& p, int vec, int n_active)
+{
+    p.cvb = std::min(kBnSmallCvb, bn_cvb(p.C, vec));
+    return dim3((unsigned)((p.C / vec + p.cvb - 1) / p.cvb), (unsigned)n_active);
+}
 }  // namespace
 
 hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
@@ -1255,6 +1427,12 @@ hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
     BnParams p = p0;
     const int vec = p.bf16 ? 8 : 4;
     const dim3 block(256);
+    if (p.C % vec == 0 && bn_small(p, n_active)) {
+        const dim3 grid = bn_small_grid(p, vec, n_active);
+        if (p.bf16) hipLaunchKernelGGL(bn_small_fwd_kernel<__bf16>, grid, dim3(kBnSmallThreads), 0, s, p);
+        else hipLaunchKernelGGL(bn_small_fwd_kernel<float>, grid, dim3(kBnSmallThreads), 0, s, p);
+        return hipGetLastError();
+    }
     if (p.C % vec == 0) {
         p.cvb = bn_cvb(p.C, vec);
         const int cgroups = (p.C / vec + p.cvb - 1) / p.cvb;
@@ -1293,6 +1471,12 @@ hipError_t launch_bn_bwd(const BnParams& p0, int n_active, hipStream_t s)
     BnParams p = p0;
     const int vec = p.bf16 ? 8 : 4;
     const dim3 block(256);
+    if (p.C % vec == 0 && !p.bwd_stats_done && bn_small(p, n_active)) {
+        const dim3 grid = bn_small_grid(p, vec, n_active);
+        if (p.bf16) hipLaunchKernelGGL(bn_small_bwd_kernel<__bf16>, grid, dim3(kBnSmallThreads), 0, s, p);
+        else hipLaunchKernelGGL(bn_small_bwd_kernel<float>, grid, dim3(kBnSmallThreads), 0, s, p);
+        return hipGetLastError();
+    }
     if (p.C % vec == 0) {
         p.cvb = bn_cvb(p.C, vec);
         const int cgroups = (p.C / vec + p.cvb - 1) / p.cvb;
