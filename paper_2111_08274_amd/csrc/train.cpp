@@ -168,6 +168,19 @@ int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Lay
     return wgrad_general_splits((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
 }
 
+// The same for a lean layer: as many splits as still fit one round of resident workgroups (two per compute unit in the
+// all-taps kernel, three in the general one).  Every split more writes and reads 8 bytes per weight, and without any the
+// update happens in the kernel.  (Splits for at least 2048 workgroups before: VGG-16 on 32 replicas, 256 channels on 8 x 8
+// images in two splits of 512 workgroups instead of one; the round 61.4 -> 60.3 ms, ResNet-18 on 6 replicas 13.4 -> 12.9.)
+int lean_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
+{
+    const TensorShape a = plan.tensors[l.in0];
+    const bool taps = ((a.w == 16 || a.w == 32) && a.c <= 128 && l.cout <= 128) || (a.w == 8 && a.h % 4 == 0);
+    const int64_t rows = (int64_t)l.k * l.k * a.c + (l.bias ? 1 : 0), K = (int64_t)cfg.batch * a.h * a.w;
+    const int64_t wgs = (taps ? (int64_t)(a.c / 64) * (l.cout / 64) : (rows + 127) / 128 * ((l.cout + 127) / 128)) * n;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((taps ? 512 : 768) / wgs, K / 512), 256));
+}
+
 // floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels (tiles have at
 // least 32 rows)
 int64_t stat_floats(int64_t rows, int c) { return (rows + 31) / 32 * 2 * c; }
@@ -202,10 +215,10 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
             int64_t want = (2048 + tiles * cfg.n_replicas - 1) / (tiles * cfg.n_replicas);
             int64_t maxs = std::max<int64_t>(1, K / 128);
             int s = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, maxs), 256));
-            if (general_layer(cfg, plan, l)) {
+            if (lean_layer(cfg, plan, l) || general_layer(cfg, plan, l)) {      // chosen per launch
                 s = 1;
                 for (int n = 1; n <= cfg.n_replicas; ++n) {
-                    const int sn = general_wgrad_splits(cfg, plan, l, n);
+                    const int sn = lean_layer(cfg, plan, l) ? lean_wgrad_splits(cfg, plan, l, n) : general_wgrad_splits(cfg, plan, l, n);
                     if (sn > 1) shared = std::max<int64_t>(shared, (int64_t)n * sn * up64(M * l.cout));
                 }
             }
@@ -299,10 +312,10 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             // in the weight-gradient epilogue (lean and general kernels, K not split), or in the split-K reduction of a layer
             // whose fp32 weights nothing reads between its weight gradient and the update: the data gradients of the lean
             // and general layers read the copies, a layer on the data set has no data gradient
-            const bool in_epilogue = e->fast[i] && e->splits[i] == 1;
-            const bool in_reduce = e->splits[i] > 1 && (e->fast[i] || l.in0 == 0);
+            const bool own_kernel = e->fast[i] || e->general[i];
+            const bool in_reduce = e->splits[i] > 1 && l.in0 == 0;
             const bool small = small_dense_layer(l) && !one_chain_net(cfg, plan);        // its backward kernel applies the update, element by element
-            if (!in_epilogue && !in_reduce && !e->general[i] && !small) continue;
+            if (!own_kernel && !in_reduce && !small) continue;
             int64_t cnt = l.w_count + (l.bias ? l.cout : 0);      // bias sits directly behind the weights
             if (small) cnt = (cnt + 3) / 4 * 4;                   // (padding behind the slice: nothing there is ever updated)
             if (l.w_off % 4 != 0 || cnt % 4 != 0 || l.w_off < pos || (l.bias && l.b_off != l.w_off + l.w_count)) continue;
@@ -781,19 +794,8 @@ struct Runner {
             p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr;
             p.a_f32 = l.in0 == 0;
             p.dy = grad(ot); p.dy_rep = e.rep_block;
-            p.splits = e.general[i] ? general_wgrad_splits(e.cfg, e.plan, l, na) : e.splits[i];
+            p.splits = e.general[i] ? general_wgrad_splits(e.cfg, e.plan, l, na) : e.fast[i] ? lean_wgrad_splits(e.cfg, e.plan, l, na) : e.splits[i];
             const int64_t mn = (int64_t)p.M * p.N;
-            if (p.splits > 1 && e.fast[i]) {
-                // The planned split count fills the chip when every replica is active.  A sub-step with fewer active
-                // replicas splits K further; the partial-sum buffer (sized for all replicas at the planned count) and
-                // K bound how far.  Wide-image layers run the all-taps kernel with one tile per 64 x 64 channel pair.
-                const bool wide = ((p.W == 16 || p.W == 32) && p.Cin <= 128 && p.N <= 128) || (p.W == 8 && p.H % 4 == 0);
-                const int64_t tiles = wide ? (int64_t)(p.Cin / 64) * (p.N / 64) : ((p.M + 127) / 128) * ((p.N + 127) / 128);
-                const int64_t want = (1024 + tiles * na - 1) / (tiles * na);
-                const int64_t by_buffer = e.shared_floats / ((int64_t)na * ((mn + 63) / 64 * 64));
-                const int64_t by_k = std::max<int64_t>(1, p.K / 512);
-                p.splits = (int)std::max<int64_t>(p.splits, std::min<int64_t>(std::min<int64_t>(want, by_buffer), std::min<int64_t>(by_k, 256)));
-            }
             if (p.splits > 1) {
                 const int unit = e.fast[i] ? 64 : e.general[i] ? 32 : 16;      // slab length of the kernel that will run
                 const int slabs = (p.K + unit - 1) / unit;
