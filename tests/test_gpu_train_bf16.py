@@ -199,6 +199,20 @@ def test_regular_layers_bf16_position_sorted_rows(hint):
     p.close()
 
 
+def test_position_sorted_rows_of_an_odd_multiple_of_32_images():
+    """Batch 96 on 4x4 images, 256 output channels, largest tiles: no slab of the weight gradient may straddle two positions."""
+    b = nets._Builder()
+    b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(b.relu(b.conv(0, 64)), 256))), 256))), 5)
+    ops, shape, batch, N = b.array(), (4, 4, 3), 96, 2
+    x, y = _data(N, 2 * batch, shape, 5, seed=80)
+    p = Pair(ops, shape, N, 1, x, y, batch, 0.01, 0.9, [2, 1], bf16=True, options={hadfl.OPT_TILE_HINT: 1})
+    w = p.forced_steps()
+    d = p.max_rel_diff()
+    print("96 images bf16 rel", d, "updates:", pm.show(w), flush=True)
+    assert w["compared"] > 0 and d <= REL
+    p.close()
+
+
 @pytest.mark.parametrize("side,batch", [(16, 6), (32, 3)])
 def test_wide_image_layers_bf16_patch_kernel(side, batch):
     """16- and 32-pixel-wide images with 64 / 128 channels: forward and data gradient run in the kernel that keeps a
