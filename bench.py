@@ -26,23 +26,23 @@ PAPER_CONTEXT = {"speedup_vs_decentralized_fedavg": 3.15, "speedup_vs_pytorch_di
 # concatenation at measurement, bytes)
 TRAFFIC = {
     ("aggregate", "agg-stress-n64"): (("paper_2111_08274_amd/csrc/aggregate.hip",),
-                                      "6b6bc47f1584798896ab4395b0a3a8cedd8eec64ecd27d1eed8fa062f3c54da8",
-                                      402287976.8),
+                                      "07f6ea535d5a85ec9476282da427d1f3b14491645d0eec86612cbb44a6f0b83a",
+                                      402301504.5),
     # all launches of the class in a cycle, averaged
     ("conv_dgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                       "cc0afcd2862a6484e800f471bc016390d19f86eb04bffca742fcb93523bb020d",
-                                       468965566.6),
+                                       "09aefceed6f017f36acf65332c22d67f87201a7f499bbcc88cff54c7a401ad3f",
+                                       469177032.3),
     ("conv_fwd", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                       "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
                                       "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                     "6d0b5b6f326de0b4d04d62e23f359ecac5d4aeece24567464504b1531826c890",
-                                     324417802.8),
+                                     "1a1db6b52885404607eedbc42bb24e5beef89a81e50e84847cd300a17ff7dfa5",
+                                     324582150.9),
     # (the figure includes the fused update's parameter and momentum traffic)
     ("conv_wgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_first_bf16.hip"),
-                                       "3a34545bbf20a11296692c6e63155e1cb74b497520169af88177b48f30ff7ecd",
-                                       552115616.3),
+                                       "f7057e988412d565fb10012bbb937add6c14a60b146fa79f6a192dbfad93632b",
+                                       533122275.3),
 }
 
 
