@@ -24,7 +24,7 @@ public:
     std::vector<int64_t> saved_off;       // per layer (BN): offset of saved mean/istd inside the replica block
     int64_t shared_off = 0;               // start of the region shared by all layers (split-K partials, BN partials)
     int64_t shared_floats = 0;
-    int64_t bn_off = 0;                   // per-chunk partial sums of the batch-norm reductions (their own region: weight
+    int64_t bn_off = 0, bn_floats = 0;    // per-chunk partial sums of the batch-norm reductions (their own region: weight
                                           // gradients may run beside them on the side stream)
     std::vector<int> splits;              // per layer: split-K factor of the weight gradient (general layers: chosen per launch)
     std::vector<int> bn_chunks;           // per layer
@@ -181,9 +181,9 @@ int lean_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer&
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((taps ? 512 : 768) / wgs, K / 512), 256));
 }
 
-// floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels (tiles have at
-// least 32 rows)
-int64_t stat_floats(int64_t rows, int c) { return (rows + 31) / 32 * 2 * c; }
+// floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels: one entry per
+// tile, which has at least 128 rows in the lean kernels and 32 in the general ones
+int64_t stat_floats(int64_t rows, int c, bool lean) { const int64_t tile = lean ? 128 : 32; return (rows + tile - 1) / tile * 2 * c; }
 
 Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
 {
@@ -253,12 +253,15 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
         }
         L.wbf_rep = woff;
     }
-    // a lean or general convolution in front of a batch norm leaves statistics entries of its output
+    // a lean or general convolution in front of a batch norm leaves statistics entries of its output, and a lean one behind
+    // a batch norm (and its ReLU and pool) leaves entries of that batch norm's gradient, the size of its own input
     for (size_t k = 0; k < plan.layers.size(); ++k) {
         const Layer& l = plan.layers[k];
-        if (l.type != HADFL_OP_BN || l.in0 < 1 || (!L.fast[l.in0 - 1] && !L.general[l.in0 - 1])) continue;
         const TensorShape a = plan.tensors[l.in0];
-        bn_shared = std::max<int64_t>(bn_shared, cfg.n_replicas * stat_floats(B * a.h * a.w, a.c));
+        const bool behind = l.type == HADFL_OP_BN && l.in0 > 0 && (L.fast[l.in0 - 1] || L.general[l.in0 - 1]);
+        if (!behind && !L.fast[k]) continue;
+        const bool lean = L.fast[k] || L.fast[l.in0 - 1];
+        bn_shared = std::max<int64_t>(bn_shared, cfg.n_replicas * stat_floats(B * a.h * a.w, a.c, lean));
     }
     L.bn_floats = up64(bn_shared);
     // position tables: worth it for small images (many border pixels), and the weight gradient needs slabs of 32
@@ -302,6 +305,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
     e->shared_floats = L.shared_floats;
     e->fast = L.fast; e->general = L.general; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
     e->bn_off = e->shared_off + L.shared_floats;
+    e->bn_floats = L.bn_floats;
     e->wbf_off = e->bn_off + L.bn_floats;
     {
         e->fused_update.assign(plan.layers.size(), 0);
@@ -481,7 +485,12 @@ struct Runner {
         if (rc != hipSuccess) failed = "join";
     }
     float* shared() const { return e.buf.work + e.shared_off; }
-    float* bn_shared() const { return e.buf.work + e.bn_off; }
+    // the region of the batch-norm partial sums, for one launch's entries of `rep` floats per replica
+    float* bn_shared(int64_t rep)
+    {
+        if (na * rep > e.bn_floats && rc == hipSuccess) { rc = hipErrorInvalidValue; failed = "batch-norm sums beyond their region"; }
+        return e.buf.work + e.bn_off;
+    }
     __bf16* wbf() const { return reinterpret_cast<__bf16*>(e.buf.work + e.wbf_off); }
     const int* perm(size_t i) const { return e.tab_idx[i] < 0 ? nullptr : reinterpret_cast<const int*>(e.buf.work + e.tab_off) + e.tab_idx[i]; }
     const unsigned* posmask(size_t i) const
@@ -652,7 +661,7 @@ struct Runner {
                 f.perm = perm(i); f.posmask = posmask(i);
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat = bn_shared(); f.stat_rep = stat_floats(p.M, p.Cout);
+                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run("conv_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_fast(f, 0, na, s, srows); });
@@ -668,7 +677,7 @@ struct Runner {
                 f.relu = p.relu;
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat = bn_shared(); f.stat_rep = stat_floats(p.M, p.Cout);
+                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_general(f, 0, na, s, srows); });
@@ -695,7 +704,7 @@ struct Runner {
             b.y = actw(ot); b.relu = e.fused_relu[i];
             if (e.stat_from[i] >= 0 && e.stat_rows[i] > 0) {          // the convolution in front left the sums
                 b.stats_done = 1; b.stat_entries = (b.rows + e.stat_rows[i] - 1) / e.stat_rows[i];
-                b.partial_rep = stat_floats(b.rows, b.C);
+                b.partial_rep = stat_floats(b.rows, b.C, e.fast[e.stat_from[i]]);
                 const Layer& conv = e.plan.layers[e.stat_from[i]];
                 b.stat_shift = conv.bias ? e.buf.replicas + conv.b_off : nullptr; b.stat_shift_rep = e.plan.row_stride;
             }
@@ -740,7 +749,7 @@ struct Runner {
         return conv_first_supported(f);
     }
 
-    BnParams bn_params(size_t i) const
+    BnParams bn_params(size_t i)
     {
         const Layer& l = e.plan.layers[i];
         const TensorShape a = e.plan.tensors[l.in0];
@@ -753,7 +762,7 @@ struct Runner {
         b.rows = (int)((int64_t)e.cfg.batch * a.h * a.w); b.C = a.c;
         b.chunks = e.bn_chunks[i];
         b.chunk_rows = (b.rows + b.chunks - 1) / b.chunks;
-        b.partial = bn_shared(); b.partial_rep = (long long)b.chunks * 2 * a.c;
+        b.partial_rep = (long long)b.chunks * 2 * a.c; b.partial = bn_shared(b.partial_rep);
         b.order = e.buf.order; b.bf16 = e.cfg.bf16;
         return b;
     }
@@ -874,7 +883,7 @@ struct Runner {
                     int* brows = nullptr;
                     if (e.bstat_for[i] >= 0 && !acc0) {        // this data gradient is the whole gradient of a BN's output
                         const int k = e.bstat_for[i];
-                        f.stat = bn_shared(); f.stat_rep = stat_floats(d.M, d.N);
+                        f.stat_rep = stat_floats(d.M, d.N, true); f.stat = bn_shared(f.stat_rep);
                         f.stat_y = act(l.in0); f.stat_y_rep = e.rep_block; f.stat_relu = e.fused_relu[k];
                         e.bstat_rep[k] = f.stat_rep;
                         brows = &e.bstat_rows[k];

@@ -1,0 +1,72 @@
+"""What hadfl_local_steps asks the GPU to touch, checked without one: the library's real launch path runs on a stand-in for
+the HIP runtime that holds every launch's operands to their regions (tests/native/launch_check.cpp)."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from oracle import nets
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="session")
+def checked(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip") / "launch_check.so")
+    subprocess.run(["/opt/rocm/llvm/bin/clang++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "native", "launch_check.cpp"), "-o", so], check=True)
+
+    def run(cases):
+        r = subprocess.run([sys.executable, os.path.join(HERE, "native", "run_checked.py"), so], input=json.dumps(cases), text=True,
+                           capture_output=True, cwd=os.path.dirname(HERE), env=dict(os.environ, PYTHONPATH=os.path.dirname(HERE)))
+        assert r.returncode == 0, r.stderr[-3000:]
+        return json.loads(r.stdout)
+    return run
+
+
+def case(builder, shape, batch, ratio, bf16, classes=10, **more):
+    return dict(ops=builder.array()[:, [0, 1, 2, 4, 5, 6, 7, 8]].tolist(), shape=list(shape), batch=batch, ratio=ratio, bf16=int(bf16),
+                classes=classes, **more)
+
+
+def assert_clean(checked, cases):
+    for c, r in zip(cases, checked(cases)):
+        assert r["status"] == 0 and r["report"] == "", (c, r["report"])
+
+
+def first_norm(ch=64, cout=64):
+    """a batch norm behind the first convolution, read by one regular convolution, and no other batch norm"""
+    b = nets._Builder()
+    b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(0, ch))), cout))), 10)
+    return b
+
+
+def pre_activation(ch=64):
+    """a residual block whose batch norm sits behind a sum"""
+    b = nets._Builder()
+    t = b.relu(b.conv(0, ch))
+    u = b.add(b.conv(t, ch), t)
+    v = b.conv(b.relu(b.bn(u)), ch)
+    b.dense(b.gap(b.relu(b.add(v, u))), 10)
+    return b
+
+
+def pooled(ch=64):
+    """a batch norm behind a pool and one with a pool folded into it"""
+    b = nets._Builder()
+    t = b.maxpool(b.relu(b.conv(0, ch)))
+    t = b.maxpool(b.relu(b.bn(t)))
+    b.dense(b.gap(b.relu(b.conv(t, 2 * ch))), 10)
+    return b
+
+
+@pytest.mark.parametrize("bf16", [1, 0])
+def test_batch_norm_sums_stay_in_their_region(checked, bf16):
+    """Batch norms that do not sit behind a convolution of their own size, from 64 to 131072 rows."""
+    cases = []
+    for make in (first_norm, pre_activation, pooled):
+        for side, batch, n in ((8, 32, 2), (8, 64, 4), (16, 64, 16), (32, 32, 3), (32, 128, 2), (4, 4, 5)):
+            cases.append(case(make(), (side, side, 3), batch, [2] + [1] * (n - 1), bf16))
+    assert_clean(checked, cases)
