@@ -485,9 +485,15 @@ struct Runner {
         if (rc != hipSuccess) failed = "join";
     }
     float* shared() const { return e.buf.work + e.shared_off; }
-    // the region of the batch-norm partial sums, for one launch's entries of `rep` floats per replica
-    float* bn_shared(int64_t rep)
+    // The region of the batch-norm partial sums, for one launch's entries of `rep` floats per replica, and what it holds for a
+    // later launch: the forward sums of batch norm `owner`, or (kBackward + owner) those of its backward pass.  Other layers
+    // may run between the convolution that leaves them and the batch norm, and take the region for sums of their own; the
+    // batch norm then forms its sums itself.
+    static constexpr int kBackward = 1 << 30;
+    int sums_of = -1;
+    float* bn_shared(int64_t rep, int owner)
     {
+        sums_of = owner;
         if (na * rep > e.bn_floats && rc == hipSuccess) { rc = hipErrorInvalidValue; failed = "batch-norm sums beyond their region"; }
         return e.buf.work + e.bn_off;
     }
@@ -661,7 +667,7 @@ struct Runner {
                 f.perm = perm(i); f.posmask = posmask(i);
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep);
+                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run("conv_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_fast(f, 0, na, s, srows); });
@@ -677,7 +683,7 @@ struct Runner {
                 f.relu = p.relu;
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep);
+                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_general(f, 0, na, s, srows); });
@@ -700,9 +706,10 @@ struct Runner {
             break;
         case HADFL_OP_GAP: run("gap_fwd", 0, asz() * (4.0 * (B * a.numel() + q.count)), [&] { return launch_gap_fwd(q, na, s); }); break;
         case HADFL_OP_BN: {
+            const bool sums_done = e.stat_from[i] >= 0 && e.stat_rows[i] > 0 && sums_of == (int)i;
             BnParams b = bn_params(i);
             b.y = actw(ot); b.relu = e.fused_relu[i];
-            if (e.stat_from[i] >= 0 && e.stat_rows[i] > 0) {          // the convolution in front left the sums
+            if (sums_done) {                                 // the convolution in front left the sums
                 b.stats_done = 1; b.stat_entries = (b.rows + e.stat_rows[i] - 1) / e.stat_rows[i];
                 b.partial_rep = stat_floats(b.rows, b.C, e.fast[e.stat_from[i]]);
                 const Layer& conv = e.plan.layers[e.stat_from[i]];
@@ -762,7 +769,7 @@ struct Runner {
         b.rows = (int)((int64_t)e.cfg.batch * a.h * a.w); b.C = a.c;
         b.chunks = e.bn_chunks[i];
         b.chunk_rows = (b.rows + b.chunks - 1) / b.chunks;
-        b.partial_rep = (long long)b.chunks * 2 * a.c; b.partial = bn_shared(b.partial_rep);
+        b.partial_rep = (long long)b.chunks * 2 * a.c; b.partial = bn_shared(b.partial_rep, -1);
         b.order = e.buf.order; b.bf16 = e.cfg.bf16;
         return b;
     }
@@ -883,7 +890,7 @@ struct Runner {
                     int* brows = nullptr;
                     if (e.bstat_for[i] >= 0 && !acc0) {        // this data gradient is the whole gradient of a BN's output
                         const int k = e.bstat_for[i];
-                        f.stat_rep = stat_floats(d.M, d.N, true); f.stat = bn_shared(f.stat_rep);
+                        f.stat_rep = stat_floats(d.M, d.N, true); f.stat = bn_shared(f.stat_rep, kBackward + k);
                         f.stat_y = act(l.in0); f.stat_y_rep = e.rep_block; f.stat_relu = e.fused_relu[k];
                         e.bstat_rep[k] = f.stat_rep;
                         brows = &e.bstat_rows[k];
@@ -928,6 +935,7 @@ struct Runner {
             run("gap_bwd", 0, asz() * (4.0 * (q.count + B * a.c)), [&] { return launch_gap_bwd(q, na, s); });
             break;
         case HADFL_OP_BN: {
+            const bool sums_done = e.bstat_rows[i] > 0 && sums_of == kBackward + (int)i;
             BnParams b = bn_params(i);
             b.dy = grad(ot); b.dy_rep = e.rep_block;
             b.y = grad(l.in0); b.y_rep = e.rep_block;
@@ -937,12 +945,12 @@ struct Runner {
                 b.pool = 1; b.H = a.h; b.W = a.w; b.relu = e.fused_relu[i];
                 b.pool_g = grad(e.plan.layers[e.pool_of[i]].out); b.pool_g_rep = e.rep_block;
             }
-            if (e.bstat_rows[i] > 0) {                       // the data gradient of the layer above left the sums
+            if (sums_done) {                                 // the data gradient of the layer above left the sums
                 const int64_t rows_out = e.pool_of[i] >= 0 ? b.rows / 4 : b.rows;
                 b.bwd_stats_done = 1; b.stat_entries = (int)((rows_out + e.bstat_rows[i] - 1) / e.bstat_rows[i]);
                 b.partial_rep = e.bstat_rep[i];
-                e.bstat_rows[i] = 0;
             }
+            e.bstat_rows[i] = 0;
             run("bn_bwd", 0, asz() * (12.0 * B * a.numel()), [&] { return launch_bn_bwd(b, na, s); });
             break; }
         }

@@ -5,7 +5,7 @@ import pytest
 
 from tests import parity_metrics as pm
 from tests.pair import Pair
-from tests.test_launch_checks import first_norm, pooled, pre_activation
+from tests.test_launch_checks import first_norm, interleaved, pooled, pre_activation
 
 pytestmark = pytest.mark.gpu
 
@@ -26,3 +26,9 @@ def forced(builder, shape, batch, replicas, bf16):
 def test_gradient_sums_of_a_lone_batch_norm_bf16(make, batch, replicas):
     """The sums from a lean data gradient, for a batch norm behind the first layer, a sum or a pool."""
     forced(make(), (8, 8, 3), batch, replicas, True)
+
+
+@pytest.mark.parametrize("ch,bf16", [(40, False), (40, True), (64, False), (64, True)])
+def test_layers_between_a_convolution_and_its_batch_norm(ch, bf16):
+    """Batch norms whose sums another layer's have replaced by the time they run form their own."""
+    forced(interleaved(ch), (8, 8, 3), 32, 3, bf16)

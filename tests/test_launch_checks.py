@@ -2,6 +2,7 @@
 the HIP runtime that holds every launch's operands to their regions (tests/native/launch_check.cpp)."""
 import json
 import os
+import random
 import subprocess
 import sys
 
@@ -69,4 +70,62 @@ def test_batch_norm_sums_stay_in_their_region(checked, bf16):
     for make in (first_norm, pre_activation, pooled):
         for side, batch, n in ((8, 32, 2), (8, 64, 4), (16, 64, 16), (32, 32, 3), (32, 128, 2), (4, 4, 5)):
             cases.append(case(make(), (side, side, 3), batch, [2] + [1] * (n - 1), bf16))
+    assert_clean(checked, cases)
+
+
+def interleaved(ch=40):
+    """Layers between a convolution and its batch norm, and between a batch norm and the convolution that reads it, which
+    have sums of their own."""
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, ch)))
+    u, v = b.conv(t, ch), b.conv(t, ch, k=1, pad=0)
+    w = b.conv(b.add(t, t), ch)
+    x, y, z = b.bn(w), b.bn(v), b.relu(b.bn(u))
+    p = b.relu(b.bn(b.add(x, y)))
+    q = b.conv(z, ch)
+    r = b.relu(b.bn(b.conv(p, ch)))
+    b.dense(b.gap(b.add(b.bn(q), r)), 10)
+    return b
+
+
+@pytest.mark.parametrize("bf16", [1, 0])
+@pytest.mark.parametrize("ch", [40, 64])
+def test_batch_norm_reads_its_own_sums(checked, bf16, ch):
+    assert_clean(checked, [case(interleaved(ch), (side, side, 3), 64, [1] * n, bf16) for side, n in ((8, 3), (32, 2))])
+
+
+def random_net(rng):
+    """Layers over the tensors at hand in any order: sums and batch norms of tensors made long before among them."""
+    b = nets._Builder()
+    side, widths = rng.choice([4, 6, 8, 16, 32]), rng.choice([(8, 40), (64, 128), (64, 128, 24), (16, 64)])
+    live = [(b.conv(0, rng.choice(widths), bias=rng.random() < 0.5), side, None)]
+    live[0] = (live[0][0], side, int(b.ops[-1][7]))
+    for _ in range(rng.randint(3, 12)):
+        t, s, c = rng.choice(live)
+        kind = rng.choice(["conv", "conv", "bn", "bn", "relu", "pool", "add"])
+        if kind == "conv":
+            c, stride, k = rng.choice(widths), rng.choice([1, 1, 1, 2]), rng.choice([1, 3, 3])
+            live.append((b.conv(t, c, k=k, stride=stride, pad=k // 2, bias=rng.random() < 0.5), (s + 2 * (k // 2) - k) // stride + 1, c))
+        elif kind == "bn":
+            live.append((b.bn(t), s, c))
+        elif kind == "relu":
+            live.append((b.relu(t), s, c))
+        elif kind == "pool" and s % 2 == 0:
+            live.append((b.maxpool(t), s // 2, c))
+        elif kind == "add":
+            same = [u for u in live if u[1:] == (s, c)]
+            live.append((b.add(t, rng.choice(same)[0]), s, c))
+    b.dense(b.gap(live[-1][0]), 10)
+    return b, side
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_random_networks_stay_in_their_regions(checked, seed):
+    rng = random.Random(seed)
+    cases = []
+    for _ in range(40):
+        b, side = random_net(rng)
+        n = rng.randint(1, 16)
+        cases.append(case(b, (side, side, 3), rng.choice([4, 32, 50, 64, 96]), [rng.randint(1, 2) for _ in range(n)], rng.randint(0, 1),
+                          momentum=rng.choice([0.0, 0.9]), options=[(0, rng.randint(0, 1)), (1, rng.choice([0, 0, 1, 2]))]))
     assert_clean(checked, cases)
