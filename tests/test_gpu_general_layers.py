@@ -113,3 +113,23 @@ def test_values_bf16_cannot_hold():
     assert np.array_equal(got[~same].astype(np.float64), want[~same]) and np.isfinite(got[same]).all()
     scale = np.concatenate([np.abs(wd) + lr * (np.abs(xd).T @ (np.abs(p) / batch)), lr * np.abs(p).sum(0)[None] / batch])
     assert (np.abs(got[same] - want[same]) <= 1e-5 * scale.ravel()[same] + 1e-30).all()
+
+
+@pytest.mark.parametrize("replicas", [2, 9])
+@pytest.mark.parametrize("side", [6, 8, 20])
+def test_regular_layers_without_batch_norm_f32(side, replicas):
+    """Convolutions of 64-multiple channels in a net without batch norm, behind and in front of layers that keep the
+    kernels of such nets; 6 x 6 and 8 x 8 images have their positions sorted."""
+    b = nets._Builder()
+    t = b.relu(b.conv(b.relu(b.conv(0, 64)), 64))
+    t = b.relu(b.conv(b.maxpool(b.relu(b.conv(t, 128, k=1, pad=0))), 64))
+    u = b.relu(b.conv(t, 64, bias=False))
+    b.dense(b.gap(b.relu(b.add(b.conv(u, 64), t))), 5)
+    rng = np.random.default_rng(7)
+    x = rng.standard_normal((replicas, 64, side, side, 3)).astype(np.float32)
+    y = rng.integers(0, 5, size=(replicas, 64)).astype(np.int32)
+    p = Pair(b.array(), (side, side, 3), replicas, 1, x, y, 32, 0.01, 0.9, [2] + [1] * (replicas - 1))
+    w = p.forced_steps()
+    print(side, replicas, pm.show(w), flush=True)
+    assert w["compared"] > 0 and p.max_param_diff() <= 1e-4
+    p.close()

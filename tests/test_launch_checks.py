@@ -129,3 +129,21 @@ def test_random_networks_stay_in_their_regions(checked, seed):
         cases.append(case(b, (side, side, 3), rng.choice([4, 32, 50, 64, 96]), [rng.randint(1, 2) for _ in range(n)], rng.randint(0, 1),
                           momentum=rng.choice([0.0, 0.9]), options=[(0, rng.randint(0, 1)), (1, rng.choice([0, 0, 1, 2]))]))
     assert_clean(checked, cases)
+
+
+def layers_in(trace, part):
+    return sum(part in name for name in trace)
+
+
+def test_regular_layers_without_batch_norm_in_the_general_kernels(checked):
+    """fp32 networks without batch norm: the regular layers (64-multiple channels, stride 1) in the general kernels in all three
+    directions, every other layer in the kernels whose sums run in one chain (forward 2, data gradient 1, weight gradient 2)."""
+    b = nets._Builder()
+    t = b.relu(b.conv(b.relu(b.conv(b.relu(b.conv(0, 64)), 64)), 128))
+    b.dense(b.maxpool(t), 10)
+    c = nets._Builder()
+    t = c.maxpool(c.relu(c.conv(c.maxpool(c.relu(c.conv(0, 32))), 64)))
+    c.dense(t, 10)
+    regular, narrow = (r["trace"] for r in checked([case(b, (8, 8, 3), 16, [1, 1], 0), case(c, (8, 8, 3), 16, [1, 1], 0)]))
+    assert layers_in(regular, "conv_general") == 4 and layers_in(regular, "wgrad_general") == 2
+    assert layers_in(narrow, "general") == 0 and layers_in(narrow, "igemm") == 2 + 2 + 3
