@@ -161,6 +161,14 @@ bool small_dense_layer(const Layer& l)
     return l.type == HADFL_OP_DENSE && l.cout <= 16 && l.in0 != 0 && (!l.bias || l.b_off == l.w_off + l.w_count);
 }
 
+// Its backward pass in one launch walks the samples in four chains per 64 features: 10 outputs on 512 features, 4 replicas,
+// 15 / 22 / 37 / 67 / 127 us at 64 / 128 / 256 / 512 / 1024 samples, where data gradient, weight gradient and its reduction
+// take 37 / 41 / 43 / 47 / 48 us as launches of their own: beyond 256 samples they are the shorter way.
+bool dense_one_pass_bwd(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
+{
+    return small_dense_layer(l) && !one_chain_net(cfg, plan) && cfg.batch <= 256;
+}
+
 // Forward straight from the master weights: classifiers and the dense layers on the data set, whose copies no data gradient
 // would use.  Classifiers on long rows have a workgroup per row instead (see the kernels).
 bool dense_rows_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
@@ -327,7 +335,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             // and general layers read the copies, a layer on the data set has no data gradient
             const bool own_kernel = e->fast[i] || e->general[i];
             const bool in_reduce = e->splits[i] > 1 && l.in0 == 0;
-            const bool small = small_dense_layer(l) && !one_chain_net(cfg, plan);        // its backward kernel applies the update, element by element
+            const bool small = dense_one_pass_bwd(cfg, plan, l);      // its backward kernel applies the update, element by element
             if (!own_kernel && !in_reduce && !small) continue;
             int64_t cnt = l.w_count + (l.bias ? l.cout : 0);      // bias sits directly behind the weights
             if (small) cnt = (cnt + 3) / 4 * 4;                   // (padding behind the slice: nothing there is ever updated)
@@ -805,7 +813,7 @@ struct Runner {
         case HADFL_OP_DENSE: {
             // weight (and bias) gradient
             GemmParams p = gemm_base(l);
-            if (small_dense_layer(l) && e.fused_update[i] && !one_chain_net(e.cfg, e.plan)) {
+            if (e.fused_update[i] && dense_one_pass_bwd(e.cfg, e.plan, l)) {
                 DenseSmallParams d = dense_small(l, p);
                 d.dy = grad(ot); d.dy_rep = e.rep_block; d.dx = grad(l.in0); d.dx_rep = e.rep_block;
                 d.mask = mask0; d.mask_rep = e.rep_block; d.accumulate = acc0;

@@ -133,3 +133,19 @@ def test_regular_layers_without_batch_norm_f32(side, replicas):
     print(side, replicas, pm.show(w), flush=True)
     assert w["compared"] > 0 and p.max_param_diff() <= 1e-4
     p.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("batch", [256, 257, 1000])
+def test_classifier_of_many_samples(batch, bf16):
+    """Both sides of the rule that takes a classifier's backward pass out of its one-launch kernel."""
+    b = nets._Builder()
+    b.dense(b.relu(b.dense(0, 67)), 5)
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((3, batch, 1, 1, 33)).astype(np.float32)
+    y = rng.integers(0, 5, size=(3, batch)).astype(np.int32)
+    p = Pair(b.array(), (1, 1, 33), 3, 1, x, y, batch, 0.01, 0.9, [2, 1, 1], bf16=bf16)
+    w = p.forced_steps()
+    print(batch, bf16, pm.show(w), flush=True)
+    assert w["compared"] > 0 and (p.max_rel_diff() <= 2e-2 if bf16 else p.max_param_diff() <= 1e-4)
+    p.close()

@@ -147,3 +147,12 @@ def test_regular_layers_without_batch_norm_in_the_general_kernels(checked):
     regular, narrow = (r["trace"] for r in checked([case(b, (8, 8, 3), 16, [1, 1], 0), case(c, (8, 8, 3), 16, [1, 1], 0)]))
     assert layers_in(regular, "conv_general") == 4 and layers_in(regular, "wgrad_general") == 2
     assert layers_in(narrow, "general") == 0 and layers_in(narrow, "igemm") == 2 + 2 + 3
+
+
+def test_classifier_backward_route_by_batch(checked):
+    """One launch up to 256 samples, data gradient, weight gradient and reduction beyond."""
+    b = nets._Builder()
+    b.dense(b.relu(b.dense(0, 64)), 10)
+    cases = [case(b, (1, 1, 32), batch, [1], bf16) for bf16 in (0, 1) for batch in (256, 257)]
+    assert [layers_in(r["trace"], "dense_small_bwd") for r in checked(cases)] == [1, 0, 1, 0]
+    assert_clean(checked, cases)
