@@ -177,6 +177,16 @@ bool dense_rows_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer&
     return l.type == HADFL_OP_DENSE && (l.cout <= 16 || l.in0 == 0) && (!l.bias || l.b_off == l.w_off + l.w_count);
 }
 
+// A layer on the data set leaves that kernel, which shares no operand between workgroups, where the generic kernel's 128 x 128
+// tiles fill the chip one and a half times.  2048 outputs, 256 samples on 8 / 12 / 16 replicas (256 / 384 / 512 tiles), generic
+// and this, us: 784 features fp32 143 177 186 and 114 155 200, bf16 189 232 234 and 132 190 250; 100 features bf16, a step
+// or none per wave, 42 51 52 and 42 61 77: there the line is at one round.
+bool dense_rows_pays(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
+{
+    const int64_t tiles = (int64_t)((cfg.batch + 127) / 128) * ((l.cout + 127) / 128) * n;
+    return l.in0 != 0 || tiles <= (cfg.bf16 && plan.tensors[0].numel() < 512 ? 256 : 384);
+}
+
 // Split-K factor of a general layer's weight gradient with n active replicas
 int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
@@ -664,7 +674,8 @@ struct Runner {
                     break;
                 }
             }
-            if (dense_rows_layer(e.cfg, e.plan, l)) {
+            const bool rows_layer = dense_rows_layer(e.cfg, e.plan, l);
+            if (rows_layer && dense_rows_pays(e.cfg, e.plan, l, na)) {
                 DenseRowsParams d{};
                 d.x = act(l.in0); d.x_rep = e.rep_block; d.cursor = p.cursor; d.n_samples = p.n_samples; d.batch = p.batch;
                 d.w = p.w; d.w_rep = p.w_rep; d.out = actw(ot); d.out_rep = e.rep_block;
@@ -690,7 +701,7 @@ struct Runner {
                 run("conv_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_fast(f, 0, na, s, srows); });
                 break;
             }
-            if (e.general[i]) {
+            if (e.general[i] && !rows_layer) {
                 GeneralConvParams f = general_base(i, p);
                 f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.pad = p.pad; f.sstride = p.stride;
                 f.a = act(l.in0); f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz;

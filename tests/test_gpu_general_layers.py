@@ -149,3 +149,19 @@ def test_classifier_of_many_samples(batch, bf16):
     print(batch, bf16, pm.show(w), flush=True)
     assert w["compared"] > 0 and (p.max_rel_diff() <= 2e-2 if bf16 else p.max_param_diff() <= 1e-4)
     p.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("features,cout", [(48, 128 * 28), (48, 128 * 29), (520, 128 * 42), (520, 128 * 43), (33, 128 * 43 + 5)])
+def test_wide_layer_on_the_data_set(features, cout, bf16):
+    """Both sides of the rule that takes a layer on the data set out of the few-rows kernel (nine replicas, 252 to 396 tiles)."""
+    b = nets._Builder()
+    b.dense(b.relu(b.dense(0, cout)), 5)
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((9, 6, 1, 1, features)).astype(np.float32)
+    y = rng.integers(0, 5, size=(9, 6)).astype(np.int32)
+    p = Pair(b.array(), (1, 1, features), 9, 1, x, y, 6, 0.01, 0.9, [1] * 9, bf16=bf16)
+    w = p.forced_steps()
+    print(features, cout, bf16, pm.show(w), flush=True)
+    assert w["compared"] > 0 and (p.max_rel_diff() <= 2e-2 if bf16 else p.max_param_diff() <= 1e-4)
+    p.close()

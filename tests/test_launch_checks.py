@@ -156,3 +156,16 @@ def test_classifier_backward_route_by_batch(checked):
     cases = [case(b, (1, 1, 32), batch, [1], bf16) for bf16 in (0, 1) for batch in (256, 257)]
     assert [layers_in(r["trace"], "dense_small_bwd") for r in checked(cases)] == [1, 0, 1, 0]
     assert_clean(checked, cases)
+
+
+def test_wide_layer_on_the_data_set_by_launch_size(checked):
+    """The few-rows kernel up to one and a half rounds of 128 x 128 tiles (bf16 with a short contraction: one), then generic tiles."""
+    cases = []
+    for features, bf16, tiles in ((784, 0, 384), (784, 1, 384), (100, 0, 384), (100, 1, 256), (96, 1, 256)):
+        for cout in (64 * tiles, 64 * tiles + 1):
+            b = nets._Builder()
+            b.dense(b.relu(b.dense(0, cout)), 10)
+            cases.append(case(b, (1, 1, features), 8, [1, 1], bf16))
+    runs = checked(cases)
+    assert [layers_in(r["trace"], "dense_rows_fwd") for r in runs] == [1, 0] * 5
+    assert_clean(checked, cases)
