@@ -59,7 +59,8 @@ public:
     std::vector<int64_t> bstat_rep;       // per layer (BN): floats per replica slot of those entries
     // bf16 configuration: regular convolution layers keep two bf16 weight matrices (forward / data-gradient order)
     std::vector<char> fast;               // per layer: the lean bf16 kernels apply
-    std::vector<char> general;            // per layer: not lean, but the kernels of conv_general.hip apply
+    std::vector<char> general, general_w; // per layer: not lean, but the kernels of conv_general.hip apply (forward and data
+                                          // gradient; weight gradient)
     std::vector<int64_t> wf_off, wb_off;  // per layer: offsets (2-byte units) inside one replica's block of weight copies, or -1
     int64_t wbf_rep = 0;                  // bf16 elements per replica
     int64_t wbf_off = 0;                  // start of the bf16 weight region inside `work` (floats)
@@ -93,7 +94,7 @@ struct Layout {
     std::vector<int64_t> act_off, grad_off, saved_off;
     std::vector<int> splits, bn_chunks;
     int64_t rep_block = 0, shared_floats = 0, bn_floats = 0;
-    std::vector<char> fast, general;
+    std::vector<char> fast, general, general_w;
     std::vector<int64_t> wf_off, wb_off;       // in 2-byte units inside one replica's block of weight copies
     int64_t wbf_rep = 0;
     std::vector<int64_t> tab_idx;
@@ -187,6 +188,21 @@ bool dense_rows_pays(const hadfl_config& cfg, const NetPlan& plan, const Layer& 
     return l.in0 != 0 || tiles <= (cfg.bf16 && plan.tensors[0].numel() < 512 ? 256 : 384);
 }
 
+// Directions of a general layer that run there.  A convolution on the data set is gathered value by value, which pays where the
+// generic kernel (gemm.hip) would gather too.  That one reads its source in 16-byte pieces when the channels come in sixteens
+// (forward) or fours (weight gradient), and is then the faster one, but for footprints that are one tile of 32 rows.
+// Images of 32 x 32, batch 128, 8 replicas, generic over gathered time: forward, 3 x 3 filters, 16 outputs, 1 / 3 / 8 / 16 / 64
+// channels 1.1 1.6 1.6 0.85 0.52; weight gradient, 96 outputs, 3 x 3 and 5 x 5, 3 channels 1.4 0.9, 4 channels 0.7 0.6, 8
+// channels 0.8 0.9; 1 x 1, 4 / 16 / 32 channels 1.3 1.3 1.3.
+bool general_forward(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
+{
+    return general_layer(cfg, plan, l) && !(gather_layer(cfg, l) && plan.tensors[0].c % 16 == 0);
+}
+bool general_wgrad(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
+{
+    return general_layer(cfg, plan, l) && !(gather_layer(cfg, l) && plan.tensors[0].c % 4 == 0 && l.k * l.k * plan.tensors[0].c > 32);
+}
+
 // Split-K factor of a general layer's weight gradient with n active replicas
 int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
@@ -242,7 +258,7 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
             int64_t want = (2048 + tiles * cfg.n_replicas - 1) / (tiles * cfg.n_replicas);
             int64_t maxs = std::max<int64_t>(1, K / 128);
             int s = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, maxs), 256));
-            if (lean_layer(cfg, plan, l) || general_layer(cfg, plan, l)) {      // chosen per launch
+            if (lean_layer(cfg, plan, l) || general_wgrad(cfg, plan, l)) {      // chosen per launch
                 s = 1;
                 for (int n = 1; n <= cfg.n_replicas; ++n) {
                     const int sn = lean_layer(cfg, plan, l) ? lean_wgrad_splits(cfg, plan, l, n) : general_wgrad_splits(cfg, plan, l, n);
@@ -255,17 +271,18 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
     }
     L.rep_block = up64(off);
     L.shared_floats = up64(shared);
-    L.fast.assign(plan.layers.size(), 0); L.general.assign(plan.layers.size(), 0);
+    L.fast.assign(plan.layers.size(), 0); L.general.assign(plan.layers.size(), 0); L.general_w.assign(plan.layers.size(), 0);
     L.wf_off.assign(plan.layers.size(), -1); L.wb_off.assign(plan.layers.size(), -1);
     {
         int64_t woff = 0;
         for (size_t i = 0; i < plan.layers.size(); ++i) {
             const Layer& l = plan.layers[i];
+            L.general_w[i] = general_wgrad(cfg, plan, l);
             if (lean_layer(cfg, plan, l)) {
                 L.fast[i] = 1;
                 L.wf_off[i] = woff; woff += up64(l.w_count);
                 L.wb_off[i] = woff; woff += up64(l.w_count);
-            } else if (general_layer(cfg, plan, l)) {
+            } else if (general_forward(cfg, plan, l)) {
                 const TensorShape a = plan.tensors[l.in0];
                 const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
                 L.general[i] = 1;
@@ -330,7 +347,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
     e->rep_block = L.rep_block;
     e->shared_off = L.rep_block * cfg.n_replicas;
     e->shared_floats = L.shared_floats;
-    e->fast = L.fast; e->general = L.general; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
+    e->fast = L.fast; e->general = L.general; e->general_w = L.general_w; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
     e->bn_off = e->shared_off + L.shared_floats;
     e->bn_floats = L.bn_floats;
     e->wbf_off = e->bn_off + L.bn_floats;
@@ -343,7 +360,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             // in the weight-gradient epilogue (lean and general kernels, K not split), or in the split-K reduction of a layer
             // whose fp32 weights nothing reads between its weight gradient and the update: the data gradients of the lean
             // and general layers read the copies, a layer on the data set has no data gradient
-            const bool own_kernel = e->fast[i] || e->general[i];
+            const bool own_kernel = e->fast[i] || e->general_w[i];
             const bool in_reduce = e->splits[i] > 1 && l.in0 == 0;
             const bool small = dense_one_pass_bwd(cfg, plan, l);      // its backward kernel applies the update, element by element
             if (!own_kernel && !in_reduce && !small) continue;
@@ -838,10 +855,10 @@ struct Runner {
             p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr;
             p.a_f32 = l.in0 == 0;
             p.dy = grad(ot); p.dy_rep = e.rep_block;
-            p.splits = e.general[i] ? general_wgrad_splits(e.cfg, e.plan, l, na) : e.fast[i] ? lean_wgrad_splits(e.cfg, e.plan, l, na) : e.splits[i];
+            p.splits = e.general_w[i] ? general_wgrad_splits(e.cfg, e.plan, l, na) : e.fast[i] ? lean_wgrad_splits(e.cfg, e.plan, l, na) : e.splits[i];
             const int64_t mn = (int64_t)p.M * p.N;
             if (p.splits > 1) {
-                const int unit = e.fast[i] ? 64 : e.general[i] ? 32 : 16;      // slab length of the kernel that will run
+                const int unit = e.fast[i] ? 64 : e.general_w[i] ? 32 : 16;      // slab length of the kernel that will run
                 const int slabs = (p.K + unit - 1) / unit;
                 p.kchunk = ((slabs + p.splits - 1) / p.splits) * unit;
                 p.out_split = (mn + 63) / 64 * 64;
@@ -872,7 +889,7 @@ struct Runner {
                 run("conv_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_wgrad_fast(f, na, s); });
                 if (e.fused_update[i] && na_next > 0) pending_prep = (int)i;
             } else
-            if (e.general[i]) {
+            if (e.general_w[i]) {
                 GeneralWgradParams f{};
                 f.bf16 = e.cfg.bf16;
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;

@@ -165,3 +165,20 @@ def test_wide_layer_on_the_data_set(features, cout, bf16):
     print(features, cout, bf16, pm.show(w), flush=True)
     assert w["compared"] > 0 and (p.max_rel_diff() <= 2e-2 if bf16 else p.max_param_diff() <= 1e-4)
     p.close()
+
+
+@pytest.mark.parametrize("replicas", [2, 9])
+@pytest.mark.parametrize("channels,k", [(4, 3), (8, 3), (16, 1), (16, 3)])
+def test_convolutions_on_a_data_set_of_many_channels(channels, k, replicas):
+    """Each direction on the gathering kernel or the generic one, by the channel count."""
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, 24, k=k, pad=k // 2)))
+    b.dense(b.gap(b.relu(b.conv(t, 16, stride=2))), 5)
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((replicas, 66, 12, 10, channels)).astype(np.float32)
+    y = rng.integers(0, 5, size=(replicas, 66)).astype(np.int32)
+    p = Pair(b.array(), (12, 10, channels), replicas, 1, x, y, 33, 0.01, 0.9, [2] + [1] * (replicas - 1))
+    w = p.forced_steps()
+    print(channels, k, replicas, pm.show(w), flush=True)
+    assert w["compared"] > 0 and p.max_param_diff() <= 1e-4
+    p.close()

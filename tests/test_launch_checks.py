@@ -126,7 +126,7 @@ def test_random_networks_stay_in_their_regions(checked, seed):
     for _ in range(40):
         b, side = random_net(rng)
         n = rng.randint(1, 16)
-        cases.append(case(b, (side, side, 3), rng.choice([4, 32, 50, 64, 96]), [rng.randint(1, 2) for _ in range(n)], rng.randint(0, 1),
+        cases.append(case(b, (side, side, rng.choice([3, 3, 4, 16])), rng.choice([4, 32, 50, 64, 96]), [rng.randint(1, 2) for _ in range(n)], rng.randint(0, 1),
                           momentum=rng.choice([0.0, 0.9]), options=[(0, rng.randint(0, 1)), (1, rng.choice([0, 0, 1, 2]))]))
     assert_clean(checked, cases)
 
@@ -168,4 +168,18 @@ def test_wide_layer_on_the_data_set_by_launch_size(checked):
             cases.append(case(b, (1, 1, features), 8, [1, 1], bf16))
     runs = checked(cases)
     assert [layers_in(r["trace"], "dense_rows_fwd") for r in runs] == [1, 0] * 5
+    assert_clean(checked, cases)
+
+
+def test_convolutions_on_the_data_set_by_channels(checked):
+    """fp32: gathered where the generic kernel would gather too (channels not in sixteens forward, not in fours or at most 32
+    rows in the weight gradient)."""
+    want, cases = [], []
+    for ch, k, forward, wgrad in ((3, 3, 1, 1), (8, 1, 1, 1), (8, 3, 1, 0), (12, 3, 1, 0), (16, 1, 0, 1), (16, 3, 0, 0), (32, 1, 0, 1), (18, 5, 1, 1)):
+        b = nets._Builder()
+        b.dense(b.gap(b.relu(b.bn(b.conv(0, 24, k=k, pad=k // 2)))), 10)
+        cases.append(case(b, (12, 12, ch), 32, [2, 1], 0))
+        want.append((2 * forward, 2 * wgrad))
+    runs = checked(cases)
+    assert [(layers_in(r["trace"], "conv_general"), layers_in(r["trace"], "wgrad_general")) for r in runs] == want
     assert_clean(checked, cases)
