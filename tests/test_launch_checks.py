@@ -183,3 +183,13 @@ def test_convolutions_on_the_data_set_by_channels(checked):
     runs = checked(cases)
     assert [(layers_in(r["trace"], "conv_general"), layers_in(r["trace"], "wgrad_general")) for r in runs] == want
     assert_clean(checked, cases)
+
+
+def test_narrow_layers_take_no_half_empty_tiles(checked):
+    """Up to 32 outputs: 128 x 32 tiles (fp32) where the launch is large, never 128 x 64 or wider."""
+    b = nets._Builder()
+    b.dense(b.gap(b.relu(b.bn(b.conv(b.relu(b.bn(b.conv(0, 16))), 24)))), 10)
+    r = checked([case(b, (28, 28, 3), 32, [1] * n, 0) for n in (4, 16)])
+    for run in r:
+        inner = [name for name in run["trace"] if "conv_general_kernelIf" in name][1:]
+        assert len(inner) == 2 and all("ILi" not in name and "IfLi128ELi32E" in name for name in inner), inner
