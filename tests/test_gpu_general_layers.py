@@ -182,3 +182,19 @@ def test_convolutions_on_a_data_set_of_many_channels(channels, k, replicas):
     print(channels, k, replicas, pm.show(w), flush=True)
     assert w["compared"] > 0 and p.max_param_diff() <= 1e-4
     p.close()
+
+
+@pytest.mark.parametrize("cin,cout,k", [(8, 8, 3), (8, 8, 5), (8, 16, 5), (16, 8, 5)])
+def test_narrow_filters_of_many_taps_bf16(cin, cout, k):
+    """Both sides of the rule that leaves 8-channel layers of more than nine taps to the generic kernels."""
+    b = nets._Builder()
+    t = b.relu(b.conv(0, cin))
+    b.dense(b.gap(b.relu(b.conv(b.relu(b.conv(t, cout, k=k, pad=k // 2)), cin, k=k, pad=k // 2))), 5)
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((3, 26, 12, 10, 3)).astype(np.float32)
+    y = rng.integers(0, 5, size=(3, 26)).astype(np.int32)
+    p = Pair(b.array(), (12, 10, 3), 3, 1, x, y, 13, 0.01, 0.9, [2, 1, 1], bf16=True)
+    w = p.forced_steps()
+    print(cin, cout, k, pm.show(w), flush=True)
+    assert w["compared"] > 0 and p.max_rel_diff() <= 2e-2
+    p.close()

@@ -193,3 +193,15 @@ def test_narrow_layers_take_no_half_empty_tiles(checked):
     for run in r:
         inner = [name for name in run["trace"] if "conv_general_kernelIf" in name][1:]
         assert len(inner) == 2 and all("ILi" not in name and "IfLi128ELi32E" in name for name in inner), inner
+
+
+def test_eight_channels_with_many_taps_bf16(checked):
+    want, cases = [], []
+    for cin, cout, k, general in ((8, 8, 3, 2), (8, 8, 5, 0), (8, 16, 5, 2), (16, 8, 5, 2)):
+        b = nets._Builder()
+        b.dense(b.gap(b.relu(b.conv(b.relu(b.conv(0, cin)), cout, k=k, pad=k // 2))), 10)
+        cases.append(case(b, (12, 12, 3), 32, [1, 1], 1))
+        want.append(general)
+    runs = checked(cases)
+    assert [layers_in(r["trace"], "conv_general") for r in runs] == want
+    assert_clean(checked, cases)
