@@ -1047,22 +1047,19 @@ hipError_t launch_wgrad_fast(const FastWgradParams& p0, int n_active, hipStream_
     // Only for long contractions: with few pixels per weight (the deep layers) the kernel's time is in the epilogue
     // (gradient store or fused update), which the smaller tiles overlap with other workgroups' K loops -- measured 5-30 %
     // faster there at every count of active replicas.
-    // The 256 x 256 tile's slabs of 64 must hold a single position too: with a position table and an odd multiple of 32 images
-    // the 256 x 128 tile (slabs of 32) stands in for it.
     int bmt = 128;
     const bool long_k = p.tile_hint == 1 || p.K >= 4096;
-    const bool cols256 = p.N % 256 == 0 && (!p.perm || p.B % 64 == 0);
-    if (long_k && cols256) {
+    if (long_k && p.N % 256 == 0) {
         const long long blocks = (long long)((p.M + 255) / 256) * (p.N / 256) * p.splits * n_active;
         const long long rounds = (blocks + big.n_cu - 1) / big.n_cu;
         if (p.tile_hint == 1 || blocks * 5 >= rounds * big.n_cu * 4) bmt = 256;
     } else if (long_k && p.N % 128 == 0) {
         if (p.tile_hint == 1 || (long long)((p.M + 255) / 256) * (p.N / 128) * p.splits * n_active >= 2LL * big.n_cu) bmt = 256;
     }
-    const int bkt = bmt == 256 && cols256 ? 64 : 32;
+    const int bkt = bmt == 256 && p.N % 256 == 0 ? 64 : 32;
     // position-sorted contraction: a slab must hold a single position
     if (p.perm && (p.B % bkt != 0 || (p.splits > 1 && p.kchunk % bkt != 0))) return hipErrorInvalidValue;
-    if (bmt == 256 && cols256) {
+    if (bmt == 256 && p.N % 256 == 0) {
         static const bool lds_ok = hipFuncSetAttribute((const void*)wgrad_kernel<256, 256, 2, 4, 64>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kBigWgradLds) == hipSuccess;
         if (!lds_ok) return hipErrorInvalidValue;

@@ -200,7 +200,8 @@ def test_regular_layers_bf16_position_sorted_rows(hint):
 
 
 def test_position_sorted_rows_of_an_odd_multiple_of_32_images():
-    """Batch 96 on 4x4 images, 256 output channels, largest tiles: no slab of the weight gradient may straddle two positions."""
+    """Batch 96 on 4x4 images, 256 output channels, largest tiles: forward and data gradient sort the positions, the weight
+    gradient, which gets the position table for multiples of 64 images only, does not."""
     b = nets._Builder()
     b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(b.relu(b.conv(0, 64)), 256))), 256))), 5)
     ops, shape, batch, N = b.array(), (4, 4, 3), 96, 2
