@@ -16,6 +16,8 @@
 // images with at most 128 channels: tile and border resident in LDS), wgrad_kernel (weight gradient: operands stored
 // as they arrive and transposed by the LDS read), wgrad_taps_kernel (weight gradient on wide images: all taps from one
 // patch), weight_prep_kernel.  Each has its own comment.
+#include <algorithm>
+
 #include "train_kernels.h"
 #include "conv_stats.h"
 
@@ -29,6 +31,7 @@ typedef float f16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBigLds = 2 * (256 + 256) * 72 * 2;   // dynamic LDS of the 256 x 256 kernel: two buffers of both operands
+constexpr long long kComputeUnits = 256;             // of an MI355X
 constexpr int kBigWgradLds = 2 * 64 * 2 * (256 + 32) * 2;   // 256 x 256 weight-gradient kernel: two buffers of 64 rows per operand
 
 // Workgroups are handed to the eight accelerator dies in turn (workgroup i runs on die i % 8), and each die has its own
@@ -951,7 +954,65 @@ BigTileInfo query_big_tile()
     return b;
 }
 
+// Kernel and tile of a weight gradient
+enum class WgradTile { taps, t256x256, t256x128, t128x128, t128x64 };
+WgradTile wgrad_tile(const FastWgradParams& p, long long n_active)
+{
+    // wide images with at most 128 channels in and out: all taps from one patch
+    const bool wide = (p.W == 16 || p.W == 32) && p.C <= 128 && p.N <= 128 && !p.perm;
+    const bool eight = p.W == 8 && p.H % 4 == 0;             // (the kernel walks pixels in memory order: no position table)
+    if ((wide || eight) && p.C % 64 == 0 && p.R == 3 && p.S == 3 && p.pad == 1 &&
+        (p.H * p.W) % 32 == 0 && p.K % 32 == 0 && (p.splits == 1 || p.kchunk % 32 == 0) && p.M == 9 * p.C + (p.has_bias ? 1 : 0) &&
+        p.tile_hint != 2) return WgradTile::taps;
+    // 256-row tiles (and 256 columns where the layer has them) when the launch still fills the chip.
+    // Only for long contractions: with few pixels per weight (the deep layers) the kernel's time is in the epilogue
+    // (gradient store or fused update), which the smaller tiles overlap with other workgroups' K loops -- measured 5-30 %
+    // faster there at every count of active replicas.
+    const bool long_k = p.tile_hint == 1 || p.K >= 4096;
+    if (long_k && p.N % 256 == 0) {
+        const long long blocks = (long long)((p.M + 255) / 256) * (p.N / 256) * p.splits * n_active;
+        const long long rounds = (blocks + kComputeUnits - 1) / kComputeUnits;
+        if (p.tile_hint == 1 || blocks * 5 >= rounds * kComputeUnits * 4) return WgradTile::t256x256;
+    } else if (p.tile_hint == 1 && p.N % 128 == 0) {         // (on request only: 256 to 128 channels, 16 x 16 images,
+        // batch 100, 12 replicas 1.33 ms in these tiles, 0.28 in 128 x 128)
+        return WgradTile::t256x128;
+    }
+    return p.N % 128 == 0 ? WgradTile::t128x128 : WgradTile::t128x64;
+}
+
 }  // namespace
+
+// The split-K factor with the least estimated time.  A workgroup walks K / s pixels in steps of 32 (and `extra` steps' time of
+// first loads and epilogue); `step` is the time in us of a step when one, two, ... workgroups share a compute unit, and a
+// launch of more runs in rounds of that many, the last one partly filled.  A split writes and reads 8 bytes per weight at
+// 5.7 TB/s and the reduction costs 4.5 us; without one the update in the epilogue moves them at 3.5 TB/s.
+// Fitted to 568 launches (64 to 512 channels, 2 x 2 to 32 x 32 images, 1 to 32 replicas, 1 to 64 splits), times within 10 %; the
+// choice takes 0.5 % longer than the best measured split on average and 8 % at worst.  As many splits as fit one round of
+// resident workgroups: 7 % and 66 % (256 channels, 16 x 16 images, batch 100, 12 replicas: one split 1.66 times the time of
+// two, whose 256 x 256 tiles fill their rounds); splits for 2048 workgroups of 128 x 128: 19 % and 89 %.
+int wgrad_fast_splits(const FastWgradParams& shape, int n_active)
+{
+    static constexpr struct { int m, n, resident; float extra, step[4]; } kTile[] = {
+        {64, 64, 2, 0.f, {0.79f, 1.11f}}, {256, 256, 1, 0.f, {1.17f}}, {256, 128, 1, 0.f, {8.f}},
+        {128, 128, 3, 2.15f, {0.78f, 0.85f, 0.99f}}, {128, 64, 4, 2.15f, {0.67f, 0.72f, 0.84f, 0.97f}}};
+    FastWgradParams p = shape;
+    p.kchunk = 64;                                           // (whole slabs, whatever the split)
+    const float moved = (float)p.M * (float)p.N * (float)n_active * 8e-6f;
+    int best = 1;
+    float best_t = 0.f;
+    for (p.splits = 1; p.splits <= std::min(256, std::max(1, p.K / 128)); ++p.splits) {
+        const WgradTile kind = wgrad_tile(p, n_active);
+        const auto& t = kTile[(int)kind];
+        const long long rows = kind == WgradTile::taps ? p.C : p.M;          // (that kernel's workgroup holds all taps)
+        const long long wgs = (rows + t.m - 1) / t.m * (p.N / t.n) * p.splits * n_active;
+        const long long round = kComputeUnits * t.resident, rest = wgs % round;
+        const float rounds = (float)(wgs / round) * t.step[t.resident - 1] + (rest ? t.step[(rest - 1) / kComputeUnits] : 0.f);
+        const float loop = ((float)p.K / (32.0f * (float)p.splits) + t.extra) * rounds;
+        const float time = loop + (p.splits > 1 ? moved * (float)(p.splits + 1) / 5.7f + 4.5f : moved / 3.5f);
+        if (p.splits == 1 || time < best_t) { best = p.splits; best_t = time; }
+    }
+    return best;
+}
 
 hipError_t launch_conv_fast(const FastConvParams& p0, int epi, int n_active, hipStream_t s, int* stat_rows)
 {
@@ -1023,12 +1084,8 @@ hipError_t launch_wgrad_fast(const FastWgradParams& p0, int n_active, hipStream_
     FastWgradParams p = p0;
     p.n_active = n_active;
     if (p.C % 8 != 0 || p.N % 64 != 0) return hipErrorInvalidValue;
-    // wide images with at most 128 channels in and out: all taps from one patch
-    const bool wide = (p.W == 16 || p.W == 32) && p.C <= 128 && p.N <= 128 && !p.perm;
-    const bool eight = p.W == 8 && p.H % 4 == 0;             // (the kernel walks pixels in memory order: no position table)
-    if ((wide || eight) && p.C % 64 == 0 && p.R == 3 && p.S == 3 && p.pad == 1 &&
-        (p.H * p.W) % 32 == 0 && p.K % 32 == 0 && (p.splits == 1 || p.kchunk % 32 == 0) && p.M == 9 * p.C + (p.has_bias ? 1 : 0) &&
-        p.tile_hint != 2) {
+    const WgradTile tile = wgrad_tile(p, n_active);
+    if (tile == WgradTile::taps) {
         const dim3 grid(die_grid((long long)(p.C / 64) * (p.N / 64) * p.splits * n_active));
         if (p.W == 8) {
             constexpr size_t lds = 2 * ((size_t)6 * 10 + 32) * 192;
@@ -1042,43 +1099,27 @@ hipError_t launch_wgrad_fast(const FastWgradParams& p0, int n_active, hipStream_
         }
         return hipGetLastError();
     }
-    // 256-row tiles (and 256 columns where the layer has them) when the launch still fills the chip
-    static const BigTileInfo big = query_big_tile();
-    // Only for long contractions: with few pixels per weight (the deep layers) the kernel's time is in the epilogue
-    // (gradient store or fused update), which the smaller tiles overlap with other workgroups' K loops -- measured 5-30 %
-    // faster there at every count of active replicas.
-    int bmt = 128;
-    const bool long_k = p.tile_hint == 1 || p.K >= 4096;
-    if (long_k && p.N % 256 == 0) {
-        const long long blocks = (long long)((p.M + 255) / 256) * (p.N / 256) * p.splits * n_active;
-        const long long rounds = (blocks + big.n_cu - 1) / big.n_cu;
-        if (p.tile_hint == 1 || blocks * 5 >= rounds * big.n_cu * 4) bmt = 256;
-    } else if (long_k && p.N % 128 == 0) {
-        if (p.tile_hint == 1 || (long long)((p.M + 255) / 256) * (p.N / 128) * p.splits * n_active >= 2LL * big.n_cu) bmt = 256;
-    }
-    const int bkt = bmt == 256 && p.N % 256 == 0 ? 64 : 32;
+    const int bkt = tile == WgradTile::t256x256 ? 64 : 32;
     // position-sorted contraction: a slab must hold a single position
     if (p.perm && (p.B % bkt != 0 || (p.splits > 1 && p.kchunk % bkt != 0))) return hipErrorInvalidValue;
-    if (bmt == 256 && p.N % 256 == 0) {
+    if (tile == WgradTile::t256x256) {
         static const bool lds_ok = hipFuncSetAttribute((const void*)wgrad_kernel<256, 256, 2, 4, 64>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kBigWgradLds) == hipSuccess;
         if (!lds_ok) return hipErrorInvalidValue;
         const dim3 grid(die_grid((long long)((p.M + 255) / 256) * (p.N / 256) * p.splits * n_active));
         hipLaunchKernelGGL((wgrad_kernel<256, 256, 2, 4, 64>), grid, dim3(512), kBigWgradLds, s, p);
-    } else if (bmt == 256 && p.N % 128 == 0) {
+    } else if (tile == WgradTile::t256x128) {
         constexpr size_t lds = 2 * 32 * ((256 + 32) * 2 + (128 + 32) * 2);
         const dim3 grid(die_grid((long long)((p.M + 255) / 256) * (p.N / 128) * p.splits * n_active));
         hipLaunchKernelGGL((wgrad_kernel<256, 128, 2, 2, 32>), grid, dim3(256), lds, s, p);
-    } else if (bmt == 128 && p.N % 128 == 0) {
+    } else if (tile == WgradTile::t128x128) {
         constexpr size_t lds = 2 * 32 * ((128 + 32) * 2 + (128 + 32) * 2);
         const dim3 grid(die_grid((long long)((p.M + 127) / 128) * (p.N / 128) * p.splits * n_active));
         hipLaunchKernelGGL((wgrad_kernel<128, 128, 2, 2, 32>), grid, dim3(256), lds, s, p);
-    } else if (bmt == 128) {
+    } else {
         constexpr size_t lds = 2 * 32 * ((128 + 32) * 2 + (64 + 32) * 2);
         const dim3 grid(die_grid((long long)((p.M + 127) / 128) * (p.N / 64) * p.splits * n_active));
         hipLaunchKernelGGL((wgrad_kernel<128, 64, 2, 2, 32>), grid, dim3(256), lds, s, p);
-    } else {
-        return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -214,17 +214,18 @@ int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Lay
     return wgrad_general_splits((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
 }
 
-// The same for a lean layer: as many splits as still fit one round of resident workgroups (two per compute unit in the
-// all-taps kernel, three in the general one).  Every split more writes and reads 8 bytes per weight, and without any the
-// update happens in the kernel.  (Splits for at least 2048 workgroups before: VGG-16 on 32 replicas, 256 channels on 8 x 8
-// images in two splits of 512 workgroups instead of one; the round 61.4 -> 60.3 ms, ResNet-18 on 6 replicas 13.4 -> 12.9.)
-int lean_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
+// The same for a lean layer
+FastWgradParams lean_wgrad_shape(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
     const TensorShape a = plan.tensors[l.in0];
-    const bool taps = ((a.w == 16 || a.w == 32) && a.c <= 128 && l.cout <= 128) || (a.w == 8 && a.h % 4 == 0);
-    const int64_t rows = (int64_t)l.k * l.k * a.c + (l.bias ? 1 : 0), K = (int64_t)cfg.batch * a.h * a.w;
-    const int64_t wgs = (taps ? (int64_t)(a.c / 64) * (l.cout / 64) : (rows + 127) / 128 * ((l.cout + 127) / 128)) * n;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((taps ? 512 : 768) / wgs, K / 512), 256));
+    FastWgradParams f{};
+    f.B = cfg.batch; f.H = a.h; f.W = a.w; f.C = a.c; f.N = l.cout; f.R = f.S = l.k; f.pad = l.pad;
+    f.K = cfg.batch * a.h * a.w; f.has_bias = l.bias; f.M = l.k * l.k * a.c + (l.bias ? 1 : 0);
+    return f;
+}
+int lean_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
+{
+    return wgrad_fast_splits(lean_wgrad_shape(cfg, plan, l), n);
 }
 
 // floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels: one entry per
@@ -878,9 +879,8 @@ struct Runner {
                 run("conv_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_first_wgrad(fc, na, s); });
             } else
             if (e.fast[i]) {
-                FastWgradParams f{};
-                f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
-                f.M = p.M; f.K = p.K; f.kchunk = p.kchunk; f.splits = p.splits; f.w_shift = p.w_shift; f.has_bias = l.bias;
+                FastWgradParams f = lean_wgrad_shape(e.cfg, e.plan, l);
+                f.kchunk = p.kchunk; f.splits = p.splits; f.w_shift = p.w_shift;
                 f.x = act(l.in0); f.x_rep = e.rep_block; f.dy = grad(ot); f.dy_rep = e.rep_block;
                 f.out = p.out; f.out_rep = p.out_rep; f.out_split = p.out_split; f.order = e.buf.order;
                 if (p.H * p.W <= kMaxTablePositionsWgrad && p.B % 64 == 0) { f.perm = perm(i); f.posmask = posmask(i); }

@@ -91,6 +91,7 @@ struct FastWgradParams {     // dW[(tap, ci) | bias row][co] over pixels; needs 
     int n_active;                               // set by the launcher
 };
 hipError_t launch_wgrad_fast(const FastWgradParams& p, int n_active, hipStream_t s);
+int wgrad_fast_splits(const FastWgradParams& shape, int n_active);     // split-K factor (of the fields above x)
 
 // ---- bf16 configuration, first convolution (fp32 data set in, few channels): conv_first_bf16.hip ----
 struct FirstConvParams {     // K = R*S*C footprint values per pixel (K + bias row <= 32), N = 32 or 64 output channels, stride 1

@@ -205,3 +205,15 @@ def test_eight_channels_with_many_taps_bf16(checked):
     runs = checked(cases)
     assert [layers_in(r["trace"], "conv_general") for r in runs] == want
     assert_clean(checked, cases)
+
+
+@pytest.mark.parametrize("shape", [(256, 128, 16, 64, 12), (256, 256, 16, 100, 12), (192, 320, 8, 100, 8), (512, 512, 4, 64, 3), (64, 64, 32, 32, 2)])
+def test_lean_weight_gradient_splits(checked, shape):
+    """The split sums of every count of active replicas stay in their region, and no launch takes 256 x 128 tiles unasked."""
+    cin, cout, side, batch, n = shape
+    b = nets._Builder()
+    b.dense(b.gap(b.relu(b.conv(b.relu(b.conv(0, cin)), cout))), 10)
+    cases = [case(b, (side, side, 3), batch, list(range(1, n + 1)), 1)]
+    (run,) = checked(cases)
+    assert layers_in(run["trace"], "wgrad_") > 0 and layers_in(run["trace"], "wgrad_kernelILi256ELi128E") == 0
+    assert_clean(checked, cases)
