@@ -990,7 +990,7 @@ WgradTile wgrad_tile(const FastWgradParams& p, long long n_active)
 // choice takes 0.5 % longer than the best measured split on average and 8 % at worst.  As many splits as fit one round of
 // resident workgroups: 7 % and 66 % (256 channels, 16 x 16 images, batch 100, 12 replicas: one split 1.66 times the time of
 // two, whose 256 x 256 tiles fill their rounds); splits for 2048 workgroups of 128 x 128: 19 % and 89 %.
-int wgrad_fast_splits(const FastWgradParams& shape, int n_active)
+WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active)
 {
     static constexpr struct { int m, n, resident; float extra, step[4]; } kTile[] = {
         {64, 64, 2, 0.f, {0.79f, 1.11f}}, {256, 256, 1, 0.f, {1.17f}}, {256, 128, 1, 0.f, {8.f}},
@@ -1011,7 +1011,7 @@ int wgrad_fast_splits(const FastWgradParams& shape, int n_active)
         const float time = loop + (p.splits > 1 ? moved * (float)(p.splits + 1) / 5.7f + 4.5f : moved / 3.5f);
         if (p.splits == 1 || time < best_t) { best = p.splits; best_t = time; }
     }
-    return best;
+    return {best, 0};
 }
 
 hipError_t launch_conv_fast(const FastConvParams& p0, int epi, int n_active, hipStream_t s, int* stat_rows)

@@ -957,34 +957,6 @@ hipError_t launch_conv(GeneralConvParams& p, int n_active, hipStream_t s, int* s
     }
 }
 
-// Tile and split-K factor of a weight gradient: the estimate of the launch's time with the least.  A workgroup walks K / s
-// pixels in slabs of 32 (and about three slabs' time of first loads and epilogue); per slab of a 128 x 128 tile 2.2 us when it
-// has its compute unit to itself, 2.7 when two share one, and 1.3 of the unit's time per workgroup in launches of more than
-// two per unit, which end with half a workgroup's time of partly filled units; smaller tiles in proportion.  The partial
-// sums move 8 bytes per weight and split at 4 TB/s.  64 x 64 tiles win where the larger ones leave compute units idle at
-// every split.  (Measured in us, 3 x 3, batch 64.  128 channels on 16 x 16 images, 16 replicas, s = 1 2 4 8 16 32: 1082 664 598
-// 477 426 441; 1 replica, s = 28 51 64: 49 41 49 and with 64 x 64 tiles 45 51 45; 64 channels on 32 x 32 images, 1 replica,
-// s = 32 64: 110 67 and 82 55; 80 channels on 5 x 5 images, batch 50, 3 replicas: 21 and 16.)
-struct WgradPlan { bool small; int splits; };
-WgradPlan wgrad_plan(int rows, int N, int K, int n_active, bool gather)
-{
-    struct { int m, n; float f; } tile[2] = {{128, N > 64 ? 128 : N > 32 ? 64 : 32, N > 64 ? 1.0f : N > 32 ? 0.68f : 0.45f}, {64, 64, 0.35f}};
-    if (gather) tile[0] = {32, N > 32 ? 64 : 32, 0.25f};
-    const float moved = (float)rows * (float)N * (float)n_active * 8.0f / 4e6f;
-    WgradPlan best{false, 1};
-    float best_t = 0.f;
-    for (int v = 0; v < (gather || N <= 32 ? 1 : 2); ++v) {
-        const float wgs = (float)((rows + tile[v].m - 1) / tile[v].m) * (float)((N + tile[v].n - 1) / tile[v].n) * (float)n_active;
-        for (int s = 1; s <= std::min(256, std::max(1, K / 128)); ++s) {
-            const float steps = ((float)K / (32.0f * (float)s) + 3.0f) * tile[v].f, w = wgs * (float)s;
-            float t = w <= 256.f ? steps * 2.2f : w <= 512.f ? steps * 2.7f : w * steps * 1.3f / 256.f + 0.5f * steps * 2.2f;
-            if (s > 1) t += moved * (float)(s + 1);
-            if ((v == 0 && s == 1) || t < best_t) { best = {v == 1, s}; best_t = t; }
-        }
-    }
-    return best;
-}
-
 template <typename T, typename SRC, int BMT, int BN, int WGM, int WGN, bool GATHER = false>
 hipError_t launch_wgrad_t(const GeneralWgradParams& p, int n_active, hipStream_t s)
 {
@@ -1007,12 +979,11 @@ template <typename T, typename SRC>
 hipError_t launch_wgrad(const GeneralWgradParams& p, int n_active, hipStream_t s)
 {
     const bool gather = p.cursor && p.gather;
-    const WgradPlan plan = wgrad_plan(p.R * p.S * p.C, p.N, p.K, n_active, gather);
     if constexpr (std::is_same<T, float>::value) {
         if (gather && p.N <= 32) return launch_wgrad_t<T, SRC, 32, 32, 1, 1, true>(p, n_active, s);
         if (gather) return launch_wgrad_t<T, SRC, 32, 64, 1, 2, true>(p, n_active, s);
     }
-    if (plan.small) return launch_wgrad_t<T, SRC, 64, 64, 2, 2>(p, n_active, s);
+    if (p.small_tiles) return launch_wgrad_t<T, SRC, 64, 64, 2, 2>(p, n_active, s);
     if (p.N > 64) return launch_wgrad_t<T, SRC, 128, 128, 2, 2>(p, n_active, s);
     if (p.N > 32) return launch_wgrad_t<T, SRC, 128, 64, 4, 1>(p, n_active, s);
     return launch_wgrad_t<T, SRC, 128, 32, 4, 1>(p, n_active, s);
@@ -1046,7 +1017,32 @@ hipError_t launch_conv_general(const GeneralConvParams& p0, int epi, int n_activ
     return epi == 0 ? launch_conv<__bf16, 0>(p, n_active, s, stat_rows) : launch_conv<__bf16, 1>(p, n_active, s, stat_rows);
 }
 
-int wgrad_general_splits(int rows, int N, int K, int n_active, int gather) { return wgrad_plan(rows, N, K, n_active, gather != 0).splits; }
+// Tile and split-K factor of a weight gradient: the estimate of the launch's time with the least.  A workgroup walks K / s
+// pixels in slabs of 32 (and about three slabs' time of first loads and epilogue); per slab of a 128 x 128 tile 2.2 us when it
+// has its compute unit to itself, 2.7 when two share one, and 1.3 of the unit's time per workgroup in launches of more than
+// two per unit, which end with half a workgroup's time of partly filled units; smaller tiles in proportion.  The partial
+// sums move 8 bytes per weight and split at 4 TB/s.  64 x 64 tiles win where the larger ones leave compute units idle at
+// every split.  (Measured in us, 3 x 3, batch 64.  128 channels on 16 x 16 images, 16 replicas, s = 1 2 4 8 16 32: 1082 664 598
+// 477 426 441; 1 replica, s = 28 51 64: 49 41 49 and with 64 x 64 tiles 45 51 45; 64 channels on 32 x 32 images, 1 replica,
+// s = 32 64: 110 67 and 82 55; 80 channels on 5 x 5 images, batch 50, 3 replicas: 21 and 16.)
+WgradPlan wgrad_general_plan(int rows, int N, int K, int n_active, int gather)
+{
+    struct { int m, n; float f; } tile[2] = {{128, N > 64 ? 128 : N > 32 ? 64 : 32, N > 64 ? 1.0f : N > 32 ? 0.68f : 0.45f}, {64, 64, 0.35f}};
+    if (gather) tile[0] = {32, N > 32 ? 64 : 32, 0.25f};
+    const float moved = (float)rows * (float)N * (float)n_active * 8.0f / 4e6f;
+    WgradPlan best{1, 0};
+    float best_t = 0.f;
+    for (int v = 0; v < (gather || N <= 32 ? 1 : 2); ++v) {
+        const float wgs = (float)((rows + tile[v].m - 1) / tile[v].m) * (float)((N + tile[v].n - 1) / tile[v].n) * (float)n_active;
+        for (int s = 1; s <= std::min(256, std::max(1, K / 128)); ++s) {
+            const float steps = ((float)K / (32.0f * (float)s) + 3.0f) * tile[v].f, w = wgs * (float)s;
+            float t = w <= 256.f ? steps * 2.2f : w <= 512.f ? steps * 2.7f : w * steps * 1.3f / 256.f + 0.5f * steps * 2.2f;
+            if (s > 1) t += moved * (float)(s + 1);
+            if ((v == 0 && s == 1) || t < best_t) { best = {s, v}; best_t = t; }
+        }
+    }
+    return best;
+}
 
 hipError_t launch_wgrad_general(const GeneralWgradParams& p0, int n_active, hipStream_t s)
 {

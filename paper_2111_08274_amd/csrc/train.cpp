@@ -26,7 +26,8 @@ public:
     int64_t shared_floats = 0;
     int64_t bn_off = 0, bn_floats = 0;    // per-chunk partial sums of the batch-norm reductions (their own region: weight
                                           // gradients may run beside them on the side stream)
-    std::vector<int> splits;              // per layer: split-K factor of the weight gradient (general layers: chosen per launch)
+    std::vector<int> splits;              // per layer: split-K factor of the weight gradient
+    std::vector<std::vector<WgradPlan>> wgrad_plans;   // lean and general layers: the plan for 1, 2, ... active replicas instead
     std::vector<int> bn_chunks;           // per layer
     std::vector<char> grad_written;       // scratch for the backward pass
     // ReLU fusion: a ReLU that is the only consumer of a conv / dense / BN / add output is folded into that layer's
@@ -93,6 +94,7 @@ int ilog2_exact(int v) { int s = 0; while ((1 << s) < v) ++s; return (1 << s) ==
 struct Layout {
     std::vector<int64_t> act_off, grad_off, saved_off;
     std::vector<int> splits, bn_chunks;
+    std::vector<std::vector<WgradPlan>> wgrad_plans;
     int64_t rep_block = 0, shared_floats = 0, bn_floats = 0;
     std::vector<char> fast, general, general_w;
     std::vector<int64_t> wf_off, wb_off;       // in 2-byte units inside one replica's block of weight copies
@@ -206,15 +208,15 @@ bool general_wgrad(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
     return general_layer(cfg, plan, l) && !(gather_layer(cfg, l) && plan.tensors[0].c % 4 == 0 && l.k * l.k * plan.tensors[0].c > 32);
 }
 
-// Split-K factor of a general layer's weight gradient with n active replicas
-int general_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
+// Plan of a general layer's weight gradient with n active replicas
+WgradPlan general_wgrad_plan(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
-    return wgrad_general_splits((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
+    return wgrad_general_plan((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
 }
 
-// The same for a lean layer
+// What the plan of a lean layer's follows from
 FastWgradParams lean_wgrad_shape(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
     const TensorShape a = plan.tensors[l.in0];
@@ -223,11 +225,6 @@ FastWgradParams lean_wgrad_shape(const hadfl_config& cfg, const NetPlan& plan, c
     f.K = cfg.batch * a.h * a.w; f.has_bias = l.bias; f.M = l.k * l.k * a.c + (l.bias ? 1 : 0);
     return f;
 }
-int lean_wgrad_splits(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
-{
-    return wgrad_fast_splits(lean_wgrad_shape(cfg, plan, l), n);
-}
-
 // floats per replica of the statistics entries a convolution's epilogue leaves for `rows` outputs of c channels: one entry per
 // tile, which has at least 128 rows in the lean kernels and 32 in the general ones
 int64_t stat_floats(int64_t rows, int c, bool lean) { const int64_t tile = lean ? 128 : 32; return (rows + tile - 1) / tile * 2 * c; }
@@ -242,7 +239,7 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
     for (int t = 1; t < T; ++t) { L.act_off[t] = off; off += up64(B * plan.tensors[t].numel()); }
     for (int t = 1; t < T; ++t) { L.grad_off[t] = off; off += up64(B * plan.tensors[t].numel()); }
     L.saved_off.assign(plan.layers.size(), -1);
-    L.splits.assign(plan.layers.size(), 1);
+    L.splits.assign(plan.layers.size(), 1); L.wgrad_plans.resize(plan.layers.size());
     L.bn_chunks.assign(plan.layers.size(), 1);
     int64_t shared = 0, bn_shared = 0;
     for (size_t i = 0; i < plan.layers.size(); ++i) {
@@ -265,7 +262,8 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
             if (lean_layer(cfg, plan, l) || general_wgrad(cfg, plan, l)) {      // chosen per launch
                 s = 1;
                 for (int n = 1; n <= cfg.n_replicas; ++n) {
-                    const int sn = lean_layer(cfg, plan, l) ? lean_wgrad_splits(cfg, plan, l, n) : general_wgrad_splits(cfg, plan, l, n);
+                    L.wgrad_plans[i].push_back(lean_layer(cfg, plan, l) ? wgrad_fast_plan(lean_wgrad_shape(cfg, plan, l), n) : general_wgrad_plan(cfg, plan, l, n));
+                    const int sn = L.wgrad_plans[i].back().splits;
                     if (sn > 1) shared = std::max<int64_t>(shared, (int64_t)n * sn * up64(M * l.cout));
                 }
             }
@@ -347,7 +345,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
         for (int32_t v : steps) e->n_active[s] += v > s ? 1 : 0;
     const Layout L = make_layout(cfg, plan);
     e->act_off = L.act_off; e->grad_off = L.grad_off; e->saved_off = L.saved_off;
-    e->splits = L.splits; e->bn_chunks = L.bn_chunks;
+    e->splits = L.splits; e->wgrad_plans = L.wgrad_plans; e->bn_chunks = L.bn_chunks;
     e->rep_block = L.rep_block;
     e->shared_off = L.rep_block * cfg.n_replicas;
     e->shared_floats = L.shared_floats;
@@ -859,7 +857,8 @@ struct Runner {
             p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr;
             p.a_f32 = l.in0 == 0;
             p.dy = grad(ot); p.dy_rep = e.rep_block;
-            p.splits = e.general_w[i] ? general_wgrad_splits(e.cfg, e.plan, l, na) : e.fast[i] ? lean_wgrad_splits(e.cfg, e.plan, l, na) : e.splits[i];
+            const WgradPlan wgrad = e.wgrad_plans[i].empty() ? WgradPlan{e.splits[i], 0} : e.wgrad_plans[i][na - 1];
+            p.splits = wgrad.splits;
             const int64_t mn = (int64_t)p.M * p.N;
             if (p.splits > 1) {
                 const int unit = e.fast[i] ? 64 : e.general_w[i] ? 32 : 16;      // slab length of the kernel that will run
@@ -896,7 +895,7 @@ struct Runner {
                 GeneralWgradParams f{};
                 f.bf16 = e.cfg.bf16;
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
-                f.stride = p.stride; f.K = p.K; f.kchunk = p.kchunk; f.splits = p.splits; f.has_bias = l.bias;
+                f.stride = p.stride; f.K = p.K; f.kchunk = p.kchunk; f.splits = p.splits; f.small_tiles = wgrad.small_tiles; f.has_bias = l.bias;
                 f.x = act(l.in0); f.x_rep = e.rep_block; f.dy = grad(ot); f.dy_rep = e.rep_block;
                 f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz; f.gather = gather_layer(e.cfg, l);
                 f.out = p.out; f.out_rep = p.out_rep; f.out_split = p.out_split; f.order = e.buf.order;

@@ -91,7 +91,8 @@ struct FastWgradParams {     // dW[(tap, ci) | bias row][co] over pixels; needs 
     int n_active;                               // set by the launcher
 };
 hipError_t launch_wgrad_fast(const FastWgradParams& p, int n_active, hipStream_t s);
-int wgrad_fast_splits(const FastWgradParams& shape, int n_active);     // split-K factor (of the fields above x)
+struct WgradPlan { int splits, small_tiles; };               // split-K factor; general kernels: 64 x 64 tiles
+WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active);        // (from the fields above x)
 
 // ---- bf16 configuration, first convolution (fp32 data set in, few channels): conv_first_bf16.hip ----
 struct FirstConvParams {     // K = R*S*C footprint values per pixel (K + bias row <= 32), N = 32 or 64 output channels, stride 1
@@ -146,6 +147,7 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
     int B, H, W, C, Ho, Wo, N, R, S, pad, stride;
     int gather;                                // fp32 convolution on the data set: any C
     int K, kchunk, splits, has_bias;           // K = B*Ho*Wo; kchunk a multiple of 32 when splits > 1
+    int small_tiles;                           // of the plan the splits are from
     const float* x; long long x_rep;
     const long long* cursor; int n_samples, batch; long long sample_sz;   // x is the (fp32) data set when cursor != null
     const float* dy; long long dy_rep;
@@ -157,7 +159,7 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
 };
 // Needs C and N multiples of 4 (bf16: 8), tensors of less than 4 GiB per replica.
 hipError_t launch_wgrad_general(const GeneralWgradParams& p, int n_active, hipStream_t s);
-int wgrad_general_splits(int rows, int N, int K, int n_active, int gather);   // split-K factor for rows = R*S*C weights
+WgradPlan wgrad_general_plan(int rows, int N, int K, int n_active, int gather);   // for rows = R*S*C weights
 long long weight_copy_units(int bf16, int rows, int taps, int channels);   // 2-byte units of a copy [rows][taps][channels]
 struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
     const float* w; long long w_rep;
