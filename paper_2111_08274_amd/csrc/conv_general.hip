@@ -14,8 +14,10 @@
 //   normal x normal          K = 64: 1.4e-7 / 1.1e-7 / 4.9e-8    1152: 5.9e-7 / 5.2e-7 / 1.9e-7    16384: 2.4e-6 / 2.1e-6 / 8.2e-7
 //   ReLU(normal) x normal    K = 64: 1.0e-7 / 1.1e-7 / 3.8e-8    1152: 4.3e-7 / 5.0e-7 / 1.5e-7    16384: 1.6e-6 / 2.0e-6 / 7.2e-7
 //   positive x positive      K = 64: 6.4e-7 / 4.6e-7 / 2.7e-7    1152: 1.1e-5 / 7.6e-6 / 4.0e-6    16384: 1.6e-4 / 1.1e-4 / 5.8e-5
-// A value that is not finite, or an accumulator that overflows, makes the six products disagree with the one (Inf * 0):
-// a tile that finds a result that is not finite is computed again with the fp32 instruction, which is what it then stores.
+// The parts are those of the operand times 2^24, so that no bit of a small float is lost (see split3), and the sums are
+// scaled back.  An operand from 2^104 on or not finite, or an accumulator that overflows, makes the six products disagree
+// with the one (Inf * 0): a tile that finds a result that is not finite is computed again with the fp32 instruction
+// from the floats themselves, which is what it then stores.
 //
 //   * The weights are kept as two copies per layer, refreshed from the master before every forward pass,
 //       Wf[co][tap][ci]  and  Wb[ci][flipped tap][co],
@@ -69,6 +71,28 @@ __device__ __forceinline__ void store4(__bf16* p, f4& v)
 __device__ __forceinline__ u4 round8(const f4& a, const f4& b)
 {
     return u4{to_bf16x2(a[0], a[1]), to_bf16x2(a[2], a[3]), to_bf16x2(b[0], b[1]), to_bf16x2(b[2], b[3])};
+}
+
+// The parts of a weight in its copy, of 2^24 times the weight as in split3.  A weight too large for that, or not finite, has a
+// NaN for the first part, so that no tile that meets it keeps the products of parts, and its 32 bits in the other two.
+__device__ __forceinline__ void split_weight(float x, __bf16& h, __bf16& m, __bf16& l)
+{
+    if (fabsf(x) < 0x1p103f) {
+        const float y = x * kSplitScale;
+        h = (__bf16)y;
+        const float r = y - (float)h;
+        m = (__bf16)r;
+        l = (__bf16)(r - (float)m);
+    } else {
+        const unsigned bits = __builtin_bit_cast(unsigned, x);
+        h = __builtin_bit_cast(__bf16, (unsigned short)0x7fc0);
+        m = __builtin_bit_cast(__bf16, (unsigned short)(bits >> 16)); l = __builtin_bit_cast(__bf16, (unsigned short)bits);
+    }
+}
+__device__ __forceinline__ float join_weight(__bf16 h, __bf16 m, __bf16 l)
+{
+    if ((float)h == (float)h) return (((float)l + (float)m) + (float)h) * (1.0f / kSplitScale);
+    return __builtin_bit_cast(float, (unsigned)__builtin_bit_cast(unsigned short, m) << 16 | __builtin_bit_cast(unsigned short, l));
 }
 
 // What one residue class of pixels needs (one class, the whole image, unless it is a strided data gradient)
@@ -351,7 +375,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            acc[i][j] += low[i][j];
+            acc[i][j] = (acc[i][j] + low[i][j]) * kProductScale;
 #pragma unroll
             for (int v = 0; v < 16; ++v) bad = __builtin_fmaf(acc[i][j][v], 0.f, bad);
         }
@@ -384,7 +408,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
 #pragma unroll
                     for (int j = 0; j < TN; ++j) {
                         const __bf16* w = reinterpret_cast<const __bf16*>(sBc + (wn * (BN / WGN) + j * 32 + (lane & 31)) * kRow) + k;
-                        b[j] = ((float)w[64] + (float)w[32]) + (float)w[0];
+                        b[j] = join_weight(w[0], w[32], w[64]);
                     }
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
@@ -740,7 +764,7 @@ __global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_genera
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            acc[i][j] += low[i][j];
+            acc[i][j] = (acc[i][j] + low[i][j]) * kProductScale;
 #pragma unroll
             for (int v = 0; v < 16; ++v) bad = __builtin_fmaf(acc[i][j][v], 0.f, bad);
         }
@@ -822,17 +846,7 @@ __global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_genera
 
 // fp32 master W[tap][ci][co] -> Wf[co][tap][ci] and Wb[ci][T-1-tap][co] as described at the top.  A workgroup handles one
 // tap and a 64 x 64 (ci, co) tile; each thread forms 16-byte groups of eight positions.  Bound by memory: 4 bytes read and
-// 12 (bf16: 4) written per weight.  A weight whose bf16 rounding overflows is cut instead, and one that is not finite
-// has zero lower parts, so that the three parts always add up to the weight.
-__device__ __forceinline__ void split_weight(float x, __bf16& h, __bf16& m, __bf16& l)
-{
-    h = (__bf16)x;
-    if (!(fabsf((float)h) < __builtin_inff())) h = __builtin_bit_cast(__bf16, (unsigned short)(__builtin_bit_cast(unsigned, x) >> 16));
-    float r = x - (float)h;
-    if (!(fabsf(x) < __builtin_inff())) { h = (__bf16)x; r = 0.f; }
-    m = (__bf16)r;
-    l = (__bf16)(r - (float)m);
-}
+// 12 (bf16: 4) written per weight.
 template <typename T>
 __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
 {

@@ -217,3 +217,15 @@ def test_lean_weight_gradient_splits(checked, shape):
     (run,) = checked(cases)
     assert layers_in(run["trace"], "wgrad_") > 0 and layers_in(run["trace"], "wgrad_kernelILi256ELi128E") == 0
     assert_clean(checked, cases)
+
+
+def test_split_float_layers_reach_every_tile(checked):
+    """The dense layers of tests/test_gpu_split_floats.py between them take every tile of the fp32 launcher, in both directions."""
+    from tests.test_gpu_split_floats import LAYERS, dense_net
+    runs = checked([case(dense_net(c, n, 1), (1, 1, 32), batch, [1] * replicas, 0, classes=20, options=[(1, hint)])
+                    for c, n, batch, replicas, hint in LAYERS])
+    seen = {name.split("kernelIfLi")[1].split("EEEv")[0] for r in runs for name in r["trace"] if "conv_general_kernelIf" in name}
+    tiles = ("32ELi32ELi1ELi1ELi8ELi1", "64ELi64ELi2ELi2ELi4ELi1", "64ELi64ELi2ELi2ELi2ELi1", "128ELi64ELi4ELi1ELi1ELi1", "128ELi128ELi2ELi4ELi1ELi2",
+             "256ELi128ELi4ELi2ELi1ELi2", "128ELi32ELi4ELi1ELi1ELi1")
+    missing = {"%sELi%dELb0" % (t, epi) for t in tiles for epi in (0, 1)} - seen
+    assert not missing, missing
