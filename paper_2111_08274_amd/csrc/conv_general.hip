@@ -928,30 +928,26 @@ hipError_t launch_conv(GeneralConvParams& p, int n_active, hipStream_t s, int* s
         // 10 us (16 channels, 3 x 3, 28 x 28 images, 100 k pixels, forward and data gradient: 64 x 64 in two groups 48 and 45 us,
         // 128 x 32 29 and 29).
         static constexpr struct { int m, n; float alone, share; } kTile[] = {
-            {32, 32, 0.28f, 0.37f}, {64, 64, 0.50f, 0.62f}, {64, 64, 0.61f, 0.46f}, {64, 64, 0.85f, 0.48f},
-            {128, 64, 0.92f, 0.83f}, {128, 64, 1.33f, 0.816f}, {128, 128, 1.22f, 1.50f}, {128, 128, 1.9f, 1.53f}, {256, 128, 1.95f, 2.83f},
-            {128, 32, 1.6f, 0.50f}};
+            {32, 32, 0.28f, 0.37f}, {64, 64, 0.50f, 0.62f}, {64, 64, 0.61f, 0.46f}, {128, 64, 1.33f, 0.816f},
+            {128, 128, 1.22f, 1.50f}, {256, 128, 1.95f, 2.83f}, {128, 32, 1.6f, 0.50f}};
         const float slabs = (float)(p.R * p.S * ((p.C + 31) / 32)) / (float)p.classes + 3.0f;
         int best = 0;
         float best_t = 0.f;
-        for (int i = 0; i < 10; ++i) {
-            if (p.N <= 32 ? i > 2 && i < 9 : i == 9 || (p.N <= 64 && kTile[i].n > 64)) continue;
+        for (int i = 0; i < 7; ++i) {
+            if (p.N <= 32 ? i > 2 && i < 6 : i == 6 || (p.N <= 64 && kTile[i].n > 64)) continue;
             const long long tiles = (rows0 + kTile[i].m - 1) / kTile[i].m * ((p.N + kTile[i].n - 1) / kTile[i].n) * groups;
             const float step = tiles <= 256 ? kTile[i].alone : std::max(kTile[i].alone, (float)((tiles + 255) / 256) * kTile[i].share);
             const float loaded = tiles > 128 && tiles <= 256 ? std::max(step, 0.9f * kTile[i].share) : step;
             if (i == 0 || slabs * loaded < best_t) { best = i; best_t = slabs * loaded; }
         }
-        if (large) best = p.N > 64 ? 8 : p.N > 32 ? 5 : 9;
+        if (large) best = p.N > 64 ? 5 : p.N > 32 ? 3 : 6;
         switch (best) {
         case 0: return launch_t<T, EPI, 32, 32, 1, 1, 8>(p, n_active, s, stat_rows);
         case 1: return launch_t<T, EPI, 64, 64, 2, 2, 4>(p, n_active, s, stat_rows);
         case 2: return launch_t<T, EPI, 64, 64, 2, 2, 2>(p, n_active, s, stat_rows);
-        case 3: return launch_t<T, EPI, 64, 64, 2, 2, 1>(p, n_active, s, stat_rows);
-        case 4: return launch_t<T, EPI, 128, 64, 4, 2, 1, 2>(p, n_active, s, stat_rows);
-        case 5: return launch_t<T, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
-        case 6: return launch_t<T, EPI, 128, 128, 2, 4, 1, 2>(p, n_active, s, stat_rows);
-        case 7: return launch_t<T, EPI, 128, 128, 2, 2, 1>(p, n_active, s, stat_rows);
-        case 8: return launch_t<T, EPI, 256, 128, 4, 2, 1, 2>(p, n_active, s, stat_rows);
+        case 3: return launch_t<T, EPI, 128, 64, 4, 1, 1>(p, n_active, s, stat_rows);
+        case 4: return launch_t<T, EPI, 128, 128, 2, 4, 1, 2>(p, n_active, s, stat_rows);
+        case 5: return launch_t<T, EPI, 256, 128, 4, 2, 1, 2>(p, n_active, s, stat_rows);
         default: return launch_t<T, EPI, 128, 32, 4, 1, 1>(p, n_active, s, stat_rows);
         }
     } else {
