@@ -12,13 +12,14 @@ constexpr int kAggThreads = 256;
 constexpr int kAggUnrollPlain = 2;  // float4 chunks per thread: 2*NP loads of 16 bytes in flight
 constexpr int kAggUnrollBcast = 4;  // (the broadcast rows are written with plain stores: 4 % faster than non-temporal ones there)
 
-// NP > 0: that many rows, all their loads in flight at once.  NP = 0: any number of rows, eight at a time with all their loads
-// in flight (a row after the other was a chain of load latencies: 12 of 24 rows of 1 M, every row written, 45 us; now 22 us
-// = 6.7 TB/s).  The sum runs in the order of the list either way.
-template <int NP, bool BCAST> constexpr int kAggUnrollFor = BCAST && NP > 0 ? kAggUnrollBcast : kAggUnrollPlain;
+// NP > 0: that many rows, all their loads in flight at once.  NP = 0: any number of rows, AHEAD at a time with all their loads
+// in flight: eight (a row after the other was a chain of load latencies: 12 of 24 rows of 1 M, every row written, 45 us; now
+// 22 us = 6.7 TB/s), or in LARGE launches two, four where the result is written to all rows (see agg_large).  The sum runs in
+// the order of the list either way.
+template <int NP, bool BCAST, bool LARGE> constexpr int kAggUnrollFor = BCAST && (NP > 0 || LARGE) ? kAggUnrollBcast : kAggUnrollPlain;
 
 // BCAST: the result is also written to n_bcast replica rows (a kernel name of its own in traces)
-template <int NP, bool BCAST, int kAggUnroll = kAggUnrollFor<NP, BCAST>>
+template <int NP, bool BCAST, bool LARGE, int kAggUnroll = kAggUnrollFor<NP, BCAST, LARGE>>
 __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(
     const float* rows, int64_t row_stride, int64_t n4, const int32_t* __restrict__ sel,
     const float* __restrict__ wgt, int n_select, float* __restrict__ agg, int n_bcast, float* rows_out,
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(
             }
         }
     } else {
-        constexpr int CH = 8;
+        constexpr int CH = !LARGE ? 8 : BCAST ? 4 : 2;
         f4 acc[kAggUnroll];
         for (int i0 = 0; i0 < n_select; i0 += CH) {
             f4 v[kAggUnroll][CH];
@@ -85,12 +86,14 @@ __global__ __launch_bounds__(kAggThreads) void aggregate_kernel(
             if (j < n4) __builtin_nontemporal_store(acc[u], reinterpret_cast<f4*>(agg) + j);
         }
         if (BCAST)
-            for (int r = 0; r < n_bcast; ++r) {
-                f4* const dst = reinterpret_cast<f4*>(rows_out + (int64_t)(bcast_list ? bcast_list[r] : r) * row_stride);
 #pragma unroll
-                for (int u = 0; u < kAggUnroll; ++u) {
-                    const int64_t j = base + (int64_t)u * kAggThreads;
-                    if (j < n4) dst[j] = acc[u];
+            for (int u = 0; u < kAggUnroll; ++u) {
+                const int64_t j = base + (int64_t)u * kAggThreads;
+                if (j >= n4) continue;
+                for (int r = 0; r < n_bcast; ++r) {
+                    f4* const dst = reinterpret_cast<f4*>(rows_out + (int64_t)(bcast_list ? bcast_list[r] : r) * row_stride) + j;
+                    if (LARGE) __builtin_nontemporal_store(acc[u], dst);
+                    else *dst = acc[u];
                 }
             }
     }
@@ -123,29 +126,38 @@ int grid_for(int64_t count, int per_block, int cap)
 
 }  // namespace
 
+// Where many workgroups hide the latency, the memory does better the fewer rows a wavefront reads at once: 24 / 64 of 64 rows,
+// eight and two rows ahead, us: 2 M values 31 34 / 81 87, 4 M 63 59 / 169 155, 11 M 184 171 / 465 433.  Written to every row
+// the line is where the rows leave the last-level cache, and non-temporal stores are the better ones from there on (eight and
+// four rows ahead): 64 rows, 24 / 64 selected, 384 MB 86 99 / 138 145, 768 MB 207 195 / 305 275, 2.9 GB 791 786 / 1148 1088.
+static bool agg_large(int64_t n4, int n_bcast)
+{
+    return n_bcast > 0 ? n4 * 16 * n_bcast >= 450000000 : n4 >= 600000;
+}
+
 hipError_t launch_aggregate(const float* rows, int64_t row_stride, int64_t len, const int32_t* sel_sorted,
                             const float* sel_weight, int n_select, float* agg, int n_bcast, float* rows_out,
                             const int32_t* bcast_list, hipStream_t s)
 {
     const int64_t n4 = len / 4;
     const dim3 block(kAggThreads);
-#define HADFL_AGG(NP) do { \
-        const int64_t per_block = (int64_t)kAggThreads * (n_bcast > 0 ? kAggUnrollFor<NP, true> : kAggUnrollFor<NP, false>); \
+#define HADFL_AGG(NP, LARGE) do { \
+        const int64_t per_block = (int64_t)kAggThreads * (n_bcast > 0 ? kAggUnrollFor<NP, true, LARGE> : kAggUnrollFor<NP, false, LARGE>); \
         const dim3 grid((unsigned)((n4 + per_block - 1) / per_block)); \
-        if (n_bcast > 0) hipLaunchKernelGGL((aggregate_kernel<NP, true>), grid, block, 0, s, rows, row_stride, n4, sel_sorted, \
+        if (n_bcast > 0) hipLaunchKernelGGL((aggregate_kernel<NP, true, LARGE>), grid, block, 0, s, rows, row_stride, n4, sel_sorted, \
                                             sel_weight, n_select, agg, n_bcast, rows_out, bcast_list); \
-        else hipLaunchKernelGGL((aggregate_kernel<NP, false>), grid, block, 0, s, rows, row_stride, n4, sel_sorted, \
+        else hipLaunchKernelGGL((aggregate_kernel<NP, false, LARGE>), grid, block, 0, s, rows, row_stride, n4, sel_sorted, \
                                 sel_weight, n_select, agg, n_bcast, rows_out, bcast_list); } while (0)
     switch (n_select) {
-    case 1: HADFL_AGG(1); break;
-    case 2: HADFL_AGG(2); break;
-    case 3: HADFL_AGG(3); break;
-    case 4: HADFL_AGG(4); break;
-    case 5: HADFL_AGG(5); break;
-    case 6: HADFL_AGG(6); break;
-    case 7: HADFL_AGG(7); break;
-    case 8: HADFL_AGG(8); break;
-    default: HADFL_AGG(0); break;
+    case 1: HADFL_AGG(1, false); break;
+    case 2: HADFL_AGG(2, false); break;
+    case 3: HADFL_AGG(3, false); break;
+    case 4: HADFL_AGG(4, false); break;
+    case 5: HADFL_AGG(5, false); break;
+    case 6: HADFL_AGG(6, false); break;
+    case 7: HADFL_AGG(7, false); break;
+    case 8: HADFL_AGG(8, false); break;
+    default: if (agg_large(n4, n_bcast)) HADFL_AGG(0, true); else HADFL_AGG(0, false); break;
     }
 #undef HADFL_AGG
     return hipGetLastError();

@@ -189,3 +189,9 @@ def test_aggregation_stress_workload_full_size():
 def test_aggregate_in_chunks_of_rows(N, n_select, m):
     """More rows than the kernels with a fixed count take: one and more chunks of eight, full and ragged."""
     test_aggregate_matches_fp64_sum_and_resync_copies_it(N, n_select, m)
+
+
+@pytest.mark.parametrize("N,n_select,m", [(10, 9, 2400003), (12, 11, 2400001 - 4), (17, 16, 2399999), (20, 17, 6000001), (40, 13, 2900005)])
+def test_aggregate_of_many_rows_in_large_launches(N, n_select, m):
+    """Two (written to every row: four) rows ahead: both sides of the size where it begins, full and ragged groups of rows."""
+    test_aggregate_matches_fp64_sum_and_resync_copies_it(N, n_select, m)
