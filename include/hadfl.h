@@ -264,12 +264,13 @@ HADFL_API hadfl_status hadfl_set_params(hadfl_ctx *ctx, int32_t replica, const f
 HADFL_API hadfl_status hadfl_get_momentum(hadfl_ctx *ctx, int32_t replica, float *out, size_t n);
 HADFL_API hadfl_status hadfl_set_momentum(hadfl_ctx *ctx, int32_t replica, const float *in, size_t n);
 
-/* Execution options of one context (they change how the work is issued, never a bit of the result):
+/* Execution options of one context (they change how the work is issued):
  *   HADFL_OPT_SIDE_STREAM  1 (default): weight-gradient kernels of hadfl_local_steps run on a second stream owned by
- *                          the context; 0: every launch goes to the context's stream
- *   HADFL_OPT_TILE_HINT    0 (default): tile shapes chosen per launch; 1: the bf16 / fp32 lean convolution kernels take
- *                          their 256-row tiles wherever the layer shape allows, whatever the launch size; 2: layers on
- *                          16- and 32-pixel-wide images stay on the general kernels
+ *                          the context; 0: every launch goes to the context's stream.  Changes no bit of the result.
+ *   HADFL_OPT_TILE_HINT    0 (default): tile shapes chosen per launch; 1: the convolution kernels take their largest
+ *                          tiles wherever the layer shape allows, whatever the launch size; 2: layers on 16- and
+ *                          32-pixel-wide images stay out of the kernels for such images.  Other tiles add some of the
+ *                          sums in another order: results agree to rounding.
  * Takes effect from the next hadfl_local_steps.  EINVAL for an unknown option or value; ESTATE without a
  * trainable network. */
 typedef enum { HADFL_OPT_SIDE_STREAM = 0, HADFL_OPT_TILE_HINT = 1 } hadfl_option;

@@ -79,7 +79,8 @@ def test_general_layers_against_oracle(name, bf16, replicas, hint):
 
 
 def test_values_bf16_cannot_hold():
-    """A dense classifier on the data set, compared with 64-bit arithmetic where fp32 stays finite but the bf16 parts do not:
+    """A dense classifier on the data set (forward in the kernel for few rows, weight gradient in the general one, whose second
+    pass this reaches; the convolution kernels' is in test_gpu_split_floats.py), compared with 64-bit arithmetic where fp32 stays finite but the bf16 parts do not:
     a weight of -Inf (logit -Inf, probability 0), a weight and an input above bf16's largest number, the input against
     zero weights.  Error bound: 64 products and 24 samples in fp32, 88 * 2^-24 < 1e-5 relative."""
     d, classes, batch, lr = 64, 20, 24, 0.5
