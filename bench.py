@@ -26,23 +26,23 @@ PAPER_CONTEXT = {"speedup_vs_decentralized_fedavg": 3.15, "speedup_vs_pytorch_di
 # concatenation at measurement, bytes)
 TRAFFIC = {
     ("aggregate", "agg-stress-n64"): (("paper_2111_08274_amd/csrc/aggregate.hip",),
-                                      "07f6ea535d5a85ec9476282da427d1f3b14491645d0eec86612cbb44a6f0b83a",
-                                      402301504.5),
+                                      "c22583d4d32953228aa0edf6c53022af645f8207beb80c048d09e7e895666a1e",
+                                      402301497.1),
     # all launches of the class in a cycle, averaged
     ("conv_dgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                       "09aefceed6f017f36acf65332c22d67f87201a7f499bbcc88cff54c7a401ad3f",
-                                       469177032.3),
+                                       "17ba1571a6b51147e327fec758db206c9053a2efbac8b7f5ed651a091938878b",
+                                       468804174.7),
     ("conv_fwd", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                       "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
                                       "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                     "1a1db6b52885404607eedbc42bb24e5beef89a81e50e84847cd300a17ff7dfa5",
-                                     324582150.9),
+                                     "8738e514a33e0fa8739fd16f7626ddece2215104639cb7f3c5b49e76cfdc7c8a",
+                                     324661700.5),
     # (the figure includes the fused update's parameter and momentum traffic)
     ("conv_wgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_first_bf16.hip"),
-                                       "f7057e988412d565fb10012bbb937add6c14a60b146fa79f6a192dbfad93632b",
-                                       533122275.3),
+                                       "e446bcac0caa8b31e26b6f150f9bc45601d4f30a043bb6b1e05efef49bae6036",
+                                       529800645.5),
 }
 
 
