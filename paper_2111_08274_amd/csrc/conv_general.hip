@@ -26,8 +26,9 @@
 //     pixels of one residue class are a dense problem over that class's taps, one class after another in the grid.
 //   * K is walked in slabs of 32 (float) or 64 (bf16) channels of one tap, the last one of a tap padded with zeros.  A
 //     slab of a row is 208 bytes of LDS (three planes of 32 bf16 and 16 bytes of padding) or 144 (64 bf16 and 16), so that
-//     sixteen consecutive rows start in distinct groups of four banks and the 16-byte operand reads run at full rate.
-//     The weights lie in memory in that very order, 192 or 128 contiguous bytes per slab; float activations are split
+//     sixteen consecutive rows start in distinct groups of four banks and the 16-byte operand reads run at full rate
+//     (the stores of float activations, four rows of 64 bytes at a time, meet two to a bank: bank conflicts are a fifth to
+//     a quarter of the fp32 kernels' LDS cycles).  The weights lie in memory in that very order, 192 or 128 contiguous bytes per slab; float activations are split
 //     on their way into LDS.
 //   * Position of float channel k inside a slab: pos = ((k / 4) % 4) * 8 + (k / 16) * 4 + k % 4, the same for both operands:
 //     a thread reads channels 4g..4g+3 and 16+4g..16+4g+3 (64 contiguous bytes over four lanes each) and stores one
