@@ -31,18 +31,18 @@ TRAFFIC = {
     # all launches of the class in a cycle, averaged
     ("conv_dgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                       "17ba1571a6b51147e327fec758db206c9053a2efbac8b7f5ed651a091938878b",
-                                       468804174.7),
+                                       "af87472c9757601a35f7caf7cdd4d1e67e12bb00c1f41ab6076cc11234124dc4",
+                                       468811747.8),
     ("conv_fwd", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                       "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
                                       "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                     "8738e514a33e0fa8739fd16f7626ddece2215104639cb7f3c5b49e76cfdc7c8a",
-                                     324661700.5),
+                                     "63accfde27adcaf3fd9755c46f3145b9c60738ac096618c65ad73580cbe33a5f",
+                                     324735679.0),
     # (the figure includes the fused update's parameter and momentum traffic)
     ("conv_wgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_first_bf16.hip"),
-                                       "e446bcac0caa8b31e26b6f150f9bc45601d4f30a043bb6b1e05efef49bae6036",
-                                       529800645.5),
+                                       "df356755a15fbe000e3f523f2100289fa7b770b10a3deb64740409819a790c45",
+                                       529837990.4),
 }
 
 

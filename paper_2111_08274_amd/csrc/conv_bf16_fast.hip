@@ -1001,6 +1001,8 @@ WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active)
     int best = 1;
     float best_t = 0.f;
     for (p.splits = 1; p.splits <= std::min(256, std::max(1, p.K / 128)); ++p.splits) {
+        const float sums = p.splits > 1 ? moved * (float)(p.splits + 1) / 5.7f + 4.5f : moved / 3.5f;
+        if (p.splits > 1 && sums >= best_t) break;           // (and any further split more)
         const WgradTile kind = wgrad_tile(p, n_active);
         const auto& t = kTile[(int)kind];
         const long long rows = kind == WgradTile::taps ? p.C : p.M;          // (that kernel's workgroup holds all taps)
@@ -1008,8 +1010,7 @@ WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active)
         const long long round = kComputeUnits * t.resident, rest = wgs % round;
         const float rounds = (float)(wgs / round) * t.step[t.resident - 1] + (rest ? t.step[(rest - 1) / kComputeUnits] : 0.f);
         const float loop = ((float)p.K / (32.0f * (float)p.splits) + t.extra) * rounds;
-        const float time = loop + (p.splits > 1 ? moved * (float)(p.splits + 1) / 5.7f + 4.5f : moved / 3.5f);
-        if (p.splits == 1 || time < best_t) { best = p.splits; best_t = time; }
+        if (p.splits == 1 || loop + sums < best_t) { best = p.splits; best_t = loop + sums; }
     }
     return {best, 0};
 }

@@ -1046,6 +1046,7 @@ WgradPlan wgrad_general_plan(int rows, int N, int K, int n_active, int gather)
     for (int v = 0; v < (gather || N <= 32 ? 1 : 2); ++v) {
         const float wgs = (float)((rows + tile[v].m - 1) / tile[v].m) * (float)((N + tile[v].n - 1) / tile[v].n) * (float)n_active;
         for (int s = 1; s <= std::min(256, std::max(1, K / 128)); ++s) {
+            if (s > 1 && moved * (float)(s + 1) >= best_t) break;        // (and any further split moves more)
             const float steps = ((float)K / (32.0f * (float)s) + 3.0f) * tile[v].f, w = wgs * (float)s;
             float t = w <= 256.f ? steps * 2.2f : w <= 512.f ? steps * 2.7f : w * steps * 1.3f / 256.f + 0.5f * steps * 2.2f;
             if (s > 1) t += moved * (float)(s + 1);

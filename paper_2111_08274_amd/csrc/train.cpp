@@ -229,6 +229,13 @@ FastWgradParams lean_wgrad_shape(const hadfl_config& cfg, const NetPlan& plan, c
 // tile, which has at least 128 rows in the lean kernels and 32 in the general ones
 int64_t stat_floats(int64_t rows, int c, bool lean) { const int64_t tile = lean ? 128 : 32; return (rows + tile - 1) / tile * 2 * c; }
 
+bool same_shape(const NetPlan& plan, const Layer& l, const Layer& m)
+{
+    const auto same = [&](int t, int u) { const TensorShape a = plan.tensors[t], b = plan.tensors[u]; return a.h == b.h && a.w == b.w && a.c == b.c; };
+    return l.type == m.type && l.k == m.k && l.stride == m.stride && l.pad == m.pad && l.cout == m.cout && l.bias == m.bias &&
+           (l.in0 == 0) == (m.in0 == 0) && same(l.in0, m.in0) && same(l.out, m.out);
+}
+
 Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
 {
     Layout L;
@@ -261,7 +268,10 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
             int s = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, maxs), 256));
             if (lean_layer(cfg, plan, l) || general_wgrad(cfg, plan, l)) {      // chosen per launch
                 s = 1;
-                for (int n = 1; n <= cfg.n_replicas; ++n) {
+                size_t same = 0;                      // an earlier layer of the same shape has the same plans
+                while (same < i && !(!L.wgrad_plans[same].empty() && same_shape(plan, plan.layers[same], l))) ++same;
+                if (same < i) L.wgrad_plans[i] = L.wgrad_plans[same];
+                else for (int n = 1; n <= cfg.n_replicas; ++n) {
                     L.wgrad_plans[i].push_back(lean_layer(cfg, plan, l) ? wgrad_fast_plan(lean_wgrad_shape(cfg, plan, l), n) : general_wgrad_plan(cfg, plan, l, n));
                     const int sn = L.wgrad_plans[i].back().splits;
                     if (sn > 1) shared = std::max<int64_t>(shared, (int64_t)n * sn * up64(M * l.cout));
