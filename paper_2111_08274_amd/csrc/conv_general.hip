@@ -40,6 +40,7 @@
 #include "train_kernels.h"
 #include "conv_stats.h"
 #include "mfma_tiles.h"
+#include "slabs.h"
 
 namespace hadfl {
 namespace {
@@ -48,52 +49,9 @@ using namespace tiles;
 using conv_stats::store_column_stats;
 using conv_stats::kStatLdsBytes;
 
-// channels per slab, LDS bytes per row of a slab, bytes of the same row in memory (weights), groups of a row that a thread
-// stages at a time (32 bytes of float, 16 of bf16), planes
-template <typename T> struct Slab;
-template <> struct Slab<float> { static constexpr int channels = 32, row = 208, bytes = 192, groups = 4, planes = 3; };
-template <> struct Slab<__bf16> { static constexpr int channels = 64, row = 144, bytes = 128, groups = 8, planes = 1; };
-
-// four consecutive elements as floats
-__device__ __forceinline__ f4 load4(const float* p) { return *reinterpret_cast<const f4*>(p); }
-__device__ __forceinline__ f4 load4(const __bf16* p)
-{
-    const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
-    return f4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-}
-// stores v rounded to the element type and leaves the rounded values in v
-__device__ __forceinline__ void store4(float* p, f4& v) { *reinterpret_cast<f4*>(p) = v; }
-__device__ __forceinline__ void store4(__bf16* p, f4& v)
-{
-    const bf16x4 r = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-    *reinterpret_cast<bf16x4*>(p) = r;
-    v = f4{(float)r[0], (float)r[1], (float)r[2], (float)r[3]};
-}
 __device__ __forceinline__ u4 round8(const f4& a, const f4& b)
 {
     return u4{to_bf16x2(a[0], a[1]), to_bf16x2(a[2], a[3]), to_bf16x2(b[0], b[1]), to_bf16x2(b[2], b[3])};
-}
-
-// The parts of a weight in its copy, of 2^24 times the weight as in split3.  A weight too large for that, or not finite, has a
-// NaN for the first part, so that no tile that meets it keeps the products of parts, and its 32 bits in the other two.
-__device__ __forceinline__ void split_weight(float x, __bf16& h, __bf16& m, __bf16& l)
-{
-    if (fabsf(x) < 0x1p103f) {
-        const float y = x * kSplitScale;
-        h = (__bf16)y;
-        const float r = y - (float)h;
-        m = (__bf16)r;
-        l = (__bf16)(r - (float)m);
-    } else {
-        const unsigned bits = __builtin_bit_cast(unsigned, x);
-        h = __builtin_bit_cast(__bf16, (unsigned short)0x7fc0);
-        m = __builtin_bit_cast(__bf16, (unsigned short)(bits >> 16)); l = __builtin_bit_cast(__bf16, (unsigned short)bits);
-    }
-}
-__device__ __forceinline__ float join_weight(__bf16 h, __bf16 m, __bf16 l)
-{
-    if ((float)h == (float)h) return (((float)l + (float)m) + (float)h) * (1.0f / kSplitScale);
-    return __builtin_bit_cast(float, (unsigned)__builtin_bit_cast(unsigned short, m) << 16 | __builtin_bit_cast(unsigned short, l));
 }
 
 // What one residue class of pixels needs (one class, the whole image, unless it is a strided data gradient)
@@ -846,7 +804,9 @@ __global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_genera
 }
 
 // fp32 master W[tap][ci][co] -> Wf[co][tap][ci] and Wb[ci][T-1-tap][co] as described at the top.  A workgroup handles one
-// tap and a 64 x 64 (ci, co) tile; each thread forms 16-byte groups of eight positions.  Bound by memory: 4 bytes read and
+// tap and a 64 x 64 (ci, co) tile; each thread forms 16-byte groups of eight positions.  p.fragments: the order of the lanes of a
+// matrix instruction instead (conv_general_patch.hip), [32 rows][slab][tap][16 channels][plane][half of them][row], rows beyond the
+// last zero.  Bound by memory: 4 bytes read and
 // 12 (bf16: 4) written per weight.
 template <typename T>
 __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
@@ -874,10 +834,14 @@ __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
         char* const base = (char*)(dst + (long long)rep * p.wcopy_rep);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int i = threadIdx.x + q * 256, g = i % GR, sl = (i / GR) % (64 / kSlab), row = i >> 3;
+            const int i = threadIdx.x + q * 256;
+            const int row = p.fragments ? i & 63 : i >> 3, j = p.fragments ? i >> 6 : i & 7, g = j % GR, sl = j / GR;
             const int slab = k0 / kSlab + sl;
-            if (row0 + row >= rows || slab >= cs) continue;
-            char* const o = base + ((long long)(row0 + row) * p.taps * cs + t * cs + slab) * kSlabBytes + g * 16;
+            if (row0 + row >= (p.fragments ? (rows + 31) / 32 * 32 : rows) || slab >= cs) continue;
+            char* const o = p.fragments
+                ? base + (((long long)((row0 + row) / 32) * cs + slab) * p.taps + t) * (32 * kSlabBytes) + (g >> 1) * (kSplit ? 3072 : 1024) + (g & 1) * 512 + (row & 31) * 16
+                : base + ((long long)(row0 + row) * p.taps * cs + t * cs + slab) * kSlabBytes + g * 16;
+            const int plane = p.fragments ? 1024 : 64;
             bf16x8 h, m, l;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -888,7 +852,7 @@ __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
                 else h[e] = (__bf16)v;
             }
             *reinterpret_cast<bf16x8*>(o) = h;
-            if (kSplit) { *reinterpret_cast<bf16x8*>(o + 64) = m; *reinterpret_cast<bf16x8*>(o + 128) = l; }
+            if (kSplit) { *reinterpret_cast<bf16x8*>(o + plane) = m; *reinterpret_cast<bf16x8*>(o + 2 * plane) = l; }
         }
     }
 }
@@ -1006,6 +970,11 @@ long long weight_copy_units(int bf16, int rows, int taps, int channels)
 {
     const int per = bf16 ? Slab<__bf16>::channels : Slab<float>::channels, bytes = bf16 ? Slab<__bf16>::bytes : Slab<float>::bytes;
     return (long long)rows * taps * ((channels + per - 1) / per) * (bytes / 2);
+}
+
+long long weight_fragment_units(int bf16, int rows, int taps, int channels)
+{
+    return weight_copy_units(bf16, (rows + 31) / 32 * 32, taps, channels);
 }
 
 hipError_t launch_conv_general(const GeneralConvParams& p0, int epi, int n_active, hipStream_t s, int* stat_rows)

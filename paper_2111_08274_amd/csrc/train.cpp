@@ -208,6 +208,14 @@ bool general_wgrad(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
     return general_layer(cfg, plan, l) && !(gather_layer(cfg, l) && plan.tensors[0].c % 4 == 0 && l.k * l.k * plan.tensors[0].c > 32);
 }
 
+// General layers whose forward pass and data gradient run from patches (conv_general_patch.hip)
+bool patch_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
+{
+    if (l.type != HADFL_OP_CONV || l.in0 == 0 || l.stride != 1 || 2 * l.pad != l.k - 1 || !general_layer(cfg, plan, l)) return false;
+    const TensorShape a = plan.tensors[l.in0];
+    return conv_patch_supported(cfg.bf16, a.h, a.w, a.c, l.cout, l.k);
+}
+
 // Plan of a general layer's weight gradient with n active replicas
 WgradPlan general_wgrad_plan(const hadfl_config& cfg, const NetPlan& plan, const Layer& l, int n)
 {
@@ -303,8 +311,9 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
                     L.wf_off[i] = woff; woff += up64(weight_copy_units(0, l.cout, 1, taps * cin));
                     continue;
                 }
-                L.wf_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, l.cout, taps, cin));
-                L.wb_off[i] = woff; woff += up64(weight_copy_units(cfg.bf16, cin, taps, l.cout));
+                const auto units = patch_layer(cfg, plan, l) ? weight_fragment_units : weight_copy_units;
+                L.wf_off[i] = woff; woff += up64(units(cfg.bf16, l.cout, taps, cin));
+                L.wb_off[i] = woff; woff += up64(units(cfg.bf16, cin, taps, l.cout));
             }
         }
         L.wbf_rep = woff;
@@ -575,6 +584,7 @@ struct Runner {
             w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
             w.C = layer_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.bf16 = e.cfg.bf16; w.order = e.buf.order;
             if (gather_layer(e.cfg, l)) { w.C *= w.taps; w.taps = 1; }
+            w.fragments = patch_layer(e.cfg, e.plan, l);
             run("weight_prep", 0, (e.cfg.bf16 ? 8.0 : 16.0) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
         } else {
             WeightPrepParams w{};
@@ -743,7 +753,7 @@ struct Runner {
                     f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
-                run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_general(f, 0, na, s, srows); });
+                run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return patch_layer(e.cfg, e.plan, l) ? launch_conv_general_patch(f, 0, na, s, srows) : launch_conv_general(f, 0, na, s, srows); });
                 break;
             }
             if (small_dense_layer(l) && !p.relu) {
@@ -961,7 +971,7 @@ struct Runner {
                     f.wmat = wbf() + e.wb_off[i];
                     f.out = grad(l.in0);
                     f.mask = mask0; f.mask_rep = e.rep_block; f.accumulate = acc0;
-                    run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return launch_conv_general(f, 1, na, s); });
+                    run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return patch_layer(e.cfg, e.plan, l) ? launch_conv_general_patch(f, 1, na, s) : launch_conv_general(f, 1, na, s); });
                 } else
                 run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return gemm(d); });
             }

@@ -138,10 +138,16 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     float* stat; long long stat_rep;           // forward, optional: statistics entries as in FastConvParams
     int tile_hint;                             // 1: the largest tiles whatever the launch size
     int tiles_m, n_active;                     // set by the launcher
+    int halo; unsigned inv_hw, inv_w;          // the same (conv_general_patch.hip): pixels of border before and behind a tile, 2^32 / HW, 2^32 / W
+    const float* stat_y; long long stat_y_rep; int stat_relu;      // bf16 data gradient with stat set (conv_general_patch.hip): as in FastConvParams
 };
 // epi 0: forward (+bias, ReLU); epi 1: data gradient (mask, accumulate).  Needs C % 4 == 0 (bf16: 8), N % 4 == 0, R * S <= 32,
 // tensors of less than 4 GiB per replica.  stat_rows (may be null): rows per statistics entry of the kernel that was launched.
 hipError_t launch_conv_general(const GeneralConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows = nullptr);
+// The same for stride-1 "same" convolutions (conv_general_patch.hip) that conv_patch_supported accepts: k x k filters, C channels of the
+// source and N of the result in either direction.  The copy is in fragments.
+bool conv_patch_supported(int bf16, int H, int W, int C, int N, int k);
+hipError_t launch_conv_general_patch(const GeneralConvParams& p, int epi, int n_active, hipStream_t s, int* stat_rows = nullptr);
 struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias) the bias gradient as row R*S*C
     int bf16;                                  // element type of x and dy
     int B, H, W, C, Ho, Wo, N, R, S, pad, stride;
@@ -161,10 +167,12 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
 hipError_t launch_wgrad_general(const GeneralWgradParams& p, int n_active, hipStream_t s);
 WgradPlan wgrad_general_plan(int rows, int N, int K, int n_active, int gather);   // for rows = R*S*C weights
 long long weight_copy_units(int bf16, int rows, int taps, int channels);   // 2-byte units of a copy [rows][taps][channels]
+long long weight_fragment_units(int bf16, int rows, int taps, int channels);   // the same in fragments
 struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]
     const float* w; long long w_rep;
     __bf16* wf; __bf16* wb; long long wcopy_rep;
     int C, N, taps, bf16;
+    int fragments;                             // in the order of conv_general_patch.hip
     const int* order;
 };
 hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s);

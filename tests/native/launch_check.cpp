@@ -105,11 +105,15 @@ void conv_general(Launch l, const GeneralConvParams& p, const std::vector<int>& 
     else l.act(p.a, p.a_rep, (long long)p.B * p.H * p.W * p.C);
     l.act(p.out, p.out_rep, out * p.N);
     l.act(p.mask, p.mask_rep, out * p.N);
-    const long long units = weight_copy_units(p.bf16, p.N, p.cursor ? 1 : p.R * p.S, p.cursor ? p.R * p.S * p.C : p.C);
+    const bool patch = has(l.name, "patch");
+    const long long units = patch ? weight_fragment_units(p.bf16, p.N, p.R * p.S, p.C)
+                                  : weight_copy_units(p.bf16, p.N, p.cursor ? 1 : p.R * p.S, p.cursor ? p.R * p.S * p.C : p.C);
+    const int rows = patch ? 32 * t[0] * t[1] : t[0];
+    l.act(p.stat_y, p.stat_y_rep, p.stat ? out * p.N : 0);
     for (int g = 0; g < l.n; ++g) use(l.name, kCopy, p.wmat + l.order[g] * p.wmat_rep, units * 2);
     l.tensor(kParam, p.bias, p.bias_rep, p.N * 4);
     if (p.perm) { use(l.name, kTable, p.perm, p.H * p.W * 4); use(l.name, kTable, p.posmask, p.H * p.W * 4); }
-    if (p.stat) l.sums(p.stat, p.stat_rep, (int)((out + t[0] - 1) / t[0]), p.N, p.out);
+    if (p.stat) l.sums(p.stat, p.stat_rep, (int)((out + rows - 1) / rows), p.N, p.out);
 }
 
 void conv_fast(Launch l, const FastConvParams& p, int rows)
@@ -164,7 +168,7 @@ void look(const std::string& name, dim3 grid, void** args)
 {
     Launch l{name, nullptr, 0, 4};
     const std::vector<int> t = ints_of(name);
-    if (has(name, "conv_general_kernel")) conv_general(l, *(GeneralConvParams*)args[0], t);
+    if (has(name, "conv_general_kernel") || has(name, "conv_general_patch_kernel")) conv_general(l, *(GeneralConvParams*)args[0], t);
     else if (has(name, "conv_patch_kernel")) conv_fast(l, *(FastConvParams*)args[0], t.back());
     else if (has(name, "11conv_kernel")) conv_fast(l, *(FastConvParams*)args[0], t[0]);
     else if (has(name, "wgrad_general_kernel")) {
@@ -191,8 +195,9 @@ void look(const std::string& name, dim3 grid, void** args)
         const WeightCopyParams& c = *(WeightCopyParams*)args[0];
         const WeightPrepParams& q = *(WeightPrepParams*)args[0];
         l.order = general ? c.order : q.order; l.n = (int)grid.z;
-        const long long nf = general ? weight_copy_units(c.bf16, c.N, c.taps, c.C) : (long long)q.C * q.N * q.taps;
-        const long long nb = general ? weight_copy_units(c.bf16, c.C, c.taps, c.N) : nf;
+        const auto units = general && c.fragments ? weight_fragment_units : weight_copy_units;
+        const long long nf = general ? units(c.bf16, c.N, c.taps, c.C) : (long long)q.C * q.N * q.taps;
+        const long long nb = general ? units(c.bf16, c.C, c.taps, c.N) : nf;
         for (int g = 0; g < l.n; ++g) {
             const long long at = l.order[g] * (general ? c.wcopy_rep : q.wbf_rep);
             use(name, kCopy, (general ? c.wf : q.wf) + at, nf * 2);
@@ -303,3 +308,4 @@ long long hadfl::weight_copy_units(int bf16, int rows, int taps, int channels)
     const int per = bf16 ? 64 : 32, bytes = bf16 ? 128 : 192;
     return (long long)rows * taps * ((channels + per - 1) / per) * (bytes / 2);
 }
+long long hadfl::weight_fragment_units(int bf16, int rows, int taps, int channels) { return weight_copy_units(bf16, (rows + 31) / 32 * 32, taps, channels); }

@@ -1,0 +1,104 @@
+"""Stride-1 "same" convolutions from patches (conv_general_patch.hip): every tile of the launcher, tiles of whole images and tiles with
+a border, sorted positions, ragged channels, images and batches, and operands whose bf16 parts are not finite, in both directions."""
+import numpy as np
+import pytest
+
+from oracle import nets
+from paper_2111_08274_amd import hadfl
+from tests import parity_metrics as pm, torch_ref
+from tests.pair import Pair
+
+pytestmark = pytest.mark.gpu
+CLASSES = 5
+
+# (image, channels in and out, k, batch, replicas, tile hint)
+SHAPES = [((8, 6), 36, 132, 3, 7, 1, 0), ((8, 6), 132, 36, 3, 33, 2, 1), ((5, 7), 40, 80, 3, 50, 3, 0), ((5, 7), 40, 64, 5, 9, 2, 1),
+          ((2, 2), 128, 64, 3, 32, 3, 0), ((2, 2), 64, 256, 3, 96, 2, 1), ((2, 2), 96, 64, 3, 1024, 16, 0), ((4, 4), 64, 256, 3, 32, 2, 1), ((4, 4), 160, 192, 3, 32, 2, 0),
+          ((9, 63), 40, 48, 3, 2, 1, 0), ((63, 5), 48, 40, 3, 3, 2, 1), ((12, 31), 40, 48, 5, 2, 1, 1), ((16, 16), 72, 132, 3, 8, 1, 1), ((16, 16), 64, 64, 3, 32, 8, 0),
+          ((10, 10), 80, 160, 3, 40, 4, 0), ((10, 10), 256, 256, 3, 16, 4, 0),
+          ((4, 4), 512, 512, 3, 64, 1, 0), ((2, 2), 512, 512, 3, 64, 1, 0), ((8, 8), 256, 256, 3, 64, 1, 0)]
+
+
+def net(c, n, k):
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, c, bias=False)))
+    t = b.relu(b.bn(b.conv(t, n, k=k, pad=k // 2, bias=False)))
+    t = b.relu(b.conv(t, n, k=k, pad=k // 2))
+    b.dense(b.gap(t), CLASSES)
+    return b
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_patch_layers(shape):
+    """Gradients of one step, read from the momentum buffers, against the same network in 64 bits.  Bound: the error of a sum of
+    K products in fp32, 2^-24 sqrt(K), K <= 4608 products and up to 16384 pixels, and as much again through each of two batch
+    norms and a softmax: 3e-5 of a tensor's largest gradient (floored at 1e-3 of the largest of all).  Where a ReLU's input lies within that of zero its unit may open on one side and not on the other: up to a
+    hundredth of a tensor's values (one filter and one column) may be off by 5e-3 for it."""
+    (h, w), c, n, k, batch, replicas, hint = shape
+    rng = np.random.default_rng(c + n + batch)
+    x = rng.standard_normal((1, batch, h, w, 3)).astype(np.float32)
+    y = rng.integers(0, CLASSES, (1, batch)).astype(np.int32)
+    cfg = hadfl.make_config(replicas, 1, net="custom", custom_ops=net(c, n, k).array()[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=batch, n_samples=batch,
+                            in_shape=(h, w, 3), n_classes=CLASSES, lr=1e-30, momentum=0.5)
+    layout = hadfl.param_layout(cfg)
+    w0 = np.zeros(max(o + m for o, m, _, _ in layout), dtype=np.float32)
+    for off, cnt, kind, fan_in in layout:
+        w0[off:off + cnt] = {"weight": rng.standard_normal(cnt) * np.sqrt(2.0 / max(fan_in, 1)), "bias": 0.1 * rng.standard_normal(cnt), "gamma": 1.0, "running_var": 1.0}.get(kind, 0.0)
+    ctx = hadfl.Context(cfg, [1] * replicas, w0=w0, x=np.repeat(x, replicas, 0), y=np.repeat(y, replicas, 0), options={hadfl.OPT_TILE_HINT: hint})
+    ctx.local_steps()
+    got = [ctx.momentum(r).astype(np.float64) for r in sorted({0, replicas - 1})]
+    ctx.close()
+    want = torch_ref.loss_grad(net(c, n, k).array(), (h, w, 3), w0.astype(np.float64), x[0].astype(np.float64).reshape(batch, -1), y[0])[1]
+    floor = 1e-3 * max(np.abs(want[o:o + m]).max() for o, m, kind, _ in layout if o + m <= got[0].size)
+    for g in got:
+        for off, cnt, kind, _ in layout:
+            if off + cnt > g.size:
+                continue
+            err = np.abs(g[off:off + cnt] - want[off:off + cnt]) / max(np.abs(want[off:off + cnt]).max(), floor)
+            print(shape, kind, cnt, "max %.1e median %.1e" % (err.max(), np.median(err)), flush=True)
+            assert err.max() <= 5e-3 and (err > 3e-5).mean() <= 0.01, (shape, kind, float(err.max()), float((err > 3e-5).mean()))
+
+
+@pytest.mark.parametrize("what", ["activation", "gradient"])
+@pytest.mark.parametrize("side,k,batch,hint", [(8, 3, 32, 0), (8, 3, 32, 1), (2, 3, 256, 0), (7, 3, 16, 0), (16, 5, 16, 1), (32, 3, 64, 0)])
+def test_patch_layers_above_bf16(side, k, batch, hint, what):
+    """2^106 in an activation or a gradient, against zero weights: as parts they are Inf * 0.  Error as in
+    tests/test_gpu_split_floats.py, whose layers are narrower: 3e-5 of a tensor's largest value, the huge ones apart."""
+    c, n, huge, classes = 40, 72, 2.0 ** 106, 20
+    k2 = int(np.log2(batch * side * side))
+    b = nets._Builder()
+    t = b.conv(b.relu(b.bn(b.conv(0, c, bias=False))), n, k=k, pad=k // 2, bias=False)
+    for _ in range(k2):
+        t = b.add(t, t)
+    b.dense(b.gap(t), classes)
+    rng = np.random.default_rng(k + side)
+    x = rng.standard_normal((batch, side, side, 3)).astype(np.float32)
+    y = rng.integers(4, classes, batch)
+    w0, gamma, beta = 0.3 * rng.standard_normal((3, 3, 3, c)), np.ones(c), 0.1 * rng.standard_normal(c)
+    w1 = 2.0 ** -k2 * 0.2 * rng.standard_normal((k, k, c, n))
+    w2, b2 = 0.3 * rng.standard_normal((n, classes)), np.zeros(classes)
+    if what == "activation":
+        gamma[5], beta[5] = 0.0, huge
+        w1[:, :, 5] = 0.0
+    else:
+        w1[..., 7] = 0.0
+        w2[7] = 0.0
+        w2[7, 3], b2[3], y[2] = huge, -1e4, 3
+    w = np.concatenate([v.ravel() for v in (w0, gamma, beta, w1, w2, b2, np.zeros(c), np.ones(c))]).astype(np.float32)
+    cfg = hadfl.make_config(1, 1, net="custom", custom_ops=b.array()[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=batch, n_samples=batch,
+                            in_shape=(side, side, 3), n_classes=classes, lr=1e-30, momentum=0.5)
+    ctx = hadfl.Context(cfg, [1], w0=w, x=x[None], y=y[None].astype(np.int32), options={hadfl.OPT_TILE_HINT: hint})
+    ctx.local_steps()
+    got = ctx.momentum(0).astype(np.float64)
+    ctx.close()
+    want = torch_ref.loss_grad(b.array(), (side, side, 3), w.astype(np.float64), x.astype(np.float64).reshape(batch, -1), y)[1]
+    at = 0
+    for shape in ((3, 3, 3, c), (c,), (c,), (k, k, c, n), (n, classes), (classes,)):
+        m = int(np.prod(shape))
+        g, r = got[at:at + m], want[at:at + m]
+        at += m
+        assert np.isfinite(g).all()
+        big = np.abs(r) > 1e20
+        for sel in (big, ~big):
+            if sel.any():
+                assert np.abs(g - r)[sel].max() <= 3e-5 * max(np.abs(r)[sel].max(), 1e-3), (shape, float(np.abs(g - r)[sel].max() / np.abs(r)[sel].max()))

@@ -229,3 +229,24 @@ def test_split_float_layers_reach_every_tile(checked):
              "256ELi128ELi4ELi2ELi1ELi2", "128ELi32ELi4ELi1ELi1ELi1")
     missing = {"%sELi%dELb0" % (t, epi) for t in tiles for epi in (0, 1)} - seen
     assert not missing, missing
+
+
+def test_patch_layers_reach_every_tile(checked):
+    """The layers of tests/test_gpu_patch_layers.py between them take every tile of that launcher, in both directions, and the
+    route is theirs alone: a narrow, strided, 1 x 1 or very wide layer stays out of it."""
+    from tests.test_gpu_patch_layers import SHAPES, net
+    cases = [case(net(c, n, k), (h, w, 3), batch, [1] * replicas, 0, classes=5, options=[(1, hint)]) for (h, w), c, n, k, batch, replicas, hint in SHAPES]
+    runs = checked(cases)
+    assert all(r["status"] == 0 and r["report"] == "" and layers_in(r["trace"], "general_patch") == 4 for r in runs)
+    seen = {name.split("patch_kernelIfLi")[1].split("EEEv")[0] for r in runs for name in r["trace"] if "general_patch" in name}
+    tiles = ("4ELi1ELi4ELi1ELi4ELi1ELi%dELb0", "4ELi1ELi4ELi1ELi2ELi1ELi%dELb1", "4ELi2ELi2ELi1ELi6ELi1ELi%dELb0", "2ELi2ELi2ELi1ELi4ELi1ELi%dELb0",
+             "2ELi2ELi2ELi1ELi2ELi2ELi%dELb1", "2ELi1ELi2ELi2ELi5ELi2ELi%dELb0", "2ELi1ELi2ELi4ELi5ELi2ELi%dELb0", "2ELi1ELi1ELi8ELi6ELi2ELi%dELb0",
+             "2ELi1ELi1ELi8ELi4ELi2ELi%dELb1", "1ELi1ELi2ELi4ELi3ELi2ELi%dELb0")
+    missing = {t % epi for t in tiles for epi in (0, 1)} - seen
+    assert not missing, missing
+    out = []
+    for side, c, n, k, stride in ((8, 32, 64, 3, 1), (8, 64, 32, 3, 1), (8, 64, 64, 3, 2), (8, 64, 64, 1, 1), (64, 40, 40, 3, 1), (1, 64, 64, 3, 1)):
+        b = nets._Builder()
+        b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(0, c))), n, k=k, stride=stride, pad=k // 2))), 5)
+        out.append(case(b, (side, side, 3), 16, [1], 0, classes=5))
+    assert all(layers_in(r["trace"], "general_patch") == 0 for r in checked(out))
