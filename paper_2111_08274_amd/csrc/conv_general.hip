@@ -1022,6 +1022,7 @@ WgradPlan wgrad_general_plan(int rows, int N, int K, int n_active, int gather)
             if ((v == 0 && s == 1) || t < best_t) { best = {s, v}; best_t = t; }
         }
     }
+    best.time = best_t;
     return best;
 }
 

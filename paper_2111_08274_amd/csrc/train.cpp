@@ -221,7 +221,13 @@ WgradPlan general_wgrad_plan(const hadfl_config& cfg, const NetPlan& plan, const
 {
     const TensorShape a = plan.tensors[l.in0], r = plan.tensors[l.out];
     const bool conv = l.type == HADFL_OP_CONV;
-    return wgrad_general_plan((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
+    const WgradPlan pixels = wgrad_general_plan((int)(conv ? l.k * l.k * a.c : a.numel()), l.cout, (int)(cfg.batch * (conv ? r.h * r.w : 1)), n, gather_layer(cfg, l));
+    if (cfg.bf16 || !conv || l.in0 == 0 || l.k != 3 || l.stride != 1 || l.pad != 1 || !wgrad_positions_supported(cfg.batch, a.h, a.w, a.c, l.cout)) return pixels;
+    // The estimate for the kernel that walks pixels is low for launches of few workgroups (64 channels, 32 x 32 images, batch 64, one
+    // replica: 42 us, measured with the reduction 67, the other 46).  With this margin the choice is the faster one or within 1 us of
+    // it on layers of 64 to 512 channels and 1 to 16 replicas.
+    const WgradPlan positions = wgrad_positions_plan(cfg.batch, a.h, a.w, a.c, l.cout, n);
+    return positions.time <= 1.25f * pixels.time + 1.0f ? positions : pixels;
 }
 
 // What the plan of a lean layer's follows from
@@ -924,7 +930,7 @@ struct Runner {
                     f.sgd_w = e.buf.replicas + l.w_off; f.sgd_buf = e.buf.mom ? e.buf.mom + l.w_off : nullptr;
                     f.lr = e.cfg.lr; f.momentum = e.cfg.momentum;
                 }
-                run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return launch_wgrad_general(f, na, s); });
+                run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return wgrad.positions ? launch_wgrad_positions(f, na, s) : launch_wgrad_general(f, na, s); });
                 if (e.fused_update[i] && na_next > 0 && e.wf_off[i] >= 0) pending_prep = (int)i;
             } else
                 run(l.type == HADFL_OP_CONV ? "conv_wgrad" : "dense_wgrad", gemm_flops(p), gemm_bytes(p), [&] { return gemm(p); });

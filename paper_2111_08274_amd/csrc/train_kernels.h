@@ -91,7 +91,8 @@ struct FastWgradParams {     // dW[(tap, ci) | bias row][co] over pixels; needs 
     int n_active;                               // set by the launcher
 };
 hipError_t launch_wgrad_fast(const FastWgradParams& p, int n_active, hipStream_t s);
-struct WgradPlan { int splits, small_tiles; };               // split-K factor; general kernels: 64 x 64 tiles
+// split-K factor; general kernels: 64 x 64 tiles, wgrad_positions.hip; estimated cost with the reduction in us
+struct WgradPlan { int splits, small_tiles, positions = 0; float time = 0.f; };
 WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active);        // (from the fields above x)
 
 // ---- bf16 configuration, first convolution (fp32 data set in, few channels): conv_first_bf16.hip ----
@@ -166,6 +167,10 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
 // Needs C and N multiples of 4 (bf16: 8), tensors of less than 4 GiB per replica.
 hipError_t launch_wgrad_general(const GeneralWgradParams& p, int n_active, hipStream_t s);
 WgradPlan wgrad_general_plan(int rows, int N, int K, int n_active, int gather);   // for rows = R*S*C weights
+// The same for fp32 3 x 3 stride-1 "same" convolutions (wgrad_positions.hip); kchunk, small_tiles and the position table are not read.
+bool wgrad_positions_supported(int B, int H, int W, int C, int N);
+WgradPlan wgrad_positions_plan(int B, int H, int W, int C, int N, int n_active);
+hipError_t launch_wgrad_positions(const GeneralWgradParams& p, int n_active, hipStream_t s);
 long long weight_copy_units(int bf16, int rows, int taps, int channels);   // 2-byte units of a copy [rows][taps][channels]
 long long weight_fragment_units(int bf16, int rows, int taps, int channels);   // the same in fragments
 struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (unless null) Wb[C][taps-1-tap][N]

@@ -171,7 +171,7 @@ void look(const std::string& name, dim3 grid, void** args)
     if (has(name, "conv_general_kernel") || has(name, "conv_general_patch_kernel")) conv_general(l, *(GeneralConvParams*)args[0], t);
     else if (has(name, "conv_patch_kernel")) conv_fast(l, *(FastConvParams*)args[0], t.back());
     else if (has(name, "11conv_kernel")) conv_fast(l, *(FastConvParams*)args[0], t[0]);
-    else if (has(name, "wgrad_general_kernel")) {
+    else if (has(name, "wgrad_general_kernel") || has(name, "wgrad_general_position_kernel")) {
         const GeneralWgradParams& p = *(GeneralWgradParams*)args[0];
         l.order = p.order; l.n = p.n_active; l.es = p.bf16 ? 2 : 4;
         if (p.cursor) l.data(p.x, p.n_samples, p.B, p.sample_sz); else l.act(p.x, p.x_rep, (long long)p.B * p.H * p.W * p.C);

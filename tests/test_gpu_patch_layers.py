@@ -1,4 +1,4 @@
-"""Stride-1 "same" convolutions from patches (conv_general_patch.hip): every tile of the launcher, tiles of whole images and tiles with
+"""Stride-1 "same" convolutions from patches (conv_general_patch.hip) and their weight gradients by position (wgrad_positions.hip): every tile of the launcher, tiles of whole images and tiles with
 a border, sorted positions, ragged channels, images and batches, and operands whose bf16 parts are not finite, in both directions."""
 import numpy as np
 import pytest
@@ -16,7 +16,8 @@ SHAPES = [((8, 6), 36, 132, 3, 7, 1, 0), ((8, 6), 132, 36, 3, 33, 2, 1), ((5, 7)
           ((2, 2), 128, 64, 3, 32, 3, 0), ((2, 2), 64, 256, 3, 96, 2, 1), ((2, 2), 96, 64, 3, 1024, 16, 0), ((4, 4), 64, 256, 3, 32, 2, 1), ((4, 4), 160, 192, 3, 32, 2, 0),
           ((9, 63), 40, 48, 3, 2, 1, 0), ((63, 5), 48, 40, 3, 3, 2, 1), ((12, 31), 40, 48, 5, 2, 1, 1), ((16, 16), 72, 132, 3, 8, 1, 1), ((16, 16), 64, 64, 3, 32, 8, 0),
           ((10, 10), 80, 160, 3, 40, 4, 0), ((10, 10), 256, 256, 3, 16, 4, 0),
-          ((4, 4), 512, 512, 3, 64, 1, 0), ((2, 2), 512, 512, 3, 64, 1, 0), ((8, 8), 256, 256, 3, 64, 1, 0)]
+          ((4, 4), 512, 512, 3, 64, 1, 0), ((2, 2), 512, 512, 3, 64, 1, 0), ((8, 8), 256, 256, 3, 64, 1, 0),
+          ((7, 9), 64, 60, 3, 50, 40, 0), ((3, 2), 192, 128, 3, 37, 6, 0), ((17, 6), 116, 64, 3, 130, 3, 0), ((16, 16), 64, 64, 3, 72, 8, 0)]
 
 
 def net(c, n, k):
@@ -60,11 +61,12 @@ def test_patch_layers(shape):
 
 
 @pytest.mark.parametrize("what", ["activation", "gradient"])
-@pytest.mark.parametrize("side,k,batch,hint", [(8, 3, 32, 0), (8, 3, 32, 1), (2, 3, 256, 0), (7, 3, 16, 0), (16, 5, 16, 1), (32, 3, 64, 0)])
-def test_patch_layers_above_bf16(side, k, batch, hint, what):
+@pytest.mark.parametrize("c,n,side,k,batch,hint", [(40, 72, 8, 3, 32, 0), (40, 72, 8, 3, 32, 1), (40, 72, 2, 3, 256, 0), (40, 72, 7, 3, 16, 0),
+                                                   (40, 72, 16, 5, 16, 1), (40, 72, 32, 3, 64, 0), (64, 64, 16, 3, 50, 0), (64, 128, 9, 3, 130, 0)])
+def test_patch_layers_above_bf16(c, n, side, k, batch, hint, what):
     """2^106 in an activation or a gradient, against zero weights: as parts they are Inf * 0.  Error as in
     tests/test_gpu_split_floats.py, whose layers are narrower: 3e-5 of a tensor's largest value, the huge ones apart."""
-    c, n, huge, classes = 40, 72, 2.0 ** 106, 20
+    huge, classes = 2.0 ** 106, 20
     k2 = int(np.log2(batch * side * side))
     b = nets._Builder()
     t = b.conv(b.relu(b.bn(b.conv(0, c, bias=False))), n, k=k, pad=k // 2, bias=False)
