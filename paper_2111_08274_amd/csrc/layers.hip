@@ -211,6 +211,11 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(BnParams p)
     }
 }
 
+__device__ __forceinline__ float bn_left_out(const BnParams& p, int rep, int c)
+{
+    return p.left_out ? p.left_out[rep * p.left_out_rep + c] : 0.f;
+}
+
 // y = gamma * (x - mean) * istd + beta; the blocks of chunk 0 also store mean / istd and update the running statistics
 template <typename T>
 __global__ __launch_bounds__(256) void bn_apply_fwd_kernel(BnParams p)
@@ -235,7 +240,7 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_kernel(BnParams p)
         sv[c] = mean; sv[p.C + c] = istd;
         const float unb = p.rows > 1 ? q / (float)(p.rows - 1) : var;
         float* rm = row + p.stat_off;
-        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * mean;
+        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + bn_left_out(p, rep, c));
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     }
     const int r0 = chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
@@ -641,7 +646,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
         sv[c] = mean; sv[p.C + c] = 1.0f / sqrtf(var + kBnEps);
         const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
         float* rm = p.params + rep * p.row_stride + p.stat_off;
-        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * mean;
+        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + bn_left_out(p, rep, c));
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     } else {
         if (p.bwd_stats_done && !direct) q = (q - beta * s) / gamma;
@@ -998,7 +1003,7 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
             sv[c] = mean; sv[p.C + c] = istd;
             const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
             float* rm = row + p.stat_off;
-            rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * mean;
+            rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + bn_left_out(p, rep, c));
             rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
         }
         bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);

@@ -752,7 +752,7 @@ struct Runner {
                 f.a = act(l.in0); f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz;
                 f.wmat = wbf() + e.wf_off[i];
                 f.out = actw(ot);
-                f.bias = l.bias ? e.buf.replicas + l.b_off : nullptr; f.bias_rep = e.plan.row_stride;
+                f.bias = l.bias && !bias_left_out(i) ? e.buf.replicas + l.b_off : nullptr; f.bias_rep = e.plan.row_stride;
                 f.relu = p.relu;
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
@@ -786,7 +786,10 @@ struct Runner {
                 b.stats_done = 1; b.stat_entries = (b.rows + e.stat_rows[i] - 1) / e.stat_rows[i];
                 b.partial_rep = stat_floats(b.rows, b.C, e.fast[e.stat_from[i]]);
                 const Layer& conv = e.plan.layers[e.stat_from[i]];
-                b.stat_shift = conv.bias ? e.buf.replicas + conv.b_off : nullptr; b.stat_shift_rep = e.plan.row_stride;
+                b.stat_shift = conv.bias && !bias_left_out(e.stat_from[i]) ? e.buf.replicas + conv.b_off : nullptr; b.stat_shift_rep = e.plan.row_stride;
+            }
+            if (e.stat_from[i] >= 0 && bias_left_out(e.stat_from[i])) {
+                b.left_out = e.buf.replicas + e.plan.layers[e.stat_from[i]].b_off; b.left_out_rep = e.plan.row_stride;
             }
             if (e.pool_of[i] >= 0) {
                 b.pool = 1; b.H = a.h; b.W = a.w;
@@ -802,6 +805,10 @@ struct Runner {
             break; }
         }
     }
+
+    // An fp32 convolution whose output only a batch norm reads stores it without its bias (in bf16 the stored values are those of
+    // the network as written, rounded).
+    bool bias_left_out(size_t i) const { return !e.cfg.bf16 && e.general[i] && e.stat_for[i] >= 0 && e.plan.layers[i].bias; }
 
     DenseSmallParams dense_small(const Layer& l, const GemmParams& g) const
     {

@@ -258,6 +258,9 @@ struct BnParams {
     // stat_shift[c] (zero without one): what the outputs are centred on when the bias is large beside their spread
     int stats_done, stat_entries;
     const float* stat_shift; long long stat_shift_rep;
+    // forward: a bias that the producing convolution left out of x, since a normalised value does not depend on it; the running
+    // mean is that of x with it (a bias large beside the spread of x would cost x the low bits of its sums)
+    const float* left_out; long long left_out_rep;
     // backward: the data-gradient kernel of the layer above already left per-entry sums of g and g * y in `partial`
     // ([stat_entries][2][C], see FastConvParams::stat_y); the sums pass is skipped and d(gamma) is formed from them
     int bwd_stats_done;
