@@ -12,10 +12,10 @@
 //     added; all offsets are 32-bit;
 //   * the MFMA operands are swapped (C^T = B^T A^T), which leaves 4 consecutive output channels in each lane, so
 //     the epilogue stores 8 bytes (bf16) or 16 bytes (fp32) per lane instead of single elements.
-// Kernels: conv_kernel (forward / data gradient, any image size), conv_patch_kernel (the same on 16- and 32-pixel-wide
-// images with at most 128 channels: tile and border resident in LDS), wgrad_kernel (weight gradient: operands stored
-// as they arrive and transposed by the LDS read), wgrad_taps_kernel (weight gradient on wide images: all taps from one
-// patch), weight_prep_kernel.  Each has its own comment.
+// Kernels: conv_kernel (forward / data gradient of the layers that conv_general_patch.hip does not take: images wider than its
+// border allows, or of fewer than four pixels), wgrad_kernel (weight gradient: operands stored as they arrive and transposed by the
+// LDS read), wgrad_taps_kernel (weight gradient on wide images: all taps from one patch), weight_prep_kernel.  Each has its own
+// comment.
 #include <algorithm>
 
 #include "train_kernels.h"
@@ -243,220 +243,6 @@ __global__ __launch_bounds__(WGM * WGN * 64, NBUF == 2 && WGM * WGN == 8 ? 1 : 2
             for (int g = 0; g < 4; ++g) {
                 const int n = n0 + wn * (BN / WGN) + j * 32 + 8 * g + 4 * (lane >> 5);
                 const unsigned o = (unsigned)(pix * p.N + n) * 2u;
-                f4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-                bf16x4 mk = {};
-                f4 sh = {0.f, 0.f, 0.f, 0.f};                  // what the statistics are centred on: the bias
-                if (EPI == 0) {
-                    if (bias) { sh = *reinterpret_cast<const f4*>(bias + n); v += sh; }
-                    if (p.relu) { v[0] = fmaxf(v[0], 0.f); v[1] = fmaxf(v[1], 0.f); v[2] = fmaxf(v[2], 0.f); v[3] = fmaxf(v[3], 0.f); }
-                } else {
-                    if (mask) {
-                        mk = *reinterpret_cast<const bf16x4*>(mask + o);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) if (!((float)mk[e] > 0.f)) v[e] = 0.f;
-                    }
-                    if (p.accumulate) {
-                        const bf16x4 old = *reinterpret_cast<const bf16x4*>(obase + o);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] += (float)old[e];
-                    }
-                }
-                bf16x4 r;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) r[e] = (__bf16)v[e];
-                *reinterpret_cast<bf16x4*>(obase + o) = r;
-                if (stats) {
-                    if (EPI == 0) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) { const float f = (float)r[e] - sh[e]; ss[j][4 * g + e] += f; qq[j][4 * g + e] += f * f; }
-                    } else {
-                        // the mask of a fused ReLU is that very tensor: its values are already here
-                        const bf16x4 yv = y_is_mask ? mk : *reinterpret_cast<const bf16x4*>(ysrc + o);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float yy = (float)yv[e];
-                            const float f = (p.stat_relu && !(yy > 0.f)) ? 0.f : (float)r[e];
-                            ss[j][4 * g + e] += f; qq[j][4 * g + e] += f * yy;
-                        }
-                    }
-                }
-            }
-        }
-    }
-    if (stats) {
-        // (the launcher asks for the larger of the K loop's LDS and kStatLdsBytes)
-        __syncthreads();                                      // every wave is past its last operand read
-        const int slot = (int)(item / (tiles_m * tiles_n));
-        store_column_stats<TN, WGM, WGN>(ss, qq, reinterpret_cast<float*>(smem), wave, lane, p.stat + (long long)slot * p.stat_rep,
-                                         m0 / BMT, n0 + wn * (BN / WGN), p.N);
-    }
-}
-
-// Wide images (16 or 32 pixels per row) with few channels move more bytes per multiply-add than the general kernel can
-// fetch: it reads every activation once per tap.  Here a workgroup owns BMT consecutive pixels of one image (whole
-// rows), loads them ONCE per 64-channel slice together with their one-pixel border (zeros outside the image) into
-// LDS, and serves all R*S taps from that patch by shifting the row it reads; only the weights still stream per tap.
-// IW = image width; 3x3-style filters with pad = (R-1)/2 <= 1.
-// With 16-pixel rows the 32 lanes of an operand read span two patch rows; the read only runs at full rate when the
-// second row starts a multiple of 256 bytes after the first (measured: half rate otherwise), so patch rows are padded
-// to kPatchRowBytes<16>.
-template <int IW> constexpr int kPatchRowBytes = IW == 16 ? ((IW + 2) * 144 + 255) / 256 * 256 : (IW + 2) * 144;
-// TPS = taps per step (R * S a multiple of it): the weights of TPS taps of a channel slice are staged together, so a
-// wave multiplies TPS * 64 contraction indices between two barriers instead of 64.
-template <int IW, int BN, int WGM, int EPI, int TPS = 1, int BMT = 256>
-__global__ __launch_bounds__(256, BMT == 256 ? 2 : 4) void conv_patch_kernel(FastConvParams p)
-{
-    constexpr int LDQ = 72, PW = IW + 2, TR = BMT / IW, PR = (TR + 2) * PW;   // patch: (TR + 2) x (IW + 2) pixels
-    constexpr int RPB = kPatchRowBytes<IW>;                   // bytes per patch row
-    constexpr int WGN = 4 / WGM;                              // wave grid WGM x WGN, wave tile (BMT / WGM) x (BN / WGN)
-    constexpr int TM = BMT / WGM / 32, TN = BN / WGN / 32;
-    static_assert(TM >= 1 && TN >= 1, "");
-    constexpr int NQB = BN * 8 / 256;
-    constexpr int NQP = (PR * 8 + 255) / 256;                 // patch slots per thread
-    constexpr unsigned P_BYTES = (TR + 2) * RPB;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    char* const sP = smem;                                    // [TR + 2][RPB]: rows of PW pixels x LDQ, activations with border
-    char* const sB = smem + P_BYTES;                          // [TPS][BN][LDQ] weights of TPS taps of one channel slice
-    constexpr unsigned B_TAP = BN * LDQ * 2;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const unsigned tiles_m = (unsigned)p.M / BMT, tiles_n = (unsigned)p.N / BN;
-    const unsigned item = logical_block();
-    if (item >= tiles_m * tiles_n * (unsigned)p.n_active) return;
-    const int rep = p.order[item / (tiles_m * tiles_n)];
-    const int m0 = (int)(item % tiles_m) * BMT, n0 = (int)((item / tiles_m) % tiles_n) * BN;
-    const int img = m0 / (p.H * IW), y0 = (m0 - img * p.H * IW) / IW;          // first image row of the tile
-    const char* abase = (const char*)p.a + (long long)rep * p.a_rep * 4;
-    const char* wbase = (const char*)(p.wmat + (long long)rep * p.wmat_rep);
-
-    // patch slots: slot i = (patch pixel i / 8, 16-byte channel group i % 8)
-    int poff[NQP];                                            // byte offset of the source pixel's slice start, or -1
-    unsigned pst[NQP];
-#pragma unroll
-    for (int q = 0; q < NQP; ++q) {
-        const int i = tid + q * 256, pr = i >> 3, kq = i & 7;
-        const int py = pr / PW, px = pr - py * PW;
-        const int yy = y0 - 1 + py, xx = px - 1;
-        const bool ok = pr < PR && yy >= 0 && yy < p.H && xx >= 0 && xx < IW;
-        poff[q] = ok ? (((img * p.H + yy) * IW + xx) * p.C + kq * 8) * 2 : -1;
-        pst[q] = (unsigned)(py * RPB + (px * LDQ + kq * 8) * 2);
-    }
-    unsigned boff[NQB], sb_st[NQB];
-#pragma unroll
-    for (int q = 0; q < NQB; ++q) {
-        const int i = tid + q * 256;
-        boff[q] = (unsigned)((n0 + (i >> 3)) * p.K + (i & 7) * 8) * 2u;
-        sb_st[q] = (unsigned)((i >> 3) * LDQ + (i & 7) * 8) * 2u;
-    }
-    unsigned a_rd[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int pm = wm * (BMT / WGM) + i * 32 + (lane & 31);
-        a_rd[i] = (unsigned)((pm / IW) * RPB + ((pm % IW) * LDQ + (lane >> 5) * 8) * 2);
-    }
-    const unsigned b_rd = (unsigned)((wn * (BN / WGN) + (lane & 31)) * LDQ + (lane >> 5) * 8) * 2u;
-
-    f16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int taps = p.R * p.S;
-    const int off0 = 1 - p.pad;                               // patch border is one pixel: tap (r, s) reads patch pixel + (r + off0, s + off0)
-    // One step = TPS taps of one 64-channel slice: TPS * 64 contraction indices, too little matrix work to cover the
-    // latency of its own weight load.  The weights of step i are therefore requested D steps ahead, into a ring of
-    // register sets.
-    constexpr int D = TPS > 1 ? 2 : (BN <= 64 ? 4 : 2);
-    const int spt = taps / TPS;                               // steps per channel slice
-    const int steps = (p.C / 64) * spt;
-    u4 rb[D][TPS][NQB];
-    auto load_w = [&](int step, u4 (&dst)[TPS][NQB]) {
-        const int sl = step / spt, tap0 = (step - sl * spt) * TPS;
-#pragma unroll
-        for (int t = 0; t < TPS; ++t) {
-            const unsigned kb = (unsigned)((tap0 + t) * p.C + sl * 64) * 2u;
-#pragma unroll
-            for (int q = 0; q < NQB; ++q) dst[t][q] = ldg16(wbase, boff[q] + kb);
-        }
-    };
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d < steps) load_w(d, rb[d]);
-    for (int step0 = 0; step0 < steps; step0 += D) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const int step = step0 + d;
-            if (step >= steps) break;
-            const int sl = step / spt, tap0 = (step - sl * spt) * TPS;
-            if (tap0 == 0) {
-                u4 rp[NQP];
-#pragma unroll
-                for (int q = 0; q < NQP; ++q) {
-                    u4 v = {0u, 0u, 0u, 0u};
-                    if (poff[q] >= 0) v = ldg16(abase, (unsigned)(poff[q] + sl * 128));
-                    rp[q] = v;
-                }
-                __syncthreads();                              // every wave is done with the previous slice
-#pragma unroll
-                for (int q = 0; q < NQP; ++q)
-                    if (tid + q * 256 < PR * 8) *reinterpret_cast<u4*>(sP + pst[q]) = rp[q];
-            } else {
-                __syncthreads();                              // every wave is done reading the previous step's weights
-            }
-#pragma unroll
-            for (int t = 0; t < TPS; ++t)
-#pragma unroll
-                for (int q = 0; q < NQB; ++q) *reinterpret_cast<u4*>(sB + t * B_TAP + sb_st[q]) = rb[d][t][q];
-            __syncthreads();
-            if (step + D < steps) load_w(step + D, rb[d]);
-#pragma unroll
-            for (int t = 0; t < TPS; ++t) {
-                const int tap = tap0 + t;
-                const int r = tap / p.S, s2 = tap - r * p.S;
-                const unsigned toff = (unsigned)((r + off0) * RPB + (s2 + off0) * LDQ * 2);
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    bf16x8 a[TM], b[TN];
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const bf16x8*>(sP + a_rd[i] + toff + ks * 32);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const bf16x8*>(sB + t * B_TAP + b_rd + (j * 32 * LDQ + ks * 16) * 2);
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-                }
-            }
-        }
-    }
-
-    // ---- epilogue: lane holds output row (lane & 31) and channels 8*g + 4*(lane >> 5) + {0..3}, g = 0..3 ----
-    char* obase = (char*)p.out + (long long)rep * p.out_rep * 4;
-    const float* bias = (EPI == 0 && p.bias) ? p.bias + (long long)rep * p.bias_rep : nullptr;
-    const char* mask = (EPI == 1 && p.mask) ? (const char*)p.mask + (long long)rep * p.mask_rep * 4 : nullptr;
-    const bool stats = p.stat != nullptr;
-    // data gradient with statistics: values of the tensor whose gradient this is (see FastConvParams::stat_y)
-    const char* ysrc = (EPI == 1 && stats) ? (const char*)p.stat_y + (long long)rep * p.stat_y_rep * 4 : nullptr;
-    const bool y_is_mask = mask != nullptr && ysrc == mask;
-    float ss[TN][16], qq[TN][16];
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) { ss[j][kk] = 0.f; qq[j][kk] = 0.f; }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int mm = m0 + wm * (BMT / WGM) + i * 32 + (lane & 31);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n0 + wn * (BN / WGN) + j * 32 + 8 * g + 4 * (lane >> 5);
-                const unsigned o = (unsigned)(mm * p.N + n) * 2u;
                 f4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
                 bf16x4 mk = {};
                 f4 sh = {0.f, 0.f, 0.f, 0.f};                  // what the statistics are centred on: the bias
@@ -1023,35 +809,6 @@ hipError_t launch_conv_fast(const FastConvParams& p0, int epi, int n_active, hip
     FastConvParams p = p0;
     p.n_active = n_active;
     if (p.C % 64 != 0 || p.N % 64 != 0) return hipErrorInvalidValue;
-    // wide images with at most 128 channels in and out: the patch kernel (tiles are whole rows of one image)
-    if ((p.W == 16 || p.W == 32) && p.C <= 128 && p.N <= 128 && p.R == p.S && p.R <= 3 && 2 * p.pad == p.R - 1 &&
-        (p.H * p.W) % 256 == 0 && p.M % 256 == 0 && p.tile_hint != 2) {
-        const int bn = (p.N % 128 == 0) ? 128 : 64;
-        const dim3 block(256);
-#define HADFL_PATCH(IW_, BN_, WGM_, TPS_, BMT_) do { \
-            constexpr size_t loop_lds = (size_t)(BMT_ / IW_ + 2) * kPatchRowBytes<IW_> + (size_t)TPS_ * BN_ * 72 * 2; \
-            constexpr size_t stat_lds = kStatLdsBytes<BN_ / (4 / WGM_) / 32, WGM_, 4 / WGM_>; \
-            constexpr size_t lds = loop_lds > stat_lds ? loop_lds : stat_lds; \
-            static const bool ok = hipFuncSetAttribute((const void*)conv_patch_kernel<IW_, BN_, WGM_, 0, TPS_, BMT_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess && \
-                                   hipFuncSetAttribute((const void*)conv_patch_kernel<IW_, BN_, WGM_, 1, TPS_, BMT_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess; \
-            if (!ok) return hipErrorInvalidValue; \
-            const dim3 grid(die_grid((long long)(p.M / BMT_) * (p.N / bn) * n_active)); \
-            srows = BMT_; \
-            if (epi == 0) hipLaunchKernelGGL((conv_patch_kernel<IW_, BN_, WGM_, 0, TPS_, BMT_>), grid, block, lds, s, p); \
-            else hipLaunchKernelGGL((conv_patch_kernel<IW_, BN_, WGM_, 1, TPS_, BMT_>), grid, block, lds, s, p); } while (0)
-        // 128 output channels: waves 2 x 2; 64: waves 4 x 1
-        // 32-pixel rows, 64 channels: 128-pixel tiles, four workgroups per compute unit (a tile's nine steps are too
-        // short to hide its own patch load and stores: 10 % faster than 256-pixel tiles with two).  16-pixel rows, 64
-        // channels: a whole filter row of weights per step where the filter has three (3-6 % faster); 128-pixel tiles
-        // measured no different there, nor with 128 channels.
-        if (p.W == 32 && bn == 128) HADFL_PATCH(32, 128, 2, 1, 256);
-        else if (p.W == 32) HADFL_PATCH(32, 64, 4, 1, 128);
-        else if (bn == 128) HADFL_PATCH(16, 128, 2, 1, 256);
-        else if (p.R == 3 && p.S == 3) HADFL_PATCH(16, 64, 4, 3, 256);
-        else HADFL_PATCH(16, 64, 4, 1, 256);
-#undef HADFL_PATCH
-        return hipGetLastError();
-    }
     if (p.N % 256 == 0) {
         // One 256 x 256 workgroup per compute unit at a time: worth it when the last round of workgroups is nearly full.
         static const BigTileInfo big = query_big_tile();     // once per process (one GPU per process)

@@ -59,9 +59,10 @@ public:
     std::vector<int> bstat_rows;          // per layer (BN): rows per entry of the latest data-gradient launch (0: none)
     std::vector<int64_t> bstat_rep;       // per layer (BN): floats per replica slot of those entries
     // bf16 configuration: regular convolution layers keep two bf16 weight matrices (forward / data-gradient order)
-    std::vector<char> fast;               // per layer: the lean bf16 kernels apply
-    std::vector<char> general, general_w; // per layer: not lean, but the kernels of conv_general.hip apply (forward and data
-                                          // gradient; weight gradient)
+    std::vector<char> fast;               // per layer: the lean bf16 kernels apply (those of forward and data gradient unless `general`)
+    std::vector<char> general, general_w; // per layer: the kernels of conv_general.hip apply (forward and data gradient; weight
+                                          // gradient)
+    std::vector<char> patch;              // per general layer: forward and data gradient run in conv_general_patch.hip
     std::vector<int64_t> wf_off, wb_off;  // per layer: offsets (2-byte units) inside one replica's block of weight copies, or -1
     int64_t wbf_rep = 0;                  // bf16 elements per replica
     int64_t wbf_off = 0;                  // start of the bf16 weight region inside `work` (floats)
@@ -96,7 +97,7 @@ struct Layout {
     std::vector<int> splits, bn_chunks;
     std::vector<std::vector<WgradPlan>> wgrad_plans;
     int64_t rep_block = 0, shared_floats = 0, bn_floats = 0;
-    std::vector<char> fast, general, general_w;
+    std::vector<char> fast, general, general_w, patch;
     std::vector<int64_t> wf_off, wb_off;       // in 2-byte units inside one replica's block of weight copies
     int64_t wbf_rep = 0;
     std::vector<int64_t> tab_idx;
@@ -208,12 +209,13 @@ bool general_wgrad(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
     return general_layer(cfg, plan, l) && !(gather_layer(cfg, l) && plan.tensors[0].c % 4 == 0 && l.k * l.k * plan.tensors[0].c > 32);
 }
 
-// General layers whose forward pass and data gradient run from patches (conv_general_patch.hip)
+// Lean and general layers whose forward pass and data gradient run from patches (conv_general_patch.hip)
 bool patch_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
-    if (l.type != HADFL_OP_CONV || l.in0 == 0 || l.stride != 1 || 2 * l.pad != l.k - 1 || !general_layer(cfg, plan, l)) return false;
+    if (l.type != HADFL_OP_CONV || l.in0 == 0 || l.stride != 1 || 2 * l.pad != l.k - 1) return false;
     const TensorShape a = plan.tensors[l.in0];
-    return conv_patch_supported(cfg.bf16, a.h, a.w, a.c, l.cout, l.k);
+    const bool fits = cfg.batch * (int64_t)a.h * a.w * std::max(a.c, l.cout) * 4 < int64_t(1) << 31 && (int64_t)l.k * l.k * a.c * l.cout * 2 < int64_t(1) << 31;
+    return (lean_layer(cfg, plan, l) ? fits : general_layer(cfg, plan, l)) && conv_patch_supported(cfg.bf16, a.h, a.w, a.c, l.cout, l.k);
 }
 
 // Plan of a general layer's weight gradient with n active replicas
@@ -298,17 +300,19 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
     L.rep_block = up64(off);
     L.shared_floats = up64(shared);
     L.fast.assign(plan.layers.size(), 0); L.general.assign(plan.layers.size(), 0); L.general_w.assign(plan.layers.size(), 0);
+    L.patch.assign(plan.layers.size(), 0);
     L.wf_off.assign(plan.layers.size(), -1); L.wb_off.assign(plan.layers.size(), -1);
     {
         int64_t woff = 0;
         for (size_t i = 0; i < plan.layers.size(); ++i) {
             const Layer& l = plan.layers[i];
             L.general_w[i] = general_wgrad(cfg, plan, l);
-            if (lean_layer(cfg, plan, l)) {
-                L.fast[i] = 1;
+            L.fast[i] = lean_layer(cfg, plan, l);
+            L.patch[i] = patch_layer(cfg, plan, l);
+            if (L.fast[i] && !L.patch[i]) {
                 L.wf_off[i] = woff; woff += up64(l.w_count);
                 L.wb_off[i] = woff; woff += up64(l.w_count);
-            } else if (general_forward(cfg, plan, l)) {
+            } else if (L.patch[i] || general_forward(cfg, plan, l)) {
                 const TensorShape a = plan.tensors[l.in0];
                 const int cin = (int)(l.type == HADFL_OP_CONV ? a.c : a.numel()), taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1;
                 L.general[i] = 1;
@@ -317,21 +321,22 @@ Layout make_layout(const hadfl_config& cfg, const NetPlan& plan)
                     L.wf_off[i] = woff; woff += up64(weight_copy_units(0, l.cout, 1, taps * cin));
                     continue;
                 }
-                const auto units = patch_layer(cfg, plan, l) ? weight_fragment_units : weight_copy_units;
+                const auto units = L.patch[i] ? weight_fragment_units : weight_copy_units;
                 L.wf_off[i] = woff; woff += up64(units(cfg.bf16, l.cout, taps, cin));
                 L.wb_off[i] = woff; woff += up64(units(cfg.bf16, cin, taps, l.cout));
             }
         }
         L.wbf_rep = woff;
     }
-    // a lean or general convolution in front of a batch norm leaves statistics entries of its output, and a lean one behind
-    // a batch norm (and its ReLU and pool) leaves entries of that batch norm's gradient, the size of its own input
+    // a lean or general convolution in front of a batch norm leaves statistics entries of its output, and in bf16 a lean one or
+    // one from patches behind a batch norm (and its ReLU and pool) leaves entries of that batch norm's gradient, the size of its
+    // own input
     for (size_t k = 0; k < plan.layers.size(); ++k) {
         const Layer& l = plan.layers[k];
         const TensorShape a = plan.tensors[l.in0];
         const bool behind = l.type == HADFL_OP_BN && l.in0 > 0 && (L.fast[l.in0 - 1] || L.general[l.in0 - 1]);
-        if (!behind && !L.fast[k]) continue;
-        const bool lean = L.fast[k] || L.fast[l.in0 - 1];
+        if (!behind && !L.fast[k] && !(cfg.bf16 && L.patch[k])) continue;
+        const bool lean = !L.general[behind ? l.in0 - 1 : (int)k];
         bn_shared = std::max<int64_t>(bn_shared, cfg.n_replicas * stat_floats(B * a.h * a.w, a.c, lean));
     }
     L.bn_floats = up64(bn_shared);
@@ -374,7 +379,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
     e->rep_block = L.rep_block;
     e->shared_off = L.rep_block * cfg.n_replicas;
     e->shared_floats = L.shared_floats;
-    e->fast = L.fast; e->general = L.general; e->general_w = L.general_w; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
+    e->fast = L.fast; e->general = L.general; e->general_w = L.general_w; e->patch = L.patch; e->wf_off = L.wf_off; e->wb_off = L.wb_off; e->wbf_rep = L.wbf_rep;
     e->bn_off = e->shared_off + L.shared_floats;
     e->bn_floats = L.bn_floats;
     e->wbf_off = e->bn_off + L.bn_floats;
@@ -479,7 +484,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
                 const int t_out = e->pool_of[k] >= 0 ? plan.layers[e->pool_of[k]].out : e->out_tensor[k];
                 if (consumers[t_out] != 1) continue;
                 for (int j = 0; j < nl; ++j)
-                    if (plan.layers[j].type == HADFL_OP_CONV && plan.layers[j].in0 == t_out && e->fast[j]) e->bstat_for[j] = k;
+                    if (plan.layers[j].type == HADFL_OP_CONV && plan.layers[j].in0 == t_out && (e->fast[j] || e->patch[j])) e->bstat_for[j] = k;
             }
     }
     *out = e;
@@ -590,7 +595,7 @@ struct Runner {
             w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
             w.C = layer_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.bf16 = e.cfg.bf16; w.order = e.buf.order;
             if (gather_layer(e.cfg, l)) { w.C *= w.taps; w.taps = 1; }
-            w.fragments = patch_layer(e.cfg, e.plan, l);
+            w.fragments = e.patch[i];
             run("weight_prep", 0, (e.cfg.bf16 ? 8.0 : 16.0) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
         } else {
             WeightPrepParams w{};
@@ -728,7 +733,7 @@ struct Runner {
                 run("dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_dense_rows_fwd(d, na, s); });
                 break;
             }
-            if (e.fast[i]) {
+            if (e.fast[i] && !e.general[i]) {
                 FastConvParams f{};
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
                 f.M = p.M; f.K = p.K;
@@ -740,7 +745,7 @@ struct Runner {
                 f.perm = perm(i); f.posmask = posmask(i);
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
+                    f.stat_rep = stat_floats(p.M, p.Cout, true); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
                 run("conv_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_conv_fast(f, 0, na, s, srows); });
@@ -756,10 +761,10 @@ struct Runner {
                 f.relu = p.relu;
                 int* srows = nullptr;
                 if (e.stat_for[i] >= 0) {
-                    f.stat_rep = stat_floats(p.M, p.Cout, e.fast[i]); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
+                    f.stat_rep = stat_floats(p.M, p.Cout, false); f.stat = bn_shared(f.stat_rep, e.stat_for[i]);
                     srows = &e.stat_rows[e.stat_for[i]];
                 }
-                run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return patch_layer(e.cfg, e.plan, l) ? launch_conv_general_patch(f, 0, na, s, srows) : launch_conv_general(f, 0, na, s, srows); });
+                run(l.type == HADFL_OP_CONV ? "conv_fwd" : "dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return e.patch[i] ? launch_conv_general_patch(f, 0, na, s, srows) : launch_conv_general(f, 0, na, s, srows); });
                 break;
             }
             if (small_dense_layer(l) && !p.relu) {
@@ -784,7 +789,7 @@ struct Runner {
             b.y = actw(ot); b.relu = e.fused_relu[i];
             if (sums_done) {                                 // the convolution in front left the sums
                 b.stats_done = 1; b.stat_entries = (b.rows + e.stat_rows[i] - 1) / e.stat_rows[i];
-                b.partial_rep = stat_floats(b.rows, b.C, e.fast[e.stat_from[i]]);
+                b.partial_rep = stat_floats(b.rows, b.C, !e.general[e.stat_from[i]]);
                 const Layer& conv = e.plan.layers[e.stat_from[i]];
                 b.stat_shift = conv.bias && !bias_left_out(e.stat_from[i]) ? e.buf.replicas + conv.b_off : nullptr; b.stat_shift_rep = e.plan.row_stride;
             }
@@ -852,6 +857,17 @@ struct Runner {
         b.partial_rep = (long long)b.chunks * 2 * a.c; b.partial = bn_shared(b.partial_rep, -1);
         b.order = e.buf.order; b.bf16 = e.cfg.bf16;
         return b;
+    }
+
+    // Data gradient d of layer i, which is the whole gradient of a batch norm's output: it leaves that batch norm's sums.  Returns
+    // where the rows per entry go.
+    template <typename P> int* gradient_sums(P& f, size_t i, const GemmParams& d, bool lean)
+    {
+        const int k = e.bstat_for[i];
+        f.stat_rep = stat_floats(d.M, d.N, lean); f.stat = bn_shared(f.stat_rep, kBackward + k);
+        f.stat_y = act(e.plan.layers[i].in0); f.stat_y_rep = e.rep_block; f.stat_relu = e.fused_relu[k];
+        e.bstat_rep[k] = f.stat_rep;
+        return &e.bstat_rows[k];
     }
 
     // d(out) is complete; produce d(in0) (and d(in1)), and the parameter gradients of the layer
@@ -958,7 +974,7 @@ struct Runner {
                 d.out = grad(l.in0); d.out_rep = e.rep_block;
                 d.accumulate = acc0;
                 d.mask = mask0; d.mask_rep = e.rep_block;
-                if (e.fast[i]) {
+                if (e.fast[i] && !e.general[i]) {
                     FastConvParams f{};
                     f.B = d.B; f.H = d.H; f.W = d.W; f.C = d.Cout; f.N = d.Cin; f.R = d.R; f.S = d.S; f.pad = d.R - 1 - d.pad;
                     f.M = d.M; f.K = d.K;
@@ -968,13 +984,7 @@ struct Runner {
                     f.mask = mask0; f.mask_rep = e.rep_block; f.accumulate = acc0; f.order = e.buf.order; f.tile_hint = e.tile_hint;
                     f.perm = perm(i); f.posmask = posmask(i);
                     int* brows = nullptr;
-                    if (e.bstat_for[i] >= 0 && !acc0) {        // this data gradient is the whole gradient of a BN's output
-                        const int k = e.bstat_for[i];
-                        f.stat_rep = stat_floats(d.M, d.N, true); f.stat = bn_shared(f.stat_rep, kBackward + k);
-                        f.stat_y = act(l.in0); f.stat_y_rep = e.rep_block; f.stat_relu = e.fused_relu[k];
-                        e.bstat_rep[k] = f.stat_rep;
-                        brows = &e.bstat_rows[k];
-                    }
+                    if (e.bstat_for[i] >= 0 && !acc0) brows = gradient_sums(f, i, d, true);
                     run("conv_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return launch_conv_fast(f, 1, na, s, brows); });
                 } else if (e.general[i]) {
                     GeneralConvParams f = general_base(i, d);
@@ -984,7 +994,9 @@ struct Runner {
                     f.wmat = wbf() + e.wb_off[i];
                     f.out = grad(l.in0);
                     f.mask = mask0; f.mask_rep = e.rep_block; f.accumulate = acc0;
-                    run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return patch_layer(e.cfg, e.plan, l) ? launch_conv_general_patch(f, 1, na, s) : launch_conv_general(f, 1, na, s); });
+                    int* brows = nullptr;
+                    if (e.bstat_for[i] >= 0 && !acc0) brows = gradient_sums(f, i, d, false);
+                    run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return e.patch[i] ? launch_conv_general_patch(f, 1, na, s, brows) : launch_conv_general(f, 1, na, s); });
                 } else
                 run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return gemm(d); });
             }

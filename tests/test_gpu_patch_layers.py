@@ -2,6 +2,7 @@
 a border, sorted positions, ragged channels, images and batches, and operands whose bf16 parts are not finite, in both directions."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import nets
 from paper_2111_08274_amd import hadfl
@@ -58,6 +59,46 @@ def test_patch_layers(shape):
             err = np.abs(g[off:off + cnt] - want[off:off + cnt]) / max(np.abs(want[off:off + cnt]).max(), floor)
             print(shape, kind, cnt, "max %.1e median %.1e" % (err.max(), np.median(err)), flush=True)
             assert err.max() <= 5e-3 and (err > 3e-5).mean() <= 0.01, (shape, kind, float(err.max()), float((err > 3e-5).mean()))
+
+
+# bf16 (image, channels in and out, k, batch, replicas, tile hint)
+SHAPES_BF16 = [((8, 8), 64, 136, 3, 9, 2, 1), ((16, 32), 72, 64, 3, 5, 2, 1), ((5, 7), 40, 264, 3, 50, 1, 0), ((8, 6), 72, 200, 5, 40, 12, 0), ((16, 16), 128, 128, 3, 60, 4, 0),
+               ((8, 8), 128, 256, 3, 64, 16, 0), ((10, 10), 40, 80, 3, 33, 6, 0), ((32, 32), 64, 64, 3, 17, 2, 0), ((4, 4), 256, 512, 3, 32, 1, 0), ((4, 4), 512, 512, 3, 50, 2, 0),
+               ((2, 2), 256, 512, 3, 32, 1, 0), ((2, 2), 512, 512, 3, 128, 12, 0), ((2, 2), 256, 256, 3, 1024, 4, 0), ((7, 31), 48, 64, 1, 20, 2, 0), ((64, 9), 64, 64, 1, 8, 2, 0)]
+
+
+@pytest.mark.parametrize("shape", SHAPES_BF16)
+def test_patch_layers_bf16(shape):
+    """Gradients of one step against the same network in 64 bits, in the 2-norm of a tensor.  What roundings to bf16 do to a
+    tensor (units within 2^-9 of zero that open on one side only, sums that nearly cancel) is measured on the 64-bit network: the
+    difference that rounding its weights to bf16 makes.  The library also rounds three activations and their gradients, so at
+    most some three times as many roundings of that size: bound 4 times that difference, and 1e-2 (ten roundings of 2^-9) for what
+    it misses.  A tap, channel or pixel astray is of order 1."""
+    (h, w), c, n, k, batch, replicas, hint = shape
+    rng = np.random.default_rng(c + n + batch)
+    x = rng.standard_normal((1, batch, h, w, 3)).astype(np.float32)
+    y = rng.integers(0, CLASSES, (1, batch)).astype(np.int32)
+    cfg = hadfl.make_config(replicas, 1, net="custom", custom_ops=net(c, n, k).array()[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=batch, n_samples=batch,
+                            in_shape=(h, w, 3), n_classes=CLASSES, lr=1e-30, momentum=0.5, bf16=1)
+    layout = hadfl.param_layout(cfg)
+    w0 = np.zeros(max(o + m for o, m, _, _ in layout), dtype=np.float32)
+    for off, cnt, kind, fan_in in layout:
+        w0[off:off + cnt] = {"weight": rng.standard_normal(cnt) * np.sqrt(2.0 / max(fan_in, 1)), "bias": 0.1 * rng.standard_normal(cnt), "gamma": 1.0, "running_var": 1.0}.get(kind, 0.0)
+    ctx = hadfl.Context(cfg, [1] * replicas, w0=w0, x=np.repeat(x, replicas, 0), y=np.repeat(y, replicas, 0), options={hadfl.OPT_TILE_HINT: hint})
+    ctx.local_steps()
+    got = [ctx.momentum(r).astype(np.float64) for r in sorted({0, replicas - 1})]
+    ctx.close()
+    exact, rounded = (torch_ref.loss_grad(net(c, n, k).array(), (h, w, 3), v.astype(np.float64), x[0].astype(np.float64).reshape(batch, -1), y[0])[1]
+                      for v in (w0, torch.as_tensor(w0).bfloat16().float().numpy()))
+    for g in got:
+        for off, cnt, kind, _ in layout:
+            if off + cnt > g.size:
+                continue
+            part = slice(off, off + cnt)
+            size = np.linalg.norm(exact[part])
+            err, twin = np.linalg.norm(g[part] - exact[part]) / size, np.linalg.norm(rounded[part] - exact[part]) / size
+            print(shape, kind, cnt, "%.1e (twin %.1e)" % (err, twin), flush=True)
+            assert err <= 4 * twin + 1e-2, (shape, kind, off, float(err), float(twin))
 
 
 @pytest.mark.parametrize("what", ["activation", "gradient"])

@@ -239,9 +239,9 @@ def test_patch_layers_reach_every_tile(checked):
     runs = checked(cases)
     assert all(r["status"] == 0 and r["report"] == "" and layers_in(r["trace"], "general_patch") == 4 for r in runs)
     seen = {name.split("patch_kernelIfLi")[1].split("EEEv")[0] for r in runs for name in r["trace"] if "general_patch" in name}
-    tiles = ("4ELi1ELi4ELi1ELi4ELi1ELi%dELb0", "4ELi1ELi4ELi1ELi2ELi1ELi%dELb1", "4ELi2ELi2ELi1ELi6ELi1ELi%dELb0", "2ELi2ELi2ELi1ELi4ELi1ELi%dELb0",
-             "2ELi2ELi2ELi1ELi2ELi2ELi%dELb1", "2ELi1ELi2ELi2ELi5ELi2ELi%dELb0", "2ELi1ELi2ELi4ELi5ELi2ELi%dELb0", "2ELi1ELi1ELi8ELi6ELi2ELi%dELb0",
-             "2ELi1ELi1ELi8ELi4ELi2ELi%dELb1", "1ELi1ELi2ELi4ELi3ELi2ELi%dELb0")
+    tiles = ("4ELi1ELi4ELi1ELi4ELi1ELi%dELb0ELi1", "4ELi1ELi4ELi1ELi2ELi1ELi%dELb1ELi1", "4ELi2ELi2ELi1ELi6ELi1ELi%dELb0ELi1", "2ELi2ELi2ELi1ELi4ELi1ELi%dELb0ELi1",
+             "2ELi2ELi2ELi1ELi2ELi2ELi%dELb1ELi1", "2ELi1ELi2ELi2ELi5ELi2ELi%dELb0ELi1", "2ELi1ELi2ELi4ELi5ELi2ELi%dELb0ELi1", "2ELi1ELi1ELi8ELi6ELi2ELi%dELb0ELi1",
+             "2ELi1ELi1ELi8ELi4ELi2ELi%dELb1ELi1", "1ELi1ELi2ELi4ELi3ELi2ELi%dELb0ELi1")
     missing = {t % epi for t in tiles for epi in (0, 1)} - seen
     assert not missing, missing
     out = []
@@ -249,6 +249,25 @@ def test_patch_layers_reach_every_tile(checked):
         b = nets._Builder()
         b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(0, c))), n, k=k, stride=stride, pad=k // 2))), 5)
         out.append(case(b, (side, side, 3), 16, [1], 0, classes=5))
+    assert all(layers_in(r["trace"], "general_patch") == 0 for r in checked(out))
+
+
+def test_patch_layers_reach_every_tile_bf16(checked):
+    """The same for the bf16 layers: every tile in both directions; a strided, narrow or too wide layer stays out."""
+    from tests.test_gpu_patch_layers import SHAPES_BF16, net
+    runs = checked([case(net(c, n, k), (h, w, 3), batch, [1] * replicas, 1, classes=5, options=[(1, hint)]) for (h, w), c, n, k, batch, replicas, hint in SHAPES_BF16])
+    assert all(r["status"] == 0 and r["report"] == "" and layers_in(r["trace"], "general_patch") == 4 for r in runs)
+    seen = {name.split("patch_kernelIDF16bLi")[1].split("EEEv")[0] for r in runs for name in r["trace"] if "general_patch" in name}
+    tiles = ("4ELi2ELi2ELi1ELi11ELi1ELi%dELb0ELi2", "4ELi2ELi2ELi1ELi11ELi1ELi%dELb0ELi1", "4ELi1ELi4ELi1ELi7ELi1ELi%dELb0ELi2",
+             "2ELi2ELi2ELi1ELi7ELi1ELi%dELb0ELi2", "2ELi2ELi2ELi1ELi7ELi1ELi%dELb0ELi1", "2ELi1ELi2ELi2ELi9ELi2ELi%dELb0ELi1",
+             "2ELi1ELi2ELi4ELi9ELi2ELi%dELb0ELi1", "1ELi1ELi2ELi4ELi7ELi2ELi%dELb0ELi1", "1ELi4ELi1ELi1ELi4ELi1ELi%dELb1ELi2")
+    missing = {t % epi for t in tiles for epi in (0, 1)} - seen
+    assert not missing, missing
+    out = []
+    for side, c, n, k, stride in ((8, 32, 64, 3, 1), (8, 64, 32, 3, 1), (8, 64, 64, 3, 2), (40, 64, 64, 3, 1), (16, 64, 64, 5, 1), (1, 64, 64, 3, 1)):
+        b = nets._Builder()
+        b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(0, c))), n, k=k, stride=stride, pad=k // 2))), 5)
+        out.append(case(b, (side, side, 3), 16, [1], 1, classes=5))
     assert all(layers_in(r["trace"], "general_patch") == 0 for r in checked(out))
 
 
