@@ -806,23 +806,27 @@ __global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_genera
 // fp32 master W[tap][ci][co] -> Wf[co][tap][ci] and Wb[ci][T-1-tap][co] as described at the top.  A workgroup handles one
 // tap and a 64 x 64 (ci, co) tile; each thread forms 16-byte groups of eight positions.  p.fragments: the order of the lanes of a
 // matrix instruction instead (conv_general_patch.hip), [32 rows][slab][tap][16 channels][plane][half of them][row], rows beyond the
-// last zero.  Bound by memory: 4 bytes read and
-// 12 (bf16: 4) written per weight.
+// last zero.  Bound by memory: 4 bytes read and 12 (bf16: 4) written per weight.  Weights are read, and pass through LDS, sixteen bytes a
+// lane (N and the layer's offset are multiples of four).
 template <typename T>
 __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
 {
     constexpr bool kSplit = std::is_same<T, float>::value;
     constexpr int kSlab = Slab<T>::channels, kSlabBytes = Slab<T>::bytes, GR = Slab<T>::groups;
-    __shared__ float tile[64][65];                            // [ci][co], zero outside the layer
+    __shared__ __attribute__((aligned(16))) float tile[64][68];          // [ci][co], zero outside the layer
     const int rep = p.order[blockIdx.z];
     const int tap = blockIdx.y % p.taps, co0 = (blockIdx.y / p.taps) * 64, ci0 = blockIdx.x * 64;
     const float* w = p.w + (long long)rep * p.w_rep + (long long)tap * p.C * p.N;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const int tx = (threadIdx.x & 15) * 4, ty = threadIdx.x >> 4;
+    f4 in[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int ci = ci0 + ty + 4 * r;
-        tile[ty + 4 * r][tx] = (ci < p.C && co0 + tx < p.N) ? w[(long long)ci * p.N + co0 + tx] : 0.f;
+    for (int r = 0; r < 4; ++r) {
+        const int ci = ci0 + ty + 16 * r;
+        in[r] = f4{0.f, 0.f, 0.f, 0.f};
+        if (ci < p.C && co0 + tx < p.N) in[r] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(w + (long long)ci * p.N + co0 + tx));
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) *reinterpret_cast<f4*>(&tile[ty + 16 * r][tx]) = in[r];
     __syncthreads();
     const int csf = (p.C + kSlab - 1) / kSlab, csb = (p.N + kSlab - 1) / kSlab;
 #pragma unroll
@@ -843,13 +847,18 @@ __global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
                 : base + ((long long)(row0 + row) * p.taps * cs + t * cs + slab) * kSlabBytes + g * 16;
             const int plane = p.fragments ? 1024 : 64;
             bf16x8 h, m, l;
+            f4 v[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {                     // positions k .. k + 3 twice: sixteen apart, or neighbours (bf16)
+                const int k = kSplit ? sl * kSlab + u * 16 + g * 4 : g * 8 + u * 4;
+                if (which) v[u] = *reinterpret_cast<const f4*>(&tile[row][k]);
+                else v[u] = f4{tile[k][row], tile[k + 1][row], tile[k + 2][row], tile[k + 3][row]};
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int k = kSplit ? sl * kSlab + (e >> 2) * 16 + g * 4 + (e & 3) : g * 8 + e;
-                const float v = which ? tile[row][k] : tile[k][row];
                 __bf16 a, b, c;
-                if (kSplit) { split_weight(v, a, b, c); h[e] = a; m[e] = b; l[e] = c; }
-                else h[e] = (__bf16)v;
+                if (kSplit) { split_weight(v[e >> 2][e & 3], a, b, c); h[e] = a; m[e] = b; l[e] = c; }
+                else h[e] = (__bf16)v[e >> 2][e & 3];
             }
             *reinterpret_cast<bf16x8*>(o) = h;
             if (kSplit) { *reinterpret_cast<bf16x8*>(o + plane) = m; *reinterpret_cast<bf16x8*>(o + 2 * plane) = l; }

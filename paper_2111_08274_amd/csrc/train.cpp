@@ -214,7 +214,7 @@ bool patch_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
     if (l.type != HADFL_OP_CONV || l.in0 == 0 || l.stride != 1 || 2 * l.pad != l.k - 1) return false;
     const TensorShape a = plan.tensors[l.in0];
-    const bool fits = cfg.batch * (int64_t)a.h * a.w * std::max(a.c, l.cout) * 4 < int64_t(1) << 31 && (int64_t)l.k * l.k * a.c * l.cout * 2 < int64_t(1) << 31;
+    const bool fits = cfg.batch * (int64_t)a.h * a.w * std::max(a.c, l.cout) * 4 < int64_t(1) << 31 && (int64_t)l.k * l.k * a.c * l.cout * 2 < int64_t(1) << 31 && l.w_off % 4 == 0;
     return (lean_layer(cfg, plan, l) ? fits : general_layer(cfg, plan, l)) && conv_patch_supported(cfg.bf16, a.h, a.w, a.c, l.cout, l.k);
 }
 
