@@ -14,12 +14,13 @@
 //     the epilogue stores 8 bytes (bf16) or 16 bytes (fp32) per lane instead of single elements.
 // Kernels: conv_kernel (forward / data gradient of the layers that conv_general_patch.hip does not take: images wider than its
 // border allows, or of fewer than four pixels), wgrad_kernel (weight gradient: operands stored as they arrive and transposed by the
-// LDS read), wgrad_taps_kernel (weight gradient on wide images: all taps from one patch), weight_prep_kernel.  Each has its own
-// comment.
+// LDS read), wgrad_taps_kernel (weight gradient on wide images: all taps from one patch), wgrad_images_kernel (on 4 x 4 images: all
+// taps, sixteen images a contraction), weight_prep_kernel.  Each has its own comment.
 #include <algorithm>
 
 #include "train_kernels.h"
 #include "conv_stats.h"
+#include "mfma_tiles.h"
 
 namespace hadfl {
 namespace {
@@ -683,6 +684,139 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(FastWgradParams p)
 }
 
 // ---------------------------------------------------------------------------------------------------------------
+// Weight gradient on images of 4 x 4 pixels: dW[tap][ci][co] = sum over positions and images of
+// x[image][position + tap][ci] * dy[image][position][co], a contraction of sixteen IMAGES at one position.  A tap then moves whole
+// operands: one outside the image is a matrix instruction less (31 % of them), and all nine taps come from one fetch of x.
+// wgrad_kernel, a tile of which has one or two taps, fetches x once per tap and skips positions only where all its taps are outside.
+// A workgroup owns nine taps of 64 input against 64 output channels, a wave 32 x 32 of them, and takes sixteen images at a time
+// through LDS as they arrive, [position][image] rows of 128 bytes, transposed by the read; the halves of a row change places with bit 1
+// of the row, so that the four rows x 64 bytes of a read meet different banks.  Along a row of positions x operands are kept in
+// registers, three columns at a time (56 operands read for 100 matrix instructions).  One workgroup's loads and update run beside the
+// other's matrix instructions: two are resident per compute unit (64 KiB of LDS each).
+// 512 to 512 channels with the update (16 bytes a weight), batch 128, us, wgrad_kernel / this: 1 replica (two splits) 52 / 34, 4 replicas
+// 91 / 54, 16 replicas 245 / 150, 32 replicas 448 / 277 (the update alone 250 at a copy's rate).  The same on 2 x 2 images, 64 of them
+// at a time: 25 / 21, 40 / 34, 115 / 116, 214 / 223, bound by the update either way; they stay in wgrad_kernel.
+// ---------------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256, 2) void wgrad_images_kernel(FastWgradParams p)
+{
+    constexpr int H = 4, W = 4, HW = H * W, kImages = 16, kBytes = HW * kImages * 128;       // images and LDS bytes of a stage
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char* const sX = smem;
+    char* const sD = smem + kBytes;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ch = wave & 1, nh = wave >> 1;
+    // logical item = (slot, split, input slice, output tile)
+    const unsigned cslices = (unsigned)p.C / 64, ntiles = (unsigned)p.N / 64, tiles = cslices * ntiles;
+    const unsigned item = logical_block();
+    if (item >= tiles * (unsigned)p.splits * (unsigned)p.n_active) return;
+    const int g = (int)(item / (tiles * (unsigned)p.splits));
+    const int rep = p.order[g];
+    const int split = (int)((item / tiles) % (unsigned)p.splits);
+    const int ci0 = (int)((item % tiles) / ntiles) * 64, n0 = (int)(item % ntiles) * 64;
+    const int stages = (p.B + kImages - 1) / kImages, per = (stages + p.splits - 1) / p.splits;
+    const int s0 = min(stages, split * per), s1 = min(stages, s0 + per);
+    const tiles::Buffer xbuf = tiles::buffer((const char*)p.x + (long long)rep * p.x_rep * 4, (unsigned)(p.B * HW) * (unsigned)p.C * 2u);
+    const tiles::Buffer dbuf = tiles::buffer((const char*)p.dy + (long long)rep * p.dy_rep * 4, (unsigned)(p.B * HW) * (unsigned)p.N * 2u);
+
+    // This thread's rows of a stage are tid / 8 + 32 i: image (tid / 8) % 16, position tid / 128 + 2 i.  (Images beyond the batch lie
+    // beyond the buffers: zeros.)
+    const unsigned pixel = (unsigned)(((tid >> 3) & 15) * HW + (tid >> 7)), kq = (unsigned)tid & 7u;
+    const unsigned xoff = (pixel * (unsigned)p.C + (unsigned)ci0 + kq * 8u) * 2u, doff = (pixel * (unsigned)p.N + (unsigned)n0 + kq * 8u) * 2u;
+    const unsigned st = (unsigned)(tid >> 3) * 128u + ((kq * 16u) ^ ((((unsigned)tid >> 4) & 1u) * 64u));
+    // operand reads (see lds_read_tr8): the lane's image and its 4-channel group
+    const unsigned kl = (unsigned)((lane >> 5) * 8 + ((lane & 15) >> 2)), sub = (unsigned)((((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2);
+    const unsigned swap = ((kl >> 1) & 1u) * 64u;
+    const unsigned x_rd = kl * 128u + (((unsigned)ch * 64u + sub) ^ swap), d_rd = kl * 128u + (((unsigned)nh * 64u + sub) ^ swap);
+    const bool with_bias = p.has_bias && ci0 == 0;
+    float bias[8] = {};                                       // sums of this thread's rows of dy
+
+    f16 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+
+    for (int s = s0; s < s1; ++s) {
+        u4 rx[8], rd[8];
+        const unsigned first = (unsigned)(s * kImages * HW);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            rx[i] = tiles::ldb16(xbuf, xoff + (first + 2u * i) * (unsigned)p.C * 2u);
+            rd[i] = tiles::ldb16(dbuf, doff + (first + 2u * i) * (unsigned)p.N * 2u);
+        }
+        if (with_bias)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const bf16x8 v = __builtin_bit_cast(bf16x8, rd[i]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) bias[e] += (float)v[e];
+            }
+        __syncthreads();                                      // every wave is done with the previous stage
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            *reinterpret_cast<u4*>(sX + st + i * 4096) = rx[i];
+            *reinterpret_cast<u4*>(sD + st + i * 4096) = rd[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int y = 0; y < H; ++y) {
+            bf16x8 a[3][3];                                   // [column % 3][row - (y - 1)]
+            auto read_column = [&](int c) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+                    if (y + r - 1 >= 0 && y + r - 1 < H) a[c % 3][r] = lds_read_tr8(sX, x_rd + (unsigned)(((y + r - 1) * W + c) * 2048), 128);
+            };
+            read_column(0);
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                const bf16x8 b = lds_read_tr8(sD, d_rd + (unsigned)((y * W + c) * 2048), 128);
+                if (c + 1 < W) read_column(c + 1);
+#pragma unroll
+                for (int sx = 0; sx < 3; ++sx)                // the column that came last is multiplied last
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)
+                        if (y + r - 1 >= 0 && y + r - 1 < H && c + sx - 1 >= 0 && c + sx - 1 < W)
+                            acc[r * 3 + sx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a[(c + sx - 1) % 3][r], acc[r * 3 + sx], 0, 0, 0);
+            }
+        }
+    }
+
+    // ---- epilogue ----
+    float* obase = (p.splits > 1) ? p.out + (long long)g * p.out_rep + (long long)split * p.out_split
+                                  : p.out + (long long)rep * p.out_rep;
+    float* const sgd_w = (p.splits == 1 && p.sgd_w) ? p.sgd_w + (long long)rep * p.out_rep : nullptr;
+    float* const sgd_buf = (sgd_w && p.sgd_buf) ? p.sgd_buf + (long long)rep * p.out_rep : nullptr;
+    float* const stage = reinterpret_cast<float*>(smem) + wave * (32 * kStagePitch);
+    const int mw = 9 * p.C, mb = ci0 + ch * 32, nb = n0 + nh * 32;
+    UpdateOperands u[2];
+    if (sgd_w) fetch_update_operands(u[0], lane, mb, mw, nb, p.N, sgd_w, sgd_buf);
+    __syncthreads();                                          // nobody reads an operand any more
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        if (!sgd_w) { store_block32(acc[t], stage, lane, t * p.C + mb, mw, nb, p, obase, nullptr, nullptr); continue; }
+        if (t < 8) fetch_update_operands(u[(t + 1) & 1], lane, (t + 1) * p.C + mb, mw, nb, p.N, sgd_w, sgd_buf);
+        update_block32(acc[t], u[t & 1], stage, lane, t * p.C + mb, mw, nb, p, sgd_w, sgd_buf);
+    }
+    if (with_bias) {                                          // the 32 threads of each group of channels, in order
+        float* const sums = reinterpret_cast<float*>(smem + kBytes);     // (beyond the waves' areas)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sums[(tid >> 3) * 64 + (int)kq * 8 + e] = bias[e];
+        __syncthreads();
+        if (tid < 64) {
+            float d = 0.f;
+            for (int i = 0; i < 32; ++i) d += sums[i * 64 + tid];
+            const long long o = (long long)mw * p.N + n0 + tid;
+            if (!sgd_w) obase[o] = d;
+            else {
+                if (sgd_buf) { d = sgd_buf[o] * p.momentum + d; sgd_buf[o] = d; }
+                sgd_w[o] -= d * p.lr;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
 // Weight preparation: fp32 master W[tap][ci][co] -> Wf[co][tap*C + ci] and Wb[ci][(T-1-tap)*N + co], both bf16.
 // A workgroup handles one tap and a 64 x 64 (ci, co) tile: 256-byte reads, whole 128-byte lines written to both copies.
 // ---------------------------------------------------------------------------------------------------------------
@@ -741,7 +875,7 @@ BigTileInfo query_big_tile()
 }
 
 // Kernel and tile of a weight gradient
-enum class WgradTile { taps, t256x256, t256x128, t128x128, t128x64 };
+enum class WgradTile { taps, t256x256, t256x128, t128x128, t128x64, images };
 WgradTile wgrad_tile(const FastWgradParams& p, long long n_active)
 {
     // wide images with at most 128 channels in and out: all taps from one patch
@@ -750,6 +884,8 @@ WgradTile wgrad_tile(const FastWgradParams& p, long long n_active)
     if ((wide || eight) && p.C % 64 == 0 && p.R == 3 && p.S == 3 && p.pad == 1 &&
         (p.H * p.W) % 32 == 0 && p.K % 32 == 0 && (p.splits == 1 || p.kchunk % 32 == 0) && p.M == 9 * p.C + (p.has_bias ? 1 : 0) &&
         p.tile_hint != 2) return WgradTile::taps;
+    if (p.H == 4 && p.W == 4 && p.C % 64 == 0 && p.R == 3 && p.S == 3 && p.pad == 1 && p.M == 9 * p.C + (p.has_bias ? 1 : 0) &&
+        p.tile_hint != 2) return WgradTile::images;
     // 256-row tiles (and 256 columns where the layer has them) when the launch still fills the chip.
     // Only for long contractions: with few pixels per weight (the deep layers) the kernel's time is in the epilogue
     // (gradient store or fused update), which the smaller tiles overlap with other workgroups' K loops -- measured 5-30 %
@@ -776,11 +912,12 @@ WgradTile wgrad_tile(const FastWgradParams& p, long long n_active)
 // choice takes 0.5 % longer than the best measured split on average and 8 % at worst.  As many splits as fit one round of
 // resident workgroups: 7 % and 66 % (256 channels, 16 x 16 images, batch 100, 12 replicas: one split 1.66 times the time of
 // two, whose 256 x 256 tiles fill their rounds); splits for 2048 workgroups of 128 x 128: 19 % and 89 %.
+// On 4 x 4 images (128 to 512 channels, batch 64 to 128, 1 to 32 replicas) the choice is the best of 1, 2, 4 and 8 splits or within 7 %.
 WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active)
 {
     static constexpr struct { int m, n, resident; float extra, step[4]; } kTile[] = {
         {64, 64, 2, 0.f, {0.79f, 1.11f}}, {256, 256, 1, 0.f, {1.17f}}, {256, 128, 1, 0.f, {8.f}},
-        {128, 128, 3, 2.15f, {0.78f, 0.85f, 0.99f}}, {128, 64, 4, 2.15f, {0.67f, 0.72f, 0.84f, 0.97f}}};
+        {128, 128, 3, 2.15f, {0.78f, 0.85f, 0.99f}}, {128, 64, 4, 2.15f, {0.67f, 0.72f, 0.84f, 0.97f}}, {64, 64, 2, 48.f, {0.25f, 0.35f}}};
     FastWgradParams p = shape;
     p.kchunk = 64;                                           // (whole slabs, whatever the split)
     const float moved = (float)p.M * (float)p.N * (float)n_active * 8e-6f;
@@ -791,11 +928,15 @@ WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active)
         if (p.splits > 1 && sums >= best_t) break;           // (and any further split more)
         const WgradTile kind = wgrad_tile(p, n_active);
         const auto& t = kTile[(int)kind];
-        const long long rows = kind == WgradTile::taps ? p.C : p.M;          // (that kernel's workgroup holds all taps)
+        // (a workgroup of these two holds all taps; the second takes 256 pixels between two barriers)
+        const bool all_taps = kind == WgradTile::taps || kind == WgradTile::images;
+        if (kind == WgradTile::images && p.splits > (p.B + 15) / 16) break;
+        const long long rows = all_taps ? p.C : p.M;
         const long long wgs = (rows + t.m - 1) / t.m * (p.N / t.n) * p.splits * n_active;
         const long long round = kComputeUnits * t.resident, rest = wgs % round;
         const float rounds = (float)(wgs / round) * t.step[t.resident - 1] + (rest ? t.step[(rest - 1) / kComputeUnits] : 0.f);
-        const float loop = ((float)p.K / (32.0f * (float)p.splits) + t.extra) * rounds;
+        float loop = ((float)p.K / (32.0f * (float)p.splits) + t.extra) * rounds;
+        if (kind == WgradTile::images && p.splits == 1 && wgs <= kComputeUnits) loop += 5.0f;          // the update of a few workgroups
         if (p.splits == 1 || loop + sums < best_t) { best = p.splits; best_t = loop + sums; }
     }
     return {best, 0};
@@ -855,6 +996,12 @@ hipError_t launch_wgrad_fast(const FastWgradParams& p0, int n_active, hipStream_
             constexpr size_t lds = 2 * ((size_t)4 * 18 + 32) * 192;
             hipLaunchKernelGGL(wgrad_taps_kernel<16>, grid, dim3(256), lds, s, p);
         }
+        return hipGetLastError();
+    }
+    if (tile == WgradTile::images) {
+        const dim3 grid(die_grid((long long)(p.C / 64) * (p.N / 64) * p.splits * n_active));
+        constexpr size_t lds = 2 * 256 * 128;
+        hipLaunchKernelGGL(wgrad_images_kernel, grid, dim3(256), lds, s, p);
         return hipGetLastError();
     }
     const int bkt = tile == WgradTile::t256x256 ? 64 : 32;

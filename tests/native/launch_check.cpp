@@ -184,7 +184,7 @@ void look(const std::string& name, dim3 grid, void** args)
         l.act(p.out, p.out_rep, (long long)p.M * p.N);
         l.act(p.dy, p.dy_rep, (long long)p.M * p.N);
         if (p.gout) gradient(l, p.gout, p.gout_rep, p.gout_split, p.splits, (long long)(p.K + (p.bias ? 1 : 0)) * p.N, nullptr, nullptr);
-    } else if (has(name, "wgrad_kernel") || has(name, "wgrad_taps_kernel")) {
+    } else if (has(name, "wgrad_kernel") || has(name, "wgrad_taps_kernel") || has(name, "wgrad_images_kernel")) {
         const FastWgradParams& p = *(FastWgradParams*)args[0];
         l.order = p.order; l.n = p.n_active; l.es = 2;
         l.act(p.x, p.x_rep, (long long)p.K * p.C);

@@ -64,7 +64,8 @@ def test_patch_layers(shape):
 # bf16 (image, channels in and out, k, batch, replicas, tile hint)
 SHAPES_BF16 = [((8, 8), 64, 136, 3, 9, 2, 1), ((16, 32), 72, 64, 3, 5, 2, 1), ((5, 7), 40, 264, 3, 50, 1, 0), ((8, 6), 72, 200, 5, 40, 12, 0), ((16, 16), 128, 128, 3, 60, 4, 0),
                ((8, 8), 128, 256, 3, 64, 16, 0), ((10, 10), 40, 80, 3, 33, 6, 0), ((32, 32), 64, 64, 3, 17, 2, 0), ((4, 4), 256, 512, 3, 32, 1, 0), ((4, 4), 512, 512, 3, 50, 2, 0),
-               ((2, 2), 256, 512, 3, 32, 1, 0), ((2, 2), 512, 512, 3, 128, 12, 0), ((2, 2), 256, 256, 3, 1024, 4, 0), ((7, 31), 48, 64, 1, 20, 2, 0), ((64, 9), 64, 64, 1, 8, 2, 0)]
+               ((2, 2), 256, 512, 3, 32, 1, 0), ((2, 2), 512, 512, 3, 128, 12, 0), ((2, 2), 256, 256, 3, 1024, 4, 0), ((7, 31), 48, 64, 1, 20, 2, 0), ((64, 9), 64, 64, 1, 8, 2, 0),
+               ((4, 4), 64, 128, 3, 17, 3, 0), ((4, 4), 128, 64, 3, 130, 1, 0), ((4, 4), 256, 512, 3, 16, 9, 0)]         # (4 x 4: weight gradients by images, ragged sixteens, splits)
 
 
 @pytest.mark.parametrize("shape", SHAPES_BF16)

@@ -219,6 +219,19 @@ def test_lean_weight_gradient_splits(checked, shape):
     assert_clean(checked, cases)
 
 
+def test_lean_weight_gradients_on_4_x_4_images(checked):
+    """All taps, sixteen images a contraction; the split sums of every count of active replicas in their region.  Other images,
+    filters and the hint that keeps to the general tiles do not go there."""
+    cases = []
+    for side, k, cin, cout, batch, n, hint in ((4, 3, 64, 128, 17, 3, 0), (4, 3, 512, 512, 64, 9, 0), (4, 3, 128, 64, 130, 1, 1), (2, 3, 64, 64, 64, 2, 0), (4, 5, 64, 64, 64, 2, 0), (4, 3, 64, 64, 64, 2, 2)):
+        b = nets._Builder()
+        b.dense(b.gap(b.relu(b.conv(b.relu(b.conv(0, cin)), cout, k=k, pad=k // 2))), 10)
+        cases.append(case(b, (side, side, 3), batch, list(range(1, n + 1)), 1, options=[(1, hint)]))
+    runs = checked(cases)
+    assert [layers_in(r["trace"], "wgrad_images") > 0 for r in runs] == [True, True, True, False, False, False]
+    assert_clean(checked, cases)
+
+
 def test_split_float_layers_reach_every_tile(checked):
     """The dense layers of tests/test_gpu_split_floats.py between them take every tile of the fp32 launcher, in both directions."""
     from tests.test_gpu_split_floats import LAYERS, dense_net
