@@ -340,6 +340,7 @@ hadfl_status hadfl_init_replicas(const hadfl_config* cfg, const void* w0_dev, vo
     ctx->tb.cursor = (long long*)(b + c.cursor);
     ctx->tb.loss = (float*)(b + c.loss);
     ctx->steps_d = (int32_t*)(b + c.steps);
+    ctx->tb.steps = ctx->steps_d;
     ctx->selected = (int32_t*)(b + c.selected);
     ctx->sel_sorted = (int32_t*)(b + c.sel_sorted);
     ctx->sel_weight = (float*)(b + c.sel_weight);

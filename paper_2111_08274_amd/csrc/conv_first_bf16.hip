@@ -26,7 +26,7 @@ constexpr int WP = 40;              // LDS pitch of a weight row in bf16 element
 // first sample row of the replica's current batch inside the data set
 __device__ __forceinline__ const float* batch_base(const FirstConvParams& p, int rep)
 {
-    const long long first = (p.cursor[rep] * (long long)p.B) % p.n_samples;
+    const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.B) % p.n_samples;
     return p.x + ((long long)rep * p.n_samples + first) * (long long)(p.H * p.W * p.C);
 }
 

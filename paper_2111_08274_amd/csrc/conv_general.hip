@@ -119,7 +119,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, WGM * WGN * KG == 4 ? 2 : WGM 
     if (m0 >= M) return;
     const char* abase = (const char*)(p.a + (long long)rep * p.a_rep);
     if constexpr (GATHER) {                           // the batch inside the data set
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.batch) % p.n_samples;
         abase = (const char*)(p.a + ((long long)rep * p.n_samples + first) * p.sample_sz);
     }
     const char* wbase = (const char*)(p.wmat + (long long)rep * p.wmat_rep);
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_genera
     const int kbeg = split * p.kchunk, kend = min(p.K, kbeg + p.kchunk);
     const char* xbase;
     if (p.cursor) {
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.batch) % p.n_samples;
         xbase = (const char*)(p.x + ((long long)rep * p.n_samples + first) * p.sample_sz);
     } else {
         xbase = (const char*)(p.x + (long long)rep * p.x_rep);

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(GemmParams p)
     // activation-side base for this replica (the data set is indexed through the batch cursor)
     const float* abase;
     if (p.cursor) {
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.batch) % p.n_samples;
         abase = p.a + ((long long)rep * p.n_samples + first) * p.sample_sz;
     } else {
         abase = p.a + (long long)rep * p.a_rep;

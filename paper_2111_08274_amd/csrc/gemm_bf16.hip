@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_bf16_kernel(GemmParams p)
 
     const char* abase;
     if (p.cursor) {
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.batch) % p.n_samples;
         abase = (const char*)p.a + ((long long)rep * p.n_samples + first) * p.sample_sz * 4;     // the data set is fp32
     } else {
         abase = (const char*)p.a + (long long)rep * p.a_rep * 4;

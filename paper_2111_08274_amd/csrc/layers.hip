@@ -1087,6 +1087,20 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_bwd_kernel(BnParams 
     }
 }
 
+// Loss of one sample and d(loss)/d(logits), n_classes values through `value` and `store`
+template <typename V, typename S>
+__device__ __forceinline__ float softmax_row(int n_classes, int batch, int label, V&& value, S&& store)
+{
+    float m = value(0);
+    for (int j = 1; j < n_classes; ++j) m = fmaxf(m, value(j));
+    float s = 0.f;
+    for (int j = 0; j < n_classes; ++j) s += expf(value(j) - m);
+    const float li = (logf(s) + m - value(label)) / (float)batch;
+    const float inv = 1.0f / s;
+    for (int j = 0; j < n_classes; ++j) store(j, (expf(value(j) - m) * inv - (j == label ? 1.f : 0.f)) / (float)batch);
+    return li;
+}
+
 // One workgroup per replica, one thread per sample: softmax, loss, d(loss)/d(logits); loss summed by an LDS tree.
 template <typename T>
 __global__ __launch_bounds__(1024) void softmax_ce_kernel(LossParams p)
@@ -1096,18 +1110,11 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(LossParams p)
     const int b = threadIdx.x;
     float li = 0.f;
     if (b < p.batch) {
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.batch) % p.n_samples;
         const int label = p.y[(long long)rep * p.n_samples + first + b];
         const T* z = tptr<T>(p.logits, rep, p.logits_rep) + (long long)b * p.n_classes;
         T* dz = tptr<T>(p.dlogits, rep, p.dlogits_rep) + (long long)b * p.n_classes;
-        float m = ldf(z, 0);
-        for (int j = 1; j < p.n_classes; ++j) m = fmaxf(m, ldf(z, j));
-        float s = 0.f;
-        for (int j = 0; j < p.n_classes; ++j) s += expf(ldf(z, j) - m);
-        li = (logf(s) + m - ldf(z, label)) / (float)p.batch;
-        const float inv = 1.0f / s;
-        for (int j = 0; j < p.n_classes; ++j)
-            stf(dz, j, (expf(ldf(z, j) - m) * inv - (j == label ? 1.f : 0.f)) / (float)p.batch);
+        li = softmax_row(p.n_classes, p.batch, label, [&](int j) { return ldf(z, j); }, [&](int j, float d) { stf(dz, j, d); });
     }
     red[b] = li;
     __syncthreads();
@@ -1137,7 +1144,11 @@ __global__ __launch_bounds__(256) void sgd_kernel(SgdParams p)
         if (buf) { d = *reinterpret_cast<const f4*>(buf + o) * p.momentum + d; *reinterpret_cast<f4*>(buf + o) = d; }
         *reinterpret_cast<f4*>(w + o) = *reinterpret_cast<const f4*>(w + o) - d * p.lr;
     }
-    if (p.bump && blockIdx.x == 0 && threadIdx.x == 0) { p.cursor[rep] += 1; p.versions[rep] += 1; }
+}
+
+__global__ __launch_bounds__(256) void advance_kernel(const int* steps, int* versions, long long* cursor, int n)
+{
+    for (int k = gtid(); k < n; k += gstride()) { versions[k] = steps[k]; cursor[k] += steps[k]; }
 }
 
 // Narrow dense layer (the classifier: out <= 16): one workgroup per sample row; threads stride over the input
@@ -1195,7 +1206,7 @@ __global__ __launch_bounds__(1024) void dense_rows_fwd_kernel(DenseRowsParams p)
     const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32, m = m0 + (lane & 31), n = n0 + (lane & 31);
     const SRC* x;
     if (p.cursor) {
-        const long long first = (p.cursor[rep] * (long long)p.batch) % p.n_samples;
+        const long long first = ((p.cursor[rep] + p.ahead) * (long long)p.batch) % p.n_samples;
         x = reinterpret_cast<const SRC*>(p.x) + ((long long)rep * p.n_samples + first) * p.K;
     } else {
         x = tptr<SRC>(p.x, rep, p.x_rep);
@@ -1246,12 +1257,15 @@ __global__ __launch_bounds__(1024) void dense_rows_fwd_kernel(DenseRowsParams p)
 // sample: the lane keeps the feature's weights and its N partial gradients in registers, the samples' dY rows come from LDS at
 // a wave-uniform address.  The four waves' partial gradients are added in wave order, and since no other workgroup reads
 // these features' weights, the update (buf = momentum*buf + g; w -= lr*buf) follows on the spot.
+// The classifier of a network also forms its dY, the gradient of the softmax cross-entropy, a thread per sample: again in every
+// workgroup, some 2 us where a launch of its own (softmax_ce_kernel) takes 6, and its reader waits for it.
 template <int NMAX, typename T>
 __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p)
 {
-    constexpr int ROWS = 64;                      // samples staged at a time
+    constexpr int ROWS = 256;                     // samples staged at a time
     __shared__ __attribute__((aligned(16))) float sdy[ROWS][NMAX];
     __shared__ float red[4][64][NMAX + 1];
+    __shared__ float losses[256];
     __shared__ float redb[4][NMAX];
     const int rep = p.order[blockIdx.y];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1274,9 +1288,26 @@ __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p
     for (int r0 = 0; r0 < p.rows; r0 += ROWS) {
         const int nr = min(ROWS, p.rows - r0);
         __syncthreads();
-        for (int i = threadIdx.x; i < ROWS * NMAX; i += 256) {
-            const int r = i / NMAX, n = i % NMAX;
-            sdy[r][n] = r < nr && n < p.N ? ldf(dy, (long long)(r0 + r) * p.N + n) : 0.f;
+        if (p.criterion.loss) {                   // (the launcher checks that there is one round, and n_classes = N)
+            const LossParams& c = p.criterion;
+            const int r = threadIdx.x;
+            float li = 0.f;
+            if (r < nr) {
+                const long long first = ((c.cursor[rep] + c.ahead) * (long long)c.batch) % c.n_samples;
+                const int label = c.y[(long long)rep * c.n_samples + first + r];
+                const T* z = tptr<T>(c.logits, rep, c.logits_rep) + (long long)r * p.N;
+                float* const row = sdy[r];
+#pragma unroll
+                for (int n = 0; n < NMAX; ++n) row[n] = n < p.N ? ldf(z, n) : 0.f;
+                // a value is read for the last time before its place takes the gradient (rounded as it would be stored)
+                li = softmax_row(p.N, c.batch, label, [&](int j) { return row[j]; }, [&](int j, float d) { row[j] = (float)(T)d; });
+            }
+            losses[threadIdx.x] = li;
+        } else {
+            for (int i = threadIdx.x; i < nr * NMAX; i += 256) {
+                const int r = i / NMAX, n = i % NMAX;
+                sdy[r][n] = n < p.N ? ldf(dy, (long long)(r0 + r) * p.N + n) : 0.f;
+            }
         }
         __syncthreads();
 #pragma unroll 4
@@ -1302,6 +1333,13 @@ __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p
     for (int n = 0; n < NMAX; ++n) red[wave][lane][n] = acc[n];
     if (lane < NMAX) redb[wave][lane] = accb;
     __syncthreads();
+    if (p.criterion.loss && blockIdx.x == 0) {    // (the order of softmax_ce_kernel)
+        for (int i = 128; i > 0; i >>= 1) {
+            if ((int)threadIdx.x < i) losses[threadIdx.x] += losses[threadIdx.x + i];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) p.criterion.loss[rep] = losses[0];
+    }
     const int cnt = min(64, p.K - k0) * p.N;
     for (int i = threadIdx.x; i < cnt; i += 256) {
         const int kk = i / p.N, n = i - kk * p.N;
@@ -1406,7 +1444,7 @@ hipError_t launch_dense_rows_fwd(const DenseRowsParams& p, int n_active, hipStre
 hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipStream_t s)
 {
     if (n_active < 1 || p.rows < 1) return hipSuccess;
-    if (p.N > 16) return hipErrorInvalidValue;
+    if (p.N > 16 || (p.criterion.loss && (p.rows > 256 || p.criterion.batch != p.rows || p.criterion.n_classes != p.N))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((p.K + 63) / 64), (unsigned)n_active);
     if (p.bf16) hipLaunchKernelGGL((dense_small_bwd_kernel<16, __bf16>), grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((dense_small_bwd_kernel<16, float>), grid, dim3(256), 0, s, p);
@@ -1535,7 +1573,14 @@ hipError_t launch_sgd(const SgdParams& p, int n_active, hipStream_t s)
         if (p.count[k] % 4 != 0 || p.first[k] % 4 != 0 || p.count[k] < 0) return hipErrorInvalidValue;
         n4 += p.count[k] / 4;
     }
-    hipLaunchKernelGGL(sgd_kernel, ew_grid(n4 > 0 ? n4 : 1, n_active), dim3(256), 0, s, p);
+    if (n4 < 1) return hipSuccess;
+    hipLaunchKernelGGL(sgd_kernel, ew_grid(n4, n_active), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_advance(const int* steps, int* versions, long long* cursor, int n, hipStream_t s)
+{
+    hipLaunchKernelGGL(advance_kernel, dim3((unsigned)std::min((n + 255) / 256, 64)), dim3(256), 0, s, steps, versions, cursor, n);
     return hipGetLastError();
 }
 

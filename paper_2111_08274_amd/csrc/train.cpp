@@ -524,6 +524,7 @@ struct Runner {
     hipStream_t s;
     Profiler* prof;
     int na = 0;
+    int step = 0;                         // steps of this call before the present one
     int cur_layer = -1;
     hipError_t rc = hipSuccess;
     const char* failed = nullptr;
@@ -712,7 +713,7 @@ struct Runner {
             p.mode = kFwd;
             p.M = (int)(B * p.Ho * p.Wo); p.N = p.Cout; p.K = p.R * p.S * p.Cin;
             p.a = act(l.in0); p.a_rep = e.rep_block;
-            p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr;
+            p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr; p.ahead = step;
             p.a_f32 = l.in0 == 0;
             p.out = actw(ot); p.out_rep = e.rep_block;
             p.relu = e.fused_relu[i];
@@ -727,7 +728,7 @@ struct Runner {
             const bool rows_layer = dense_rows_layer(e.cfg, e.plan, l);
             if (rows_layer && dense_rows_pays(e.cfg, e.plan, l, na)) {
                 DenseRowsParams d{};
-                d.x = act(l.in0); d.x_rep = e.rep_block; d.cursor = p.cursor; d.n_samples = p.n_samples; d.batch = p.batch;
+                d.x = act(l.in0); d.x_rep = e.rep_block; d.cursor = p.cursor; d.ahead = p.ahead; d.n_samples = p.n_samples; d.batch = p.batch;
                 d.w = p.w; d.w_rep = p.w_rep; d.out = actw(ot); d.out_rep = e.rep_block;
                 d.rows = (int)B; d.K = p.Cin; d.N = l.cout; d.has_bias = l.bias; d.relu = p.relu; d.bf16 = e.cfg.bf16; d.order = e.buf.order;
                 run("dense_fwd", gemm_flops(p), gemm_bytes(p), [&] { return launch_dense_rows_fwd(d, na, s); });
@@ -754,7 +755,7 @@ struct Runner {
             if (e.general[i] && !rows_layer) {
                 GeneralConvParams f = general_base(i, p);
                 f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.pad = p.pad; f.sstride = p.stride;
-                f.a = act(l.in0); f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz;
+                f.a = act(l.in0); f.cursor = p.cursor; f.ahead = p.ahead; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz;
                 f.wmat = wbf() + e.wf_off[i];
                 f.out = actw(ot);
                 f.bias = l.bias && !bias_left_out(i) ? e.buf.replicas + l.b_off : nullptr; f.bias_rep = e.plan.row_stride;
@@ -832,7 +833,7 @@ struct Runner {
         const TensorShape a = e.plan.tensors[0], r = e.plan.tensors[l.out];
         if (r.h != a.h || r.w != a.w) return false;
         f = FirstConvParams{};
-        f.x = e.buf.x; f.cursor = e.buf.cursor; f.n_samples = e.cfg.n_samples;
+        f.x = e.buf.x; f.cursor = e.buf.cursor; f.ahead = step; f.n_samples = e.cfg.n_samples;
         f.B = e.cfg.batch; f.H = a.h; f.W = a.w; f.C = a.c; f.N = l.cout; f.R = f.S = l.k; f.pad = l.pad;
         f.K = l.k * l.k * a.c; f.M = e.cfg.batch * a.h * a.w;
         f.w = e.buf.replicas + l.w_off; f.w_rep = e.plan.row_stride;
@@ -857,6 +858,24 @@ struct Runner {
         b.partial_rep = (long long)b.chunks * 2 * a.c; b.partial = bn_shared(b.partial_rep, -1);
         b.order = e.buf.order; b.bf16 = e.cfg.bf16;
         return b;
+    }
+
+    LossParams criterion() const
+    {
+        const int T = (int)e.plan.tensors.size();
+        LossParams lp{};
+        lp.logits = act(T - 1); lp.logits_rep = e.rep_block;
+        lp.dlogits = grad(T - 1); lp.dlogits_rep = e.rep_block;
+        lp.y = e.buf.y; lp.cursor = e.buf.cursor; lp.ahead = step; lp.n_samples = e.cfg.n_samples; lp.batch = e.cfg.batch;
+        lp.n_classes = e.cfg.n_classes; lp.loss = e.buf.loss; lp.order = e.buf.order; lp.bf16 = e.cfg.bf16;
+        return lp;
+    }
+    // The last layer is a classifier whose backward kernel forms the gradient of the loss itself
+    bool forms_criterion(size_t i) const
+    {
+        const Layer& l = e.plan.layers[i];
+        return i + 1 == e.plan.layers.size() && e.fused_update[i] && dense_one_pass_bwd(e.cfg, e.plan, l) && e.out_tensor[i] == (int)e.plan.tensors.size() - 1 &&
+               l.cout == e.cfg.n_classes;
     }
 
     // Data gradient d of layer i, which is the whole gradient of a batch norm's output: it leaves that batch norm's sums.  Returns
@@ -897,13 +916,14 @@ struct Runner {
                 d.dy = grad(ot); d.dy_rep = e.rep_block; d.dx = grad(l.in0); d.dx_rep = e.rep_block;
                 d.mask = mask0; d.mask_rep = e.rep_block; d.accumulate = acc0;
                 d.buf = e.buf.mom ? e.buf.mom + l.w_off : nullptr; d.lr = e.cfg.lr; d.momentum = e.cfg.momentum;
+                if (forms_criterion(i)) d.criterion = criterion();
                 run("dense_small_bwd", 2.0 * gemm_flops(p), 2.0 * gemm_bytes(p), [&] { return launch_dense_small_bwd(d, na, s); });
                 break;
             }
             p.mode = kWgrad;
             p.M = p.R * p.S * p.Cin + (l.bias ? 1 : 0); p.N = p.Cout; p.K = (int)(B * p.Ho * p.Wo);
             p.a = act(l.in0); p.a_rep = e.rep_block;
-            p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr;
+            p.cursor = l.in0 == 0 ? e.buf.cursor : nullptr; p.ahead = step;
             p.a_f32 = l.in0 == 0;
             p.dy = grad(ot); p.dy_rep = e.rep_block;
             const WgradPlan wgrad = e.wgrad_plans[i].empty() ? WgradPlan{e.splits[i], 0} : e.wgrad_plans[i][na - 1];
@@ -946,7 +966,7 @@ struct Runner {
                 f.B = p.B; f.H = p.H; f.W = p.W; f.C = p.Cin; f.Ho = p.Ho; f.Wo = p.Wo; f.N = p.Cout; f.R = p.R; f.S = p.S; f.pad = p.pad;
                 f.stride = p.stride; f.K = p.K; f.kchunk = p.kchunk; f.splits = p.splits; f.small_tiles = wgrad.small_tiles; f.has_bias = l.bias;
                 f.x = act(l.in0); f.x_rep = e.rep_block; f.dy = grad(ot); f.dy_rep = e.rep_block;
-                f.cursor = p.cursor; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz; f.gather = gather_layer(e.cfg, l);
+                f.cursor = p.cursor; f.ahead = p.ahead; f.n_samples = p.n_samples; f.batch = p.batch; f.sample_sz = p.sample_sz; f.gather = gather_layer(e.cfg, l);
                 f.out = p.out; f.out_rep = p.out_rep; f.out_split = p.out_split; f.order = e.buf.order;
                 if (p.H * p.W <= kMaxTablePositionsWgrad) { f.perm = perm(i); f.posmask = posmask(i); }
                 if (e.fused_update[i]) {
@@ -1056,7 +1076,6 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
 {
     Runner r{*e, s, (prof && prof->on) ? prof : nullptr};
     const int N = e->cfg.n_replicas;
-    r.run("zero_versions", 0, 0, [&] { return launch_fill_u32((uint32_t*)e->buf.versions, 0u, N, s); });
     if (!e->tables_uploaded && !e->tables.empty()) {
         const hipError_t rc = hipMemcpyAsync(e->buf.work + e->tab_off, e->tables.data(), e->tables.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
         if (rc != hipSuccess) { err = std::string("copy position tables: ") + hipGetErrorString(rc); return HADFL_EDEVICE; }
@@ -1072,15 +1091,13 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
     const int T = (int)e->plan.tensors.size();
     e->prepped.assign(e->plan.layers.size(), 0);       // the weights may have changed since the last call (aggregation)
     for (int step = 0; step < e->e_max && r.rc == hipSuccess; ++step) {
-        r.na = e->n_active[step];
+        r.na = e->n_active[step]; r.step = step;
         r.prepare_weights();
         for (size_t i = 0; i < e->plan.layers.size(); ++i) r.forward_layer(i);
-        LossParams lp{};
-        lp.logits = r.act(T - 1); lp.logits_rep = e->rep_block;
-        lp.dlogits = r.grad(T - 1); lp.dlogits_rep = e->rep_block;
-        lp.y = e->buf.y; lp.cursor = e->buf.cursor; lp.n_samples = e->cfg.n_samples; lp.batch = e->cfg.batch;
-        lp.n_classes = e->cfg.n_classes; lp.loss = e->buf.loss; lp.order = e->buf.order; lp.bf16 = e->cfg.bf16;
-        r.run("softmax_ce", 0, r.asz() * 8.0 * e->cfg.batch * e->cfg.n_classes, [&] { return launch_softmax_ce(lp, r.na, s); });
+        if (!r.forms_criterion(e->plan.layers.size() - 1)) {
+            const LossParams lp = r.criterion();
+            r.run("softmax_ce", 0, r.asz() * 8.0 * e->cfg.batch * e->cfg.n_classes, [&] { return launch_softmax_ce(lp, r.na, s); });
+        }
         e->grad_written.assign(T, 0);
         e->grad_written[T - 1] = 1;
         r.na_next = step + 1 < e->e_max ? e->n_active[step + 1] : 0;
@@ -1090,12 +1107,11 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
         SgdParams sp{};
         sp.w = e->buf.replicas; sp.g = e->buf.grad; sp.buf = e->buf.mom; sp.row_stride = e->plan.row_stride;
         sp.lr = e->cfg.lr; sp.momentum = e->cfg.momentum;
-        sp.cursor = e->buf.cursor; sp.versions = e->buf.versions; sp.order = e->buf.order;
+        sp.order = e->buf.order;
         r.cur_layer = 0;
-        // the pieces of the row no weight-gradient kernel has updated already, several per launch; the last launch (there
-        // is always one) also advances the replicas' batch cursors and versions
+        // the pieces of the row no weight-gradient kernel has updated already, several per launch
         const size_t nseg = e->update_segments.size();
-        for (size_t k0 = 0; k0 < std::max<size_t>(nseg, 1); k0 += kMaxSgdSegments) {
+        for (size_t k0 = 0; k0 < nseg; k0 += kMaxSgdSegments) {
             const size_t k1 = std::min(nseg, k0 + kMaxSgdSegments);
             double floats = 0.0;
             sp.n_seg = (int)(k1 - k0);
@@ -1103,10 +1119,11 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
                 sp.first[k - k0] = e->update_segments[k].first; sp.count[k - k0] = e->update_segments[k].second;
                 floats += (double)e->update_segments[k].second;
             }
-            sp.bump = k1 == nseg;
             r.run("sgd", 0, (e->buf.mom ? 20.0 : 12.0) * floats, [&] { return launch_sgd(sp, r.na, s); });
         }
     }
+    // Every step read its batch at the cursor and the steps before it in this call; the cursors and versions advance once, here.
+    r.run("advance", 0, 24.0 * N / std::max(r.na, 1), [&] { return launch_advance(e->buf.steps, e->buf.versions, e->buf.cursor, N, s); });
     if (r.rc != hipSuccess) {
         err = std::string("kernel launch failed in ") + (r.failed ? r.failed : "?") + ": " + hipGetErrorString(r.rc);
         return HADFL_EDEVICE;

@@ -15,6 +15,7 @@ struct TrainBuffers {
     const float* x = nullptr;       // [N][n_samples][H][W][C]
     const int32_t* y = nullptr;     // [N][n_samples]
     int32_t* order = nullptr;       // [N] replica indices sorted by step count, descending
+    const int32_t* steps = nullptr; // [N] steps of a call
     int32_t* versions = nullptr;    // [N]
     long long* cursor = nullptr;     // [N] steps taken since init
     float* loss = nullptr;          // [N]

@@ -23,6 +23,7 @@ struct GemmParams {
     // activation-side source: X (fwd, wgrad) or dY (dgrad)
     const float* a; long long a_rep;
     const long long* cursor; int n_samples, batch; long long sample_sz;   // a is the data set when cursor != null
+    long long ahead;              // steps of this call so far: the cursor counts them at its end
     const float* w; long long w_rep;              // weights of this layer inside the replica rows
     const float* dy; long long dy_rep;            // kWgrad: dY
     float* out; long long out_rep, out_split;     // kWgrad with splits > 1: partial sums [g][split][M*N]
@@ -97,7 +98,7 @@ WgradPlan wgrad_fast_plan(const FastWgradParams& shape, int n_active);        //
 
 // ---- bf16 configuration, first convolution (fp32 data set in, few channels): conv_first_bf16.hip ----
 struct FirstConvParams {     // K = R*S*C footprint values per pixel (K + bias row <= 32), N = 32 or 64 output channels, stride 1
-    const float* x; const long long* cursor; int n_samples;     // data set [replica][n_samples][H][W][C] and batch cursors
+    const float* x; const long long* cursor; long long ahead; int n_samples;     // data set [replica][n_samples][H][W][C] and batch cursors (see GemmParams)
     int B, H, W, C, N, R, S, pad, K, M;                          // M = B*H*W pixels of a batch
     const float* w; long long w_rep;                             // fp32 weights [K][N] inside the replica rows (stride w_rep)
     const float* bias;                                           // inside the same rows, or null
@@ -128,7 +129,7 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     int ostride, wst, classes;                 // data gradient: stride, stride, stride^2; forward 1, 1, 1
     const float* a; long long a_rep;
     // forward of an fp32 convolution on the data set (a) when cursor != null: any C, the copy is [N][1][R*S*C]
-    const long long* cursor; int n_samples, batch; long long sample_sz;
+    const long long* cursor; int n_samples, batch; long long sample_sz, ahead;
     const __bf16* wmat; long long wmat_rep;    // weight copy, per-replica stride in 2-byte units
     float* out; long long out_rep;
     const float* bias; long long bias_rep;     // forward: bias inside the replica rows, or null
@@ -156,7 +157,7 @@ struct GeneralWgradParams {    // dW[(tap, ci)][co] over pixels, then (has_bias)
     int K, kchunk, splits, has_bias;           // K = B*Ho*Wo; kchunk a multiple of 32 when splits > 1
     int small_tiles;                           // of the plan the splits are from
     const float* x; long long x_rep;
-    const long long* cursor; int n_samples, batch; long long sample_sz;   // x is the (fp32) data set when cursor != null
+    const long long* cursor; int n_samples, batch; long long sample_sz, ahead;   // x is the (fp32) data set when cursor != null
     const float* dy; long long dy_rep;
     float* out; long long out_rep, out_split;
     const int* order;
@@ -182,9 +183,17 @@ struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (u
 };
 hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s);
 
+struct LossParams {
+    const float* logits; long long logits_rep;
+    float* dlogits; long long dlogits_rep;
+    const int* y; const long long* cursor; long long ahead; int n_samples, batch, n_classes;
+    float* loss;
+    int bf16;
+    const int* order;
+};
 struct DenseRowsParams {      // out[m][n] = sum_k x[m][k] w[k][n] + bias[n]
     const float* x; long long x_rep;
-    const long long* cursor; int n_samples, batch;    // x is the (fp32) data set when cursor != null
+    const long long* cursor; int n_samples, batch; long long ahead;    // x is the (fp32) data set when cursor != null
     const float* w; long long w_rep;     // weights [K][N] followed by bias [N]
     float* out; long long out_rep;
     int rows, K, N, has_bias, relu, bf16;
@@ -205,6 +214,9 @@ struct DenseSmallParams {     // dense layer with N <= 16 outputs.  Forward: out
     float* dx; long long dx_rep;
     const float* mask; long long mask_rep; int accumulate;
     float* buf; float lr, momentum;
+    // backward, optional (at most 256 rows): dy is the gradient of the softmax cross-entropy of this layer's output, formed here; the
+    // mean loss of every replica goes to loss
+    LossParams criterion;                 // (none: criterion.loss null)
 };
 hipError_t launch_dense_small_fwd(const DenseSmallParams& p, int n_active, hipStream_t s);
 hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipStream_t s);
@@ -273,26 +285,18 @@ struct BnParams {
 hipError_t launch_bn_fwd(const BnParams& p, int n_active, hipStream_t s);
 hipError_t launch_bn_bwd(const BnParams& p, int n_active, hipStream_t s);
 
-struct LossParams {
-    const float* logits; long long logits_rep;
-    float* dlogits; long long dlogits_rep;
-    const int* y; const long long* cursor; int n_samples, batch, n_classes;
-    float* loss;
-    int bf16;
-    const int* order;
-};
 hipError_t launch_softmax_ce(const LossParams& p, int n_active, hipStream_t s);
 
 constexpr int kMaxSgdSegments = 16;
 struct SgdParams {
     float* w; const float* g; float* buf; long long row_stride;
     float lr, momentum;
-    long long* cursor; int* versions;      // bumped once per replica per step (when bump is set)
-    int bump;
     // the launch covers n_seg pieces of each row: floats [first[k], first[k] + count[k]), all multiples of 4
     int n_seg; long long first[kMaxSgdSegments], count[kMaxSgdSegments];
     const int* order;
 };
 hipError_t launch_sgd(const SgdParams& p, int n_active, hipStream_t s);
+// versions[k] = steps[k], cursor[k] += steps[k]
+hipError_t launch_advance(const int* steps, int* versions, long long* cursor, int n, hipStream_t s);
 
 }  // namespace hadfl
