@@ -2,6 +2,7 @@
 // residual add, global average pool, batch normalisation (training mode), softmax cross-entropy and the fused
 // SGD/momentum update.  All reductions run in a fixed order (no floating-point atomics): results are repeatable.
 #include "train_kernels.h"
+#include "mfma_tiles.h"
 
 namespace hadfl {
 namespace {
@@ -1087,20 +1088,6 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_bwd_kernel(BnParams 
     }
 }
 
-// Loss of one sample and d(loss)/d(logits), n_classes values through `value` and `store`
-template <typename V, typename S>
-__device__ __forceinline__ float softmax_row(int n_classes, int batch, int label, V&& value, S&& store)
-{
-    float m = value(0);
-    for (int j = 1; j < n_classes; ++j) m = fmaxf(m, value(j));
-    float s = 0.f;
-    for (int j = 0; j < n_classes; ++j) s += expf(value(j) - m);
-    const float li = (logf(s) + m - value(label)) / (float)batch;
-    const float inv = 1.0f / s;
-    for (int j = 0; j < n_classes; ++j) store(j, (expf(value(j) - m) * inv - (j == label ? 1.f : 0.f)) / (float)batch);
-    return li;
-}
-
 // One workgroup per replica, one thread per sample: softmax, loss, d(loss)/d(logits); loss summed by an LDS tree.
 template <typename T>
 __global__ __launch_bounds__(1024) void softmax_ce_kernel(LossParams p)
@@ -1114,7 +1101,14 @@ __global__ __launch_bounds__(1024) void softmax_ce_kernel(LossParams p)
         const int label = p.y[(long long)rep * p.n_samples + first + b];
         const T* z = tptr<T>(p.logits, rep, p.logits_rep) + (long long)b * p.n_classes;
         T* dz = tptr<T>(p.dlogits, rep, p.dlogits_rep) + (long long)b * p.n_classes;
-        li = softmax_row(p.n_classes, p.batch, label, [&](int j) { return ldf(z, j); }, [&](int j, float d) { stf(dz, j, d); });
+        float m = ldf(z, 0);
+        for (int j = 1; j < p.n_classes; ++j) m = fmaxf(m, ldf(z, j));
+        float s = 0.f;
+        for (int j = 0; j < p.n_classes; ++j) s += expf(ldf(z, j) - m);
+        li = (logf(s) + m - ldf(z, label)) / (float)p.batch;
+        const float inv = 1.0f / s;
+        for (int j = 0; j < p.n_classes; ++j)
+            stf(dz, j, (expf(ldf(z, j) - m) * inv - (j == label ? 1.f : 0.f)) / (float)p.batch);
     }
     red[b] = li;
     __syncthreads();
@@ -1211,30 +1205,56 @@ __global__ __launch_bounds__(1024) void dense_rows_fwd_kernel(DenseRowsParams p)
     } else {
         x = tptr<SRC>(p.x, rep, p.x_rep);
     }
-    x += (long long)m * p.K;
+    x += (long long)m0 * p.K;
     const float* const w = p.w + rep * p.w_rep;
     const bool m_ok = m < p.rows, n_ok = n < p.N, vec = p.K % 4 == 0;
     f16v acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll 4
-    for (int k8 = wave * 8; k8 < p.K; k8 += 128) {
-        const int k = k8 + 4 * h;
-        float a[4] = {0.f, 0.f, 0.f, 0.f}, b[4];
-        if (m_ok) {
-            if (vec) { if (k < p.K) { a[0] = ldf(x, k); a[1] = ldf(x, k + 1); a[2] = ldf(x, k + 2); a[3] = ldf(x, k + 3); } }
-            else {
+    // The loads of kAhead steps are in flight together: through buffer descriptors, which give zeros for what lies outside, there is no
+    // branch between them.
+    constexpr int kAhead = 8;
+    constexpr unsigned ES = sizeof(SRC), kAll = tiles::kOutside;
+    const unsigned xoff = ((unsigned)(lane & 31) * (unsigned)p.K + 4u * h) * ES, woff = (4u * h * (unsigned)p.N + (unsigned)n) * 4u;
+    for (int k8 = wave * 8; k8 < p.K; k8 += 128 * kAhead) {
+        float a[kAhead][4], b[kAhead][4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) if (k + e < p.K) a[e] = ldf(x, k + e);
+        for (int u = 0; u < kAhead; ++u) {
+            const int ku = k8 + 128 * u, k = ku + 4 * h;
+            if (ku >= p.K) break;
+            const tiles::Buffer xb = tiles::buffer(x + ku, kAll), wb = tiles::buffer(w + (long long)ku * p.N, kAll);
+            if (vec) {
+                const unsigned o = m_ok && k < p.K ? xoff : kAll;
+                if constexpr (sizeof(SRC) == 4) {
+                    const tiles::f4 v = __builtin_bit_cast(tiles::f4, tiles::ldb16(xb, o));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[u][e] = v[e];
+                } else {
+                    const tiles::bf16x4 v = __builtin_bit_cast(tiles::bf16x4, __builtin_amdgcn_raw_buffer_load_b64(xb, (int)o, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[u][e] = (float)v[e];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned o = m_ok && k + e < p.K ? xoff + e * ES : kAll;
+                    if constexpr (sizeof(SRC) == 4) a[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xb, (int)o, 0, 0));
+                    else a[u][e] = __builtin_bit_cast(float, (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(xb, (int)o, 0, 0) << 16);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                b[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wb, (int)(n_ok && k + e < p.K ? woff + (unsigned)(e * p.N) * 4u : kAll), 0, 0));
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (k8 + 128 * u >= p.K) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (kRound) { a[u][e] = (float)(__bf16)a[u][e]; b[u][e] = (float)(__bf16)b[u][e]; }
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][e], b[u][e], acc, 0, 0, 0);
             }
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            b[e] = n_ok && k + e < p.K ? w[(long long)(k + e) * p.N + n] : 0.f;
-            if (kRound) { a[e] = (float)(__bf16)a[e]; b[e] = (float)(__bf16)b[e]; }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
@@ -1285,6 +1305,30 @@ __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p
         wv[n] = on && n < p.N ? w[(long long)k * p.N + n] : 0.f;
         if (kRoundW) wv[n] = (float)(__bf16)wv[n];
     }
+    // The weights to update and the first of a wave's rows of x are on their way while dY is formed.  (A row or feature beyond the last
+    // is the last again.)
+    constexpr int kRows = 8, kMine = 64 * NMAX / 256;
+    const int cnt = min(64, p.K - k0) * p.N;
+    const long long u0 = (long long)k0 * p.N;
+    float wu[kMine], bu[kMine];
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+        const long long o = u0 + min((int)threadIdx.x + q * 256, cnt - 1);
+        wu[q] = w[o];
+        bu[q] = buf ? buf[o] : 0.f;
+    }
+    const int kc = min(k, p.K - 1);
+    float xv[kRows], mv[kRows], old[kRows];
+    auto load_rows = [&](int first) {                         // rows first + wave, first + wave + 4, ...
+#pragma unroll
+        for (int q = 0; q < kRows; ++q) {
+            const long long o = (long long)min(first + wave + 4 * q, p.rows - 1) * p.K + kc;
+            xv[q] = ldf(x, o);
+            mv[q] = !mask ? 1.f : mask == x ? xv[q] : ldf(mask, o);
+            old[q] = p.accumulate ? ldf(dx, o) : 0.f;
+        }
+    };
+    load_rows(0);
     for (int r0 = 0; r0 < p.rows; r0 += ROWS) {
         const int nr = min(ROWS, p.rows - r0);
         __syncthreads();
@@ -1296,11 +1340,24 @@ __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p
                 const long long first = ((c.cursor[rep] + c.ahead) * (long long)c.batch) % c.n_samples;
                 const int label = c.y[(long long)rep * c.n_samples + first + r];
                 const T* z = tptr<T>(c.logits, rep, c.logits_rep) + (long long)r * p.N;
-                float* const row = sdy[r];
+                // as in softmax_ce_kernel, in registers
+                float v[NMAX], m, sum = 0.f, own = 0.f;
 #pragma unroll
-                for (int n = 0; n < NMAX; ++n) row[n] = n < p.N ? ldf(z, n) : 0.f;
-                // a value is read for the last time before its place takes the gradient (rounded as it would be stored)
-                li = softmax_row(p.N, c.batch, label, [&](int j) { return row[j]; }, [&](int j, float d) { row[j] = (float)(T)d; });
+                for (int n = 0; n < NMAX; ++n) v[n] = ldf(z, min(n, p.N - 1));
+                m = v[0];
+#pragma unroll
+                for (int n = 1; n < NMAX; ++n) m = fmaxf(m, v[n]);           // (the last value again does not change it)
+#pragma unroll
+                for (int n = 0; n < NMAX; ++n) {
+                    if (n == label) own = v[n];
+                    v[n] = n < p.N ? expf(v[n] - m) : 0.f;
+                    sum += v[n];
+                }
+                li = (logf(sum) + m - own) / (float)c.batch;
+                const float inv = 1.0f / sum;
+#pragma unroll
+                for (int n = 0; n < NMAX; ++n)                               // rounded as it would be stored
+                    sdy[r][n] = n < p.N ? (float)(T)((v[n] * inv - (n == label ? 1.f : 0.f)) / (float)c.batch) : 0.f;
             }
             losses[threadIdx.x] = li;
         } else {
@@ -1310,20 +1367,20 @@ __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p
             }
         }
         __syncthreads();
-#pragma unroll 4
-        for (int r = wave; r < nr; r += 4) {
-            float g[NMAX];
+        for (int rb = 0; rb < nr; rb += 4 * kRows) {
+            if (r0 + rb > 0) load_rows(r0 + rb);
 #pragma unroll
-            for (int n = 0; n < NMAX; ++n) g[n] = sdy[r][n];
-            if (on) {
-                const long long o = (long long)(r0 + r) * p.K + k;
-                const float xv = ldf(x, o);
-                float d = 0.f;
+            for (int q = 0; q < kRows; ++q) {
+                const int r = rb + wave + 4 * q;
+                if (r >= nr) break;
+                float g[NMAX], d = 0.f;
 #pragma unroll
-                for (int n = 0; n < NMAX; ++n) { d += g[n] * wv[n]; acc[n] += xv * g[n]; }
-                if (mask && !(ldf(mask, o) > 0.f)) d = 0.f;
-                if (p.accumulate) d += ldf(dx, o);
-                stf(dx, o, d);
+                for (int n = 0; n < NMAX; ++n) g[n] = sdy[r][n];
+#pragma unroll
+                for (int n = 0; n < NMAX; ++n) { d += g[n] * wv[n]; acc[n] += xv[q] * g[n]; }
+                if (!(mv[q] > 0.f)) d = 0.f;
+                if (p.accumulate) d += old[q];
+                if (on) stf(dx, (long long)(r0 + r) * p.K + k, d);
             }
         }
         if (blockIdx.x == 0 && lane < NMAX)
@@ -1340,13 +1397,13 @@ __global__ __launch_bounds__(256) void dense_small_bwd_kernel(DenseSmallParams p
         }
         if (threadIdx.x == 0) p.criterion.loss[rep] = losses[0];
     }
-    const int cnt = min(64, p.K - k0) * p.N;
-    for (int i = threadIdx.x; i < cnt; i += 256) {
-        const int kk = i / p.N, n = i - kk * p.N;
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+        const int i = threadIdx.x + q * 256, kk = i / p.N, n = i - kk * p.N;
+        if (i >= cnt) break;
         float d = ((red[0][kk][n] + red[1][kk][n]) + red[2][kk][n]) + red[3][kk][n];
-        const long long o = (long long)k0 * p.N + i;
-        if (buf) { d = buf[o] * p.momentum + d; buf[o] = d; }
-        w[o] -= d * p.lr;
+        if (buf) { d = bu[q] * p.momentum + d; buf[u0 + i] = d; }
+        w[u0 + i] = wu[q] - d * p.lr;
     }
     if (blockIdx.x == 0 && p.has_bias && threadIdx.x < p.N) {
         const int n = threadIdx.x;

@@ -386,6 +386,11 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
     {
         e->fused_update.assign(plan.layers.size(), 0);
         int64_t pos = 0;
+        // (the padding between and behind the layers has neither gradient nor value: a piece of nothing else needs no update)
+        auto segment = [&](int64_t first, int64_t end) {
+            for (const Layer& l : plan.layers)
+                if (l.w_count > 0 && l.w_off < end && l.w_off + l.w_count > first) { e->update_segments.push_back({first, end - first}); return; }
+        };
         for (size_t i = 0; i < plan.layers.size(); ++i) {
             const Layer& l = plan.layers[i];
             if (l.type != HADFL_OP_CONV && l.type != HADFL_OP_DENSE) continue;
@@ -400,10 +405,10 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             if (small) cnt = (cnt + 3) / 4 * 4;                   // (padding behind the slice: nothing there is ever updated)
             if (l.w_off % 4 != 0 || cnt % 4 != 0 || l.w_off < pos || (l.bias && l.b_off != l.w_off + l.w_count)) continue;
             e->fused_update[i] = 1;
-            if (l.w_off > pos) e->update_segments.push_back({pos, l.w_off - pos});
+            segment(pos, l.w_off);
             pos = l.w_off + cnt;
         }
-        if (plan.train_end > pos) e->update_segments.push_back({pos, plan.train_end - pos});
+        segment(pos, plan.train_end);
     }
     e->tab_off = e->wbf_off + up64(L.wbf_rep * cfg.n_replicas / 2 + 64);
     e->tab_idx = L.tab_idx;
