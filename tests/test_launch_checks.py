@@ -158,6 +158,20 @@ def test_classifier_backward_route_by_batch(checked):
     assert_clean(checked, cases)
 
 
+def test_loss_gradient_by_the_classifier(checked):
+    """Formed in the classifier's backward kernel where that is one launch; a launch of its own otherwise.  A row whose pieces are all
+    updated elsewhere has no update launch, and cursors advance once a call."""
+    cases = []
+    for batch, classes, hidden in ((64, 10, 64), (256, 16, 64), (257, 10, 64), (64, 17, 64)):
+        b = nets._Builder()
+        b.dense(b.relu(b.dense(0, hidden)), classes)
+        cases.append(case(b, (1, 1, 32), batch, [2, 1], 0, classes=classes))
+    runs = checked(cases)
+    assert [layers_in(r["trace"], "softmax_ce") for r in runs] == [0, 0, 2, 2]
+    assert all(layers_in(r["trace"], "advance") == 1 for r in runs) and layers_in(runs[0]["trace"], "sgd_kernel") == 0
+    assert_clean(checked, cases)
+
+
 def test_wide_layer_on_the_data_set_by_launch_size(checked):
     """The few-rows kernel up to one and a half rounds of 128 x 128 tiles (bf16 with a short contraction: one), then generic tiles."""
     cases = []
