@@ -212,9 +212,15 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(BnParams p)
     }
 }
 
-__device__ __forceinline__ float bn_left_out(const BnParams& p, int rep, int c)
+// The bias that the convolution in front left out of its outputs; it belongs to the running mean.  An Inf or NaN
+// among the biases would have made the outputs NaN or Inf: then `mean` (of the outputs, shifted or not) becomes NaN,
+// and with it all that is normalised.
+__device__ __forceinline__ float bn_left_out(const BnParams& p, int rep, int c, float& mean)
 {
-    return p.left_out ? p.left_out[rep * p.left_out_rep + c] : 0.f;
+    if (!p.left_out) return 0.f;
+    const float bias = p.left_out[rep * p.left_out_rep + c];
+    mean += 0.f * (mean + bias);
+    return bias;
 }
 
 // y = gamma * (x - mean) * istd + beta; the blocks of chunk 0 also store mean / istd and update the running statistics
@@ -241,7 +247,7 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_kernel(BnParams p)
         sv[c] = mean; sv[p.C + c] = istd;
         const float unb = p.rows > 1 ? q / (float)(p.rows - 1) : var;
         float* rm = row + p.stat_off;
-        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + bn_left_out(p, rep, c));
+        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * mean;
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     }
     const int r0 = chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
@@ -640,14 +646,15 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
         // the shift the sums were taken with: the producing convolution's bias, or the tensor's first row
         const float x0 = p.stats_done ? (p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c] : 0.f)
                                       : ldf(tptr<T>(p.x, rep, p.x_rep), c);
-        const float md = s / n;                               // mean of the shifted values
+        float md = s / n;                                     // mean of the shifted values
+        const float left_out = bn_left_out(p, rep, c, md);
         const float cen = fmaxf(q - s * md, 0.f);             // sum of squared deviations from the mean
         const float mean = x0 + md, var = cen / n;
         float* sv = p.saved + rep * p.saved_rep;
         sv[c] = mean; sv[p.C + c] = 1.0f / sqrtf(var + kBnEps);
         const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
         float* rm = p.params + rep * p.row_stride + p.stat_off;
-        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + bn_left_out(p, rep, c));
+        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + left_out);
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     } else {
         if (p.bwd_stats_done && !direct) q = (q - beta * s) / gamma;
@@ -998,13 +1005,15 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {                           // as in bn_finalize_kernel<0>
         const int c = c0 + e;
-        const float md = t[e] / n, cen = fmaxf(t[VEC + e] - t[e] * md, 0.f), mean = x0[e] + md, var = cen / n, istd = 1.0f / sqrtf(var + kBnEps);
+        float md = t[e] / n;
+        const float left_out = bn_left_out(p, rep, c, md);
+        const float cen = fmaxf(t[VEC + e] - t[e] * md, 0.f), mean = x0[e] + md, var = cen / n, istd = 1.0f / sqrtf(var + kBnEps);
         if (rl == 0) {
             float* sv = p.saved + rep * p.saved_rep;
             sv[c] = mean; sv[p.C + c] = istd;
             const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
             float* rm = row + p.stat_off;
-            rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + bn_left_out(p, rep, c));
+            rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + left_out);
             rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
         }
         bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
@@ -1551,7 +1560,7 @@ hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
         }
         return hipGetLastError();
     }
-    if (p.pool || p.stats_done || p.add) return hipErrorInvalidValue;  // the caller asks for these only where the vector kernels apply
+    if (p.pool || p.stats_done || p.add || p.left_out) return hipErrorInvalidValue;  // the caller asks for these only where the vector kernels apply
     const dim3 grid((unsigned)(p.chunks * ((p.C + 63) / 64)), (unsigned)n_active);
     if (p.bf16) {
         hipLaunchKernelGGL((bn_reduce_kernel<0, __bf16>), grid, block, 0, s, p);

@@ -3,6 +3,7 @@ every step against the oracle."""
 import numpy as np
 import pytest
 
+from oracle import nets
 from tests import parity_metrics as pm
 from tests.pair import Pair
 from tests.test_launch_checks import first_norm, interleaved, pooled, pre_activation
@@ -32,3 +33,39 @@ def test_gradient_sums_of_a_lone_batch_norm_bf16(make, batch, replicas):
 def test_layers_between_a_convolution_and_its_batch_norm(ch, bf16):
     """Batch norms whose sums another layer's have replaced by the time they run form their own."""
     forced(interleaved(ch), (8, 8, 3), 32, 3, bf16)
+
+
+def biased(kind):
+    """A convolution with a bias in front of a batch norm of each kind: few values (one launch), many, and a pool folded in; from
+    patches, and strided."""
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, 40)))
+    t = b.bn(b.conv(t, 48, stride=2) if kind == "strided" else b.conv(t, 48))
+    t = b.relu(t)
+    b.dense(b.gap(b.maxpool(t) if kind == "pool" else t), 10)
+    return b
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("kind,side,batch,replicas", [("patch", 4, 8, 1), ("patch", 16, 64, 3), ("pool", 8, 32, 2), ("strided", 8, 16, 2), ("strided", 16, 64, 4)])
+def test_bias_that_is_not_finite(kind, side, batch, replicas, value):
+    """A bias of Inf or NaN in front of a batch norm reaches what the network as written makes it reach: after a step the same
+    parameters and running means are not finite as in the oracle (the library's variances are clamped at zero, NaN among them).
+    First layer and second, one channel."""
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((replicas, batch, side, side, 3)).astype(np.float32)
+    y = rng.integers(0, 10, size=(replicas, batch)).astype(np.int32)
+    for layer in (0, 1):
+        p = Pair(biased(kind).array(), (side, side, 3), replicas, 1, x, y, batch, 0.01, 0.9, [1] * replicas)
+        off, count = [(o, m) for o, m, what, _ in p.layout if what == "bias"][layer]
+        for k in range(replicas):
+            p.cpu.params[k][off + 3] = value
+        p.share_state()
+        p.gpu.local_steps()
+        p.cpu.local_steps()
+        for k in range(replicas):
+            got, want = np.isfinite(p.gpu.params(k)), np.isfinite(p.cpu.params[k])
+            differ = [(o, m, what) for o, m, what, _ in p.layout if what != "running_var" and (got[o:o + m] != want[o:o + m]).any()]
+            print(kind, side, batch, replicas, value, layer, "not finite: %d of %d" % ((~want).sum(), want.size), differ, flush=True)
+            assert not differ
+        p.close()
