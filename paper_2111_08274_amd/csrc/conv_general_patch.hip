@@ -447,6 +447,15 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
     }
 }
 
+constexpr int kMaxTile = 256;                        // pixels of the tallest tile
+
+// x / d as umulhi(x, inverse(d)), d > 1: inverse(d) d is 2^32 + e with e < d (0 for powers of two), which adds x e / (d 2^32) to the quotient,
+// less than the 1 / d that would take it to the next whole number while x e < 2^32.
+unsigned inverse(unsigned d) { return 0xffffffffu / d + 1u; }
+bool exact_quotients(unsigned d, unsigned long long largest) { return d > 1 && largest * ((unsigned long long)inverse(d) * d - (1ull << 32)) < 1ull << 32; }
+// Those of a pixel's number by the image and of its place in the image by the width
+bool exact_places(long long H, long long W) { return H * W < 1ll << 31 && exact_quotients((unsigned)(H * W), H * W - 1 + kMaxTile) && exact_quotients((unsigned)W, H * W - 1); }
+
 constexpr size_t kMaxLds = 159 * 1024;               // (__syncthreads_or has a little of its own)
 
 // LDS bytes of a launch with tiles of 32 TM WGM pixels, and the tile's border
@@ -467,10 +476,11 @@ hipError_t launch_t(GeneralConvParams& p, int n_active, hipStream_t s, int* stat
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds) == hipSuccess;
         if (!ok) return hipErrorInvalidValue;
     }
-    if (p.W < 2 || lds > kMaxLds || (BMT + 2 * p.halo) * Slab<T>::groups > Q * WGM * WGN * 64) return hipErrorInvalidValue;
+    static_assert(BMT <= kMaxTile, "");
+    if (!exact_places(p.H, p.W) || lds > kMaxLds || (BMT + 2 * p.halo) * Slab<T>::groups > Q * WGM * WGN * 64) return hipErrorInvalidValue;
     if (stat_rows) *stat_rows = BMT;
     p.tiles_m = (p.B * p.H * p.W + BMT - 1) / BMT;
-    p.inv_hw = 0xffffffffu / (unsigned)(p.H * p.W) + 1u; p.inv_w = 0xffffffffu / (unsigned)p.W + 1u;     // x / d for x d < 2^32, d > 1
+    p.inv_hw = inverse(p.H * p.W); p.inv_w = inverse(p.W);
     const dim3 grid(die_grid((long long)p.tiles_m * ((p.N + 32 * TN * WGN - 1) / (32 * TN * WGN)) * n_active)), block(WGM * WGN * KG * 64);
     hipLaunchKernelGGL((conv_general_patch_kernel<T, TM, WGM, WGN, KG, Q, D, EPI, SORTED, TN>), grid, block, lds, s, p);
     return hipGetLastError();
@@ -570,11 +580,12 @@ hipError_t launch_bf16(GeneralConvParams& p, int n_active, hipStream_t s, int* s
 // fp32: the patch of 128 pixels has room for 64 pixels of border on either side, 3 x 3 filters on images up to 63 pixels wide; layers of
 // up to 32 channels stay with conv_general_kernel, whose tiles have 32 columns.  1 x 1 filters have one tap for each patch: in fp32
 // conv_general_kernel, which splits as much there, keeps them; in bf16 they run here (64 channels, 32 x 32 images, batch 128, 16
-// replicas 152 -> 123 us forward, 282 -> 163 us data gradient against the kernels of conv_bf16_fast.hip).
+// replicas 152 -> 123 us forward, 282 -> 163 us data gradient against the kernels of conv_bf16_fast.hip).  Images of some 65 thousand pixels
+// and more whose quotients would not be exact stay with the earlier kernels.
 bool conv_patch_supported(int bf16, int H, int W, int C, int N, int k)
 {
     const int unit = bf16 ? 8 : 4, border = k / 2 * (W + 1);
-    return k % 2 == 1 && k * k <= 32 && (bf16 ? border <= kBorderBf16 : k > 1 && border <= 64) && W >= 2 && H * W >= 4 &&
+    return k % 2 == 1 && k * k <= 32 && (bf16 ? border <= kBorderBf16 : k > 1 && border <= 64) && (long long)H * W >= 4 && exact_places(H, W) &&
            C % unit == 0 && N % unit == 0 && std::min(C, N) > 32;
 }
 

@@ -20,6 +20,10 @@ SHAPES = [((8, 6), 36, 132, 3, 7, 1, 0), ((8, 6), 132, 36, 3, 33, 2, 1), ((5, 7)
           ((4, 4), 512, 512, 3, 64, 1, 0), ((2, 2), 512, 512, 3, 64, 1, 0), ((8, 8), 256, 256, 3, 64, 1, 0),
           ((7, 9), 64, 60, 3, 50, 40, 0), ((3, 2), 192, 128, 3, 37, 6, 0), ((17, 6), 116, 64, 3, 130, 3, 0), ((16, 16), 64, 64, 3, 72, 8, 0)]
 
+# tall images: the first of either list has too many pixels for the kernel's quotients (tests/test_launch_checks.py), the second has not
+TALL = [((1112, 60), 36, 40, 3, 1, 1, 0), ((1060, 60), 36, 40, 3, 1, 1, 0)]
+TALL_BF16 = [((2200, 31), 40, 48, 3, 1, 1, 0), ((2048, 32), 40, 48, 3, 1, 1, 0)]
+
 
 def net(c, n, k):
     b = nets._Builder()
@@ -30,10 +34,10 @@ def net(c, n, k):
     return b
 
 
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SHAPES + TALL)
 def test_patch_layers(shape):
     """Gradients of one step, read from the momentum buffers, against the same network in 64 bits.  Bound: the error of a sum of
-    K products in fp32, 2^-24 sqrt(K), K <= 4608 products and up to 16384 pixels, and as much again through each of two batch
+    K products in fp32, 2^-24 sqrt(K), K <= 4608 products and up to 66720 pixels, and as much again through each of two batch
     norms and a softmax: 3e-5 of a tensor's largest gradient (floored at 1e-3 of the largest of all).  Where a ReLU's input lies within that of zero its unit may open on one side and not on the other: up to a
     hundredth of a tensor's values (one filter and one column) may be off by 5e-3 for it."""
     (h, w), c, n, k, batch, replicas, hint = shape
@@ -68,7 +72,7 @@ SHAPES_BF16 = [((8, 8), 64, 136, 3, 9, 2, 1), ((16, 32), 72, 64, 3, 5, 2, 1), ((
                ((4, 4), 64, 128, 3, 17, 3, 0), ((4, 4), 128, 64, 3, 130, 1, 0), ((4, 4), 256, 512, 3, 16, 9, 0)]         # (4 x 4: weight gradients by images, ragged sixteens, splits)
 
 
-@pytest.mark.parametrize("shape", SHAPES_BF16)
+@pytest.mark.parametrize("shape", SHAPES_BF16 + TALL_BF16)
 def test_patch_layers_bf16(shape):
     """Gradients of one step against the same network in 64 bits, in the 2-norm of a tensor.  What roundings to bf16 do to a
     tensor (units within 2^-9 of zero that open on one side only, sums that nearly cancel) is measured on the 64-bit network: the

@@ -6,6 +6,7 @@ import random
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 from oracle import nets
@@ -296,6 +297,24 @@ def test_patch_layers_reach_every_tile_bf16(checked):
         b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(0, c))), n, k=k, stride=stride, pad=k // 2))), 5)
         out.append(case(b, (side, side, 3), 16, [1], 1, classes=5))
     assert all(layers_in(r["trace"], "general_patch") == 0 for r in checked(out))
+
+
+def test_patch_layers_only_where_their_quotients_are_exact(checked):
+    """The kernel divides a pixel's number by the image's size with a multiplication, umulhi(x, 2^32 / d rounded up): on images that it
+    takes, every quotient of a pixel in a tile (up to 256 beyond the image) is the true one.  Tall images on either side."""
+    from tests.test_gpu_patch_layers import TALL, TALL_BF16, net
+    rng = random.Random(1)
+    shapes = [(h, w, bf16) for bf16, tall in ((0, TALL), (1, TALL_BF16)) for (h, w), *_ in tall]
+    for bf16, widest in ((0, 63), (1, 32)):
+        shapes += [(rng.randint(900, 5000) * 32 // w, w, bf16) for w in (rng.randint(2, widest) for _ in range(12))] + [(2048, 32, bf16), (4096, 16, bf16)]
+    runs = checked([case(net(40, 48, 3), (h, w, 3), 1, [1], bf16, classes=5) for h, w, bf16 in shapes])
+    inside = [layers_in(r["trace"], "general_patch") for r in runs]
+    assert {0, 4} == set(inside) and all(r["status"] == 0 and r["report"] == "" for r in runs)
+    for (h, w, _), n in zip(shapes, inside):
+        x = np.arange(h * w + 256, dtype=np.uint64)
+        exact = all(np.array_equal((x * np.uint64(0xffffffff // d + 1)) >> np.uint64(32), x // np.uint64(d)) for d in (h * w, w))
+        assert exact or n == 0, (h, w)
+        assert n == 4 or h * w > 32768, (h, w)
 
 
 def test_weight_gradients_by_position(checked):
