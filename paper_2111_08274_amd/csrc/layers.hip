@@ -1497,9 +1497,13 @@ hipError_t launch_dense_small_fwd(const DenseSmallParams& p, int n_active, hipSt
     return hipGetLastError();
 }
 
+// Offsets of the rows of a workgroup from its first are 32-bit byte offsets, of floats at most, the last piece of the last row included.
+bool dense_rows_supported(int rows, long long K) { return ((std::min(rows, 32) - 1) * K + 8) * 4 <= tiles::kOutside; }
+
 hipError_t launch_dense_rows_fwd(const DenseRowsParams& p, int n_active, hipStream_t s)
 {
     if (n_active < 1 || p.rows < 1) return hipSuccess;
+    if (!dense_rows_supported(p.rows, p.K)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((p.rows + 31) / 32), (unsigned)((p.N + 31) / 32), (unsigned)n_active), block(1024);
     if (!p.bf16) hipLaunchKernelGGL((dense_rows_fwd_kernel<float, float>), grid, block, 0, s, p);
     else if (p.cursor) hipLaunchKernelGGL((dense_rows_fwd_kernel<__bf16, float>), grid, block, 0, s, p);

@@ -180,6 +180,7 @@ bool dense_one_pass_bwd(const hadfl_config& cfg, const NetPlan& plan, const Laye
 // would use.  Classifiers on long rows have a workgroup per row instead (see the kernels).
 bool dense_rows_layer(const hadfl_config& cfg, const NetPlan& plan, const Layer& l)
 {
+    if (!dense_rows_supported(cfg.batch, plan.tensors[l.in0].numel())) return false;
     if (one_chain_net(cfg, plan) || (l.in0 != 0 && plan.tensors[l.in0].numel() >= 2048)) return false;
     return l.type == HADFL_OP_DENSE && (l.cout <= 16 || l.in0 == 0) && (!l.bias || l.b_off == l.w_off + l.w_count);
 }

@@ -199,6 +199,7 @@ struct DenseRowsParams {      // out[m][n] = sum_k x[m][k] w[k][n] + bias[n]
     int rows, K, N, has_bias, relu, bf16;
     const int* order;
 };
+bool dense_rows_supported(int rows, long long K);
 hipError_t launch_dense_rows_fwd(const DenseRowsParams& p, int n_active, hipStream_t s);
 
 struct DenseSmallParams {     // dense layer with N <= 16 outputs.  Forward: out[m][n] = sum_k x[m][k] w[k][n] + bias[n].  Backward:

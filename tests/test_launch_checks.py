@@ -186,6 +186,19 @@ def test_wide_layer_on_the_data_set_by_launch_size(checked):
     assert_clean(checked, cases)
 
 
+def test_very_long_rows_on_the_data_set(checked):
+    """The few-rows kernel addresses up to 32 samples by 32-bit byte offsets from the first: longer ones stay in the generic kernels."""
+    cases = []
+    for features, batch in ((34636830, 32), (34636834, 32), (34636834, 31), (268435458, 4), (268435458, 5), (357913952, 4)):
+        b = nets._Builder()
+        b.dense(0, 2)
+        cases.append(case(b, (1, 1, features), batch, [1], 0, classes=2, momentum=0.0))
+    for c, inside in zip(cases, (1, 0, 1, 1, 0, 0)):
+        (run,) = checked([c])
+        assert layers_in(run["trace"], "dense_rows_fwd") == inside and layers_in(run["trace"], "igemm") == 2 - inside, (c["shape"], c["batch"])
+        assert run["status"] == 0 and run["report"] == "", run["report"]
+
+
 def test_convolutions_on_the_data_set_by_channels(checked):
     """fp32: gathered where the generic kernel would gather too (channels not in sixteens forward, not in fours or at most 32
     rows in the weight gradient)."""
