@@ -107,10 +107,11 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(GemmParams p)
     // three slabs ahead in registers instead of one: the whole pass 6 % slower.)
     // (The taps of a kDgrad class step back one source pixel each: y + pad - r is a multiple of the stride for all of them.)
     const int ntap = (MODE == kFwd) ? p.R * p.S : (p.Cout > 0 ? kend / p.Cout : 0), row_taps = (MODE == kFwd) ? p.S : max(d_ns, 1);
-    const bool by_mask = MODE != kWgrad && fastA && ntap <= 32;
+    const int ach = (MODE == kFwd) ? p.Cin : p.Cout, ah = (MODE == kFwd) ? p.H : p.Ho, aw = (MODE == kFwd) ? p.W : p.Wo;
+    const bool by_mask = MODE != kWgrad && fastA && ntap <= 32 &&
+                         ((long long)(ntap / row_taps - 1) * aw + row_taps) * ach < 1ll << 31;        // the offset is an int
     const float* a_row[NQA]; unsigned a_in[NQA];
     int next_r = 0, next_s = 0, next_c = 0;
-    const int ach = (MODE == kFwd) ? p.Cin : p.Cout, ah = (MODE == kFwd) ? p.H : p.Ho, aw = (MODE == kFwd) ? p.W : p.Wo;
     if (by_mask) {
         const int tap0 = kbeg / ach;
         next_c = kbeg - tap0 * ach; next_r = tap0 / row_taps; next_s = tap0 - next_r * row_taps;

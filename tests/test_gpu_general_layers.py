@@ -2,10 +2,11 @@
 and batches, each tile size of the launchers, and floats that bf16 cannot hold."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import nets
 from paper_2111_08274_amd import hadfl
-from tests import parity_metrics as pm
+from tests import parity_metrics as pm, torch_ref
 from tests.pair import Pair
 
 pytestmark = pytest.mark.gpu
@@ -199,3 +200,36 @@ def test_narrow_filters_of_many_taps_bf16(cin, cout, k):
     print(cin, cout, k, pm.show(w), flush=True)
     assert w["compared"] > 0 and p.max_rel_diff() <= 2e-2
     p.close()
+
+
+def test_image_rows_of_gibibytes():
+    """A filter's rows lie more than 2^31 values apart: three rows of 2^26 pixels with sixteen channels, of which a strided convolution
+    reads windows of 3 x 3.  Reference: the windows side by side, in 64 bits.  Sums of 16385 values in fp32, 2^-24 sqrt(16385), in
+    the average, the loss gradient behind it and the weight gradient: 3e-5 of the largest gradient of a tensor."""
+    width, step, classes = 2 ** 26 + 3, 4096, 3
+    n = (width - 3) // step + 1
+    b, c = nets._Builder(), nets._Builder()
+    for net, stride in ((b, step), (c, 3)):
+        net.dense(net.gap(net.conv(0, 4, stride=stride, pad=0)), classes)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x = torch.zeros(1, 1, 3, width, 16, device="cuda")
+    windows = torch.randn(3, n, 3, 16, device="cuda", generator=g) + 0.5
+    x[0, 0, :, :(n - 1) * step].view(3, n - 1, step, 16)[:, :, :3] = windows[:, :-1]
+    x[0, 0, :, (n - 1) * step:] = windows[:, -1]
+    y = np.ones((1, 1), dtype=np.int32)
+    w0 = (0.1 * np.random.default_rng(2).standard_normal(144 * 4 + 4 + 4 * classes + classes)).astype(np.float32)
+    cfg = hadfl.make_config(1, 1, net="custom", custom_ops=b.array()[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=1, n_samples=1, in_shape=(3, width, 16),
+                            n_classes=classes, lr=1e-30, momentum=0.5)
+    ctx = hadfl.Context(cfg, [1], w0=w0, x=x, y=y)
+    ctx.local_steps()
+    got = ctx.momentum(0).astype(np.float64)
+    ctx.close()
+    compact = windows.reshape(1, 3, 3 * n, 16).double().cpu().numpy().reshape(1, -1)
+    want = torch_ref.loss_grad(c.array(), (3, 3 * n, 16), w0.astype(np.float64), compact, y[0])[1]
+    at = 0
+    for size in (144 * 4, 4, 4 * classes, classes):
+        err = np.abs(got[at:at + size] - want[at:at + size]).max() / np.abs(want[at:at + size]).max()
+        print(size, "%.1e" % err, flush=True)
+        assert err <= 3e-5
+        at += size
