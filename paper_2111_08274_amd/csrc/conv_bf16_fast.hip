@@ -884,8 +884,10 @@ WgradTile wgrad_tile(const FastWgradParams& p, long long n_active)
     if ((wide || eight) && p.C % 64 == 0 && p.R == 3 && p.S == 3 && p.pad == 1 &&
         (p.H * p.W) % 32 == 0 && p.K % 32 == 0 && (p.splits == 1 || p.kchunk % 32 == 0) && p.M == 9 * p.C + (p.has_bias ? 1 : 0) &&
         p.tile_hint != 2) return WgradTile::taps;
+    // (offsets of the sixteen images of a stage, those beyond the batch among them, fit 32 bits)
+    const bool offsets = (long long)((p.B + 15) / 16) * 16 * 16 * std::max(p.C, p.N) * 2 < 1ll << 32;
     if (p.H == 4 && p.W == 4 && p.C % 64 == 0 && p.R == 3 && p.S == 3 && p.pad == 1 && p.M == 9 * p.C + (p.has_bias ? 1 : 0) &&
-        p.tile_hint != 2) return WgradTile::images;
+        offsets && p.tile_hint != 2) return WgradTile::images;
     // 256-row tiles (and 256 columns where the layer has them) when the launch still fills the chip.
     // Only for long contractions: with few pixels per weight (the deep layers) the kernel's time is in the epilogue
     // (gradient store or fused update), which the smaller tiles overlap with other workgroups' K loops -- measured 5-30 %

@@ -260,6 +260,20 @@ def test_lean_weight_gradients_on_4_x_4_images(checked):
     assert_clean(checked, cases)
 
 
+def test_lean_weight_gradients_of_nearly_4_gib(checked):
+    """The all-taps kernel of 4 x 4 images takes sixteen images at a time, those beyond the batch by offsets beyond the tensor: the
+    offsets have to fit 32 bits (1023 images would be 1024)."""
+    cases = []
+    for batch, cout in ((1008, 131072), (1023, 131072), (1024, 131008)):
+        b = nets._Builder()
+        b.dense(b.gap(b.conv(b.relu(b.conv(0, 64)), cout)), 2)
+        cases.append(case(b, (4, 4, 3), batch, [1], 1, classes=2, momentum=0.0))
+    for c, inside in zip(cases, (1, 0, 1)):
+        (run,) = checked([c])
+        assert layers_in(run["trace"], "wgrad_images") == inside and layers_in(run["trace"], "wgrad_kernel") == 1 - inside, c["batch"]
+        assert run["status"] == 0 and run["report"] == "", run["report"]
+
+
 def test_split_float_layers_reach_every_tile(checked):
     """The dense layers of tests/test_gpu_split_floats.py between them take every tile of the fp32 launcher, in both directions."""
     from tests.test_gpu_split_floats import LAYERS, dense_net
