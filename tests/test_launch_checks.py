@@ -270,7 +270,7 @@ def test_lean_weight_gradients_of_nearly_4_gib(checked):
         cases.append(case(b, (4, 4, 3), batch, [1], 1, classes=2, momentum=0.0))
     for c, inside in zip(cases, (1, 0, 1)):
         (run,) = checked([c])
-        assert layers_in(run["trace"], "wgrad_images") == inside and layers_in(run["trace"], "wgrad_kernel") == 1 - inside, c["batch"]
+        assert layers_in(run["trace"], "wgrad_images") == inside and layers_in(run["trace"], "12wgrad_kernel") == 1 - inside, c["batch"]
         assert run["status"] == 0 and run["report"] == "", run["report"]
 
 
