@@ -125,7 +125,7 @@ void conv_fast(Launch l, const FastConvParams& p, int rows)
     l.act(p.stat_y, p.stat_y_rep, p.stat ? (long long)p.M * p.N : 0);
     for (int g = 0; g < l.n; ++g) use(l.name, kCopy, p.wmat + l.order[g] * p.wmat_rep, (long long)p.N * p.K * 2);
     l.tensor(kParam, p.bias, p.bias_rep, p.N * 4);
-    if (p.perm) { use(l.name, kTable, p.perm, p.H * p.W * 4); use(l.name, kTable, p.posmask, p.H * p.W * 4); }
+    if (p.perm) { use(l.name, kTable, p.perm, p.H * p.W * 4); use(l.name, kTable, p.posmask, p.H * p.W * 4); g_trace += "(its_rows_sorted)\n"; }
     if (p.stat) l.sums(p.stat, p.stat_rep, (p.M + rows - 1) / rows, p.N, p.out);
 }
 
@@ -169,7 +169,6 @@ void look(const std::string& name, dim3 grid, void** args)
     Launch l{name, nullptr, 0, 4};
     const std::vector<int> t = ints_of(name);
     if (has(name, "conv_general_kernel") || has(name, "conv_general_patch_kernel")) conv_general(l, *(GeneralConvParams*)args[0], t);
-    else if (has(name, "conv_patch_kernel")) conv_fast(l, *(FastConvParams*)args[0], t.back());
     else if (has(name, "11conv_kernel")) conv_fast(l, *(FastConvParams*)args[0], t[0]);
     else if (has(name, "wgrad_general_kernel") || has(name, "wgrad_general_position_kernel")) {
         const GeneralWgradParams& p = *(GeneralWgradParams*)args[0];
@@ -256,7 +255,7 @@ void check_reset(const unsigned long long* bufs, int n)
     for (int i = 0; i < n; ++i) g_bufs.push_back({bufs[2 * i], bufs[2 * i + 1]});
 }
 const char* check_report() { return g_report.c_str(); }
-const char* check_trace() { return g_trace.c_str(); }          // mangled kernel names, one a line, in launch order
+const char* check_trace() { return g_trace.c_str(); }          // mangled kernel names, one a line, in launch order (conv_kernel: a line more where its rows are sorted)
 
 // ---- the HIP runtime ----
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }

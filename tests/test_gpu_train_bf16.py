@@ -35,7 +35,8 @@ def test_layer_kinds_bf16(name):
 
 
 def _regular_cases():
-    """Layers wide enough (channels multiple of 64, power-of-two images) for the lean bf16 convolution kernels."""
+    """Regular bf16 layers (channels multiple of 64, power-of-two images): forward and data gradient from patches, weight gradients in
+    the lean kernels."""
     c = {}
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
@@ -80,7 +81,8 @@ def test_regular_layers_bf16_lean_kernels(name):
 
 
 def test_regular_layer_bf16_tall_tiles():
-    """Enough output rows (12 x 64 x 64 per replica, 3 replicas) that the lean kernels pick their 256-row tiles."""
+    """Enough output rows (12 x 64 x 64 per replica, 3 replicas) that conv_kernel, which has the 3 x 3 layers from 64 pixels' width
+    on, picks its 256-row tiles."""
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
     t = b.relu(b.conv(t, 64))
@@ -155,15 +157,18 @@ def test_vgg16_full_width_bf16_against_oracle():
     p.close()
 
 
-def test_regular_layer_bf16_256_tiles():
-    """Forward and data-gradient kernels with 256 x 256 tiles (one workgroup of eight waves per compute unit).  The
-    launcher only picks them when a launch fills the chip; the hint makes this small problem take them."""
+@pytest.mark.parametrize("shape,k,batch", [((16, 16, 3), 5, 1), ((8, 1, 3), 3, 41), ((8, 8, 3), 3, 5)])
+def test_regular_layer_bf16_256_tiles(shape, k, batch):
+    """Forward and data-gradient kernels with 256-row tiles: conv_kernel's 256 x 256 ones (one workgroup of eight waves per compute
+    unit) on the layers that it keeps, 5 x 5 filters and images of one pixel's width (328 rows per replica: one full and one ragged
+    tile), and the patch kernel's on 8 x 8 images (320 rows).  The launchers only pick them when a launch fills the chip; the hint makes
+    these small problems take them."""
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
-    t = b.relu(b.conv(t, 256))
-    t = b.relu(b.bn(b.conv(t, 256, bias=False)))         # the convolution also leaves the BN's sums (ragged last tile)
+    t = b.relu(b.conv(t, 256, k=k, pad=k // 2))
+    t = b.relu(b.bn(b.conv(t, 256, k=k, pad=k // 2, bias=False)))         # the convolution also leaves the BN's sums (ragged last tile)
     b.dense(b.gap(t), 5)
-    ops, shape, batch = b.array(), (8, 8, 3), 5          # 320 rows per replica: one full and one ragged 256-row tile
+    ops = b.array()
     N = 3
     x, y = _data(N, batch, shape, 5, seed=78)
     p = Pair(ops, shape, N, 2, x, y, batch, 0.01, 0.9, [2, 1, 1], bf16=True, options={hadfl.OPT_TILE_HINT: 1})
@@ -176,9 +181,9 @@ def test_regular_layer_bf16_256_tiles():
 
 @pytest.mark.parametrize("hint", [0, 1])
 def test_regular_layers_bf16_position_sorted_rows(hint):
-    """Batch 64 on 8x8 / 4x4 / 2x2 images: the lean kernels order GEMM rows (and the weight gradient's contraction) by
-    pixel position and leave out the taps no row of a tile can reach.  hint 1 also sends the 128- and 256-wide layers
-    through the 256-row tiles."""
+    """Batch 64 on 8x8 / 4x4 / 2x2 images: on 2x2 the patch kernel orders its rows, and wgrad_kernel its contraction, by pixel
+    position and leave out the taps no row of a tile can reach; on 4x4 the weight gradient leaves them out image by image.  hint 1 sends
+    all layers through the largest tiles.  (The sorted rows of conv_kernel: tests/test_gpu_patch_layers.py.)"""
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
     t = b.relu(b.bn(b.conv(t, 64)))
@@ -200,11 +205,11 @@ def test_regular_layers_bf16_position_sorted_rows(hint):
 
 
 def test_position_sorted_rows_of_an_odd_multiple_of_32_images():
-    """Batch 96 on 4x4 images, 256 output channels, largest tiles: forward and data gradient sort the positions, the weight
+    """Batch 96 on images of 4x1 pixels, 256 output channels, largest tiles: forward and data gradient sort the positions, the weight
     gradient, which gets the position table for multiples of 64 images only, does not."""
     b = nets._Builder()
     b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(b.relu(b.conv(0, 64)), 256))), 256))), 5)
-    ops, shape, batch, N = b.array(), (4, 4, 3), 96, 2
+    ops, shape, batch, N = b.array(), (4, 1, 3), 96, 2
     x, y = _data(N, 2 * batch, shape, 5, seed=80)
     p = Pair(ops, shape, N, 1, x, y, batch, 0.01, 0.9, [2, 1], bf16=True, options={hadfl.OPT_TILE_HINT: 1})
     w = p.forced_steps()
@@ -216,9 +221,9 @@ def test_position_sorted_rows_of_an_odd_multiple_of_32_images():
 
 @pytest.mark.parametrize("side,batch", [(16, 6), (32, 3)])
 def test_wide_image_layers_bf16_patch_kernel(side, batch):
-    """16- and 32-pixel-wide images with 64 / 128 channels: forward and data gradient run in the kernel that keeps a
-    256-pixel tile with its border in LDS and serves all nine taps from it (one and two 64-channel slices, 64 and 128
-    output channels, tiles at the top, middle and bottom of an image)."""
+    """16- and 32-pixel-wide images with 64 / 128 channels: forward and data gradient from patches with a border that is part of an
+    image (one and two 64-channel slices, 64 and 128 output channels, tiles at the top, middle and bottom of an image), the weight
+    gradient in the kernel of all taps on wide images."""
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
     t = b.relu(b.bn(b.conv(t, 64)))

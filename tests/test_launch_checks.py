@@ -286,6 +286,12 @@ def test_split_float_layers_reach_every_tile(checked):
     assert not missing, missing
 
 
+# fp32 tiles of conv_general_patch_kernel, for either direction
+PATCH_TILES = ("4ELi1ELi4ELi1ELi4ELi1ELi%dELb0ELi1", "4ELi1ELi4ELi1ELi2ELi1ELi%dELb1ELi1", "4ELi2ELi2ELi1ELi6ELi1ELi%dELb0ELi1", "2ELi2ELi2ELi1ELi4ELi1ELi%dELb0ELi1",
+               "2ELi2ELi2ELi1ELi2ELi2ELi%dELb1ELi1", "2ELi1ELi2ELi2ELi5ELi2ELi%dELb0ELi1", "2ELi1ELi2ELi4ELi5ELi2ELi%dELb0ELi1", "2ELi1ELi1ELi8ELi6ELi2ELi%dELb0ELi1",
+               "2ELi1ELi1ELi8ELi4ELi2ELi%dELb1ELi1", "1ELi1ELi2ELi4ELi3ELi2ELi%dELb0ELi1")
+
+
 def test_patch_layers_reach_every_tile(checked):
     """The layers of tests/test_gpu_patch_layers.py between them take every tile of that launcher, in both directions, and the
     route is theirs alone: a narrow, strided, 1 x 1 or very wide layer stays out of it."""
@@ -294,10 +300,7 @@ def test_patch_layers_reach_every_tile(checked):
     runs = checked(cases)
     assert all(r["status"] == 0 and r["report"] == "" and layers_in(r["trace"], "general_patch") == 4 for r in runs)
     seen = {name.split("patch_kernelIfLi")[1].split("EEEv")[0] for r in runs for name in r["trace"] if "general_patch" in name}
-    tiles = ("4ELi1ELi4ELi1ELi4ELi1ELi%dELb0ELi1", "4ELi1ELi4ELi1ELi2ELi1ELi%dELb1ELi1", "4ELi2ELi2ELi1ELi6ELi1ELi%dELb0ELi1", "2ELi2ELi2ELi1ELi4ELi1ELi%dELb0ELi1",
-             "2ELi2ELi2ELi1ELi2ELi2ELi%dELb1ELi1", "2ELi1ELi2ELi2ELi5ELi2ELi%dELb0ELi1", "2ELi1ELi2ELi4ELi5ELi2ELi%dELb0ELi1", "2ELi1ELi1ELi8ELi6ELi2ELi%dELb0ELi1",
-             "2ELi1ELi1ELi8ELi4ELi2ELi%dELb1ELi1", "1ELi1ELi2ELi4ELi3ELi2ELi%dELb0ELi1")
-    missing = {t % epi for t in tiles for epi in (0, 1)} - seen
+    missing = {t % epi for t in PATCH_TILES for epi in (0, 1)} - seen
     assert not missing, missing
     out = []
     for side, c, n, k, stride in ((8, 32, 64, 3, 1), (8, 64, 32, 3, 1), (8, 64, 64, 3, 2), (8, 64, 64, 1, 1), (64, 40, 40, 3, 1), (1, 64, 64, 3, 1)):
@@ -324,6 +327,57 @@ def test_patch_layers_reach_every_tile_bf16(checked):
         b.dense(b.gap(b.relu(b.conv(b.relu(b.bn(b.conv(0, c))), n, k=k, stride=stride, pad=k // 2))), 5)
         out.append(case(b, (side, side, 3), 16, [1], 1, classes=5))
     assert all(layers_in(r["trace"], "general_patch") == 0 for r in checked(out))
+
+
+def test_tiled_layers_reach_every_tile_bf16(checked):
+    """The regular bf16 layers that the patch kernel refuses between them take every tile of conv_kernel in both directions, with rows in
+    memory order and sorted by position; all four of a network's launches are that kernel's."""
+    from tests.test_gpu_patch_layers import TILED_BF16, net
+    runs = checked([case(net(c, n, k), (h, w, 3), batch, [1] * replicas, 1, classes=5, options=[(1, hint)]) for (h, w), c, n, k, batch, replicas, hint in TILED_BF16])
+    assert all(r["status"] == 0 and r["report"] == "" and layers_in(r["trace"], "11conv_kernel") == 4 and layers_in(r["trace"], "patch") == 0 for r in runs)
+    seen = set()
+    for r in runs:
+        for name, after in zip(r["trace"], r["trace"][1:]):
+            if "11conv_kernel" in name:
+                seen.add((name.split("conv_kernelILi")[1].split("EEEv")[0], after == "(its_rows_sorted)"))
+    tiles = ("256ELi256ELi2ELi4ELi2", "256ELi128ELi2ELi2ELi1", "256ELi64ELi2ELi2ELi1", "128ELi128ELi2ELi2ELi1", "128ELi64ELi2ELi2ELi1")
+    missing = {("%sELi%d" % (t, epi), rows) for t in tiles for epi in (0, 1) for rows in (False, True)} - seen
+    assert not missing, missing
+
+
+def test_networks_of_the_bf16_tests_run_where_their_texts_say(checked):
+    """Forward, data gradient and weight gradient of the second and third convolution in tests/test_gpu_train_bf16.py."""
+    def net(k, *widths):
+        b = nets._Builder()
+        t = 0
+        for c in widths:
+            t = b.relu(b.conv(t, c, k=k if t else 3, pad=k // 2 if t else 1))
+        b.dense(b.gap(t), 5)
+        return b
+    want = (((16, 16), 5, 1, 1, "conv_kernelILi256ELi256", "12wgrad_kernel", 0), ((8, 1), 3, 41, 1, "conv_kernelILi256ELi256", "12wgrad_kernel", 0),
+            ((4, 1), 3, 96, 1, "conv_kernelILi256ELi256", "12wgrad_kernel", 1), ((8, 8), 3, 5, 1, "patch_kernelIDF16bLi4ELi2ELi2ELi1ELi11", "wgrad_taps", 0),
+            ((2, 2), 3, 64, 0, "Lb1ELi2", "12wgrad_kernel", 0), ((4, 4), 3, 64, 0, "conv_general_patch", "wgrad_images", 0), ((32, 32), 3, 3, 0, "conv_general_patch", "wgrad_taps", 0))
+    for ((h, w), k, batch, hint, forward, wgrad, rows) in want:
+        wide = 128 if h == 32 else 256
+        (run,) = checked([case(net(k, 64, wide, wide), (h, w, 3), batch, [1, 1, 1], 1, classes=5, options=[(1, hint)])])
+        assert run["status"] == 0 and run["report"] == ""
+        conv = [name for name in run["trace"] if "11conv_kernel" in name or "general_patch" in name]
+        assert len(conv) == 4 and forward in conv[0] and forward in conv[1] and forward in conv[2], (h, w, conv)
+        assert layers_in(run["trace"], wgrad) == 2 and (layers_in(run["trace"], "rows_sorted") > 0) == bool(rows), (h, w, run["trace"])
+
+
+def test_layers_above_bf16_reach_every_second_pass(checked):
+    """The layers of test_patch_layers_above_bf16 between them take every fp32 tile of the patch kernel in both directions, and the weight
+    gradient by position in launches with split sums and without."""
+    from tests.test_gpu_patch_layers import ABOVE, doubled_net
+    runs = checked([case(doubled_net(c, n, k, batch * h * w, 20), (h, w, 3), batch, [1] * replicas, 0, classes=20, options=[(1, hint)])
+                    for (h, w), c, n, k, batch, replicas, hint in ABOVE])
+    assert all(r["status"] == 0 and r["report"] == "" for r in runs)
+    seen = {name.split("patch_kernelIfLi")[1].split("EEEv")[0] for r in runs for name in r["trace"] if "general_patch" in name}
+    missing = {t % epi for t in PATCH_TILES for epi in (0, 1)} - seen
+    assert not missing, missing
+    by_position = [r["trace"][i + 1] for r in runs for i, name in enumerate(r["trace"]) if "general_position" in name]
+    assert {"splitk_reduce" in after for after in by_position} == {False, True}
 
 
 def test_patch_layers_only_where_their_quotients_are_exact(checked):
