@@ -268,8 +268,9 @@ HADFL_API hadfl_status hadfl_set_momentum(hadfl_ctx *ctx, int32_t replica, const
  *   HADFL_OPT_SIDE_STREAM  1 (default): weight-gradient kernels of hadfl_local_steps run on a second stream owned by
  *                          the context; 0: every launch goes to the context's stream.  Changes no bit of the result.
  *   HADFL_OPT_TILE_HINT    0 (default): tile shapes chosen per launch; 1: the convolution kernels take their largest
- *                          tiles wherever the layer shape allows, whatever the launch size; 2: layers on 16- and
- *                          32-pixel-wide images stay out of the kernels for such images.  Other tiles add some of the
+ *                          tiles wherever the layer shape allows, whatever the launch size; 2: the weight gradients of
+ *                          bf16 convolutions on images 4, 8, 16 or 32 pixels wide stay out of the kernels for such images
+ *                          (forward pass and data gradient have none, and run as with 0).  Other tiles add some of the
  *                          sums in another order: results agree to rounding.
  * Takes effect from the next hadfl_local_steps.  EINVAL for an unknown option or value; ESTATE without a
  * trainable network. */

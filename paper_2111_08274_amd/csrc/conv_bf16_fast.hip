@@ -13,7 +13,7 @@
 //   * the MFMA operands are swapped (C^T = B^T A^T), which leaves 4 consecutive output channels in each lane, so
 //     the epilogue stores 8 bytes (bf16) or 16 bytes (fp32) per lane instead of single elements.
 // Kernels: conv_kernel (forward / data gradient of the layers that conv_general_patch.hip does not take: images wider than its
-// border allows, or of fewer than four pixels), wgrad_kernel (weight gradient: operands stored as they arrive and transposed by the
+// border allows, of one pixel's width, or of fewer than four pixels), wgrad_kernel (weight gradient: operands stored as they arrive and transposed by the
 // LDS read), wgrad_taps_kernel (weight gradient on wide images: all taps from one patch), wgrad_images_kernel (on 4 x 4 images: all
 // taps, sixteen images a contraction), weight_prep_kernel.  Each has its own comment.
 #include <algorithm>

@@ -531,7 +531,10 @@ hipError_t launch_split(GeneralConvParams& p, int n_active, hipStream_t s, int* 
     }
 }
 
-constexpr int kBorderBf16 = 33;      // pixels of border before and behind a tile that the bf16 launches have room for
+// Pixels of border before and behind a tile that the bf16 launches have room for: 3 x 3 filters on images up to 32 pixels wide.  A patch on
+// its way is in registers, 11 loads of 16 bytes a thread for the 256 + 66 pixels of the largest tiles; more was not measured, and
+// wider images stay in the earlier kernels.
+constexpr int kBorderBf16 = 33;
 
 template <int EPI>
 hipError_t launch_bf16(GeneralConvParams& p, int n_active, hipStream_t s, int* stat_rows)

@@ -66,8 +66,8 @@ public:
     std::vector<int64_t> wf_off, wb_off;  // per layer: offsets (2-byte units) inside one replica's block of weight copies, or -1
     int64_t wbf_rep = 0;                  // bf16 elements per replica
     int64_t wbf_off = 0;                  // start of the bf16 weight region inside `work` (floats)
-    // Option HADFL_OPT_TILE_HINT: 1 makes the lean kernels take their 256 x 256 tiles wherever the layer shape allows,
-    // whatever the launch size (lets small problems exercise them); 2 keeps wide-image layers on the general kernels.
+    // Option HADFL_OPT_TILE_HINT: 1 makes the convolution kernels take their largest tiles wherever the layer shape allows,
+    // whatever the launch size (lets small problems exercise them); 2 keeps the lean weight gradients in wgrad_kernel.
     int tile_hint = 0;
     // Weight gradients (and their split-K reduction / fused update) depend only on dY and the stored activations, not on
     // the data-gradient chain, so they run on a second stream beside it; joined before the update kernel.

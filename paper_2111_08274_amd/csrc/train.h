@@ -33,7 +33,7 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
 void train_set_steps(TrainEngine* e, const std::vector<int32_t>& steps);
 void train_set_lr(TrainEngine* e, float lr);
 void train_set_side_stream(TrainEngine* e, bool on);      // weight gradients on the engine's second stream
-void train_set_tile_hint(TrainEngine* e, int hint);       // 0 automatic, 1 tall tiles wherever they fit, 2 no wide-image kernels
+void train_set_tile_hint(TrainEngine* e, int hint);       // HADFL_OPT_TILE_HINT
 bool train_has_momentum(const TrainEngine* e);
 void train_destroy(TrainEngine* e);
 

@@ -58,7 +58,7 @@ struct FastConvParams {      // out[m][n] = sum_k act[pixel(m) + tap(k)][c(k)] *
     int relu;
     const void* mask; long long mask_rep; int accumulate;   // data gradient
     const int* order;
-    int tile_hint;                             // 1: take the 256 x 256 tiles whenever the shape allows (N % 256 == 0)
+    int tile_hint;                             // 1: take the 256 x 256 tiles whenever the shape allows (N % 256 == 0); 2: as 0
     // optional position table (both null or both set): GEMM row ps * B + b is image b at pixel perm[ps]; posmask[ps] has
     // bit r * S + s set when tap (r, s) of that pixel lies inside the image
     const int* perm; const unsigned* posmask;
@@ -85,7 +85,7 @@ struct FastWgradParams {     // dW[(tap, ci) | bias row][co] over pixels; needs 
     float* out; long long out_rep, out_split;
     const int* order;
     const int* perm; const unsigned* posmask;   // optional position table as in FastConvParams; needs B % 64 == 0, kchunk % 64 == 0
-    int tile_hint;                              // 1: 256-row tiles whenever N % 128 == 0
+    int tile_hint;                              // 1: 256-row tiles in wgrad_kernel whenever N % 128 == 0; 2: wgrad_kernel for any image
     // splits == 1 only: when sgd_w is set the epilogue applies the update (buf = momentum*buf + g; w -= lr*buf) to the
     // layer's slice of the parameter rows (same per-replica stride as `out`) instead of storing the gradient
     float* sgd_w; float* sgd_buf; float lr, momentum;
@@ -138,7 +138,7 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     const int* order;
     const int* perm; const unsigned* posmask;  // optional position table as in FastConvParams (stride 1)
     float* stat; long long stat_rep;           // forward, optional: statistics entries as in FastConvParams
-    int tile_hint;                             // 1: the largest tiles whatever the launch size
+    int tile_hint;                             // 1: the largest tiles whatever the launch size; 2: as 0
     int tiles_m, n_active;                     // set by the launcher
     int halo; unsigned inv_hw, inv_w;          // the same (conv_general_patch.hip): pixels of border before and behind a tile, 2^32 / HW, 2^32 / W
     const float* stat_y; long long stat_y_rep; int stat_relu;      // bf16 data gradient with stat set (conv_general_patch.hip): as in FastConvParams

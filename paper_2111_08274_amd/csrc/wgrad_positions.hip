@@ -13,8 +13,9 @@
 // A workgroup owns all nine taps of 64 input against 64 output channels and walks positions along the rows of sixteen images.  A
 // step multiplies one position: of x it needs the 3 x 3 positions around it, the columns to the left of which came with the steps
 // before, so a step fetches one column of three (six operands of 32 channels) and the position's dy (two): one for each of the
-// eight waves.  Columns are numbered along the walk and kept in a ring of four, dy in one of two; a step's operands are fetched
-// two steps before they are written, beside the matrix instructions.  One barrier a step.
+// eight waves.  Columns are numbered along the walk, and x and dy have a ring of four places each: with one barrier a step, step t reads the
+// columns t - 1 to t + 1 and, ahead, dy of t + 1 (in front of the first step that of t too) while those of t + 2 are written.  Operands
+// are fetched two steps before they are written, beside the matrix instructions.
 // Waves 0 to 3 multiply the corner taps and the middle one, waves 4 to 7 the four others, each for a block of 32 x 32 channels: on a
 // SIMD, which has one of either, that is nine.  Per step: 54 matrix instructions a SIMD (1728 clocks), some 130 KiB of LDS read
 // (600 at the measured 220 bytes a clock), 24 KiB written (350 at 70), a wave's eight loads and some 90 vector instructions.

@@ -25,7 +25,7 @@ def forced(builder, shape, batch, replicas, bf16):
 @pytest.mark.parametrize("batch,replicas", [(32, 2), (64, 4)])
 @pytest.mark.parametrize("make", [first_norm, pre_activation, pooled])
 def test_gradient_sums_of_a_lone_batch_norm_bf16(make, batch, replicas):
-    """The sums from a lean data gradient, for a batch norm behind the first layer, a sum or a pool."""
+    """The sums from a data gradient, for a batch norm behind the first layer, a sum or a pool."""
     forced(make(), (8, 8, 3), batch, replicas, True)
 
 

@@ -237,9 +237,9 @@ def test_resnet18_full_width_against_oracle():
 
 @pytest.mark.parametrize("hint", [0, 1])
 def test_lean_fp32_kernels_position_sorted_rows(hint):
-    """fp32 configuration, layers with 64 / 128 channels on 8x8, 4x4 and 2x2 images at batch 32: forward and data gradient
-    run in the lean fp32 kernels with rows ordered by pixel position and out-of-range taps skipped (hint 1: 256-row
-    tiles); bias + ReLU, BN and pooling around them; the weight gradient stays in the generic kernel."""
+    """fp32 configuration, layers with 64 / 128 channels on 8x8, 4x4 and 2x2 images at batch 32: forward and data gradient from
+    patches, on 2x2 (hint 1, the largest tiles: on 4x4 too) in tiles whose rows are ordered by pixel position and leave out-of-range
+    taps out; bias + ReLU, BN and pooling around them; the weight gradient by position on 2x2, else in the general kernel."""
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
     t = b.maxpool(b.relu(b.bn(b.conv(t, 64, bias=False))))
@@ -261,9 +261,9 @@ def test_lean_fp32_kernels_position_sorted_rows(hint):
 @pytest.mark.parametrize("bf16,bias", [(False, 200.0), (True, 8.0)])
 def test_batch_norm_statistics_from_a_convolution_with_a_large_bias(bf16, bias):
     """A convolution whose bias is large beside the spread of its outputs, followed by a batch norm that takes its
-    statistics from that convolution's epilogue (64 channels: the lean kernels).  Sums of x and x^2 taken about zero
-    would lose the variance to cancellation in fp32 (mean^2 / var = 4e4 here: an error of 1e-2 in the variance); the
-    epilogue centres them on the bias.  (In the workloads a bias in front of a batch norm has zero gradient and
+    statistics from that convolution's epilogue.  Sums of x and x^2 taken about zero would lose the variance to cancellation in
+    fp32 (mean^2 / var = 4e4 here: an error of 1e-2 in the variance); the epilogue centres them on the bias, in fp32 by leaving it
+    out of what it stores.  (In the workloads a bias in front of a batch norm has zero gradient and
     stays where the initialisation put it.)"""
     b = nets._Builder()
     t = b.relu(b.conv(0, 64))
