@@ -28,21 +28,24 @@ TRAFFIC = {
     ("aggregate", "agg-stress-n64"): (("paper_2111_08274_amd/csrc/aggregate.hip",),
                                       "c22583d4d32953228aa0edf6c53022af645f8207beb80c048d09e7e895666a1e",
                                       402301497.1),
-    # all launches of the class in a cycle, averaged
-    ("conv_dgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
-                                        "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                       "af87472c9757601a35f7caf7cdd4d1e67e12bb00c1f41ab6076cc11234124dc4",
-                                       468811747.8),
-    ("conv_fwd", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
+    # all launches of the class in a cycle, averaged; the files hold the kernels that take this network's layers
+    ("conv_dgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_general_patch.hip",
+                                        "paper_2111_08274_amd/csrc/mfma_tiles.h",
+                                        "paper_2111_08274_amd/csrc/slabs.h"),
+                                       "dc4b7a23e384a464c0a8be9ce29e0f625b54427703f89c3e65d36ed818029f35",
+                                       285552027.4),
+    ("conv_fwd", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_general_patch.hip",
                                       "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
-                                      "paper_2111_08274_amd/csrc/conv_stats.h"),
-                                     "63accfde27adcaf3fd9755c46f3145b9c60738ac096618c65ad73580cbe33a5f",
-                                     324735679.0),
+                                      "paper_2111_08274_amd/csrc/mfma_tiles.h",
+                                      "paper_2111_08274_amd/csrc/slabs.h"),
+                                     "59b4ee5d26dff79123b233ff10001e9dd31ae9a4ee9ff7d233064dd61e91d6dd",
+                                     223324031.8),
     # (the figure includes the fused update's parameter and momentum traffic)
     ("conv_wgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
-                                        "paper_2111_08274_amd/csrc/conv_first_bf16.hip"),
-                                       "df356755a15fbe000e3f523f2100289fa7b770b10a3deb64740409819a790c45",
-                                       529837990.4),
+                                        "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
+                                        "paper_2111_08274_amd/csrc/mfma_tiles.h"),
+                                       "e8e93db763c155aeb1c5665d5f237d97d145c827da9a7035a84c010664c50a81",
+                                       514597249.6),
 }
 
 
