@@ -21,6 +21,10 @@ SHAPES = [((8, 6), 36, 132, 3, 7, 1, 0), ((8, 6), 132, 36, 3, 33, 2, 1), ((5, 7)
           ((4, 4), 512, 512, 3, 64, 1, 0), ((2, 2), 512, 512, 3, 64, 1, 0), ((8, 8), 256, 256, 3, 64, 1, 0),
           ((7, 9), 64, 60, 3, 50, 40, 0), ((3, 2), 192, 128, 3, 37, 6, 0), ((17, 6), 116, 64, 3, 130, 3, 0), ((16, 16), 64, 64, 3, 72, 8, 0)]
 
+# images of one or two pixels' width or height
+THIN = [((8, 1), 64, 64, 3, 50, 3, 0), ((1, 1), 64, 128, 3, 64, 2, 0), ((1, 2), 64, 64, 3, 48, 4, 0), ((2, 1), 128, 64, 3, 96, 2, 0), ((1, 8), 40, 80, 3, 32, 2, 0),
+        ((1, 63), 64, 64, 3, 40, 3, 0), ((1, 9), 72, 64, 3, 130, 2, 1), ((31, 2), 64, 64, 3, 40, 4, 0), ((1, 5), 64, 64, 5, 33, 2, 0)]
+THIN_BF16 = [((1, 32), 64, 64, 3, 20, 2, 0), ((1, 9), 40, 80, 3, 33, 2, 0), ((32, 2), 64, 128, 3, 18, 2, 0), ((2, 31), 64, 72, 3, 32, 2, 1), ((1, 4), 128, 128, 3, 64, 3, 0)]
 # tall images: the first of either list has too many pixels for the kernel's quotients (tests/test_launch_checks.py), the second has not
 TALL = [((1112, 60), 36, 40, 3, 1, 1, 0), ((1060, 60), 36, 40, 3, 1, 1, 0)]
 # bf16 regular layers that the kernel does not take (wide images, large filters on 16 pixels' width, images of one pixel's width or less than
@@ -40,7 +44,7 @@ def net(c, n, k):
     return b
 
 
-@pytest.mark.parametrize("shape", SHAPES + TALL)
+@pytest.mark.parametrize("shape", SHAPES + THIN + TALL)
 def test_patch_layers(shape):
     """Gradients of one step, read from the momentum buffers, against the same network in 64 bits.  Bound: the error of a sum of
     K products in fp32, 2^-24 sqrt(K), K <= 4608 products and up to 66720 pixels, and as much again through each of two batch
@@ -78,7 +82,7 @@ SHAPES_BF16 = [((8, 8), 64, 136, 3, 9, 2, 1), ((16, 32), 72, 64, 3, 5, 2, 1), ((
                ((4, 4), 64, 128, 3, 17, 3, 0), ((4, 4), 128, 64, 3, 130, 1, 0), ((4, 4), 256, 512, 3, 16, 9, 0)]         # (4 x 4: weight gradients by images, ragged sixteens, splits)
 
 
-@pytest.mark.parametrize("shape", SHAPES_BF16 + TALL_BF16 + TILED_BF16)
+@pytest.mark.parametrize("shape", SHAPES_BF16 + THIN_BF16 + TALL_BF16 + TILED_BF16)
 def test_patch_layers_bf16(shape):
     """Gradients of one step against the same network in 64 bits, in the 2-norm of a tensor.  What roundings to bf16 do to a
     tensor (units within 2^-9 of zero that open on one side only, sums that nearly cancel) is measured on the 64-bit network: the

@@ -400,10 +400,10 @@ def test_patch_layers_only_where_their_quotients_are_exact(checked):
 
 def test_weight_gradients_by_position(checked):
     """fp32 3 x 3 stride-1 layers of (nearly) whole 64-channel tiles whose launch is large enough; every plan's split sums in their region."""
-    from tests.test_gpu_patch_layers import SHAPES, net
-    shapes = [s for s in SHAPES if s[0] in ((7, 9), (3, 2), (17, 6), (16, 16)) and s[3] == 3 and s[1] != 72]
+    from tests.test_gpu_patch_layers import SHAPES, THIN, net
+    shapes = THIN[:4] + [s for s in SHAPES if s[0] in ((7, 9), (3, 2), (17, 6), (16, 16)) and s[3] == 3 and s[1] != 72]
     cases = [case(net(c, n, k), (h, w, 3), batch, [2] + [1] * (replicas - 1), 0, classes=5) for (h, w), c, n, k, batch, replicas, hint in shapes]
-    assert len(cases) == 5 and all(layers_in(r["trace"], "general_position") > 0 for r in checked(cases))
+    assert len(cases) == 9 and all(layers_in(r["trace"], "general_position") > 0 for r in checked(cases))
     assert_clean(checked, cases)
     out = [case(net(c, n, k), (8, 8, 3), 64, [1] * 4, bf16, classes=5) for c, n, k, bf16 in ((64, 64, 5, 0), (80, 80, 3, 0), (64, 64, 3, 1))]
     assert all(layers_in(r["trace"], "general_position") == 0 for r in checked(out))
