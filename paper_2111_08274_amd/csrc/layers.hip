@@ -212,16 +212,12 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(BnParams p)
     }
 }
 
-// The bias that the convolution in front left out of its outputs; it belongs to the running mean.  An Inf or NaN
-// among the biases would have made the outputs NaN or Inf: then `mean` (of the outputs, shifted or not) becomes NaN,
-// and with it all that is normalised.
-__device__ __forceinline__ float bn_left_out(const BnParams& p, int rep, int c, float& mean)
-{
-    if (!p.left_out) return 0.f;
-    const float bias = p.left_out[rep * p.left_out_rep + c];
-    mean += 0.f * (mean + bias);
-    return bias;
-}
+// (fused explicitly: which of the two products is rounded would otherwise be the compiler's choice, kernel by kernel)
+__device__ __forceinline__ float bn_running_mean(float old, float mean) { return __builtin_fmaf(1.f - kBnStatMomentum, old, kBnStatMomentum * mean); }
+
+// The bias that the convolution in front left out of its outputs; it belongs to the running mean.  An Inf or NaN among the biases would
+// have made the outputs NaN or Inf: added to the mean times zero, it makes that NaN, and with it all that is normalised.
+__device__ __forceinline__ float bn_left_out(const BnParams& p, int rep, int c) { return p.left_out ? p.left_out[rep * p.left_out_rep + c] : 0.f; }
 
 // y = gamma * (x - mean) * istd + beta; the blocks of chunk 0 also store mean / istd and update the running statistics
 template <typename T>
@@ -247,7 +243,7 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_kernel(BnParams p)
         sv[c] = mean; sv[p.C + c] = istd;
         const float unb = p.rows > 1 ? q / (float)(p.rows - 1) : var;
         float* rm = row + p.stat_off;
-        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * mean;
+        rm[c] = bn_running_mean(rm[c], mean);
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     }
     const int r0 = chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
@@ -564,6 +560,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
     const bool live = c < p.C;
     float* part = p.partial + gi * p.partial_rep;
     const int nk = ((MODE == 0 && p.stats_done) || (MODE == 1 && p.bwd_stats_done)) ? p.stat_entries : p.chunks;
+    const float left_out = MODE == 0 && live ? bn_left_out(p, rep, c) : 0.f;          // (on its way beside the sums)
     float s = 0.f, q = 0.f;
     // Backward sums left by the data gradient above are s = sum g and q = sum g * y, y = gamma * xhat + beta the stored
     // (bf16) output, so that  sum g * xhat = (q - beta * s) / gamma.  The bf16 rounding of y enters xhat multiplied by
@@ -646,15 +643,14 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
         // the shift the sums were taken with: the producing convolution's bias, or the tensor's first row
         const float x0 = p.stats_done ? (p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c] : 0.f)
                                       : ldf(tptr<T>(p.x, rep, p.x_rep), c);
-        float md = s / n;                                     // mean of the shifted values
-        const float left_out = bn_left_out(p, rep, c, md);
+        const float md = s / n + 0.f * left_out;              // mean of the shifted values
         const float cen = fmaxf(q - s * md, 0.f);             // sum of squared deviations from the mean
         const float mean = x0 + md, var = cen / n;
         float* sv = p.saved + rep * p.saved_rep;
         sv[c] = mean; sv[p.C + c] = 1.0f / sqrtf(var + kBnEps);
         const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
         float* rm = p.params + rep * p.row_stride + p.stat_off;
-        rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + left_out);
+        rm[c] = bn_running_mean(rm[c], mean + left_out);
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     } else {
         if (p.bwd_stats_done && !direct) q = (q - beta * s) / gamma;
@@ -997,6 +993,11 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
                 for (int e = 0; e < VEC; ++e) { const float d = v[e] - x0[e]; t[e] += d; t[VEC + e] += d * d; }
             }
     }
+    float left_out[VEC] = {};                                 // (on its way beside the totals)
+    if (p.left_out) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) left_out[e] = p.left_out[rep * p.left_out_rep + c0 + e];
+    }
     bn_small_total(t, red, p.cvb);
     if (!live) return;
     const float n = (float)p.rows;
@@ -1005,15 +1006,13 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {                           // as in bn_finalize_kernel<0>
         const int c = c0 + e;
-        float md = t[e] / n;
-        const float left_out = bn_left_out(p, rep, c, md);
-        const float cen = fmaxf(t[VEC + e] - t[e] * md, 0.f), mean = x0[e] + md, var = cen / n, istd = 1.0f / sqrtf(var + kBnEps);
+        const float md = t[e] / n + 0.f * left_out[e], cen = fmaxf(t[VEC + e] - t[e] * md, 0.f), mean = x0[e] + md, var = cen / n, istd = 1.0f / sqrtf(var + kBnEps);
         if (rl == 0) {
             float* sv = p.saved + rep * p.saved_rep;
             sv[c] = mean; sv[p.C + c] = istd;
             const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
             float* rm = row + p.stat_off;
-            rm[c] = (1.f - kBnStatMomentum) * rm[c] + kBnStatMomentum * (mean + left_out);
+            rm[c] = bn_running_mean(rm[c], mean + left_out[e]);
             rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
         }
         bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
