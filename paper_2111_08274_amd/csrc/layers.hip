@@ -127,6 +127,13 @@ __global__ __launch_bounds__(256) void pass_grad_kernel(EwParams p)
     }
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void zero_kernel(EwParams p)
+{
+    T* out = tptr<T>(p.out, p.order[blockIdx.y], p.out_rep);
+    for (long long i = gtid(); i < p.count; i += gstride()) stf(out, i, 0.f);
+}
+
 // out[b][c] = mean over H*W; count = B*C
 template <typename T>
 __global__ __launch_bounds__(256) void gap_fwd_kernel(EwParams p)
@@ -1458,6 +1465,14 @@ HADFL_EW_LAUNCH(launch_gap_bwd, gap_bwd_kernel)
         return hipGetLastError(); }
 HADFL_EW_VEC_LAUNCH(launch_add_fwd, add_fwd_vec_kernel, add_fwd_kernel)
 HADFL_EW_VEC_LAUNCH(launch_pass_grad, pass_grad_vec_kernel, pass_grad_kernel)
+
+hipError_t launch_zero(const EwParams& p, int n_active, hipStream_t s)
+{
+    if (n_active < 1 || p.count < 1) return hipSuccess;
+    if (p.bf16) hipLaunchKernelGGL(zero_kernel<__bf16>, ew_grid(p.count, n_active), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(zero_kernel<float>, ew_grid(p.count, n_active), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
 #undef HADFL_EW_VEC_LAUNCH
 
 hipError_t launch_maxpool_fwd(const EwParams& p, int n_active, hipStream_t s)

@@ -38,6 +38,7 @@ public:
     std::vector<char> skip;               // per layer: fused away
     std::vector<char> fused_relu;         // per layer: applies max(., 0) in its store
     std::vector<char> masked;             // per tensor: gradient writers must apply the (value > 0) mask
+    std::vector<int> unread;              // tensors that no layer reads, the network's output apart: their gradient is zero
     // Pool fusion: a 2x2 max-pool that is the only consumer of a batch-norm layer's (ReLU'd) output is folded into the
     // BN kernels: forward writes the pooled tensor as well, backward forms the full-resolution gradient on the fly from
     // the pooled gradient.  The pool layer itself issues nothing.
@@ -439,6 +440,7 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
         std::vector<int> consumers(T, 0);
         for (const Layer& l : plan.layers) { consumers[l.in0]++; if (l.type == HADFL_OP_ADD) consumers[l.in1]++; }
         for (int i = 0; i < nl; ++i) e->out_tensor[i] = plan.layers[i].out;
+        for (int t = 1; t < T - 1; ++t) if (!consumers[t]) e->unread.push_back(t);
         for (int j = 0; j < nl; ++j) {
             const Layer& r = plan.layers[j];
             if (r.type != HADFL_OP_RELU || r.in0 < 1 || consumers[r.in0] != 1 || r.out == T - 1) continue;
@@ -1107,6 +1109,11 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
         e->grad_written.assign(T, 0);
         e->grad_written[T - 1] = 1;
         r.na_next = step + 1 < e->e_max ? e->n_active[step + 1] : 0;
+        for (int t : e->unread) {
+            EwParams z{};
+            z.out = r.grad(t); z.out_rep = e->rep_block; z.count = e->cfg.batch * e->plan.tensors[t].numel(); z.bf16 = e->cfg.bf16; z.order = e->buf.order;
+            r.run("zero_grad", 0, r.asz() * 4.0 * z.count, [&] { return launch_zero(z, r.na, s); });
+        }
         for (size_t i = e->plan.layers.size(); i-- > 0;) r.backward_layer(i);
         if (r.pending_prep >= 0) { r.fork(0.0); r.flush_pending_prep(); r.unfork(); }
         r.join();

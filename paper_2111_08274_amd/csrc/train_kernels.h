@@ -243,6 +243,7 @@ hipError_t launch_maxpool_bwd(const EwParams& p, int n_active, hipStream_t s);
 hipError_t launch_add_fwd(const EwParams& p, int n_active, hipStream_t s);
 // out(din) (+)= in(dout)
 hipError_t launch_pass_grad(const EwParams& p, int n_active, hipStream_t s);
+hipError_t launch_zero(const EwParams& p, int n_active, hipStream_t s);       // out = 0
 hipError_t launch_gap_fwd(const EwParams& p, int n_active, hipStream_t s);
 hipError_t launch_gap_bwd(const EwParams& p, int n_active, hipStream_t s);
 

@@ -227,6 +227,10 @@ void look(const std::string& name, dim3 grid, void** args)
         if (p.cursor) l.data(p.a, p.n_samples, p.B, p.sample_sz); else l.act(p.a, p.a_rep, p.mode == kDgrad ? dst : src);
         if (p.mode == kWgrad) { l.act(p.dy, p.dy_rep, dst); gradient(l, p.out, p.out_rep, p.out_split, p.splits, (long long)p.M * p.N, nullptr, nullptr); }
         else l.act(p.out, p.out_rep, p.mode == kDgrad ? src : dst);
+    } else if (has(name, "zero_kernel")) {
+        const EwParams& p = *(EwParams*)args[0];
+        l.order = p.order; l.n = (int)grid.y; l.es = p.bf16 ? 2 : 4;
+        l.act(p.out, p.out_rep, p.count);
     } else if (has(name, "bn_")) batch_norm(l, *(BnParams*)args[0], (int)grid.y);
     else if (has(name, "softmax_ce")) {
         const LossParams& p = *(LossParams*)args[0];

@@ -233,3 +233,26 @@ def test_image_rows_of_gibibytes():
         print(size, "%.1e" % err, flush=True)
         assert err <= 3e-5
         at += size
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_layers_whose_output_nobody_reads(bf16):
+    """A convolution with a ReLU, a batch norm with a pool, a sum and a dense layer beside the network: their gradient is zero, whatever
+    the workspace holds (NaN here), and their parameters stay where they are."""
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, 64)))
+    b.relu(b.conv(t, 40))
+    b.maxpool(b.relu(b.bn(b.conv(t, 64))))
+    b.add(t, b.conv(t, 64, k=1, pad=0))
+    b.dense(t, 20)
+    b.dense(b.gap(b.relu(b.conv(t, 48))), 5)
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal((2, 2 * 24, 8, 8, 3)).astype(np.float32)
+    y = rng.integers(0, 5, size=(2, 2 * 24)).astype(np.int32)
+    p = Pair(b.array(), (8, 8, 3), 2, 1, x, y, 24, 0.01, 0.9, [2, 1], bf16=bf16)
+    # (in front: the aggregate and the momentum of two replicas; behind: small state, less than 16 KiB)
+    p.gpu.scratch.view(torch.float32)[3 * p.gpu.row_stride:-4096] = float("nan")
+    w = p.forced_steps()
+    print(bf16, pm.show(w), flush=True)
+    assert w["compared"] > 0 and (p.max_rel_diff() <= 2e-2 if bf16 else p.max_param_diff() <= 1e-4)
+    p.close()
