@@ -62,9 +62,43 @@ __device__ __forceinline__ long long uniform_key(long long v)
     return ((long long)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// Sixteen fp64 registers that a wave-uniform index can address (the compiler turns an indexed write into one
-// register-relative move)
-typedef double F16 __attribute__((ext_vector_type(16)));
+// Inclusive sums along the lanes of a row of 16, and along the whole wavefront.  One rounding per step of a tree of depth 4
+// (6): not the sums of the rule, which add one value after another, but within kSumError of them.
+template <int kCtrl, int kRows> __device__ __forceinline__ double lanes_below(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRows, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRows, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sums(double v)
+{
+    v = v + lanes_below<0x111, 0xf>(v);                    // row_shr:1, 2, 4, 8
+    v = v + lanes_below<0x112, 0xf>(v);
+    v = v + lanes_below<0x114, 0xf>(v);
+    return v + lanes_below<0x118, 0xf>(v);
+}
+__device__ __forceinline__ double wave_sums(double v)
+{
+    v = row_sums(v);
+    v = v + lanes_below<0x142, 0xa>(v);                    // row_bcast:15 into the second and fourth row
+    return v + lanes_below<0x143, 0xc>(v);                 // row_bcast:31 into the upper half
+}
+
+// A draw picks the first replica whose running sum R_i, added one value after another with a rounding each, exceeds
+// fl(u * R_N).  That chain of N dependent additions need not be run to know the pick.  Let A_i be a sum of the same values
+// formed by a tree, less what was picked since, and `total` the sum of all values when the tree was formed.  No value is negative, so
+// a rounding is at most 2^-53 total: R_i has fewer than N <= 1024 of them, A_i at most ten for the tree and two for every one of
+// up to 1024 picks, the threshold one more than its sum.  |A_i - R_i| and the difference of the thresholds are each below 3100 *
+// 2^-53 total, so where A_i is further than kSumError * total from the threshold, R_i is on the same side.  Where it is not
+// (some N * 2^-40 of all draws, and more of them as the picks leave little of the total), the tree is formed anew, and where that is not
+// enough either, the chain decides.  NaN compares false, on neither side.
+constexpr double kSumError = 0x1p-40;
+struct Sides { unsigned long long above, below; };         // lanes whose running sum exceeds the threshold, lanes whose does not
+__device__ __forceinline__ Sides sides(double sum, double thr, double error)
+{
+    const double d = sum - thr;
+    return Sides{__ballot(d > error), __ballot(d < -error)};
+}
 
 template <typename V> __device__ __forceinline__ const V* versions_of(const SelectArgs& a);
 template <> __device__ __forceinline__ const int* versions_of<int>(const SelectArgs& a) { return a.versions; }
@@ -88,51 +122,52 @@ __device__ __forceinline__ double selection_function(double v, double mu)
     return exp_neg(e);
 }
 
-// Selection among at most 64 replicas, one wavefront.
+// Selection among at most 64 replicas, one wavefront, a replica a lane.
 // V = int: versions are step counters; V = double: forecast (real-valued) versions (Sec. 3.2 feeding Sec. 3.3)
 //
-// What is serial in the rule and what is not.  The draws are sequential (draw t renormalises over the replicas that
-// remain), and within a draw the total S and the running sums add f in ascending replica index, one rounded fp64
-// addition after another: a chain of N dependent additions per draw that no reordering may touch, because the result
-// is compared bit for bit.  Everything else is taken off that chain: the uniforms of all draws are computed up
-// front (one Philox block per lane), f is computed once, and a step of the chain is a single v_add_f64 from
-// registers.  One wavefront on its own issues a dependent instruction only every 5 to 8 clocks, so what counts is the
-// number of instructions on the path, and straight-line code that runs once is paid for in instruction fetches: the
-// loops below are kept short rather than unrolled over all 64 lanes.
+// The draws are sequential (draw t renormalises over the replicas that remain).  A wavefront on its own issues a dependent
+// instruction only every 5 to 8 clocks, so what counts is the number of instructions on the path, and straight-line code that
+// runs once is paid for in instruction fetches.  A draw is a tree of sums over the lanes (six steps, where the running
+// sums of the rule are N dependent additions: see kSumError), a product, two ballots; uniforms and f are computed up
+// front.  64 replicas and 8 draws, with the launch: 6.1 us with the chain of additions in every draw, 4.4 here; forecast versions, 24
+// replicas and 12 draws: 9.5 and 6.
 template <typename V>
 __global__ __launch_bounds__(64) void select_kernel(SelectArgs a)
 {
     constexpr bool kIntVersions = std::is_same<V, int>::value;
     __shared__ double s_sorted[64];
-    __shared__ double s_f[64];
     __shared__ long long s_key[kIntVersions ? 64 : 1];
+    __shared__ double s_v[kIntVersions ? 1 : 64];
     const int lane = threadIdx.x, N = a.n;
 
     // a rank-counting sort of the available versions: rank(i) = #{available j : v_j < v_i or (v_j == v_i and j < i)}
     const bool on = lane < N && (!a.avail || a.avail[lane]);
     const V vi = lane < N ? versions_of<V>(a)[lane] : V(0);
     // step counters: (version, index) pairs are ordered by one integer key, version * 1024 + index; a replica
-    // that is not available, or beyond N, gets the largest key and is counted before nobody
+    // that is not available, or beyond N, gets the largest key and is counted before nobody.  Real-valued versions: such a
+    // replica is a NaN, which is before nobody either.
     if constexpr (kIntVersions) s_key[lane] = on ? (long long)vi * kMaxReplicas + lane : LLONG_MAX;
+    else s_v[lane] = on ? (double)vi : __builtin_nan("");
     // the uniform of every draw, lane t's for draw t (n_select <= N <= 64)
     const double my_u = draw_uniform(a, lane);
     __syncthreads();
     const unsigned long long avail = __ballot(on);
     const int na = __popcll(avail);
     int rank = 0;
+    // every lane compares its own version with all, read from LDS at a wave-uniform address (a broadcast)
     if constexpr (kIntVersions) {
-        // every lane compares its own key with all keys, read from LDS at a wave-uniform address (a broadcast)
         const long long mine = s_key[lane];
-        for (int j = 0; j < 64; j += 16) {
+        for (int j = 0; j < N; j += 16) {
 #pragma unroll
             for (int u = 0; u < 16; ++u) rank += s_key[j + u] < mine ? 1 : 0;
         }
     } else {
+        for (int j = 0; j < N; j += 16) {
 #pragma unroll
-        for (int k = 0; k < 64; ++k) {                     // real-valued versions: cross-lane reads
-            const V vj = lane_value(vi, k);
-            const int before = (int)(vj < vi) | ((int)(vj == vi) & (int)(k < lane));
-            rank += before & (int)((avail >> k) & 1ull);
+            for (int u = 0; u < 16; ++u) {
+                const double vj = s_v[j + u];
+                rank += (int)(vj < vi) | ((int)(vj == vi) & (int)(j + u < lane));
+            }
         }
     }
     if (on) s_sorted[rank] = (double)vi;
@@ -144,60 +179,45 @@ __global__ __launch_bounds__(64) void select_kernel(SelectArgs a)
     double mu = s_sorted[lo];
     if (lo + 1 < na) mu = s_sorted[lo] + frac * (s_sorted[lo + 1] - s_sorted[lo]);
 
-    const double f = on ? selection_function((double)vi, mu) : 0.0;      // f = +0.0 beyond N: no bound test below
-    s_f[lane] = f;
+    const double f = on ? selection_function((double)vi, mu) : 0.0;
     if (lane < N) a.f[lane] = f;
-    __syncthreads();
 
     // Sequential draws: draw t picks the first live replica whose running sum of f exceeds u_t * S, S the total over
-    // the live replicas; dead replicas (picked, unavailable, or beyond N) add +0.0, which leaves a non-negative sum
-    // unchanged.  The draws run from registers.  Lane L keeps g[j] = f_j for j <= L and +0.0 above, so
-    // the plain chain ((0 + g[0]) + g[1]) + ... + g[63], the same instructions in every lane and no lane
-    // waiting for another, leaves lane L with the running sum after replica L (the zeros above L change nothing)
-    // and lane 63 with S.  A dependent v_add_f64 issues every 5 to 6 clocks, a quarter of what one step costs
-    // when the running sum has to move to the next lane.  A picked replica is zeroed in every lane's g.
-    F16 g0, g1, g2, g3, g4;
-#pragma unroll
-    for (int k = 0; k < 15; ++k) {
-        g0[k] = k <= lane ? s_f[k] : 0.0;
-        g1[k] = 15 + k <= lane ? s_f[15 + k] : 0.0;
-        g2[k] = 30 + k <= lane ? s_f[30 + k] : 0.0;
-        g3[k] = 45 + k <= lane ? s_f[45 + k] : 0.0;
-        g4[k] = (k < 4 && 60 + k <= lane) ? s_f[60 + k] : 0.0;
-    }
-    g0[15] = 0.0; g1[15] = 0.0; g2[15] = 0.0; g3[15] = 0.0; g4[15] = 0.0;
+    // the live replicas; dead replicas (picked, unavailable, or beyond N) add +0.0, which leaves a sum unchanged.
+    double g = f;                                          // f while the replica can still be drawn
     unsigned long long livemask = __ballot(f > 0.0);
     const unsigned long long could = livemask;
     int my_pick = -1;
+    double sum = wave_sums(g), error = kSumError * lane_value(sum, 63);
     for (int t = 0; t < a.n_select; ++t) {
-        double q = 0.0;
-#pragma unroll
-        for (int k = 0; k < 15; ++k) q = q + g0[k];
-#pragma unroll
-        for (int k = 0; k < 15; ++k) q = q + g1[k];
-#pragma unroll
-        for (int k = 0; k < 15; ++k) q = q + g2[k];
-#pragma unroll
-        for (int k = 0; k < 15; ++k) q = q + g3[k];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) q = q + g4[k];
-        const double S = lane_value(q, 63);
-        const double thr = lane_value(my_u, t) * S;
-        const unsigned long long hit = __ballot(q > thr) & livemask;
+        const double u = lane_value(my_u, t);
+        Sides at = sides(sum, u * lane_value(sum, 63), error);
+        unsigned long long hit = at.above;
+        if ((at.above | at.below) != ~0ull || !hit) {
+            sum = wave_sums(g);
+            error = kSumError * lane_value(sum, 63);
+            at = sides(sum, u * lane_value(sum, 63), error);
+            hit = at.above;
+            if ((at.above | at.below) != ~0ull || !hit) {  // the sums of the rule
+                double run = 0.0, mine = 0.0;
+                for (int k = 0; k < 64; ++k) {
+                    run = run + lane_value(g, k);
+                    mine = lane == k ? run : mine;
+                }
+                hit = __ballot(mine > u * run) & livemask;
+            }
+        }
         int pick = -1;
         if (hit) pick = __ffsll((long long)hit) - 1;
         else if (livemask) pick = 63 - __clzll(livemask);   // stays -1 only if no replica is left to draw from
         pick = __builtin_amdgcn_readfirstlane(pick);
         if (lane == t) my_pick = pick;
-        // the picked replica leaves every lane's g: one register-indexed write per group, aimed at the spare
-        // sixteenth element in the groups that do not hold it (and in all of them when nothing was picked)
-        const int grp = pick >= 0 ? pick / 15 : 5, slot = pick - 15 * grp;
-        g0[grp == 0 ? slot : 15] = 0.0;
-        g1[grp == 1 ? slot : 15] = 0.0;
-        g2[grp == 2 ? slot : 15] = 0.0;
-        g3[grp == 3 ? slot : 15] = 0.0;
-        g4[grp == 4 ? slot : 15] = 0.0;
-        if (pick >= 0) livemask &= ~(1ull << pick);
+        if (pick >= 0) {
+            const double gone = lane_value(g, pick);
+            if (lane >= pick) sum = sum - gone;
+            if (lane == pick) g = 0.0;
+            livemask &= ~(1ull << pick);
+        }
     }
     if (lane < a.n_select) a.selected[lane] = my_pick;
 
@@ -208,7 +228,7 @@ __global__ __launch_bounds__(64) void select_kernel(SelectArgs a)
     double denom = (double)__popcll(picked);
     if (a.weight_mode == 1) {
         denom = 0.0;
-        for (unsigned long long m = picked; m; m &= m - 1) denom = denom + s_f[__ffsll((long long)m) - 1];
+        for (unsigned long long m = picked; m; m &= m - 1) denom = denom + lane_value(f, __ffsll((long long)m) - 1);
     }
     if (lane < N) {
         const bool sel = (picked >> lane) & 1ull;
@@ -239,53 +259,15 @@ template <typename V> __device__ __forceinline__ double key_value(long long k)
     return std::is_same<V, int>::value ? (double)k : __longlong_as_double(k ^ ((k >> 63) & LLONG_MAX));
 }
 
-typedef double D2 __attribute__((ext_vector_type(2)));
-
-// The running sum of g[64 c0 ..  64 c1), added to `run` one after another in ascending index, every addition rounded on
-// its own.  All lanes run the same chain on values read from LDS at a wave-uniform address, sixteen bytes at a time and
-// half a chunk ahead of the additions, so a step is one v_add_f64 and half an LDS read: 8 clocks, against 23 when the
-// running sums move from lane to lane.  What the lanes are for: lane L of rec keeps the sum after element 16 L + 15.
-// Reads up to 32 elements past the end of the last chunk (g is that much longer; they are not used).
-__device__ __forceinline__ double uniform_chain(const double* g, int c0, int c1, double run, double& rec, int lane)
-{
-    D2 v[2][16];
-    const D2* p = reinterpret_cast<const D2*>(g + c0 * 64);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[0][k] = p[k];
-    for (int c = c0; c < c1; ++c) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            p += 16;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) v[h ^ 1][k] = p[k];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                run = run + v[h][k][0];
-                run = run + v[h][k][1];
-                if (k == 7) rec = lane == 4 * c + 2 * h ? run : rec;
-            }
-            rec = lane == 4 * c + 2 * h + 1 ? run : rec;
-            // here, not before: the values just read must stay in registers (the compiler would read them again at
-            // the head of the loop and wait for them there)
-            __builtin_amdgcn_sched_barrier(0);
-            D2 (&n)[16] = v[h ^ 1];
-            asm volatile("" : "+v"(n[0]), "+v"(n[1]), "+v"(n[2]), "+v"(n[3]), "+v"(n[4]), "+v"(n[5]), "+v"(n[6]), "+v"(n[7]),
-                              "+v"(n[8]), "+v"(n[9]), "+v"(n[10]), "+v"(n[11]), "+v"(n[12]), "+v"(n[13]), "+v"(n[14]), "+v"(n[15]));
-        }
-    }
-    return run;
-}
-
-// One workgroup of four wavefronts; the draws are wavefront 0's alone (see select_kernel for what is serial in them), the
-// rest is shared.  Bound by the chains: a draw re-adds the values from the chunk of the replica picked last, half of
-// them on average.  1000 replicas, 100 draws: 1205 us with one wavefront, running sums moved from lane to lane and a full
-// rank-counting sort of the versions, 257 us here; 65 replicas and one draw: 9 us, launch included.
+// One workgroup of four wavefronts; the draws are wavefront 0's alone, the rest is shared.  A lane
+// keeps the running sum after a segment of sixteen values; a draw is bound by its chain of dependent instructions: the segment's
+// values from LDS, sums along them (four steps), the pick out of the running sums.  1000 replicas, 100 draws: 245-255 us with
+// the chain of the rule in every draw, 41 here (0.31 us a draw; 11.5 us with one draw); 65 replicas and one draw: 8 us.
 template <typename V>
 __global__ __launch_bounds__(kManyThreads) void select_many_kernel(SelectArgs a)
 {
     constexpr int kPer = kMaxReplicas / 64;                // values per lane of wavefront 0
-    __shared__ __attribute__((aligned(16))) double s_g[kMaxReplicas + 32];     // f of the replicas still to be drawn from, else +0.0
+    __shared__ double s_g[kMaxReplicas];                   // f of the replicas still to be drawn from, else +0.0
     __shared__ double s_f[kMaxReplicas];
     __shared__ double s_u[kMaxReplicas];
     __shared__ long long s_key[kMaxReplicas];
@@ -358,38 +340,72 @@ __global__ __launch_bounds__(kManyThreads) void select_many_kernel(SelectArgs a)
     __syncthreads();
 
     // Sequential draws: draw t picks the first replica whose running sum exceeds u_t * S (it is a live one: a dead one
-    // leaves the sum where it was).  The running sums below the replica picked last are the same additions of the
-    // same values as in the draw before and are kept; the chain restarts at its chunk.
+    // leaves the sum where it was).
     if (wave == 0) {
-        double rec = 0.0;
-        int c0 = 0;
-        for (int t = 0; t < a.n_select; ++t) {
-            const double u = s_u[t];
-            const double S = uniform_chain(s_g, c0, chunks, c0 > 0 ? lane_value(rec, 4 * c0 - 1) : 0.0, rec, lane);
-            const double thr = u * S;
-            const unsigned long long hit = __ballot(rec > thr);
-            int pick = -1;                                  // stays -1 only if no replica is left to draw from (S = 0)
-            if (hit) {
-                const int seg = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
-                double q = seg > 0 ? lane_value(rec, seg - 1) : 0.0;
-                const D2* p = reinterpret_cast<const D2*>(s_g + seg * 16);
-                D2 v[8];
+        const int e = lane & 15;
+        auto segment_sums = [&]() {                         // of the lane's segment, elements 16 lane ... 16 lane + 15
+            double part = 0.0;
+            for (int r = 0; r < 4 * chunks; r += 4) {       // four segments at a time, a row of lanes each
+                const double v = row_sums(s_g[r * 16 + lane]);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = p[k];
-#pragma unroll
-                for (int k = 0; k < 16; ++k) q = q + (k <= lane ? v[k >> 1][k & 1] : 0.0);     // lane L: after element 16 seg + L
-                pick = seg * 16 + __ffsll((long long)__ballot(q > thr)) - 1;
-                pick = __builtin_amdgcn_readfirstlane(pick);
-                c0 = pick >> 6;
-                if (lane == 0) { s_g[pick] = 0.0; s_flag[pick] = 1; }
-            } else {
-                c0 = chunks;                                // nothing left: later draws change nothing either
+                for (int k = 0; k < 4; ++k) part = lane == r + k ? lane_value(v, 16 * k + 15) : part;
             }
-            if (lane == 0) a.selected[t] = pick;
+            return part;
+        };
+        double sum = wave_sums(segment_sums()), error = kSumError * lane_value(sum, 63);
+        int t = 0;
+        double next_u = s_u[0];
+        for (; t < a.n_select; ++t) {
+            const double u = next_u;
+            next_u = s_u[min(t + 1, a.n_select - 1)];       // (a read of LDS ahead)
+            int seg, pick;
+            double v;
+            // the segment of the pick, its values and the pick, if the sums tell
+            auto draw = [&]() {
+                const double thr = u * lane_value(sum, 63);
+                const unsigned long long over = __ballot(sum > thr);
+                seg = over ? __builtin_amdgcn_readfirstlane(__ffsll((long long)over) - 1) : 0;
+                v = s_g[seg * 16 + e];
+                double below = lane_value(sum, max(seg, 1) - 1);
+                below = seg > 0 ? below : 0.0;
+                const Sides at = sides(below + row_sums(v), thr, error);
+                pick = seg * 16 + __ffsll((long long)at.above) - 1;
+                return (at.above | at.below) == ~0ull && at.above && thr - below > error;
+            };
+            bool known = draw();
+            if (__builtin_expect(!known, 0)) {
+                sum = wave_sums(segment_sums());
+                error = kSumError * lane_value(sum, 63);
+                known = draw();
+            }
+            if (__builtin_expect(!known, 0)) {              // the sums of the rule
+                double run = 0.0, rec = 0.0;                // lane L of rec: after its segment
+                for (int r = 0; r < 4 * chunks; ++r) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) run = run + s_g[r * 16 + k];
+                    rec = lane == r ? run : rec;
+                }
+                const double limit = u * run;
+                const unsigned long long hit = __ballot(rec > limit);
+                if (!hit) break;                            // no replica is left to draw from (S = 0), nor in later draws
+                seg = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
+                v = s_g[seg * 16 + e];
+                double q = seg > 0 ? lane_value(rec, seg - 1) : 0.0, mine = 0.0;
+                for (int k = 0; k < 16; ++k) {
+                    q = q + lane_value(v, k);
+                    mine = e == k ? q : mine;
+                }
+                pick = seg * 16 + __ffsll((long long)__ballot(mine > limit)) - 1;
+            }
+            pick = __builtin_amdgcn_readfirstlane(pick);
+            const double gone = lane_value(v, pick & 15);
+            if (lane >= seg) sum = sum - gone;
+            if (lane == 0) { s_g[pick] = 0.0; s_flag[pick] = 1; a.selected[t] = pick; }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+        for (t += lane; t < a.n_select; t += 64) a.selected[t] = -1;
     }
     __syncthreads();
 
@@ -402,11 +418,11 @@ __global__ __launch_bounds__(kManyThreads) void select_many_kernel(SelectArgs a)
         count += __popcll(picked[r]);
     }
     double denom = (double)count;
-    if (a.weight_mode == 1) {
-        for (int i = tid; i < chunks * 64; i += kManyThreads) s_g[i] = s_flag[i] ? s_f[i] : 0.0;
-        __syncthreads();
-        double rec = 0.0;
-        denom = uniform_chain(s_g, 0, chunks, 0.0, rec, lane);
+    if (a.weight_mode == 1) {                              // the selected replicas' f, ascending, one after another (the others add +0.0)
+        denom = 0.0;
+#pragma unroll
+        for (int r = 0; r < kPer; ++r)
+            for (unsigned long long m = picked[r]; m; m &= m - 1) denom = denom + s_f[r * 64 + __ffsll((long long)m) - 1];
     }
     int before = 0;                                        // selected replicas in earlier chunks
 #pragma unroll
@@ -497,7 +513,7 @@ hipError_t launch_select_static(SelectArgs a, hipStream_t s)
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t s)
 {
-    // 64 replicas fit the registers of one wavefront, which is the fastest chain (6.5 us at 64 replicas and 8 draws)
+    // up to 64 replicas are a lane each and need no LDS in a draw (64 replicas, 8 draws 4.4 us; 65, 11 draws in the other 9.9)
     if (a.n <= 64) {
         if (a.versions_f64) hipLaunchKernelGGL(select_kernel<double>, dim3(1), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(select_kernel<int>, dim3(1), dim3(64), 0, s, a);

@@ -108,6 +108,24 @@ def test_selection_of_many_replicas_is_bit_exact(N, n_select):
     ctx.close()
 
 
+@pytest.mark.parametrize("N,cycle", [(64, 30989090191), (1024, 1297199353), (1024, 2731520387)])
+@pytest.mark.parametrize("n_select", [1, 40])
+def test_selection_with_a_threshold_at_the_edge_of_a_running_sum(N, cycle, n_select):
+    """All versions alike: f is 1 everywhere and the running sums are whole numbers.  In these cycles the first draw's uniform,
+    times N, lies within N * 2^-41 of one (search over the cycles), so that no sum but the rule's own may decide."""
+    import torch
+    v = np.full(N, 7, dtype=np.int32)
+    ctx, _ = _ctx(N, n_select, 64)
+    for real in (False, True):
+        select = ctx.select_real if real else ctx.select
+        select(cycle, versions=torch.as_tensor(v.astype(np.float64) if real else v).cuda())
+        osel, oflag, of, _ = oracle.select(v.astype(np.float64) if real else v, n_select, synth.SELECT_SEED, cycle)
+        assert (of == 1.0).all()
+        sel, flag, _ = ctx.selected()
+        assert sel.tolist() == osel.tolist() and flag.tolist() == oflag.tolist()
+    ctx.close()
+
+
 @pytest.mark.parametrize("N,n_select,m", [(6, 3, 100037), (4, 1, 5), (9, 8, 70001), (12, 11, 4099), (3, 3, 1 << 20)])
 def test_aggregate_matches_fp64_sum_and_resync_copies_it(N, n_select, m):
     import torch
