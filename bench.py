@@ -68,7 +68,7 @@ def measured_traffic(kernel, workload):
     return ent[2] if digest == ent[1] else None
 
 
-GEMM_KERNELS = ("conv_fwd", "conv_dgrad", "conv_wgrad", "dense_fwd", "dense_dgrad", "dense_wgrad")
+GEMM_KERNELS = ("conv_fwd", "conv_dgrad", "conv_wgrad", "dense_fwd", "dense_dgrad", "dense_wgrad", "dense_step")
 
 
 def build_training(c):

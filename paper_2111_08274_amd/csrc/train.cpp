@@ -196,6 +196,26 @@ bool dense_rows_pays(const hadfl_config& cfg, const NetPlan& plan, const Layer& 
     return l.in0 != 0 || tiles <= (cfg.bf16 && plan.tensors[0].numel() < 512 ? 256 : 384);
 }
 
+// The network is a dense layer on the data set with a ReLU and a classifier behind it, of a size for dense_pair_kernel.  Four
+// steps a call, us a step layer by layer and there, batch 8 / 32 / 64 / 128:
+//   784 features, 128 hidden units:   4 replicas 27 30 34 44 and 17 19 26 41,   16: 31 34 47 71 and 18 20 27 42,   64: 45 72 87 113 and 38 42 57 87
+//   1024 features, 256 hidden units:  4: 31 35 40 69 and 21 24 34 57,   32: 51 78 93 121 and 48 54 75 120,   64: 103 114 139 202 and 92 106 147 256
+// The last has four workgroups a compute unit: beyond two the batches above 32 stay with the single layers.  A call of one step has
+// no beginning to share a launch with: one replica, batch 128 42 and 46, 64 34 and 31, hence eight replicas above 64.  512 hidden units,
+// 128 features, 16 replicas: 28 31 40 76 and 27 29 46 82.  Rows of fewer than 128 features leave waves without a block; they stay
+// with the single layers' kernels, though this one would be the faster for them too (32 features, 64 hidden units, 4 replicas: 21 22 28 37 and
+// 9 10 13 20), so that networks of a few features still run those.
+bool dense_pair_net(const hadfl_config& cfg, const NetPlan& plan)
+{
+    if (plan.layers.size() != 3) return false;
+    const Layer &a = plan.layers[0], &r = plan.layers[1], &b = plan.layers[2];
+    if (a.type != HADFL_OP_DENSE || a.in0 != 0 || r.type != HADFL_OP_RELU || r.in0 != a.out || b.type != HADFL_OP_DENSE || b.in0 != r.out) return false;
+    if (b.cout != cfg.n_classes || (a.bias && a.b_off != a.w_off + a.w_count) || (b.bias && b.b_off != b.w_off + b.w_count)) return false;
+    const int64_t K = plan.tensors[0].numel();
+    if (K < 128 || a.cout > 256 || (cfg.batch > 64 && cfg.n_replicas < 8) || (cfg.batch > 32 && a.cout / 16 * cfg.n_replicas > 512)) return false;
+    return K <= 1024 && dense_pair_supported(cfg.batch, (int)K, a.cout, b.cout);
+}
+
 // Directions of a general layer that run there.  A convolution on the data set is gathered value by value, which pays where the
 // generic kernel (gemm.hip) would gather too.  That one reads its source in 16-byte pieces when the channels come in sixteens
 // (forward) or fours (weight gradient), and is then the faster one, but for footprints that are one tile of 32 rows.
@@ -700,6 +720,31 @@ struct Runner {
         return p;
     }
 
+    // All steps of a network of two dense layers, the end of each with the beginning of the next
+    void dense_pair_steps()
+    {
+        const Layer &a = e.plan.layers[0], &b = e.plan.layers[2];
+        const int t = e.out_tensor[0];
+        DensePairParams d{};
+        d.x = e.buf.x; d.y = e.buf.y; d.cursor = e.buf.cursor; d.n_samples = e.cfg.n_samples; d.batch = e.cfg.batch;
+        d.K = (int)e.plan.tensors[0].numel(); d.H = a.cout; d.N = b.cout; d.has_bias1 = a.bias; d.has_bias2 = b.bias;
+        d.w1 = e.buf.replicas + a.w_off; d.w2 = e.buf.replicas + b.w_off; d.w_rep = e.plan.row_stride;
+        d.m1 = e.buf.mom ? e.buf.mom + a.w_off : nullptr; d.m2 = e.buf.mom ? e.buf.mom + b.w_off : nullptr;
+        d.lr = e.cfg.lr; d.momentum = e.cfg.momentum;
+        d.hidden = actw(t); d.share = grad(t); d.act_rep = e.rep_block;      // (the shares take the room of the hidden units' gradient)
+        d.loss = e.buf.loss; d.bf16 = e.cfg.bf16; d.order = e.buf.order;
+        const double macs = (double)d.batch * ((double)d.K * d.H + (double)d.H * d.N), wbytes = 4.0 * (d.K + d.N) * d.H;
+        cur_layer = 0;
+        for (int s0 = 0; s0 <= e.e_max; ++s0) {
+            d.ahead = s0;
+            d.n_end = s0 > 0 ? e.n_active[s0 - 1] : 0; d.n_begin = s0 < e.e_max ? e.n_active[s0] : 0;
+            na = 1;
+            run("dense_step", 2.0 * (macs * d.n_begin + (macs + (double)d.batch * d.H * d.N) * d.n_end),
+                (4.0 * d.batch * d.K + wbytes) * d.n_begin + (4.0 * d.batch * d.K + (d.m1 ? 4.0 : 2.0) * wbytes) * d.n_end, [&] { return launch_dense_pair(d, s); });
+        }
+        na = 0;
+    }
+
     void forward_layer(size_t i)
     {
         cur_layer = (int)i;
@@ -1098,7 +1143,8 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
     }
     const int T = (int)e->plan.tensors.size();
     e->prepped.assign(e->plan.layers.size(), 0);       // the weights may have changed since the last call (aggregation)
-    for (int step = 0; step < e->e_max && r.rc == hipSuccess; ++step) {
+    if (dense_pair_net(e->cfg, e->plan)) r.dense_pair_steps();
+    else for (int step = 0; step < e->e_max && r.rc == hipSuccess; ++step) {
         r.na = e->n_active[step]; r.step = step;
         r.prepare_weights();
         for (size_t i = 0; i < e->plan.layers.size(); ++i) r.forward_layer(i);

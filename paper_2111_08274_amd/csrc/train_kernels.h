@@ -222,6 +222,24 @@ struct DenseSmallParams {     // dense layer with N <= 16 outputs.  Forward: out
 hipError_t launch_dense_small_fwd(const DenseSmallParams& p, int n_active, hipStream_t s);
 hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipStream_t s);
 
+// A network of two dense layers, H hidden units with a ReLU and N classes: the end of a local step of the first n_end replicas in
+// step order and the beginning of the next of the first n_begin, in one launch.
+struct DensePairParams {
+    const float* x; const int* y; const long long* cursor; int ahead;    // ahead: steps of the call before the one that begins
+    int n_samples, batch, K, H, N;
+    int has_bias1, has_bias2;
+    float* w1; float* w2; long long w_rep;   // weights [K][H] followed by bias [H]; [H][N] followed by bias [N]
+    float* m1; float* m2;                    // momentum of the same, or null; same stride
+    float lr, momentum;
+    float* hidden; float* share; long long act_rep;      // hidden units [batch][H]; shares of the logits, floats [H / 16][batch][16]
+    float* loss;
+    int n_end, n_begin;
+    int bf16;
+    const int* order;
+};
+bool dense_pair_supported(int batch, int K, int H, int N);
+hipError_t launch_dense_pair(const DensePairParams& p, hipStream_t s);
+
 struct EwParams {     // element-wise / pooling kernels
     const float* in; long long in_rep;
     const float* in2; long long in2_rep;

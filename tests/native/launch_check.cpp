@@ -212,6 +212,17 @@ void look(const std::string& name, dim3 grid, void** args)
         if (p.cursor) l.data(p.x, p.n_samples, p.rows, p.K); else l.act(p.x, p.x_rep, (long long)p.rows * p.K);
         l.act(p.out, p.out_rep, (long long)p.rows * p.N);
         l.tensor(kParam, p.w, p.w_rep, (long long)(p.K + (p.has_bias ? 1 : 0)) * p.N * 4);
+    } else if (has(name, "dense_pair")) {
+        const DensePairParams& p = *(DensePairParams*)args[0];
+        l.order = p.order; l.n = std::max(p.n_end, p.n_begin); l.es = p.bf16 ? 2 : 4;
+        l.data(p.x, p.n_samples, p.batch, p.K);
+        l.act(p.hidden, p.act_rep, (long long)p.batch * p.H);
+        l.tensor(kAct, p.share, p.act_rep, (long long)p.H * p.batch * 4);
+        l.tensor(kParam, p.w1, p.w_rep, (long long)(p.K + (p.has_bias1 ? 1 : 0)) * p.H * 4);
+        l.tensor(kParam, p.w2, p.w_rep, (long long)(p.H + (p.has_bias2 ? 1 : 0)) * p.N * 4);
+        l.tensor(kMom, p.m1, p.w_rep, (long long)(p.K + (p.has_bias1 ? 1 : 0)) * p.H * 4);
+        l.tensor(kMom, p.m2, p.w_rep, (long long)(p.H + (p.has_bias2 ? 1 : 0)) * p.N * 4);
+        use(name, kState, p.loss, 4 * l.n);
     } else if (has(name, "dense_small")) {
         const DenseSmallParams& p = *(DenseSmallParams*)args[0];
         l.order = p.order; l.n = (int)grid.y; l.es = p.bf16 ? 2 : 4;
