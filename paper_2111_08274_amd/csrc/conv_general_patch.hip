@@ -348,6 +348,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
         float* const area = reinterpret_cast<float*>(smem) + wave * (32 * P);
         T* const obase = reinterpret_cast<T*>(p.out + (long long)rep * p.out_rep);
         const float* bias = (EPI == 0 && p.bias) ? p.bias + (long long)rep * p.bias_rep : nullptr;
+        const T* const added = p.addend ? reinterpret_cast<const T*>(p.addend + (long long)rep * p.addend_rep) : obase;
         const T* mask = (EPI == 1 && p.mask) ? reinterpret_cast<const T*>(p.mask + (long long)rep * p.mask_rep) : nullptr;
         // data gradient with statistics: values of the tensor whose gradient this is (see FastConvParams::stat_y)
         const T* ysrc = (EPI == 1 && stats) ? reinterpret_cast<const T*>(p.stat_y + (long long)rep * p.stat_y_rep) : nullptr;
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
                     unsigned o;
                     if (!offset(i, t, o)) continue;
                     if (mask) mk[t].load(mask + o);
-                    if (p.accumulate) old[t].load(obase + o);
+                    if (p.accumulate) old[t].load(added + o);
                 }
             }
             wave_lds_fence();                                 // the block before has been read
@@ -397,8 +398,8 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
                 } else {
 #pragma unroll
                     for (int e = 0; e < VE; ++e) {
-                        if (mask && !(mk[t].at(e) > 0.f)) v[e] = 0.f;
                         if (p.accumulate) v[e] += old[t].at(e);
+                        if (mask && !(mk[t].at(e) > 0.f)) v[e] = 0.f;
                     }
                 }
                 Vec<T> out;

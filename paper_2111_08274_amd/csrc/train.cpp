@@ -48,6 +48,11 @@ public:
     // but for those with no ReLU mask and no other reader: their gradient IS the sum's, and shares its buffer.
     std::vector<int> add_into;            // per layer (BN): the ADD layer folded into its forward store, or -1
     std::vector<char> add_done;           // per layer (ADD): forward folded away
+    // An operand that does need a copy, but whose next gradient comes from a convolution run from patches (the shortcut of a residual block
+    // without a convolution in it: the block's first convolution), gets none: that convolution's data gradient adds the sum's
+    // gradient from where it lies.
+    std::vector<char> late_add;           // per layer (ADD): bit 0, 1: operand 0, 1 is one of these
+    std::vector<int> pending_grad;        // per tensor, scratch for the backward pass: the tensor whose gradient is still to be added, or -1
     // Statistics fusion: a lean or general convolution whose output feeds a batch norm only leaves the per-channel
     // sums of its output in the BN partial region, and that BN's forward skips its own sums pass.
     std::vector<int> stat_for;            // per layer: the BN layer fed by this convolution's statistics, or -1
@@ -502,6 +507,18 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
                 if (plan.layers[i].type == HADFL_OP_BN && !e->fused_relu[i] && e->pool_of[i] < 0 && other < t && plan.tensors[t].c % vec == 0) {
                     e->add_into[i] = j; e->add_done[j] = 1;
                 }
+            }
+        }
+        e->late_add.assign(nl, 0);
+        for (int j = 0; j < nl; ++j) {
+            const Layer& q = plan.layers[j];
+            if (q.type != HADFL_OP_ADD || q.in0 == q.in1) continue;
+            for (int side = 0; side < 2; ++side) {
+                const int t = side ? q.in1 : q.in0;
+                if (t < 1 || e->grad_off[t] == e->grad_off[e->out_tensor[j]]) continue;
+                int i = j - 1;                             // the reader whose gradient of t follows
+                while (i >= 0 && plan.layers[i].in0 != t && !(plan.layers[i].type == HADFL_OP_ADD && plan.layers[i].in1 == t)) --i;
+                if (i >= 0 && plan.layers[i].type == HADFL_OP_CONV && e->patch[i]) e->late_add[j] |= 1 << side;
             }
         }
         e->bstat_for.assign(nl, -1); e->bstat_rows.assign(nl, 0); e->bstat_rep.assign(nl, 0);
@@ -1067,6 +1084,8 @@ struct Runner {
                     f.wmat = wbf() + e.wb_off[i];
                     f.out = grad(l.in0);
                     f.mask = mask0; f.mask_rep = e.rep_block; f.accumulate = acc0;
+                    int& pending = e.pending_grad[l.in0];
+                    if (pending >= 0) { f.addend = grad(pending); f.addend_rep = e.rep_block; pending = -1; }
                     int* brows = nullptr;
                     if (e.bstat_for[i] >= 0 && !acc0) brows = gradient_sums(f, i, d, false);
                     run(l.type == HADFL_OP_CONV ? "conv_dgrad" : "dense_dgrad", gemm_flops(d), gemm_bytes(d), [&] { return e.patch[i] ? launch_conv_general_patch(f, 1, na, s, brows) : launch_conv_general(f, 1, na, s); });
@@ -1087,12 +1106,15 @@ struct Runner {
         case HADFL_OP_ADD: {
             q.in = grad(ot); q.in_rep = e.rep_block; q.count = B * a.numel();
             const int64_t own = e.grad_off[ot];                // operands that share this buffer need no copy
-            if (e.grad_off[l.in0] != own) run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q, na, s); });
+            const bool late0 = !acc0 && (e.late_add[i] & 1), late1 = !e.grad_written[l.in1] && (e.late_add[i] & 2);
+            if (late0) e.pending_grad[l.in0] = ot;
+            else if (e.grad_off[l.in0] != own) run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q, na, s); });
             EwParams q2 = q;
             if (l.in1 == l.in0) q2.accumulate = 1; else q2.accumulate = e.grad_written[l.in1] ? 1 : 0;
             q2.out = grad(l.in1);
             q2.mask = e.masked[l.in1] ? act(l.in1) : nullptr;
-            if (e.grad_off[l.in1] != own) run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q2, na, s); });
+            if (late1) e.pending_grad[l.in1] = ot;
+            else if (e.grad_off[l.in1] != own) run("add_bwd", 0, asz() * (8.0 * q.count), [&] { return launch_pass_grad(q2, na, s); });
             e.grad_written[l.in1] = 1;
             break; }
         case HADFL_OP_GAP:
@@ -1154,6 +1176,7 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
         }
         e->grad_written.assign(T, 0);
         e->grad_written[T - 1] = 1;
+        e->pending_grad.assign(T, -1);
         r.na_next = step + 1 < e->e_max ? e->n_active[step + 1] : 0;
         for (int t : e->unread) {
             EwParams z{};

@@ -135,6 +135,8 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     const float* bias; long long bias_rep;     // forward: bias inside the replica rows, or null
     int relu;
     const float* mask; long long mask_rep; int accumulate;   // data gradient
+    // with accumulate, conv_general_patch.hip: what is added to, if not what `out` holds; not masked yet
+    const float* addend; long long addend_rep;
     const int* order;
     const int* perm; const unsigned* posmask;  // optional position table as in FastConvParams (stride 1)
     float* stat; long long stat_rep;           // forward, optional: statistics entries as in FastConvParams

@@ -105,6 +105,7 @@ void conv_general(Launch l, const GeneralConvParams& p, const std::vector<int>& 
     else l.act(p.a, p.a_rep, (long long)p.B * p.H * p.W * p.C);
     l.act(p.out, p.out_rep, out * p.N);
     l.act(p.mask, p.mask_rep, out * p.N);
+    l.act(p.addend, p.addend_rep, out * p.N);
     const bool patch = has(l.name, "patch");
     const long long units = patch ? weight_fragment_units(p.bf16, p.N, p.R * p.S, p.C)
                                   : weight_copy_units(p.bf16, p.N, p.cursor ? 1 : p.R * p.S, p.cursor ? p.R * p.S * p.C : p.C);

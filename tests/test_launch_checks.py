@@ -407,3 +407,19 @@ def test_weight_gradients_by_position(checked):
     assert_clean(checked, cases)
     out = [case(net(c, n, k), (8, 8, 3), 64, [1] * 4, bf16, classes=5) for c, n, k, bf16 in ((64, 64, 5, 0), (80, 80, 3, 0), (64, 64, 3, 1))]
     assert all(layers_in(r["trace"], "general_position") == 0 for r in checked(out))
+
+
+def test_gradient_of_a_shortcut(checked):
+    """The copy of a sum's gradient to a shortcut without a convolution is left to the block's first convolution where that runs from
+    patches, and to no other reader."""
+    cases = []
+    for ch, k in ((64, 3), (40, 3), (24, 3), (64, 1)):       # 24 channels, and 1 x 1 filters in fp32, are not for the patch kernel
+        b = nets._Builder()
+        t = b.relu(b.bn(b.conv(0, ch)))
+        for _ in range(2):
+            u = b.relu(b.bn(b.conv(t, ch, k=k, pad=k // 2)))
+            t = b.relu(b.add(b.bn(b.conv(u, ch)), t))
+        b.dense(b.gap(t), 10)
+        cases += [case(b, (8, 8, 3), 32, [1], bf16) for bf16 in (0, 1)]
+    assert [layers_in(r["trace"], "pass_grad") for r in checked(cases)] == [0, 0, 0, 0, 2, 2, 2, 0]
+    assert_clean(checked, cases)
