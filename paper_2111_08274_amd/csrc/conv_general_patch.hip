@@ -66,7 +66,7 @@ __device__ __forceinline__ void wave_lds_fence()
 // Q: passes of a group's threads over a patch (the launcher checks that they cover it).  D: taps that the weights are fetched ahead.
 // SORTED: the tile holds whole images and its rows are ordered by position, the positions sorted by their set of taps inside the
 // image (p.perm), so that a block of 32 rows leaves out the taps that none of its positions has: 5 of 9 on a 2 x 2 image.
-// EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate, (bf16) optional statistics
+// EPI 0: + bias, optional ReLU, optional statistics;  EPI 1: optional mask, optional accumulate, optional statistics
 template <typename T, int TM, int WGM, int WGN, int KG, int Q, int D, int EPI, bool SORTED, int TN>
 __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_kernel(GeneralConvParams p)
 {
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
     // instead, and lane c of the L lanes that share a pixel takes its c-th 16 bytes: whole runs of a line per instruction, in
     // stores and in the loads of the mask and of what is added to, and a lane keeps the sums of one group of channels.
     constexpr int VE = 16 / (int)ES, L = 32 * TN / VE, ST = L / 2, P = 32 * TN + 4;      // (ST: passes over a block)
-    const bool stats = (EPI == 0 || !kSplit) && p.stat != nullptr;        // per-channel sums of the outputs for a batch norm
+    const bool stats = p.stat != nullptr;                     // per-channel sums of the outputs for a batch norm, forward or backward
     float ss[VE], qq[VE];
 #pragma unroll
     for (int e = 0; e < VE; ++e) { ss[e] = 0.f; qq[e] = 0.f; }
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
         const float* bias = (EPI == 0 && p.bias) ? p.bias + (long long)rep * p.bias_rep : nullptr;
         const T* const added = p.addend ? reinterpret_cast<const T*>(p.addend + (long long)rep * p.addend_rep) : obase;
         const T* mask = (EPI == 1 && p.mask) ? reinterpret_cast<const T*>(p.mask + (long long)rep * p.mask_rep) : nullptr;
-        // data gradient with statistics: values of the tensor whose gradient this is (see FastConvParams::stat_y)
+        // data gradient with statistics: values of the tensor whose gradient this is (see FastConvParams::stat_y), or of the batch norm's input
         const T* ysrc = (EPI == 1 && stats) ? reinterpret_cast<const T*>(p.stat_y + (long long)rep * p.stat_y_rep) : nullptr;
         auto offset = [&](int i, int t, unsigned& o) {                    // pass t of block i: this lane's place in the tensors
             const int mm = m0 + pixel((i * WGM + wm) * 32 + t * (64 / L) + lane / L);
@@ -362,9 +362,14 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
 #pragma unroll
             for (int e = 0; e < VE; e += 4) *reinterpret_cast<f4*>(sh + e) = *reinterpret_cast<const f4*>(bias + n + e);
         }
+        const bool centred = EPI == 1 && stats && p.stat_mean;            // (or that input's mean)
+        if (centred && n < p.N) {
+#pragma unroll
+            for (int e = 0; e < VE; e += 4) *reinterpret_cast<f4*>(sh + e) = *reinterpret_cast<const f4*>(p.stat_mean + (long long)rep * p.stat_mean_rep + n + e);
+        }
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            Vec<T> mk[EPI == 1 ? ST : 1], old[EPI == 1 ? ST : 1];
+            Vec<T> mk[EPI == 1 ? ST : 1], old[EPI == 1 ? ST : 1], xv[EPI == 1 && kSplit ? ST : 1];
             if constexpr (EPI == 1) {
 #pragma unroll
                 for (int t = 0; t < ST; ++t) {
@@ -372,6 +377,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
                     if (!offset(i, t, o)) continue;
                     if (mask) mk[t].load(mask + o);
                     if (p.accumulate) old[t].load(added + o);
+                    if constexpr (kSplit) if (stats) xv[t].load(ysrc + o);
                 }
             }
             wave_lds_fence();                                 // the block before has been read
@@ -410,12 +416,12 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64, 2) void conv_general_patch_ker
 #pragma unroll
                         for (int e = 0; e < VE; ++e) { const float f = out.at(e) - sh[e]; ss[e] += f; qq[e] += f * f; }
                     } else {
-                        Vec<T> yv = mk[t];                    // (the mask of a fused ReLU is that very tensor)
-                        if (ysrc != mask) yv.load(ysrc + o);
+                        Vec<T> yv = kSplit ? xv[kSplit ? t : 0] : mk[t];      // (the mask of a fused ReLU is the output)
+                        if (!kSplit && ysrc != mask) yv.load(ysrc + o);
 #pragma unroll
                         for (int e = 0; e < VE; ++e) {
-                            const float f = (p.stat_relu && !(yv.at(e) > 0.f)) ? 0.f : out.at(e);
-                            ss[e] += f; qq[e] += f * yv.at(e);
+                            const float f = (!kSplit && p.stat_relu && !(yv.at(e) > 0.f)) ? 0.f : out.at(e);
+                            ss[e] += f; qq[e] += f * (yv.at(e) - sh[e]);
                         }
                     }
                 }

@@ -581,7 +581,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
         __shared__ int s_direct[32];
         __shared__ float s_sum[32][2];
         __shared__ float s_red[256][2];
-        if (p.bwd_stats_done && live) {
+        if (p.bwd_stats_done == 1 && live) {
             const float* row = p.params + rep * p.row_stride + p.w_off;
             gamma = row[c]; beta = row[p.C + c];
             direct = gamma == 0.f || !(fabsf(beta) <= kBwdStatCond * fabsf(gamma));
@@ -660,7 +660,8 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
         rm[c] = bn_running_mean(rm[c], mean + left_out);
         rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
     } else {
-        if (p.bwd_stats_done && !direct) q = (q - beta * s) / gamma;
+        if (p.bwd_stats_done == 1 && !direct) q = (q - beta * s) / gamma;
+        if (p.bwd_stats_done == 2) q = q * p.saved[rep * p.saved_rep + p.C + c];
         float* gr = p.grads + rep * p.row_stride + p.w_off;
         gr[c] = q; gr[p.C + c] = s;
         part[c] = s; part[p.C + c] = q;
@@ -1548,6 +1549,8 @@ dim3 bn_small_grid(BnParams& p, int vec, int n_active)
 }
 }  // namespace
 
+bool bn_backward_in_one_launch(const BnParams& p, int n_active) { return p.C % (p.bf16 ? 8 : 4) == 0 && bn_small(p, n_active); }
+
 hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
 {
     if (n_active < 1) return hipSuccess;
@@ -1609,6 +1612,7 @@ hipError_t launch_bn_bwd(const BnParams& p0, int n_active, hipStream_t s)
         const int cgroups = (p.C / vec + p.cvb - 1) / p.cvb;
         const dim3 grid((unsigned)(p.chunks * cgroups), (unsigned)n_active), fgrid((unsigned)((p.C + 31) / 32), (unsigned)n_active);
         if (p.pool && (p.H % 2 != 0 || p.W % 2 != 0 || p.rows % 4 != 0 || !p.pool_g)) return hipErrorInvalidValue;
+        if (p.pool && p.bwd_stats_done == 2) return hipErrorInvalidValue;
         if (p.bf16) {
             if (p.bwd_stats_done) {}                                  // the data gradient above left the sums
             else if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
@@ -1617,8 +1621,9 @@ hipError_t launch_bn_bwd(const BnParams& p0, int n_active, hipStream_t s)
             if (p.pool) hipLaunchKernelGGL(bn_apply_bwd_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
             else hipLaunchKernelGGL(bn_apply_bwd_vec_kernel<__bf16>, grid, block, 0, s, p);
         } else {
-            if (p.bwd_stats_done) return hipErrorInvalidValue;       // only the bf16 data-gradient kernels leave them
-            if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<float>, grid, block, 0, s, p);
+            if (p.bwd_stats_done == 1) return hipErrorInvalidValue;  // (of the stored output: only the bf16 data-gradient kernels leave those)
+            if (p.bwd_stats_done) {}
+            else if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<float>, grid, block, 0, s, p);
             else hipLaunchKernelGGL((bn_sums_vec_kernel<1, float>), grid, block, 0, s, p);
             hipLaunchKernelGGL((bn_finalize_kernel<1, float>), fgrid, block, 0, s, p);
             if (p.pool) hipLaunchKernelGGL(bn_apply_bwd_pool_vec_kernel<float>, grid, block, 0, s, p);

@@ -144,6 +144,9 @@ struct GeneralConvParams {     // out[pixel][n] = sum over taps and channels of 
     int tiles_m, n_active;                     // set by the launcher
     int halo; unsigned inv_hw, inv_w;          // the same (conv_general_patch.hip): pixels of border before and behind a tile, 2^32 / HW, 2^32 / W
     const float* stat_y; long long stat_y_rep; int stat_relu;      // bf16 data gradient with stat set (conv_general_patch.hip): as in FastConvParams
+    // data gradient with stat set (conv_general_patch.hip): stat_y is the INPUT of the batch norm whose output gradient this is and stat_mean
+    // its channels' means; the second sum is that of g * (stat_y - mean)
+    const float* stat_mean; long long stat_mean_rep;
 };
 // epi 0: forward (+bias, ReLU); epi 1: data gradient (mask, accumulate).  Needs C % 4 == 0 (bf16: 8), N % 4 == 0, R * S <= 32,
 // tensors of less than 4 GiB per replica.  stat_rows (may be null): rows per statistics entry of the kernel that was launched.
@@ -297,7 +300,7 @@ struct BnParams {
     const float* left_out; long long left_out_rep;
     // backward: the data-gradient kernel of the layer above already left per-entry sums of g and g * y in `partial`
     // ([stat_entries][2][C], see FastConvParams::stat_y); the sums pass is skipped and d(gamma) is formed from them
-    int bwd_stats_done;
+    int bwd_stats_done;                    // 1; 2: sums of g and g * (x - mean)
     // forward, optional (vector kernels, no pool): y = max(bn(x) + add, 0) or without the ReLU, bn(x) rounded to the stored
     // type first as if it were stored: the layer that adds a second tensor to this one's output, folded in
     const float* add; long long add_rep; int add_relu;
@@ -306,6 +309,7 @@ struct BnParams {
 };
 hipError_t launch_bn_fwd(const BnParams& p, int n_active, hipStream_t s);
 hipError_t launch_bn_bwd(const BnParams& p, int n_active, hipStream_t s);
+bool bn_backward_in_one_launch(const BnParams& p, int n_active);       // sums that a data gradient left would make it two
 
 hipError_t launch_softmax_ce(const LossParams& p, int n_active, hipStream_t s);
 

@@ -6,7 +6,7 @@ import pytest
 from oracle import nets
 from tests import parity_metrics as pm
 from tests.pair import Pair
-from tests.test_launch_checks import first_norm, interleaved, pooled, pre_activation
+from tests.test_launch_checks import first_norm, interleaved, pooled, pre_activation, residual_stages
 
 pytestmark = pytest.mark.gpu
 
@@ -27,6 +27,13 @@ def forced(builder, shape, batch, replicas, bf16):
 def test_gradient_sums_of_a_lone_batch_norm_bf16(make, batch, replicas):
     """The sums from a data gradient, for a batch norm behind the first layer, a sum or a pool."""
     forced(make(), (8, 8, 3), batch, replicas, True)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("ch,side,batch,replicas", [(40, 12, 65, 2), (64, 16, 64, 1), (64, 16, 32, 9)])
+def test_gradient_sums_of_residual_blocks(ch, side, batch, replicas, bf16):
+    """The sums, formed with a batch norm's input, from the data gradient that completes a gradient of several parts."""
+    forced(residual_stages(ch), (side, side, 3), batch, replicas, bf16)
 
 
 @pytest.mark.parametrize("ch,bf16", [(40, False), (40, True), (64, False), (64, True)])

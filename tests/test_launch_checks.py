@@ -423,3 +423,26 @@ def test_gradient_of_a_shortcut(checked):
         cases += [case(b, (8, 8, 3), 32, [1], bf16) for bf16 in (0, 1)]
     assert [layers_in(r["trace"], "pass_grad") for r in checked(cases)] == [0, 0, 0, 0, 2, 2, 2, 0]
     assert_clean(checked, cases)
+
+
+def residual_stages(ch):
+    """two blocks with plain shortcuts, a strided one with a convolution in its shortcut, one more plain one, behind a first convolution"""
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, ch)))
+    for width, stride in ((ch, 1), (ch, 1), (2 * ch, 2), (2 * ch, 1)):
+        u = b.relu(b.bn(b.conv(t, width, stride=stride)))
+        u = b.bn(b.conv(u, width))
+        t = b.relu(b.add(u, t if stride == 1 else b.bn(b.conv(t, width, k=1, stride=stride, pad=0))))
+    b.dense(b.gap(t), 10)
+    return b
+
+
+def test_backward_sums_of_residual_blocks(checked):
+    """Ten batch norms: those of the second plain block's and the last block's sums form their own, and the one under the strided
+    shortcut; the others' come from the data gradient that completes their output's gradient.  Small tensors: one launch, no
+    sums, but for those that a bf16 convolution forms from its mask."""
+    cases = [case(residual_stages(ch), (16, 16, 3), batch, [1], bf16) for ch in (40, 64) for bf16 in (0, 1) for batch in (64, 2)]
+    runs = checked(cases)
+    assert [sum("bn_sums_vec_kernelILi1" in n for n in r["trace"]) for r in runs] == [3, 0] * 4
+    assert [layers_in(r["trace"], "bn_small_bwd") for r in runs] == [0, 10, 0, 6] * 2
+    assert_clean(checked, cases)
