@@ -1163,8 +1163,11 @@ __global__ __launch_bounds__(256) void advance_kernel(const int* steps, int* ver
 
 // Narrow dense layer (the classifier: out <= 16): one workgroup per sample row; threads stride over the input
 // features, keep `out` partial sums each and combine them with a fixed butterfly and a fixed LDS order.  Too small
-// for the matrix cores.  For long rows: 4096 features, 10 outputs, 64 rows 25 us, where dense_rows_fwd_kernel takes 40; 512
-// features 9 us and 5.
+// for the matrix cores.  For long rows, whose weights come from beyond the die's L2 (the update has just written them): what
+// bounds it is the latency of a thread's loads, four features of which are in flight, two weights a load where they are even.  4096 features,
+// 10 outputs, 64 rows on 2 / 4 / 6 / 8 replicas, us: 20 20 26 30 one feature after another, 14 14 16 18 here (eight features: the same;
+// weights through LDS, fetched a piece of 256 features ahead: 22 23 24 27); dense_rows_fwd_kernel takes 40, but 5 on 512 features.
+typedef float f2 __attribute__((ext_vector_type(2)));
 template <int NMAX, typename T>
 __global__ __launch_bounds__(256) void dense_small_fwd_kernel(DenseSmallParams p)
 {
@@ -1178,14 +1181,35 @@ __global__ __launch_bounds__(256) void dense_small_fwd_kernel(DenseSmallParams p
     float acc[NMAX];
 #pragma unroll
     for (int n = 0; n < NMAX; ++n) acc[n] = 0.f;
-    for (int k = threadIdx.x; k < p.K; k += 256) {
-        const float xv = ldf(x, k);
-        const float* wr = w + (long long)k * p.N;
+    // (rows of an even number of weights start at multiples of eight bytes)
+    constexpr int kAhead = 4;                     // features whose loads are in flight together
+    const bool pairs = p.N % 2 == 0;
+    for (int k0 = threadIdx.x; k0 < p.K; k0 += 256 * kAhead) {
+        float xv[kAhead], wv[kAhead][NMAX];
 #pragma unroll
-        for (int n = 0; n < NMAX; ++n) if (n < p.N) acc[n] += xv * (kRoundW ? (float)(__bf16)wr[n] : wr[n]);
+        for (int u = 0; u < kAhead; ++u) {
+            const int k = min(k0 + 256 * u, p.K - 1);         // (beyond the last: not used)
+            xv[u] = ldf(x, k);
+            const float* const wr = w + (long long)k * p.N;
+            if (pairs) {
+#pragma unroll
+                for (int n = 0; n < NMAX; n += 2)
+                    if (n < p.N) { const f2 v = *reinterpret_cast<const f2*>(wr + n); wv[u][n] = v[0]; wv[u][n + 1] = v[1]; }
+            } else {
+#pragma unroll
+                for (int n = 0; n < NMAX; ++n) if (n < p.N) wv[u][n] = wr[n];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (k0 + 256 * u >= p.K) break;
+#pragma unroll
+            for (int n = 0; n < NMAX; ++n) if (n < p.N) acc[n] += xv[u] * (kRoundW ? (float)(__bf16)wv[u][n] : wv[u][n]);
+        }
     }
 #pragma unroll
     for (int n = 0; n < NMAX; ++n) {
+        if (n >= p.N) continue;
         float v = acc[n];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
