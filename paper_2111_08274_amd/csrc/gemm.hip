@@ -80,11 +80,18 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(GemmParams p)
     int a_b[NQA], a_y[NQA], a_x[NQA]; bool a_ok[NQA];
     // kWgrad: A is read along M for a fixed group of 4 rows m..m+3.
     int wa_m = 0, wa_r = 0, wa_s = 0, wa_c = 0;
+    int g_y[4], g_x[4]; long long g_off[4];                   // rows gathered one by one: source pixel and value relative to the output's
     if (MODE == kWgrad) {
         wa_m = m0 + (tid % (BM / 4)) * 4;
         const int tap = wa_m / p.Cin;
         wa_c = wa_m - tap * p.Cin;
         wa_r = tap / p.S; wa_s = tap - wa_r * p.S;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int m = wa_m + j, t = m / p.Cin, r = t / p.S;
+            g_y[j] = r - p.pad; g_x[j] = t - r * p.S - p.pad;
+            g_off[j] = ((long long)g_y[j] * p.W + g_x[j]) * p.Cin + m - t * p.Cin;
+        }
     } else {
         const int hw = (MODE == kFwd) ? p.Ho * p.Wo : d_hc * d_wc;
         const int ww = (MODE == kFwd) ? p.Wo : d_wc;
@@ -103,7 +110,8 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(GemmParams p)
     // Fast path of kFwd / kDgrad, a slab inside one tap.  Divisions and 64-bit products per slab and row cost the vector units more than
     // the slab costs the matrix cores, so a row keeps the address of its tap (0, 0), to which all rows add one offset, and a mask of
     // the taps inside the image (up to 32 of them); tap and channel of the next slab are counted along.  8 replicas, 64 images of 16 x 16:
-    // 32 to 64 channels forward 75 -> 67 us, data gradient 105 -> 74 us.  (The same for the weight gradient's rows: 87 -> 89 us, left out;
+    // 32 to 64 channels forward 75 -> 67 us, data gradient 105 -> 74 us.  (The same for the weight gradient's rows: 87 -> 89 us, left out,
+    // but for those that are gathered value by value, whose divisions are the same in every slab: 3 to 32 channels, images of 32 x 32, 8 replicas 58 -> 52;
     // three slabs ahead in registers instead of one: the whole pass 6 % slower.)
     // (The taps of a kDgrad class step back one source pixel each: y + pad - r is a multiple of the stride for all of them.)
     const int ntap = (MODE == kFwd) ? p.R * p.S : (p.Cout > 0 ? kend / p.Cout : 0), row_taps = (MODE == kFwd) ? p.S : max(d_ns, 1);
@@ -243,15 +251,13 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(GemmParams p)
                                 v[0] = 1.f;
                             }
                         } else {
+                            const float* const origin = abase + (((long long)b * p.H + yo * p.stride) * p.W + xo * p.stride) * p.Cin;
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
                                 const int m = wa_m + j;
                                 if (m < mw) {
-                                    const int tap = m / p.Cin, c = m - tap * p.Cin;
-                                    const int r = tap / p.S, s = tap - r * p.S;
-                                    const int yy = yo * p.stride - p.pad + r, xx = xo * p.stride - p.pad + s;
-                                    if (yy >= 0 && yy < p.H && xx >= 0 && xx < p.W)
-                                        v[j] = abase[(((long long)b * p.H + yy) * p.W + xx) * p.Cin + c];
+                                    const int yy = yo * p.stride + g_y[j], xx = xo * p.stride + g_x[j];
+                                    if (yy >= 0 && yy < p.H && xx >= 0 && xx < p.W) v[j] = origin[g_off[j]];
                                 } else if (m == mw && p.has_bias) {
                                     v[j] = 1.f;
                                 }
