@@ -724,7 +724,14 @@ struct Runner {
         if (rc != hipSuccess) failed = name;
     }
 
-    hipError_t gemm(const GemmParams& p) const { return e.cfg.bf16 ? launch_gemm_bf16(p, na, s) : launch_gemm(p, na, s); }
+    // fp32 problems of the generic kernels that conv_chain.hip takes
+    static bool chain(const GemmParams& p)
+    {
+        if (p.mode == kWgrad || p.stride != 1 || p.R != p.S || 2 * p.pad != p.R - 1 || p.Ho != p.H || p.Wo != p.W || p.H * p.W == 1) return false;
+        if (p.cursor) return p.mode == kFwd && conv_chain_first_supported(p.B, p.H, p.W, p.Cin, p.Cout, p.R);
+        return p.mode == kFwd ? conv_chain_supported(p.B, p.H, p.W, p.Cin, p.Cout, p.R) : conv_chain_supported(p.B, p.H, p.W, p.Cout, p.Cin, p.R);
+    }
+    hipError_t gemm(const GemmParams& p) const { if (!e.cfg.bf16 && chain(p)) return launch_conv_chain(p, na, s); return e.cfg.bf16 ? launch_gemm_bf16(p, na, s) : launch_gemm(p, na, s); }
     static double gemm_flops(const GemmParams& p) { return 2.0 * p.B * p.Ho * p.Wo * p.R * p.S * (double)p.Cin * p.Cout; }
     // activations are 2 bytes in the bf16 configuration, weights and their gradients 4
     double asz() const { return e.cfg.bf16 ? 0.5 : 1.0; }

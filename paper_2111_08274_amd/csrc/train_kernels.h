@@ -35,6 +35,11 @@ struct GemmParams {
     const int* order;
 };
 hipError_t launch_gemm(const GemmParams& p, int n_active, hipStream_t s);
+// kFwd and kDgrad of stride-1 "same" convolutions, the same bits (conv_chain.hip): C source channels, N outputs, k x k filters; `first`: on
+// the data set
+bool conv_chain_supported(int B, int H, int W, int C, int N, int k);
+bool conv_chain_first_supported(int B, int H, int W, int C, int N, int k);
+hipError_t launch_conv_chain(const GemmParams& p, int n_active, hipStream_t s);
 // Same problems with bf16 activations / activation gradients (pointers still typed float*: they are byte bases whose
 // offsets and strides are counted in 4-byte units), fp32 weights rounded to bf16 on the fly, fp32 weight gradients.
 hipError_t launch_gemm_bf16(const GemmParams& p, int n_active, hipStream_t s);

@@ -43,3 +43,31 @@ def test_two_steps(cin, k, cout, side, batch, classes, momentum):
         err = [np.abs(got[r] - w)[t].max() / (np.abs(w - w0)[t].max() + 1e5 * steps * 2.0 ** -24 * np.abs(w[t]).max()) for t in parts]
         print(r, "weights", " ".join("%.1e" % e for e in err), "loss %.1e" % abs(losses[r] - want), flush=True)
         assert max(err) <= 1e-5 and abs(losses[r] - want) <= 1e-5 * max(1.0, want)
+
+
+@pytest.mark.parametrize("cin,c1,c2,k,side,batch,replicas", [(3, 16, 48, 3, 9, 7, 2), (1, 32, 16, 5, 11, 33, 1), (3, 48, 36, 1, 8, 64, 3),
+                                                             (2, 40, 32, 3, 10, 20, 2), (3, 32, 64, 3, 16, 64, 4), (8, 32, 16, 3, 5, 128, 5)])
+def test_second_layer(cin, c1, c2, k, side, batch, replicas):
+    """A step through a stride-1 layer from a patch with all channels, or (a side of it without 16-channel groups) from the tiled kernel: rows
+    that fill no tile, outputs that fill no block, both tile heights, images wider and narrower than a border.  Bound as above."""
+    b = nets._Builder()
+    b.dense(b.gap(b.relu(b.conv(b.relu(b.conv(0, c1)), c2, k=k, pad=k // 2))), 10)
+    rng = np.random.default_rng(c1 + c2 + side)
+    shape = (side, side, cin)
+    x = rng.standard_normal((replicas, batch) + shape).astype(np.float32)
+    y = rng.integers(0, 10, (replicas, batch)).astype(np.int32)
+    cfg = hadfl.make_config(replicas, 1, net="custom", custom_ops=b.array()[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=batch, n_samples=batch,
+                            in_shape=shape, lr=0.1, momentum=0.0)
+    sizes = (9 * cin * c1, c1, k * k * c1 * c2, c2, c2 * 10, 10)
+    w0 = np.concatenate([s * rng.standard_normal(n) for n, s in zip(sizes, ((4.5 * cin) ** -0.5, 0.1, (0.5 * k * k * c1) ** -0.5, 0.1, c2 ** -0.5, 0.1))]).astype(np.float32)
+    ctx = hadfl.Context(cfg, [1] * replicas, w0=w0, x=x, y=y)
+    ctx.local_steps()
+    got, losses = [ctx.params(r).astype(np.float64) for r in range(replicas)], ctx.losses()
+    ctx.close()
+    parts = [slice(o, o + n) for o, n in zip(np.cumsum((0,) + sizes[:-1]), sizes)]
+    for r in range(replicas):
+        want, grad, _ = torch_ref.loss_grad(b.array(), shape, w0.astype(np.float64), x[r].astype(np.float64).reshape(batch, -1), y[r])
+        w = w0 - 0.1 * grad
+        err = [np.abs(got[r] - w)[t].max() / (np.abs(0.1 * grad)[t].max() + 1e5 * 2.0 ** -24 * np.abs(w[t]).max()) for t in parts]
+        print(r, "weights", " ".join("%.1e" % e for e in err), "loss %.1e" % abs(losses[r] - want), flush=True)
+        assert max(err) <= 1e-5 and abs(losses[r] - want) <= 1e-5 * max(1.0, want)
