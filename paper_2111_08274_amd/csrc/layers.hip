@@ -146,6 +146,7 @@ __global__ __launch_bounds__(256) void gap_fwd_kernel(EwParams p)
         const int c = (int)(i % p.C);
         const long long b = i / p.C;
         float s = 0.f;
+#pragma unroll 8
         for (int q = 0; q < hw; ++q) s += ldf(in, (b * hw + q) * p.C + c);
         stf(out, i, s / (float)hw);
     }
@@ -935,13 +936,29 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_pool_vec_kernel(BnParams p)
     }
 }
 
+// Sixteen bytes of a tensor as they lie, and their values
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+template <typename T> __device__ __forceinline__ u4v ldraw(const T* p, long long i) { return *reinterpret_cast<const u4v*>(p + i); }
+__device__ __forceinline__ void values(const u4v& r, float (&v)[4])
+{
+    const f4v f = __builtin_bit_cast(f4v, r);                 // (of the whole: of an element, the compiler takes the first for each)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = f[e];
+}
+__device__ __forceinline__ void values(const u4v& r, float (&v)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(float, e & 1 ? r[e >> 1] & 0xffff0000u : r[e >> 1] << 16);
+}
+
 // ---- batch norm of a small tensor in one launch ----
 // A workgroup of 1024 threads owns 4 channel vectors of one replica over all rows: sums, statistics and the normalised output
-// (backward: sums, gradients and the data gradient), the second pass reading what the first left in the die's L2.  Three
-// dependent launches of 5 to 6 us each are what such a layer's backward pass otherwise costs (80 channels on 1250 rows, 5
-// replicas: 17 us and the gaps; here 9), two its forward pass where the convolution left the sums (10 and a gap; here
-// 10).  512 channels on 1024 rows, 4 replicas, 2 M values: 29 us, no better than three launches, hence the limit in bn_small().
-constexpr int kBnSmallThreads = 1024, kBnSmallWaves = kBnSmallThreads / 64;
+// (backward: sums, gradients and the data gradient).  A thread has at most eight rows of its vector: they are fetched first of all, beside
+// the sums that the convolution left, and kept in registers for the second pass (80 channels on 1250 rows, 1 to 5 replicas: forward 9.0-11.4 us and backward 9.0-10.3 when
+// the second pass read them again; 7.3-10.5 and 7.2-9.0 here).  Three dependent launches of 5 to 6 us each are what such a layer's
+// backward pass otherwise costs, two its forward pass where the convolution left the sums.  512 channels on 1024 rows, 4 replicas, 2 M
+// values: 29 us, no better than three launches, hence the limit in bn_small().
+constexpr int kBnSmallThreads = 1024, kBnSmallWaves = kBnSmallThreads / 64, kBnSmallRows = 8;      // (kBnSmallRows: of a thread)
 
 // Totals over the row lanes of one channel vector, in every thread: xor-shuffles inside the waves, the waves in order by one
 // thread per value.
@@ -979,6 +996,9 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
     const bool live = cv < CV;
     const int c0 = live ? cv * VEC : 0;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
+    u4v xr[kBnSmallRows];
+#pragma unroll
+    for (int q = 0; q < kBnSmallRows; ++q) xr[q] = ldraw(x, (long long)min(rl + q * lanes, p.rows - 1) * p.C + c0);
     float x0[VEC], t[2 * VEC];                                // the shift the sums are taken with; sums of d and d^2
 #pragma unroll
     for (int e = 0; e < 2 * VEC; ++e) t[e] = 0.f;
@@ -992,16 +1012,19 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
                 for (int e = 0; e < VEC; ++e) { t[e] += part[(long long)k * 2 * p.C + c0 + e]; t[VEC + e] += part[(long long)k * 2 * p.C + p.C + c0 + e]; }
     } else {
         ldv(x, c0, x0);
-        if (live)
-#pragma unroll 4
-            for (int r = rl; r < p.rows; r += lanes) {
-                float v[VEC];
-                ldv(x, (long long)r * p.C + c0, v);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) { const float d = v[e] - x0[e]; t[e] += d; t[VEC + e] += d * d; }
-            }
+        for (int q = 0; q < kBnSmallRows; ++q) {
+            if (!live || rl + q * lanes >= p.rows) continue;
+            float v[VEC];
+            values(xr[q], v);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { const float d = v[e] - x0[e]; t[e] += d; t[VEC + e] += d * d; }
+        }
     }
-    float left_out[VEC] = {};                                 // (on its way beside the totals)
+    float* row = p.params + rep * p.row_stride;
+    float gamma[VEC], beta[VEC], left_out[VEC] = {};          // (on their way beside the totals)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { gamma[e] = row[p.w_off + c0 + e]; beta[e] = row[p.w_off + p.C + c0 + e]; }
     if (p.left_out) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) left_out[e] = p.left_out[rep * p.left_out_rep + c0 + e];
@@ -1009,7 +1032,6 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
     bn_small_total(t, red, p.cvb);
     if (!live) return;
     const float n = (float)p.rows;
-    float* row = p.params + rep * p.row_stride;
     float sc[VEC], sh[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {                           // as in bn_finalize_kernel<0>
@@ -1023,15 +1045,17 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_fwd_kernel(BnParams 
             rm[c] = bn_running_mean(rm[c], mean + left_out[e]);
             rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
         }
-        bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
+        bn_scale_shift(mean, istd, gamma[e], beta[e], sc[e], sh[e]);
     }
     T* y = tptr<T>(p.y, rep, p.y_rep);
     const T* add = p.add ? tptr<T>(p.add, rep, p.add_rep) : nullptr;
-#pragma unroll 4
-    for (int r = rl; r < p.rows; r += lanes) {
+#pragma unroll
+    for (int q = 0; q < kBnSmallRows; ++q) {
+        const int r = rl + q * lanes;
+        if (r >= p.rows) break;
         const long long i = (long long)r * p.C + c0;
         float v[VEC];
-        ldv(x, i, v);
+        values(xr[q], v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = bn_value(v[e], sc[e], sh[e], p.relu != 0);
         if (add) {
@@ -1055,37 +1079,49 @@ __global__ __launch_bounds__(kBnSmallThreads) void bn_small_bwd_kernel(BnParams 
     const int c0 = live ? cv * VEC : 0;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     const T* dy = tptr<T>(p.dy, rep, p.dy_rep);
+    u4v xr[kBnSmallRows], dr[kBnSmallRows];
+#pragma unroll
+    for (int q = 0; q < kBnSmallRows; ++q) {
+        const long long i = (long long)min(rl + q * lanes, p.rows - 1) * p.C + c0;
+        xr[q] = ldraw(x, i); dr[q] = ldraw(dy, i);
+    }
     const float* sv = p.saved + rep * p.saved_rep;
-    float mean[VEC], istd[VEC], t[2 * VEC];                   // sums of dy and dy * xhat
+    const float* const gamma = p.params + rep * p.row_stride + p.w_off + c0;
+    float mean[VEC], istd[VEC], k1[VEC], t[2 * VEC];          // sums of dy and dy * xhat
+    constexpr bool kEarly = VEC == 4;                         // (beside the sums; eight more registers a thread does not have)
+    if constexpr (kEarly)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) k1[e] = gamma[e];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) { mean[e] = sv[c0 + e]; istd[e] = sv[p.C + c0 + e]; t[e] = 0.f; t[VEC + e] = 0.f; }
-    if (live)
-#pragma unroll 4
-        for (int r = rl; r < p.rows; r += lanes) {
-            float v[VEC], d[VEC];
-            ldv(x, (long long)r * p.C + c0, v);
-            ldv(dy, (long long)r * p.C + c0, d);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { t[e] += d[e]; t[VEC + e] += d[e] * ((v[e] - mean[e]) * istd[e]); }
-        }
+    for (int q = 0; q < kBnSmallRows; ++q) {
+        if (!live || rl + q * lanes >= p.rows) continue;
+        float v[VEC], d[VEC];
+        values(xr[q], v); values(dr[q], d);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { t[e] += d[e]; t[VEC + e] += d[e] * ((v[e] - mean[e]) * istd[e]); }
+    }
     bn_small_total(t, red, p.cvb);
     if (!live) return;
     const float inv_n = 1.0f / (float)p.rows;
-    float k1[VEC], kb[VEC], kg[VEC];
+    float kb[VEC], kg[VEC];
     float* gr = p.grads + rep * p.row_stride + p.w_off;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         if (rl == 0) { gr[c0 + e] = t[VEC + e]; gr[p.C + c0 + e] = t[e]; }
-        k1[e] = p.params[rep * p.row_stride + p.w_off + c0 + e] * istd[e];
+        k1[e] = (kEarly ? k1[e] : gamma[e]) * istd[e];
         kb[e] = t[e] * inv_n; kg[e] = t[VEC + e] * inv_n;
     }
     T* dx = tptr<T>(p.y, rep, p.y_rep);
     const T* mask = p.mask ? tptr<T>(p.mask, rep, p.mask_rep) : nullptr;
-#pragma unroll 4
-    for (int r = rl; r < p.rows; r += lanes) {
+#pragma unroll
+    for (int q = 0; q < kBnSmallRows; ++q) {
+        const int r = rl + q * lanes;
+        if (r >= p.rows) break;
         const long long i = (long long)r * p.C + c0;
         float v[VEC], d[VEC], o[VEC];
-        ldv(x, i, v); ldv(dy, i, d);
+        values(xr[q], v); values(dr[q], d);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) o[e] = k1[e] * (d[e] - kb[e] - ((v[e] - mean[e]) * istd[e]) * kg[e]);
         if (mask) {
@@ -1563,9 +1599,8 @@ hipError_t launch_dense_small_bwd(const DenseSmallParams& p, int n_active, hipSt
 namespace {
 // channel vectors per workgroup: the largest power of two that is at most min(C / vec, 32)
 int bn_cvb(int C, int vec) { int cv = C / vec, b = 1; while (b * 2 <= cv && b * 2 <= 32) b *= 2; return b; }
-// One launch for the whole layer: few rows, so that a workgroup's two walks over them take no longer than the launches saved,
-// and a tensor that the few workgroups can move in that time
-bool bn_small(const BnParams& p, int n_active) { return !p.pool && p.rows <= 2048 && (long long)p.rows * p.C * n_active <= (1 << 20); }
+// One launch for the whole layer: as many rows as a workgroup's registers hold, and a tensor that the few workgroups can move in that time
+bool bn_small(const BnParams& p, int n_active) { return !p.pool && p.rows <= kBnSmallRows * (kBnSmallThreads / kBnSmallCvb) && (long long)p.rows * p.C * n_active <= (1 << 20); }
 dim3 bn_small_grid(BnParams& p, int vec, int n_active)
 {
     p.cvb = std::min(kBnSmallCvb, bn_cvb(p.C, vec));

@@ -42,6 +42,17 @@ def test_layers_between_a_convolution_and_its_batch_norm(ch, bf16):
     forced(interleaved(ch), (8, 8, 3), 32, 3, bf16)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("side,batch,ch", [(4, 128, 40), (5, 50, 24), (2, 3, 8)])
+def test_one_launch_batch_norm(side, batch, ch, bf16):
+    """2048 rows, eight of a thread, the most of the kernels that keep them in registers; 1250, not a multiple; 12, fewer than threads."""
+    b = nets._Builder()
+    t = b.relu(b.bn(b.conv(0, ch)))
+    t = b.relu(b.add(b.bn(b.conv(t, ch)), t))
+    b.dense(b.gap(t), 10)
+    forced(b, (side, side, 3), batch, 2, bf16)
+
+
 def biased(kind):
     """A convolution with a bias in front of a batch norm of each kind: few values (one launch), many, and a pool folded in; from
     patches, and strided."""
