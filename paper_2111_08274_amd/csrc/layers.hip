@@ -556,6 +556,58 @@ template <typename T> __device__ __forceinline__ float bn_stored_value(float x, 
     return (float)(T)bn_value(x, sc, sh, relu);
 }
 
+// Mean and 1 / sqrt(var + eps) of a channel from its sums s and q of d = x - x0 and d^2; `keeps`: the thread that leaves them for the backward pass
+// and updates the running statistics.
+__device__ __forceinline__ void bn_statistics(const BnParams& p, int rep, int c, float s, float q, float x0, float left_out, bool keeps, float& mean, float& istd)
+{
+    const float n = (float)p.rows;
+    const float md = s / n + 0.f * left_out;                  // mean of the shifted values
+    const float cen = fmaxf(q - s * md, 0.f);                 // sum of squared deviations from the mean
+    const float var = cen / n;
+    mean = x0 + md; istd = 1.0f / sqrtf(var + kBnEps);
+    if (!keeps) return;
+    float* sv = p.saved + rep * p.saved_rep;
+    sv[c] = mean; sv[p.C + c] = istd;
+    const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
+    float* rm = p.params + rep * p.row_stride + p.stat_off;
+    rm[c] = bn_running_mean(rm[c], mean + left_out);
+    rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
+}
+
+// Batch norms whose sums have few entries: every workgroup of the apply kernel adds those of its own channels, in the order of
+// bn_finalize_kernel, whose launch is saved; `finish` makes two numbers per channel of the totals (one thread a channel), which all threads
+// get in u and v.
+template <int VEC> struct BnFold { float part[8][32][2 * VEC + 1]; float done[32][2 * VEC]; };
+template <int VEC, typename F>
+__device__ __forceinline__ void bn_fold(const BnParams& p, const BnGeo& g, int gi, int entries, BnFold<VEC>& lds, F&& finish, float (&u)[VEC], float (&v)[VEC])
+{
+    const int cl = threadIdx.x % g.cvb;
+    if (g.rl < 8 && g.live) {                                 // (a workgroup has at least eight row lanes)
+        float a[2 * VEC];
+#pragma unroll
+        for (int e = 0; e < 2 * VEC; ++e) a[e] = 0.f;
+        const float* part = p.partial + gi * p.partial_rep + g.c;
+#pragma unroll 4
+        for (int k = g.rl; k < entries; k += 8)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { a[e] += part[(long long)k * 2 * p.C + e]; a[VEC + e] += part[(long long)k * 2 * p.C + p.C + e]; }
+#pragma unroll
+        for (int e = 0; e < 2 * VEC; ++e) lds.part[g.rl][cl][e] = a[e];
+    }
+    __syncthreads();
+    const int tc = threadIdx.x / VEC, te = threadIdx.x % VEC, c = (g.cv - cl + tc) * VEC + te;      // this thread's channel
+    if (tc < g.cvb && c < p.C) {
+        auto total = [&](int e) {
+            const auto at = [&](int k) { return lds.part[k][tc][e]; };
+            return ((at(0) + at(4)) + (at(2) + at(6))) + ((at(1) + at(5)) + (at(3) + at(7)));
+        };
+        finish(c, total(te), total(VEC + te), lds.done[tc][te], lds.done[tc][VEC + te]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { u[e] = lds.done[cl][e]; v[e] = lds.done[cl][VEC + e]; }
+}
+
 // MODE 0: mean and 1/sqrt(var+eps) -> saved, running statistics updated.  x0 is the shift used by the sums pass.
 // MODE 1: totals of dy and dy*xhat -> gradient of beta and gamma, and into chunk 0 of the partial buffer.
 template <int MODE, typename T>
@@ -588,8 +640,8 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
             direct = gamma == 0.f || !(fabsf(beta) <= kBwdStatCond * fabsf(gamma));
         }
         if (kl == 0) s_direct[cl] = direct ? 1 : 0;
-        __syncthreads();
-        for (int j = 0; j < 32; ++j) {
+        const int any = __syncthreads_or(direct);
+        for (int j = 0; any && j < 32; ++j) {
             if (!s_direct[j]) continue;                       // uniform over the workgroup
             const int cj = blockIdx.x * 32 + j;
             const T* x = tptr<T>(p.x, rep, p.x_rep);
@@ -647,19 +699,11 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
     if (kl != 0 || !live) return;
     s = red[0][cl][0]; q = red[0][cl][1];
     if (MODE == 0) {
-        const float n = (float)p.rows;
         // the shift the sums were taken with: the producing convolution's bias, or the tensor's first row
         const float x0 = p.stats_done ? (p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c] : 0.f)
                                       : ldf(tptr<T>(p.x, rep, p.x_rep), c);
-        const float md = s / n + 0.f * left_out;              // mean of the shifted values
-        const float cen = fmaxf(q - s * md, 0.f);             // sum of squared deviations from the mean
-        const float mean = x0 + md, var = cen / n;
-        float* sv = p.saved + rep * p.saved_rep;
-        sv[c] = mean; sv[p.C + c] = 1.0f / sqrtf(var + kBnEps);
-        const float unb = p.rows > 1 ? cen / (n - 1.f) : var;
-        float* rm = p.params + rep * p.row_stride + p.stat_off;
-        rm[c] = bn_running_mean(rm[c], mean + left_out);
-        rm[p.C + c] = (1.f - kBnStatMomentum) * rm[p.C + c] + kBnStatMomentum * unb;
+        float mean, istd;
+        bn_statistics(p, rep, c, s, q, x0, left_out, true, mean, istd);
     } else {
         if (p.bwd_stats_done == 1 && !direct) q = (q - beta * s) / gamma;
         if (p.bwd_stats_done == 2) q = q * p.saved[rep * p.saved_rep + p.C + c];
@@ -669,23 +713,34 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
     }
 }
 
-template <typename T>
+template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void bn_apply_fwd_vec_kernel(BnParams p)
 {
     constexpr int VEC = VecOf<T>::n;
     const int gi = blockIdx.y, rep = p.order[gi];
     const BnGeo g = bn_geo(p, VEC);
-    if (!g.live) return;
+    if (!FOLD && !g.live) return;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     T* y = tptr<T>(p.y, rep, p.y_rep);
     const T* add = p.add ? tptr<T>(p.add, rep, p.add_rep) : nullptr;
     const float* row = p.params + rep * p.row_stride;
     float sc[VEC], sh[VEC];
-    const float* sv = p.saved + rep * p.saved_rep;
+    if constexpr (FOLD) {
+        __shared__ BnFold<VEC> lds;
+        bn_fold<VEC>(p, g, gi, p.stats_done ? p.stat_entries : p.chunks, lds, [&](int c, float s, float q, float& scale, float& shift) {
+            const float x0 = p.stats_done ? (p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c] : 0.f) : ldf(x, c);
+            float mean, istd;
+            bn_statistics(p, rep, c, s, q, x0, bn_left_out(p, rep, c), g.chunk == 0, mean, istd);
+            bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], scale, shift);
+        }, sc, sh);
+        if (!g.live) return;
+    } else {
+        const float* sv = p.saved + rep * p.saved_rep;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        const int c = g.c + e;
-        bn_scale_shift(sv[c], sv[p.C + c], row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
+        for (int e = 0; e < VEC; ++e) {
+            const int c = g.c + e;
+            bn_scale_shift(sv[c], sv[p.C + c], row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
+        }
     }
     const int r0 = g.chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
 #pragma unroll 4
@@ -705,13 +760,13 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_vec_kernel(BnParams p)
     }
 }
 
-template <typename T>
+template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void bn_apply_bwd_vec_kernel(BnParams p)
 {
     constexpr int VEC = VecOf<T>::n;
     const int gi = blockIdx.y, rep = p.order[gi];
     const BnGeo g = bn_geo(p, VEC);
-    if (!g.live) return;
+    if (!FOLD && !g.live) return;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     const T* dy = tptr<T>(p.dy, rep, p.dy_rep);
     T* dx = tptr<T>(p.y, rep, p.y_rep);
@@ -720,13 +775,24 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_vec_kernel(BnParams p)
     const float* sv = p.saved + rep * p.saved_rep;
     const float inv_n = 1.0f / (float)p.rows;
     float mean[VEC], istd[VEC], k1[VEC], kb[VEC], kg[VEC];
+    const int c0 = g.live ? g.c : 0;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        const int c = g.c + e;
-        const float db = part[c], dg = part[p.C + c];       // totals left in chunk 0 by bn_finalize_kernel<1>
-        mean[e] = sv[c]; istd[e] = sv[p.C + c];
-        k1[e] = p.params[rep * p.row_stride + p.w_off + c] * istd[e];
-        kb[e] = db * inv_n; kg[e] = dg * inv_n;
+        mean[e] = sv[c0 + e]; istd[e] = sv[p.C + c0 + e];
+        k1[e] = p.params[rep * p.row_stride + p.w_off + c0 + e] * istd[e];
+        if (!FOLD) { kb[e] = part[c0 + e] * inv_n; kg[e] = part[p.C + c0 + e] * inv_n; }      // totals left in chunk 0 by bn_finalize_kernel<1>
+    }
+    if constexpr (FOLD) {
+        __shared__ BnFold<VEC> lds;
+        bn_fold<VEC>(p, g, gi, p.bwd_stats_done ? p.stat_entries : p.chunks, lds, [&](int c, float s, float q, float& b, float& w) {
+            if (p.bwd_stats_done == 2) q = q * sv[p.C + c];
+            if (g.chunk == 0) {
+                float* gr = p.grads + rep * p.row_stride + p.w_off;
+                gr[c] = q; gr[p.C + c] = s;
+            }
+            b = s * inv_n; w = q * inv_n;
+        }, kb, kg);
+        if (!g.live) return;
     }
     const int r0 = g.chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
 #pragma unroll 4
@@ -1610,6 +1676,17 @@ dim3 bn_small_grid(BnParams& p, int vec, int n_active)
 
 bool bn_backward_in_one_launch(const BnParams& p, int n_active) { return p.C % (p.bf16 ? 8 : 4) == 0 && bn_small(p, n_active); }
 
+// Sums with few entries are added by the apply kernel's workgroups, each for its own channels, in place of a launch.  Finalize and apply, us, with
+// that launch and folded: 512 channels on 1024 rows (8 to 32 entries), fp32, 3 / 8 / 16 replicas forward 16 18 23 and 13 14 18, backward 13
+// 17 23 and 10 13 19; 256 channels on 4096 rows (16 to 64 entries) 19 25 37 and 13 21 33, 16 24 40 and 11 20 35.  Beyond some 64 entries,
+// or 64 MB that all workgroups read together, the launch is the shorter way (bf16, 128 channels on 32768 rows, 128 entries, 7 / 32
+// replicas forward 18 59 and 19 71).
+namespace {
+constexpr int kFoldEntries = 64;
+constexpr long long kFoldBytes = 64 << 20;
+bool bn_folds(const BnParams& p, int vec, int entries, long long workgroups) { return !p.pool && entries <= kFoldEntries && workgroups * entries * 2 * p.cvb * vec * 4 <= kFoldBytes; }
+}  // namespace
+
 hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
 {
     if (n_active < 1) return hipSuccess;
@@ -1627,16 +1704,19 @@ hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
         const int cgroups = (p.C / vec + p.cvb - 1) / p.cvb;
         const dim3 grid((unsigned)(p.chunks * cgroups), (unsigned)n_active), fgrid((unsigned)((p.C + 31) / 32), (unsigned)n_active);
         if (p.pool && (p.H % 2 != 0 || p.W % 2 != 0 || p.rows % 4 != 0 || !p.pool_out)) return hipErrorInvalidValue;
+        const bool fold = bn_folds(p, vec, p.stats_done ? p.stat_entries : p.chunks, (long long)grid.x * n_active);
         if (p.bf16) {
             if (!p.stats_done) hipLaunchKernelGGL((bn_sums_vec_kernel<0, __bf16>), grid, block, 0, s, p);
-            hipLaunchKernelGGL((bn_finalize_kernel<0, __bf16>), fgrid, block, 0, s, p);
+            if (fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<__bf16, true>), grid, block, 0, s, p);
+            else hipLaunchKernelGGL((bn_finalize_kernel<0, __bf16>), fgrid, block, 0, s, p);
             if (p.pool) hipLaunchKernelGGL(bn_apply_fwd_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
-            else hipLaunchKernelGGL(bn_apply_fwd_vec_kernel<__bf16>, grid, block, 0, s, p);
+            else if (!fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<__bf16, false>), grid, block, 0, s, p);
         } else {
             if (!p.stats_done) hipLaunchKernelGGL((bn_sums_vec_kernel<0, float>), grid, block, 0, s, p);
-            hipLaunchKernelGGL((bn_finalize_kernel<0, float>), fgrid, block, 0, s, p);
+            if (fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<float, true>), grid, block, 0, s, p);
+            else hipLaunchKernelGGL((bn_finalize_kernel<0, float>), fgrid, block, 0, s, p);
             if (p.pool) hipLaunchKernelGGL(bn_apply_fwd_pool_vec_kernel<float>, grid, block, 0, s, p);
-            else hipLaunchKernelGGL(bn_apply_fwd_vec_kernel<float>, grid, block, 0, s, p);
+            else if (!fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<float, false>), grid, block, 0, s, p);
         }
         return hipGetLastError();
     }
@@ -1672,21 +1752,25 @@ hipError_t launch_bn_bwd(const BnParams& p0, int n_active, hipStream_t s)
         const dim3 grid((unsigned)(p.chunks * cgroups), (unsigned)n_active), fgrid((unsigned)((p.C + 31) / 32), (unsigned)n_active);
         if (p.pool && (p.H % 2 != 0 || p.W % 2 != 0 || p.rows % 4 != 0 || !p.pool_g)) return hipErrorInvalidValue;
         if (p.pool && p.bwd_stats_done == 2) return hipErrorInvalidValue;
+        // (sums of the stored output need the finalize kernel's second look at the scales)
+        const bool fold = p.bwd_stats_done != 1 && bn_folds(p, vec, p.bwd_stats_done ? p.stat_entries : p.chunks, (long long)grid.x * n_active);
         if (p.bf16) {
             if (p.bwd_stats_done) {}                                  // the data gradient above left the sums
             else if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
             else hipLaunchKernelGGL((bn_sums_vec_kernel<1, __bf16>), grid, block, 0, s, p);
-            hipLaunchKernelGGL((bn_finalize_kernel<1, __bf16>), fgrid, block, 0, s, p);
+            if (fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<__bf16, true>), grid, block, 0, s, p);
+            else hipLaunchKernelGGL((bn_finalize_kernel<1, __bf16>), fgrid, block, 0, s, p);
             if (p.pool) hipLaunchKernelGGL(bn_apply_bwd_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
-            else hipLaunchKernelGGL(bn_apply_bwd_vec_kernel<__bf16>, grid, block, 0, s, p);
+            else if (!fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<__bf16, false>), grid, block, 0, s, p);
         } else {
             if (p.bwd_stats_done == 1) return hipErrorInvalidValue;  // (of the stored output: only the bf16 data-gradient kernels leave those)
             if (p.bwd_stats_done) {}
             else if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<float>, grid, block, 0, s, p);
             else hipLaunchKernelGGL((bn_sums_vec_kernel<1, float>), grid, block, 0, s, p);
-            hipLaunchKernelGGL((bn_finalize_kernel<1, float>), fgrid, block, 0, s, p);
+            if (fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<float, true>), grid, block, 0, s, p);
+            else hipLaunchKernelGGL((bn_finalize_kernel<1, float>), fgrid, block, 0, s, p);
             if (p.pool) hipLaunchKernelGGL(bn_apply_bwd_pool_vec_kernel<float>, grid, block, 0, s, p);
-            else hipLaunchKernelGGL(bn_apply_bwd_vec_kernel<float>, grid, block, 0, s, p);
+            else if (!fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<float, false>), grid, block, 0, s, p);
         }
         return hipGetLastError();
     }

@@ -160,9 +160,9 @@ void batch_norm(Launch l, const BnParams& p, int n)
     else l.tensor(kGrad, p.grads + p.w_off, p.row_stride, 2 * p.C * 4);
     if (has(l.name, "sums") || has(l.name, "reduce")) l.sums(p.partial, p.partial_rep, p.chunks, p.C, p.x);
     else if (bwd ? p.bwd_stats_done : p.stats_done) {
-        if (has(l.name, "finalize") || has(l.name, "small"))
+        if (has(l.name, "finalize") || has(l.name, "small") || has(l.name, "Lb1E"))
             l.check_sums(p.partial, p.partial_rep, p.stat_entries, p.C, !bwd ? (const void*)p.x : p.pool ? (const void*)p.pool_g : (const void*)p.dy);
-    } else if (has(l.name, "finalize")) l.check_sums(p.partial, p.partial_rep, p.chunks, p.C, p.x);
+    } else if (has(l.name, "finalize") || has(l.name, "Lb1E")) l.check_sums(p.partial, p.partial_rep, p.chunks, p.C, p.x);
 }
 
 void look(const std::string& name, dim3 grid, void** args)

@@ -446,3 +446,17 @@ def test_backward_sums_of_residual_blocks(checked):
     assert [sum("bn_sums_vec_kernelILi1" in n for n in r["trace"]) for r in runs] == [3, 0] * 4
     assert [layers_in(r["trace"], "bn_small_bwd") for r in runs] == [0, 10, 0, 6] * 2
     assert_clean(checked, cases)
+
+
+def test_batch_norms_that_add_their_sums_themselves(checked):
+    """Up to 64 entries, and 64 MB read by all workgroups: no launch for the totals.  Sums of a stored bf16 output keep
+    theirs, and a bf16 convolution in tiles of 256 pixels leaves fewer."""
+    cases = []
+    for side, batch, n in ((8, 64, 2), (8, 64, 40), (16, 64, 2)):
+        b = nets._Builder()
+        t = b.relu(b.bn(b.conv(0, 256)))
+        b.dense(b.gap(b.relu(b.bn(b.conv(t, 256)))), 10)
+        cases += [case(b, (side, side, 3), batch, [1] * n, bf16, options=[(1, 1)]) for bf16 in (0, 1)]
+    runs = checked(cases)
+    assert [sum("finalize" in name for name in r["trace"]) for r in runs] == [0, 1, 4, 3, 4, 3]
+    assert_clean(checked, cases)
