@@ -807,15 +807,21 @@ __global__ __launch_bounds__(GATHER ? 256 : WGM * WGN * 64, 2) void wgrad_genera
 // tap and a 64 x 64 (ci, co) tile; each thread forms 16-byte groups of eight positions.  p.fragments: the order of the lanes of a
 // matrix instruction instead (conv_general_patch.hip), [32 rows][slab][tap][16 channels][plane][half of them][row], rows beyond the
 // last zero.  Bound by memory: 4 bytes read and 12 (bf16: 4) written per weight.  Weights are read, and pass through LDS, sixteen bytes a
-// lane (N and the layer's offset are multiples of four).
+// lane (N and the layer's offset are multiples of four).  One launch takes up to 32 layers: a small layer's few hundred tiles take
+// less time than the launch, and a sub-step whose layers all wait for their copies had a launch and a drained chip for each
+// (five layers of 64 to 256 channels, 5 replicas, four sub-steps: 1355 -> 1325 us with one; residual nets of 20 layers 0.5 to 0.9 %).
 template <typename T>
-__global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopyParams p)
+__global__ __launch_bounds__(256) void weight_copy_kernel(WeightCopies all)
 {
     constexpr bool kSplit = std::is_same<T, float>::value;
     constexpr int kSlab = Slab<T>::channels, kSlabBytes = Slab<T>::bytes, GR = Slab<T>::groups;
     __shared__ __attribute__((aligned(16))) float tile[64][68];          // [ci][co], zero outside the layer
-    const int rep = p.order[blockIdx.z];
-    const int tap = blockIdx.y % p.taps, co0 = (blockIdx.y / p.taps) * 64, ci0 = blockIdx.x * 64;
+    const int lane = threadIdx.x & 63;                                   // the last layer that begins at or before this workgroup
+    const int which_layer = __popcll(__ballot(lane < all.count && (int)blockIdx.x >= all.first[lane & (kWeightCopies - 1)])) - 1;
+    const WeightCopyParams& p = all.layer[which_layer];
+    const int rep = p.order[blockIdx.y];
+    const int block = (int)blockIdx.x - all.first[which_layer], tiles_c = (p.C + 63) / 64, rest = block / tiles_c;
+    const int tap = rest % p.taps, co0 = (rest / p.taps) * 64, ci0 = (block % tiles_c) * 64;
     const float* w = p.w + (long long)rep * p.w_rep + (long long)tap * p.C * p.N;
     const int tx = (threadIdx.x & 15) * 4, ty = threadIdx.x >> 4;
     f4 in[4];
@@ -1048,11 +1054,19 @@ hipError_t launch_wgrad_general(const GeneralWgradParams& p0, int n_active, hipS
     return p.cursor ? launch_wgrad<__bf16, float>(p, n_active, s) : launch_wgrad<__bf16, __bf16>(p, n_active, s);
 }
 
-hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s)
+hipError_t launch_weight_copies(WeightCopies& p, int n_active, hipStream_t s)
 {
-    if (n_active < 1) return hipSuccess;
-    const dim3 grid((unsigned)((p.C + 63) / 64), (unsigned)(p.taps * ((p.N + 63) / 64)), (unsigned)n_active), block(256);
-    if (p.bf16) hipLaunchKernelGGL(weight_copy_kernel<__bf16>, grid, block, 0, s, p);
+    if (n_active < 1 || p.count < 1) return hipSuccess;
+    if (p.count > kWeightCopies) return hipErrorInvalidValue;
+    long long tiles = 0;
+    for (int i = 0; i < p.count; ++i) {
+        const WeightCopyParams& l = p.layer[i];
+        p.first[i] = (int)tiles;
+        tiles += (long long)((l.C + 63) / 64) * ((l.N + 63) / 64) * l.taps;
+        if (l.bf16 != p.layer[0].bf16 || tiles > 0x7fffffff / 256) return hipErrorInvalidValue;
+    }
+    const dim3 grid((unsigned)tiles, (unsigned)n_active), block(256);
+    if (p.layer[0].bf16) hipLaunchKernelGGL(weight_copy_kernel<__bf16>, grid, block, 0, s, p);
     else hipLaunchKernelGGL(weight_copy_kernel<float>, grid, block, 0, s, p);
     return hipGetLastError();
 }

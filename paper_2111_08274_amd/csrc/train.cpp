@@ -647,20 +647,32 @@ struct Runner {
 
     // K-contiguous copies of layer i's filters for the lean kernels (forward layout and flipped/transposed for the data
     // gradient; bf16, or split floats in the fp32 configuration), refreshed from the fp32 master for the first n replicas in step
-    // order
+    // order.  The general layers' are gathered, and written by one launch in write_copies.
+    WeightCopies copies{};
+    double copies_bytes = 0;
+    void write_copies(int n)
+    {
+        if (copies.count == 0) return;
+        const int keep_na = na;
+        na = n;
+        run("weight_prep", 0, copies_bytes, [&] { return launch_weight_copies(copies, na, s); });
+        copies.count = 0; copies_bytes = 0;
+        na = keep_na;
+    }
     void prep_layer(size_t i, int n)
     {
         const int keep_na = na, keep_layer = cur_layer;
         na = n; cur_layer = (int)i;
         const Layer& l = e.plan.layers[i];
         if (e.general[i]) {
-            WeightCopyParams w{};
+            if (copies.count == kWeightCopies) write_copies(n);
+            WeightCopyParams& w = copies.layer[copies.count++];
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
             w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
             w.C = layer_channels(l); w.N = l.cout; w.taps = l.type == HADFL_OP_CONV ? l.k * l.k : 1; w.bf16 = e.cfg.bf16; w.order = e.buf.order;
             if (gather_layer(e.cfg, l)) { w.C *= w.taps; w.taps = 1; }
             w.fragments = e.patch[i];
-            run("weight_prep", 0, (e.cfg.bf16 ? 8.0 : 16.0) * l.w_count, [&] { return launch_weight_copy(w, na, s); });
+            copies_bytes += (e.cfg.bf16 ? 8.0 : 16.0) * l.w_count;
         } else {
             WeightPrepParams w{};
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
@@ -691,6 +703,7 @@ struct Runner {
             if (e.prepped[i]) { e.prepped[i] = 0; continue; }      // written during the previous sub-step's backward pass
             prep_layer(i, na);
         }
+        write_copies(na);
     }
     // A layer whose update is fused into its weight-gradient kernel has its final weights of this sub-step as soon as
     // that kernel ends, so the copies for the next sub-step are written right behind it on the same stream, off the
@@ -702,6 +715,7 @@ struct Runner {
     {
         if (pending_prep < 0) return;
         prep_layer((size_t)pending_prep, na_next);
+        write_copies(na_next);
         e.prepped[pending_prep] = 1;
         pending_prep = -1;
     }

@@ -191,7 +191,13 @@ struct WeightCopyParams {    // fp32 W[tap][C][N] -> copies Wf[N][tap][C] and (u
     int fragments;                             // in the order of conv_general_patch.hip
     const int* order;
 };
-hipError_t launch_weight_copy(const WeightCopyParams& p, int n_active, hipStream_t s);
+constexpr int kWeightCopies = 32;
+struct WeightCopies {        // layers whose copies one launch writes
+    WeightCopyParams layer[kWeightCopies];
+    int first[kWeightCopies];                  // a layer's first workgroup
+    int count;
+};
+hipError_t launch_weight_copies(WeightCopies& p, int n_active, hipStream_t s);
 
 struct LossParams {
     const float* logits; long long logits_rep;

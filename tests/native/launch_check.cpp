@@ -192,16 +192,20 @@ void look(const std::string& name, dim3 grid, void** args)
         gradient(l, p.out, p.out_rep, p.out_split, p.splits, (long long)p.M * p.N, p.sgd_w, p.sgd_buf);
     } else if (has(name, "weight_copy_kernel") || has(name, "weight_prep_kernel")) {
         const bool general = has(name, "weight_copy");
-        const WeightCopyParams& c = *(WeightCopyParams*)args[0];
+        const WeightCopies& all = *(WeightCopies*)args[0];
         const WeightPrepParams& q = *(WeightPrepParams*)args[0];
-        l.order = general ? c.order : q.order; l.n = (int)grid.z;
-        const auto units = general && c.fragments ? weight_fragment_units : weight_copy_units;
-        const long long nf = general ? units(c.bf16, c.N, c.taps, c.C) : (long long)q.C * q.N * q.taps;
-        const long long nb = general ? units(c.bf16, c.C, c.taps, c.N) : nf;
-        for (int g = 0; g < l.n; ++g) {
-            const long long at = l.order[g] * (general ? c.wcopy_rep : q.wbf_rep);
-            use(name, kCopy, (general ? c.wf : q.wf) + at, nf * 2);
-            if (general ? c.wb : q.wb) use(name, kCopy, (general ? c.wb : q.wb) + at, nb * 2);
+        l.n = (int)(general ? grid.y : grid.z);
+        for (int k = 0; k < (general ? all.count : 1); ++k) {
+            const WeightCopyParams& c = all.layer[k];
+            l.order = general ? c.order : q.order;
+            const auto units = general && c.fragments ? weight_fragment_units : weight_copy_units;
+            const long long nf = general ? units(c.bf16, c.N, c.taps, c.C) : (long long)q.C * q.N * q.taps;
+            const long long nb = general ? units(c.bf16, c.C, c.taps, c.N) : nf;
+            for (int g = 0; g < l.n; ++g) {
+                const long long at = l.order[g] * (general ? c.wcopy_rep : q.wbf_rep);
+                use(name, kCopy, (general ? c.wf : q.wf) + at, nf * 2);
+                if (general ? c.wb : q.wb) use(name, kCopy, (general ? c.wb : q.wb) + at, nb * 2);
+            }
         }
     } else if (has(name, "splitk_reduce")) {
         l.n = (int)grid.y;

@@ -460,3 +460,17 @@ def test_batch_norms_that_add_their_sums_themselves(checked):
     runs = checked(cases)
     assert [sum("finalize" in name for name in r["trace"]) for r in runs] == [0, 1, 4, 3, 4, 3]
     assert_clean(checked, cases)
+
+
+def test_weight_copies_of_many_layers(checked):
+    """One launch writes the copies of up to 32 layers (the first layer, on the data set, needs none)."""
+    def deep(n):
+        b = nets._Builder()
+        t = 0
+        for _ in range(n):
+            t = b.relu(b.bn(b.conv(t, 16)))
+        b.dense(b.gap(t), 10)
+        return b
+    cases = [case(deep(n), (8, 8, 16), 4, [1, 1], bf16) for n in (33, 34) for bf16 in (0, 1)]
+    assert [layers_in(r["trace"], "weight_copy") for r in checked(cases)] == [1, 1, 2, 2]
+    assert_clean(checked, cases)
