@@ -713,6 +713,53 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p)
     }
 }
 
+// Scale and shift of a thread's channels, with the statistics of bn_finalize_kernel<0> or (FOLD, all threads of the workgroup) formed here
+template <typename T, bool FOLD>
+__device__ __forceinline__ void bn_forward_scales(const BnParams& p, const BnGeo& g, int gi, int rep, const T* x, float (&sc)[VecOf<T>::n], float (&sh)[VecOf<T>::n])
+{
+    constexpr int VEC = VecOf<T>::n;
+    const float* row = p.params + rep * p.row_stride;
+    if constexpr (FOLD) {
+        __shared__ BnFold<VEC> lds;
+        bn_fold<VEC>(p, g, gi, p.stats_done ? p.stat_entries : p.chunks, lds, [&](int c, float s, float q, float& scale, float& shift) {
+            const float x0 = p.stats_done ? (p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c] : 0.f) : ldf(x, c);
+            float mean, istd;
+            bn_statistics(p, rep, c, s, q, x0, bn_left_out(p, rep, c), g.chunk == 0, mean, istd);
+            bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], scale, shift);
+        }, sc, sh);
+    } else {
+        const float* sv = p.saved + rep * p.saved_rep;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const int c = g.c + e;
+            bn_scale_shift(sv[c], sv[p.C + c], row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
+        }
+    }
+}
+
+// Means of dy and of dy xhat over the batch, for a thread's channels: of the totals that bn_finalize_kernel<1> left in chunk 0, or (FOLD)
+// formed here, and the gradients of beta and gamma with them
+template <int VEC, bool FOLD>
+__device__ __forceinline__ void bn_backward_means(const BnParams& p, const BnGeo& g, int gi, int rep, float (&kb)[VEC], float (&kg)[VEC])
+{
+    const float inv_n = 1.0f / (float)p.rows;
+    if constexpr (FOLD) {
+        __shared__ BnFold<VEC> lds;
+        bn_fold<VEC>(p, g, gi, p.bwd_stats_done ? p.stat_entries : p.chunks, lds, [&](int c, float s, float q, float& b, float& w) {
+            if (p.bwd_stats_done == 2) q = q * p.saved[rep * p.saved_rep + p.C + c];
+            if (g.chunk == 0) {
+                float* gr = p.grads + rep * p.row_stride + p.w_off;
+                gr[c] = q; gr[p.C + c] = s;
+            }
+            b = s * inv_n; w = q * inv_n;
+        }, kb, kg);
+    } else {
+        const float* part = p.partial + gi * p.partial_rep;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { kb[e] = part[g.c + e] * inv_n; kg[e] = part[p.C + g.c + e] * inv_n; }
+    }
+}
+
 template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void bn_apply_fwd_vec_kernel(BnParams p)
 {
@@ -723,25 +770,9 @@ __global__ __launch_bounds__(256) void bn_apply_fwd_vec_kernel(BnParams p)
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     T* y = tptr<T>(p.y, rep, p.y_rep);
     const T* add = p.add ? tptr<T>(p.add, rep, p.add_rep) : nullptr;
-    const float* row = p.params + rep * p.row_stride;
     float sc[VEC], sh[VEC];
-    if constexpr (FOLD) {
-        __shared__ BnFold<VEC> lds;
-        bn_fold<VEC>(p, g, gi, p.stats_done ? p.stat_entries : p.chunks, lds, [&](int c, float s, float q, float& scale, float& shift) {
-            const float x0 = p.stats_done ? (p.stat_shift ? p.stat_shift[rep * p.stat_shift_rep + c] : 0.f) : ldf(x, c);
-            float mean, istd;
-            bn_statistics(p, rep, c, s, q, x0, bn_left_out(p, rep, c), g.chunk == 0, mean, istd);
-            bn_scale_shift(mean, istd, row[p.w_off + c], row[p.w_off + p.C + c], scale, shift);
-        }, sc, sh);
-        if (!g.live) return;
-    } else {
-        const float* sv = p.saved + rep * p.saved_rep;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const int c = g.c + e;
-            bn_scale_shift(sv[c], sv[p.C + c], row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
-        }
-    }
+    bn_forward_scales<T, FOLD>(p, g, gi, rep, x, sc, sh);
+    if (!g.live) return;
     const int r0 = g.chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
 #pragma unroll 4
     for (int r = r0 + g.rl; r < r1; r += g.rl_count) {
@@ -771,29 +802,16 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_vec_kernel(BnParams p)
     const T* dy = tptr<T>(p.dy, rep, p.dy_rep);
     T* dx = tptr<T>(p.y, rep, p.y_rep);
     const T* mask = p.mask ? tptr<T>(p.mask, rep, p.mask_rep) : nullptr;
-    const float* part = p.partial + gi * p.partial_rep;
     const float* sv = p.saved + rep * p.saved_rep;
-    const float inv_n = 1.0f / (float)p.rows;
     float mean[VEC], istd[VEC], k1[VEC], kb[VEC], kg[VEC];
     const int c0 = g.live ? g.c : 0;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         mean[e] = sv[c0 + e]; istd[e] = sv[p.C + c0 + e];
         k1[e] = p.params[rep * p.row_stride + p.w_off + c0 + e] * istd[e];
-        if (!FOLD) { kb[e] = part[c0 + e] * inv_n; kg[e] = part[p.C + c0 + e] * inv_n; }      // totals left in chunk 0 by bn_finalize_kernel<1>
     }
-    if constexpr (FOLD) {
-        __shared__ BnFold<VEC> lds;
-        bn_fold<VEC>(p, g, gi, p.bwd_stats_done ? p.stat_entries : p.chunks, lds, [&](int c, float s, float q, float& b, float& w) {
-            if (p.bwd_stats_done == 2) q = q * sv[p.C + c];
-            if (g.chunk == 0) {
-                float* gr = p.grads + rep * p.row_stride + p.w_off;
-                gr[c] = q; gr[p.C + c] = s;
-            }
-            b = s * inv_n; w = q * inv_n;
-        }, kb, kg);
-        if (!g.live) return;
-    }
+    bn_backward_means<VEC, FOLD>(p, g, gi, rep, kb, kg);
+    if (!g.live) return;
     const int r0 = g.chunk * p.chunk_rows, r1 = min(p.rows, r0 + p.chunk_rows);
 #pragma unroll 4
     for (int r = r0 + g.rl; r < r1; r += g.rl_count) {
@@ -826,23 +844,18 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_vec_kernel(BnParams p)
 // is formed on the fly from the stored output and the pooled gradient, so the full-resolution gradient tensor is
 // neither written nor read (two passes less).  Window w of chunk c: [c * chunk_windows, (c + 1) * chunk_windows).
 // ------------------------------------------------------------------------------------------------------
-template <typename T>
+template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void bn_apply_fwd_pool_vec_kernel(BnParams p)
 {
     constexpr int VEC = VecOf<T>::n;
     const int gi = blockIdx.y, rep = p.order[gi];
     const BnGeo g = bn_geo(p, VEC);
-    if (!g.live) return;
+    if (!FOLD && !g.live) return;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     T* po = tptr<T>(p.pool_out, rep, p.pool_out_rep);
-    const float* row = p.params + rep * p.row_stride;
     float sc[VEC], sh[VEC];
-    const float* sv = p.saved + rep * p.saved_rep;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        const int c = g.c + e;
-        bn_scale_shift(sv[c], sv[p.C + c], row[p.w_off + c], row[p.w_off + p.C + c], sc[e], sh[e]);
-    }
+    bn_forward_scales<T, FOLD>(p, g, gi, rep, x, sc, sh);
+    if (!g.live) return;
     const int windows = p.rows / 4, cw = (windows + p.chunks - 1) / p.chunks;
     const int w0 = g.chunk * cw, w1 = min(windows, w0 + cw);
 #pragma unroll 2
@@ -937,29 +950,27 @@ __global__ __launch_bounds__(256) void bn_sums_pool_vec_kernel(BnParams p)
     }
 }
 
-template <typename T>
+template <typename T, bool FOLD>
 __global__ __launch_bounds__(256) void bn_apply_bwd_pool_vec_kernel(BnParams p)
 {
     constexpr int VEC = VecOf<T>::n;
     const int gi = blockIdx.y, rep = p.order[gi];
     const BnGeo g = bn_geo(p, VEC);
-    if (!g.live) return;
+    if (!FOLD && !g.live) return;
     const T* x = tptr<T>(p.x, rep, p.x_rep);
     const T* pg = tptr<T>(p.pool_g, rep, p.pool_g_rep);
     T* dx = tptr<T>(p.y, rep, p.y_rep);
     const T* mask = p.mask ? tptr<T>(p.mask, rep, p.mask_rep) : nullptr;
-    const float* part = p.partial + gi * p.partial_rep;
     const float* sv = p.saved + rep * p.saved_rep;
-    const float inv_n = 1.0f / (float)p.rows;
     float mean[VEC], istd[VEC], k1[VEC], kb[VEC], kg[VEC], sc[VEC], sh[VEC];
+    bn_backward_means<VEC, FOLD>(p, g, gi, rep, kb, kg);
+    if (!g.live) return;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         const int c = g.c + e;
-        const float db = part[c], dg = part[p.C + c];       // totals left in chunk 0 by bn_finalize_kernel<1>
         const float* row = p.params + rep * p.row_stride + p.w_off;
         mean[e] = sv[c]; istd[e] = sv[p.C + c];
         k1[e] = row[c] * istd[e];
-        kb[e] = db * inv_n; kg[e] = dg * inv_n;
         bn_scale_shift(mean[e], istd[e], row[c], row[p.C + c], sc[e], sh[e]);
     }
     const int windows = p.rows / 4, cw = (windows + p.chunks - 1) / p.chunks;
@@ -1680,11 +1691,32 @@ bool bn_backward_in_one_launch(const BnParams& p, int n_active) { return p.C % (
 // that launch and folded: 512 channels on 1024 rows (8 to 32 entries), fp32, 3 / 8 / 16 replicas forward 16 18 23 and 13 14 18, backward 13
 // 17 23 and 10 13 19; 256 channels on 4096 rows (16 to 64 entries) 19 25 37 and 13 21 33, 16 24 40 and 11 20 35.  Beyond some 64 entries,
 // or 64 MB that all workgroups read together, the launch is the shorter way (bf16, 128 channels on 32768 rows, 128 entries, 7 / 32
-// replicas forward 18 59 and 19 71).
+// replicas forward 18 59 and 19 71).  With a max-pool folded in the same: a network of 13 such layers, five with a pool, three of
+// those below the limit, fp32, 4 replicas 7.52 -> 7.44 ms.
 namespace {
 constexpr int kFoldEntries = 64;
 constexpr long long kFoldBytes = 64 << 20;
-bool bn_folds(const BnParams& p, int vec, int entries, long long workgroups) { return !p.pool && entries <= kFoldEntries && workgroups * entries * 2 * p.cvb * vec * 4 <= kFoldBytes; }
+bool bn_folds(const BnParams& p, int vec, int entries, long long workgroups) { return entries <= kFoldEntries && workgroups * entries * 2 * p.cvb * vec * 4 <= kFoldBytes; }
+
+// (finalize and) apply kernels
+template <typename T> void bn_apply_fwd(const BnParams& p, bool fold, dim3 grid, dim3 fgrid, hipStream_t s)
+{
+    const dim3 block(256);
+    if (!fold) hipLaunchKernelGGL((bn_finalize_kernel<0, T>), fgrid, block, 0, s, p);
+    if (p.pool && fold) hipLaunchKernelGGL((bn_apply_fwd_pool_vec_kernel<T, true>), grid, block, 0, s, p);
+    else if (p.pool) hipLaunchKernelGGL((bn_apply_fwd_pool_vec_kernel<T, false>), grid, block, 0, s, p);
+    else if (fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<T, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<T, false>), grid, block, 0, s, p);
+}
+template <typename T> void bn_apply_bwd(const BnParams& p, bool fold, dim3 grid, dim3 fgrid, hipStream_t s)
+{
+    const dim3 block(256);
+    if (!fold) hipLaunchKernelGGL((bn_finalize_kernel<1, T>), fgrid, block, 0, s, p);
+    if (p.pool && fold) hipLaunchKernelGGL((bn_apply_bwd_pool_vec_kernel<T, true>), grid, block, 0, s, p);
+    else if (p.pool) hipLaunchKernelGGL((bn_apply_bwd_pool_vec_kernel<T, false>), grid, block, 0, s, p);
+    else if (fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<T, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<T, false>), grid, block, 0, s, p);
+}
 }  // namespace
 
 hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
@@ -1707,16 +1739,10 @@ hipError_t launch_bn_fwd(const BnParams& p0, int n_active, hipStream_t s)
         const bool fold = bn_folds(p, vec, p.stats_done ? p.stat_entries : p.chunks, (long long)grid.x * n_active);
         if (p.bf16) {
             if (!p.stats_done) hipLaunchKernelGGL((bn_sums_vec_kernel<0, __bf16>), grid, block, 0, s, p);
-            if (fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<__bf16, true>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((bn_finalize_kernel<0, __bf16>), fgrid, block, 0, s, p);
-            if (p.pool) hipLaunchKernelGGL(bn_apply_fwd_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
-            else if (!fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<__bf16, false>), grid, block, 0, s, p);
+            bn_apply_fwd<__bf16>(p, fold, grid, fgrid, s);
         } else {
             if (!p.stats_done) hipLaunchKernelGGL((bn_sums_vec_kernel<0, float>), grid, block, 0, s, p);
-            if (fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<float, true>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((bn_finalize_kernel<0, float>), fgrid, block, 0, s, p);
-            if (p.pool) hipLaunchKernelGGL(bn_apply_fwd_pool_vec_kernel<float>, grid, block, 0, s, p);
-            else if (!fold) hipLaunchKernelGGL((bn_apply_fwd_vec_kernel<float, false>), grid, block, 0, s, p);
+            bn_apply_fwd<float>(p, fold, grid, fgrid, s);
         }
         return hipGetLastError();
     }
@@ -1758,19 +1784,13 @@ hipError_t launch_bn_bwd(const BnParams& p0, int n_active, hipStream_t s)
             if (p.bwd_stats_done) {}                                  // the data gradient above left the sums
             else if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
             else hipLaunchKernelGGL((bn_sums_vec_kernel<1, __bf16>), grid, block, 0, s, p);
-            if (fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<__bf16, true>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((bn_finalize_kernel<1, __bf16>), fgrid, block, 0, s, p);
-            if (p.pool) hipLaunchKernelGGL(bn_apply_bwd_pool_vec_kernel<__bf16>, grid, block, 0, s, p);
-            else if (!fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<__bf16, false>), grid, block, 0, s, p);
+            bn_apply_bwd<__bf16>(p, fold, grid, fgrid, s);
         } else {
             if (p.bwd_stats_done == 1) return hipErrorInvalidValue;  // (of the stored output: only the bf16 data-gradient kernels leave those)
             if (p.bwd_stats_done) {}
             else if (p.pool) hipLaunchKernelGGL(bn_sums_pool_vec_kernel<float>, grid, block, 0, s, p);
             else hipLaunchKernelGGL((bn_sums_vec_kernel<1, float>), grid, block, 0, s, p);
-            if (fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<float, true>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((bn_finalize_kernel<1, float>), fgrid, block, 0, s, p);
-            if (p.pool) hipLaunchKernelGGL(bn_apply_bwd_pool_vec_kernel<float>, grid, block, 0, s, p);
-            else if (!fold) hipLaunchKernelGGL((bn_apply_bwd_vec_kernel<float, false>), grid, block, 0, s, p);
+            bn_apply_bwd<float>(p, fold, grid, fgrid, s);
         }
         return hipGetLastError();
     }

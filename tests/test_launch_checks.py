@@ -474,3 +474,18 @@ def test_weight_copies_of_many_layers(checked):
     cases = [case(deep(n), (8, 8, 16), 4, [1, 1], bf16) for n in (33, 34) for bf16 in (0, 1)]
     assert [layers_in(r["trace"], "weight_copy") for r in checked(cases)] == [1, 1, 2, 2]
     assert_clean(checked, cases)
+
+
+def test_batch_norms_with_a_pool_that_add_their_sums_themselves(checked):
+    """The same limit of 64 entries where a max-pool is folded into the batch norm."""
+    cases = []
+    for side in (16, 32):
+        b = nets._Builder()
+        t = b.relu(b.bn(b.conv(0, 64)))
+        t = b.maxpool(b.relu(b.bn(b.conv(t, 64))))
+        b.dense(b.gap(t), 10)
+        cases += [case(b, (side, side, 3), 16, [1, 1], bf16, options=[(1, 1)]) for bf16 in (0, 1)]
+    runs = checked(cases)
+    totals_here = [[any(k in name and "Lb1" in name for name in r["trace"]) for k in ("fwd_pool", "bwd_pool")] for r in runs]
+    assert totals_here == [[True, True]] * 2 + [[True, False]] * 2     # (of 16 images of 32 x 32: 64 tiles of the convolution, 128 chunks)
+    assert_clean(checked, cases)
