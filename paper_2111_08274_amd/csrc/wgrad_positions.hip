@@ -13,13 +13,17 @@
 // A workgroup owns all nine taps of 64 input against 64 output channels and walks positions along the rows of sixteen images.  A
 // step multiplies one position: of x it needs the 3 x 3 positions around it, the columns to the left of which came with the steps
 // before, so a step fetches one column of three (six operands of 32 channels) and the position's dy (two): one for each of the
-// eight waves.  Columns are numbered along the walk, and x and dy have a ring of four places each: with one barrier a step, step t reads the
-// columns t - 1 to t + 1 and, ahead, dy of t + 1 (in front of the first step that of t too) while those of t + 2 are written.  Operands
-// are fetched two steps before they are written, beside the matrix instructions.
+// eight waves.  Two steps make a pair with one barrier: within it the waves of a SIMD drift apart, so that one's splits and
+// LDS traffic lie beside the other's matrix instructions (a barrier after each step, 16 / 4 replicas: 14.94 / 2.67 ms of these launches
+// in ResNet-18 / VGG-16; a pair 14.24 / 2.60).  Columns are numbered along the walk, and x and dy have a ring of six places each, which
+// fills the 160 KB together: the pair of t and t + 1 reads the columns t - 1 to t + 2 and, ahead, dy of t + 2 (in front of
+// the first pair that of t too) while those of t + 3 and t + 4 are written.  Operands are fetched two steps before they are written, beside
+// the matrix instructions.
 // Waves 0 to 3 multiply the corner taps and the middle one, waves 4 to 7 the four others, each for a block of 32 x 32 channels: on a
 // SIMD, which has one of either, that is nine.  Per step: 54 matrix instructions a SIMD (1728 clocks), some 130 KiB of LDS read
 // (600 at the measured 220 bytes a clock), 24 KiB written (350 at 70), a wave's eight loads and some 90 vector instructions.
-// 3 x 3, batch 64, us with the reduction of the split sums (wgrad_general_kernel / this; TFLOP/s of fp32 products):
+// 3 x 3, batch 64, us with the reduction of the split sums (wgrad_general_kernel / this, with a barrier after each step: pairs take some
+// 4 % less; TFLOP/s of fp32 products):
 //   64 channels, 32 x 32 images:   1 replica 67 / 46,  4 replicas 207 / 117,  16 replicas 629 / 414 (187 TFLOP/s)
 //   128 channels, 16 x 16:         64 / 47,  128 / 108,  481 / 382 (207)
 //   256 channels, 8 x 8:           67 / 49,  139 / 110,  525 / 339 (224)
@@ -37,10 +41,10 @@ using namespace tiles;
 
 constexpr int kImages = 16;                                   // a step's contraction
 constexpr int kOperand = 3 * 1024, kColumn = 6 * kOperand;    // bytes: 32 channels x 16 images; three positions x 64 channels
-constexpr int kRing = 4 * kColumn, kStepLds = kRing + 8 * kOperand;
+constexpr int kPlaces = 6, kRing = kPlaces * kColumn, kStepLds = kRing + kPlaces * 2 * kOperand;
 // taps 0, 2, 4, 6, 8 of the corner waves, 1, 3, 5, 7 of the others (and a fifth that is not multiplied)
 constexpr int kCornerRow[5] = {0, 0, 1, 2, 2}, kCornerCol[5] = {0, 2, 1, 0, 2}, kEdgeRow[5] = {0, 1, 1, 2, 1}, kEdgeCol[5] = {1, 0, 2, 1, 1};
-// (The first of either reads a column that was written before the last step, so that its operands can be read before the barrier.)
+// (The first of either reads a column that was written before the last pair, so that its operands can be read before the barrier.)
 constexpr int kStagePitch = 36;                               // floats per staged row
 
 // A 32 x 32 block or a bias: stored, or (w set: it is the complete gradient) applied as the update
@@ -74,7 +78,7 @@ __global__ __launch_bounds__(512, 2) void wgrad_general_position_kernel(GeneralW
     const Buffer src = buffer(is_x ? p.x + (long long)rep * p.x_rep : p.dy + (long long)rep * p.dy_rep, (unsigned)(p.B * hw) * (unsigned)channels * 4u);
     const unsigned image = (unsigned)(hw * channels) * 4u;    // bytes; images beyond the batch lie outside the buffer: zeros
     const unsigned at = (unsigned)(lane >> 5) * 8u * image + (unsigned)ch * 4u;
-    constexpr int lead = 2;                                   // steps between writing an operand and multiplying it
+    constexpr int kPair = 2, lead = kPair + 1;                // positions a barrier; steps between writing an operand and multiplying it
     int lt, lg, ly, lx;                                       // the column that is fetched next
     auto seek = [&](int t) { lt = t; lg = t / hw; ly = (t - lg * hw) / p.W; lx = t - lg * hw - ly * p.W; };
     auto fetch = [&](f4 (&v)[2]) {
@@ -87,12 +91,15 @@ __global__ __launch_bounds__(512, 2) void wgrad_general_position_kernel(GeneralW
         if (lx == p.W) { lx = 0; ++ly; }
         if (ly == p.H) { ly = 0; ++lg; }
     };
-    auto place = [&](int t) { return smem + (is_x ? (t & 3) * kColumn + wave * kOperand : kRing + ((t & 3) * 2 + block) * kOperand); };
-    auto write = [&](const f4 (&v)[2], int t) {
+    int ring[kPlaces];                                        // places of the columns t - 1 to t + 4, t the first position of a pair
+#pragma unroll
+    for (int k = 0; k < kPlaces; ++k) ring[k] = k;
+    auto place = [&](int at) { return smem + (is_x ? at * kColumn + wave * kOperand : kRing + (at * 2 + block) * kOperand); };
+    auto write = [&](const f4 (&v)[2], int at) {
         u2 h0, m0, l0, h1, m1, l1;
         split3(v[0], h0, m0, l0);
         split3(v[1], h1, m1, l1);
-        char* const o = place(t) + lane * 16;
+        char* const o = place(at) + lane * 16;
         *reinterpret_cast<u4*>(o) = join8(h0, h1);
         *reinterpret_cast<u4*>(o + 1024) = join8(m0, m1);
         *reinterpret_cast<u4*>(o + 2048) = join8(l0, l1);
@@ -109,27 +116,27 @@ __global__ __launch_bounds__(512, 2) void wgrad_general_position_kernel(GeneralW
     };
     const bool mine = c0 + cib * 32 < p.C && n0 + cob * 32 < p.N;
     int y, x;                                                 // position of the present step
-    auto column = [&](int t, int r, int s) { return smem + ((t + s - 1) & 3) * kColumn + (r * 2 + cib) * kOperand; };
+    auto column = [&](int at, int r) { return smem + at * kColumn + (r * 2 + cib) * kOperand; };
     auto has_tap = [&](int j) {
         const int r = corners ? kCornerRow[j] : kEdgeRow[j], s = corners ? kCornerCol[j] : kEdgeCol[j];
         return (j < 4 || corners) && (unsigned)(y + r - 1) < (unsigned)p.H && (unsigned)(x + s - 1) < (unsigned)p.W;
     };
     bf16x8 a[2][3], b[2][3];                                  // read a tap ahead, the first of a step before the barrier (of a tap outside the image whatever is there)
-    auto read_x = [&](bf16x8 (&o)[3], int t, int j) {
-        const char* const from = column(t, corners ? kCornerRow[j] : kEdgeRow[j], corners ? kCornerCol[j] : kEdgeCol[j]) + lane * 16;
+    auto read_x = [&](bf16x8 (&o)[3], int d, int j) {         // of position t + d
+        const char* const from = column(corners ? ring[d + kCornerCol[j]] : ring[d + kEdgeCol[j]], corners ? kCornerRow[j] : kEdgeRow[j]) + lane * 16;
 #pragma unroll
         for (int q = 0; q < 3; ++q) o[q] = *reinterpret_cast<const bf16x8*>(from + q * 1024);
     };
-    auto read_dy = [&](bf16x8 (&o)[3], int t) {
+    auto read_dy = [&](bf16x8 (&o)[3], int d) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) o[q] = *reinterpret_cast<const bf16x8*>(smem + kRing + ((t & 3) * 2 + cob) * kOperand + q * 1024 + lane * 16);
+        for (int q = 0; q < 3; ++q) o[q] = *reinterpret_cast<const bf16x8*>(smem + kRing + (ring[d + 1] * 2 + cob) * kOperand + q * 1024 + lane * 16);
     };
-    auto multiply = [&](int t, int d) {
+    auto multiply = [&](int d) {
         if (!mine) return;
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
-            if (j == 4) { read_x(a[(d + 1) & 1], t + 1, 0); read_dy(b[(d + 1) & 1], t + 1); }
-            else if (j < 3 || corners) read_x(a[(d + j + 1) & 1], t, j + 1);
+            if (j == 4) { read_x(a[(d + 1) & 1], d + 1, 0); read_dy(b[(d + 1) & 1], d + 1); }
+            else if (j < 3 || corners) read_x(a[(d + j + 1) & 1], d, j + 1);
             if (!has_tap(j)) continue;
             const bf16x8 (&u)[3] = a[(d + j) & 1], (&v)[3] = b[d & 1];
             // operands swapped: the accumulator holds the transposed block.  Small products in ascending size.
@@ -144,33 +151,40 @@ __global__ __launch_bounds__(512, 2) void wgrad_general_position_kernel(GeneralW
     clear();
     y = t0 % hw / p.W; x = t0 % hw % p.W;
     if (t0 < t1) {
-        constexpr int kAhead = 2;                                // columns on their way
-        f4 v[kAhead][2] = {};
+        f4 v[kPair][2] = {};                                  // columns on their way
         auto sum8 = [&](const f4 (&u)[2]) { return ((u[0][0] + u[0][1]) + (u[0][2] + u[0][3])) + ((u[1][0] + u[1][1]) + (u[1][2] + u[1][3])); };
         seek(is_x ? t0 - 1 : t0);
         {
-            f4 u[3][2] = {};
-            fetch(u[0]); fetch(u[1]);
-            if (is_x) { fetch(u[2]); write(u[0], t0 - 1); write(u[1], t0); write(u[2], t0 + 1); }
-            else { write(u[0], t0); write(u[1], t0 + 1); bias = sum8(u[0]); if (t0 + 1 < t1) bias += sum8(u[1]); }
+            f4 u[4][2] = {};
+            fetch(u[0]); fetch(u[1]); fetch(u[2]);
+            if (is_x) fetch(u[3]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (is_x) write(u[k], ring[k]);
+                else if (k < 3) { write(u[k], ring[k + 1]); if (t0 + k < t1) bias += sum8(u[k]); }
+            }
         }
 #pragma unroll
-        for (int d = 0; d < kAhead; ++d) fetch(v[d]);         // columns t0 + 2, t0 + 3
+        for (int d = 0; d < kPair; ++d) fetch(v[d]);          // columns t0 + 3, t0 + 4
         __syncthreads();
-        read_x(a[0], t0, 0);
-        read_dy(b[0], t0);
-        for (int t = t0; t < t1; t += kAhead) {
+        read_x(a[0], 0, 0);
+        read_dy(b[0], 0);
+        for (int t = t0; t < t1; t += kPair) {
 #pragma unroll
-            for (int d = 0; d < kAhead; ++d) {
+            for (int d = 0; d < kPair; ++d) {
                 const int now = t + d;
                 if (now >= t1) break;
-                write(v[d], now + lead);
+                write(v[d], ring[d + lead + 1]);
                 if (with_bias && now + lead < t1) bias += sum8(v[d]);
                 fetch(v[d]);
-                multiply(now, d);
+                multiply(d);
                 next_position();
-                __syncthreads();
             }
+            __syncthreads();
+            const int u0 = ring[0], u1 = ring[1];
+#pragma unroll
+            for (int k = 0; k + kPair < kPlaces; ++k) ring[k] = ring[k + kPair];
+            ring[kPlaces - 2] = u0; ring[kPlaces - 1] = u1;
         }
     }
     float bad = 0.f;
@@ -187,19 +201,19 @@ __global__ __launch_bounds__(512, 2) void wgrad_general_position_kernel(GeneralW
             f4 v[2] = {};
             seek(is_x ? t - 1 : t);
             for (int q = 0; q < (is_x ? 3 : 1); ++q) {
-                const int at_t = lt;
+                const int at = lt - t + 1;
                 fetch(v);
-                char* const o = place(at_t) + lane * 32;
+                char* const o = place(at) + lane * 32;
                 *reinterpret_cast<f4*>(o) = v[0];
                 *reinterpret_cast<f4*>(o + 16) = v[1];
             }
             __syncthreads();
-            const float* const b = reinterpret_cast<const float*>(smem + kRing + ((t & 3) * 2 + cob) * kOperand + lane * 32);
+            const float* const b = reinterpret_cast<const float*>(smem + kRing + (1 * 2 + cob) * kOperand + lane * 32);
 #pragma unroll
             for (int j = 0; j < 5; ++j) {
                 const int r = corners ? kCornerRow[j] : kEdgeRow[j], s = corners ? kCornerCol[j] : kEdgeCol[j];
                     if (!has_tap(j)) continue;
-                const float* const a = reinterpret_cast<const float*>(column(t, r, s) + lane * 32);
+                const float* const a = reinterpret_cast<const float*>(column(s, r) + lane * 32);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], a[e], acc[j], 0, 0, 0);
             }
