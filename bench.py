@@ -32,20 +32,20 @@ TRAFFIC = {
     ("conv_dgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_general_patch.hip",
                                         "paper_2111_08274_amd/csrc/mfma_tiles.h",
                                         "paper_2111_08274_amd/csrc/slabs.h"),
-                                       "dc4b7a23e384a464c0a8be9ce29e0f625b54427703f89c3e65d36ed818029f35",
-                                       285552027.4),
+                                       "fcffdfb6ff06c3f10b09f13c26e4b8ed01dd42e5bd531bdb22a3550bbbd7b5b0",
+                                       285460338.4),
     ("conv_fwd", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_general_patch.hip",
                                       "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
                                       "paper_2111_08274_amd/csrc/mfma_tiles.h",
                                       "paper_2111_08274_amd/csrc/slabs.h"),
-                                     "59b4ee5d26dff79123b233ff10001e9dd31ae9a4ee9ff7d233064dd61e91d6dd",
-                                     223324031.8),
+                                     "b38f2447507b6862ca588622c452904176af5466a670fa73e5ca2724fb560ebf",
+                                     223288850.9),
     # (the figure includes the fused update's parameter and momentum traffic)
     ("conv_wgrad", "vgg16-bf16-n32"): (("paper_2111_08274_amd/csrc/conv_bf16_fast.hip",
                                         "paper_2111_08274_amd/csrc/conv_first_bf16.hip",
                                         "paper_2111_08274_amd/csrc/mfma_tiles.h"),
                                        "e8e93db763c155aeb1c5665d5f237d97d145c827da9a7035a84c010664c50a81",
-                                       514597249.6),
+                                       514575904.6),
 }
 
 

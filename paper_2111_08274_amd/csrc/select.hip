@@ -129,8 +129,8 @@ __device__ __forceinline__ double selection_function(double v, double mu)
 // instruction only every 5 to 8 clocks, so what counts is the number of instructions on the path, and straight-line code that
 // runs once is paid for in instruction fetches.  A draw is a tree of sums over the lanes (six steps, where the running
 // sums of the rule are N dependent additions: see kSumError), a product, two ballots; uniforms and f are computed up
-// front.  64 replicas and 8 draws, with the launch: 6.1 us with the chain of additions in every draw, 4.4 here; forecast versions, 24
-// replicas and 12 draws: 9.5 and 6.
+// front.  64 replicas and 8 draws, with the launch: 5.7 us with the chain of additions in every draw, 4.2 here; forecast versions, 24
+// replicas and 12 draws: 11.0 and 6.3.
 template <typename V>
 __global__ __launch_bounds__(64) void select_kernel(SelectArgs a)
 {
@@ -513,7 +513,7 @@ hipError_t launch_select_static(SelectArgs a, hipStream_t s)
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t s)
 {
-    // up to 64 replicas are a lane each and need no LDS in a draw (64 replicas, 8 draws 4.4 us; 65, 11 draws in the other 9.9)
+    // up to 64 replicas are a lane each and need no LDS in a draw (64 replicas, 8 draws 4.2 us; 65, 11 draws in the other 9.9)
     if (a.n <= 64) {
         if (a.versions_f64) hipLaunchKernelGGL(select_kernel<double>, dim3(1), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(select_kernel<int>, dim3(1), dim3(64), 0, s, a);
