@@ -47,6 +47,7 @@ public:
     // Sum fusion: the addition of two tensors behind a batch norm that is only read there runs in that BN's forward store (the
     // second of two such BNs: the other operand exists by then).  Its backward pass copies the gradient to both operands,
     // but for those with no ReLU mask and no other reader: their gradient IS the sum's, and shares its buffer.
+    std::vector<double> beside;           // per layer: flops of the data gradients of this layer and those below, one replica
     std::vector<int> add_into;            // per layer (BN): the ADD layer folded into its forward store, or -1
     std::vector<char> add_done;           // per layer (ADD): forward folded away
     // An operand that does need a copy, but whose next gradient comes from a convolution run from patches (the shortcut of a residual block
@@ -550,6 +551,15 @@ hadfl_status train_create(const hadfl_config& cfg, const NetPlan& plan, const Tr
             e->bstat_for[i] = k; e->bstat_input[i] = 1;
         }
     }
+    e->beside.assign(plan.layers.size(), 0.0);
+    for (size_t i = 0; i < plan.layers.size(); ++i) {
+        const Layer& l = plan.layers[i];
+        const TensorShape a = plan.tensors[l.in0], o = plan.tensors[l.out];
+        double flops = 0.0;
+        if (l.in0 != 0 && l.type == HADFL_OP_CONV) flops = 2.0 * cfg.batch * o.h * o.w * l.k * l.k * a.c * (double)l.cout;
+        if (l.in0 != 0 && l.type == HADFL_OP_DENSE) flops = 2.0 * cfg.batch * (double)a.numel() * l.cout;
+        e->beside[i] = (i ? e->beside[i - 1] : 0.0) + flops;
+    }
     *out = e;
     return HADFL_OK;
 }
@@ -580,7 +590,7 @@ void train_destroy(TrainEngine* e)
 
 namespace {
 
-constexpr double kMinSideFlops = 2e8;
+constexpr double kMinBesideFlops = 4e8;
 
 struct Runner {
     TrainEngine& e;
@@ -598,16 +608,19 @@ struct Runner {
     hipStream_t main_stream = nullptr;
     bool forked = false;                  // a flag, not the handle: the caller's stream may be the null stream
     bool side_busy = false;               // the side stream has work of this sub-step
-    // The launches that follow, a layer's weight gradient of `flops`, go to the side stream, ordered after everything
-    // enqueued on the main stream so far.  A weight gradient that takes about as long as the two events (some 10 us) stays on
-    // the main stream as long as nothing of this sub-step is on the side stream; behind that everything follows
-    // in order there, for the scratch of the split sums and the updated weights are the side stream's until the join.
-    // Four perceptrons, ten sub-steps: 341 us with every weight gradient on the side stream, 230 us with none; a residual
-    // net of 40 channels on 5 replicas: 1650 us and 1800 us.
-    void fork(double flops)
+    // The launches that follow, a layer's weight gradient, go to the side stream, ordered after everything enqueued on the main
+    // stream so far.  `beside`: flops of the data gradients that are still to come on the main stream, which is what the side stream's
+    // work can lie beside; where they take less time than the events (some 20 us a sub-step) the weight gradients stay on the
+    // main stream as long as nothing of this sub-step is on the side stream.  Behind the first that is there everything
+    // follows in order, for the scratch of the split sums and the updated weights are the side stream's until the join.
+    // Earlier the line was at 2e8 flops of the one weight gradient.  That / this, us a cycle: residual net of 64 to 128 channels on 5 replicas
+    // 1327 / 1270, of 40 to 80 on 2 772 / 720; convolution net of 32 and 64 channels, batch 16, on 2 (302 Mflop beside) 329 / 296 and on 8
+    // 379 / 372; perceptron of 784 x 128, batch 256, whose wide layer has nothing beside it, on 4 157 / 129 and on 16 199 / 153.
+    // Lines at 2e8 / 4e8: a residual net of 24 to 48 channels on 8 (304) 653 / 636 (earlier 629), that convolution net on 2 326 / 296.
+    void fork(double beside)
     {
         if (!e.use_side || !e.side || rc != hipSuccess) return;
-        if (!side_busy && flops < kMinSideFlops) return;
+        if (!side_busy && beside < kMinBesideFlops) return;
         side_busy = true;
         rc = hipEventRecord(e.ev_fork, s);
         if (rc == hipSuccess) rc = hipStreamWaitEvent(e.side, e.ev_fork, 0);
@@ -1058,7 +1071,7 @@ struct Runner {
             } else {
                 p.out = e.buf.grad + l.w_off; p.out_rep = e.plan.row_stride;
             }
-            fork(na * gemm_flops(p));
+            fork(na * e.beside[i]);
             flush_pending_prep();
             FirstConvParams fc;
             if (first_conv(i, fc)) {
