@@ -4,7 +4,8 @@
 // Layer by layer a step of such a network is four dependent launches of 5 to 10 us that compute for one or two.  A workgroup
 // here owns sixteen hidden units of a replica through the whole step: their column of the first layer's weights and row of
 // the second's are read and updated by nobody else, so all that the workgroups of a replica have to exchange are their shares of
-// the logits.  The kernel boundary is that exchange:
+// the logits.  The kernel boundary is that exchange, through two buffers that steps take in turn: a launch reads the shares that the one before
+// it wrote, of all workgroups of a replica, and writes its own for the next where none of this launch reads, since nothing orders its workgroups:
 //   end of a step     logits = sum of the shares; loss and its gradient; the gradient of the own hidden units; both weight
 //                     gradients and their updates;
 //   begin of a step   the own hidden units of the next batch, from the weights just updated, still in registers; their share of
@@ -57,7 +58,8 @@ __global__ __launch_bounds__(kThreads, 2) void dense_pair_kernel(DensePairParams
     float* const m1 = p.m1 ? p.m1 + rep * p.w_rep : nullptr;
     float* const m2 = p.m2 ? p.m2 + rep * p.w_rep : nullptr;
     T* const hidden = reinterpret_cast<T*>(p.hidden + rep * p.act_rep) + u0;
-    float* const share = p.share + rep * p.act_rep;
+    const float* const share_in = p.share_in + rep * p.act_rep;
+    float* const share_out = p.share_out + rep * p.act_rep;
     const long long bias1 = (long long)p.K * p.H + u0, bias2 = (long long)p.H * p.N;
 
     // the own weights: 16 features x 16 units a block
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_pair_kernel(DensePairParams
     float w2v = own2 ? w2[o2] : 0.f;
     if (tid >= 256) s_w2[a2][n2] = kSplit ? w2v : (float)(__bf16)w2v;
     if (tid < kUnits) s_b1[tid] = p.has_bias1 ? w1[bias1 + tid] : 0.f;
-    if (tid < kMaxClasses) s_b2[tid] = p.has_bias2 && tid < p.N ? w2[bias2 + tid] : 0.f;
+    if (tid < kMaxClasses) s_b2[tid] = p.has_bias2 && j == 0 && tid < p.N ? w2[bias2 + tid] : 0.f;      // (the first workgroup's alone, which updates it)
     // the rows of the step that ends and of the one that begins (n_samples is a multiple of the batch)
     long long row = ((p.cursor[rep] + p.ahead - (ends ? 1 : 0)) * (long long)B) % p.n_samples;
     const float* const data = p.x + (long long)rep * p.n_samples * p.K;
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_pair_kernel(DensePairParams
         for (int i = tid; i < B * kUnits; i += kThreads) {
             const int r = i >> 4, n = i & 15;
             float z = 0.f;
-            for (int q = 0; q < J; ++q) z += share[(q * B + r) * 16 + n];
+            for (int q = 0; q < J; ++q) z += share_in[(q * B + r) * 16 + n];
             s_dy[r][n] = (float)(T)z;                      // the logits as they would be stored
             s_h[r][n] = (float)hidden[(long long)r * p.H + n];
         }
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_pair_kernel(DensePairParams
         float z = j == 0 ? s_b2[n] : 0.f;
 #pragma unroll
         for (int k = 0; k < kUnits; ++k) z += s_h[r0 + r][k] * s_w2[k][n];
-        if (r0 + r < B) share[(j * B + r0 + r) * 16 + n] = z;
+        if (r0 + r < B) share_out[(j * B + r0 + r) * 16 + n] = z;
     }
 }
 
@@ -313,6 +315,7 @@ hipError_t launch_dense_pair(const DensePairParams& p, hipStream_t s)
     const int n = p.n_end > p.n_begin ? p.n_end : p.n_begin;
     if (n < 1) return hipSuccess;
     if (p.batch < 1 || p.N < 1 || p.K < 16 || p.H < kUnits || !dense_pair_supported(p.batch, p.K, p.H, p.N) || p.n_samples % p.batch != 0) return hipErrorInvalidValue;
+    if (p.n_end > 0 && p.n_begin > 0 && p.share_in == p.share_out) return hipErrorInvalidValue;
     const dim3 grid(die_grid((long long)n * (p.H / kUnits)));
     if (p.bf16) hipLaunchKernelGGL((dense_pair_kernel<__bf16>), grid, dim3(kThreads), 0, s, p);
     else hipLaunchKernelGGL((dense_pair_kernel<float>), grid, dim3(kThreads), 0, s, p);

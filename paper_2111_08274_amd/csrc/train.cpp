@@ -209,13 +209,13 @@ bool dense_rows_pays(const hadfl_config& cfg, const NetPlan& plan, const Layer& 
 
 // The network is a dense layer on the data set with a ReLU and a classifier behind it, of a size for dense_pair_kernel.  Four
 // steps a call, us a step layer by layer and there, batch 8 / 32 / 64 / 128:
-//   784 features, 128 hidden units:   4 replicas 27 30 34 44 and 17 19 26 41,   16: 31 34 47 71 and 18 20 27 42,   64: 45 72 87 113 and 38 42 57 87
-//   1024 features, 256 hidden units:  4: 31 35 40 69 and 21 24 34 57,   32: 51 78 93 121 and 48 54 75 120,   64: 103 114 139 202 and 92 106 147 256
+//   784 features, 128 hidden units:   4 replicas 27 30 33 44 and 16 17 24 39,   16: 30 34 60 71 and 16 18 24 40,   64: 45 72 88 113 and 37 42 56 86
+//   1024 features, 256 hidden units:  4: 29 34 39 70 and 19 22 32 52,   32: 51 79 94 121 and 47 54 74 120,   64: 104 115 138 202 and 90 104 146 265
 // The last has four workgroups a compute unit: beyond two the batches above 32 stay with the single layers.  A call of one step has
-// no beginning to share a launch with: one replica, batch 128 42 and 46, 64 34 and 31, hence eight replicas above 64.  512 hidden units,
-// 128 features, 16 replicas: 28 31 40 76 and 27 29 46 82.  Rows of fewer than 128 features leave waves without a block; they stay
-// with the single layers' kernels, though this one would be the faster for them too (32 features, 64 hidden units, 4 replicas: 21 22 28 37 and
-// 9 10 13 20), so that networks of a few features still run those.
+// no beginning to share a launch with: one replica, batch 128 43 and 45, 64 33 and 31, hence eight replicas above 64.  More than 256 hidden
+// units stay with the single layers too (512, 128 features, 16 replicas 27 30 40 77 and 23 25 37 62; others not measured).  Rows of fewer
+// than 128 features leave waves without a block; they stay with the single layers' kernels, though this one would be the faster for them
+// too (32 features, 64 hidden units, 4 replicas: 21 22 28 38 and 9 10 13 20), so that networks of a few features still run those.
 bool dense_pair_net(const hadfl_config& cfg, const NetPlan& plan)
 {
     if (plan.layers.size() != 3) return false;
@@ -793,19 +793,20 @@ struct Runner {
     void dense_pair_steps()
     {
         const Layer &a = e.plan.layers[0], &b = e.plan.layers[2];
-        const int t = e.out_tensor[0];
+        float* const shares[2] = {grad(a.out), grad(e.plan.layers[1].out)};      // taken in turn: the room of gradients that these launches never write
         DensePairParams d{};
         d.x = e.buf.x; d.y = e.buf.y; d.cursor = e.buf.cursor; d.n_samples = e.cfg.n_samples; d.batch = e.cfg.batch;
         d.K = (int)e.plan.tensors[0].numel(); d.H = a.cout; d.N = b.cout; d.has_bias1 = a.bias; d.has_bias2 = b.bias;
         d.w1 = e.buf.replicas + a.w_off; d.w2 = e.buf.replicas + b.w_off; d.w_rep = e.plan.row_stride;
         d.m1 = e.buf.mom ? e.buf.mom + a.w_off : nullptr; d.m2 = e.buf.mom ? e.buf.mom + b.w_off : nullptr;
         d.lr = e.cfg.lr; d.momentum = e.cfg.momentum;
-        d.hidden = actw(t); d.share = grad(t); d.act_rep = e.rep_block;      // (the shares take the room of the hidden units' gradient)
+        d.hidden = actw(e.out_tensor[0]); d.act_rep = e.rep_block;
         d.loss = e.buf.loss; d.bf16 = e.cfg.bf16; d.order = e.buf.order;
         const double macs = (double)d.batch * ((double)d.K * d.H + (double)d.H * d.N), wbytes = 4.0 * (d.K + d.N) * d.H;
         cur_layer = 0;
         for (int s0 = 0; s0 <= e.e_max; ++s0) {
             d.ahead = s0;
+            d.share_in = shares[(s0 + 1) & 1]; d.share_out = shares[s0 & 1];
             d.n_end = s0 > 0 ? e.n_active[s0 - 1] : 0; d.n_begin = s0 < e.e_max ? e.n_active[s0] : 0;
             na = 1;
             run("dense_step", 2.0 * (macs * d.n_begin + (macs + (double)d.batch * d.H * d.N) * d.n_end),

@@ -247,7 +247,8 @@ struct DensePairParams {
     float* w1; float* w2; long long w_rep;   // weights [K][H] followed by bias [H]; [H][N] followed by bias [N]
     float* m1; float* m2;                    // momentum of the same, or null; same stride
     float lr, momentum;
-    float* hidden; float* share; long long act_rep;      // hidden units [batch][H]; shares of the logits, floats [H / 16][batch][16]
+    float* hidden; long long act_rep;        // hidden units [batch][H]
+    const float* share_in; float* share_out;             // shares of the logits of the step that ends and of the one that begins, floats [H / 16][batch][16]; two buffers
     float* loss;
     int n_end, n_begin;
     int bf16;

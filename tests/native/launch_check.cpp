@@ -4,7 +4,9 @@
 //   * every range lies inside one of the buffers the caller gave to the library;
 //   * ranges of different purposes (activations and their gradients, weight copies, split-K partial sums, batch-norm partial sums,
 //     parameters, gradients, momentum, position tables, small state) never share a byte;
-//   * the partial sums a batch norm reads are those that were left for it: no other launch has written the region since.
+//   * the partial sums a batch norm reads are those that were left for it: no other launch has written the region since;
+//   * the shares of the logits that the workgroups of a network of two dense layers read of each other are the launch before's, and
+//     no workgroup of the launch writes to them.
 // Loaded ahead of libhadfl.so with RTLD_GLOBAL, so that its symbols are found first.
 #include <hip/hip_runtime.h>
 
@@ -31,6 +33,7 @@ std::map<const void*, std::string> g_names;
 std::string g_report, g_trace;
 int g_errors = 0;
 struct { const void* of; int entries; long long rep; } g_sums = {nullptr, 0, 0};      // what the batch-norm sums region holds
+struct { const float* of; int n; } g_shares = {nullptr, 0};      // dense_pair_kernel: shares of the logits that the launch before wrote, of how many replicas
 const void* g_mom = nullptr;                          // (parameters, gradients and momentum have one stride and one layout)
 
 void error(const std::string& kernel, const std::string& what)
@@ -165,6 +168,28 @@ void batch_norm(Launch l, const BnParams& p, int n)
     } else if (has(l.name, "finalize") || has(l.name, "Lb1E")) l.check_sums(p.partial, p.partial_rep, p.chunks, p.C, p.x);
 }
 
+// Shares of the logits: what a launch reads of a step that ends is what the launch before it wrote of it, and it writes to none of
+// that, nor to the hidden units of that step, whatever its workgroups' order.
+void shares(const Launch& l, const DensePairParams& p)
+{
+    const long long bytes = (long long)p.H * p.batch * 4;
+    if (p.n_end > 0) {
+        l.tensor(kAct, p.share_in, p.act_rep, bytes);
+        if (g_shares.of != p.share_in || g_shares.n < p.n_end) error(l.name, "reads shares that the launch before did not write");
+    }
+    g_shares = {nullptr, 0};
+    if (p.n_begin < 1) return;
+    l.tensor(kAct, p.share_out, p.act_rep, bytes);
+    g_shares = {p.share_out, p.n_begin};
+    const auto apart = [](const void* a, long long na, const void* b, long long nb) { return (Addr)a + (Addr)na <= (Addr)b || (Addr)b + (Addr)nb <= (Addr)a; };
+    for (int g = 0; g < p.n_begin; ++g) {
+        const float* const out = p.share_out + l.order[g] * p.act_rep;
+        if (!apart(out, bytes, p.hidden + l.order[g] * p.act_rep, (long long)p.batch * p.H * l.es)) error(l.name, "writes shares over hidden units");
+        for (int o = 0; o < p.n_end; ++o)
+            if (!apart(out, bytes, p.share_in + l.order[o] * p.act_rep, bytes)) { error(l.name, "writes shares that another workgroup of the launch may still read"); return; }
+    }
+}
+
 void look(const std::string& name, dim3 grid, void** args)
 {
     Launch l{name, nullptr, 0, 4};
@@ -222,7 +247,7 @@ void look(const std::string& name, dim3 grid, void** args)
         l.order = p.order; l.n = std::max(p.n_end, p.n_begin); l.es = p.bf16 ? 2 : 4;
         l.data(p.x, p.n_samples, p.batch, p.K);
         l.act(p.hidden, p.act_rep, (long long)p.batch * p.H);
-        l.tensor(kAct, p.share, p.act_rep, (long long)p.H * p.batch * 4);
+        shares(l, p);
         l.tensor(kParam, p.w1, p.w_rep, (long long)(p.K + (p.has_bias1 ? 1 : 0)) * p.H * 4);
         l.tensor(kParam, p.w2, p.w_rep, (long long)(p.H + (p.has_bias2 ? 1 : 0)) * p.N * 4);
         l.tensor(kMom, p.m1, p.w_rep, (long long)(p.K + (p.has_bias1 ? 1 : 0)) * p.H * 4);
@@ -270,7 +295,7 @@ extern "C" {
 // ---- for the test ----
 void check_reset(const unsigned long long* bufs, int n)
 {
-    g_bufs.clear(); g_report.clear(); g_trace.clear(); g_errors = 0; g_sums = {nullptr, 0, 0};
+    g_bufs.clear(); g_report.clear(); g_trace.clear(); g_errors = 0; g_sums = {nullptr, 0, 0}; g_shares = {nullptr, 0};
     for (auto& m : g_used) m.clear();
     for (int i = 0; i < n; ++i) g_bufs.push_back({bufs[2 * i], bufs[2 * i + 1]});
 }

@@ -69,3 +69,47 @@ def test_against_the_oracle(features, hidden, batch, replicas, bf16):
         p.forced_steps()
     p.local_steps(check_updates=True)
     p.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("hidden,replicas,batch", [(128, 36, 32), (128, 36, 64), (192, 24, 32), (192, 64, 8), (256, 66, 32)])
+def test_more_workgroups_than_run_at_once(hidden, replicas, batch, bf16):
+    """288 to 1056 workgroups, so that those of one replica begin at different times; one to three steps, momentum, two calls.  A replica's
+    arithmetic does not depend on the others: every third one has the same data and steps, and the same bits as in a context of three
+    replicas.  That one's first call is the same as test_steps_of_one_call's, with its bound (bf16: test_against_the_oracle)."""
+    rng = np.random.default_rng(hidden + replicas + batch)
+    ops, features, lr, mom = net(hidden, 10), 784, 0.1, 0.9
+    x = rng.standard_normal((3, 2 * batch, 1, 1, features)).astype(np.float32)
+    y = rng.integers(0, 10, (3, 2 * batch)).astype(np.int32)
+    w0 = np.concatenate([v.ravel() for v in (rng.standard_normal((features, hidden)) / np.sqrt(features), 0.1 * rng.standard_normal(hidden),
+                                             rng.standard_normal((hidden, 10)) / np.sqrt(hidden), 0.1 * rng.standard_normal(10))]).astype(np.float32)
+
+    def calls(n):
+        which = np.arange(n) % 3
+        cfg = hadfl.make_config(n, 1, net="custom", custom_ops=ops[:, [0, 1, 2, 4, 5, 6, 7, 8]], batch=batch, n_samples=2 * batch,
+                                in_shape=(1, 1, features), n_classes=10, lr=lr, momentum=mom, bf16=int(bf16))
+        ctx = hadfl.Context(cfg, 1 + which, w0=w0, x=x[which], y=y[which])
+        out = []
+        for _ in range(2):
+            ctx.local_steps()
+            out.append(([ctx.params(k) for k in range(n)], ctx.losses()))
+        ctx.close()
+        return out
+
+    few, many = calls(3), calls(replicas)
+    for (w_few, l_few), (w_many, l_many) in zip(few, many):
+        for k in range(replicas):
+            assert np.array_equal(w_many[k], w_few[k % 3]) and l_many[k] == l_few[k % 3], k
+    if bf16:
+        return
+    for k in range(3):
+        w, buf = w0.astype(np.float64), 0.0
+        for s in range(k + 1):
+            part = slice(s % 2 * batch, (s % 2 + 1) * batch)
+            want, grad, _ = torch_ref.loss_grad(ops, (1, 1, features), w, x[k, part].astype(np.float64).reshape(batch, -1), y[k, part])
+            buf = mom * buf + grad
+            w = w - lr * buf
+        got, losses = few[0]
+        err = np.abs(got[k] - w).max() / np.abs(w - w0).max()
+        print(k, "weights %.1e loss %.1e of %.1e" % (err, abs(losses[k] - want), want), flush=True)
+        assert err <= 1e-5 and abs(losses[k] - want) <= 1e-5 * max(1.0, want)

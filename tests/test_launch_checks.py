@@ -489,3 +489,15 @@ def test_batch_norms_with_a_pool_that_add_their_sums_themselves(checked):
     totals_here = [[any(k in name and "Lb1" in name for name in r["trace"]) for k in ("fwd_pool", "bwd_pool")] for r in runs]
     assert totals_here == [[True, True]] * 2 + [[True, False]] * 2     # (of 16 images of 32 x 32: 64 tiles of the convolution, 128 chunks)
     assert_clean(checked, cases)
+
+
+def test_steps_of_two_dense_layers_exchange_through_two_buffers(checked):
+    """A launch ends a step of some replicas and begins the next: its workgroups read each other's shares of the logits, and write those
+    of the next step where none of them reads.  With replicas whose workgroups do not all run at once, and of one to three steps."""
+    cases = []
+    for hidden, n, batch in ((16, 3, 8), (128, 36, 32), (128, 36, 64), (192, 24, 32), (128, 9, 128)):
+        b = nets._Builder()
+        b.dense(b.relu(b.dense(0, hidden)), 10)
+        cases += [case(b, (1, 1, 128), batch, [1 + k % 3 for k in range(n)], bf16, momentum=mom) for bf16 in (0, 1) for mom in (0.0, 0.9)]
+    assert [layers_in(r["trace"], "dense_pair") for r in checked(cases)] == [4] * len(cases)
+    assert_clean(checked, cases)
