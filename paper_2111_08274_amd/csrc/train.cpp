@@ -663,14 +663,15 @@ struct Runner {
     // order.  The general layers' are gathered, and written by one launch in write_copies.
     WeightCopies copies{};
     double copies_bytes = 0;
+    int copies_layer = -1;                // the first of them
     void write_copies(int n)
     {
         if (copies.count == 0) return;
-        const int keep_na = na;
-        na = n;
+        const int keep_na = na, keep_layer = cur_layer;
+        na = n; cur_layer = copies_layer;
         run("weight_prep", 0, copies_bytes, [&] { return launch_weight_copies(copies, na, s); });
         copies.count = 0; copies_bytes = 0;
-        na = keep_na;
+        na = keep_na; cur_layer = keep_layer;
     }
     void prep_layer(size_t i, int n)
     {
@@ -679,6 +680,7 @@ struct Runner {
         const Layer& l = e.plan.layers[i];
         if (e.general[i]) {
             if (copies.count == kWeightCopies) write_copies(n);
+            if (copies.count == 0) copies_layer = (int)i;
             WeightCopyParams& w = copies.layer[copies.count++];
             w.w = e.buf.replicas + l.w_off; w.w_rep = e.plan.row_stride;
             w.wf = wbf() + e.wf_off[i]; w.wb = e.wb_off[i] >= 0 ? wbf() + e.wb_off[i] : nullptr; w.wcopy_rep = e.wbf_rep;
@@ -804,15 +806,15 @@ struct Runner {
         d.loss = e.buf.loss; d.bf16 = e.cfg.bf16; d.order = e.buf.order;
         const double macs = (double)d.batch * ((double)d.K * d.H + (double)d.H * d.N), wbytes = 4.0 * (d.K + d.N) * d.H;
         cur_layer = 0;
-        for (int s0 = 0; s0 <= e.e_max; ++s0) {
+        for (int s0 = 0; s0 <= e.e_max && e.e_max > 0; ++s0) {
             d.ahead = s0;
             d.share_in = shares[(s0 + 1) & 1]; d.share_out = shares[s0 & 1];
             d.n_end = s0 > 0 ? e.n_active[s0 - 1] : 0; d.n_begin = s0 < e.e_max ? e.n_active[s0] : 0;
-            na = 1;
-            run("dense_step", 2.0 * (macs * d.n_begin + (macs + (double)d.batch * d.H * d.N) * d.n_end),
-                (4.0 * d.batch * d.K + wbytes) * d.n_begin + (4.0 * d.batch * d.K + (d.m1 ? 4.0 : 2.0) * wbytes) * d.n_end, [&] { return launch_dense_pair(d, s); });
+            na = std::max(d.n_end, d.n_begin);
+            const double ends = (double)d.n_end / na, begins = (double)d.n_begin / na;      // (work is given per replica)
+            run("dense_step", 2.0 * (macs * begins + (macs + (double)d.batch * d.H * d.N) * ends),
+                (4.0 * d.batch * d.K + wbytes) * begins + (4.0 * d.batch * d.K + (d.m1 ? 4.0 : 2.0) * wbytes) * ends, [&] { return launch_dense_pair(d, s); });
         }
-        na = 0;
     }
 
     void forward_layer(size_t i)

@@ -36,8 +36,16 @@ def run(case):
     hadfl._check(L.hadfl_init_replicas(ctypes.byref(cfg), ptr[4], ptr[0], ptr[1], ptr[2], ptr[3], hadfl._np_ptr(ratio), None, ctypes.byref(h)))
     for option, value in case.get("options", []):
         hadfl._check(L.hadfl_set_option(h, option, value), h)
+    if "steps" in case:
+        hadfl._check(L.hadfl_set_steps(h, hadfl._np_ptr(np.asarray(case["steps"], dtype=np.int32))), h)
+    if case.get("profile"):
+        hadfl._check(L.hadfl_profile_enable(h, 2))
     status = L.hadfl_local_steps(h)
     out = dict(status=status, report=fake.check_report().decode(), trace=fake.check_trace().decode().split())
+    if case.get("profile"):
+        rows, count = (hadfl.HadflKernelTime * 256)(), ctypes.c_int32()
+        hadfl._check(L.hadfl_profile_read(h, rows, 256, ctypes.byref(count)), h)
+        out["profile"] = {r.name.decode(): [r.launches, r.flops, r.bytes] for r in rows[:count.value]}
     L.hadfl_destroy(h)
     return out
 

@@ -501,3 +501,28 @@ def test_steps_of_two_dense_layers_exchange_through_two_buffers(checked):
         cases += [case(b, (1, 1, 128), batch, [1 + k % 3 for k in range(n)], bf16, momentum=mom) for bf16 in (0, 1) for mom in (0.0, 0.9)]
     assert [layers_in(r["trace"], "dense_pair") for r in checked(cases)] == [4] * len(cases)
     assert_clean(checked, cases)
+
+
+def test_profile_of_launches_for_several_layers_or_steps(checked):
+    """Names carry a layer of the launch (the first whose copies it writes) and the replicas that it works for; work is counted
+    once; a call without steps launches nothing but what counts them."""
+    b = nets._Builder()
+    t = 0
+    for _ in range(4):
+        t = b.relu(b.bn(b.conv(t, 16)))
+    b.dense(b.gap(t), 10)
+    pair = nets._Builder()
+    pair.dense(pair.relu(pair.dense(0, 32)), 10)
+    deep, mlp, none = checked([case(b, (8, 8, 16), 4, [2, 1], 0, profile=1), case(pair, (1, 1, 128), 8, [3, 1, 2], 0, profile=1, momentum=0.0),
+                               case(pair, (1, 1, 128), 8, [3, 1, 2], 0, profile=1, steps=[0, 0, 0])])
+    copies = [name for name in deep["profile"] if name.startswith("weight_prep")]
+    layers = {int(name.split(":")[1][1:]) for name in copies}
+    assert layers and layers <= {3, 6, 9} and {name.split(":")[2] for name in copies} == {"n2", "n1"}, copies
+    assert sum(deep["profile"][name][0] for name in copies) == layers_in(deep["trace"], "weight_copy")
+    assert sum(deep["profile"][name][2] for name in copies) == 3 * (2 + 1) * 16.0 * 9 * 16 * 16
+    steps = {name: v for name, v in mlp["profile"].items() if name.startswith("dense_step")}
+    assert {name: v[0] for name, v in steps.items()} == {"dense_step:L0:n3": 2, "dense_step:L0:n2": 1, "dense_step:L0:n1": 1}
+    macs, out = 8 * (128 * 32 + 32 * 10), 8 * 32 * 10
+    assert abs(sum(v[1] for v in steps.values()) - 6 * 2.0 * (2 * macs + out)) < 1.0
+    assert [v[2] for name, v in mlp["profile"].items() if name.startswith("advance")] == [24.0 * 3]
+    assert all(name.startswith("advance") for name in none["profile"]) and len(none["profile"]) == 1, none["profile"]
