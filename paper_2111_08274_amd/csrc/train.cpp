@@ -207,24 +207,31 @@ bool dense_rows_pays(const hadfl_config& cfg, const NetPlan& plan, const Layer& 
     return l.in0 != 0 || tiles <= (cfg.bf16 && plan.tensors[0].numel() < 512 ? 256 : 384);
 }
 
-// The network is a dense layer on the data set with a ReLU and a classifier behind it, of a size for dense_pair_kernel.  Four
-// steps a call, us a step layer by layer and there, batch 8 / 32 / 64 / 128:
-//   784 features, 128 hidden units:   4 replicas 27 30 33 44 and 16 17 24 39,   16: 30 34 60 71 and 16 18 24 40,   64: 45 72 88 113 and 37 42 56 86
-//   1024 features, 256 hidden units:  4: 29 34 39 70 and 19 22 32 52,   32: 51 79 94 121 and 47 54 74 120,   64: 104 115 138 202 and 90 104 146 265
-// The last has four workgroups a compute unit: beyond two the batches above 32 stay with the single layers.  A call of one step has
-// no beginning to share a launch with: one replica, batch 128 43 and 45, 64 33 and 31, hence eight replicas above 64.  More than 256 hidden
-// units stay with the single layers too (512, 128 features, 16 replicas 27 30 40 77 and 23 25 37 62; others not measured).  Rows of fewer
-// than 128 features leave waves without a block; they stay with the single layers' kernels, though this one would be the faster for them
-// too (32 features, 64 hidden units, 4 replicas: 21 22 28 38 and 9 10 13 20), so that networks of a few features still run those.
-bool dense_pair_net(const hadfl_config& cfg, const NetPlan& plan)
+// The network is a dense layer on the data set with a ReLU and a classifier behind it, of a size for dense_pair_kernel in a call of this many
+// steps.  Four steps a call, us a step layer by layer and there, batch 8 / 32 / 64 / 128:
+//   784 features, 128 hidden units:   1 replica 25 28 32 41 and 17 19 26 41,   4: 27 30 33 44 and 16 17 24 39,   16: 30 34 39 50 and 16 18 24 40,
+//                                     64: 45 50 66 91 and 37 42 57 86,   128: 72 80 106 157 and 71 80 110 192
+//   1024 features, 256 hidden units:  4: 30 34 39 49 and 19 22 32 52,   16: 44 48 55 74 and 23 27 38 61,   32: 51 58 73 100 and 47 54 74 120,
+//                                     64: 83 94 118 182 and 89 104 146 267
+//   128 features, 256 hidden units:   32: 26 29 38 53 and 20 22 31 51,   64: 32 35 46 67 and 36 41 75 133
+// A compute unit holds one workgroup of sixteen hidden units: up to 256 this is the shorter way, but for batches above 64 on few replicas
+// in calls of one step, which have no beginning to share a launch with (one replica, batch 128 43 and 45).  Beyond 256 the second round of
+// workgroups costs as much as the first, and the line is at 6.5 million multiply-adds of a replica's hidden layer (layer by layer over
+// this: below it, two steps a call and more, 0.91 to 1.46, half of them above 1.2; above it 0.73 to 1.15) and at small weights for calls of one step (1024 x 256, 32
+// replicas 53 59 74 101 and 55 63 85 131).  From 512 on the layers' own kernels fill the chip: 1024 workgroups 0.50 to 1.06, 2048 0.39 to 0.93.
+// More than 256 hidden units stay with them too (512, 128 features, 16 replicas 27 30 40 56 and 23 25 37 62; others not measured).  Rows of
+// fewer than 128 features leave waves without a block; they stay with the single layers' kernels, though this one would be the faster for
+// them too (32 features, 64 hidden units, 4 replicas: 20 22 28 38 and 9 10 13 20), so that networks of a few features still run those.
+bool dense_pair_net(const hadfl_config& cfg, const NetPlan& plan, int steps)
 {
     if (plan.layers.size() != 3) return false;
     const Layer &a = plan.layers[0], &r = plan.layers[1], &b = plan.layers[2];
     if (a.type != HADFL_OP_DENSE || a.in0 != 0 || r.type != HADFL_OP_RELU || r.in0 != a.out || b.type != HADFL_OP_DENSE || b.in0 != r.out) return false;
     if (b.cout != cfg.n_classes || (a.bias && a.b_off != a.w_off + a.w_count) || (b.bias && b.b_off != b.w_off + b.w_count)) return false;
-    const int64_t K = plan.tensors[0].numel();
-    if (K < 128 || a.cout > 256 || (cfg.batch > 64 && cfg.n_replicas < 8) || (cfg.batch > 32 && a.cout / 16 * cfg.n_replicas > 512)) return false;
-    return K <= 1024 && dense_pair_supported(cfg.batch, (int)K, a.cout, b.cout);
+    const int64_t K = plan.tensors[0].numel(), groups = (int64_t)(a.cout / 16) * cfg.n_replicas;
+    if (K < 128 || K > 1024 || a.cout > 256 || (cfg.batch > 64 && cfg.n_replicas < 8)) return false;
+    if (groups > 256 && (groups > 512 || cfg.batch * a.w_count > 6500000 || (steps == 1 && a.w_count > 131072))) return false;
+    return dense_pair_supported(cfg.batch, (int)K, a.cout, b.cout);
 }
 
 // Directions of a general layer that run there.  A convolution on the data set is gathered value by value, which pays where the
@@ -1232,7 +1239,7 @@ hadfl_status train_run(TrainEngine* e, hipStream_t s, Profiler* prof, std::strin
     }
     const int T = (int)e->plan.tensors.size();
     e->prepped.assign(e->plan.layers.size(), 0);       // the weights may have changed since the last call (aggregation)
-    if (dense_pair_net(e->cfg, e->plan)) r.dense_pair_steps();
+    if (dense_pair_net(e->cfg, e->plan, e->e_max)) r.dense_pair_steps();
     else for (int step = 0; step < e->e_max && r.rc == hipSuccess; ++step) {
         r.na = e->n_active[step]; r.step = step;
         r.prepare_weights();

@@ -15,8 +15,8 @@
 // before, so a step fetches one column of three (six operands of 32 channels) and the position's dy (two): one for each of the
 // eight waves.  Two steps make a pair with one barrier: within it the waves of a SIMD drift apart, so that one's splits and
 // LDS traffic lie beside the other's matrix instructions (a barrier after each step, 16 / 4 replicas: 14.94 / 2.67 ms of these launches
-// in ResNet-18 / VGG-16; a pair 14.24 / 2.60).  Columns are numbered along the walk, and x and dy have a ring of six places each, which
-// fills the 160 KB together: the pair of t and t + 1 reads the columns t - 1 to t + 2 and, ahead, dy of t + 2 (in front of
+// in ResNet-18 / VGG-16; a pair 14.24 / 2.60).  Columns are numbered along the walk, and x and dy have a ring of six places each, 144 of
+// the 160 KiB together (a seventh place, 24 KiB, does not fit): the pair of t and t + 1 reads the columns t - 1 to t + 2 and, ahead, dy of t + 2 (in front of
 // the first pair that of t too) while those of t + 3 and t + 4 are written.  Operands are fetched two steps before they are written, beside
 // the matrix instructions.
 // Waves 0 to 3 multiply the corner taps and the middle one, waves 4 to 7 the four others, each for a block of 32 x 32 channels: on a

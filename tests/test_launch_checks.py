@@ -526,3 +526,19 @@ def test_profile_of_launches_for_several_layers_or_steps(checked):
     assert abs(sum(v[1] for v in steps.values()) - 6 * 2.0 * (2 * macs + out)) < 1.0
     assert [v[2] for name, v in mlp["profile"].items() if name.startswith("advance")] == [24.0 * 3]
     assert all(name.startswith("advance") for name in none["profile"]) and len(none["profile"]) == 1, none["profile"]
+
+
+def test_two_dense_layers_in_one_launch_by_launch_size(checked):
+    """Up to a workgroup a compute unit; up to two where a workgroup's batches and weights are small, of wide layers in calls of several
+    steps; beyond that the layers' own kernels."""
+    cases, want = [], []
+    for features, hidden, n, batch, steps, pair in ((128, 256, 16, 64, 1, 1), (128, 256, 32, 8, 1, 1), (128, 256, 33, 8, 4, 0), (256, 256, 64, 16, 4, 0),
+                                                    (784, 128, 32, 128, 1, 1), (784, 128, 33, 64, 2, 1), (784, 128, 33, 65, 2, 0),
+                                                    (1024, 256, 32, 8, 2, 1), (1024, 256, 32, 8, 1, 0), (1024, 256, 16, 8, 1, 1),
+                                                    (784, 128, 7, 64, 2, 1), (784, 128, 7, 65, 2, 0)):
+        b = nets._Builder()
+        b.dense(b.relu(b.dense(0, hidden)), 10)
+        cases.append(case(b, (1, 1, features), batch, [1] * n, 0, steps=[steps] * n))
+        want.append(pair * (steps + 1))
+    assert [layers_in(r["trace"], "dense_pair") for r in checked(cases)] == want
+    assert_clean(checked, cases)
